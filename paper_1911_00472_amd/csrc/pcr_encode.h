@@ -606,12 +606,13 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
     if (counts_out) memset(counts_out, 0, sizeof(uint32_t) * kHistPerImage);
     if (src_bytes >= (1ull << 32)) return kEUnsupported;
     if (restart_interval > 65535) return kERange;
-    ParseState st;
-    for (int a = 0; a < 2; a++) for (int b = 0; b < 4; b++) st.dht[a][b] = 0;
-    st.ri = 0; st.have_frame = 0;
     ImgDesc img; memset(&img, 0, sizeof img);
     ScanDesc first; memset(&first, 0, sizeof first);
-    int rc = parse_region(src, 0, (uint32_t)src_bytes, 1, &st, &img, &first, 0);      // up to the first scan header
+    RegionWalk w;
+    int rc = walk_region(src, 0, (uint32_t)src_bytes, 0, &w, &img);                   // up to the first scan header
+    if (rc == kOk) rc = resolve_scan(src, w, (uint32_t)src_bytes, w.dht, w.ri >= 0 ? (uint32_t)w.ri : 0u, &img, &first);
+    if (rc == kOk) rc = scan_history(&first, 0);
+    for (int t = 0; t < 4; t++) { img.qoff[t] = w.qoff[t]; img.qprec[t] = w.qprec[t]; }
     if (rc != kOk) return rc;
     Frame F;
     F.W = img.W; F.H = img.H; F.nc = img.nc; F.hmax = img.hmax; F.vmax = img.vmax; F.mcux = img.mcux; F.mcuy = img.mcuy;

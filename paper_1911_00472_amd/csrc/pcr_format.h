@@ -76,14 +76,19 @@ PCR_HD int parse_record_header(const uint8_t* bytes, uint64_t nbytes, RecordHead
 // ---------------------------------------------------------------------------------------
 // Marker parsing of one image: walks the headers of regions 0..kmax-1 (never the
 // entropy-coded data) and fills the image and scan descriptors.
-//   rec      record bytes (host or device pointer, matching where this runs)
+//   rec      record bytes: a pointer, or on the device anything indexed by record offset (HeaderBytes)
 //   off,len  index tables [G][n] (absolute offsets / lengths of the regions)
 // Every read is bounds-checked against the region it belongs to.
+// The walk over a region's segments (walk_region) needs nothing from other regions; what a scan takes over from
+// earlier ones -- tables in force, restart interval, the scans it refines -- is put together afterwards
+// (resolve_scan, scan_history).  The host goes through an image's regions one by one (parse_image), the device
+// walks all of them at once, one lane each (k_headers).
 // ---------------------------------------------------------------------------------------
-struct ParseState {
-    uint32_t dht[2][4];                    // offset of BITS of the table last defined for (class, id)
-    uint16_t ri;
-    int have_frame;
+struct RegionWalk {
+    uint32_t dht[8];                       // offset of BITS of the table this region last defines for class * 4 + id (0: none)
+    uint32_t qoff[4]; uint8_t qprec[4];    // the same for quantisation tables
+    uint32_t sos, sos_end;                 // payload of the scan header; entropy-coded data starts at sos_end
+    int32_t ri;                            // restart interval defined here, -1: none
 };
 
 PCR_HD void setup_geometry(ImgDesc* d) {
@@ -98,10 +103,15 @@ PCR_HD void setup_geometry(ImgDesc* d) {
     }
 }
 
-PCR_HD int parse_region(const uint8_t* rec, uint32_t p, uint32_t end, int first_region, ParseState* st, ImgDesc* img,
-                        ScanDesc* scans, uint32_t g) {
-    ScanDesc* sd = &scans[g];
-    if (first_region) {
+// The segments of region g up to its scan header.  The frame header goes into *img (region 0 must hold it, later
+// regions must not).
+template <class Bytes>
+PCR_HD int walk_region(const Bytes& rec, uint32_t p, uint32_t end, uint32_t g, RegionWalk* w, ImgDesc* img) {
+    for (int t = 0; t < 8; t++) w->dht[t] = 0;
+    for (int t = 0; t < 4; t++) { w->qoff[t] = 0; w->qprec[t] = 0; }
+    w->ri = -1; w->sos = w->sos_end = 0;
+    bool have_frame = g > 0;
+    if (g == 0) {
         if (end - p < 2 || rec[p] != 0xFF || rec[p + 1] != 0xD8) return kEFormat;
         p += 2;
     }
@@ -110,7 +120,7 @@ PCR_HD int parse_region(const uint8_t* rec, uint32_t p, uint32_t end, int first_
         if (rec[p] != 0xFF) return kEFormat;
         uint32_t m = rec[p + 1];
         if (m == 0xFF) { p++; continue; }
-        uint32_t L = ld_be16(rec + p + 2);
+        uint32_t L = ((uint32_t)rec[p + 2] << 8) | rec[p + 3];
         if (L < 2 || L + 2 > end - p) return kEFormat;
         uint32_t s = p + 4, se = p + 2 + L;
         p = se;
@@ -118,14 +128,15 @@ PCR_HD int parse_region(const uint8_t* rec, uint32_t p, uint32_t end, int first_
             while (s < se) {
                 uint32_t pq = rec[s] >> 4, tq = rec[s] & 15; s++;
                 if (tq > 3 || pq > 1 || se - s < 64 * (pq + 1)) return kEFormat;
-                img->qoff[tq] = s; img->qprec[tq] = (uint8_t)pq;
+                // (selects over the four slots: an index would put the array into scratch memory on the device)
+                for (uint32_t t = 0; t < 4; t++) if (t == tq) { w->qoff[t] = s; w->qprec[t] = (uint8_t)pq; }
                 s += 64 * (pq + 1);
             }
         } else if (m == 0xC0 || m == 0xC1 || m == 0xC2) {
-            if (st->have_frame || se - s < 6) return kEFormat;
+            if (have_frame || se - s < 6) return kEFormat;
             if (rec[s] != 8) return kEUnsupported;
             img->progressive = (m == 0xC2);
-            img->H = (uint16_t)ld_be16(rec + s + 1); img->W = (uint16_t)ld_be16(rec + s + 3); img->nc = rec[s + 5];
+            img->H = (uint16_t)(((uint32_t)rec[s + 1] << 8) | rec[s + 2]); img->W = (uint16_t)(((uint32_t)rec[s + 3] << 8) | rec[s + 4]); img->nc = rec[s + 5];
             if (img->H == 0 || img->W == 0) return kEUnsupported;
             if (img->nc != 1 && img->nc != 3) return kEUnsupported;
             if (se - s < 6u + 3u * img->nc) return kEFormat;
@@ -135,7 +146,7 @@ PCR_HD int parse_region(const uint8_t* rec, uint32_t p, uint32_t end, int first_
             }
             if (img->nc == 1) { img->hs[0] = 1; img->vs[0] = 1; }
             setup_geometry(img);
-            st->have_frame = 1;
+            have_frame = true;
         } else if ((m >= 0xC3 && m <= 0xCF && m != 0xC4 && m != 0xC8 && m != 0xCC) || m == 0xDC) {
             return kEUnsupported;                  // lossless, hierarchical, arithmetic coding, DNL
         } else if (m == 0xC4) {
@@ -144,81 +155,110 @@ PCR_HD int parse_region(const uint8_t* rec, uint32_t p, uint32_t end, int first_
                 if (tc > 1 || th > 3 || se - s < 17) return kEFormat;
                 uint32_t nv = 0; for (int i = 0; i < 16; i++) nv += rec[s + 1 + i];
                 if (nv > 256 || se - s < 17 + nv) return kEFormat;
-                st->dht[tc][th] = s + 1;
+                for (uint32_t t = 0; t < 8; t++) if (t == tc * 4 + th) w->dht[t] = s + 1;
                 s += 17 + nv;
             }
         } else if (m == 0xDD) {
             if (se - s < 2) return kEFormat;
-            st->ri = (uint16_t)ld_be16(rec + s);
+            w->ri = (int32_t)(((uint32_t)rec[s] << 8) | rec[s + 1]);
         } else if (m == 0xDA) {
-            if (!st->have_frame || se - s < 1) return kEFormat;
-            uint32_t ns = rec[s];
-            if (ns < 1 || ns > img->nc || se - s < 1 + 2 * ns + 3) return kEFormat;
-            sd->ns = (uint8_t)ns;
-            uint32_t td[kMaxComp], ta[kMaxComp];
-            for (uint32_t j = 0; j < ns; j++) {
-                int c = -1;
-                for (int q = 0; q < img->nc; q++) if (img->cid[q] == rec[s + 1 + 2 * j]) c = q;
-                if (c < 0) return kEFormat;
-                sd->comp[j] = (uint8_t)c; td[j] = rec[s + 2 + 2 * j] >> 4; ta[j] = rec[s + 2 + 2 * j] & 15;
-                if (td[j] > 3 || ta[j] > 3) return kEFormat;
-            }
-            sd->Ss = rec[s + 1 + 2 * ns]; sd->Se = rec[s + 2 + 2 * ns]; sd->Ah = rec[s + 3 + 2 * ns] >> 4; sd->Al = rec[s + 3 + 2 * ns] & 15;
-            for (int j = 0; j < kMaxComp; j++) sd->ac_offc[j] = 0;
-            if (!img->progressive) {
-                // Sequential (baseline) file, the format a record of non-progressive images holds (one scan group, or
-                // one per component): the scan header must say "all 64 coefficients, full precision".
-                if (sd->Ss != 0 || sd->Se != 63 || sd->Ah != 0 || sd->Al != 0) return kEFormat;
-                for (uint32_t j = 0; j < ns; j++) {
-                    if (!st->dht[0][td[j]] || !st->dht[1][ta[j]]) return kEFormat;
-                    sd->dc_off[j] = st->dht[0][td[j]]; sd->ac_offc[j] = st->dht[1][ta[j]];
-                }
-                sd->ac_off = sd->ac_offc[0];
-            } else {
-                if (sd->Ss > sd->Se || sd->Se > 63 || (sd->Ss == 0 && sd->Se != 0) || (sd->Ss > 0 && ns != 1) || sd->Al > 13) return kEFormat;
-                if (sd->Ah != 0 && sd->Ah != sd->Al + 1) return kEFormat;
-                for (uint32_t j = 0; j < ns; j++) {
-                    sd->dc_off[j] = 0;
-                    if (sd->Ss == 0 && sd->Ah == 0) { if (!st->dht[0][td[j]]) return kEFormat; sd->dc_off[j] = st->dht[0][td[j]]; }
-                }
-                sd->ac_off = 0;
-                if (sd->Ss > 0) { if (!st->dht[1][ta[0]]) return kEFormat; sd->ac_off = st->dht[1][ta[0]]; }
-            }
-            sd->ri = st->ri;
-            if (ns > 1) { sd->mcu_w = img->mcux; sd->mcus = (uint32_t)img->mcux * img->mcuy; }
-            else { sd->mcu_w = img->cw[sd->comp[0]]; sd->mcus = (uint32_t)img->cw[sd->comp[0]] * img->ch[sd->comp[0]]; }
-            sd->data_off = p; sd->data_len = end - p;
-            // A refinement scan works on the positions of its band that are already non-zero.  Those made
-            // non-zero by AC first scans are read back from the coefficients; those added by earlier
-            // refinement scans of the component (not applied to the coefficients yet) come from the masks
-            // those scans leave, so they are listed here.
-            sd->nhist = 0;
-            if (sd->Ss > 0) {
-                bool has_first = false;
-                for (uint32_t q = 0; q < g; q++) {
-                    const ScanDesc* e = &scans[q];
-                    if (e->Ss > 0 && e->comp[0] == sd->comp[0] && e->Ss <= sd->Se && sd->Ss <= e->Se) {
-                        if (e->Ah == 0) { has_first = true; continue; }
-                        if (sd->nhist >= kMaxHist) return kEUnsupported;
-                        sd->hist[sd->nhist++] = (uint8_t)q;
-                    }
-                }
-                if (sd->Ah > 0 && !has_first) return kEFormat;
-                if (sd->Ah == 0) sd->nhist = 0;            // first scans need no history
-            }
-            sd->valid = 1;
+            if (!have_frame || se - s < 1) return kEFormat;
+            w->sos = s; w->sos_end = se;
             return kOk;
         }
         // APPn, COM, anything else with a length: skipped
     }
 }
 
+// The descriptor of a scan from its header: dht, ri: the tables and the restart interval in force; end: of its region.
+template <class Bytes>
+PCR_HD int resolve_scan(const Bytes& rec, const RegionWalk& w, uint32_t end, const uint32_t dht[8], uint32_t ri, const ImgDesc* img, ScanDesc* sd) {
+    const uint32_t s = w.sos, se = w.sos_end, ns = rec[s];
+    if (ns < 1 || ns > img->nc || se - s < 1 + 2 * ns + 3) return kEFormat;
+    sd->ns = (uint8_t)ns;
+    uint32_t dc_def[kMaxComp] = {0, 0, 0}, ac_def[kMaxComp] = {0, 0, 0};           // the tables the components name
+    for (uint32_t j = 0; j < (uint32_t)kMaxComp; j++) {
+        if (j >= ns) continue;
+        int c = -1;
+        for (int q = 0; q < kMaxComp; q++) if (q < img->nc && img->cid[q] == rec[s + 1 + 2 * j]) c = q;
+        if (c < 0) return kEFormat;
+        const uint32_t td = rec[s + 2 + 2 * j] >> 4, ta = rec[s + 2 + 2 * j] & 15;
+        sd->comp[j] = (uint8_t)c;
+        if (td > 3 || ta > 3) return kEFormat;
+        for (uint32_t t = 0; t < 4; t++) { dc_def[j] = t == td ? dht[t] : dc_def[j]; ac_def[j] = t == ta ? dht[4 + t] : ac_def[j]; }
+    }
+    sd->Ss = rec[s + 1 + 2 * ns]; sd->Se = rec[s + 2 + 2 * ns]; sd->Ah = rec[s + 3 + 2 * ns] >> 4; sd->Al = rec[s + 3 + 2 * ns] & 15;
+    for (int j = 0; j < kMaxComp; j++) sd->ac_offc[j] = 0;
+    if (!img->progressive) {
+        // Sequential (baseline) file, the format a record of non-progressive images holds (one scan group, or
+        // one per component): the scan header must say "all 64 coefficients, full precision".
+        if (sd->Ss != 0 || sd->Se != 63 || sd->Ah != 0 || sd->Al != 0) return kEFormat;
+        for (uint32_t j = 0; j < (uint32_t)kMaxComp; j++) {
+            if (j >= ns) continue;
+            if (!dc_def[j] || !ac_def[j]) return kEFormat;
+            sd->dc_off[j] = dc_def[j]; sd->ac_offc[j] = ac_def[j];
+        }
+        sd->ac_off = ac_def[0];
+    } else {
+        if (sd->Ss > sd->Se || sd->Se > 63 || (sd->Ss == 0 && sd->Se != 0) || (sd->Ss > 0 && ns != 1) || sd->Al > 13) return kEFormat;
+        if (sd->Ah != 0 && sd->Ah != sd->Al + 1) return kEFormat;
+        for (uint32_t j = 0; j < (uint32_t)kMaxComp; j++) {
+            if (j >= ns) continue;
+            sd->dc_off[j] = 0;
+            if (sd->Ss == 0 && sd->Ah == 0) { if (!dc_def[j]) return kEFormat; sd->dc_off[j] = dc_def[j]; }
+        }
+        sd->ac_off = 0;
+        if (sd->Ss > 0) { if (!ac_def[0]) return kEFormat; sd->ac_off = ac_def[0]; }
+    }
+    sd->ri = (uint16_t)ri;
+    if (ns > 1) { sd->mcu_w = img->mcux; sd->mcus = (uint32_t)img->mcux * img->mcuy; }
+    else { sd->mcu_w = img->cw[sd->comp[0]]; sd->mcus = (uint32_t)img->cw[sd->comp[0]] * img->ch[sd->comp[0]]; }
+    sd->data_off = se; sd->data_len = end - se;
+    return kOk;
+}
+
+// A refinement scan works on the positions of its band that are already non-zero.  Those made non-zero by AC first
+// scans are read back from the coefficients; those added by earlier refinement scans of the component (not applied to
+// the coefficients yet) come from the masks those scans leave, so they are listed here.
+PCR_HD int scan_history(ScanDesc* scans, uint32_t g) {
+    ScanDesc* sd = &scans[g];
+    sd->nhist = 0;
+    if (sd->Ss > 0 && sd->Ah > 0) {                // (first scans need no history)
+        bool has_first = false;
+        for (uint32_t q = 0; q < g; q++) {
+            const ScanDesc* e = &scans[q];
+            if (e->Ss > 0 && e->comp[0] == sd->comp[0] && e->Ss <= sd->Se && sd->Ss <= e->Se) {
+                if (e->Ah == 0) { has_first = true; continue; }
+                if (sd->nhist >= kMaxHist) return kEUnsupported;
+                sd->hist[sd->nhist++] = (uint8_t)q;
+            }
+        }
+        if (!has_first) return kEFormat;
+    }
+    sd->valid = 1;
+    return kOk;
+}
+
+// What is left once all regions are parsed (img->nscans of them): the status of an image whose scans are all valid.
+PCR_HD int check_image(const ImgDesc* img, const ScanDesc* scans) {
+    if (img->nscans == 0) return kEFormat;
+    // the refinement scans of a component are replayed from a list of fixed length when its coefficients are loaded
+    for (int c = 0; c < img->nc; c++) {
+        int nref = 0;
+        for (uint32_t g = 0; g < img->nscans; g++) {
+            if (scans[g].Ah == 0) continue;
+            for (int j = 0; j < scans[g].ns; j++) if (scans[g].comp[j] == c) nref++;
+        }
+        if (nref > kApplyMaxScans) return kEUnsupported;
+    }
+    for (int c = 0; c < img->nc; c++) if (!img->qoff[img->tq[c]]) return kEFormat;
+    return kOk;
+}
+
 // Parse image i: regions 0..kmax-1.  scans points at this image's G descriptors.
 PCR_HD void parse_image(const uint8_t* rec, const uint32_t* off, const uint32_t* len, uint32_t n, uint32_t i,
                         uint32_t nscans_i, uint32_t kmax, ImgDesc* img, ScanDesc* scans) {
-    ParseState st;
-    for (int a = 0; a < 2; a++) for (int b = 0; b < 4; b++) st.dht[a][b] = 0;
-    st.ri = 0; st.have_frame = 0;
+    uint32_t dht[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ri = 0;
     for (int t = 0; t < 4; t++) { img->qoff[t] = 0; img->qprec[t] = 0; }
     img->status = kOk; img->nscans = 0; img->nc = 0; img->W = 0; img->H = 0;
     for (int c = 0; c < kMaxComp; c++) img->zmax[c] = 0;
@@ -227,7 +267,15 @@ PCR_HD void parse_image(const uint8_t* rec, const uint32_t* off, const uint32_t*
     for (uint32_t g = 0; g < upto; g++) {
         scans[g].valid = 0;
         uint32_t p = off[(size_t)g * n + i], L = len[(size_t)g * n + i];
-        int rc = parse_region(rec, p, p + L, g == 0, &st, img, scans, g);
+        RegionWalk w;
+        int rc = walk_region(rec, p, p + L, g, &w, img);
+        if (rc == kOk) {
+            for (int t = 0; t < 8; t++) if (w.dht[t]) dht[t] = w.dht[t];
+            for (int t = 0; t < 4; t++) if (w.qoff[t]) { img->qoff[t] = w.qoff[t]; img->qprec[t] = w.qprec[t]; }
+            if (w.ri >= 0) ri = (uint32_t)w.ri;
+            rc = resolve_scan(rec, w, p + L, dht, ri, img, &scans[g]);
+        }
+        if (rc == kOk) rc = scan_history(scans, g);
         if (rc != kOk) { img->status = rc; return; }
         img->nscans = g + 1;
         for (int j = 0; j < scans[g].ns; j++) {
@@ -235,17 +283,7 @@ PCR_HD void parse_image(const uint8_t* rec, const uint32_t* off, const uint32_t*
             if (scans[g].Se + 1 > img->zmax[c]) img->zmax[c] = (uint8_t)(scans[g].Se + 1);
         }
     }
-    if (img->nscans == 0) { img->status = kEFormat; return; }
-    // the refinement scans of a component are replayed from a list of fixed length when its coefficients are loaded
-    for (int c = 0; c < img->nc; c++) {
-        int nref = 0;
-        for (uint32_t g = 0; g < img->nscans; g++) {
-            if (scans[g].Ah == 0) continue;
-            for (int j = 0; j < scans[g].ns; j++) if (scans[g].comp[j] == c) nref++;
-        }
-        if (nref > kApplyMaxScans) { img->status = kEUnsupported; return; }
-    }
-    for (int c = 0; c < img->nc; c++) if (!img->qoff[img->tq[c]]) { img->status = kEFormat; return; }
+    img->status = check_image(img, scans);
 }
 
 }  // namespace pcr

@@ -1,6 +1,6 @@
 // gfx950 kernels of the PCR decode path.  One kernel per step:
 //   k_index      scan-group index (prefix sums of region lengths)
-//   k_parse      JPEG marker parsing, one lane per image
+//   k_headers    JPEG marker parsing and Huffman tables, one workgroup per image
 //   k_unstuff    byte un-stuffing + restart-interval location, one workgroup per (image, scan)
 //   k_dc_first, k_ac_first, k_ac_refine   progressive Huffman decode, one wavefront per unit: a restart
 //                interval of a scan, or the stretch between two entry points of the record (the whole scan
@@ -42,6 +42,12 @@ PCR_D uint32_t xcd_major(uint32_t b, uint32_t n) {
     const uint32_t q = n / kXcds, r = n - q * kXcds, x = b % kXcds, i = b / kXcds;
     return x * q + (x < r ? x : r) + i;
 }
+// What lanes of a wavefront have written to LDS is there for its other lanes from here on.
+PCR_D void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 PCR_D void dc_kernel_priority() { __builtin_amdgcn_s_setprio(2); }
 
 struct DevRecord {
@@ -65,13 +71,11 @@ struct DevRecord {
                                // coefficient export
     uint64_t* masks;
     int32_t* status;           // [n]
-    AcTab* tabs;               // Huffman tables of the AC scans: those of the refinement scans are written by phase 1 for phase 2;
-                               // with tabs_prebuilt, k_build_tables has written all of them before the entropy kernels start
+    AcTab* tabs;               // Huffman tables of the AC scans, written by k_headers
     const uint32_t* tab_idx;   // [n][G] index into tabs
-    DcTab* dctabs;             // with tabs_prebuilt: the DC tables of the DC first scans, three slots per scan (one per scan component)
+    DcTab* dctabs;             // the DC tables of the DC first scans, three slots per scan (one per scan component)
     const uint32_t* dctab_idx; // [n][G] first slot of the scan in dctabs
     const uint32_t* ent_off;   // [n][G] record offset of the scan's entry points (0: none; then slot_cnt - 1 of them)
-    uint32_t tabs_prebuilt;    // set per call by the host (records whose scans have restart intervals)
 };
 
 // segment of a scan in the clean buffer: 4-byte aligned base (big-endian words)
@@ -109,15 +113,218 @@ __global__ void __launch_bounds__(256) k_index(DevRecord R, uint32_t kmax) {
 }
 
 // --------------------------------------------------------------------------------------
-// k_parse: one lane per image walks the marker segments of its regions 1..kmax.
+// k_headers: the marker segments of one image per workgroup, and the Huffman tables of its scans.
+//   1. where the regions of scan groups 0 .. kmax-1 lie: the offsets k_index left, or (own_index, small records, one
+//      launch fewer) the sum of the lengths ahead of the image's, taken here;
+//   2. the first bytes of every region into LDS, all of them at once -- a walk over marker segments is a chain of byte
+//      reads that depend on one another, and from memory each of them is a trip of a microsecond;
+//   3. one LANE PER REGION walks its segments (walk_region) and reads its scan header; the tables and the restart
+//      interval a scan takes over from earlier regions are found with ballots over the lanes;
+//   4. one wavefront per scan builds the scan's tables from its definition, every lane its share of the entries.
+// One lane per image for all of this, with the tables in a kernel of their own, took 125 + 81 us for 1024 images of
+// 10 scans; see the design notes for what this takes.
+// keep_status: a fidelity upgrade builds on planes decoded earlier; an image those calls found damaged stays so.
+// tables from scan k0 on are built (none: k0 = kmax); dc_too = 0: the DC first scans of this call are all decoded by
+// k_dc_first_lanes, which builds its own tables.
 // --------------------------------------------------------------------------------------
-// keep_status: a fidelity upgrade builds on planes decoded earlier; an image those calls found damaged stays so
-__global__ void __launch_bounds__(64) k_parse(DevRecord R, uint32_t kmax, uint32_t keep_status) {
+constexpr int kHeaderWaves = 4, kHeaderLanes = 64 * kHeaderWaves;
+constexpr uint32_t kMaxGroups = 64;                        // (parse_record_header refuses more)
+constexpr uint32_t kHeaderStage = 16384;                   // bytes of LDS for the heads of the regions, shared out evenly
+constexpr uint32_t kHeaderWindow = 1024;                   // ... but at most this much per region (a first region with its tables is 600-700 bytes)
+constexpr uint32_t kOwnIndexImages = 512;                  // own_index up to this many images (a workgroup sums n lengths per scan group)
+
+// Record bytes by record offset: from the staged window, or (past it: long comments and profiles) from memory.
+// (The address spaces are spelled out: through two generic pointers every read became a flat one.)
+typedef const __attribute__((address_space(3))) uint8_t* LdsBytes;
+typedef const __attribute__((address_space(1))) uint8_t* GlobalBytes;
+struct HeaderBytes {
+    GlobalBytes rec; LdsBytes lds; uint32_t base, count;
+    PCR_D uint8_t operator[](uint32_t p) const { const uint32_t o = p - base; return o < count ? lds[o] : rec[p]; }
+};
+
+// A canonical code's lengths, for building look-ups entry by entry: lim[L] = first left-aligned 16-bit value that is not
+// a code of length <= L (so codes of length L occupy lim[L-1] .. lim[L]), first[L] = index of the first code of length L.
+struct CanonCode { uint32_t lim[17]; uint32_t first[17]; uint8_t vals[256]; };
+
+// From a DHT payload (16 counts, then the symbols in code order); call with a whole wavefront.
+PCR_D void canon_build(CanonCode* c, const HeaderBytes& def, uint32_t at, uint32_t lane) {
+    const uint32_t mine = lane < 16 ? def[at + lane] : 0u;
+    uint32_t code = 0, k = 0;
+    if (lane == 0) c->lim[0] = 0;
+    for (uint32_t L = 1; L <= 16; L++) {
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(L - 1));
+        if (lane == 0) c->first[L] = k;
+        code += cnt; k += cnt;
+        const uint64_t lim = (uint64_t)code << (16 - L);
+        if (lane == 0) c->lim[L] = lim > 65536 ? 65536u : (uint32_t)lim;
+        code <<= 1;
+    }
+    for (uint32_t i = lane; i < 256; i += 64) c->vals[i] = i < k ? def[at + 16 + i] : (uint8_t)0;
+}
+// (length << 8) | index of the code at the head of the left-aligned 16-bit value c16; 0 if none of the lengths lo .. hi
+PCR_D uint32_t canon_find(const CanonCode* c, uint32_t c16, uint32_t lo, uint32_t hi) {
+    uint32_t L = lo;
+    while (L <= hi && c16 >= c->lim[L]) L++;
+    if (L > hi || c16 < c->lim[L - 1]) return 0;
+    const uint32_t idx = c->first[L] + ((c16 - c->lim[L - 1]) >> (16 - L));
+    return idx < 256u ? (L << 8) | idx : 0u;
+}
+// What actab_build and actab_pack make of the definition, entry by entry (same contents).
+PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t lane) {
+    const uint32_t lim8 = c->lim[8], D = 65536u - lim8;
+    uint32_t sh2 = 0;
+    while (D && ((D - 1) >> sh2) >= 128) sh2++;
+    for (uint32_t e = lane; e < 256; e += 64) {
+        const uint32_t f = canon_find(c, e << 8, 1, 8);
+        const uint32_t v = f ? (f & 0xFF00u) | c->vals[f & 255u] : 0u;
+        t->lut[e] = (uint16_t)v;
+        t->lutp[e] = packed_entry(v, first);
+        t->huffval[e] = c->vals[e];
+    }
+    for (uint32_t e = lane; e < 128; e += 64) {
+        const uint32_t c16 = lim8 + (e << sh2);
+        const uint32_t f = c16 < 65536u ? canon_find(c, c16, 9, 16) : 0u;
+        t->lut2[e] = (uint16_t)((f && 16u - (f >> 8) >= sh2) ? (f & 0xFF00u) | c->vals[f & 255u] : 0u);
+    }
+    if (lane < 9) t->limit[lane] = c->lim[8 + lane];
+    if (lane < 8) t->valptr[lane] = (uint16_t)c->first[9 + lane];
+    if (lane == 0) { t->sh2 = sh2; t->pad = 0; }
+}
+// ... and dctab_build (only the first sixteen codes are DC categories).
+PCR_D void dctab_build_wave(DcTab* t, const CanonCode* c, uint32_t lane) {
+    for (uint32_t e = lane; e < 256; e += 64) {
+        const uint32_t f = canon_find(c, e << 8, 1, 8);
+        t->lut[e] = (f && (f & 255u) < 16u) ? (uint8_t)(((f >> 8) << 4) | (c->vals[f & 255u] & 15)) : (uint8_t)0xFF;
+    }
+    if (lane < 16) t->huffval[lane] = c->vals[lane];
+    if (lane < 9) t->limit[lane] = c->lim[8 + lane];
+    if (lane < 8) t->valptr[lane] = (uint16_t)c->first[9 + lane];
+}
+
+__global__ void __launch_bounds__(kHeaderLanes) k_headers(DevRecord R, uint32_t kmax, uint32_t keep_status, uint32_t own_index, uint32_t k0, uint32_t dc_too) {
+    __shared__ __attribute__((aligned(16))) uint8_t stage[kHeaderStage];
+    __shared__ uint32_t s_off[kMaxGroups], s_len[kMaxGroups];
+    __shared__ ScanDesc s_scan[kMaxGroups];
+    __shared__ ImgDesc s_img;
+    __shared__ CanonCode s_code[kHeaderWaves];
     short_kernel_priority();
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= R.n) return;
-    parse_image(R.rec, R.off, R.len, R.n, i, R.nscans[i], kmax, &R.img[i], &R.scan[(size_t)i * R.G]);
-    if (!(keep_status && R.status[i] != kOk)) R.status[i] = R.img[i].status;
+    const uint32_t i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t n = R.n, nsc = R.nscans[i];
+    uint32_t upto = nsc < kmax ? nsc : kmax;
+    if (upto > kMaxGroups) upto = kMaxGroups;               // (cannot happen: the header check refuses such records)
+    // ---- where the regions lie ----
+    if (own_index) {
+        for (uint32_t g = wave; g < upto; g += kHeaderWaves) {
+            uint32_t before = 0;
+            for (uint32_t j = lane; j < i; j += 64) before += R.len[(size_t)g * n + j];
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d);
+            if (lane == 0) {
+                const uint32_t start = g == 0 ? (uint32_t)ld_le64(R.rec + 16) : (uint32_t)ld_le64(R.rec + hdr_group_end_pos(g - 1));
+                s_off[g] = start + before; s_len[g] = R.len[(size_t)g * n + i];
+            }
+        }
+    } else if (tid < upto) { s_off[tid] = R.off[(size_t)tid * n + i]; s_len[tid] = R.len[(size_t)tid * n + i]; }
+    for (uint32_t e = tid; e < sizeof(ScanDesc) * kMaxGroups / 4; e += kHeaderLanes) reinterpret_cast<uint32_t*>(s_scan)[e] = 0;
+    for (uint32_t e = tid; e < sizeof(ImgDesc) / 4; e += kHeaderLanes) reinterpret_cast<uint32_t*>(&s_img)[e] = 0;
+    __syncthreads();
+    // ---- their first bytes ----
+    uint32_t window = upto ? (kHeaderStage / upto) & ~15u : 0u;
+    if (window > kHeaderWindow) window = kHeaderWindow;
+    const uint32_t pieces = window >> 4;                     // 16-byte pieces per region
+    for (uint32_t e = tid; e < pieces * upto; e += kHeaderLanes) {
+        const uint32_t g = e / pieces, o = (e - g * pieces) * 16, L = s_len[g];
+        if (o >= L) continue;
+        const uint8_t* src = R.rec + s_off[g] + o;
+        uint8_t* dst = stage + g * window + o;
+        if (o + 16 <= L) {
+            struct __attribute__((packed, aligned(1))) Sixteen { uint32_t a, b, c, d; };
+            const Sixteen t = *reinterpret_cast<const Sixteen*>(src);
+            *reinterpret_cast<uint4*>(dst) = uint4{t.a, t.b, t.c, t.d};
+        } else for (uint32_t b = 0; b < L - o; b++) dst[b] = src[b];
+    }
+    __syncthreads();
+    auto bytes_of = [&](uint32_t g) { return HeaderBytes{(GlobalBytes)R.rec, (LdsBytes)(stage + g * window), s_off[g], s_len[g] < window ? s_len[g] : window}; };
+    // ---- the walk: lane g of the first wavefront takes region g ----
+    RegionWalk w{};
+    int rc = kOk;
+    uint32_t dht[8], ri = 0;
+    if (wave == 0) {
+        const uint32_t g = lane;
+        if (g < upto) rc = walk_region(bytes_of(g), s_off[g], s_off[g] + s_len[g], g, &w, &s_img);
+        // what is in force at the scan: the last definition in this region or an earlier one
+        const uint64_t upto_me = g >= 63 ? ~0ull : (2ull << g) - 1;
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+            const uint64_t m = __ballot(g < upto && w.dht[t] != 0) & upto_me;
+            const uint32_t v = (uint32_t)__shfl((int)w.dht[t], m ? 63 - __builtin_clzll(m) : 0);
+            dht[t] = m ? v : 0u;
+        }
+        {
+            const uint64_t m = __ballot(g < upto && w.ri >= 0) & upto_me;
+            const int v = __shfl(w.ri, m ? 63 - __builtin_clzll(m) : 0);
+            ri = m ? (uint32_t)v : 0u;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const uint64_t m = __ballot(g < upto && w.qoff[t] != 0);
+            const int last = m ? 63 - __builtin_clzll(m) : 0;
+            const uint32_t qo = (uint32_t)__shfl((int)w.qoff[t], last), qp = (uint32_t)__shfl((int)w.qprec[t], last);
+            if (lane == 0) { s_img.qoff[t] = m ? qo : 0u; s_img.qprec[t] = (uint8_t)(m ? qp : 0u); }
+        }
+    }
+    __syncthreads();                                        // (the frame header is lane 0's)
+    if (wave == 0 && lane < upto && rc == kOk) rc = resolve_scan(bytes_of(lane), w, s_off[lane] + s_len[lane], dht, ri, &s_img, &s_scan[lane]);
+    __syncthreads();
+    if (wave == 0) {
+        if (lane < upto && rc == kOk) rc = scan_history(s_scan, lane);
+        const uint64_t bad = __ballot(lane < upto && rc != kOk);
+        const uint32_t good = bad ? (uint32_t)__builtin_ctzll(bad) : upto;            // scans ahead of the first damaged region
+        const int first_rc = __shfl(rc, bad ? (int)good : 0);
+        if (lane < (uint32_t)kMaxComp) {                                              // per component: how far its scans reach
+            uint32_t z = 0;
+            for (uint32_t g = 0; g < good; g++)
+                for (uint32_t j = 0; j < s_scan[g].ns; j++)
+                    if (s_scan[g].comp[j] == lane && s_scan[g].Se + 1u > z) z = s_scan[g].Se + 1u;
+            s_img.zmax[lane] = (uint8_t)z;
+        }
+        if (lane == 0) s_img.nscans = good;
+        if (lane >= good && lane < upto) s_scan[lane].valid = 0;
+        const int st = bad ? first_rc : check_image(&s_img, s_scan);
+        if (lane == 0) {
+            s_img.status = st;
+            if (!(keep_status && R.status[i] != kOk)) R.status[i] = st;
+        }
+    }
+    __syncthreads();
+    {
+        uint32_t* dst = reinterpret_cast<uint32_t*>(&R.scan[(size_t)i * R.G]);
+        static_assert(sizeof(ScanDesc) % 4 == 0, "ScanDesc is copied as dwords");
+        for (uint32_t e = tid; e < sizeof(ScanDesc) / 4 * upto; e += kHeaderLanes) dst[e] = reinterpret_cast<const uint32_t*>(s_scan)[e];
+        uint32_t* di = reinterpret_cast<uint32_t*>(&R.img[i]);
+        for (uint32_t e = tid; e < sizeof(ImgDesc) / 4; e += kHeaderLanes) di[e] = reinterpret_cast<const uint32_t*>(&s_img)[e];
+    }
+    if (s_img.status != kOk) return;
+    // ---- the tables ----
+    CanonCode* code = &s_code[wave];
+    for (uint32_t g = k0 + wave; g < upto; g += kHeaderWaves) {
+        const ScanDesc& sd = s_scan[g];
+        const size_t ig = (size_t)i * R.G + g;
+        // (a table may have been defined ahead of this scan's own region: in memory then, unless it is region 0)
+        if (sd.Ss > 0) {
+            canon_build(code, bytes_of(g), sd.ac_off, lane);
+            wave_sync();
+            actab_build_wave(&R.tabs[R.tab_idx[ig]], code, sd.Ah == 0, lane);
+        } else if (dc_too && sd.Ah == 0 && s_img.progressive) {
+            for (uint32_t j = 0; j < sd.ns; j++) {
+                canon_build(code, bytes_of(g), sd.dc_off[j], lane);
+                wave_sync();
+                dctab_build_wave(&R.dctabs[R.dctab_idx[ig] + j], code, lane);
+                wave_sync();
+            }
+        }
+        wave_sync();
+    }
 }
 
 // --------------------------------------------------------------------------------------
@@ -427,7 +634,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_dc_first(DevRecord R, const U
     int tj1 = 0, tj2 = 0, ntab = 1;
     if (o1 != o0) { tj1 = 1; ntab = 2; }
     if (o2 == o1) tj2 = tj1; else if (o2 != o0) { tj2 = ntab; ntab++; }
-    if (R.tabs_prebuilt) {                                  // built once per scan by k_build_tables: copy the distinct ones
+    {                                                       // built by k_headers: copy the distinct ones
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.dctabs[R.dctab_idx[(size_t)un.img * R.G + un.scan]]);
         uint32_t* dst = reinterpret_cast<uint32_t*>(&tabs[0]);
         constexpr uint32_t kWords = sizeof(DcTab) / 4;
@@ -436,10 +643,6 @@ __global__ void __launch_bounds__(kEntropyLanes) k_dc_first(DevRecord R, const U
             if (tj1 == 1) dst[kWords + e] = src[kWords + e];
             if (tj2 != 0 && tj2 != tj1) dst[(uint32_t)tj2 * kWords + e] = src[2 * kWords + e];
         }
-    } else {
-        if (threadIdx.x == 0) dctab_build(&tabs[0], R.rec + o0);
-        if (threadIdx.x == 1 && tj1 == 1) dctab_build(&tabs[1], R.rec + o1);
-        if (threadIdx.x == 2 && tj2 != 0 && tj2 != tj1) dctab_build(&tabs[tj2], R.rec + o2);
     }
     __syncthreads();
     DcWindowReader wr;                                      // tables by scan component
@@ -452,45 +655,12 @@ __global__ void __launch_bounds__(kEntropyLanes) k_dc_first(DevRecord R, const U
     if (rc != kOk) R.status[un.img] = rc;
 }
 
-// The AC table of a unit's scan into LDS: copied from the pre-built one (k_build_tables), or built here from the
-// table definition in the record by one lane and packed by all.  Call with every lane of the wavefront.
-PCR_D void load_ac_table(const DevRecord& R, size_t ig, bool first, AcTab* tab) {
-    if (R.tabs_prebuilt) {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.tabs[R.tab_idx[ig]]);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(tab);
-        for (uint32_t e = threadIdx.x; e < sizeof(AcTab) / 4; e += kEntropyLanes) dst[e] = src[e];
-        __syncthreads();
-        return;
-    }
-    if (threadIdx.x == 0) actab_build(tab, R.rec + R.scan[ig].ac_off);
-    __syncthreads();
-    actab_pack(tab, first, threadIdx.x, kEntropyLanes);
-    __syncthreads();
-}
-
-// One wavefront per (image, scan): the scan's AC table, built once for all its restart intervals.
-// grid: (n, scans), scans k0 .. k0 + gridDim.y - 1.  dc_too = 0: the DC first scans of this call are all decoded by
-// k_dc_first_lanes, which builds its own tables.
-__global__ void __launch_bounds__(kEntropyLanes) k_build_tables(DevRecord R, uint32_t k0, uint32_t dc_too) {
-    __shared__ AcTab tab;
-    short_kernel_priority();
-    const uint32_t i = blockIdx.x, g = k0 + blockIdx.y;
-    if (R.status[i] != kOk || g >= R.img[i].nscans) return;
-    const size_t ig = (size_t)i * R.G + g;
-    const ScanDesc* sd = &R.scan[ig];
-    if (!sd->valid) return;
-    if (sd->Ss == 0) {                                      // DC first scans: the table of every scan component (sequential scans build their own)
-        if (dc_too && sd->Ah == 0 && R.img[i].progressive && threadIdx.x < sd->ns)
-            dctab_build(&R.dctabs[R.dctab_idx[ig] + threadIdx.x], R.rec + sd->dc_off[threadIdx.x]);
-        return;
-    }
-    if (threadIdx.x == 0) actab_build(&tab, R.rec + sd->ac_off);
-    __syncthreads();
-    actab_pack(&tab, sd->Ah == 0, threadIdx.x, kEntropyLanes);
-    __syncthreads();
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(&tab);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(&R.tabs[R.tab_idx[ig]]);
+// The AC table of a unit's scan (built by k_headers) into LDS.  Call with every lane of the wavefront.
+PCR_D void load_ac_table(const DevRecord& R, size_t ig, AcTab* tab) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.tabs[R.tab_idx[ig]]);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(tab);
     for (uint32_t e = threadIdx.x; e < sizeof(AcTab) / 4; e += kEntropyLanes) dst[e] = src[e];
+    __syncthreads();
 }
 
 __global__ void __launch_bounds__(kEntropyLanes) k_ac_first(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
@@ -501,7 +671,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_first(DevRecord R, const U
     unit_setup(R, un, clean32, &L);
     if (!L.ok) return;
     const size_t ig = (size_t)un.img * R.G + un.scan;
-    load_ac_table(R, ig, true, &tab);
+    load_ac_table(R, ig, &tab);
     WindowReader wr;
     wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, &tab, true, threadIdx.x, true);
     IndexSink sink;
@@ -512,7 +682,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_first(DevRecord R, const U
 
 // The same scan kind with one LANE per unit (pcr_lanes.h).  One wavefront per job: up to 64 consecutive units of the
 // launch's list that use at most kLaneTabs different Huffman tables between them (the host cuts the list that way; the
-// units of one scan lie together).  The tables (built by k_build_tables) are copied into LDS first: every lane looks
+// units of one scan lie together).  The tables (built by k_headers) are copied into LDS first: every lane looks
 // its codes up in its own table, and 64 scattered reads of memory per symbol would bound the kernel by the rate at
 // which the memory pipeline takes requests.
 __global__ void __launch_bounds__(kEntropyLanes) k_ac_first_lanes(DevRecord R, const Unit* __restrict__ units, const LaneJob* __restrict__ jobs,
@@ -678,12 +848,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_refine(DevRecord R, const 
     if (!L.ok) return;
     const size_t ig = (size_t)un.img * R.G + un.scan;
     const ScanDesc* sd = &R.scan[ig];
-    load_ac_table(R, ig, false, &tab);
-    if (un.interval == 0 && !R.tabs_prebuilt) {             // phase 2 needs the same table: keep a copy
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(&tab);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(&R.tabs[R.tab_idx[ig]]);
-        for (uint32_t e = threadIdx.x; e < sizeof(AcTab) / 4; e += kEntropyLanes) dst[e] = src[e];
-    }
+    load_ac_table(R, ig, &tab);
     HistPlanes hp;
     hp.coef = L.plane[0];
     hp.n = sd->nhist;

@@ -1,6 +1,6 @@
 // Entropy decoders with ONE LANE PER UNIT: the 64 lanes of a wavefront decode 64 different units (restart intervals or
 // entry-point units) of the same kind of scan, each lane with its own bit buffer, Huffman table (the wavefront's copy, in
-// LDS, of a table k_build_tables left in memory) and position in its image's coefficient plane.
+// LDS, of a table k_headers left in memory) and position in its image's coefficient plane.
 //
 // When they pay.  A wavefront that decodes one unit on the scalar ALU (pcr_entropy.h) spends about 14 scalar
 // instructions per symbol, and the chip issues 256 of those per cycle: a throughput bound that a record with tens of

@@ -128,7 +128,7 @@ struct pcr_record {
     uint32_t flat_row_cells = 0;                                    // cells per row of the widest image
     PixelTile* d_flat_rows = nullptr; uint32_t n_flat_rows = 0;     // ... and rows of cells (none if an image is too wide for k_pixel_flat_rows)
     uint32_t* d_dims = nullptr;             // [n][2] width, height (for kernels that run without a decode before them)
-    bool prebuild_tables = false;           // some AC scan has restart intervals: k_build_tables runs before the entropy kernels
+    bool several_units = false;             // some scan has several units (restart intervals, entry points): lane decoders are worth considering
     int lane_mode = 0;                      // pcr_set_lane_decoders: 0 by the number of units, 1 wherever possible, -1 never
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
@@ -356,10 +356,9 @@ int add_call_times(const CallTiming& c, double* ms, uint32_t* marks) {
 // the decodes of other records (other streams) already from a few thousand, because what it leaves idle the others use:
 // four records in flight decode twice as fast with lanes.  The library cannot see what
 // else runs on the device; it takes the number of records the process has open as the sign of it.
-// The lane kernels read the Huffman tables from memory: the tables must be pre-built.
 constexpr uint32_t kLanesMinUnitsShared = 8192, kLanesMinUnitsAlone = 32768;
 bool lanes_pay(const pcr_record* r, const LevelList& l) {
-    if (!r->prebuild_tables || r->lane_mode < 0 || l.n_jobs == 0) return false;
+    if (!r->several_units || r->lane_mode < 0 || l.n_jobs == 0) return false;
     if (r->lane_mode > 0) return true;
     const uint32_t least = g_open_records.load(std::memory_order_relaxed) > 1 ? kLanesMinUnitsShared : kLanesMinUnitsAlone;
     return l.n >= least && l.n >= 32u * l.n_jobs;            // (jobs half full at least: few tables per 64 units)
@@ -375,6 +374,16 @@ bool dc_lanes_pay(const pcr_record* r, const LevelList& l) {
     return g_open_records.load(std::memory_order_relaxed) > 1 && l.n >= kDcLanesMinUnits;
 }
 
+// Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
+// regions in the same kernel: a launch costs about as much as k_index runs, and a workgroup of k_headers sums at most
+// kOwnIndexImages lengths per scan group.
+void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bool dc_tables, hipStream_t s) {
+    const uint32_t n = r->hdr.n;
+    const bool own = n <= kOwnIndexImages;
+    if (!own) hipLaunchKernelGGL(k_index, dim3(k), dim3(256), 0, s, r->d, k);
+    hipLaunchKernelGGL(k_headers, dim3(n), dim3(kHeaderLanes), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
+}
+
 // Steps 1-5 of the path (index .. entropy decode + refinement) for scans 1..k.
 // refine_in_memory: also run k_apply, which leaves the refined coefficients in the planes (the coefficient
 // export needs that; the pixel kernel replays the refinement itself from the lists of k_apply_prep).
@@ -386,9 +395,6 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     *plan_out = plan;
     const uint32_t n = r->hdr.n;
     call_begin(r, s);
-    hipLaunchKernelGGL(k_index, dim3(k), dim3(256), 0, s, r->d, (uint32_t)k);
-    hipLaunchKernelGGL(k_parse, dim3((n + 63) / 64), dim3(64), 0, s, r->d, (uint32_t)k, (uint32_t)(k0 > 0));
-    r->d.tabs_prebuilt = r->prebuild_tables ? 1u : 0u;
     // (the wavefront decoders of DC first scans read pre-built tables, the lane decoder makes its own: when every launch
     // of DC first scans of this call goes to the lanes their tables are not built, and with DC first scans only, none are)
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
@@ -400,8 +406,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         dc_by_lanes[li] = dc_lanes_pay(r, l) ? 1 : 0;
         if (!dc_by_lanes[li]) dc_tables = true;
     }
-    if (r->prebuild_tables && k > k0 && (dc_tables || plan->has_ac))
-        hipLaunchKernelGGL(k_build_tables, dim3(n, k - k0), dim3(kEntropyLanes), 0, s, r->d, (uint32_t)k0, dc_tables ? 1u : 0u);
+    launch_headers(r, (uint32_t)k, k0 > 0, dc_tables || plan->has_ac ? (uint32_t)k0 : (uint32_t)k, dc_tables, s);
     mark(r, PCR_STAGE_INDEX_PARSE, s);
     if (k > k0) hipLaunchKernelGGL(k_unstuff, dim3(n, k - k0), dim3(256), 0, s, r->d, (uint32_t)k0, (uint32_t)k);
     const size_t coef_bytes = r->coef_off[n] * sizeof(int16_t);
@@ -517,7 +522,7 @@ static int finish_open(pcr_record* r, hipStream_t s) {
     uint64_t nm = 0; uint64_t ns = 0;
     std::vector<uint32_t> tab_idx((size_t)n * G, 0); uint32_t ntabs = 0;
     std::vector<uint32_t> dctab_idx((size_t)n * G, 0); uint32_t ndctabs = 0;
-    r->prebuild_tables = false;
+    r->several_units = false;
     // version 2: where the entry points of every scan lie (behind the regions of the scan's group)
     std::vector<uint32_t> ent_off((size_t)n * G, 0), ent_cnt((size_t)n * G, 0);
     if (r->hdr.version == 2) {
@@ -557,7 +562,7 @@ static int finish_open(pcr_record* r, hipStream_t s) {
             if (sd.ri == 0 && serial && ent_cnt[ig] > 0) cnt = 1 + ent_cnt[ig];         // units start at the entry points
             else ent_off[ig] = 0;
             if (d.progressive && sd.Ss == 0 && sd.Ah == 0) { dctab_idx[ig] = ndctabs; ndctabs += kMaxComp; }
-            if (cnt > 1 && (sd.Ss > 0 || d.progressive)) r->prebuild_tables = true;     // several units share a scan's tables: build them once
+            if (cnt > 1 && (sd.Ss > 0 || d.progressive)) r->several_units = true;
             r->slot_base[ig] = (uint32_t)ns; r->slot_cnt[ig] = cnt;
             ns += cnt + 1;
         }
@@ -739,8 +744,7 @@ static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, hipStr
     rc = validate_index(r->header.data(), h, &off, &len, &nsc);
     if (!rc) { r->d.rec = (const uint8_t*)d_bytes; rc = alloc_descriptor_buffers(r, s); }
     if (!rc) {
-        hipLaunchKernelGGL(k_index, dim3(h.k_avail), dim3(256), 0, s, r->d, h.k_avail);
-        hipLaunchKernelGGL(k_parse, dim3((n + 63) / 64), dim3(64), 0, s, r->d, h.k_avail, 0u);
+        launch_headers(r, h.k_avail, false, h.k_avail, false, s);          // (no tables: where they go is not laid out yet)
         r->img.resize(n); r->scan.resize((size_t)n * G);
         if (hipMemcpyAsync(r->img.data(), r->d.img, n * sizeof(ImgDesc), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipMemcpyAsync(r->scan.data(), r->d.scan, (size_t)n * G * sizeof(ScanDesc), hipMemcpyDeviceToHost, s) != hipSuccess ||
