@@ -139,7 +139,6 @@ struct pcr_record {
     uint8_t* d_edge = nullptr; uint64_t* d_edge_off = nullptr; uint32_t* d_mcu_px_h = nullptr;
     float2* d_ssim_part = nullptr;          // per-tile sums of the similarity kernels (allocated at their first call)
     uint8_t* d_planes = nullptr;            // rounded samples per component, for pcr_decode_batch_triangle (allocated at its first call)
-    uint32_t ssim_tiles_max = 0;
     uint8_t* d_gather = nullptr; size_t gather_cap = 0;
     std::map<int, Plan> plans;
     bool timing = false;
@@ -720,7 +719,7 @@ int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out)
 static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, hipStream_t s) {
     r->plans.clear(); r->resident_k = 0; r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0;
     r->out_off.assign(1, 0); r->coef_off.assign(1, 0);        // until the bind succeeds the handle holds no record
-    r->d_dims = nullptr; r->d_ssim_part = nullptr; r->ssim_tiles_max = 0; r->d_planes = nullptr;
+    r->d_dims = nullptr; r->d_ssim_part = nullptr; r->d_planes = nullptr;
     r->d_tail_tiles = nullptr; r->n_tail_tiles = 0; r->d_edge = nullptr; r->d_edge_off = nullptr; r->d_mcu_px_h = nullptr;
     // fixed part of the header, then the whole metadata block
     uint8_t fixed[24];
@@ -1144,6 +1143,25 @@ int pcr_decode_crop_batch(pcr_record* r, int k, const pcr_crop* d_crops, uint8_t
     return pcr_crop_resize_batch(r, d_pixels, d_crops, out_h, out_w, mean, inv_std, d_out_f16, out_capacity, stream);
 }
 
+// Rows per tile and tiles of the picture that needs most, for the similarity kernels.
+static void ssim_layout(const pcr_record* r, uint32_t* rows, uint32_t* tiles_max) {
+    const uint32_t n = r->hdr.n;
+    for (uint32_t pick : kSsimRowChoices) {
+        uint32_t t = 1;
+        for (uint32_t i = 0; i < n; i++) t = std::max(t, ssim_tiles_all((uint32_t)r->img[i].W, (uint32_t)r->img[i].H, pick));
+        *rows = pick; *tiles_max = t;
+        if (ssim_rows_suit(n, t)) return;
+    }
+}
+static int launch_ssim(pcr_record* r, const uint8_t* d_a, const uint8_t* d_b, float2* part, uint32_t rows, uint32_t tmax, float* d_scores, hipStream_t s) {
+    const uint32_t n = r->hdr.n, groups = (tmax + kSsimWaves - 1) / kSsimWaves;
+    if ((uint64_t)groups * n >= (1ull << 31)) return PCR_E_UNSUPPORTED;
+    if (r->img[0].nc == 3) hipLaunchKernelGGL(k_ssim_tiles<3>, dim3(groups * n), dim3(64 * kSsimWaves), 0, s, r->d_dims, r->d.out_off, d_a, d_b, part, n, tmax, rows);
+    else hipLaunchKernelGGL(k_ssim_tiles<1>, dim3(groups * n), dim3(64 * kSsimWaves), 0, s, r->d_dims, r->d.out_off, d_a, d_b, part, n, tmax, rows);
+    hipLaunchKernelGGL(k_ssim_score, dim3(n), dim3(64), 0, s, r->d_dims, part, tmax, rows, d_scores);
+    return hipGetLastError() == hipSuccess ? PCR_OK : PCR_E_DEVICE;
+}
+
 int pcr_msssim_batch(pcr_record* r, const uint8_t* d_a, const uint8_t* d_b, float* d_scores, void* stream) {
     if (!r || !d_a || !d_b || !d_scores) return PCR_E_ARG;
     const uint32_t n = r->hdr.n;
@@ -1153,18 +1171,13 @@ int pcr_msssim_batch(pcr_record* r, const uint8_t* d_a, const uint8_t* d_b, floa
     for (uint32_t i = 1; i < n; i++) if (r->img[i].nc != C) return PCR_E_UNSUPPORTED;
     if (n > 65535) return PCR_E_UNSUPPORTED;                  // (images are the grid's second dimension)
     HIP_TRY(hipSetDevice(r->device));
+    uint32_t rows, tmax;
+    ssim_layout(r, &rows, &tmax);
     if (!r->d_ssim_part) {
-        uint32_t tmax = 1;
-        for (uint32_t i = 0; i < n; i++) tmax = std::max(tmax, ssim_tiles_all((uint32_t)r->img[i].W, (uint32_t)r->img[i].H));
         int rc = arena_alloc(&r->big, &r->d_ssim_part, (size_t)n * tmax);
         if (rc) return rc;
-        r->ssim_tiles_max = tmax;
     }
-    hipLaunchKernelGGL(k_ssim_tiles, dim3(r->ssim_tiles_max, n), dim3(256), 0, (hipStream_t)stream, r->d_dims, r->d.out_off, C, d_a, d_b,
-                       r->d_ssim_part, r->ssim_tiles_max);
-    hipLaunchKernelGGL(k_ssim_score, dim3(n), dim3(64), 0, (hipStream_t)stream, r->d_dims, r->d_ssim_part, r->ssim_tiles_max, d_scores);
-    if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
-    return PCR_OK;
+    return launch_ssim(r, d_a, d_b, r->d_ssim_part, rows, tmax, d_scores, (hipStream_t)stream);
 }
 
 // ---- similarity scores without any allocation ----
@@ -1199,18 +1212,17 @@ int pcr_msssim_batch_static(pcr_record* r, const uint8_t* d_a, const uint8_t* d_
     if (C != 1 && C != 3) return PCR_E_UNSUPPORTED;
     for (uint32_t i = 1; i < n; i++) if (r->img[i].nc != C) return PCR_E_UNSUPPORTED;
     if (n > 65535) return PCR_E_UNSUPPORTED;
-    uint32_t tmax = 1;
-    for (uint32_t i = 0; i < n; i++) tmax = std::max(tmax, ssim_tiles_all((uint32_t)r->img[i].W, (uint32_t)r->img[i].H));
-    if ((uint64_t)n * tmax > kStaticSsimTiles) return PCR_E_RANGE;   // the record's tile sums do not fit the fixed array
+    // (the limit is stated, and stays, in tiles of 32 x 32 window positions, of which the kernels' tiles are fewer)
+    uint32_t limit = 1, rows, tmax;
+    for (uint32_t i = 0; i < n; i++) limit = std::max(limit, ssim_limit_tiles((uint32_t)r->img[i].W, (uint32_t)r->img[i].H));
+    if ((uint64_t)n * limit > kStaticSsimTiles) return PCR_E_RANGE;   // the record's tile sums do not fit the fixed array
     HIP_TRY(hipSetDevice(r->device));
     float2* part = nullptr;
     int rc = static_scratch(r->device, &part);
     if (rc) return rc;
     // (nothing to clear: every entry k_ssim_score reads is written by k_ssim_tiles in the same call)
-    hipLaunchKernelGGL(k_ssim_tiles, dim3(tmax, n), dim3(256), 0, (hipStream_t)stream, r->d_dims, r->d.out_off, C, d_a, d_b, part, tmax);
-    hipLaunchKernelGGL(k_ssim_score, dim3(n), dim3(64), 0, (hipStream_t)stream, r->d_dims, part, tmax, d_scores);
-    if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
-    return PCR_OK;
+    ssim_layout(r, &rows, &tmax);
+    return launch_ssim(r, d_a, d_b, part, rows, tmax, d_scores, (hipStream_t)stream);
 }
 
 // ---- record creation (host only) ----

@@ -8,18 +8,30 @@
 // scales as keep the smaller side at least 11 samples (with fewer than five, the exponents used are rescaled to
 // sum to 1); a negative scale mean counts as 0.
 //
-// Layout of the work: one workgroup per 32 x 32 tile of window positions of one scale of one picture.  A
-// sample of scale j is the mean of an aligned 2^j x 2^j block of the picture (what j rounds of 2 x 2 averaging
-// give), taken straight from the uint8 pixels with exact integer sums, so no pyramid is ever stored.  The
-// window is separable: 11 taps along rows into LDS, 11 taps down columns out of it.  Samples are centred on
-// 128 before squaring, which keeps the fp32 variances (a difference of two large numbers) accurate.
+// Layout of the work: ONE WAVEFRONT per strip of 64 columns (54 window positions) and up to 96 rows of window positions
+// of one scale of one picture.  A lane owns a column and walks down it: it makes the two samples of its column, and adds
+// them to the eleven windows that are open in its column -- a chain of eleven fused multiply-adds per moment that also
+// moves every open window on by one (a[t] = a[t-1] + g[t] v), so the column pass takes no memory at all.  Every fourth
+// row the four finished rows of column sums go through LDS, and the lanes finish them as four neighbouring window
+// positions each: sixteen values per moment, read as four 16-byte vectors, make 4 x 11 taps.
+// Four moments are enough: with s = a + b and d = a - b (a, b: the two pictures) the terms are
+//   (2 cov + C2) / (var_a + var_b + C2)             = (var_s - var_d + 2 C2) / (var_s + var_d + 2 C2),
+//   (2 mu_a mu_b + C1) / (mu_a^2 + mu_b^2 + C1)     = (mu_s^2 - mu_d^2 + 2 C1) / (mu_s^2 + mu_d^2 + 2 C1),
+// and only the term a scale contributes is computed (contrast-structure below the last scale, the product at it).
+// A sample of scale j is the mean of an aligned 2^j x 2^j block of the picture (what j rounds of 2 x 2 averaging
+// give), taken straight from the uint8 pixels with exact integer sums, so no pyramid is ever stored.  Samples are
+// centred on 128 before squaring, which keeps the fp32 variances (a difference of two large numbers) accurate.
+// Bound by vector issue (about 165 vector instructions per 64 columns and row, 88 of them the taps).  The version before --
+// a workgroup per 32 x 32 tile, five moments, both passes through LDS, 84 LDS reads and 210 operations per window
+// position -- took 5.3 ms for 1024 pictures of 300..500 pixels a side where this one takes 1.6.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "pcr_kernels.h"
 
 namespace pcr {
 
-constexpr int kSsimScales = 5, kSsimWin = 11, kSsimTile = 32, kSsimIn = kSsimTile + kSsimWin - 1;     // 42
+constexpr int kSsimScales = 5, kSsimWin = 11, kSsimCols = 64 - (kSsimWin - 1);     // window positions across a strip
 
 __host__ __device__ inline int ssim_scale_count(uint32_t W, uint32_t H) {
     const uint32_t m = W < H ? W : H;
@@ -28,120 +40,234 @@ __host__ __device__ inline int ssim_scale_count(uint32_t W, uint32_t H) {
     while (M < kSsimScales && (m >> M) >= (uint32_t)kSsimWin) M++;
     return M;
 }
-// Tiles of scale j of a W x H picture (j below its scale count), and how many lie side by side.
-__host__ __device__ inline uint32_t ssim_tiles(uint32_t W, uint32_t H, int j, uint32_t* across) {
+// Tiles (strips of `rows` window positions down) of scale j of a W x H picture (j below its scale count), and how many
+// lie side by side.
+__host__ __device__ inline uint32_t ssim_tiles(uint32_t W, uint32_t H, int j, uint32_t rows, uint32_t* across) {
     const uint32_t ow = (W >> j) - (kSsimWin - 1), oh = (H >> j) - (kSsimWin - 1);
-    *across = (ow + kSsimTile - 1) / kSsimTile;
-    return *across * ((oh + kSsimTile - 1) / kSsimTile);
+    *across = (ow + kSsimCols - 1) / kSsimCols;
+    return *across * ((oh + rows - 1) / rows);
 }
-__host__ __device__ inline uint32_t ssim_tiles_all(uint32_t W, uint32_t H) {
+__host__ __device__ inline uint32_t ssim_tiles_all(uint32_t W, uint32_t H, uint32_t rows) {
     uint32_t t = 0, across;
-    for (int j = 0, M = ssim_scale_count(W, H); j < M; j++) t += ssim_tiles(W, H, j, &across);
+    for (int j = 0, M = ssim_scale_count(W, H); j < M; j++) t += ssim_tiles(W, H, j, rows, &across);
+    return t;
+}
+// Rows per tile: ten rows are walked down before the first window is complete, so tall tiles waste less, but tiles of very
+// different heights leave the last wave of wavefronts ragged.  1024 photographs, ms: 256 rows 1.92, 128 1.71, 96 1.61,
+// 64 1.68.  A launch wants eight wavefronts per SIMD (8192); few or small pictures are cut finer to have them.
+constexpr uint32_t kSsimRowChoices[3] = {96, 64, 32};
+inline bool ssim_rows_suit(uint32_t n, uint32_t tiles_max) { return (uint64_t)n * tiles_max >= 8192; }
+
+// What the entry point that allocates nothing counts its limit in: tiles of 32 x 32 window positions of all scales.
+inline uint32_t ssim_limit_tiles(uint32_t W, uint32_t H) {
+    uint32_t t = 0;
+    for (int j = 0, M = ssim_scale_count(W, H); j < M; j++) {
+        const uint32_t ow = (W >> j) - (kSsimWin - 1), oh = (H >> j) - (kSsimWin - 1);
+        t += ((ow + 31) / 32) * ((oh + 31) / 32);
+    }
     return t;
 }
 
-// part[i * tiles_max + t] = (sum of contrast-structure, sum of luminance x contrast-structure) over the
-// window positions of tile t of picture i; tiles are numbered scale by scale.
-__global__ void __launch_bounds__(256) k_ssim_tiles(const uint32_t* __restrict__ dims, const uint64_t* __restrict__ out_off, int C,
+// sums of the bytes of 2^j pixels of one row, per channel
+struct SsimSum { uint32_t c0, c1, c2; };
+template <class T> __device__ inline T ssim_load(const uint8_t* p) { struct __attribute__((packed, aligned(1))) U { T v; }; return reinterpret_cast<const U*>(p)->v; }
+__device__ inline void ssim_add4(SsimSum* s, uint32_t w0, uint32_t w1, uint32_t w2) {       // four RGB pixels in twelve bytes
+    s->c0 = __builtin_amdgcn_udot4(w2, 0x00000100u, __builtin_amdgcn_udot4(w1, 0x00010000u, __builtin_amdgcn_udot4(w0, 0x01000001u, s->c0, false), false), false);
+    s->c1 = __builtin_amdgcn_udot4(w2, 0x00010000u, __builtin_amdgcn_udot4(w1, 0x01000001u, __builtin_amdgcn_udot4(w0, 0x00000100u, s->c1, false), false), false);
+    s->c2 = __builtin_amdgcn_udot4(w2, 0x01000001u, __builtin_amdgcn_udot4(w1, 0x00000100u, __builtin_amdgcn_udot4(w0, 0x00010000u, s->c2, false), false), false);
+}
+// The bytes of the block of one sample of scale J that lie in kRows rows of it (C channels), as loaded.
+template <int C, int J, int kRows>
+struct SsimRaw {
+    static constexpr int kBytes = C << J, kWords = (kBytes + 3) / 4;
+    uint32_t w[kRows][kWords];
+    __device__ inline void load(const uint8_t* p, uint32_t pitch) {
+#pragma unroll
+        for (int r = 0; r < kRows; r++) {
+            const uint8_t* q = p + (size_t)r * pitch;
+            if (kBytes == 1) w[r][0] = q[0];
+            else if (kBytes == 2) w[r][0] = ssim_load<uint16_t>(q);
+            else if (kBytes == 3) w[r][0] = ssim_load<uint16_t>(q) | ((uint32_t)q[2] << 16);      // (never a byte past the block: it may be the buffer's last)
+            else if (kBytes == 6) { w[r][0] = ssim_load<uint32_t>(q); w[r][kWords - 1] = ssim_load<uint16_t>(q + 4); }
+            else {
+                constexpr int kVec = kWords % 4 == 0 ? 4 : (kWords % 3 == 0 ? 3 : 1);
+                struct V { uint32_t e[kVec]; };
+#pragma unroll
+                for (int v = 0; v < kWords / kVec; v++) {
+                    const V t = ssim_load<V>(q + 4 * kVec * v);
+#pragma unroll
+                    for (int e = 0; e < kVec; e++) w[r][kVec * v + e] = t.e[e];
+                }
+            }
+        }
+    }
+    __device__ inline void add_to(SsimSum* s) const {
+#pragma unroll
+        for (int r = 0; r < kRows; r++) {
+            if (C == 1) {
+#pragma unroll
+                for (int q = 0; q < kWords; q++) s->c0 = __builtin_amdgcn_udot4(w[r][q], 0x01010101u, s->c0, false);
+            } else if (kBytes == 3) {
+                s->c0 += w[r][0] & 255u; s->c1 += (w[r][0] >> 8) & 255u; s->c2 += w[r][0] >> 16;
+            } else if (kBytes == 6) {
+                s->c0 = __builtin_amdgcn_udot4(w[r][0], 0x01000001u, s->c0, false);
+                s->c1 = __builtin_amdgcn_udot4(w[r][kWords - 1], 0x00000001u, __builtin_amdgcn_udot4(w[r][0], 0x00000100u, s->c1, false), false);
+                s->c2 = __builtin_amdgcn_udot4(w[r][kWords - 1], 0x00000100u, __builtin_amdgcn_udot4(w[r][0], 0x00010000u, s->c2, false), false);
+            } else {
+#pragma unroll
+                for (int q = 0; q + 2 < kWords; q += 3) ssim_add4(s, w[r][q], w[r][q + 1], w[r][q + 2]);
+            }
+        }
+    }
+};
+template <int C>
+__device__ inline float ssim_luma(const SsimSum& s, float inv_area) {
+    if (C == 3) return (0.299f * (float)s.c0 + 0.587f * (float)s.c1 + 0.114f * (float)s.c2) * inv_area - 128.0f;
+    return (float)s.c0 * inv_area - 128.0f;
+}
+// num / den, den > 0 far from the ends of the range: one refinement of the reciprocal, exact where num == den
+__device__ inline float ssim_ratio(float num, float den) {
+    const float r = __builtin_amdgcn_rcpf(den), q = num * r;
+    return __builtin_fmaf(__builtin_fmaf(-q, den, num), r, q);
+}
+
+constexpr int kSsimWaves = 4;              // strips per workgroup: neighbours in the picture, which read the same lines at the edges
+constexpr int kSsimRowLen = 80;            // columns of a row in LDS: 64, and what the last lanes' vectors run over
+struct SsimRows { float v[4][4][kSsimRowLen]; };       // [moment][row][column]
+
+// One strip: rows_in rows of samples of scale J whose column starts at A and B (rows of the pictures pitch bytes apart);
+// ow, x0: window positions across the scale and the strip's first; last: the scale contributes the product of both terms.
+// Returns this lane's share of the sum.
+template <int C, int J>
+__device__ inline float ssim_strip(const uint8_t* A, const uint8_t* B, uint32_t pitch, uint32_t rows_in, uint32_t x0, uint32_t ow, bool last, SsimRows* L, uint32_t lane) {
+    // the window: exp(-(t - 5)^2 / (2 1.5^2)), normalised (symmetric)
+    constexpr float g[kSsimWin] = {0.0010283801f, 0.0075987582f, 0.036000773f, 0.10936069f, 0.21300554f, 0.26601172f,
+                                   0.21300554f, 0.10936069f, 0.036000773f, 0.0075987582f, 0.0010283801f};
+    constexpr float inv_area = 1.0f / (float)(1 << (2 * J));
+    // Rows of pixels in flight: at the two largest scales (94 % of the work) the next sample's block is under way while
+    // this one's is added to the windows; at the smaller ones a block is more registers than that is worth.
+    constexpr bool kAhead = J <= 1;
+    constexpr int kRows = J == 0 ? 1 : (J == 4 ? 2 : (J == 3 ? 4 : 1 << J));
+    const uint32_t rows_out = rows_in - (kSsimWin - 1);
+    float ms[kSsimWin], md[kSsimWin], ss[kSsimWin], dd[kSsimWin];     // open windows of the column: [rows of the window behind it]
+#pragma unroll
+    for (int q = 0; q < kSsimWin; q++) ms[q] = md[q] = ss[q] = dd[q] = 0.f;
+    const uint32_t hrow = lane >> 4, hcol = (lane & 15u) * 4; // the finishing pass: row of the four, first of four positions
+    float sum = 0.f;
+    const size_t down = (size_t)pitch << J;
+    SsimRaw<C, J, kRows> ra, rb;
+    if (kAhead) { ra.load(A, pitch); rb.load(B, pitch); }
+    for (uint32_t y = 0; y < rows_in; y++) {
+        SsimSum sa{0, 0, 0}, sb{0, 0, 0};
+        if (kAhead) {
+            ra.add_to(&sa); rb.add_to(&sb);
+            if (y + 1 < rows_in) { A += down; B += down; }    // (the last row once more: its bytes are there)
+            ra.load(A, pitch); rb.load(B, pitch);
+        } else {
+#pragma unroll 1
+            for (int r = 0; r < (1 << J); r += kRows) {
+                ra.load(A + (size_t)r * pitch, pitch); rb.load(B + (size_t)r * pitch, pitch);
+                ra.add_to(&sa); rb.add_to(&sb);
+            }
+            A += down; B += down;
+        }
+        const float va = ssim_luma<C>(sa, inv_area), vb = ssim_luma<C>(sb, inv_area);
+        const float s = va + vb, d = va - vb, s2 = s * s, d2 = d * d;
+#pragma unroll
+        for (int q = kSsimWin - 1; q > 0; q--) {
+            ms[q] = __builtin_fmaf(g[q], s, ms[q - 1]); md[q] = __builtin_fmaf(g[q], d, md[q - 1]);
+            ss[q] = __builtin_fmaf(g[q], s2, ss[q - 1]); dd[q] = __builtin_fmaf(g[q], d2, dd[q - 1]);
+        }
+        ms[0] = g[0] * s; md[0] = g[0] * d; ss[0] = g[0] * s2; dd[0] = g[0] * d2;
+        if (y < (uint32_t)(kSsimWin - 1)) continue;
+        const uint32_t r = y - (kSsimWin - 1);
+        L->v[0][r & 3][lane] = ms[kSsimWin - 1]; L->v[1][r & 3][lane] = md[kSsimWin - 1];
+        L->v[2][r & 3][lane] = ss[kSsimWin - 1]; L->v[3][r & 3][lane] = dd[kSsimWin - 1];
+        if ((r & 3) != 3 && r + 1 != rows_out) continue;
+        wave_sync();                                          // window rows r & ~3 .. r of the tile are in LDS
+        float m[4][4];                                        // [moment][position]
+#pragma unroll
+        for (int f = 0; f < 4; f++) {
+            float v[16];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const float4 x = *reinterpret_cast<const float4*>(&L->v[f][hrow][hcol + 4 * q]);
+                v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+            }
+#pragma unroll
+            for (int o = 0; o < 4; o++) {
+                float acc = g[0] * v[o];
+#pragma unroll
+                for (int q = 1; q < kSsimWin; q++) acc = __builtin_fmaf(g[q], v[o + q], acc);
+                m[f][o] = acc;
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < 4; o++) {
+            const float m2 = m[0][o] * m[0][o], e2 = m[1][o] * m[1][o];
+            const float var_s = m[2][o] - m2, var_d = m[3][o] - e2, c2 = 2.0f * 58.5225f;
+            float v = ssim_ratio(var_s - var_d + c2, var_s + var_d + c2);
+            if (last) {
+                const float ps = m[0][o] + 256.0f, p2 = ps * ps, c1 = 2.0f * 6.5025f;
+                v *= ssim_ratio(p2 - e2 + c1, p2 + e2 + c1);
+            }
+            const uint32_t x = hcol + o;
+            sum += (x < (uint32_t)kSsimCols && x0 + x < ow && (r & ~3u) + hrow < rows_out) ? v : 0.f;
+        }
+        wave_sync();
+    }
+    return sum;
+}
+
+// part[i * tiles_max + t] = (sum of contrast-structure, sum of luminance x contrast-structure; only the one its scale
+// contributes) over the window positions of tile t of picture i; tiles are numbered scale by scale.
+template <int C>
+__global__ void __launch_bounds__(64 * kSsimWaves) k_ssim_tiles(const uint32_t* __restrict__ dims, const uint64_t* __restrict__ out_off,
                                                     const uint8_t* __restrict__ pa, const uint8_t* __restrict__ pb,
-                                                    float2* __restrict__ part, uint32_t tiles_max) {
-    __shared__ float sa[kSsimIn][kSsimIn + 1], sb[kSsimIn][kSsimIn + 1];
-    __shared__ float hp[5][kSsimIn][kSsimTile + 1];
-    __shared__ float g[kSsimWin];
-    __shared__ float red[4][2];
-    const uint32_t i = blockIdx.y, tid = threadIdx.x;
+                                                    float2* __restrict__ part, uint32_t n, uint32_t tiles_max, uint32_t rows) {
+    __shared__ __attribute__((aligned(16))) SsimRows buf[kSsimWaves];
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // (every die works through a contiguous eighth of the pictures: the scales of a picture read the same pixels)
+    const uint32_t groups = (tiles_max + kSsimWaves - 1) / kSsimWaves;
+    const uint32_t item = xcd_major(blockIdx.x, gridDim.x), i = item / groups;
+    if (i >= n) return;
+    uint32_t t = uni((item - i * groups) * kSsimWaves + wave);
     const uint32_t W = dims[2 * i], H = dims[2 * i + 1];
     const int M = ssim_scale_count(W, H);
-    uint32_t t = blockIdx.x, across = 1;
+    const uint32_t slot = t;
+    uint32_t across = 1;
     int j = 0;
     for (; j < M; j++) {
-        const uint32_t cnt = ssim_tiles(W, H, j, &across);
+        const uint32_t cnt = ssim_tiles(W, H, j, rows, &across);
         if (t < cnt) break;
         t -= cnt;
     }
-    if (j >= M) return;                                              // (uniform over the workgroup)
+    if (j >= M) return;                                     // (the wavefronts of a workgroup share nothing)
     const uint32_t Wj = W >> j, Hj = H >> j, ow = Wj - (kSsimWin - 1), oh = Hj - (kSsimWin - 1);
-    const uint32_t ox = (t % across) * kSsimTile, oy = (t / across) * kSsimTile;
-    if (tid < (uint32_t)kSsimWin) {
-        float sum = 0;
-        for (int k = 0; k < kSsimWin; k++) sum += expf(-(float)((k - 5) * (k - 5)) / 4.5f);
-        g[tid] = expf(-(float)(((int)tid - 5) * ((int)tid - 5)) / 4.5f) / sum;
+    const uint32_t ox = (t % across) * kSsimCols, oy = (t / across) * rows;
+    const uint32_t rows_in = (oh - oy < rows ? oh - oy : rows) + (kSsimWin - 1);
+    const uint32_t X = ox + lane < Wj ? ox + lane : Wj - 1;  // (columns past the picture only reach positions past it)
+    const uint32_t pitch = W * C;
+    const size_t at = out_off[i] + (size_t)(oy << j) * pitch + (size_t)(X << j) * C;
+    const uint8_t *A = pa + at, *B = pb + at;
+    const bool last = j == M - 1;
+    float sum = 0.f;
+    switch (j) {
+        case 0: sum = ssim_strip<C, 0>(A, B, pitch, rows_in, ox, ow, last, &buf[wave], lane); break;
+        case 1: sum = ssim_strip<C, 1>(A, B, pitch, rows_in, ox, ow, last, &buf[wave], lane); break;
+        case 2: sum = ssim_strip<C, 2>(A, B, pitch, rows_in, ox, ow, last, &buf[wave], lane); break;
+        case 3: sum = ssim_strip<C, 3>(A, B, pitch, rows_in, ox, ow, last, &buf[wave], lane); break;
+        default: sum = ssim_strip<C, 4>(A, B, pitch, rows_in, ox, ow, last, &buf[wave], lane); break;
     }
-    // samples of this scale under the tile: means of 2^j x 2^j blocks, centred on 128
-    const uint32_t s = 1u << j;
-    const float inv_area = 1.0f / (float)(s * s);
-    const uint8_t* A = pa + out_off[i];
-    const uint8_t* B = pb + out_off[i];
-    for (uint32_t idx = tid; idx < (uint32_t)(kSsimIn * kSsimIn); idx += 256) {
-        const uint32_t sy = idx / kSsimIn, sx = idx % kSsimIn, X = ox + sx, Y = oy + sy;
-        float va = 0, vb = 0;
-        if (X < Wj && Y < Hj) {
-            uint32_t a0 = 0, a1 = 0, a2 = 0, b0 = 0, b1 = 0, b2 = 0;
-            for (uint32_t dy = 0; dy < s; dy++) {
-                const size_t row = ((size_t)(Y * s + dy) * W + (size_t)X * s) * (size_t)C;
-                if (C == 3) {
-                    for (uint32_t dx = 0; dx < 3 * s; dx += 3) {
-                        a0 += A[row + dx]; a1 += A[row + dx + 1]; a2 += A[row + dx + 2];
-                        b0 += B[row + dx]; b1 += B[row + dx + 1]; b2 += B[row + dx + 2];
-                    }
-                } else {
-                    for (uint32_t dx = 0; dx < s; dx++) { a0 += A[row + dx]; b0 += B[row + dx]; }
-                }
-            }
-            if (C == 3) {
-                va = (0.299f * (float)a0 + 0.587f * (float)a1 + 0.114f * (float)a2) * inv_area - 128.0f;
-                vb = (0.299f * (float)b0 + 0.587f * (float)b1 + 0.114f * (float)b2) * inv_area - 128.0f;
-            } else {
-                va = (float)a0 * inv_area - 128.0f;
-                vb = (float)b0 * inv_area - 128.0f;
-            }
-        }
-        sa[sy][sx] = va; sb[sy][sx] = vb;
-    }
-    __syncthreads();
-    // 11 taps along the rows: weighted sums of a, b, a*a, b*b, a*b
-    for (uint32_t idx = tid; idx < (uint32_t)(kSsimIn * kSsimTile); idx += 256) {
-        const uint32_t y = idx / kSsimTile, x = idx % kSsimTile;
-        float ma = 0, mb = 0, aa = 0, bb = 0, ab = 0;
 #pragma unroll
-        for (int k = 0; k < kSsimWin; k++) {
-            const float w = g[k], va = sa[y][x + k], vb = sb[y][x + k];
-            ma += w * va; mb += w * vb; aa += w * va * va; bb += w * vb * vb; ab += w * va * vb;
-        }
-        hp[0][y][x] = ma; hp[1][y][x] = mb; hp[2][y][x] = aa; hp[3][y][x] = bb; hp[4][y][x] = ab;
-    }
-    __syncthreads();
-    // 11 taps down the columns, then the two terms at every window position inside the picture
-    const float C1 = 6.5025f, C2 = 58.5225f;
-    float sum_cs = 0, sum_lcs = 0;
-    for (uint32_t idx = tid; idx < (uint32_t)(kSsimTile * kSsimTile); idx += 256) {
-        const uint32_t y = idx / kSsimTile, x = idx % kSsimTile;
-        if (ox + x >= ow || oy + y >= oh) continue;
-        float ma = 0, mb = 0, aa = 0, bb = 0, ab = 0;
-#pragma unroll
-        for (int k = 0; k < kSsimWin; k++) {
-            const float w = g[k];
-            ma += w * hp[0][y + k][x]; mb += w * hp[1][y + k][x];
-            aa += w * hp[2][y + k][x]; bb += w * hp[3][y + k][x]; ab += w * hp[4][y + k][x];
-        }
-        const float var_a = aa - ma * ma, var_b = bb - mb * mb, cov = ab - ma * mb;
-        const float mua = ma + 128.0f, mub = mb + 128.0f;
-        const float lum = (2.0f * mua * mub + C1) / (mua * mua + mub * mub + C1);
-        const float cs = (2.0f * cov + C2) / (var_a + var_b + C2);
-        sum_cs += cs; sum_lcs += lum * cs;
-    }
-    for (int d = 32; d > 0; d >>= 1) { sum_cs += __shfl_down(sum_cs, d); sum_lcs += __shfl_down(sum_lcs, d); }
-    if ((tid & 63) == 0) { red[tid >> 6][0] = sum_cs; red[tid >> 6][1] = sum_lcs; }
-    __syncthreads();
-    if (tid == 0)
-        part[(size_t)i * tiles_max + blockIdx.x] = make_float2(red[0][0] + red[1][0] + red[2][0] + red[3][0],
-                                                               red[0][1] + red[1][1] + red[2][1] + red[3][1]);
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+    if (lane == 0) part[(size_t)i * tiles_max + slot] = last ? make_float2(0.f, sum) : make_float2(sum, 0.f);
 }
 
 // One wavefront per picture: the scale means from the tile sums (in double, in a fixed order), then the
 // product of powers.  A picture too small for the window scores NaN.
 __global__ void __launch_bounds__(64) k_ssim_score(const uint32_t* __restrict__ dims, const float2* __restrict__ part, uint32_t tiles_max,
-                                                   float* __restrict__ scores) {
+                                                   uint32_t rows, float* __restrict__ scores) {
     const double weight[kSsimScales] = {0.0448, 0.2856, 0.3001, 0.2363, 0.1333};
     const uint32_t i = blockIdx.x, lane = threadIdx.x;
     const uint32_t W = dims[2 * i], H = dims[2 * i + 1];
@@ -154,7 +280,7 @@ __global__ void __launch_bounds__(64) k_ssim_score(const uint32_t* __restrict__ 
     uint32_t first = 0;
     for (int j = 0; j < M; j++) {
         uint32_t across;
-        const uint32_t cnt = ssim_tiles(W, H, j, &across);
+        const uint32_t cnt = ssim_tiles(W, H, j, rows, &across);
         double cs = 0, lcs = 0;
         for (uint32_t t = lane; t < cnt; t += 64) {
             const float2 p = part[(size_t)i * tiles_max + first + t];
