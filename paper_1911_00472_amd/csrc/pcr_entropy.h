@@ -29,21 +29,35 @@ namespace pcr {
 // canonical code the longer code words are the numerically largest ones, so all of them lie in
 // [limit8, 65536) when left-aligned in 16 bits; `lut2`, indexed by the distance from limit8
 // scaled to 128 entries, resolves every long code that owns at least one whole entry, and the
-// canonical limits resolve the rest.  An entry is (length << 8) | symbol; 0 means "not here".
+// canonical limits resolve the rest (of a photograph's tables under one symbol in 10 000).  The two look-ups lie one
+// behind the other, so that a lane picks its index into either and reads once.  An entry (code_entry) is what a decoder
+// needs of the symbol, taken apart; 0 means "not here".
 // ---------------------------------------------------------------------------------------
 struct AcTab {
     uint16_t lut[256];
-    uint16_t lut2[128];
+    uint16_t lut2[128];         // (right behind lut)
     uint32_t limit[9];          // limit[L-8]: first 16-bit-left-aligned code value NOT of length <= L (L = 8..16)
     uint16_t valptr[8];         // valptr[L-9]: index in huffval of the first code of length L
     uint32_t sh2;               // lut2 index = (code16 - limit[0]) >> sh2
     uint8_t huffval[256];
-    uint32_t pad;
+    uint32_t pad[2];            // (what comes before lutp is copied in 16-byte pieces)
     // the 8-bit look-up again, pre-packed for the lanes of a window reader (see packed_entry): everything
     // of a symbol's packed word that does not depend on the bits after the code
     uint32_t lutp[256];
 };
-static_assert(sizeof(AcTab) == 1084 + 1024, "AcTab layout");
+static_assert(sizeof(AcTab) == 1088 + 1024 && sizeof(AcTab) % 16 == 0 && offsetof(AcTab, lut2) == 512, "AcTab layout");
+
+// An AC symbol with a code of `len` bits: bits 0..3 how many bits follow the code (the value of a coefficient, the length
+// of an end-of-band run), bits 4..7 the zeros ahead of the position it lands on (0 for an end of band), bits 8..12 len,
+// bit 13 end of band, bit 14 coefficient.
+constexpr uint32_t kCodeEob = 0x2000u, kCodeCoef = 0x4000u;
+PCR_HD uint32_t code_entry(uint32_t len, uint32_t sym) {
+    const uint32_t r = sym >> 4, s = sym & 15u;
+    if (s) return kCodeCoef | (len << 8) | sym;
+    return r == 15u ? (len << 8) | 0xF0u : kCodeEob | (len << 8) | r;
+}
+// ... and back: (length << 8) | symbol
+PCR_HD uint32_t entry_code(uint32_t e) { return (e & 0x1F00u) | ((e & kCodeEob) ? (e & 15u) << 4 : e & 255u); }
 
 struct DcTab {                  // DC symbols are categories 0..15
     uint8_t lut[256];           // (length << 4) | symbol for codes of <= 8 bits, 0xFF otherwise
@@ -91,7 +105,7 @@ PCR_HD void actab_build(AcTab* t, const uint8_t* bits_vals) {
                 t->huffval[k] = sym;
                 if (L <= 8) {
                     uint32_t first = code << (8 - L), span = 1u << (8 - L);
-                    for (uint32_t e = 0; e < span && first + e < 256; e++) t->lut[first + e] = (uint16_t)((L << 8) | sym);
+                    for (uint32_t e = 0; e < span && first + e < 256; e++) t->lut[first + e] = (uint16_t)code_entry((uint32_t)L, sym);
                 }
             }
             code++; k++;
@@ -113,7 +127,7 @@ PCR_HD void actab_build(AcTab* t, const uint8_t* bits_vals) {
                 uint64_t c = (uint64_t)code << (16 - L);
                 if (c >= lim8 && c < 65536) {
                     uint32_t first = ((uint32_t)c - lim8) >> sh2, span = 1u << (16 - L - sh2);
-                    for (uint32_t e = 0; e < span && first + e < 128; e++) t->lut2[first + e] = (uint16_t)((L << 8) | bits_vals[16 + k]);
+                    for (uint32_t e = 0; e < span && first + e < 128; e++) t->lut2[first + e] = (uint16_t)code_entry((uint32_t)L, bits_vals[16 + k]);
                 }
             }
             code++; k++;
@@ -162,7 +176,7 @@ PCR_HD uint32_t ac_long_code(const AcTab* t, uint32_t win) {
     if (c16 < lim8) return 0;
     const uint32_t i2 = (c16 - lim8) >> t->sh2;
     uint32_t e = i2 < 128 ? t->lut2[i2] : 0;
-    if (e) return e;
+    if (e) return entry_code(e);
     for (int L = 9; L <= 16; L++) {
         if (c16 < t->limit[L - 8]) {
             uint32_t idx = t->valptr[L - 9] + ((c16 - t->limit[L - 9]) >> (16 - L));
@@ -173,7 +187,7 @@ PCR_HD uint32_t ac_long_code(const AcTab* t, uint32_t win) {
 }
 PCR_HD uint32_t ac_code(const AcTab* t, uint32_t win) {
     uint32_t e = t->lut[win >> 24];
-    return e ? e : ac_long_code(t, win);
+    return e ? entry_code(e) : ac_long_code(t, win);
 }
 // DC: returns (length << 4) | category, or 0 if it is no code (a valid entry is never 0: length >= 1)
 PCR_HD uint32_t dc_code(const DcTab* t, uint32_t win) {
@@ -264,7 +278,7 @@ PCR_HD uint32_t finish_packed(uint32_t p, uint32_t win, bool first) {
 }
 // fills lutp from lut: entry i by lane (i mod nlanes); call with every lane of the workgroup, after lut is complete
 PCR_HD void actab_pack(AcTab* t, bool first, uint32_t lane, uint32_t nlanes) {
-    for (uint32_t i = lane; i < 256; i += nlanes) t->lutp[i] = packed_entry(t->lut[i], first);
+    for (uint32_t i = lane; i < 256; i += nlanes) t->lutp[i] = packed_entry(entry_code(t->lut[i]), first);
 }
 
 // packed DC word: difference (16 bits, signed) << 16 | total bits (6) << 8 | category (4)
@@ -921,9 +935,18 @@ PCR_HD uint64_t band_mask(int Ss, int Se) { return ((Se >= 63) ? ~0ull : ((1ull 
 // at w * blocks + b): every kernel that writes a word for consecutive blocks then writes whole lines (records of five
 // words per block, of which a kernel writes two or three, were measured to cost 1.7 - 2.4 times the bytes in partial
 // sectors); what the consumers of a finished scan need (the replay of the refinement on the coefficients) is the first
-// three words.
+// three words.  On the device the first two arrays are one of pairs, kRefNz and kRefSign of a block side by side: the
+// lane decoder, which knows both at the end of a block, writes them with one 16-byte store, and the replay reads them with
+// one load.
 constexpr int kRefNz = 0, kRefSign = 1, kRefPlus = 2, kRefStart = 3, kRefHist = 4, kRefWords = 5;
-PCR_HD size_t ref_word(int w, size_t blk, size_t nblk) { return (size_t)w * nblk + blk; }
+PCR_HD size_t ref_word(int w, size_t blk, size_t nblk) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (w <= kRefSign) return 2 * blk + (size_t)w;
+#endif
+    return (size_t)w * nblk + blk;
+}
+// u64 words of the records of a scan over a plane of nblk blocks (pairs are 16-byte aligned)
+PCR_HD uint64_t ref_words(uint64_t nblk) { return (nblk * kRefWords + 1) & ~1ull; }
 
 // History of a refinement scan: the positions of its band that are non-zero when it starts.  What the
 // AC first scans made non-zero is read back from the coefficient plane (one coefficient per lane, a ballot
@@ -945,7 +968,7 @@ struct HistWords {                                            // one block's his
 PCR_HD HistWords hist_fetch(const HistPlanes& hp, uint32_t blk, uint32_t lane) {
     HistWords w;
     static_assert(kRefNz == 0, "the words that become history are a scan's first array");
-    const uint32_t off = blk * 8;                             // (32-bit offsets: a plane has far fewer than 2^29 blocks)
+    const uint32_t off = (uint32_t)ref_word(kRefNz, blk, 0) * 8;   // (32-bit offsets: a plane has fewer than 2^26 blocks)
 #if defined(__HIP_DEVICE_COMPILE__)
     w.half = 0;
     if (hp.n > 0) {
@@ -1098,9 +1121,9 @@ PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes
     // history registers: handing the words from one variable to the next would mean waiting for the fetch that is
     // still in flight.)
     auto one_block = [&](HistWords& hw, uint32_t& bcur) {
+        const uint32_t b = bcur;
         const uint64_t h = hist_combine(hw) & band;           // already non-zero
         const uint64_t z = h ^ band;                         // still zero
-        uint64_t* rec = recs + bcur;
         left--;
         fblk++; if (++fcol == mcu_w) { fcol = 0; fblk += row_skip; }
         bcur = fblk < last_blk ? fblk : last_blk;
@@ -1161,7 +1184,7 @@ PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes
             wr->consume(ncorr);
             eobrun--;
         }
-        rec[ref_word(kRefNz, 0, nblk)] = newm; rec[ref_word(kRefStart, 0, nblk)] = start; rec[ref_word(kRefHist, 0, nblk)] = h;   // (phase 2 and the refinement replay work on the same history)
+        recs[ref_word(kRefNz, b, nblk)] = newm; recs[ref_word(kRefStart, b, nblk)] = start; recs[ref_word(kRefHist, b, nblk)] = h;   // (phase 2 and the refinement replay work on the same history)
         bad |= wr->overrun_bit();
         left = bad ? 0 : left;                               // stop at the first damaged block
     };

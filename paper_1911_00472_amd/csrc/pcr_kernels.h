@@ -177,18 +177,18 @@ PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t l
     for (uint32_t e = lane; e < 256; e += 64) {
         const uint32_t f = canon_find(c, e << 8, 1, 8);
         const uint32_t v = f ? (f & 0xFF00u) | c->vals[f & 255u] : 0u;
-        t->lut[e] = (uint16_t)v;
+        t->lut[e] = (uint16_t)(f ? code_entry(f >> 8, v & 255u) : 0u);
         t->lutp[e] = packed_entry(v, first);
         t->huffval[e] = c->vals[e];
     }
     for (uint32_t e = lane; e < 128; e += 64) {
         const uint32_t c16 = lim8 + (e << sh2);
         const uint32_t f = c16 < 65536u ? canon_find(c, c16, 9, 16) : 0u;
-        t->lut2[e] = (uint16_t)((f && 16u - (f >> 8) >= sh2) ? (f & 0xFF00u) | c->vals[f & 255u] : 0u);
+        t->lut2[e] = (uint16_t)((f && 16u - (f >> 8) >= sh2) ? code_entry(f >> 8, c->vals[f & 255u]) : 0u);
     }
     if (lane < 9) t->limit[lane] = c->lim[8 + lane];
     if (lane < 8) t->valptr[lane] = (uint16_t)c->first[9 + lane];
-    if (lane == 0) { t->sh2 = sh2; t->pad = 0; }
+    if (lane == 0) t->sh2 = sh2;
 }
 // ... and dctab_build (only the first sixteen codes are DC categories).
 PCR_D void dctab_build_wave(DcTab* t, const CanonCode* c, uint32_t lane) {
@@ -598,24 +598,43 @@ PCR_D void lane_unit_setup(const DevRecord& R, const Unit& un, const uint32_t* _
 constexpr int kLaneTabs = 8;
 struct LaneJob { uint32_t first, count, ntab; uint32_t key[kLaneTabs]; };
 
-// The AC tables of a job into LDS (call with every lane of the wavefront) and the slot of the table of scan `key`
-// (>= kLaneTabs: not among the job's -- the host never makes such a job).
-PCR_D uint32_t lane_table_slots(const DevRecord& R, const LaneJob& job, uint32_t key, bool mine, uint32_t (*tabs)[kLaneTabWords]) {
-    const uint32_t t = threadIdx.x;
-    uint32_t slot = ~0u;
+// The AC tables of a job on their way into LDS: fetch with every lane of the wavefront, put once the loads may be waited for
+// (the pieces of all tables are under way together, and the set-up of the units beside them).
+struct LaneTables {
+    uint4 v[kLaneTabs], w[kLaneTabs];
+    PCR_D void fetch(const DevRecord& R, const LaneJob& job) {
+        const uint32_t t = threadIdx.x;
+        static_assert(kLaneTabPieces > kEntropyLanes && kLaneTabPieces <= 2 * kEntropyLanes, "two pieces per lane");
 #pragma unroll
-    for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) {
-        if (sl < job.ntab) {                                  // (the same for all lanes)
+        for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) {
             const uint32_t k = job.key[sl];
-            if (k < R.n * R.G) {
-                const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.tabs[R.tab_idx[k]]);
-                for (uint32_t e = t; e < kLaneTabWords; e += kEntropyLanes) tabs[sl][e] = src[e];
-                if (k == key) slot = sl;
+            v[sl] = w[sl] = uint4{0, 0, 0, 0};
+            if (sl < job.ntab && k < R.n * R.G) {             // (the same for all lanes)
+                const uint4* src = reinterpret_cast<const uint4*>(&R.tabs[R.tab_idx[k]]);
+                v[sl] = src[t];
+                if (t < kLaneTabPieces - kEntropyLanes) w[sl] = src[kEntropyLanes + t];
             }
         }
     }
-    __syncthreads();
-    return mine ? slot : ~0u;
+    PCR_D void put(const LaneJob& job, uint4 (*tabs)[kLaneTabPieces]) const {
+        const uint32_t t = threadIdx.x;
+#pragma unroll
+        for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) {
+            if (sl < job.ntab) {
+                tabs[sl][t] = v[sl];
+                if (t < kLaneTabPieces - kEntropyLanes) tabs[sl][kEntropyLanes + t] = w[sl];
+            }
+        }
+        __syncthreads();
+    }
+};
+// the slot of the table of scan `key` (>= kLaneTabs: not among the job's -- the host never makes such a job)
+PCR_D uint32_t lane_table_slot(const DevRecord& R, const LaneJob& job, uint32_t key) {
+    uint32_t slot = ~0u;
+#pragma unroll
+    for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++)
+        if (sl < job.ntab && job.key[sl] == key && key < R.n * R.G) slot = sl;
+    return slot;
 }
 
 // SHAPE: which DC decoder (dc_shape) the units of this launch take; the host sorts the units by it.
@@ -687,17 +706,20 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_first(DevRecord R, const U
 // which the memory pipeline takes requests.
 __global__ void __launch_bounds__(kEntropyLanes) k_ac_first_lanes(DevRecord R, const Unit* __restrict__ units, const LaneJob* __restrict__ jobs,
         const uint32_t* __restrict__ clean32) {
-    __shared__ uint32_t tabs[kLaneTabs][kLaneTabWords];
+    __shared__ uint4 tabs[kLaneTabs][kLaneTabPieces];
     __shared__ LaneRing rings;
     const LaneJob job = jobs[blockIdx.x];
     const uint32_t t = threadIdx.x;
     const bool mine = t < job.count;
     Unit un = units[job.first + (mine ? t : 0u)];
     const uint32_t key = un.img * R.G + un.scan;
-    const uint32_t slot = lane_table_slots(R, job, key, mine, tabs);
+    LaneTables staged;
+    staged.fetch(R, job);
+    const uint32_t slot = lane_table_slot(R, job, key);
     LaneUnit U;
     U.ok = false;
     if (mine && slot < (uint32_t)kLaneTabs) lane_unit_setup(R, un, clean32, &U);
+    staged.put(job, tabs);
     if (!U.ok) return;
     U.tab = reinterpret_cast<const LaneTab*>(&tabs[slot][0]);
     const int rc = lane_decode_ac_first(U, &rings, t);
@@ -708,7 +730,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_first_lanes(DevRecord R, c
 // launch, k_refine_deal must follow.
 __global__ void __launch_bounds__(kEntropyLanes) k_ac_refine_lanes(DevRecord R, const Unit* __restrict__ units, const LaneJob* __restrict__ jobs,
         const uint32_t* __restrict__ clean32) {
-    __shared__ uint32_t tabs[kLaneTabs][kLaneTabWords];
+    __shared__ uint4 tabs[kLaneTabs][kLaneTabPieces];
     __shared__ LaneRing rings;
     __shared__ LaneHistRing hring;
     const LaneJob job = jobs[blockIdx.x];
@@ -716,10 +738,13 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_refine_lanes(DevRecord R, 
     const bool mine = t < job.count;
     Unit un = units[job.first + (mine ? t : 0u)];
     const uint32_t key = un.img * R.G + un.scan;
-    const uint32_t slot = lane_table_slots(R, job, key, mine, tabs);
+    LaneTables staged;
+    staged.fetch(R, job);
+    const uint32_t slot = lane_table_slot(R, job, key);
     LaneUnit U;
     U.ok = false;
     if (mine && slot < (uint32_t)kLaneTabs) lane_unit_setup(R, un, clean32, &U);
+    staged.put(job, tabs);
     if (!U.ok) return;
     U.tab = reinterpret_cast<const LaneTab*>(&tabs[slot][0]);
     const int rc = lane_decode_ac_refine(U, R.masks + R.mask_off[key], U.plane_elems >> 6, &rings, &hring, t);
@@ -913,7 +938,7 @@ __global__ void __launch_bounds__(256) k_refine_history(DevRecord R, const Refin
     const ScanDesc* first = sd->nhist ? &R.scan[(size_t)a.img * R.G + sd->hist[0]] : sd;
     const bool from_records = sd->nhist && first->Ss == sd->Ss && first->Se == sd->Se;
     if (from_records) {
-        if (blk < plane) m = R.masks[R.mask_off[(size_t)a.img * R.G + sd->hist[0]] + (size_t)kRefHist * plane + blk];
+        if (blk < plane) m = R.masks[R.mask_off[(size_t)a.img * R.G + sd->hist[0]] + ref_word(kRefHist, blk, plane)];
     } else {
         size_t po = 0;
         for (int q = 0; q < c; q++) po += (size_t)img->bw[q] * img->bh[q] * 64;
@@ -937,8 +962,8 @@ __global__ void __launch_bounds__(256) k_refine_history(DevRecord R, const Refin
     if (blk >= plane) return;
     if (!from_records) m = *reinterpret_cast<const uint64_t*>(&bytes[wave][lane * 8]);
     for (uint32_t q = 0; q < sd->nhist && q < (uint32_t)kMaxHist; q++)
-        m |= R.masks[R.mask_off[(size_t)a.img * R.G + sd->hist[q]] + (size_t)kRefNz * plane + blk];
-    R.masks[R.mask_off[ig] + (size_t)kRefHist * plane + blk] = m & band_mask(sd->Ss, sd->Se);
+        m |= R.masks[R.mask_off[(size_t)a.img * R.G + sd->hist[q]] + ref_word(kRefNz, blk, plane)];
+    R.masks[R.mask_off[ig] + ref_word(kRefHist, blk, plane)] = m & band_mask(sd->Ss, sd->Se);
 }
 // grid: one workgroup per tile (chunks of the blocks the image covers)
 __global__ void __launch_bounds__(256) k_refine_deal(DevRecord R, const RefineScan* __restrict__ rs, const RefineTile* __restrict__ tiles) {
@@ -947,8 +972,8 @@ __global__ void __launch_bounds__(256) k_refine_deal(DevRecord R, const RefineSc
     const RefineScan a = rs[tile.entry];
     size_t ig; uint32_t blk, plane;
     if (!refine_block_of_lane(R, a, tile.chunk, &ig, &blk, &plane)) return;
-    uint64_t* rec = R.masks + R.mask_off[ig] + blk;
-    rec[(size_t)kRefPlus * plane] = deal_bits(rec[(size_t)kRefPlus * plane], rec[(size_t)kRefHist * plane]);
+    uint64_t* rec = R.masks + R.mask_off[ig];
+    rec[ref_word(kRefPlus, blk, plane)] = deal_bits(rec[ref_word(kRefPlus, blk, plane)], rec[ref_word(kRefHist, blk, plane)]);
 }
 
 __global__ void __launch_bounds__(256) k_refine_blocks(DevRecord R, const RefineScan* __restrict__ rs, const RefineTile* __restrict__ tiles) {
@@ -974,14 +999,13 @@ __global__ void __launch_bounds__(256) k_refine_blocks(DevRecord R, const Refine
     const uint32_t bw = img->bw[c];
     const size_t blk = (size_t)(b / cw) * bw + (b % cw);
     const size_t plane = (size_t)bw * img->bh[c];
-    uint64_t* mk = R.masks + R.mask_off[ig];
-    uint64_t* rec = mk + blk;                                // (word w of the block: rec[w * plane])
-    const uint64_t h = rec[kRefHist * plane];                // the history phase 1 worked on
+    uint64_t* rec = R.masks + R.mask_off[ig];
+    const uint64_t h = rec[ref_word(kRefHist, blk, plane)];  // the history phase 1 worked on
     const uint32_t ivl = sd->ri ? b / sd->ri : 0;
     const uint32_t* words = reinterpret_cast<const uint32_t*>(R.clean + clean_base(sd->data_off));
     uint64_t sgn, plus;
-    refine_block(words, R.ivl_start[R.slot_base[ig] + ivl], rec[kRefStart * plane], &tab, h, rec[kRefNz * plane], sd->Ss, sd->Se, &sgn, &plus);
-    rec[kRefSign * plane] = sgn; rec[kRefPlus * plane] = plus;
+    refine_block(words, R.ivl_start[R.slot_base[ig] + ivl], rec[ref_word(kRefStart, blk, plane)], &tab, h, rec[ref_word(kRefNz, blk, plane)], sd->Ss, sd->Se, &sgn, &plus);
+    rec[ref_word(kRefSign, blk, plane)] = sgn; rec[ref_word(kRefPlus, blk, plane)] = plus;
 }
 
 // --------------------------------------------------------------------------------------
@@ -1076,8 +1100,8 @@ __global__ void __launch_bounds__(256) k_apply(DevRecord R, const ApplyUnit* __r
                 if (k != 0) continue;
                 if (dc_refinement_bit(R, S, row, col, hs, vs, covered)) v |= (int16_t)(1 << S.Al);
             } else if (k != 0 && covered && k >= S.Ss && k <= S.Se) {
-                const uint64_t* rec = R.masks + S.mask_off + b;
-                v = refine_apply(v, k, rec[kRefNz * nblk], rec[kRefSign * nblk], rec[kRefPlus * nblk], S.Al);
+                const uint64_t* rec = R.masks + S.mask_off;
+                v = refine_apply(v, k, rec[ref_word(kRefNz, b, nblk)], rec[ref_word(kRefSign, b, nblk)], rec[ref_word(kRefPlus, b, nblk)], S.Al);
             }
         }
         if (v != v0) pl[idx] = v;
@@ -1333,8 +1357,9 @@ PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8],
         } else if (B.covered) {
             // the three words of the block's record: positions that become non-zero, their signs, positions
             // whose magnitude grows (all inside the scan's band)
-            const uint64_t* rec = R.masks + S.mask_off + B.b;
-            const uint64_t nzm = rec[kRefNz * (size_t)B.nblk], sgm = rec[kRefSign * (size_t)B.nblk], plm = rec[kRefPlus * (size_t)B.nblk];
+            const uint64_t* rec = R.masks + S.mask_off;
+            const ulonglong2 ns = *reinterpret_cast<const ulonglong2*>(rec + ref_word(kRefNz, B.b, B.nblk));
+            const uint64_t nzm = ns.x, sgm = ns.y, plm = rec[ref_word(kRefPlus, B.b, B.nblk)];
             // A position either grows (it was non-zero: + 2^Al with its own sign) or is new (it was zero: +- 2^Al by the
             // sign bit) or stays: one step with one sign, taken from the coefficient or from the record.
             const uint64_t anym = nzm | plm, negm = nzm & ~sgm;

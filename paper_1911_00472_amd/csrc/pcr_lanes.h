@@ -29,11 +29,14 @@ struct uint2 { uint32_t x, y; };
 // true if `v` holds in any lane of the wavefront that is still in the loop
 PCR_HD bool any_lane(bool v) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    return __any(v) != 0;
+    return __builtin_amdgcn_ballot_w64(v) != 0;
 #else
     return v;
 #endif
 }
+// the same for what hardly ever holds: the branch behind it is laid out of the way, so that the wavefront runs past it (a
+// taken branch costs it the fetch of the instructions it lands on, once per trip of a loop that is little else)
+#define PCR_RARELY(v) __builtin_expect(any_lane(v), 0)
 // Waits here for every load issued so far (device).  The wait the compiler would otherwise place at a loaded value's
 // first use -- or at the first re-use of its register -- can land inside the symbol loop, and a wait for a load is a wait
 // for every store issued before it as well: the loop would stand still for the round trip of its own stores in every
@@ -43,15 +46,6 @@ PCR_HD void loads_arrived() {
     __builtin_amdgcn_s_waitcnt(0x0F70);
 #endif
 }
-// bits [n, n + 32) of hi:lo counted from hi's top bit, n in 1..31 (one instruction on the device)
-PCR_HD uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t n) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return __builtin_amdgcn_alignbit(hi, lo, 32u - n);
-#else
-    return (uint32_t)((((uint64_t)hi << 32) | lo) >> (32u - n));
-#endif
-}
-
 // The part of an AcTab (pcr_entropy.h) a lane decoder reads: everything before the pre-packed look-up of the window
 // readers.  A wavefront keeps one per scan its lanes decode in LDS, and LDS is what bounds the number of resident
 // wavefronts.
@@ -62,9 +56,10 @@ struct LaneTab {
     uint16_t valptr[8];
     uint32_t sh2;
     uint8_t huffval[256];
+    uint32_t pad[2];
 };
-constexpr uint32_t kLaneTabWords = sizeof(LaneTab) / 4;
-static_assert(sizeof(LaneTab) == 1080 && offsetof(AcTab, lutp) >= sizeof(LaneTab) && offsetof(AcTab, lut2) == offsetof(LaneTab, lut2) &&
+constexpr uint32_t kLaneTabPieces = sizeof(LaneTab) / 16;     // 68
+static_assert(sizeof(LaneTab) == 1088 && offsetof(AcTab, lutp) >= sizeof(LaneTab) && offsetof(AcTab, lut2) == offsetof(LaneTab, lut2) &&
               offsetof(AcTab, limit) == offsetof(LaneTab, limit) && offsetof(AcTab, valptr) == offsetof(LaneTab, valptr) &&
               offsetof(AcTab, sh2) == offsetof(LaneTab, sh2) && offsetof(AcTab, huffval) == offsetof(LaneTab, huffval), "a LaneTab is the head of an AcTab");
 
@@ -80,147 +75,220 @@ struct LaneUnit {
     bool ok;
 };
 
-// A lane's view of its stream.  The next unread bit is the top bit of `hi`; hi:lo hold `have` valid bits (always more
-// than 32 after top_up(), so that hi is a full look-ahead window; a symbol takes 31 at most).  A symbol's bits leave
-// through a funnel shift (one instruction where a 64-bit shift of the pair and the copies around it are three or four).
+// The loops below are bound by how many instructions stand between one symbol and the next: a lone wavefront issues one
+// every eight cycles or so, whatever it is, and a launch takes as long as its longest unit.  Hence the style: conditions
+// are kept as sign bits and masks and merged with and / or / bit-field inserts, which are one instruction each, where a
+// comparison costs the comparison, a wait for its result and scalar instructions that combine it with others; whatever is
+// rare sits behind a branch that is the same for the whole wavefront.
+
+// bits [off, off + width) of v, width 0 included (one instruction on the device; off and width below 32)
+PCR_HD uint32_t bit_range(uint32_t v, uint32_t off, uint32_t width) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ubfe(v, off, width);
+#else
+    return width ? (v >> (off & 31u)) & ((1u << width) - 1u) : 0u;
+#endif
+}
+// all ones if v is negative as a signed number, else zero; the same of one bit of v; a where the mask is ones, b where it
+// is zero
+PCR_HD uint32_t sign_mask(uint32_t v) { return (uint32_t)((int)v >> 31); }
+PCR_HD uint32_t bit_mask(uint32_t v, uint32_t bit) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__builtin_amdgcn_sbfe((int)v, bit, 1);
+#else
+    return (uint32_t)((int)(v << (31u - bit)) >> 31);
+#endif
+}
+// v - 1, or 0
+PCR_HD uint32_t less_one(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_elementwise_sub_sat(v, 1u);
+#else
+    return v ? v - 1u : 0u;
+#endif
+}
+PCR_HD uint32_t by_mask(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
+
+// A lane's view of its stream: three words of it (w0, w1 and the one after them), and one counter.  With p the position
+// of the next unread bit, counted from base16's first bit, and m = p + 63, the counter is kept as n = ~m: then the word
+// after w1 has index m >> 5, n (its low five bits) is the amount a funnel shift of w0:w1 takes to put the unread bits at
+// the top (w0 ends with the bit before p at the latest, so that the shift is never 32), and the words move on by one where
+// bit 5 of n changes.  A symbol's bits are consumed by one subtraction; the word after w1 is read ahead of the trip that
+// needs it.
 //
 // Words come from a ring of kRingWords words per lane in LDS, not from memory: the counter a wavefront waits on for a
-// load is shared by all its lanes and returns in order, so a loop in which some lane or other fetches a word in every
+// load is shared by its lanes and returns in order, so a loop in which some lane or other fetches a word in every
 // trip waits for memory in every trip.  The ring is filled for all lanes at once (refill: 16-byte chunks, as many as
 // each lane has room for) whenever some lane is about to run short (short_of), every few dozen symbols; between two
-// refills the loop reads no memory at all.
-constexpr uint32_t kRingWords = 16, kRingChunks = kRingWords / 4;
-struct LaneRing { uint4 chunk[kRingChunks][64]; };           // chunk c of lane i: its words 4c .. 4c+3 (mod kRingWords)
+// refills the loop reads no memory at all.  Past the unit's end the chunks repeat, so a lane that follows damaged data
+// there reads nothing it should not.
+constexpr uint32_t kRingWords = 16;
+struct LaneRing { uint32_t w[kRingWords][64]; };             // word i of lane l: row 15 - (i & 15), read without bank conflicts
 
 struct LaneStream {
     const uint4* base16;          // 16-byte aligned address at or before the unit's first word; word indices count from here
-    uint32_t* ring;               // this lane's slot of chunk 0, as words (LDS); chunk c lies 256 c words further on
-    uint32_t wi, wr;              // next word to enter the buffer; the ring holds the words before wr (a multiple of 4)
-    uint32_t hi, lo; int have;
-    int remain;                   // bits of the unit not consumed yet (negative: the decoder ran past the end)
-    PCR_HD uint32_t ring_word(uint32_t w) const { return ring[((w >> 2) & (kRingChunks - 1)) * 256u + (w & 3u)]; }
-    // Call with every lane that is still decoding.
+    uint32_t* ring;               // this lane's column of the ring (LDS)
+    uint32_t n;                   // (see above)
+    uint32_t past;                // n when the unit's bits are used up: n below it (as a signed difference) is too far
+    uint32_t wr;                  // the ring holds the words before this one (a multiple of 4)
+    uint32_t last;                // last chunk of 16 bytes read
+    uint32_t w0, w1, w2;
+    uint4 v0, v1, v2, v3;         // the chunks behind wr, under way or arrived
+    PCR_HD uint32_t next_word() const { return ring[bit_range(n, 5, 4) * 64u]; }
+    // Call with every lane that is still decoding.  The chunks written were fetched when the ring was filled the last time,
+    // and the next ones set out here: a refill waits for memory only if the ring ran dry sooner than memory answers.
     PCR_HD void refill() {
-        const uint32_t room = (kRingWords - (wr - wi)) >> 2;  // whole chunks that fit
-        const uint4* src = base16 + (wr >> 2);
-        static_assert(kRingChunks == 4, "the chunks are spelled out (an array indexed in a loop ends up in scratch memory)");
-        const uint4 v0 = src[0], v1 = src[1], v2 = src[2], v3 = src[3];   // (all four: the data stays readable well past a unit's end)
+        const uint32_t room = (kRingWords - (wr - (~n >> 5))) >> 2, c = wr >> 2;   // whole chunks that fit
+        static_assert(kRingWords == 16, "the chunks are spelled out (an array indexed in a loop ends up in scratch memory)");
         loads_arrived();
-        const uint32_t c0 = wr >> 2;
-        if (room > 0) *reinterpret_cast<uint4*>(ring + ((c0 + 0) & 3u) * 256u) = v0;
-        if (room > 1) *reinterpret_cast<uint4*>(ring + ((c0 + 1) & 3u) * 256u) = v1;
-        if (room > 2) *reinterpret_cast<uint4*>(ring + ((c0 + 2) & 3u) * 256u) = v2;
-        if (room > 3) *reinterpret_cast<uint4*>(ring + ((c0 + 3) & 3u) * 256u) = v3;
+        if (room > 0) put(c, v0);
+        if (room > 1) put(c + 1u, v1);
+        if (room > 2) put(c + 2u, v2);
+        if (room > 3) put(c + 3u, v3);
         wr += room * 4;
+        fetch();
     }
-    PCR_HD bool short_of(uint32_t words) const { return wr - wi < words; }
+    PCR_HD void fetch() {
+        const uint32_t c = wr >> 2;
+        v0 = chunk(c); v1 = chunk(c + 1u); v2 = chunk(c + 2u); v3 = chunk(c + 3u);
+    }
+    PCR_HD uint4 chunk(uint32_t c) const { return base16[c < last ? c : last]; }
+    PCR_HD void put(uint32_t c, const uint4& v) {
+        uint32_t* r = ring + (kRingWords - 4u - (c & 3u) * 4u) * 64u;
+        r[192] = v.x; r[128] = v.y; r[64] = v.z; r[0] = v.w;
+    }
+    // the value of n below which fewer than `words` words lie in the ring behind the one read ahead
+    PCR_HD uint32_t low_water(uint32_t words) const { return ~(32u * (wr - 1u - words)); }
     PCR_HD void init(const uint32_t* words, uint32_t bit0, uint32_t bit1, LaneRing* rings, uint32_t lane) {
         const uint32_t* first = words + (bit0 >> 5);
         const uint32_t before = (uint32_t)(reinterpret_cast<uintptr_t>(first) & 15u) >> 2;   // words between the 16-byte boundary and the unit's first
         base16 = reinterpret_cast<const uint4*>(first - before);     // (pointer arithmetic: the address stays a global one)
-        ring = reinterpret_cast<uint32_t*>(&rings->chunk[0][lane]);
-        wi = before; wr = 0;
-        refill();                                             // (wi < 4: all four chunks)
-        const uint32_t off = bit0 & 31;
-        const uint64_t buf = ((((uint64_t)ring_word(wi)) << 32) | ring_word(wi + 1)) << off;
-        hi = (uint32_t)(buf >> 32); lo = (uint32_t)buf;
-        have = 64 - (int)off; wi += 2;
-        remain = (int)(bit1 - bit0);
+        ring = &rings->w[0][lane];
+        const uint32_t m = before * 32u + (bit0 & 31u) + 63u;
+        past = ~(m + (bit1 - bit0));
+        last = (m + (bit1 - bit0)) >> 7;                      // (the chunk of the last bit, or the one behind it: slack follows the data)
+        n = ~0u; wr = 0;
+        fetch();
+        refill();                                             // (all four chunks)
+        n = ~m;
+        const uint32_t i = m >> 5;                            // 1 .. 5
+        w0 = ring[(15u - ((i - 2u) & 15u)) * 64u]; w1 = ring[(15u - ((i - 1u) & 15u)) * 64u]; w2 = next_word();   // (i = 1: w0 is not looked at)
     }
-    PCR_HD void top_up() {
-        if (have <= 32) {                                     // (then lo is empty)
-            const uint64_t t = (uint64_t)ring_word(wi) << (32 - have);
-            hi |= (uint32_t)(t >> 32); lo = (uint32_t)t;
-            have += 32; wi++;
-        }
+    PCR_HD uint32_t window() const {
+#if defined(__HIP_DEVICE_COMPILE__)
+        return __builtin_amdgcn_alignbit(w0, w1, n);
+#else
+        return (uint32_t)((((uint64_t)w0 << 32) | w1) >> (n & 31u));
+#endif
     }
-    PCR_HD uint32_t window() const { return hi; }
-    PCR_HD void consume(uint32_t n) {                          // n in 1..31
-        hi = funnel(hi, lo, n);
-        lo <<= n; have -= (int)n; remain -= (int)n;
+    PCR_HD void consume(uint32_t bits) {                       // bits in 0..31
+        const uint32_t t = n - bits, next = bit_mask(t ^ n, 5);   // (the word index has changed where bit 5 has)
+        w0 = by_mask(next, w1, w0); w1 = by_mask(next, w2, w1);
+        n = t;
+        w2 = next_word();
     }
-    PCR_HD void consume_any(uint32_t n) {                      // n in 0..31
-        hi = n ? funnel(hi, lo, n) : hi;
-        lo <<= n; have -= (int)n; remain -= (int)n;
-    }
+    PCR_HD uint32_t beyond() const { return n - past; }        // negative once bits past the unit's end have been consumed
 };
 
-// A code of more than 8 bits.  Some lane of 64 meets one in most trips, so the common case is kept short: the second
-// look-up (pcr_entropy.h: indexed by the distance from the first long code, scaled to 128 entries) resolves every long
-// code that owns a whole entry; the few that do not go through the canonical limits -- limit[L - 8] is the first
-// left-aligned 16-bit value that is not a code of length <= L, so the length is 9 + the number of limits at or below
-// the code.  Returns (length << 8) | symbol, or 0 if it is no code.
-PCR_HD uint32_t lane_long_code(const LaneTab* t, uint32_t win) {
-    const uint32_t c16 = win >> 16, lim8 = t->limit[0];
-    const uint32_t i2 = (c16 - lim8) >> t->sh2;
-    const bool longer = c16 >= lim8;
-    uint32_t e = (longer && i2 < 128u) ? t->lut2[i2 & 127u] : 0u;
-    if (longer && e == 0) {
+// A lane's look-up of AC codes: the constants of its table in registers, the table itself in LDS.
+constexpr uint32_t kCodeBad = 0x8000u | kCodeEob;           // no code: an end of band without any bits, marked
+struct LaneLookup {
+    const LaneTab* tab;
+    uint32_t lim8, bias, sh2;
+    PCR_HD void init(const LaneTab* t) { tab = t; lim8 = t->limit[0]; sh2 = t->sh2; bias = lim8 - (256u << sh2); }
+    // The entry (code_entry) of the code at the head of the window, as the table has it (0: in neither look-up).  The index
+    // of either look-up is picked first, so one read of LDS serves codes of any length.
+    PCR_HD uint32_t entry(uint32_t win) const {
+        const uint32_t c16 = win >> 16;
+        const uint32_t i = c16 >= lim8 ? (c16 - bias) >> sh2 : win >> 24;
+        static_assert(offsetof(LaneTab, lut2) == 512, "lut2 lies right behind lut");
+        return reinterpret_cast<const uint16_t*>(tab)[i];
+    }
+    // ... and what to make of it: kCodeBad if there is no such code.  A decoder reads the entry of the next symbol as soon
+    // as it knows where that begins, does the rest of this symbol's work while LDS answers, and looks at it then.
+    PCR_HD uint32_t resolve(uint32_t e, uint32_t win) const {
+        if (PCR_RARELY(e == 0)) {
+#if defined(__HIP_DEVICE_COMPILE__)
+            asm volatile("");                                 // (keeps the two conditions from being merged into a longer one)
+#endif
+            if (e == 0) e = by_limits(win >> 16);
+        }
+        return e;
+    }
+    // A code neither look-up resolves: limit[L - 8] is the first left-aligned 16-bit value that is not a code of length <= L,
+    // so the length is 9 + the number of limits at or below the code.
+    PCR_HD uint32_t by_limits(uint32_t c16) const {
         uint32_t L = 9, below = lim8;
 #pragma unroll
         for (int q = 1; q <= 7; q++) {
-            const uint32_t lim = t->limit[q];
+            const uint32_t lim = tab->limit[q];
             const bool over = c16 >= lim;
             L += over ? 1u : 0u; below = over ? lim : below;
         }
-        const uint32_t idx = t->valptr[L - 9] + ((c16 - below) >> (16 - L));
-        const uint32_t sym = t->huffval[idx & 255u];
-        e = (c16 < t->limit[8] && idx < 256u) ? (L << 8) | sym : 0u;
+        const uint32_t idx = tab->valptr[L - 9] + ((c16 - below) >> (16 - L));
+        return (c16 >= lim8 && c16 < tab->limit[8] && idx < 256u) ? code_entry(L, tab->huffval[idx & 255u]) : kCodeBad;
     }
-    return e;
+};
+
+// The blocks [mcu0, mcu1) of a unit all lie inside its component's plane.
+PCR_HD bool lane_unit_inside(const LaneUnit& U) {
+    if (U.mcu0 >= U.mcu1 || U.mcu_w == 0 || U.bw < U.mcu_w) return false;
+    const uint32_t row = (U.mcu1 - 1) / U.mcu_w, col = (U.mcu1 - 1) - row * U.mcu_w;
+    return (uint64_t)row * U.bw + col < (U.plane_elems >> 6);
 }
 
 // AC first scan (one component, band Ss..Se, point transform Al) of one unit.  Every coefficient the unit's symbols
 // carry is stored (2 bytes); everything else in the plane was zero-filled before.  One symbol per trip, the three kinds
-// of symbol (coefficient after a run, sixteen zeros, end of band) told apart by selects.
+// of symbol (coefficient after a run, sixteen zeros, end of band) told apart by masks.  Damaged data sets the sign of
+// `bad` and is followed to the unit's last block (every store is inside the unit's blocks whatever the data say).
 PCR_HD int lane_decode_ac_first(const LaneUnit& U, LaneRing* rings, uint32_t lane) {
+    if (!lane_unit_inside(U)) return kEFormat;
     LaneStream st;
     st.init(U.words, U.bit0, U.bit1, rings, lane);
-    const uint32_t Ss = U.Ss, Se = U.Se, mcu_w = U.mcu_w;
+    LaneLookup code;
+    code.init(U.tab);
+    const uint32_t Ss = U.Ss, Se = U.Se, mcu_w = U.mcu_w, Al = U.Al;
+    int16_t* const plane = U.plane;
     uint32_t left = U.mcu1 - U.mcu0;                          // blocks of the unit not finished yet (the current one included)
-    const uint32_t row0 = U.mcu0 / mcu_w;
-    uint32_t col = U.mcu0 - row0 * mcu_w;
-    uint32_t base = (row0 * U.bw + col) * 64;                 // element index of the current block
+    const uint32_t row0 = U.mcu0 / mcu_w, col0 = U.mcu0 - row0 * mcu_w;
+    int in_row = (int)(mcu_w - col0);                         // blocks left in the row of blocks (the current one included)
+    uint32_t base = (row0 * U.bw + col0) * 64;                // element index of the current block
     const uint32_t row_skip = (U.bw - mcu_w) * 64;           // elements of the padded grid between two rows of the scan
     const float rcp_w = 1.0f / (float)mcu_w;
     uint32_t k = Ss, bad = 0;
+    uint32_t low = st.low_water(1);                           // (a trip takes one word at most)
+    uint32_t next_win = st.window(), next_e = code.entry(next_win);
     while (left != 0) {
-        if (any_lane(st.short_of(2))) st.refill();              // (a trip takes one word at most)
-        st.top_up();
-        const uint32_t win = st.window();
-        uint32_t e = U.tab->lut[win >> 24];
-        if (e == 0) e = lane_long_code(U.tab, win);           // a code longer than 8 bits, or none
-        bad |= e == 0 ? 1u : 0u;
-        e = e ? e : (1u << 8);                                // (no code: one bit, nothing else; the lane stops below)
-        const uint32_t len = e >> 8, r = (e >> 4) & 15u, s = e & 15u;
-        const bool coef = s != 0, eob = s == 0 && r != 15u;
-        const uint32_t nx = coef ? s : (eob ? r : 0u);        // appended bits: the value, or the length of an end-of-band run
-        const uint32_t extra = ((win << len) >> 1) >> (31u - nx);
-        st.consume(len + nx);
-        k += eob ? 0u : (coef ? r : 16u);                     // the position the symbol lands on (sixteen zeros: passes)
-        const uint32_t elem = base + k;
-        const bool inside = k <= Se;
-        if (coef && inside && elem < U.plane_elems) U.plane[elem] = (int16_t)((int16_t)extend(extra, (int)s) * (1 << U.Al));
-        bad |= (coef && !inside) ? 1u : 0u;                   // a coefficient beyond the band
-        bad |= st.remain < 0 ? 1u : 0u;                       // never walk beyond the unit's data
-        k += coef ? 1u : 0u;
-        const bool done = eob || k > Se;
-        uint32_t adv = eob ? (1u << r) + extra : 1u;          // blocks to move on by: this one and the rest of an end-of-band run
-        adv = adv < left ? adv : left;
-        adv = done ? adv : 0u;
-        left = bad ? 0u : left - adv;                         // stop at the first damaged block
-        col += adv; base += adv * 64; k = done ? Ss : k;
-        const bool wrap = col >= mcu_w;
-        col -= wrap ? mcu_w : 0u; base += wrap ? row_skip : 0u;
-        if (col >= mcu_w) {                                   // an end-of-band run over more than one row of blocks
-            uint32_t q = (uint32_t)((float)col * rcp_w);      // rows passed, estimated: off by less than 1 + col / 2^22
-            const uint32_t margin = 1u + (col >> 22);
-            q = q > margin ? q - margin : 0;                  // never too high; the loop adds what is missing
-            col -= q * mcu_w; base += q * row_skip;
-            while (col >= mcu_w) { col -= mcu_w; base += row_skip; }
+        if (PCR_RARELY((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(1); }
+        const uint32_t win = next_win, e = code.resolve(next_e, win), nx = e & 15u;
+        st.consume(bit_range(e, 8, 5) + nx);
+        next_win = st.window(); next_e = code.entry(next_win);
+        const uint32_t x = win << ((e >> 8) & 31u), extra = bit_range(x, 32u - nx, nx);   // the appended bits: the value, or the length of an end-of-band run
+        const uint32_t at = k + bit_range(e, 4, 4);           // the position the symbol lands on (sixteen zeros: the last of them)
+        const uint32_t room = Se - at, coef = e << 17;        // negative: beyond the band; negative: a coefficient
+        // no code; a coefficient beyond the band; bits beyond the unit's
+        bad |= (e << 16) | (room & coef) | st.beyond();
+        if ((int)(room | ~coef) >= 0) {
+            const uint32_t neg = ~sign_mask(x) & ((1u << nx) - 1u);     // (a value without its top bit stands for a negative one)
+            plane[base + at] = (int16_t)((extra - neg) << Al);
+        }
+        const uint32_t eob = bit_mask(e, 13), done = eob | sign_mask(room - 1u);
+        // blocks to move on by: this one and the rest of an end-of-band run
+        uint32_t adv = by_mask(eob, (1u << nx) | extra, 1u);
+        adv = (adv < left ? adv : left) & done;
+        k = by_mask(done, Ss, at + 1u);
+        left -= adv; base += adv * 64; in_row -= (int)adv;
+        if (PCR_RARELY(in_row <= 0)) {                          // on to the next row of blocks
+            if (in_row <= -(int)mcu_w) {                      // an end-of-band run over more than one row
+                uint32_t q = (uint32_t)((float)(-in_row) * rcp_w);      // rows passed, estimated: off by less than 1 + blocks / 2^22
+                const uint32_t margin = 1u + ((uint32_t)-in_row >> 22);
+                q = q > margin ? q - margin : 0;              // never too high; the loop adds what is missing
+                in_row += (int)(q * mcu_w); base += q * row_skip;
+            }
+            while (in_row <= 0) { in_row += (int)mcu_w; base += row_skip; }
         }
     }
-    return bad ? kEFormat : kOk;
+    return (int)bad < 0 ? kEFormat : kOk;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -310,10 +378,9 @@ PCR_HD __attribute__((always_inline)) int lane_decode_dc_first(const LaneDcUnit&
     uint32_t left = U.mcu1 - U.mcu0;                          // MCUs not finished yet
     uint32_t my = U.mcu0 / U.mcu_w, mx = U.mcu0 - my * U.mcu_w, j = 0;
     int pred0 = U.pred0, pred1 = U.pred1, pred2 = U.pred2;
-    uint32_t bad = 0;
+    uint32_t bad = 0, low = st.low_water(1);
     while (left != 0) {
-        if (any_lane(st.short_of(2))) st.refill();
-        st.top_up();
+        if (PCR_RARELY((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(1); }
         const uint32_t win = st.window(), w16 = win >> 16;
         // the block: component c of the scan, block (by, bx) of its part of the MCU (sampling factors are 1 or 2)
         const uint32_t c = (j >= n0 ? 1u : 0u) + (j >= n01 ? 1u : 0u);
@@ -344,7 +411,7 @@ PCR_HD __attribute__((always_inline)) int lane_decode_dc_first(const LaneDcUnit&
         const int diff = extend(extra, (int)s);
         st.consume(len + s);
         bad |= code_ok ? 0u : 1u;
-        bad |= st.remain < 0 ? 1u : 0u;                       // never walk beyond the unit's data
+        bad |= st.beyond() >> 31;                             // never walk beyond the unit's data
         int pred = c == 0 ? pred0 : (c == 1 ? pred1 : pred2);
         pred += diff;
         pred0 = c == 0 ? pred : pred0; pred1 = c == 1 ? pred : pred1; pred2 = c == 2 ? pred : pred2;
@@ -377,107 +444,151 @@ PCR_HD __attribute__((always_inline)) int lane_decode_dc_first(const LaneDcUnit&
 // One trip of the loop is one symbol with the correction bits that follow it, or one block inside an end-of-band run
 // (correction bits only).
 // ---------------------------------------------------------------------------------------
+// position of the n-th (n = 1 .. 16) set bit of z, 64 if there is none
+PCR_HD uint32_t nth_zero_position(uint64_t z, uint32_t n) {
+    const uint32_t lo = (uint32_t)z, hi = (uint32_t)(z >> 32);
+    uint32_t need = 0u - n, t = (uint32_t)__builtin_popcount(lo) + need, off = 0;
+    const uint32_t upper = sign_mask(t), w = by_mask(upper, hi, lo);
+    need = t > need ? t : need;
+    const uint32_t none = sign_mask((uint32_t)__builtin_popcount(w) + need);              // (fewer than n set bits in all)
+#pragma unroll
+    for (uint32_t width = 16, lg = 4; width > 0; width >>= 1, lg--) {
+        t = (uint32_t)__builtin_popcount(bit_range(w, off, width)) + need;
+        need = t > need ? t : need;
+        off |= (t >> (31u - lg)) & width;
+    }
+    return off | (upper & 32u) | (none & 64u);
+}
+
 constexpr uint32_t kHistRing = 4;
 struct LaneHistRing { uint64_t h[kHistRing][64]; };
 
+// What is left of the block is kept relative to the first position k not passed yet: h the history bits from k on (bit 0
+// is position k; positions beyond the band are zeros in it), rem the positions of the band from k on.  The zeros are then
+// ~h, and a run that ends at relative position p >= rem has run out of the band.
+// Damaged data sets the sign of `bad` and is followed to the unit's last block: records are written for the unit's own
+// blocks only, whatever the data say.
 PCR_HD int lane_decode_ac_refine(const LaneUnit& U, uint64_t* recs, uint32_t nblk, LaneRing* rings, LaneHistRing* hring, uint32_t lane) {
+    if (!lane_unit_inside(U) || nblk != U.plane_elems >> 6 || U.Ss == 0) return kEFormat;
     LaneStream st;
     st.init(U.words, U.bit0, U.bit1, rings, lane);
-    const uint32_t Ss = U.Ss, Se = U.Se, mcu_w = U.mcu_w, row_skip = U.bw - mcu_w;
-    const uint64_t band = band_mask((int)Ss, (int)Se);
-    const uint32_t total = U.mcu1 - U.mcu0;
-    uint32_t left = total;                                    // blocks of the unit not finished yet (the current one included)
-    const uint32_t row0 = U.mcu0 / mcu_w;
-    uint32_t col = U.mcu0 - row0 * mcu_w, blk = row0 * U.bw + col;
-    const uint64_t* hist = recs + (size_t)kRefHist * nblk;
-    // the cursor of the history fetches runs ahead of the decoder's
-    uint32_t fcol = col, fblk = blk, fetched = 0, used_up = 0;
-    auto fetch_history = [&]() {                              // every lane: as many blocks' words as its ring has room for
-        static_assert(kHistRing == 4, "the entries are spelled out (an array indexed in a loop ends up in scratch memory)");
-        uint32_t room = kHistRing - (fetched - used_up);
-        room = room < total - fetched ? room : total - fetched;
-        uint32_t b0 = fblk, b1, b2, b3;
-        auto step = [&](uint32_t b) { uint32_t n = b + 1; fcol++; if (fcol == mcu_w) { fcol = 0; n += row_skip; } return n; };
-        const uint32_t c0 = fcol;
-        b1 = step(b0); b2 = step(b1); b3 = step(b2); const uint32_t b4 = step(b3);
-        // (blocks past the unit's last are not read: the index is held at the last one wanted)
-        const uint32_t l1 = room > 1 ? b1 : b0, l2 = room > 2 ? b2 : l1, l3 = room > 3 ? b3 : l2;
-        const uint64_t v0 = hist[room > 0 ? b0 : blk];
-        const uint64_t v1 = hist[room > 0 ? l1 : blk], v2 = hist[room > 0 ? l2 : blk], v3 = hist[room > 0 ? l3 : blk];
+    LaneLookup code;
+    code.init(U.tab);
+    const uint32_t Ss = U.Ss, band = U.Se - U.Ss + 1u, mcu_w = U.mcu_w, row_skip = U.bw - mcu_w;
+    const uint32_t to_place = 64u - band;                     // from the top of a word down to its bottom, once the whole band has passed
+    uint32_t left = U.mcu1 - U.mcu0;                          // blocks of the unit not finished yet (the current one included)
+    const uint32_t row0 = U.mcu0 / mcu_w, col0 = U.mcu0 - row0 * mcu_w;
+    uint32_t blk = row0 * U.bw + col0, in_row = mcu_w - col0; // the current block; blocks left in its row (itself included)
+    const uint64_t* hist = recs + ref_word(kRefHist, 0, nblk);
+    uint64_t* plus = recs + ref_word(kRefPlus, 0, nblk);
+    // The history words of the next blocks: a ring of kHistRing of them in LDS, and the kHistRing after those under way from
+    // memory or arrived (h0 .. h3), fetched as the stream's chunks are.  The cursor fblk runs ahead of the decoder's block.
+    uint32_t fblk = blk, f_in_row = in_row, fetched = 0, used_up = 0;
+    static_assert(kHistRing == 4, "the entries are spelled out (an array indexed in a loop ends up in scratch memory)");
+    uint64_t h0, h1, h2, h3;
+    auto next_block = [&](uint32_t* b, uint32_t* r) {         // (held at the plane's end: past the unit's last block nothing is looked at)
+        *b += 1u; *r -= 1u;
+        const bool wrap = *r == 0;
+        *b += wrap ? row_skip : 0u; *r = wrap ? mcu_w : *r;
+        *b = *b < nblk ? *b : nblk - 1u;
+    };
+    auto fetch_history = [&]() {
+        uint32_t b = fblk, r = f_in_row;
+        h0 = hist[b]; next_block(&b, &r);
+        h1 = hist[b]; next_block(&b, &r);
+        h2 = hist[b]; next_block(&b, &r);
+        h3 = hist[b];
+    };
+    auto more_history = [&]() {                               // every lane: as many blocks' words as its ring has room for
+        const uint32_t room = kHistRing - (fetched - used_up);
         loads_arrived();
-        if (room > 0) hring->h[(fetched + 0) & 3u][lane] = v0;
-        if (room > 1) hring->h[(fetched + 1) & 3u][lane] = v1;
-        if (room > 2) hring->h[(fetched + 2) & 3u][lane] = v2;
-        if (room > 3) hring->h[(fetched + 3) & 3u][lane] = v3;
-        // the cursor moves on by `room` blocks
-        fblk = room == 0 ? b0 : (room == 1 ? b1 : (room == 2 ? b2 : (room == 3 ? b3 : b4)));
-        uint32_t fc = c0 + room;
-        while (fc >= mcu_w) fc -= mcu_w;
-        fcol = fc;
+        if (room > 0) { hring->h[(fetched + 0) & 3u][lane] = h0; next_block(&fblk, &f_in_row); }
+        if (room > 1) { hring->h[(fetched + 1) & 3u][lane] = h1; next_block(&fblk, &f_in_row); }
+        if (room > 2) { hring->h[(fetched + 2) & 3u][lane] = h2; next_block(&fblk, &f_in_row); }
+        if (room > 3) { hring->h[(fetched + 3) & 3u][lane] = h3; next_block(&fblk, &f_in_row); }
         fetched += room;
+        fetch_history();
     };
     fetch_history();
-    uint64_t h = hring->h[0][lane] & band, z = band & ~h;
-    used_up = 1;
+    more_history();
+    uint64_t h = hring->h[0][lane] >> Ss;                     // (the words hold nothing outside the band)
+    uint64_t hn = hring->h[1][lane];                          // the next block's word (as it comes), read a block ahead
+    used_up = 2;
     uint64_t newm = 0, sgn = 0, corr = 0;
-    uint32_t ncorr = 0, k = Ss, eobrun = 0, bad = 0;
+    uint32_t ncorr = 0, rem = band, eobrun = 0, bad = 0;
+    uint32_t low = st.low_water(4);                           // (a trip takes up to four words)
+    uint32_t next_win = st.window(), next_e = code.entry(next_win);
     while (left != 0) {
-        if (any_lane(st.short_of(4) || (fetched == used_up && fetched < total))) { st.refill(); fetch_history(); }
-        st.top_up();
-        const uint32_t win = st.window();
-        uint32_t pos = Se;                                    // inside an end-of-band run: every correction of the block, nothing else
-        uint32_t used = 0;                                    // bits of the window the symbol takes
-        bool endb = true;
-        if (eobrun == 0) {
-            uint32_t e = U.tab->lut[win >> 24];
-            if (e == 0) e = lane_long_code(U.tab, win);
-            bad |= e == 0 ? 1u : 0u;
-            e = e ? e : (1u << 8);
-            const uint32_t len = e >> 8, r = (e >> 4) & 15u, s = e & 15u;
-            bad |= s > 1 ? 1u : 0u;                           // sizes above 1 do not exist in a refinement scan
-            const bool coef = s != 0, eob = s == 0 && r != 15u;
-            const uint32_t extra = ((win << len) >> 1) >> (31u - (eob ? r : 0u));   // the length bits of an end-of-band run
-            const uint32_t sign = (win << len) >> 31;
-            // a coefficient takes the (r + 1)-th zero from k on, sixteen zeros land on the sixteenth (and leave it zero)
-            const int p = nth_set_bit(z & (~0ull << k), coef ? r + 1u : 16u, 64);
-            bad |= (coef && p == 64) ? 1u : 0u;               // a new coefficient with no zero left to take
-            pos = (eob || p == 64) ? Se : (uint32_t)p;
-            const uint64_t bit = coef ? 1ull << pos : 0ull;
-            newm |= bit; sgn |= sign ? bit : 0ull;
-            eobrun = eob ? (1u << r) + extra : 0u;
-            used = len + (coef ? 1u : (eob ? r : 0u));
-            endb = eob;
+        if (PCR_RARELY((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(4); }
+        if (PCR_RARELY(fetched == used_up)) more_history();
+        const uint32_t win = next_win;
+        // what the search below needs of the block (while LDS still answers)
+        const uint32_t z = ~(uint32_t)h, z16 = (uint32_t)__builtin_popcount(z & 0xFFFFu), z32 = (uint32_t)__builtin_popcount(z);
+        const uint32_t hc = (uint32_t)__builtin_popcountll(h);
+        const uint32_t in_run = sign_mask(0u - eobrun);       // inside an end-of-band run: no symbol, every correction of the block
+        const uint32_t e = by_mask(in_run, kCodeEob, code.resolve(next_e, win));
+        const uint32_t nx = e & 15u, r = bit_range(e, 4, 4);
+        // A coefficient takes the (r + 1)-th zero from k on, sixteen zeros land on the sixteenth (and leave it zero): a binary
+        // search on population counts.  The count still to go is kept negative, as the addend of the next count t: t < 0 says
+        // that the zero lies beyond the part counted, and the larger of the two as unsigned numbers is what is still to go
+        // either way.  The next 32 positions nearly always hold it.
+        uint32_t need = ~r, t = z16 + need;
+        uint32_t p = (t >> 27) & 16u;
+        need = t > need ? t : need;
+#pragma unroll
+        for (uint32_t width = 8, lg = 3; width > 0; width >>= 1, lg--) {
+            t = (uint32_t)__builtin_popcount(bit_range(z, p, width)) + need;
+            need = t > need ? t : need;
+            p |= (t >> (31u - lg)) & width;
         }
-        // the correction bits of the history positions from k to pos follow: mostly a few, inside the window still
-        uint32_t m = (uint32_t)__builtin_popcountll(h & (~0ull << k) & ((2ull << pos) - 1ull));
-        if (used + m <= 31u) {
-            corr |= (uint64_t)(bitrev32(win << used) & ((1u << m) - 1u)) << ncorr;
-            ncorr += m;
-            st.consume_any(used + m);
-        } else {
-            st.consume_any(used);
-            while (m) {
-                st.top_up();
-                const uint32_t t = m < 31u ? m : 31u;
-                corr |= (uint64_t)(bitrev32(st.window()) & ((1u << t) - 1u)) << ncorr;
-                ncorr += t; m -= t;
-                st.consume(t);
+        if (PCR_RARELY((int)(z32 + ~r) < 0)) p = (int)(z32 + ~r) < 0 ? nth_zero_position(~h, r + 1u) : p;
+        const uint32_t eob = bit_mask(e, 13), coef = bit_mask(e, 14);
+        const uint32_t past = sign_mask(rem - 1u - p), all = eob | past;   // past: no zero of the band left to land on
+        const uint32_t last = by_mask(all, rem - 1u, p);      // what is passed: the positions up to this one
+        // the correction bits of the history positions passed follow (of the p positions ahead of the zero all but r): mostly
+        // a few, inside the window still
+        const uint32_t nc = by_mask(all, hc, p - r);
+        const uint32_t used = bit_range(e, 8, 5) + nx;        // bits of the window the symbol takes (30 at most)
+        uint32_t fit = 31u - used;
+        fit = nc < fit ? nc : fit;
+        uint64_t cbits = bit_range(bitrev32(win), used, fit);
+        st.consume(used + fit);
+        if (PCR_RARELY(fit < nc)) {
+            while (fit < nc) {
+                const uint32_t q = nc - fit < 31u ? nc - fit : 31u;
+                cbits |= (uint64_t)bit_range(bitrev32(st.window()), 0, q) << fit;
+                fit += q;
+                st.consume(q);
             }
         }
-        k = pos + 1;
-        bad |= st.remain < 0 ? 1u : 0u;
-        if (endb || k > Se) {                                 // the block is complete
-            uint64_t* rec = recs + blk;
-            rec[(size_t)kRefNz * nblk] = newm; rec[(size_t)kRefSign * nblk] = sgn; rec[(size_t)kRefPlus * nblk] = corr;
-            eobrun -= eobrun ? 1u : 0u;                       // (a run counts the block it starts in)
+        next_win = st.window(); next_e = code.entry(next_win);
+        corr |= cbits << ncorr; ncorr += nc;
+        const uint32_t x = win << ((e >> 8) & 31u);
+        eobrun = by_mask(eob & ~in_run, (1u << nx) | bit_range(x, 32u - nx, nx), eobrun);
+        // no code; no zero to take; sizes above 1 do not exist in a refinement scan; bits beyond the unit's
+        bad |= (e << 16) | (coef & (past | (1u - nx))) | st.beyond();
+        // the block's masks move down with it, what the symbol made of its position enters at their top
+        const uint32_t on = last + 1u, hit = coef & ~past & 0x80000000u;
+        h >>= on;
+        newm = (newm >> on) | ((uint64_t)hit << 32); sgn = (sgn >> on) | ((uint64_t)(hit & x) << 32);
+        rem -= on;
+        if (rem == 0) {                                       // the block is complete
+            newm = (newm >> to_place) << Ss; sgn = (sgn >> to_place) << Ss;
+#if defined(__HIP_DEVICE_COMPILE__)
+            *reinterpret_cast<ulonglong2*>(recs + ref_word(kRefNz, blk, nblk)) = ulonglong2{newm, sgn};
+#else
+            recs[ref_word(kRefNz, blk, nblk)] = newm; recs[ref_word(kRefSign, blk, nblk)] = sgn;
+#endif
+            plus[blk] = corr;
+            eobrun = less_one(eobrun);                        // (a run counts the block it starts in)
             left--;
-            blk++; if (++col == mcu_w) { col = 0; blk += row_skip; }
-            if (left != 0) { h = hring->h[used_up & 3u][lane] & band; used_up++; z = band & ~h; }
-            newm = 0; sgn = 0; corr = 0; ncorr = 0; k = Ss;
+            blk++; in_row--;
+            if (PCR_RARELY(in_row == 0)) { blk += in_row == 0 ? row_skip : 0u; in_row = in_row == 0 ? mcu_w : in_row; }
+            h = hn >> Ss; hn = hring->h[used_up & 3u][lane]; used_up++;
+            newm = 0; sgn = 0; corr = 0; ncorr = 0; rem = band;
         }
-        if (bad) left = 0;                                    // stop at the first damaged block
     }
-    return bad ? kEFormat : kOk;
+    return (int)bad < 0 ? kEFormat : kOk;
 }
 
 }  // namespace pcr

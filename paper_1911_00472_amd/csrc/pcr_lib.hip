@@ -553,7 +553,7 @@ static int finish_open(pcr_record* r, hipStream_t s) {
             const ScanDesc& sd = r->scan[ig];
             if (sd.Ss > 0) {
                 r->mask_off[ig] = nm;
-                nm += (uint64_t)d.bw[sd.comp[0]] * d.bh[sd.comp[0]] * (sd.Ah ? kRefWords : 0);   // one record per block of a refinement scan
+                nm += sd.Ah ? ref_words((uint64_t)d.bw[sd.comp[0]] * d.bh[sd.comp[0]]) : 0;   // one record per block of a refinement scan
                 tab_idx[ig] = ntabs++;                       // (first scans use theirs only when the tables are built ahead)
             }
             uint32_t cnt = sd.ri ? (sd.mcus + sd.ri - 1) / sd.ri : 1;
