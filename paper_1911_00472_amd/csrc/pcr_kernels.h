@@ -1,7 +1,7 @@
 // gfx950 kernels of the PCR decode path.  One kernel per step:
 //   k_index      scan-group index (prefix sums of region lengths)
 //   k_headers    JPEG marker parsing and Huffman tables, one workgroup per image
-//   k_unstuff    byte un-stuffing + restart-interval location, one workgroup per (image, scan)
+//   k_unstuff    byte un-stuffing + restart-interval location, one or four wavefronts per (image, scan); zero fills
 //   k_dc_first, k_ac_first, k_ac_refine   progressive Huffman decode, one wavefront per unit: a restart
 //                interval of a scan, or the stretch between two entry points of the record (the whole scan
 //                where there is neither)
@@ -48,11 +48,24 @@ PCR_D void wave_sync() {
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+// the value of the lane before this one (lane 0: `first`), and the sum over the lanes up to this one
+PCR_D uint32_t lane_before(uint32_t v, uint32_t first) { return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xF, 0xF, false); }   // wave_shr:1
+PCR_D uint32_t lanes_prefix_sum(uint32_t v) {
+    uint32_t x = v;
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);           // row_shr:1, 2, 4, 8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);           // row_bcast:15 into rows 1 and 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);           // row_bcast:31 into rows 2 and 3
+    return x;
+}
 PCR_D void dc_kernel_priority() { __builtin_amdgcn_s_setprio(2); }
 
 struct DevRecord {
     const uint8_t* rec;        // record bytes
     uint8_t* clean;            // unstuffed entropy data, same offsets as rec
+    uint64_t nbytes;           // of rec
     uint32_t n, G;
     uint32_t* off;             // [G][n] absolute region offsets (k_index)
     const uint32_t* len;       // [G][n] region lengths (inside rec's header)
@@ -127,7 +140,7 @@ __global__ void __launch_bounds__(256) k_index(DevRecord R, uint32_t kmax) {
 // tables from scan k0 on are built (none: k0 = kmax); dc_too = 0: the DC first scans of this call are all decoded by
 // k_dc_first_lanes, which builds its own tables.
 // --------------------------------------------------------------------------------------
-constexpr int kHeaderWaves = 4, kHeaderLanes = 64 * kHeaderWaves;
+constexpr int kHeaderWaves = 8, kHeaderLanes = 64 * kHeaderWaves;
 constexpr uint32_t kMaxGroups = 64;                        // (parse_record_header refuses more)
 constexpr uint32_t kHeaderStage = 16384;                   // bytes of LDS for the heads of the regions, shared out evenly
 constexpr uint32_t kHeaderWindow = 1024;                   // ... but at most this much per region (a first region with its tables is 600-700 bytes)
@@ -149,25 +162,30 @@ struct CanonCode { uint32_t lim[17]; uint32_t first[17]; uint8_t vals[256]; };
 // From a DHT payload (16 counts, then the symbols in code order); call with a whole wavefront.
 PCR_D void canon_build(CanonCode* c, const HeaderBytes& def, uint32_t at, uint32_t lane) {
     const uint32_t mine = lane < 16 ? def[at + lane] : 0u;
-    uint32_t code = 0, k = 0;
-    if (lane == 0) c->lim[0] = 0;
+    const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)lanes_prefix_sum(mine), 15);       // symbols in all
+    for (uint32_t i = lane; i < 256; i += 64) c->vals[i] = i < k ? def[at + 16 + i] : (uint8_t)0;
+    uint32_t code = 0, lim = 0, first = 0;                    // of this lane's length (lane 0: length 1), put together by going down the lengths
+#pragma unroll
     for (uint32_t L = 1; L <= 16; L++) {
         const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(L - 1));
-        if (lane == 0) c->first[L] = k;
-        code += cnt; k += cnt;
-        const uint64_t lim = (uint64_t)code << (16 - L);
-        if (lane == 0) c->lim[L] = lim > 65536 ? 65536u : (uint32_t)lim;
+        code += cnt;
+        const uint64_t t = (uint64_t)code << (16 - L);
+        if (lane == L - 1) lim = t > 65536 ? 65536u : (uint32_t)t;
         code <<= 1;
     }
-    for (uint32_t i = lane; i < 256; i += 64) c->vals[i] = i < k ? def[at + 16 + i] : (uint8_t)0;
+    first = lanes_prefix_sum(mine) - mine;
+    if (lane < 16) { c->lim[lane + 1] = lim; c->first[lane + 1] = first; }
+    if (lane == 16) c->lim[0] = 0;
 }
-// (length << 8) | index of the code at the head of the left-aligned 16-bit value c16; 0 if none of the lengths lo .. hi
-PCR_D uint32_t canon_find(const CanonCode* c, uint32_t c16, uint32_t lo, uint32_t hi) {
-    uint32_t L = lo;
-    while (L <= hi && c16 >= c->lim[L]) L++;
-    if (L > hi || c16 < c->lim[L - 1]) return 0;
-    const uint32_t idx = c->first[L] + ((c16 - c->lim[L - 1]) >> (16 - L));
-    return idx < 256u ? (L << 8) | idx : 0u;
+// (length << 8) | index of the code at the head of the left-aligned 16-bit value c16; 0 if none of the lengths kLo .. kHi.
+// (The limits are counted, not searched: eight reads of LDS that wait for nothing, then two for the length found.)
+template <int kLo, int kHi>
+PCR_D uint32_t canon_find(const CanonCode* c, uint32_t c16) {
+    uint32_t L = kLo;
+#pragma unroll
+    for (int q = kLo; q < kHi; q++) L += c16 >= c->lim[q] ? 1u : 0u;
+    const uint32_t below = c->lim[L - 1], idx = c->first[L] + ((c16 - below) >> (16 - L));
+    return (c16 < c->lim[kHi] && c16 >= below && idx < 256u) ? (L << 8) | idx : 0u;
 }
 // What actab_build and actab_pack make of the definition, entry by entry (same contents).
 PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t lane) {
@@ -175,7 +193,7 @@ PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t l
     uint32_t sh2 = 0;
     while (D && ((D - 1) >> sh2) >= 128) sh2++;
     for (uint32_t e = lane; e < 256; e += 64) {
-        const uint32_t f = canon_find(c, e << 8, 1, 8);
+        const uint32_t f = canon_find<1, 8>(c, e << 8);
         const uint32_t v = f ? (f & 0xFF00u) | c->vals[f & 255u] : 0u;
         t->lut[e] = (uint16_t)(f ? code_entry(f >> 8, v & 255u) : 0u);
         t->lutp[e] = packed_entry(v, first);
@@ -183,7 +201,7 @@ PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t l
     }
     for (uint32_t e = lane; e < 128; e += 64) {
         const uint32_t c16 = lim8 + (e << sh2);
-        const uint32_t f = c16 < 65536u ? canon_find(c, c16, 9, 16) : 0u;
+        const uint32_t f = c16 < 65536u ? canon_find<9, 16>(c, c16) : 0u;
         t->lut2[e] = (uint16_t)((f && 16u - (f >> 8) >= sh2) ? code_entry(f >> 8, c->vals[f & 255u]) : 0u);
     }
     if (lane < 9) t->limit[lane] = c->lim[8 + lane];
@@ -193,7 +211,7 @@ PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t l
 // ... and dctab_build (only the first sixteen codes are DC categories).
 PCR_D void dctab_build_wave(DcTab* t, const CanonCode* c, uint32_t lane) {
     for (uint32_t e = lane; e < 256; e += 64) {
-        const uint32_t f = canon_find(c, e << 8, 1, 8);
+        const uint32_t f = canon_find<1, 8>(c, e << 8);
         t->lut[e] = (f && (f & 255u) < 16u) ? (uint8_t)(((f >> 8) << 4) | (c->vals[f & 255u] & 15)) : (uint8_t)0xFF;
     }
     if (lane < 16) t->huffval[lane] = c->vals[lane];
@@ -201,7 +219,7 @@ PCR_D void dctab_build_wave(DcTab* t, const CanonCode* c, uint32_t lane) {
     if (lane < 8) t->valptr[lane] = (uint16_t)c->first[9 + lane];
 }
 
-__global__ void __launch_bounds__(kHeaderLanes) k_headers(DevRecord R, uint32_t kmax, uint32_t keep_status, uint32_t own_index, uint32_t k0, uint32_t dc_too) {
+__global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32_t kmax, uint32_t keep_status, uint32_t own_index, uint32_t k0, uint32_t dc_too) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[kHeaderStage];
     __shared__ uint32_t s_off[kMaxGroups], s_len[kMaxGroups];
     __shared__ ScanDesc s_scan[kMaxGroups];
@@ -328,140 +346,216 @@ __global__ void __launch_bounds__(kHeaderLanes) k_headers(DevRecord R, uint32_t 
 }
 
 // --------------------------------------------------------------------------------------
-// k_unstuff: per (image, scan) remove stuffed zeros, fill bytes and restart markers from the
-// entropy-coded segment, stop at the first other marker, note where each restart interval
-// begins.  256 lanes x 8 bytes per step.  A lane classifies its eight bytes at once (one flag bit per
-// byte in a 64-bit word: equal to FF, to 00, a restart marker's second byte, and the same of the byte
-// that follows), squeezes out the few it drops and puts the rest, byte by byte, at their place in a ring
-// in LDS; the workgroup then stores the words the step has completed, already in the big-endian order
-// the decoders read (one 4-byte store per lane instead of eight single bytes).
+// k_unstuff: per (image, scan) remove stuffed zeros, fill bytes and restart markers from the entropy-coded segment, stop at
+// the first other marker, note where each restart interval begins -- and, in the same launch, clear the memory the
+// decoders expect to be zero (fills: a bandwidth-bound job beside a latency-bound one).
+//
+// 64 lanes x 16 bytes per step and wavefront, the next step's bytes under way meanwhile.  A byte is
+// judged by itself and the byte before it, which for a lane's first byte comes from its neighbour by a lane shift: FF says
+// nothing yet; after FF, 00 stands for a data byte FF, D0..D7 is a restart marker, FF is fill, anything else the marker
+// that ends the segment; every other byte is data.  A lane classifies its sixteen bytes at once (one flag bit per byte in
+// two 64-bit words), squeezes out the few it drops and puts the rest at its place in LDS (a prefix sum over the lanes says
+// where); whole 16-byte chunks are then stored as the big-endian words the decoders read.
+// A step takes a wavefront about 1.5 us whatever the others do, so the scans of a group that are long on average
+// (kUnstuffWide bytes) get the four wavefronts of a workgroup (three barriers per step of 4 KB), the others one each.
+// (Before: a workgroup per scan, 2 KB per step with four barriers and no loads ahead, 128 us for the 81 MB of 1024
+// photographs, and 71 us for the fill after it.)
 // --------------------------------------------------------------------------------------
-constexpr int kUnstuffPer = 8;
-constexpr uint32_t kUnstuffRing = 4096;                    // bytes; a step adds at most 2048 to fewer than 4 left over
+constexpr uint32_t kUnstuffWaves = 4, kUnstuffStep = 1024;
+constexpr int kMaxFills = 3;
+struct FillList { uint4* p[kMaxFills]; size_t n16[kMaxFills]; uint32_t groups; };      // 16-byte pieces; workgroups that share the work
 
 // 0x80 in every byte of the result whose byte in x is zero (exact, no carries between bytes)
 PCR_D uint64_t zero_bytes(uint64_t x) {
     const uint64_t m = 0x7F7F7F7F7F7F7F7Full;
     return ~(((x & m) + m) | x | m);
 }
-// the flags (0x80 per byte) of the bytes below byte n (n >= 8: all)
-PCR_D uint64_t flags_below(uint32_t n) { return n >= 8 ? 0x8080808080808080ull : ((1ull << (8 * n)) - 1) & 0x8080808080808080ull; }
+// the flags (0x80 per byte) of the bytes below byte n (n >= 8: all; n < 0: none)
+PCR_D uint64_t flags_below(int n) { return n >= 8 ? 0x8080808080808080ull : (n <= 0 ? 0ull : ((1ull << (8 * n)) - 1) & 0x8080808080808080ull); }
+struct __attribute__((packed, aligned(1))) LooseU64 { uint64_t v; };
+struct __attribute__((packed, aligned(1))) LooseU32 { uint32_t v; };
+struct __attribute__((packed, aligned(1))) LooseU16 { uint16_t v; };
 
-// grid: (images, scan groups kfrom .. kmax-1)
-__global__ void __launch_bounds__(256) k_unstuff(DevRecord R, uint32_t kfrom, uint32_t kmax) {
-    short_kernel_priority();
-    __shared__ uint32_t part[4];
-    __shared__ uint32_t s_stop;
-    __shared__ __attribute__((aligned(16))) uint32_t ring[kUnstuffRing / 4];
-    uint32_t i = blockIdx.x, g = kfrom + blockIdx.y;
-    if (g >= kmax) return;
+// What a launch works through: scan groups in order of decreasing length; first[e]: the first unstuffing workgroup of entry
+// e (first[count]: their number); bit e of `wide`: one scan per workgroup, else one per wavefront.
+constexpr uint32_t kUnstuffWide = 6144;
+struct UnstuffPlan { uint64_t wide; uint32_t count; uint32_t first[kMaxGroups + 1]; uint8_t group[kMaxGroups]; };
+
+// One scan by W wavefronts (1, or the kUnstuffWaves of a workgroup); wave: this one's number among them.  buf: W steps and
+// 32 bytes; tot: W words.
+template <uint32_t W>
+PCR_D void unstuff_scan(const DevRecord& R, uint32_t i, uint32_t g, uint8_t* buf, uint32_t* tot, uint32_t wave, uint32_t lane) {
+    auto together = [&]() { if (W > 1) __syncthreads(); else wave_sync(); };
     const ImgDesc& img = R.img[i];
     if (img.status != kOk || g >= img.nscans) return;
-    const ScanDesc& sd = R.scan[(size_t)i * R.G + g];
-    const uint8_t* src = R.rec + sd.data_off;
-    uint8_t* dst = R.clean + clean_base(sd.data_off);     // stored as big-endian 32-bit words: byte o goes to o ^ 3
-    const uint32_t L = sd.data_len;
-    const uint32_t sb = R.slot_base[(size_t)i * R.G + g], sc = R.slot_cnt[(size_t)i * R.G + g];
-    uint8_t* ringb = reinterpret_cast<uint8_t*>(ring);
-    uint32_t out_total = 0, rst_total = 0;
-    if (threadIdx.x == 0) { s_stop = 0xFFFFFFFFu; R.ivl_start[sb] = 0; }
-    __syncthreads();
-    for (uint32_t base = 0; base < L; base += 256 * kUnstuffPer) {
-        const uint32_t p0 = base + threadIdx.x * kUnstuffPer;
-        const uint32_t nvalid = p0 >= L ? 0u : (L - p0 < 8 ? L - p0 : 8u);
-        uint64_t w = 0;                                  // byte j of the lane: bits 8j .. 8j+7
-        if (nvalid == 8) {
-            struct __attribute__((packed, aligned(1))) Two { uint32_t a, b; };
-            const Two t = *reinterpret_cast<const Two*>(src + p0);
-            w = (uint64_t)t.a | ((uint64_t)t.b << 32);
-        } else for (uint32_t j = 0; j < nvalid; j++) w |= (uint64_t)src[p0 + j] << (8 * j);
-        const uint32_t prevb = (p0 > 0 && p0 <= L) ? src[p0 - 1] : 0u;
-        const bool has_next = p0 + 8 < L;
-        const uint32_t nextb = has_next ? src[p0 + 8] : 0u;
-        const uint64_t top = 0x8000000000000000ull, all = 0x8080808080808080ull;
-        const uint64_t valid = flags_below(nvalid);
-        const uint64_t ff = zero_bytes(~w), z0 = zero_bytes(w), rs = zero_bytes((w & 0xF8F8F8F8F8F8F8F8ull) ^ 0xD0D0D0D0D0D0D0D0ull);
-        // the same of the byte that follows (none follows the segment's last byte) and of the byte before
-        const uint64_t nvalid_next = (valid >> 8) | (has_next ? top : 0);
-        const uint64_t nff = ((ff >> 8) | (nextb == 0xFF ? top : 0)) & nvalid_next;
-        const uint64_t nz0 = ((z0 >> 8) | (nextb == 0x00 ? top : 0)) & nvalid_next;
-        const uint64_t nrs = ((rs >> 8) | ((nextb & 0xF8) == 0xD0 ? top : 0)) & nvalid_next;
-        const uint64_t pff = (ff << 8) | (prevb == 0xFF ? 0x80ull : 0);
-        // FF: kept if a zero follows (a data byte), a restart marker if D0..D7 follows, dropped if another FF follows (fill),
-        // else the marker that ends the segment.  Others: dropped if they are the second byte of FF 00 or of a restart marker.
-        uint64_t keep = valid & ((all & ~ff & ~(pff & (z0 | rs))) | (ff & nz0));
-        uint64_t rst = valid & ff & nrs;
-        const uint64_t stopf = valid & ff & ~nrs & ~nz0 & ~nff;
-        if (stopf) atomicMin(&s_stop, p0 + ((uint32_t)__builtin_ctzll(stopf) >> 3));
-        __syncthreads();
-        const uint32_t stop_all = s_stop;
-        if (stop_all != 0xFFFFFFFFu) {                     // drop what lies at or after the terminating marker
-            const uint64_t before = flags_below(stop_all > p0 ? stop_all - p0 : 0u);
-            keep &= before; rst &= before;
+    const size_t ig = (size_t)i * R.G + g;
+    const ScanDesc& sd = R.scan[ig];
+    const uint32_t off = uni(sd.data_off), L = uni(sd.data_len), sb = uni(R.slot_base[ig]), sc = uni(R.slot_cnt[ig]);
+    const uint8_t* src = R.rec + off;
+    uint8_t* dst = R.clean + clean_base(off);
+    // sixteen bytes from p on (bytes past the segment are whatever follows it in the record, and are not looked at) and, for
+    // lane 0, the byte ahead of them
+    auto load = [&](uint32_t p, uint64_t* lo, uint64_t* hi, uint32_t* prev) {
+        *lo = *hi = 0; *prev = 0;
+        if (p >= L) return;
+        if (lane == 0 && p > 0) *prev = src[p - 1];
+        if ((uint64_t)off + p + 16 <= R.nbytes) {
+            *lo = reinterpret_cast<const LooseU64*>(src + p)->v; *hi = reinterpret_cast<const LooseU64*>(src + p + 8)->v;
+        } else for (uint32_t q = 0; q < 16 && p + q < L; q++) {
+            if (q < 8) *lo |= (uint64_t)src[p + q] << (8 * q); else *hi |= (uint64_t)src[p + q] << (8 * (q - 8));
         }
-        // prefix sums of (bytes kept | restart markers << 16) over the 256 lanes: inside each wavefront by lane
-        // shuffles, then the four wavefront totals through LDS
-        const uint32_t nkeep = (uint32_t)__builtin_popcountll(keep);
-        const uint32_t mine = nkeep | ((uint32_t)__builtin_popcountll(rst) << 16);
-        const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        uint32_t incl = mine;
-#pragma unroll
-        for (uint32_t d = 1; d < 64; d <<= 1) {
-            const uint32_t t = (uint32_t)__shfl_up((int)incl, d, 64);
-            if (lane >= d) incl += t;
-        }
-        if (lane == 63) part[wave] = incl;
-        __syncthreads();
-        const uint32_t w0 = part[0], w1 = part[1], w2 = part[2], w3 = part[3];
-        const uint32_t before = (wave > 0 ? w0 : 0) + (wave > 1 ? w1 : 0) + (wave > 2 ? w2 : 0);
-        const uint32_t excl = before + incl - mine;
-        const uint32_t o = out_total + (excl & 0xFFFF);
-        if (rst) {                                         // (rare) where the next interval begins: behind the bytes kept ahead of the marker
-            uint32_t r = rst_total + (excl >> 16);
-            for (uint64_t m = rst; m; m &= m - 1) {
-                const uint32_t j = (uint32_t)__builtin_ctzll(m) >> 3;
-                r++;
-                if (r < sc) R.ivl_start[sb + r] = o + (uint32_t)__builtin_popcountll(keep & flags_below(j));
+    };
+    const uint32_t mine = (wave * 64 + lane) * 16, step = W * kUnstuffStep;
+    uint32_t out_total = 0, rst_total = 0, have = 0;          // bytes stored; restart markers seen; bytes waiting in buf
+    uint64_t nlo, nhi;
+    uint32_t nprev;
+    load(mine, &nlo, &nhi, &nprev);
+    bool stop = false;
+    for (uint32_t base = 0; base < L && !stop; base += step) {
+        uint64_t lo = nlo, hi = nhi;
+        const uint32_t before = lane_before((uint32_t)(hi >> 56), nprev);
+        load(base + step + mine, &nlo, &nhi, &nprev);
+        const int nvalid = (int)(L - base) - (int)mine;       // (may be more than sixteen, or negative)
+        const uint64_t vlo = flags_below(nvalid), vhi = flags_below(nvalid - 8);
+        const uint64_t flo = zero_bytes(~lo), fhi = zero_bytes(~hi);
+        const uint64_t plo = (flo << 8) | (before == 0xFF ? 0x80ull : 0), phi = (fhi << 8) | (flo >> 63 << 7);      // the byte before is FF
+        const uint64_t zlo = zero_bytes(lo), zhi = zero_bytes(hi);
+        uint64_t klo = vlo & ((~flo & ~plo) | (plo & zlo)), khi = vhi & ((~fhi & ~phi) | (phi & zhi));
+        uint64_t rlo = 0, rhi = 0;
+        bool ends = false;                                    // the marker that ends the segment is among this wavefront's bytes
+        if (__ballot(((plo & vlo & ~zlo) | (phi & vhi & ~zhi)) != 0)) {   // (rare) FF with something other than a stuffed zero behind it
+            const uint64_t d = 0xF8F8F8F8F8F8F8F8ull, e = 0xD0D0D0D0D0D0D0D0ull;
+            rlo = vlo & plo & zero_bytes((lo & d) ^ e); rhi = vhi & phi & zero_bytes((hi & d) ^ e);
+            const uint64_t slo = vlo & plo & ~zlo & ~rlo & ~flo, shi = vhi & phi & ~zhi & ~rhi & ~fhi;
+            const uint64_t who = __ballot((slo | shi) != 0);
+            if (who) {                                        // drop what lies at or behind it
+                ends = true;
+                const uint32_t first = (uint32_t)__builtin_ctzll(who);
+                const int upto = lane < first ? 16 : (lane > first ? 0 : (slo ? __builtin_ctzll(slo) >> 3 : 8 + (__builtin_ctzll(shi) >> 3)));
+                klo &= flags_below(upto); khi &= flags_below(upto - 8); rlo &= flags_below(upto); rhi &= flags_below(upto - 8);
             }
         }
-        // squeeze the dropped bytes out (few: one step of the loop per dropped byte), then the kept ones into the ring
-        uint64_t kw = w;
-        for (uint64_t drop = valid & ~keep; drop; ) {
-            const uint32_t j = 63u - (uint32_t)__builtin_clzll(drop);      // highest first, so that the positions below stay put
-            drop &= ~(1ull << j);
-            const uint32_t sh = (j >> 3) * 8;                               // first bit of the byte
-            const uint64_t low = sh ? (kw & ((1ull << sh) - 1)) : 0;
-            kw = low | (sh < 56 ? (kw >> (sh + 8)) << sh : 0);
+        // the stuffed zeros kept stand for the FF ahead of them
+        const uint64_t tlo = klo & plo, thi = khi & phi;
+        lo |= (tlo >> 7) * 0xFF; hi |= (thi >> 7) * 0xFF;
+        uint32_t nkeep = (uint32_t)__builtin_popcountll(klo) + (uint32_t)__builtin_popcountll(khi);
+        uint32_t nrst = (uint32_t)__builtin_popcountll(rlo) + (uint32_t)__builtin_popcountll(rhi);
+        const uint32_t incl = lanes_prefix_sum(nkeep | (nrst << 16));
+        uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63), ahead = 0;   // of all wavefronts; of those before this one
+        stop = ends;
+        if (W > 1) {                                          // (a wavefront's counts are below 2^11 and 2^10)
+            if (lane == 0) tot[wave] = all | (ends ? 0x80000000u : 0u);
+            __syncthreads();
+            uint32_t sum = 0;
+            stop = false;
+#pragma unroll
+            for (uint32_t q = 0; q < W; q++) {
+                const uint32_t t = uni(tot[q]);
+                if (q == wave) {
+                    ahead = sum;
+                    if (stop) nkeep = nrst = 0;               // the segment ended ahead of this wavefront's bytes
+                }
+                sum += stop ? 0u : t & 0x7FFFFFFFu;
+                stop = stop || (t >> 31);
+            }
+            all = sum;
         }
-        for (uint32_t j = 0; j < nkeep; j++) ringb[(o + j) & (kUnstuffRing - 1)] = (uint8_t)(kw >> (8 * j));
-        const uint32_t tot = w0 + w1 + w2 + w3;
-        const uint32_t end = out_total + (tot & 0xFFFF);
-        __syncthreads();
-        for (uint32_t wi = (out_total >> 2) + threadIdx.x; wi < (end >> 2); wi += 256)      // the words complete by now
-            *reinterpret_cast<uint32_t*>(dst + 4 * (size_t)wi) = __builtin_bswap32(ring[wi & (kUnstuffRing / 4 - 1)]);
-        out_total = end; rst_total += tot >> 16;
-        __syncthreads();
-        if (stop_all != 0xFFFFFFFFu) break;
+        const uint32_t at = have + (ahead & 0xFFFF) + (incl & 0xFFFF) - nkeep;
+        if (nrst) {                                           // (rare) where the next intervals begin: behind the bytes kept ahead of each marker
+            uint32_t r = rst_total + (ahead >> 16) + (incl >> 16) - nrst;
+            for (uint64_t m = rlo; m; m &= m - 1) { r++; if (r < sc) R.ivl_start[sb + r] = out_total + at + (uint32_t)__builtin_popcountll(klo & ((m & (0 - m)) - 1)); }
+            for (uint64_t m = rhi; m; m &= m - 1) { r++; if (r < sc) R.ivl_start[sb + r] = out_total + at + (uint32_t)__builtin_popcountll(klo) + (uint32_t)__builtin_popcountll(khi & ((m & (0 - m)) - 1)); }
+        }
+        rst_total += all >> 16;
+        // squeeze the dropped bytes out, the highest first (few lanes have any, and mostly one)
+        uint64_t dlo = 0x8080808080808080ull & ~klo, dhi = 0x8080808080808080ull & ~khi;
+        if (nkeep == 0) dlo = dhi = 0;
+        while (dlo | dhi) {
+            if (dhi) {
+                const uint32_t sh = (63u - (uint32_t)__builtin_clzll(dhi)) & 56u;
+                dhi &= ~(0x80ull << sh);
+                const uint64_t low = (1ull << sh) - 1;
+                hi = (hi & low) | ((hi >> 8) & ~low);
+            } else {
+                const uint32_t sh = (63u - (uint32_t)__builtin_clzll(dlo)) & 56u;
+                dlo &= ~(0x80ull << sh);
+                const uint64_t low = (1ull << sh) - 1;
+                lo = (lo & low) | (((lo >> 8) & ~low) & 0x00FFFFFFFFFFFFFFull) | (hi << 56);
+                hi >>= 8;
+            }
+        }
+        uint8_t* p = buf + at;
+        if (nkeep == 16) { reinterpret_cast<LooseU64*>(p)->v = lo; reinterpret_cast<LooseU64*>(p + 8)->v = hi; }
+        else {
+            if (nkeep & 8) { reinterpret_cast<LooseU64*>(p)->v = lo; p += 8; lo = hi; }
+            if (nkeep & 4) { reinterpret_cast<LooseU32*>(p)->v = (uint32_t)lo; p += 4; lo >>= 32; }
+            if (nkeep & 2) { reinterpret_cast<LooseU16*>(p)->v = (uint16_t)lo; p += 2; lo >>= 16; }
+            if (nkeep & 1) *p = (uint8_t)lo;
+        }
+        together();
+        have += all & 0xFFFF;
+        const uint32_t full = have >> 4, c = wave * 64 + lane;   // whole chunks: one per lane at most (fewer than sixteen bytes were waiting)
+        uint4 left{0, 0, 0, 0};
+        if (c < full) {
+            const uint4 v = *reinterpret_cast<const uint4*>(buf + c * 16);
+            *reinterpret_cast<uint4*>(dst + out_total + c * 16) = uint4{__builtin_bswap32(v.x), __builtin_bswap32(v.y), __builtin_bswap32(v.z), __builtin_bswap32(v.w)};
+        }
+        if (c == 0) left = *reinterpret_cast<const uint4*>(buf + full * 16);
+        together();
+        if (c == 0) *reinterpret_cast<uint4*>(buf) = left;    // (the next step writes behind its first have & 15 bytes, some of them into the rest of it)
+        together();
+        out_total += full * 16; have &= 15u;
     }
-    if (threadIdx.x < (out_total & 3u)) {                  // the bytes of the last, incomplete word
-        const uint32_t q = (out_total & ~3u) + threadIdx.x;
-        dst[q ^ 3u] = ringb[q & (kUnstuffRing - 1)];
-    }
-    if (threadIdx.x == 0) {
+    const uint32_t c = wave * 64 + lane;
+    // what is left: whole words (their unused bytes lie ahead of the next segment: a marker and its length are four bytes)
+    if (c * 4 < have) *reinterpret_cast<uint32_t*>(dst + out_total + c * 4) = __builtin_bswap32(*reinterpret_cast<const uint32_t*>(buf + c * 4));
+    out_total += have;
+    if (c == 0) {
+        R.ivl_start[sb] = 0;
         // intervals whose restart marker never showed up get an empty range; the end goes last
         for (uint32_t r = rst_total + 1; r <= sc; r++) R.ivl_start[sb + r] = out_total;
         R.ivl_start[sb + sc] = out_total;
         if (rst_total + 1 != (sd.ri ? sc : 1u)) R.status[i] = kEFormat;      // (without restart intervals the units of a scan start at entry points)
-        if (sd.Ss == 0 && sd.Ah != 0) {
-            // DC refinement is read in place later (one bit per block): check every interval is long enough
-            uint32_t bpm = 0;
-            for (int q = 0; q < sd.ns; q++) bpm += sd.ns > 1 ? (uint32_t)img.hs[sd.comp[q]] * img.vs[sd.comp[q]] : 1;
-            for (uint32_t r = 0; r < sc; r++) {
-                uint32_t m0 = sd.ri ? r * sd.ri : 0, m1 = sd.ri ? (m0 + sd.ri < sd.mcus ? m0 + sd.ri : sd.mcus) : sd.mcus;
-                uint32_t have = (R.ivl_start[sb + r + 1] - R.ivl_start[sb + r]) * 8;
-                if ((m1 - m0) * bpm > have) R.status[i] = kEFormat;
-            }
+    }
+    if (sd.Ss == 0 && sd.Ah != 0) {
+        // DC refinement is read in place later (one bit per block): check every interval is long enough
+        __threadfence_block();
+        together();
+        uint32_t bpm = 0;
+        for (int q = 0; q < sd.ns; q++) bpm += sd.ns > 1 ? (uint32_t)img.hs[sd.comp[q]] * img.vs[sd.comp[q]] : 1;
+        for (uint32_t r = c; r < sc; r += W * 64) {
+            const uint32_t m0 = sd.ri ? r * sd.ri : 0, m1 = sd.ri ? (m0 + sd.ri < sd.mcus ? m0 + sd.ri : sd.mcus) : sd.mcus;
+            const uint32_t bits = (R.ivl_start[sb + r + 1] - R.ivl_start[sb + r]) * 8;
+            if ((m1 - m0) * bpm > bits) R.status[i] = kEFormat;
         }
+    }
+}
+
+// Workgroups [0, P.first[P.count] + F.groups): every period-th one (until F.groups of them) fills, the others unstuff.
+__global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period) {
+    __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffWaves * (kUnstuffStep + 32)];
+    __shared__ uint32_t tot[kUnstuffWaves];
+    short_kernel_priority();
+    const uint32_t b = blockIdx.x, tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
+    const uint32_t fills = F.groups == 0 ? 0u : ((b + 1) / period < F.groups ? (b + 1) / period : F.groups);   // filling workgroups up to this one, itself included
+    if (F.groups && (b + 1) % period == 0 && (b + 1) / period <= F.groups) {
+        for (int f = 0; f < kMaxFills; f++) {
+            uint4* p = F.p[f];
+            const size_t n16 = F.n16[f], stride = (size_t)F.groups * 256;
+            for (size_t e = (size_t)(fills - 1) * 256 + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
+        }
+        return;
+    }
+    const uint32_t u = b - fills;
+    uint32_t e = 0;
+    while (e + 1 < P.count && u >= P.first[e + 1]) e++;
+    if (e >= P.count) return;
+    const uint32_t g = P.group[e], at = u - P.first[e];
+    if ((P.wide >> e) & 1) {
+        if (at < R.n) unstuff_scan<kUnstuffWaves>(R, at, g, buf, tot, wave, lane);
+    } else {
+        const uint32_t i = at * kUnstuffWaves + wave;
+        if (i < R.n) unstuff_scan<1>(R, i, g, buf + wave * (kUnstuffStep + 32), tot, 0, lane);
     }
 }
 
@@ -2328,13 +2422,6 @@ __global__ void __launch_bounds__(64) k_probe_scalar(uint32_t* out, uint32_t ite
             : "+s"(a), "+s"(b) : : "scc");
     }
     if (threadIdx.x == 0) out[blockIdx.x] = a ^ b;
-}
-
-__global__ void __launch_bounds__(256) k_fill_zero(uint4* p, size_t n16) {
-    short_kernel_priority();
-    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * 256;
-    for (; i < n16; i += stride) p[i] = make_uint4(0, 0, 0, 0);
 }
 
 }  // namespace pcr

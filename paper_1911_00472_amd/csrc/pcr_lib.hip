@@ -383,6 +383,37 @@ void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bo
     hipLaunchKernelGGL(k_headers, dim3(n), dim3(kHeaderLanes), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
 }
 
+// Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, the filling
+// workgroups spread evenly between the others so that they run beside them all the way (as many as unstuff at most, or they
+// would go ahead of them; 1024 where that is more: there is room for all at once).
+void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, hipStream_t s) {
+    const uint32_t n = r->hdr.n, count = k - k0;
+    UnstuffPlan P{};
+    uint64_t mean[kMaxGroups];
+    for (uint32_t g = k0; g < k; g++) {
+        const uint8_t* hdr = r->header.data();
+        const uint64_t start = g ? ld_le64(hdr + hdr_group_end_pos(g - 1)) : r->hdr.header_bytes;
+        mean[g] = (ld_le64(hdr + hdr_group_end_pos(g)) - start) / n;
+        uint32_t e = P.count++;
+        for (; e > 0 && mean[P.group[e - 1]] < mean[g]; e--) P.group[e] = P.group[e - 1];
+        P.group[e] = (uint8_t)g;
+    }
+    uint32_t groups = 0;
+    for (uint32_t e = 0; e < count; e++) {
+        P.first[e] = groups;
+        const bool wide = mean[P.group[e]] >= kUnstuffWide;
+        if (wide) P.wide |= 1ull << e;
+        groups += wide ? n : (n + kUnstuffWaves - 1) / kUnstuffWaves;
+    }
+    P.first[count] = groups;
+    size_t pieces = 0;
+    for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
+    fill.groups = (uint32_t)std::min<size_t>((pieces + 2047) / 2048, std::min<size_t>(2048, std::max<size_t>(groups, 1024)));     // (eight pieces per lane at least)
+    const uint32_t total = groups + fill.groups;
+    if (total == 0) return;
+    hipLaunchKernelGGL(k_unstuff, dim3(total), dim3(64 * kUnstuffWaves), 0, s, r->d, P, fill, fill.groups ? total / fill.groups : 1u);
+}
+
 // Steps 1-5 of the path (index .. entropy decode + refinement) for scans 1..k.
 // refine_in_memory: also run k_apply, which leaves the refined coefficients in the planes (the coefficient
 // export needs that; the pixel kernel replays the refinement itself from the lists of k_apply_prep).
@@ -407,7 +438,6 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     }
     launch_headers(r, (uint32_t)k, k0 > 0, dc_tables || plan->has_ac ? (uint32_t)k0 : (uint32_t)k, dc_tables, s);
     mark(r, PCR_STAGE_INDEX_PARSE, s);
-    if (k > k0) hipLaunchKernelGGL(k_unstuff, dim3(n, k - k0), dim3(256), 0, s, r->d, (uint32_t)k0, (uint32_t)k);
     const size_t coef_bytes = r->coef_off[n] * sizeof(int16_t);
     // AC first scans only write the coefficients they decode: everything else must read as zero.  With DC scans
     // only, the pixel kernels read nothing of the planes, so the fill is skipped (the coefficient export shows whole
@@ -417,10 +447,12 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // reads; the planes get them too only for the coefficient export: 2-byte stores 128 bytes apart were measured to
     // cost the DC scan a third of its time and to slow the kernels that run beside it.
     const bool dc_to_planes = refine_in_memory;
-    if (k0 == 0 ? (plan->has_ac || refine_in_memory) : (plan->has_ac && !plan->had_ac))
-        hipLaunchKernelGGL(k_fill_zero, dim3(2048), dim3(256), 0, s, (uint4*)r->d.coef, coef_bytes / 16);
-    if (k0 == 0 && !plan->dc_complete)                       // a component whose DC scan is not among the scans decoded reads as zero
-        hipLaunchKernelGGL(k_fill_zero, dim3(256), dim3(256), 0, s, (uint4*)r->d.dc, (r->coef_off[n] / 64 * sizeof(int16_t) + 15) / 16);
+    FillList fill{};
+    if (k0 == 0 ? (plan->has_ac || refine_in_memory) : (plan->has_ac && !plan->had_ac)) { fill.p[0] = (uint4*)r->d.coef; fill.n16[0] = coef_bytes / 16; }
+    if (k0 == 0 && !plan->dc_complete) {                     // a component whose DC scan is not among the scans decoded reads as zero
+        fill.p[1] = (uint4*)r->d.dc; fill.n16[1] = (r->coef_off[n] / 64 * sizeof(int16_t) + 15) / 16;
+    }
+    launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, s);
     mark(r, PCR_STAGE_UNSTUFF, s);
     const uint32_t* c32 = reinterpret_cast<const uint32_t*>(r->d.clean);
     const uint64_t* h64 = r->d.masks;
@@ -639,7 +671,7 @@ static int alloc_descriptor_buffers(pcr_record* r, hipStream_t s) {
     if (!rc && hipMemsetAsync(d.off, 0, ng * sizeof(uint32_t), s) != hipSuccess) rc = PCR_E_DEVICE;
     if (!rc && hipMemsetAsync(d.scan, 0, ng * sizeof(ScanDesc), s) != hipSuccess) rc = PCR_E_DEVICE;
     if (!rc && hipMemsetAsync(d.img, 0, (size_t)n * sizeof(ImgDesc), s) != hipSuccess) rc = PCR_E_DEVICE;
-    d.n = n; d.G = G;
+    d.n = n; d.G = G; d.nbytes = r->nbytes;
     d.len = (const uint32_t*)(d.rec + hdr_len_pos(n, G, 0, 0));
     d.nscans = (const uint32_t*)(d.rec + hdr_nscans_pos(n, G, 0));
     return rc;
