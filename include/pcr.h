@@ -404,7 +404,8 @@ int pcr_set_lane_decoders(pcr_record* rec, int mode);
 int pcr_last_decoder_shapes(pcr_record* rec, int* lane_launches, int* wavefront_launches);
 
 /* Stage timing with HIP events recorded on the call's own stream (off by default; switching it on
- * starts a new history).  A stage is one kernel or a short run of kernels:
+ * starts a new history).  While it is on, every stage has launches of its own; without it, scans for the wavefront
+ * decoders share one launch where they can, whatever their stage.  A stage is one kernel or a short run of kernels:
  *   INDEX_PARSE    k_index + k_headers               UNSTUFF        k_unstuff + zero fills
  *   DC_FIRST, AC_FIRST, AC_REFINE, REFINE_BLOCKS, SEQUENTIAL     one interval per launch of that kernel (DC_FIRST, AC_FIRST,
  *                  AC_REFINE: of either decoder shape; REFINE_BLOCKS: k_refine_blocks after a wavefront-per-unit launch, k_refine_history

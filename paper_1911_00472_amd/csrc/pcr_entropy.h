@@ -414,6 +414,18 @@ struct LaneScan {
 };
 
 // ---------------------------------------------------------------------------------------
+// How a decoder keeps in step with decoders of other scans of the same blocks that run at the same time (see ChainGate in
+// pcr_kernels.h): need(m) before anything of block m of the scan is read that an earlier scan wrote, publish(m) once
+// everything the decoder has stored lies in blocks before m or may be seen later, due(bits): whether now is a time to.
+// FreeRun: alone, everything it reads was there when it started.
+// ---------------------------------------------------------------------------------------
+struct FreeRun {
+    PCR_HD void need(uint32_t) {}
+    PCR_HD bool due(uint32_t) const { return false; }
+    PCR_HD void publish(uint32_t) {}
+};
+
+// ---------------------------------------------------------------------------------------
 // CoefSink: keeps memory off the serial path.  Every symbol the serial part passes goes, as (element
 // index, packed word with the value in its top 16 bits), into two vector registers, in the lane whose
 // number is the window offset the symbol STARTS at: symbols that start inside one window start at
@@ -771,7 +783,8 @@ PCR_HD uint32_t ac_first_symbols(WindowReader* wr, IndexSink* sink, uint32_t* kb
     return info;
 }
 
-PCR_HD int decode_ac_first(WindowReader* wr, const LaneScan& ls, IndexSink* sink) {
+template <class Gate>
+PCR_HD int decode_ac_first(WindowReader* wr, const LaneScan& ls, IndexSink* sink, Gate& gate) {
     const uint32_t Ss = (uint32_t)ls.Ss, Se = (uint32_t)ls.Se;
     const uint32_t bw = ls.bw[0], mcu_w = ls.mcu_w;
     // Positions are kept biased: kb = (zig-zag position of the next candidate) + bias with bias = 63 - Se,
@@ -786,11 +799,14 @@ PCR_HD int decode_ac_first(WindowReader* wr, const LaneScan& ls, IndexSink* sink
     uint32_t kb = Ss + bias;
     uint32_t bad = 0;
     const uint32_t adv_mask = opaque(127u), tot_field = opaque((6u << 16) | 8u);
+    uint32_t stored = 0;                                     // the coefficients of blocks before this one have been stored a window ago
     while (left != 0) {
         if (wr->exhausted()) {
             bad |= wr->overrun_bit();                        // never walk far beyond the unit's data
+            if (gate.due(wr->wbase)) gate.publish(stored);   // (ahead of this window's stores: those of the last one have had time to get there)
             const uint32_t words = wr->refill_keep();        // (before the flush: the wait for the words fetched a window ago must not include these stores)
             sink->flush(words);
+            stored = ls.mcu1 - left;
         }
         uint32_t info = opaque(ac_first_symbols(wr, sink, &kb, base_b, adv_mask, tot_field));   // (a scalar: tested on the scalar unit)
         if (kb >= 64) {                                      // the block is finished, or the lanes left the code to us
@@ -821,6 +837,7 @@ PCR_HD int decode_ac_first(WindowReader* wr, const LaneScan& ls, IndexSink* sink
     bad |= wr->overrun_bit();
     return bad ? kEFormat : kOk;
 }
+PCR_HD int decode_ac_first(WindowReader* wr, const LaneScan& ls, IndexSink* sink) { FreeRun g; return decode_ac_first(wr, ls, sink, g); }
 
 // ---------------------------------------------------------------------------------------
 // Sequential (baseline) scan: every block is a DC difference followed by AC run/size pairs up to an end of
@@ -1095,7 +1112,8 @@ PCR_HD void set_bit(uint64_t* m, uint32_t n) {
 // The history of the next block is fetched while the current one is decoded.  Conditions are kept
 // as integer arithmetic and single compares: a boolean widened to an integer, or two conditions
 // and-ed together, cost the compiler a detour through the vector unit or through 64-bit lane masks.
-PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes& hp, uint64_t* recs, size_t nblk) {     // nblk: blocks of the component's plane
+template <class Gate>
+PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes& hp, uint64_t* recs, size_t nblk, Gate& gate) {     // nblk: blocks of the component's plane
     const uint32_t bw = ls.bw[0], mcu_w = ls.mcu_w;
     const uint64_t band = band_mask(ls.Ss, ls.Se);
     const uint32_t top64 = wr->lane == (uint32_t)ls.Se ? kZtLast : 0u;
@@ -1111,9 +1129,11 @@ PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes
     uint32_t fcol = ls.mcu0 % mcu_w;
     uint32_t fblk = (ls.mcu0 / mcu_w) * bw + fcol;
     uint32_t b0 = fblk;
+    gate.need(ls.mcu0);
     HistWords h0 = hist_fetch(hp, b0, wr->lane);
     fblk++; if (++fcol == mcu_w) { fcol = 0; fblk += row_skip; }
     uint32_t b1 = fblk < last_blk ? fblk : last_blk;
+    gate.need(left > 1 ? ls.mcu0 + 1 : ls.mcu0);
     HistWords h1 = hist_fetch(hp, b1, wr->lane);
     ZeroTable zt;
     // One block.  hw, bcur: the block's history and index on entry; on return the fetch for the block two further on
@@ -1127,6 +1147,8 @@ PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes
         left--;
         fblk++; if (++fcol == mcu_w) { fcol = 0; fblk += row_skip; }
         bcur = fblk < last_blk ? fblk : last_blk;
+        const uint32_t m = ls.mcu1 - 1 - left;               // the block's number in the scan
+        gate.need(left > 1 ? m + 2 : ls.mcu1 - 1);
         hw = hist_fetch(hp, bcur, wr->lane);
         const uint64_t start = ((uint64_t)eobrun << 32) | wr->position();
         const uint32_t ncorr = (uint32_t)__builtin_popcountll(h);
@@ -1184,6 +1206,7 @@ PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes
             wr->consume(ncorr);
             eobrun--;
         }
+        gate.publish(m);                                     // (ahead of this block's record: that of the last block has had time to get there)
         recs[ref_word(kRefNz, b, nblk)] = newm; recs[ref_word(kRefStart, b, nblk)] = start; recs[ref_word(kRefHist, b, nblk)] = h;   // (phase 2 and the refinement replay work on the same history)
         bad |= wr->overrun_bit();
         left = bad ? 0 : left;                               // stop at the first damaged block
@@ -1195,6 +1218,7 @@ PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes
     }
     return bad ? kEFormat : kOk;
 }
+PCR_HD int skim_ac_refine(WindowReader* wr, const LaneScan& ls, const HistPlanes& hp, uint64_t* recs, size_t nblk) { FreeRun g; return skim_ac_refine(wr, ls, hp, recs, nblk, g); }
 
 // Phase 2 (data-parallel, one lane per block): decode one block completely from its start.
 //   words, byte_off  the unit's unstuffed data;  st  the block's kRefStart word;  h  history mask;

@@ -2,7 +2,7 @@
 //   k_index      scan-group index (prefix sums of region lengths)
 //   k_headers    JPEG marker parsing and Huffman tables, one workgroup per image
 //   k_unstuff    byte un-stuffing + restart-interval location, one or four wavefronts per (image, scan); zero fills
-//   k_dc_first, k_ac_first, k_ac_refine   progressive Huffman decode, one wavefront per unit: a restart
+//   k_decode_waves   progressive Huffman decode, one wavefront per unit: a restart
 //                interval of a scan, or the stretch between two entry points of the record (the whole scan
 //                where there is neither)
 //   k_refine_blocks   second phase of AC refinement, one lane per block
@@ -266,23 +266,9 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
     // ---- the walk: lane g of the first wavefront takes region g ----
     RegionWalk w{};
     int rc = kOk;
-    uint32_t dht[8], ri = 0;
     if (wave == 0) {
         const uint32_t g = lane;
         if (g < upto) rc = walk_region(bytes_of(g), s_off[g], s_off[g] + s_len[g], g, &w, &s_img);
-        // what is in force at the scan: the last definition in this region or an earlier one
-        const uint64_t upto_me = g >= 63 ? ~0ull : (2ull << g) - 1;
-#pragma unroll
-        for (int t = 0; t < 8; t++) {
-            const uint64_t m = __ballot(g < upto && w.dht[t] != 0) & upto_me;
-            const uint32_t v = (uint32_t)__shfl((int)w.dht[t], m ? 63 - __builtin_clzll(m) : 0);
-            dht[t] = m ? v : 0u;
-        }
-        {
-            const uint64_t m = __ballot(g < upto && w.ri >= 0) & upto_me;
-            const int v = __shfl(w.ri, m ? 63 - __builtin_clzll(m) : 0);
-            ri = m ? (uint32_t)v : 0u;
-        }
 #pragma unroll
         for (int t = 0; t < 4; t++) {
             const uint64_t m = __ballot(g < upto && w.qoff[t] != 0);
@@ -290,9 +276,22 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
             const uint32_t qo = (uint32_t)__shfl((int)w.qoff[t], last), qp = (uint32_t)__shfl((int)w.qprec[t], last);
             if (lane == 0) { s_img.qoff[t] = m ? qo : 0u; s_img.qprec[t] = (uint8_t)(m ? qp : 0u); }
         }
+        // what is in force at the scan: the last definition in this region or an earlier one
+        const uint64_t upto_me = g >= 63 ? ~0ull : (2ull << g) - 1;
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+            const uint64_t m = __ballot(g < upto && w.dht[t] != 0) & upto_me;
+            const uint32_t v = (uint32_t)__shfl((int)w.dht[t], m ? 63 - __builtin_clzll(m) : 0);
+            w.dht[t] = m ? v : 0u;
+        }
+        {
+            const uint64_t m = __ballot(g < upto && w.ri >= 0) & upto_me;
+            const int v = __shfl(w.ri, m ? 63 - __builtin_clzll(m) : 0);
+            w.ri = m ? v : 0;
+        }
     }
     __syncthreads();                                        // (the frame header is lane 0's)
-    if (wave == 0 && lane < upto && rc == kOk) rc = resolve_scan(bytes_of(lane), w, s_off[lane] + s_len[lane], dht, ri, &s_img, &s_scan[lane]);
+    if (wave == 0 && lane < upto && rc == kOk) rc = resolve_scan(bytes_of(lane), w, s_off[lane] + s_len[lane], w.dht, (uint32_t)w.ri, &s_img, &s_scan[lane]);
     __syncthreads();
     if (wave == 0) {
         if (lane < upto && rc == kOk) rc = scan_history(s_scan, lane);
@@ -561,7 +560,7 @@ __global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, Uns
 
 // --------------------------------------------------------------------------------------
 // Entropy kernels: ONE WAVEFRONT PER UNIT (a restart interval of one scan of one image).
-// Everything the decoder touches is a function of blockIdx.x alone, i.e. wave-uniform, so the
+// Everything the decoder touches is a function of the block and the wavefront's number in it, i.e. wave-uniform, so the
 // compiler keeps the decoder state in scalar registers and runs it on the scalar ALU with
 // native 64-bit shifts, population counts and find-first-set; the Huffman table sits in LDS.
 // A serial bit-stream decoder has no use for 64 lanes, but a lone wavefront issues only about
@@ -573,10 +572,9 @@ __global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, Uns
 // k_ac_first_lanes / k_ac_refine_lanes below, which the host takes for such launches.)
 // --------------------------------------------------------------------------------------
 constexpr int kEntropyLanes = 64;
-// clean32 and hist64 are R.clean and R.masks again, as separate restrict-qualified kernel arguments: the
-// kernels only read the unstuffed data and the history planes of EARLIER scans, and knowing that nothing
-// written here aliases them lets the compiler fetch them with scalar loads (straight into scalar
-// registers, waited for at the first use) instead of vector loads followed by a read-first-lane.
+// clean32 is R.clean again, as a separate restrict-qualified kernel argument: the kernels only read the unstuffed
+// data, and knowing that nothing written here aliases it lets the compiler fetch it with scalar loads (straight into
+// scalar registers, waited for at the first use) instead of vector loads followed by a read-first-lane.
 
 struct UnitSetup {
     const uint32_t* words;        // segment base, unit start and length for the window readers
@@ -731,16 +729,52 @@ PCR_D uint32_t lane_table_slot(const DevRecord& R, const LaneJob& job, uint32_t 
     return slot;
 }
 
-// SHAPE: which DC decoder (dc_shape) the units of this launch take; the host sorts the units by it.
-template <int SHAPE>
-__global__ void __launch_bounds__(kEntropyLanes) k_dc_first(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
-        const uint32_t* __restrict__ clean32, const uint64_t* __restrict__ hist64, uint32_t to_planes) {
-    __shared__ DcTab tabs[kMaxComp];
+// The scans of a component that build on each other -- its AC first scans, then one refinement scan after another -- are
+// decoded side by side by the wavefronts of one workgroup, each following the one before it through the image: a
+// refinement scan needs of a block only what the earlier scans made of that block.  (One launch after the other took the
+// SUM of the scans' times, and a scan's time is that of its longest unit: 2.9 + 4.7 + 6.0 ms for photographs without
+// entry points; side by side they take about the longest of them.)
+//
+// done[w]: blocks of the scan that wavefront w has finished and whose results are in memory (a workgroup's wavefronts run
+// on one compute unit and share its vector cache: no more than the order of the operations is needed to see them).  A
+// wavefront waits only for wavefronts before it in the chain, and every wavefront ends by releasing all of its blocks,
+// whatever became of its unit: every wait ends.
+constexpr uint32_t kChainWaves = 8;
+struct UnitChain { uint32_t first, count; uint64_t waits; };     // units [first, first + count), a wavefront each; byte w of waits: the earlier wavefronts that wavefront w follows
+
+struct ChainGate {
+    uint32_t* done;
+    uint32_t self, waits;
+    bool watched;                                             // some wavefront follows this one
+    uint32_t avail;                                           // blocks before this one have been released by all this wavefront follows
+    PCR_D void need(uint32_t m) {
+        if (m < avail) return;
+        for (;;) {
+            uint32_t least = ~0u;
+            for (uint32_t w = waits; w; w &= w - 1) {
+                const uint32_t d = uni(__hip_atomic_load(&done[__builtin_ctz(w)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+                least = d < least ? d : least;
+            }
+            avail = least;
+            if (m < avail) break;
+            __builtin_amdgcn_s_sleep(4);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+    PCR_D bool due(uint32_t bits) const { return watched && ((bits >> 6) & 3u) == 0; }      // (every fourth window)
+    PCR_D void publish(uint32_t m) {
+        if (!watched) return;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __hip_atomic_store(&done[self], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+
+// What a wavefront keeps in LDS: the AC table of its scan, or the DC tables of its components.
+constexpr uint32_t kWaveTabBytes = sizeof(AcTab);
+static_assert(kMaxComp * sizeof(DcTab) <= kWaveTabBytes, "one area serves both");
+
+PCR_D int wave_dc_first(const DevRecord& R, const Unit& un, const UnitSetup& L, DcTab* tabs, uint32_t lane, bool to_planes) {
     dc_kernel_priority();
-    const Unit un = units[blockIdx.x];
-    UnitSetup L;
-    unit_setup(R, un, clean32, &L);
-    if (!L.ok) return;
     const ScanDesc* sd = &R.scan[(size_t)un.img * R.G + un.scan];
     const uint32_t o0 = sd->dc_off[0], o1 = L.ls.ns > 1 ? sd->dc_off[1] : o0, o2 = L.ls.ns > 2 ? sd->dc_off[2] : o0;
     // distinct tables of the scan's components: slot 0 always, slot 1/2 when a component uses another one
@@ -751,46 +785,81 @@ __global__ void __launch_bounds__(kEntropyLanes) k_dc_first(DevRecord R, const U
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.dctabs[R.dctab_idx[(size_t)un.img * R.G + un.scan]]);
         uint32_t* dst = reinterpret_cast<uint32_t*>(&tabs[0]);
         constexpr uint32_t kWords = sizeof(DcTab) / 4;
-        for (uint32_t e = threadIdx.x; e < kWords; e += kEntropyLanes) {
+        for (uint32_t e = lane; e < kWords; e += kEntropyLanes) {
             dst[e] = src[e];
             if (tj1 == 1) dst[kWords + e] = src[kWords + e];
             if (tj2 != 0 && tj2 != tj1) dst[(uint32_t)tj2 * kWords + e] = src[2 * kWords + e];
         }
     }
-    __syncthreads();
+    wave_sync();
     DcWindowReader wr;                                      // tables by scan component
-    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, &tabs[0], &tabs[uni(tj1)], &tabs[uni(tj2)], L.ls.ns, threadIdx.x);
+    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, &tabs[0], &tabs[uni(tj1)], &tabs[uni(tj2)], L.ls.ns, lane);
     CoefSink sink;
     // (to_planes = 0: only the compact copy, one value per block -- all a decode without AC scans and refinements reads)
     sink.init(to_planes ? L.base : nullptr, L.base_elems, L.ls.Al, R.dc + (uni((uint64_t)R.coef_off[un.img]) >> 6));
-    int rc = kEFormat;                                      // (a unit in the wrong launch: the descriptors disagree with the host's)
-    if (dc_shape(L.ls.ns, L.ls.hs[0], L.ls.vs[0], L.ls.hs[1], L.ls.vs[1], L.ls.hs[2], L.ls.vs[2]) == SHAPE) rc = decode_dc_first_as<SHAPE>(&wr, L.ls, &sink);
-    if (rc != kOk) R.status[un.img] = rc;
+    return decode_dc_first(&wr, L.ls, &sink);
 }
 
-// The AC table of a unit's scan (built by k_headers) into LDS.  Call with every lane of the wavefront.
-PCR_D void load_ac_table(const DevRecord& R, size_t ig, AcTab* tab) {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.tabs[R.tab_idx[ig]]);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(tab);
-    for (uint32_t e = threadIdx.x; e < sizeof(AcTab) / 4; e += kEntropyLanes) dst[e] = src[e];
-    __syncthreads();
+PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab* tab, uint32_t lane, ChainGate& gate) {
+    const size_t ig = (size_t)un.img * R.G + un.scan;
+    const ScanDesc* sd = &R.scan[ig];
+    {                                                       // the scan's table (built by k_headers)
+        const uint4* src = reinterpret_cast<const uint4*>(&R.tabs[R.tab_idx[ig]]);
+        uint4* dst = reinterpret_cast<uint4*>(tab);
+        for (uint32_t e = lane; e < sizeof(AcTab) / 16; e += kEntropyLanes) dst[e] = src[e];
+    }
+    wave_sync();
+    WindowReader wr;
+    if (sd->Ah == 0) {
+        wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, true, lane, true);
+        IndexSink sink;
+        sink.init(L.plane[0], L.plane_elems[0], L.ls.Al);
+        return decode_ac_first(&wr, L.ls, &sink, gate);
+    }
+    // (the history is read through plain pointers: earlier scans may be writing it in this very launch)
+    HistPlanes hp;
+    hp.coef = L.plane[0];
+    hp.n = sd->nhist;
+#pragma unroll
+    for (int q = 0; q < kMaxHist; q++) hp.p[q] = R.masks + uni((uint64_t)R.mask_off[(size_t)un.img * R.G + sd->hist[q < hp.n ? q : 0]]);
+    hp.n = uni(hp.n);
+    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, false, lane, false);
+    return skim_ac_refine(&wr, L.ls, hp, R.masks + uni((uint64_t)R.mask_off[ig]), L.plane_elems[0] >> 6, gate);
 }
 
-__global__ void __launch_bounds__(kEntropyLanes) k_ac_first(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
-        const uint32_t* __restrict__ clean32, const uint64_t* __restrict__ hist64) {
-    __shared__ AcTab tab;
-    const Unit un = units[blockIdx.x];
+// Workgroup b: chain b of `chains`, or (without them) unit b of `units`, with a wavefront per unit.  Dynamic LDS:
+// kWaveTabBytes per wavefront.  ROLES: which kinds of scans there may be among them (each kind on its own leaves the
+// scalar registers to it).
+constexpr int kWavesDc = 1, kWavesAc = 2;
+template <int ROLES>
+__global__ void __launch_bounds__(kEntropyLanes * kChainWaves) k_decode_waves(DevRecord R, const Unit* __restrict__ units, const UnitChain* __restrict__ chains,
+        const uint32_t* __restrict__ clean32, uint32_t to_planes) {
+    extern __shared__ uint4 wave_tabs[];
+    __shared__ uint32_t done[kChainWaves];
+    const uint32_t wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    UnitChain ch{blockIdx.x, 1, 0};
+    if (chains) {
+        ch = chains[blockIdx.x];
+        if (threadIdx.x < kChainWaves) done[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    if (wave >= ch.count) return;
+    uint64_t all = ch.waits | (ch.waits >> 32);
+    all |= all >> 16; all |= all >> 8;
+    ChainGate gate{done, wave, (uint32_t)(ch.waits >> (8 * wave)) & 255u, ((all >> wave) & 1u) != 0, 0u};
+    if (gate.waits == 0) gate.avail = ~0u;
+    const Unit un = units[ch.first + wave];
     UnitSetup L;
     unit_setup(R, un, clean32, &L);
-    if (!L.ok) return;
-    const size_t ig = (size_t)un.img * R.G + un.scan;
-    load_ac_table(R, ig, &tab);
-    WindowReader wr;
-    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, &tab, true, threadIdx.x, true);
-    IndexSink sink;
-    sink.init(L.plane[0], L.plane_elems[0], L.ls.Al);
-    int rc = decode_ac_first(&wr, L.ls, &sink);
-    if (rc != kOk) R.status[un.img] = rc;
+    if (L.ok) {
+        uint4* mine = wave_tabs + wave * (kWaveTabBytes / 16);
+        const ScanDesc* sd = &R.scan[(size_t)un.img * R.G + un.scan];
+        int rc = kEFormat;                                    // (a unit in the wrong launch: the descriptors disagree with the host's)
+        if (uni((int)sd->Ss) > 0) { if (ROLES & kWavesAc) rc = wave_ac(R, un, L, reinterpret_cast<AcTab*>(mine), lane, gate); }
+        else if ((ROLES & kWavesDc) && uni((int)sd->Ah) == 0 && R.img[un.img].progressive) rc = wave_dc_first(R, un, L, reinterpret_cast<DcTab*>(mine), lane, to_planes != 0);
+        if (rc != kOk) R.status[un.img] = rc;
+    }
+    gate.publish(~0u);
 }
 
 // The same scan kind with one LANE per unit (pcr_lanes.h).  One wavefront per job: up to 64 consecutive units of the
@@ -916,8 +985,8 @@ __global__ void __launch_bounds__(kEntropyLanes) k_dc_first_lanes(DevRecord R, c
 }
 
 // Sequential (baseline) scans: the DC and AC tables of every scan component, once per distinct table.
-__global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
-        const uint32_t* __restrict__ clean32, const uint64_t* __restrict__ hist64) {
+__global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const Unit* __restrict__ units,
+        const uint32_t* __restrict__ clean32) {
     __shared__ DcTab dtabs[kMaxComp];
     __shared__ AcTab atabs[kMaxComp];
     const Unit un = units[blockIdx.x];
@@ -957,32 +1026,6 @@ __global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const
 }
 
 struct ApplyUnit { uint32_t img; uint32_t comp; };
-
-__global__ void __launch_bounds__(kEntropyLanes) k_ac_refine(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
-        const uint32_t* __restrict__ clean32, const uint64_t* __restrict__ hist64) {
-    __shared__ AcTab tab;
-    const Unit un = units[blockIdx.x];
-    UnitSetup L;
-    unit_setup(R, un, clean32, &L);
-    if (!L.ok) return;
-    const size_t ig = (size_t)un.img * R.G + un.scan;
-    const ScanDesc* sd = &R.scan[ig];
-    load_ac_table(R, ig, &tab);
-    HistPlanes hp;
-    hp.coef = L.plane[0];
-    hp.n = sd->nhist;
-#pragma unroll
-    for (int q = 0; q < kMaxHist; q++) hp.p[q] = hist64 + uni((uint64_t)R.mask_off[(size_t)un.img * R.G + sd->hist[q < hp.n ? q : 0]]);
-    hp.n = uni(hp.n);
-    const ImgDesc* img = &R.img[un.img];
-    const int c = sd->comp[0];
-    const size_t plane = (size_t)uni((uint32_t)img->bw[c]) * uni((uint32_t)img->bh[c]);
-    uint64_t* mk = R.masks + uni((uint64_t)R.mask_off[ig]);
-    WindowReader wr;
-    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, &tab, false, threadIdx.x, false);
-    int rc = skim_ac_refine(&wr, L.ls, hp, mk, plane);
-    if (rc != kOk) R.status[un.img] = rc;
-}
 
 // Phase 2 of AC refinement: one lane per block of the scan.
 struct RefineScan { uint32_t img; uint32_t scan; };

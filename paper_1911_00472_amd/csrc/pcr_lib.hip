@@ -31,15 +31,20 @@ namespace {
 enum Kind { kDcFirst = 0, kAcFirst = 1, kAcRefine = 2, kSequential = 3, kNumKinds = 4 };
 struct LevelList {
     Unit* d_units = nullptr; uint32_t n = 0; int kind = 0;
-    int shape = 0;                                                               // DC first scans: dc_shape of the units
+    uint32_t level = 0;                                                          // (0-based)
     RefineScan* d_refine = nullptr; uint32_t n_refine = 0;                      // the scans of an AC refinement launch, for its per-block kernels
     RefineTile* d_plane_tiles = nullptr; uint32_t n_plane_tiles = 0;              // k_refine_history: chunks of the padded planes of those scans
     RefineTile* d_cov_tiles = nullptr; uint32_t n_cov_tiles = 0;                  // k_refine_deal, k_refine_blocks: chunks of the blocks the images cover
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
+    bool chained = false;                                                        // the plan's chains hold these units too
 };
 
 struct Plan {                               // launch geometry for one scan group k
     std::vector<LevelList> levels;
+    // the scans decoded side by side (k_decode_waves): AC chains first, the DC units (chains of one) behind them
+    Unit* d_chain_units = nullptr; UnitChain* d_chains = nullptr; uint32_t n_ac_chains = 0, n_chains = 0, chain_waves = 0;
+    LevelList refined;                       // the refinement scans among them, for k_refine_blocks
+    bool chains_built = false;
     ApplyUnit* d_apply = nullptr; ApplyList* d_apply_lists = nullptr; int32_t* d_list_idx = nullptr; uint32_t n_apply = 0, apply_grid_x = 0;
     bool has_ac = false;                     // some scan <= k is an AC scan (else only element 0 of every block is ever touched)
     bool had_ac = false;                     // ... some scan <= k0 (the fidelity an upgrade starts from)
@@ -172,6 +177,120 @@ void compute_levels(pcr_record* r) {
     }
 }
 
+// The work lists of the per-block kernels of refinement scans.
+int refine_tiles(pcr_record* r, const std::vector<RefineScan>& rl, LevelList* ll, bool planes_too) {
+    const uint32_t G = r->hdr.G;
+    ll->n_refine = (uint32_t)rl.size();
+    int rc = arena_upload(&r->big, &ll->d_refine, rl); if (rc) return rc;
+    std::vector<RefineTile> plane_tiles, cov_tiles;
+    for (uint32_t e = 0; e < ll->n_refine; e++) {
+        const ImgDesc& im = r->img[rl[e].img];
+        const int c = r->scan[(size_t)rl[e].img * G + rl[e].scan].comp[0];
+        const uint32_t plane = (uint32_t)im.bw[c] * im.bh[c], cov = (uint32_t)im.cw[c] * im.ch[c];
+        if (planes_too) for (uint32_t ch = 0; ch * 256 < plane; ch++) plane_tiles.push_back(RefineTile{e, ch});
+        for (uint32_t ch = 0; ch * 256 < cov; ch++) cov_tiles.push_back(RefineTile{e, ch});
+    }
+    ll->n_plane_tiles = (uint32_t)plane_tiles.size(); ll->n_cov_tiles = (uint32_t)cov_tiles.size();
+    if (ll->n_plane_tiles) { rc = arena_upload(&r->big, &ll->d_plane_tiles, plane_tiles); if (rc) return rc; }
+    if (ll->n_cov_tiles) { rc = arena_upload(&r->big, &ll->d_cov_tiles, cov_tiles); if (rc) return rc; }
+    return PCR_OK;
+}
+
+// Scans whose units can be decoded by the wavefronts of one workgroup in step (k_decode_waves): AC scans of one component
+// in file order.  Interval j of each of them has to cover the same blocks, so restart intervals must agree; entry points,
+// which every scan has at places of its own, rule it out where one of the scans builds on another.
+struct ChainSet {
+    struct Chain { uint32_t img, cost, units, count, scan[kChainWaves]; uint64_t waits; };      // units: intervals; count: scans
+    std::vector<Chain> ac, dc;
+    bool ordered = false;                                     // some scan builds on another one of the call
+    bool possible = true;
+};
+void chain_scans(const pcr_record* r, uint32_t i, const std::vector<uint32_t>& scans, ChainSet* C) {
+    const uint32_t G = r->hdr.G;
+    auto at = [&](uint32_t g) -> const ScanDesc& { return r->scan[(size_t)i * G + g]; };
+    auto units = [&](uint32_t g) { return r->slot_cnt[(size_t)i * G + g]; };
+    auto cost = [&](uint32_t g) { return at(g).data_len / std::max(1u, units(g)) * (at(g).Ah ? 2u : 1u); };   // (a byte of a refinement scan takes a wavefront about twice as long)
+    std::vector<uint32_t> waits(scans.size(), 0);
+    bool ordered = false, same = scans.size() <= kChainWaves;
+    for (size_t a = 0; a < scans.size(); a++) {
+        const ScanDesc& A = at(scans[a]);
+        if (a > 0) same = same && A.ri == at(scans[0]).ri && units(scans[a]) == units(scans[0]) && r->ent_off_h[(size_t)i * G + scans[a]] == 0 && r->ent_off_h[(size_t)i * G + scans[0]] == 0;
+        for (size_t b = 0; b < a; b++) {
+            const ScanDesc& B = at(scans[b]);
+            if (B.Ss <= A.Se && A.Ss <= B.Se) { ordered = true; if (b < 32) waits[a] |= 1u << b; }
+        }
+    }
+    if (!ordered) {
+        for (uint32_t g : scans) { ChainSet::Chain c{i, cost(g), units(g), 1, {g}, 0}; C->ac.push_back(c); }
+        return;
+    }
+    C->ordered = true;
+    if (!same) { C->possible = false; return; }
+    ChainSet::Chain c{i, 0, units(scans[0]), (uint32_t)scans.size(), {}, 0};
+    for (size_t a = 0; a < scans.size(); a++) {
+        c.scan[a] = scans[a]; c.cost = std::max(c.cost, cost(scans[a]));
+        c.waits |= (uint64_t)waits[a] << (8 * a);
+    }
+    C->ac.push_back(c);
+}
+
+// The chains of a plan (once, when a call first wants them).
+int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
+    if (plan->chains_built) return PCR_OK;
+    const uint32_t n = r->hdr.n, G = r->hdr.G;
+    ChainSet chains;
+    std::vector<uint32_t> comp_scans[kMaxComp];
+    std::vector<RefineScan> refined;
+    auto alone = [&](uint32_t i, uint32_t g) {
+        const size_t ig = (size_t)i * G + g;
+        return ChainSet::Chain{i, r->scan[ig].data_len / std::max(1u, r->slot_cnt[ig]), r->slot_cnt[ig], 1, {g}, 0};
+    };
+    for (uint32_t i = 0; i < n; i++) {
+        for (auto& v : comp_scans) v.clear();
+        for (uint32_t g = (uint32_t)k0; g < std::min<uint32_t>(r->img[i].nscans, (uint32_t)k); g++) {
+            const ScanDesc& sd = r->scan[(size_t)i * G + g];
+            if (is_sequential_scan(sd)) chains.possible = false;
+            else if (sd.Ss > 0) { comp_scans[sd.comp[0]].push_back(g); if (sd.Ah > 0) refined.push_back(RefineScan{i, g}); }
+            else if (sd.Ah == 0) chains.dc.push_back(alone(i, g));
+        }
+        for (const auto& v : comp_scans) if (!v.empty()) chain_scans(r, i, v, &chains);
+    }
+    // A launch for all scans where they can keep in step; otherwise the first scans alone share one, those of level 1,
+    // which wait for nothing (the refinement scans follow level by level).
+    const bool in_step = chains.possible;
+    if (!in_step) {
+        chains.ac.clear(); chains.dc.clear(); refined.clear();
+        for (uint32_t i = 0; i < n; i++)
+            for (uint32_t g = (uint32_t)k0; g < std::min<uint32_t>(r->img[i].nscans, (uint32_t)k); g++) {
+                const size_t ig = (size_t)i * G + g;
+                const ScanDesc& sd = r->scan[ig];
+                if (is_sequential_scan(sd) || sd.Ah > 0 || r->level[ig] != 1) continue;
+                (sd.Ss > 0 ? chains.ac : chains.dc).push_back(alone(i, g));
+            }
+    }
+    for (LevelList& l : plan->levels) l.chained = l.kind != kSequential && (in_step || (l.kind != kAcRefine && l.level == 0));
+    std::vector<Unit> units; std::vector<UnitChain> list;
+    for (auto* set : {&chains.ac, &chains.dc}) {
+        std::stable_sort(set->begin(), set->end(), [](const ChainSet::Chain& a, const ChainSet::Chain& b) { return a.cost > b.cost; });     // the longest first
+        for (const ChainSet::Chain& c : *set) {
+            plan->chain_waves = std::max(plan->chain_waves, c.count);
+            for (uint32_t j = 0; j < c.units; j++) {
+                list.push_back(UnitChain{(uint32_t)units.size(), c.count, c.waits});
+                for (uint32_t a = 0; a < c.count; a++) units.push_back(Unit{c.img, c.scan[a], j, r->slot_base[(size_t)c.img * G + c.scan[a]]});
+            }
+        }
+        if (set == &chains.ac) plan->n_ac_chains = (uint32_t)list.size();
+    }
+    plan->n_chains = (uint32_t)list.size();
+    if (plan->n_chains) {
+        int rc = arena_upload(&r->big, &plan->d_chain_units, units); if (rc) return rc;
+        rc = arena_upload(&r->big, &plan->d_chains, list); if (rc) return rc;
+    }
+    if (!refined.empty()) { const int rc = refine_tiles(r, refined, &plan->refined, false); if (rc) return rc; }
+    plan->chains_built = true;
+    return PCR_OK;
+}
+
 // Launch geometry for decoding scan groups k0+1 .. k (k0 = 0: from scratch) and turning groups 1 .. k into pixels.
 int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     const int key = k0 * 256 + k;
@@ -180,8 +299,8 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     const uint32_t n = r->hdr.n, G = r->hdr.G;
     Plan plan;
     struct Item { Unit u; uint32_t bytes; uint32_t bits; };      // bytes: the scan's mean per unit; bits: the unit's own, if known
-    // one list per (dependency level, kind of scan, DC decoder shape: 0 for the AC kinds)
-    std::vector<std::vector<Item>> lists((size_t)r->max_level * kNumKinds * kDcShapes);
+    // one list per (dependency level, kind of scan)
+    std::vector<std::vector<Item>> lists((size_t)r->max_level * kNumKinds);
     // ... and, per list, the runs of units that belong to one scan (first item, count, the scan's mean bytes per unit):
     // ordering a list scan by scan moves whole runs, a few thousand of them, not hundreds of thousands of units
     struct Run { uint32_t first, count, bytes; };
@@ -202,17 +321,9 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             if (g < (uint32_t)k0) continue;                    // decoded by an earlier call
             if (sd.Ss == 0 && sd.Ah > 0) continue;             // DC refinement has no serial decode
             const int kind = seq ? kSequential : (sd.Ss == 0 ? kDcFirst : (sd.Ah == 0 ? kAcFirst : kAcRefine));
-            if (kind == kAcRefine) {
-                rlists[r->level[ig] - 1].push_back(RefineScan{i, g});
-            }
-            int shape = 0;
-            if (kind == kDcFirst) {
-                uint32_t hs[kMaxComp] = {1, 1, 1}, vs[kMaxComp] = {1, 1, 1};
-                for (int j = 0; j < sd.ns && j < kMaxComp; j++) { hs[j] = r->img[i].hs[sd.comp[j]]; vs[j] = r->img[i].vs[sd.comp[j]]; }
-                shape = dc_shape(sd.ns, hs[0], vs[0], hs[1], vs[1], hs[2], vs[2]);
-            }
+            if (kind == kAcRefine) rlists[r->level[ig] - 1].push_back(RefineScan{i, g});
             const uint32_t cnt = r->slot_cnt[ig];
-            const size_t li = ((size_t)(r->level[ig] - 1) * kNumKinds + kind) * kDcShapes + shape;
+            const size_t li = (size_t)(r->level[ig] - 1) * kNumKinds + kind;
             if (cnt) runs[li].push_back(Run{(uint32_t)lists[li].size(), cnt, sd.data_len / cnt});
             for (uint32_t j = 0; j < cnt; j++)
                 lists[li].push_back(Item{Unit{i, g, j, r->slot_base[ig]}, sd.data_len / cnt, r->unit_bits.empty() ? sd.data_len / cnt * 8 : r->unit_bits[r->slot_base[ig] + j]});
@@ -233,7 +344,7 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             for (const Run& q : rn) l.insert(l.end(), lists[li].begin() + q.first, lists[li].begin() + q.first + q.count);
             std::vector<Item>().swap(lists[li]);
         }
-        const int kind_of_list = (int)((li / kDcShapes) % kNumKinds);
+        const int kind_of_list = (int)(li % kNumKinds);
         std::vector<LaneJob> jobs;
         if (kind_of_list == kAcFirst || kind_of_list == kAcRefine) {
             // Jobs of the lane-per-unit kernels.  A wavefront takes as long as its longest lane, and it holds kLaneTabs
@@ -263,28 +374,16 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         }
         std::vector<Unit> units(l.size());
         for (size_t e = 0; e < l.size(); e++) units[e] = l[e].u;
-        LevelList ll; ll.n = (uint32_t)units.size(); ll.kind = kind_of_list; ll.shape = (int)(li % kDcShapes);
+        LevelList ll; ll.n = (uint32_t)units.size(); ll.kind = kind_of_list;
+        ll.level = (uint32_t)(li / kNumKinds);
         int rc = arena_upload(&r->big, &ll.d_units, units); if (rc) return rc;
         if (!jobs.empty()) {
             ll.n_jobs = (uint32_t)jobs.size();
             rc = arena_upload(&r->big, &ll.d_jobs, jobs); if (rc) return rc;
         }
         if (ll.kind == kAcRefine) {
-            const size_t lv = li / kDcShapes / kNumKinds;
-            const auto& rl = rlists[lv];
-            ll.n_refine = (uint32_t)rl.size();
-            rc = arena_upload(&r->big, &ll.d_refine, rl); if (rc) return rc;
-            std::vector<RefineTile> plane_tiles, cov_tiles;
-            for (uint32_t e = 0; e < ll.n_refine; e++) {
-                const ImgDesc& im = r->img[rl[e].img];
-                const int c = r->scan[(size_t)rl[e].img * G + rl[e].scan].comp[0];
-                const uint32_t plane = (uint32_t)im.bw[c] * im.bh[c], cov = (uint32_t)im.cw[c] * im.ch[c];
-                for (uint32_t ch = 0; ch * 256 < plane; ch++) plane_tiles.push_back(RefineTile{e, ch});
-                for (uint32_t ch = 0; ch * 256 < cov; ch++) cov_tiles.push_back(RefineTile{e, ch});
-            }
-            ll.n_plane_tiles = (uint32_t)plane_tiles.size(); ll.n_cov_tiles = (uint32_t)cov_tiles.size();
-            if (ll.n_plane_tiles) { rc = arena_upload(&r->big, &ll.d_plane_tiles, plane_tiles); if (rc) return rc; }
-            if (ll.n_cov_tiles) { rc = arena_upload(&r->big, &ll.d_cov_tiles, cov_tiles); if (rc) return rc; }
+            const auto& rl = rlists[li / kNumKinds];
+            rc = refine_tiles(r, rl, &ll, true); if (rc) return rc;
         }
         plan.levels.push_back(ll);
     }
@@ -429,13 +528,30 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // of DC first scans of this call goes to the lanes their tables are not built, and with DC first scans only, none are)
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
     bool dc_tables = false;
-    std::vector<char> dc_by_lanes(plan->levels.size(), 0);
+    std::vector<char> by_lanes(plan->levels.size(), 0);
+    r->last_lane_launches = r->last_wave_launches = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
-        if (l.kind != kDcFirst || !l.n) continue;
-        dc_by_lanes[li] = dc_lanes_pay(r, l) ? 1 : 0;
-        if (!dc_by_lanes[li]) dc_tables = true;
+        if (l.kind == kDcFirst) {
+            by_lanes[li] = dc_lanes_pay(r, l) ? 1 : 0;
+            if (!by_lanes[li]) dc_tables = true;
+        } else if (l.kind != kSequential) {
+            by_lanes[li] = lanes_pay(r, l) ? 1 : 0;
+            if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
+        }
     }
+    // Scans side by side where the AC scans are for the wavefront decoders (DC first scans may go to the lanes by themselves);
+    // with stage timing on, whose intervals are those of single stages, one after the other.
+    bool side_by_side = r->last_wave_launches > 0 && r->last_lane_launches == 0 && !r->timing;
+    if (side_by_side && !plan->chains_built) {               // (which copies to the device: not into a stream that is being captured)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone) side_by_side = false;
+        else if ((rc = build_chains(r, k0, k, plan)) != PCR_OK) return rc;
+    }
+    side_by_side = side_by_side && plan->n_ac_chains > 0;
+    bool dc_beside = side_by_side;
+    for (size_t li = 0; li < plan->levels.size(); li++)
+        if (plan->levels[li].kind == kDcFirst && (by_lanes[li] || !plan->levels[li].chained)) dc_beside = false;
     launch_headers(r, (uint32_t)k, k0 > 0, dc_tables || plan->has_ac ? (uint32_t)k0 : (uint32_t)k, dc_tables, s);
     mark(r, PCR_STAGE_INDEX_PARSE, s);
     const size_t coef_bytes = r->coef_off[n] * sizeof(int16_t);
@@ -455,34 +571,33 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, s);
     mark(r, PCR_STAGE_UNSTUFF, s);
     const uint32_t* c32 = reinterpret_cast<const uint32_t*>(r->d.clean);
-    const uint64_t* h64 = r->d.masks;
-    r->last_lane_launches = r->last_wave_launches = 0;
+    auto waves = [&](const LevelList& l) {
+        hipLaunchKernelGGL(l.kind == kDcFirst ? k_decode_waves<kWavesDc> : k_decode_waves<kWavesAc>, dim3(l.n), dim3(kEntropyLanes), kWaveTabBytes, s, r->d, l.d_units,
+                           (const UnitChain*)nullptr, c32, dc_to_planes ? 1u : 0u);
+    };
+    if (side_by_side) {
+        const uint32_t w = plan->chain_waves;
+        hipLaunchKernelGGL(dc_beside ? k_decode_waves<kWavesDc | kWavesAc> : k_decode_waves<kWavesAc>, dim3(dc_beside ? plan->n_chains : plan->n_ac_chains), dim3(kEntropyLanes * w), w * kWaveTabBytes, s, r->d,
+                           plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u);
+        const LevelList& f = plan->refined;
+        if (f.n_cov_tiles) hipLaunchKernelGGL(k_refine_blocks, dim3(f.n_cov_tiles), dim3(256), 0, s, r->d, f.d_refine, f.d_cov_tiles);
+    }
     for (size_t li = 0; li < plan->levels.size(); li++) {
         auto& l = plan->levels[li];
-        const dim3 grid(l.n), block(kEntropyLanes);
-        if (l.kind == kAcFirst || l.kind == kAcRefine) { if (lanes_pay(r, l)) r->last_lane_launches++; else r->last_wave_launches++; }
-        if (l.kind == kDcFirst && dc_by_lanes[li]) {
-            hipLaunchKernelGGL(k_dc_first_lanes, dim3((l.n + kEntropyLanes - 1) / kEntropyLanes), block, 0, s, r->d, l.d_units, l.n, c32, dc_to_planes ? 1u : 0u);
+        if (side_by_side && l.chained && (l.kind != kDcFirst || dc_beside)) continue;
+        const dim3 block(kEntropyLanes);
+        if (l.kind == kDcFirst) {
+            if (by_lanes[li]) hipLaunchKernelGGL(k_dc_first_lanes, dim3((l.n + kEntropyLanes - 1) / kEntropyLanes), block, 0, s, r->d, l.d_units, l.n, c32, dc_to_planes ? 1u : 0u);
+            else waves(l);
             mark(r, PCR_STAGE_DC_FIRST, s);
         }
-        else if (l.kind == kDcFirst) {
-            const uint32_t dcp = dc_to_planes ? 1u : 0u;
-            switch (l.shape) {
-                case 1: hipLaunchKernelGGL(k_dc_first<1>, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64, dcp); break;
-                case 2: hipLaunchKernelGGL(k_dc_first<2>, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64, dcp); break;
-                case 3: hipLaunchKernelGGL(k_dc_first<3>, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64, dcp); break;
-                case 4: hipLaunchKernelGGL(k_dc_first<4>, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64, dcp); break;
-                default: hipLaunchKernelGGL(k_dc_first<0>, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64, dcp); break;
-            }
-            mark(r, PCR_STAGE_DC_FIRST, s);
-        }
-        else if (l.kind == kSequential) { hipLaunchKernelGGL(k_sequential, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64); mark(r, PCR_STAGE_SEQUENTIAL, s); }
+        else if (l.kind == kSequential) { hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, c32); mark(r, PCR_STAGE_SEQUENTIAL, s); }
         else if (l.kind == kAcFirst) {
-            if (lanes_pay(r, l)) hipLaunchKernelGGL(k_ac_first_lanes, dim3(l.n_jobs), block, 0, s, r->d, l.d_units, l.d_jobs, c32);
-            else hipLaunchKernelGGL(k_ac_first, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64);
+            if (by_lanes[li]) hipLaunchKernelGGL(k_ac_first_lanes, dim3(l.n_jobs), block, 0, s, r->d, l.d_units, l.d_jobs, c32);
+            else waves(l);
             mark(r, PCR_STAGE_AC_FIRST, s);
         }
-        else if (lanes_pay(r, l)) {
+        else if (by_lanes[li]) {
             if (l.n_plane_tiles) hipLaunchKernelGGL(k_refine_history, dim3(l.n_plane_tiles), dim3(256), 0, s, r->d, l.d_refine, l.d_plane_tiles);
             mark(r, PCR_STAGE_REFINE_BLOCKS, s);
             hipLaunchKernelGGL(k_ac_refine_lanes, dim3(l.n_jobs), block, 0, s, r->d, l.d_units, l.d_jobs, c32);
@@ -491,7 +606,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
             mark(r, PCR_STAGE_REFINE_BLOCKS, s);
         }
         else {
-            hipLaunchKernelGGL(k_ac_refine, grid, block, 0, s, r->d, l.d_units, l.n, c32, h64);
+            waves(l);
             mark(r, PCR_STAGE_AC_REFINE, s);
             if (l.n_cov_tiles) hipLaunchKernelGGL(k_refine_blocks, dim3(l.n_cov_tiles), dim3(256), 0, s, r->d, l.d_refine, l.d_cov_tiles);
             mark(r, PCR_STAGE_REFINE_BLOCKS, s);
