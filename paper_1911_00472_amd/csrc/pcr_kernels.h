@@ -984,11 +984,13 @@ __global__ void __launch_bounds__(kEntropyLanes) k_dc_first_lanes(DevRecord R, c
     if (rc != kOk) R.status[un.img] = rc;
 }
 
-// Sequential (baseline) scans: the DC and AC tables of every scan component, once per distinct table.
-__global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const Unit* __restrict__ units,
+// Sequential (baseline) scans: the DC and AC tables of every scan component, once per distinct table.  done (may be null): the
+// units k_sequential_split has dealt with.
+__global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const Unit* __restrict__ units, const uint32_t* __restrict__ done,
         const uint32_t* __restrict__ clean32) {
     __shared__ DcTab dtabs[kMaxComp];
     __shared__ AcTab atabs[kMaxComp];
+    if (done && done[blockIdx.x]) return;
     const Unit un = units[blockIdx.x];
     UnitSetup L;
     unit_setup(R, un, clean32, &L);

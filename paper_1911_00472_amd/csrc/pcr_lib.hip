@@ -18,6 +18,7 @@
 
 #include "../../include/pcr.h"
 #include "pcr_kernels.h"
+#include "pcr_sequential.h"
 #include "pcr_hist.h"
 #include "pcr_similarity.h"
 #include "pcr_encode.h"
@@ -36,6 +37,7 @@ struct LevelList {
     RefineTile* d_plane_tiles = nullptr; uint32_t n_plane_tiles = 0;              // k_refine_history: chunks of the padded planes of those scans
     RefineTile* d_cov_tiles = nullptr; uint32_t n_cov_tiles = 0;                  // k_refine_deal, k_refine_blocks: chunks of the blocks the images cover
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
+    uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units k_sequential_split has dealt with
     bool chained = false;                                                        // the plan's chains hold these units too
 };
 
@@ -381,6 +383,9 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             ll.n_jobs = (uint32_t)jobs.size();
             rc = arena_upload(&r->big, &ll.d_jobs, jobs); if (rc) return rc;
         }
+        if (ll.kind == kSequential && (uint64_t)l[0].bytes * 8 >= kSplitLeastBits) {       // (the longest on average come first)
+            rc = arena_alloc(&r->big, &ll.d_done, units.size()); if (rc) return rc;
+        }
         if (ll.kind == kAcRefine) {
             const auto& rl = rlists[li / kNumKinds];
             rc = refine_tiles(r, rl, &ll, true); if (rc) return rc;
@@ -591,7 +596,11 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
             else waves(l);
             mark(r, PCR_STAGE_DC_FIRST, s);
         }
-        else if (l.kind == kSequential) { hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, c32); mark(r, PCR_STAGE_SEQUENTIAL, s); }
+        else if (l.kind == kSequential) {
+            if (l.d_done) hipLaunchKernelGGL(k_sequential_split, dim3(l.n), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
+            hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, (const uint32_t*)l.d_done, c32);
+            mark(r, PCR_STAGE_SEQUENTIAL, s);
+        }
         else if (l.kind == kAcFirst) {
             if (by_lanes[li]) hipLaunchKernelGGL(k_ac_first_lanes, dim3(l.n_jobs), block, 0, s, r->d, l.d_units, l.d_jobs, c32);
             else waves(l);

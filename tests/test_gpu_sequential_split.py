@@ -1,0 +1,77 @@
+"""Long sequential scans, decoded by many lanes per scan (k_sequential_split), against the oracle: around the length it is
+taken from, gray and every sampling layout, several scans per file, streams that never fall into step (left to the
+one-wavefront decoder), codes of the greatest lengths, damaged and truncated data."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1911_00472_amd as pkg
+import pcrgen
+from jpeg_files import planar_sequential
+
+pytestmark = pytest.mark.gpu
+
+
+def _noise(seed, w, h, c, low=0, high=256):
+    return np.random.default_rng(seed).integers(low, high, (h, w, c), dtype=np.uint8)
+
+
+def _coefficients(rec, status=False):
+    with pkg.pcr_open(rec, 0) as r:
+        st = torch.empty(r.n, dtype=torch.int32, device="cuda")
+        pix = r.decode_batch(r.G, status=st).cpu().numpy()
+        return r.decode_coefficients(r.G).cpu().numpy(), r.coef_layout(), st.cpu().numpy(), pix, r.output_layout()
+
+
+def _check(files):
+    rec = pcrgen.write_record(files)
+    coef, lay, st, _, _ = _coefficients(rec)
+    assert (st == 0).all()
+    for i in range(len(files)):
+        want, _, _ = oracle.decode_record_image(rec, i, oracle.record_header(rec)["G"])
+        assert np.array_equal(coef[int(lay[i]):int(lay[i + 1])], want), i
+
+
+@pytest.mark.parametrize("c,hs,vs", [(1, 1, 1), (3, 1, 1), (3, 2, 1), (3, 1, 2), (3, 2, 2)])
+def test_sizes_around_the_line_and_every_layout(c, hs, vs):
+    files = [pcrgen.encode_pixels(_noise(10 * s + c, s, s + 3, c), hs, vs, q, "sequential", restart=0)
+             for s, q in [(8, 90), (40, 60), (45, 90), (52, 92), (61, 96), (150, 75), (233, 97)]]
+    files += [pcrgen.encode_pixels(pcrgen.synth(77 + i, 1 + i % 2, 300 + 37 * i, 280, c, 4.0 + 9 * i), hs, vs, 85, "sequential", restart=0) for i in range(3)]
+    assert min(map(len, files)) < 1500 and sum(len(f) > 2600 for f in files) >= 5
+    _check(files)
+
+
+def test_streams_that_do_not_fall_into_step_and_several_scans():
+    flat = np.full((1024, 1024, 3), 90, np.uint8)
+    half = flat.copy()
+    half[:500] = _noise(1, 1024, 500, 3)
+    stripes = np.tile(np.arange(64, dtype=np.uint8)[None, :, None] * 3, (640, 10, 1))
+    files = [pcrgen.encode_pixels(flat, 2, 2, 90, "sequential", restart=0), pcrgen.encode_pixels(half, 2, 2, 60, "sequential", restart=0),
+             pcrgen.encode_pixels(stripes, 1, 1, 95, "sequential", restart=0), pcrgen.encode_pixels(_noise(5, 250, 250, 3), 2, 2, 100, "sequential", restart=40)]
+    _check(files)
+    _check([planar_sequential(5, 200, 170, 95), planar_sequential(6, 64, 64, 90)])
+
+
+def test_damaged_data_flag_their_image_only():
+    files = [pcrgen.encode_pixels(_noise(900 + i, 150, 141, 3), 2, 2, 90, "sequential", restart=0) for i in range(4)]
+    rec = pcrgen.write_record(files)
+    _, _, st, pix, lay = _coefficients(rec)
+    assert (st == 0).all()
+    with pkg.pcr_open(rec, 0) as r:
+        off, length = r.index()
+    o, n = int(np.asarray(off).reshape(-1)[2]), int(np.asarray(length).reshape(-1)[2])
+    flagged = 0
+    for name, at, fill in [("cut", n - 400, b"\xff\xd9" + bytes(398)), ("ones", n // 2, b"\xff\x00" * 100), ("zeros", n // 2, bytes(200)), ("noise", n // 3, None)]:
+        bad = bytearray(rec)
+        data = fill if fill is not None else bytes(x & 0x7F for x in np.random.default_rng(3).integers(0, 256, 200, dtype=np.uint8))
+        bad[o + at:o + at + len(data)] = data
+        coef, clay, st, p, _ = _coefficients(bytes(bad))
+        assert (np.delete(st, 2) == 0).all(), name
+        flagged += int(st[2] != 0)
+        for i in (0, 1, 3):
+            assert np.array_equal(p[int(lay[i]):int(lay[i + 1])], pix[int(lay[i]):int(lay[i + 1])]), (name, i)
+        if st[2] == 0:
+            want, _, _ = oracle.decode_record_image(bytes(bad), 2, 1)
+            assert np.array_equal(coef[int(clay[2]):int(clay[3])], want), name
+    assert flagged >= 2
