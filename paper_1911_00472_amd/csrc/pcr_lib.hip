@@ -92,13 +92,75 @@ template <class T> int arena_alloc(Arena* a, T** p, size_t count) {
     *p = reinterpret_cast<T*>(q);
     return PCR_OK;
 }
-// (a synchronous copy: the data is on the device when the call returns, whatever stream uses it next)
-template <class T> int arena_upload(Arena* a, T** p, const std::vector<T>& v) {
-    int rc = arena_alloc(a, p, v.size());
-    if (rc) return rc;
-    if (!v.empty() && hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess) return PCR_E_DEVICE;
-    return PCR_OK;
-}
+// Host memory in which tables are put together before they go to the device (pinned where the owner re-uses it).
+struct HostBlock {
+    uint8_t* p = nullptr; size_t cap = 0; bool pinned = false;
+    void release() { if (p) { if (pinned) (void)hipHostFree(p); else free(p); } p = nullptr; cap = 0; }
+    int reserve(size_t bytes, size_t keep) {
+        if (bytes <= cap) return PCR_OK;
+        const size_t want = std::max<size_t>(bytes + bytes / 2, 1u << 16);
+        uint8_t* q = nullptr;
+        if (pinned) { if (hipHostMalloc((void**)&q, want, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); return PCR_E_NOMEM; } }
+        else if (!(q = (uint8_t*)malloc(want))) return PCR_E_NOMEM;
+        if (keep) std::memcpy(q, p, keep);
+        release();
+        p = q; cap = want;
+        return PCR_OK;
+    }
+};
+
+// Tables on their way into an arena, all of them sent by one copy: a synchronous copy of pageable memory costs about
+// 20 us however small it is, and binding a record and planning its decode took 28 of them (0.75 of 1.16 ms of host time
+// for a record of 512 photographs).  flush() is synchronous: the data is on the device when it returns, whatever stream
+// uses it next; flush_on() is not, and the block must stay as it is until the stream got there.
+class Uploads {
+    Arena* a_; HostBlock* h_; size_t used_ = 0; int rc_ = PCR_OK;
+    struct Item { void* p; size_t at; };
+    std::vector<Item> items_;
+    int place(uint8_t** base) {
+        if (rc_) return rc_;
+        if (items_.empty()) return PCR_OK;
+        const int rc = arena_alloc(a_, base, used_);
+        if (rc) return rc;
+        for (const Item& e : items_) { uint8_t* q = *base + e.at; std::memcpy(e.p, &q, sizeof q); }
+        items_.clear();
+        return PCR_OK;
+    }
+public:
+    Uploads(Arena* a, HostBlock* h) : a_(a), h_(h) {}
+    // Room for `count` entries, to be filled in before anything else is added (null: out of memory, as the flush will say).
+    // *p is set by the flush.
+    template <class T> T* make(T** p, size_t count) {
+        *p = nullptr;
+        const size_t room = arena_round(std::max<size_t>(count, 1) * sizeof(T));
+        if (!rc_) rc_ = h_->reserve(used_ + room, used_);
+        if (rc_) return nullptr;
+        T* at = reinterpret_cast<T*>(h_->p + used_);
+        items_.push_back(Item{p, used_});
+        used_ += room;
+        return at;
+    }
+    template <class T> void add(T** p, const std::vector<T>& v) {
+        T* at = make(p, v.size());
+        if (at && !v.empty()) std::memcpy(at, v.data(), v.size() * sizeof(T));
+    }
+    int flush() {
+        uint8_t* base = nullptr;
+        if (items_.empty() && !rc_) return PCR_OK;
+        const size_t bytes = used_;
+        const int rc = place(&base); used_ = 0;
+        if (rc) return rc;
+        return hipMemcpy(base, h_->p, bytes, hipMemcpyHostToDevice) == hipSuccess ? PCR_OK : PCR_E_DEVICE;
+    }
+    int flush_on(hipStream_t s) {
+        uint8_t* base = nullptr;
+        if (items_.empty() && !rc_) return PCR_OK;
+        const size_t bytes = used_;
+        const int rc = place(&base); used_ = 0;
+        if (rc) return rc;
+        return hipMemcpyAsync(base, h_->p, bytes, hipMemcpyHostToDevice, s) == hipSuccess ? PCR_OK : PCR_E_DEVICE;
+    }
+};
 
 }  // namespace
 
@@ -128,6 +190,7 @@ struct pcr_record {
     std::vector<uint32_t> slot_base, slot_cnt;
     uint64_t n_masks = 0; uint32_t n_slots = 0; uint32_t max_level = 0;
     DevRecord d{};
+    HostBlock stage;                        // tables on their way to the device
     Arena small, big;                       // descriptor tables (sized by n and G) / everything sized by the images, and the work lists
     uint8_t* d_rec = nullptr;
     PixelTile* d_tiles = nullptr; uint32_t n_tiles = 0;
@@ -180,10 +243,10 @@ void compute_levels(pcr_record* r) {
 }
 
 // The work lists of the per-block kernels of refinement scans.
-int refine_tiles(pcr_record* r, const std::vector<RefineScan>& rl, LevelList* ll, bool planes_too) {
+void refine_tiles(const pcr_record* r, const std::vector<RefineScan>& rl, LevelList* ll, bool planes_too, Uploads* up) {
     const uint32_t G = r->hdr.G;
     ll->n_refine = (uint32_t)rl.size();
-    int rc = arena_upload(&r->big, &ll->d_refine, rl); if (rc) return rc;
+    up->add(&ll->d_refine, rl);
     std::vector<RefineTile> plane_tiles, cov_tiles;
     for (uint32_t e = 0; e < ll->n_refine; e++) {
         const ImgDesc& im = r->img[rl[e].img];
@@ -193,9 +256,8 @@ int refine_tiles(pcr_record* r, const std::vector<RefineScan>& rl, LevelList* ll
         for (uint32_t ch = 0; ch * 256 < cov; ch++) cov_tiles.push_back(RefineTile{e, ch});
     }
     ll->n_plane_tiles = (uint32_t)plane_tiles.size(); ll->n_cov_tiles = (uint32_t)cov_tiles.size();
-    if (ll->n_plane_tiles) { rc = arena_upload(&r->big, &ll->d_plane_tiles, plane_tiles); if (rc) return rc; }
-    if (ll->n_cov_tiles) { rc = arena_upload(&r->big, &ll->d_cov_tiles, cov_tiles); if (rc) return rc; }
-    return PCR_OK;
+    if (ll->n_plane_tiles) up->add(&ll->d_plane_tiles, plane_tiles);
+    if (ll->n_cov_tiles) up->add(&ll->d_cov_tiles, cov_tiles);
 }
 
 // Scans whose units can be decoded by the wavefronts of one workgroup in step (k_decode_waves): AC scans of one component
@@ -284,11 +346,11 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
         if (set == &chains.ac) plan->n_ac_chains = (uint32_t)list.size();
     }
     plan->n_chains = (uint32_t)list.size();
-    if (plan->n_chains) {
-        int rc = arena_upload(&r->big, &plan->d_chain_units, units); if (rc) return rc;
-        rc = arena_upload(&r->big, &plan->d_chains, list); if (rc) return rc;
-    }
-    if (!refined.empty()) { const int rc = refine_tiles(r, refined, &plan->refined, false); if (rc) return rc; }
+    Uploads up(&r->big, &r->stage);
+    if (plan->n_chains) { up.add(&plan->d_chain_units, units); up.add(&plan->d_chains, list); }
+    if (!refined.empty()) refine_tiles(r, refined, &plan->refined, false, &up);
+    const int rc = up.flush();
+    if (rc) return rc;
     plan->chains_built = true;
     return PCR_OK;
 }
@@ -300,13 +362,10 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     if (it != r->plans.end()) { *out = &it->second; return PCR_OK; }
     const uint32_t n = r->hdr.n, G = r->hdr.G;
     Plan plan;
-    struct Item { Unit u; uint32_t bytes; uint32_t bits; };      // bytes: the scan's mean per unit; bits: the unit's own, if known
-    // one list per (dependency level, kind of scan)
-    std::vector<std::vector<Item>> lists((size_t)r->max_level * kNumKinds);
-    // ... and, per list, the runs of units that belong to one scan (first item, count, the scan's mean bytes per unit):
-    // ordering a list scan by scan moves whole runs, a few thousand of them, not hundreds of thousands of units
-    struct Run { uint32_t first, count, bytes; };
-    std::vector<std::vector<Run>> runs(lists.size());
+    // Per (dependency level, kind of scan), the runs of units that belong to one scan (bytes: the scan's mean per unit):
+    // ordering a list scan by scan moves whole runs, a few thousand of them, not hundreds of thousands of units.
+    struct Run { uint32_t img, scan, count, bytes; };
+    std::vector<std::vector<Run>> runs((size_t)r->max_level * kNumKinds);
     std::vector<std::vector<RefineScan>> rlists(r->max_level);
     std::vector<ApplyUnit> apply; uint32_t max_blk = 0;
     for (uint32_t i = 0; i < n; i++) {
@@ -326,9 +385,7 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             if (kind == kAcRefine) rlists[r->level[ig] - 1].push_back(RefineScan{i, g});
             const uint32_t cnt = r->slot_cnt[ig];
             const size_t li = (size_t)(r->level[ig] - 1) * kNumKinds + kind;
-            if (cnt) runs[li].push_back(Run{(uint32_t)lists[li].size(), cnt, sd.data_len / cnt});
-            for (uint32_t j = 0; j < cnt; j++)
-                lists[li].push_back(Item{Unit{i, g, j, r->slot_base[ig]}, sd.data_len / cnt, r->unit_bits.empty() ? sd.data_len / cnt * 8 : r->unit_bits[r->slot_base[ig] + j]});
+            if (cnt) runs[li].push_back(Run{i, g, cnt, sd.data_len / cnt});
         }
         if (have_dc != (1u << r->img[i].nc) - 1u) plan.dc_complete = false;
         for (int c = 0; c < r->img[i].nc; c++) if (refine[c]) {
@@ -336,72 +393,95 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             max_blk = std::max<uint32_t>(max_blk, (uint32_t)r->img[i].bw[c] * r->img[i].bh[c]);
         }
     }
-    for (size_t li = 0; li < lists.size(); li++) {
-        if (lists[li].empty()) continue;
-        std::vector<Item> l;                                          // the list with the scans of the longest units first
-        {
-            auto& rn = runs[li];
-            std::stable_sort(rn.begin(), rn.end(), [](const Run& a, const Run& b) { return a.bytes > b.bytes; });
-            l.reserve(lists[li].size());
-            for (const Run& q : rn) l.insert(l.end(), lists[li].begin() + q.first, lists[li].begin() + q.first + q.count);
-            std::vector<Item>().swap(lists[li]);
-        }
-        const int kind_of_list = (int)(li % kNumKinds);
+    Uploads up(&r->big, &r->stage);
+    plan.levels.reserve(runs.size());                                // (the uploads keep pointers to its members)
+    std::vector<uint64_t> order;
+    for (size_t li = 0; li < runs.size(); li++) {
+        auto& rn = runs[li];
+        if (rn.empty()) continue;
+        std::stable_sort(rn.begin(), rn.end(), [](const Run& a, const Run& b) { return a.bytes > b.bytes; });   // the scans of the longest units first
+        plan.levels.emplace_back();
+        LevelList& ll = plan.levels.back();
+        ll.kind = (int)(li % kNumKinds);
+        for (const Run& q : rn) ll.n += q.count;
+        Unit* units = up.make(&ll.d_units, ll.n);
+        if (!units) return PCR_E_NOMEM;
         std::vector<LaneJob> jobs;
-        if (kind_of_list == kAcFirst || kind_of_list == kAcRefine) {
-            // Jobs of the lane-per-unit kernels.  A wavefront takes as long as its longest lane, and it holds kLaneTabs
-            // Huffman tables: the list (scan after scan, the scans ordered by their mean unit) is cut into windows of
-            // kLaneTabs scans, the units of a window are ordered by their own length, and every 64 of them are a job.
-            size_t w0 = 0;
-            while (w0 < l.size()) {
-                LaneJob proto{}; size_t w1 = w0;
-                while (w1 < l.size()) {
-                    const uint32_t key = l[w1].u.img * G + l[w1].u.scan;
-                    if (proto.ntab == 0 || proto.key[proto.ntab - 1] != key) {
-                        if (proto.ntab == (uint32_t)kLaneTabs) break;
-                        proto.key[proto.ntab++] = key;
-                    }
-                    w1++;
+        const bool lanes = ll.kind == kAcFirst || ll.kind == kAcRefine;
+        // Jobs of the lane-per-unit kernels.  A wavefront takes as long as its longest lane, and it holds kLaneTabs
+        // Huffman tables: the list (scan after scan, the scans ordered by their mean unit) is cut into windows of
+        // kLaneTabs scans, the units of a window are ordered by their own length, and every 64 of them are a job.
+        // (without the units' own lengths -- a record opened from device memory -- every unit carries its scan's mean,
+        // and the scans are in that order already)
+        static_assert(kLaneTabs <= 8, "three bits tell the scans of a window apart");
+        const bool by_length = lanes && !r->unit_bits.empty();
+        uint32_t at = 0;
+        for (size_t w0 = 0; w0 < rn.size(); w0 += kLaneTabs) {
+            const size_t w1 = std::min(rn.size(), w0 + kLaneTabs);
+            const uint32_t first = at;
+            if (by_length) {
+                order.clear();
+                for (size_t e = w0; e < w1; e++) {
+                    const uint32_t sb = r->slot_base[(size_t)rn[e].img * G + rn[e].scan];
+                    for (uint32_t j = 0; j < rn[e].count; j++)       // the longest first, equal ones in the order of the scans (unit numbers fit 29 bits)
+                        order.push_back((uint64_t)(0xFFFFFFFFu - r->unit_bits[sb + j]) << 32 | (uint64_t)(e - w0) << 29 | j);
                 }
-                // (without the units' own lengths -- a record opened from device memory -- every unit carries its scan's mean,
-                // and the scans are in that order already)
-                if (!r->unit_bits.empty()) std::stable_sort(l.begin() + w0, l.begin() + w1, [](const Item& a, const Item& b) { return a.bits > b.bits; });
-                for (size_t e = w0; e < w1; e += kEntropyLanes) {
-                    LaneJob j = proto;
-                    j.first = (uint32_t)e; j.count = (uint32_t)std::min<size_t>(kEntropyLanes, w1 - e);
-                    jobs.push_back(j);
+                std::sort(order.begin(), order.end());
+                for (uint64_t o : order) {
+                    const Run& q = rn[w0 + (uint32_t)(o >> 29 & 7)];
+                    units[at++] = Unit{q.img, q.scan, (uint32_t)o & 0x1FFFFFFFu, r->slot_base[(size_t)q.img * G + q.scan]};
                 }
-                w0 = w1;
+            } else {
+                for (size_t e = w0; e < w1; e++) {
+                    const uint32_t sb = r->slot_base[(size_t)rn[e].img * G + rn[e].scan];
+                    for (uint32_t j = 0; j < rn[e].count; j++) units[at++] = Unit{rn[e].img, rn[e].scan, j, sb};
+                }
+            }
+            if (!lanes) continue;
+            LaneJob job{};
+            for (size_t e = w0; e < w1; e++) job.key[job.ntab++] = rn[e].img * G + rn[e].scan;
+            for (job.first = first; job.first < at; job.first += kEntropyLanes) {
+                job.count = std::min<uint32_t>(kEntropyLanes, at - job.first);
+                jobs.push_back(job);
             }
         }
-        std::vector<Unit> units(l.size());
-        for (size_t e = 0; e < l.size(); e++) units[e] = l[e].u;
-        LevelList ll; ll.n = (uint32_t)units.size(); ll.kind = kind_of_list;
         ll.level = (uint32_t)(li / kNumKinds);
-        int rc = arena_upload(&r->big, &ll.d_units, units); if (rc) return rc;
         if (!jobs.empty()) {
             ll.n_jobs = (uint32_t)jobs.size();
-            rc = arena_upload(&r->big, &ll.d_jobs, jobs); if (rc) return rc;
+            up.add(&ll.d_jobs, jobs);
         }
-        if (ll.kind == kSequential && (uint64_t)l[0].bytes * 8 >= kSplitLeastBits) {       // (the longest on average come first)
-            rc = arena_alloc(&r->big, &ll.d_done, units.size()); if (rc) return rc;
+        if (ll.kind == kSequential && (uint64_t)rn[0].bytes * 8 >= kSplitLeastBits) {       // (the longest on average come first)
+            const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc;
         }
         if (ll.kind == kAcRefine) {
             const auto& rl = rlists[li / kNumKinds];
-            rc = refine_tiles(r, rl, &ll, true); if (rc) return rc;
+            refine_tiles(r, rl, &ll, true, &up);
         }
-        plan.levels.push_back(ll);
     }
     plan.n_apply = (uint32_t)apply.size();
     plan.apply_grid_x = (max_blk * 64 + kApplyChunk - 1) / kApplyChunk;
     if (plan.n_apply) {
-        int rc = arena_upload(&r->big, &plan.d_apply, apply); if (rc) return rc;
+        up.add(&plan.d_apply, apply);
         std::vector<int32_t> list_idx((size_t)n * kMaxComp, -1);
         for (size_t e = 0; e < apply.size(); e++) list_idx[(size_t)apply[e].img * kMaxComp + apply[e].comp] = (int32_t)e;
-        rc = arena_upload(&r->big, &plan.d_list_idx, list_idx); if (rc) return rc;
-        rc = arena_alloc(&r->big, &plan.d_apply_lists, apply.size()); if (rc) return rc;
+        up.add(&plan.d_list_idx, list_idx);
+        const int rc = arena_alloc(&r->big, &plan.d_apply_lists, apply.size()); if (rc) return rc;
     }
-    auto ins = r->plans.emplace(key, plan);
+    // decodes of DC scans only have pixel kernels, and tiles, of their own
+    if (!plan.has_ac && !r->d_flat_tiles) {
+        std::vector<PixelTile> tiles, rows;
+        tiles.reserve(r->n_flat_tiles); rows.reserve(r->n_flat_rows);
+        for (uint32_t i = 0; i < n; i++) {
+            const ImgDesc& d = r->img[i];
+            for (uint32_t c0 = 0, cells = flat_cells(d.W, d.H); c0 < cells; c0 += kFlatLanes) tiles.push_back(PixelTile{i, c0});
+            if (r->n_flat_rows) for (uint32_t cy = 0; cy * 8 < d.H; cy++) rows.push_back(PixelTile{i, cy});
+        }
+        up.add(&r->d_flat_rows, rows);
+        up.add(&r->d_flat_tiles, tiles);
+    }
+    const int rc = up.flush();
+    if (rc) { r->d_flat_tiles = nullptr; return rc; }
+    auto ins = r->plans.emplace(key, std::move(plan));
     *out = &ins.first->second;
     return PCR_OK;
 }
@@ -671,7 +751,8 @@ static int finish_open(pcr_record* r, hipStream_t s) {
     compute_levels(r);
     r->out_off.assign(n + 1, 0); r->coef_off.assign(n + 1, 0);
     r->mask_off.assign((size_t)n * G, 0); r->slot_base.assign((size_t)n * G, 0); r->slot_cnt.assign((size_t)n * G, 0);
-    std::vector<PixelTile> tiles, flat_tiles, flat_rows;
+    std::vector<PixelTile> tiles;
+    uint32_t flat_tiles = 0, flat_rows = 0;                       // (listed when a plan first needs them)
     bool rows_fit = true;
     r->flat_row_cells = 0;
     uint64_t nm = 0; uint64_t ns = 0;
@@ -723,15 +804,15 @@ static int finish_open(pcr_record* r, hipStream_t s) {
         }
         const uint32_t per = pixel_mcus_per_tile(d), mcus = (uint32_t)d.mcux * d.mcuy;       // runs of MCUs, one lane per block
         for (uint32_t m0 = 0; m0 < mcus; m0 += per) tiles.push_back(PixelTile{i, m0});
-        for (uint32_t c0 = 0, cells = flat_cells(d.W, d.H); c0 < cells; c0 += kFlatLanes) flat_tiles.push_back(PixelTile{i, c0});
+        flat_tiles += (flat_cells(d.W, d.H) + kFlatLanes - 1) / kFlatLanes;
         rows_fit = rows_fit && flat_rows_fit(d.W);
         r->flat_row_cells = std::max(r->flat_row_cells, ((uint32_t)d.W + 7) >> 3);
-        for (uint32_t cy = 0; cy * 8 < d.H; cy++) flat_rows.push_back(PixelTile{i, cy});
+        flat_rows += (d.H + 7u) / 8u;
     }
     if (ns >= (1ull << 32)) return PCR_E_UNSUPPORTED;
-    r->n_masks = nm; r->n_slots = (uint32_t)ns; r->n_tiles = (uint32_t)tiles.size(); r->n_flat_tiles = (uint32_t)flat_tiles.size();
-    if (!rows_fit) flat_rows.clear();
-    r->n_flat_rows = (uint32_t)flat_rows.size();
+    r->n_masks = nm; r->n_slots = (uint32_t)ns; r->n_tiles = (uint32_t)tiles.size(); r->n_flat_tiles = flat_tiles;
+    if (!rows_fit) flat_rows = 0;
+    r->n_flat_rows = flat_rows; r->d_flat_tiles = r->d_flat_rows = nullptr;
 
     DevRecord& d = r->d;
     const size_t padded = nbytes + 1024;      // slack: bit readers look ahead
@@ -739,7 +820,7 @@ static int finish_open(pcr_record* r, hipStream_t s) {
     // 12 per image and component, ...): anything beyond that is allocated on its own
     size_t need = arena_round(padded) + arena_round(r->coef_off[n] * sizeof(int16_t)) + arena_round((r->coef_off[n] / 64 + 1) * sizeof(int16_t)) + arena_round((nm + 2) * sizeof(uint64_t)) +
                   arena_round((ns + 1) * sizeof(uint32_t)) + 2 * arena_round((n + 1) * sizeof(uint64_t)) +
-                  4 * arena_round(((size_t)n * G + 1) * sizeof(uint64_t)) + arena_round((tiles.size() + 1) * sizeof(PixelTile)) + arena_round((flat_tiles.size() + 1) * sizeof(PixelTile)) + arena_round((flat_rows.size() + 1) * sizeof(PixelTile)) + arena_round((n + 1) * 8) +
+                  4 * arena_round(((size_t)n * G + 1) * sizeof(uint64_t)) + arena_round((tiles.size() + 1) * sizeof(PixelTile)) + arena_round((flat_tiles + 1ull) * sizeof(PixelTile)) + arena_round((flat_rows + 1ull) * sizeof(PixelTile)) + arena_round((n + 1) * 8) +
                   arena_round(((size_t)ntabs + 1) * sizeof(AcTab)) + arena_round(((size_t)ndctabs + 1) * sizeof(DcTab)) + arena_round(((size_t)n * G + 1) * sizeof(uint32_t)) + arena_round(((size_t)n * G + 1) * sizeof(uint32_t));
     need += 8 * ((ns + (size_t)n * G) * sizeof(Unit) + (size_t)n * kMaxComp * 64) + (1u << 20);
     need += 8 * (r->coef_off[n] / 64 / 256 + (size_t)n * G) * 2 * sizeof(RefineTile);     // (the tile lists of the refinement helpers: one entry per 256 blocks)
@@ -750,28 +831,26 @@ static int finish_open(pcr_record* r, hipStream_t s) {
     if (!rc) rc = arena_alloc(&r->big, &d.masks, nm + 2);
     if (!rc) rc = arena_alloc(&r->big, &d.ivl_start, ns);
     uint64_t *d_coef_off = nullptr, *d_out_off = nullptr, *d_mask_off = nullptr; uint32_t *d_sb = nullptr, *d_sc = nullptr;
-    if (!rc) rc = arena_upload(&r->big, &d_coef_off, r->coef_off);
-    if (!rc) rc = arena_upload(&r->big, &d_out_off, r->out_off);
-    if (!rc) rc = arena_upload(&r->big, &d_mask_off, r->mask_off);
-    if (!rc) rc = arena_upload(&r->big, &d_sb, r->slot_base);
-    if (!rc) rc = arena_upload(&r->big, &d_sc, r->slot_cnt);
-    if (!rc) rc = arena_upload(&r->big, &r->d_tiles, tiles);
-    if (!rc) rc = arena_upload(&r->big, &r->d_flat_tiles, flat_tiles);
-    if (!rc) rc = arena_upload(&r->big, &r->d_flat_rows, flat_rows);
     std::vector<uint32_t> dims((size_t)n * 2);
     for (uint32_t i = 0; i < n; i++) { dims[2 * i] = (uint32_t)r->img[i].W; dims[2 * i + 1] = (uint32_t)r->img[i].H; }
-    if (!rc) rc = arena_upload(&r->big, &r->d_dims, dims);
-    uint32_t* d_tab_idx = nullptr;
-    if (!rc) rc = arena_upload(&r->big, &d_tab_idx, tab_idx);
-    uint32_t* d_dctab_idx = nullptr;
-    if (!rc) rc = arena_upload(&r->big, &d_dctab_idx, dctab_idx);
+    uint32_t *d_tab_idx = nullptr, *d_dctab_idx = nullptr, *d_ent_off = nullptr;
+    Uploads up(&r->big, &r->stage);
+    up.add(&d_coef_off, r->coef_off);
+    up.add(&d_out_off, r->out_off);
+    up.add(&d_mask_off, r->mask_off);
+    up.add(&d_sb, r->slot_base);
+    up.add(&d_sc, r->slot_cnt);
+    up.add(&r->d_tiles, tiles);
+    up.add(&r->d_dims, dims);
+    up.add(&d_tab_idx, tab_idx);
+    up.add(&d_dctab_idx, dctab_idx);
+    up.add(&d_ent_off, ent_off);
+    if (!rc) rc = up.flush_on(s);
+    r->ent_off_h = std::move(ent_off); r->unit_bits.clear();
     if (!rc) rc = arena_alloc(&r->big, &d.dctabs, (size_t)ndctabs);
-    d.dctab_idx = d_dctab_idx;
-    r->ent_off_h = ent_off; r->unit_bits.clear();
-    uint32_t* d_ent_off = nullptr;
-    if (!rc) rc = arena_upload(&r->big, &d_ent_off, ent_off);
-    d.ent_off = d_ent_off;
     if (!rc) rc = arena_alloc(&r->big, &d.tabs, (size_t)ntabs);
+    d.dctab_idx = d_dctab_idx;
+    d.ent_off = d_ent_off;
     d.tab_idx = d_tab_idx;
     d.coef_off = d_coef_off; d.out_off = d_out_off; d.mask_off = d_mask_off; d.slot_base = d_sb; d.slot_cnt = d_sc;
     if (!rc && hipMemsetAsync(d.clean, 0xFF, padded, s) != hipSuccess) rc = PCR_E_DEVICE;
@@ -829,6 +908,17 @@ static void measure_units(pcr_record* r, const uint8_t* bytes, size_t nbytes) {
     }
 }
 
+// Marker parse of every image: layout, work sizes, early rejection.
+static int parse_on_host(pcr_record* r, const uint8_t* bytes, const std::vector<uint32_t>& off, const std::vector<uint32_t>& len, const std::vector<uint32_t>& nsc) {
+    const uint32_t n = r->hdr.n, G = r->hdr.G;
+    r->img.resize(n); r->scan.assign((size_t)n * G, ScanDesc{});
+    for (uint32_t i = 0; i < n; i++) {
+        parse_image(bytes, off.data(), len.data(), n, i, nsc[i], r->hdr.k_avail, &r->img[i], &r->scan[(size_t)i * G]);
+        if (r->img[i].status) return r->img[i].status;
+    }
+    return PCR_OK;
+}
+
 int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out) {
     if (!bytes_ || !out) return PCR_E_ARG;
     const uint8_t* bytes = (const uint8_t*)bytes_;
@@ -848,14 +938,7 @@ int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out)
     r->header.assign(bytes, bytes + h.header_bytes);
     std::vector<uint32_t> off, len, nsc;
     rc = validate_index(r->header.data(), h, &off, &len, &nsc);
-    // host marker parse of every image: layout, work sizes, early rejection
-    if (!rc) {
-        r->img.resize(n); r->scan.assign((size_t)n * G, ScanDesc{});
-        for (uint32_t i = 0; i < n && !rc; i++) {
-            parse_image(bytes, off.data(), len.data(), n, i, nsc[i], h.k_avail, &r->img[i], &r->scan[(size_t)i * G]);
-            rc = r->img[i].status;
-        }
-    }
+    if (!rc) rc = parse_on_host(r, bytes, off, len, nsc);
     if (!rc && hipMalloc((void**)&r->d_rec, nbytes + 64) != hipSuccess) { (void)hipGetLastError(); rc = PCR_E_NOMEM; }
     if (!rc && hipMemcpy(r->d_rec, bytes, nbytes, hipMemcpyHostToDevice) != hipSuccess) rc = PCR_E_DEVICE;
     if (!rc && hipMemset(r->d_rec + nbytes, 0, 64) != hipSuccess) rc = PCR_E_DEVICE;
@@ -868,26 +951,38 @@ int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out)
     return PCR_OK;
 }
 
-// Binds handle r (fresh, or one whose earlier work has finished) to record bytes in device memory: header
-// checks on the host, index and marker parse ON THE DEVICE (only the small descriptor tables come back),
-// buffer layout.  Everything is enqueued on s, which is synchronised before returning.  On failure the
+// Binds handle r (fresh, or one whose earlier work has finished) to record bytes in device memory.  Without a host copy of
+// them (host null): header checks on the host, index and marker parse ON THE DEVICE, and only the small descriptor tables
+// come back.  With one, everything is read from it, while the bytes may still be on their way to the device (enqueued on s
+// before).  Then the buffer layout.  Everything is enqueued on s, which is synchronised before returning.  On failure the
 // handle holds no record (pcr_close is all that may follow).
-static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, hipStream_t s) {
+static int bind_bytes(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s);
+static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s) {
     r->plans.clear(); r->resident_k = 0; r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0;
-    r->out_off.assign(1, 0); r->coef_off.assign(1, 0);        // until the bind succeeds the handle holds no record
     r->d_dims = nullptr; r->d_ssim_part = nullptr; r->d_planes = nullptr;
     r->d_tail_tiles = nullptr; r->n_tail_tiles = 0; r->d_edge = nullptr; r->d_edge_off = nullptr; r->d_mcu_px_h = nullptr;
+    int rc = bind_bytes(r, d_bytes, nbytes, host, s);
+    if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = PCR_E_DEVICE;
+    if (rc) { (void)hipGetLastError(); r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0; }
+    return rc;
+}
+static int bind_bytes(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s) {
     // fixed part of the header, then the whole metadata block
     uint8_t fixed[24];
-    HIP_TRY(hipMemcpyAsync(fixed, d_bytes, 24, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    if (host) std::memcpy(fixed, host, 24);
+    else {
+        HIP_TRY(hipMemcpyAsync(fixed, d_bytes, 24, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+    }
     if (fixed[0] != 'P' || fixed[1] != 'C' || fixed[2] != 'R' || fixed[3] != '1') return PCR_E_FORMAT;
     const uint64_t header_bytes = ld_le64(fixed + 16);
     if (header_bytes < 24 || header_bytes > (1ull << 31)) return PCR_E_FORMAT;
     if (header_bytes > nbytes) return PCR_E_TRUNCATED;
     r->header.resize(header_bytes);
-    if (hipMemcpyAsync(r->header.data(), d_bytes, header_bytes, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
-        (void)hipGetLastError(); return PCR_E_DEVICE;
+    if (host) std::memcpy(r->header.data(), host, header_bytes);
+    else {
+        HIP_TRY(hipMemcpyAsync(r->header.data(), d_bytes, header_bytes, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
     }
     RecordHeader h;
     int rc = parse_record_header(r->header.data(), nbytes, &h);
@@ -897,18 +992,22 @@ static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, hipStr
     const uint32_t n = h.n, G = h.G;
     std::vector<uint32_t> off, len, nsc;
     rc = validate_index(r->header.data(), h, &off, &len, &nsc);
-    if (!rc) { r->d.rec = (const uint8_t*)d_bytes; rc = alloc_descriptor_buffers(r, s); }
-    if (!rc) {
+    if (rc) return rc;
+    r->d.rec = (const uint8_t*)d_bytes;
+    rc = alloc_descriptor_buffers(r, s);
+    if (rc) return rc;
+    if (host) {
+        rc = parse_on_host(r, host, off, len, nsc);
+        if (rc) return rc;
+    } else {
         launch_headers(r, h.k_avail, false, h.k_avail, false, s);          // (no tables: where they go is not laid out yet)
         r->img.resize(n); r->scan.resize((size_t)n * G);
-        if (hipMemcpyAsync(r->img.data(), r->d.img, n * sizeof(ImgDesc), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpyAsync(r->scan.data(), r->d.scan, (size_t)n * G * sizeof(ScanDesc), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess) rc = PCR_E_DEVICE;
+        HIP_TRY(hipMemcpyAsync(r->img.data(), r->d.img, n * sizeof(ImgDesc), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(r->scan.data(), r->d.scan, (size_t)n * G * sizeof(ScanDesc), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
     }
-    if (!rc) rc = finish_open(r, s);
-    if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = PCR_E_DEVICE;
-    if (rc) { (void)hipGetLastError(); r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0; }
-    return rc;
+    // (the units are not measured: ordering them takes longer than it saves where a record is decoded once)
+    return finish_open(r, s);
 }
 
 static int check_device_bytes(const void* d_bytes, size_t nbytes, int* device) {
@@ -932,7 +1031,7 @@ int pcr_open_device(const void* d_bytes, size_t nbytes, void* stream, pcr_record
     pcr_record* r = new (std::nothrow) pcr_record();
     if (!r) return PCR_E_NOMEM;
     r->device = device; r->borrowed = true;
-    rc = bind_device(r, d_bytes, nbytes, (hipStream_t)stream);
+    rc = bind_device(r, d_bytes, nbytes, nullptr, (hipStream_t)stream);
     if (rc) { pcr_close(r); return rc; }
     *out = r;
     return PCR_OK;
@@ -947,7 +1046,7 @@ int pcr_rebind_device(pcr_record* r, const void* d_bytes, size_t nbytes, void* s
     HIP_TRY(hipSetDevice(device));
     if (!r->borrowed && r->d_rec) { (void)hipFree(r->d_rec); }             // the handle's own copy of its first record
     r->d_rec = nullptr; r->borrowed = true;
-    return bind_device(r, d_bytes, nbytes, (hipStream_t)stream);
+    return bind_device(r, d_bytes, nbytes, nullptr, (hipStream_t)stream);
 }
 
 void pcr_close(pcr_record* r) {
@@ -955,7 +1054,7 @@ void pcr_close(pcr_record* r) {
     (void)hipSetDevice(r->device);
     (void)hipDeviceSynchronize();
     free_plans(r);
-    arena_free(&r->small); arena_free(&r->big);
+    arena_free(&r->small); arena_free(&r->big); r->stage.release();
     if (!r->borrowed && r->d_rec) (void)hipFree(r->d_rec);
     if (r->d_gather) (void)hipFree(r->d_gather);
     for (auto& c : r->ring) for (auto& e : c.ev) (void)hipEventDestroy(e);
@@ -1232,11 +1331,13 @@ static int prepare_fused_tail(pcr_record* r) {
         eoff[i + 1] = eoff[i] + (uint64_t)2 * d.mcuy * d.W * d.nc;
         mh[i] = 8u * d.vmax;
     }
-    int rc = arena_upload(&r->big, &r->d_edge_off, eoff);
-    if (!rc) rc = arena_upload(&r->big, &r->d_mcu_px_h, mh);
-    if (!rc) rc = arena_alloc(&r->big, &r->d_edge, (size_t)eoff[n] + 16);
     PixelTile* dt = nullptr;
-    if (!rc) rc = arena_upload(&r->big, &dt, tiles);
+    Uploads up(&r->big, &r->stage);
+    up.add(&r->d_edge_off, eoff);
+    up.add(&r->d_mcu_px_h, mh);
+    up.add(&dt, tiles);
+    int rc = arena_alloc(&r->big, &r->d_edge, (size_t)eoff[n] + 16);
+    if (!rc) rc = up.flush();
     if (rc) return rc;
     r->d_tail_tiles = dt; r->n_tail_tiles = (uint32_t)tiles.size();
     return PCR_OK;
@@ -1637,9 +1738,15 @@ int pcr_loader_upload(pcr_loader* ld, int slot, size_t nbytes, pcr_record** rec)
     loader_take_tokens(ld, (double)nbytes);
     HIP_TRY(hipMemcpyAsync(sl->dev, sl->host, nbytes, hipMemcpyHostToDevice, sl->stream));
     HIP_TRY(hipMemsetAsync(sl->dev + nbytes, 0, 64, sl->stream));
-    int rc;
-    if (!sl->rec) rc = pcr_open_device(sl->dev, nbytes, (void*)sl->stream, &sl->rec);
-    else rc = pcr_rebind_device(sl->rec, sl->dev, nbytes, (void*)sl->stream);
+    // (the handle is laid out from the host's bytes while the copy runs; bind_device waits for the copy)
+    const bool fresh = !sl->rec;
+    if (fresh) {
+        sl->rec = new (std::nothrow) pcr_record();
+        if (!sl->rec) { (void)hipStreamSynchronize(sl->stream); return PCR_E_NOMEM; }
+        sl->rec->device = ld->device; sl->rec->borrowed = true; sl->rec->stage.pinned = true;
+    }
+    const int rc = bind_device(sl->rec, sl->dev, nbytes, (const uint8_t*)sl->host, sl->stream);
+    if (rc && fresh) { pcr_close(sl->rec); sl->rec = nullptr; }
     if (rc) return rc;
     if (rec) *rec = sl->rec;
     return PCR_OK;
