@@ -380,7 +380,11 @@ int pcr_transcode_progressive(const void* src_jpeg, size_t src_bytes, const int1
  * pcr_transcode_progressive_counted: pcr_transcode_progressive with the counts of the image given (host,
  *   PCR_HIST_ENTRIES counters, e.g. copied back from pcr_symbol_histograms) instead of counted on the host; the same
  *   bytes.  PCR_E_FORMAT if the coefficients hold a symbol the counts do not.
- * pcr_transcode_symbol_counts: the counts pcr_transcode_progressive makes for itself (host), for comparison. */
+ * pcr_transcode_symbol_counts: the counts pcr_transcode_progressive makes for itself (host), for comparison.
+ * pcr_transcode_batch: all of it for the n files an opened record was made of (the record's images, in order): decode,
+ *   counts (device_counts != 0; otherwise counted on the host), and the progressive files, written by up to `threads`
+ *   threads; file i goes to out + out_off[i], where it has out_off[i + 1] - out_off[i] bytes of room, and written[i]
+ *   is its size.  PCR_E_RANGE: some file needs the room written[] says, call again with it.  Synchronous. */
 #define PCR_HIST_SCANS 10
 #define PCR_HIST_ENTRIES (PCR_HIST_SCANS * 2 * 256)
 int pcr_symbol_histograms(pcr_record* rec, uint32_t restart_interval, uint32_t* d_hist, void* hip_stream);
@@ -388,6 +392,8 @@ int pcr_transcode_progressive_counted(const void* src_jpeg, size_t src_bytes, co
                                       const uint32_t* counts, void* out, size_t capacity, uint64_t* written);
 int pcr_transcode_symbol_counts(const void* src_jpeg, size_t src_bytes, const int16_t* coef, size_t coef_count, uint32_t restart_interval,
                                 uint32_t* counts);
+int pcr_transcode_batch(pcr_record* rec, const void* const* files, const size_t* sizes, uint32_t n, uint32_t restart_interval, int device_counts,
+                        int threads, void* out, const uint64_t* out_off, uint64_t* written, void* hip_stream);
 
 /* Shape of the entropy decoders (Section 4.2 of the paper: decoding is where the time goes).  A scan is cut into units
  * (restart intervals, entry-point units); a launch either gives every unit a wavefront that decodes it on the scalar

@@ -61,6 +61,7 @@ SYMBOLS = {
     "pcr_symbol_histograms": (ctypes.c_int, [_vp, ctypes.c_uint32, _vp, _vp]),
     "pcr_transcode_progressive_counted": (ctypes.c_int, [_vp, ctypes.c_size_t, _vp, ctypes.c_size_t, ctypes.c_uint32, _vp, _vp, ctypes.c_size_t,
                                                          ctypes.POINTER(ctypes.c_uint64)]),
+    "pcr_transcode_batch": (ctypes.c_int, [_vp, _vp, _vp, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_int, ctypes.c_int, _vp, _vp, _vp, _vp]),
     "pcr_transcode_symbol_counts": (ctypes.c_int, [_vp, ctypes.c_size_t, _vp, ctypes.c_size_t, ctypes.c_uint32, _vp]),
     "pcr_select_scan_group": (ctypes.c_int, [_vp, ctypes.c_float, _vp, _vp, ctypes.c_size_t, _vp, ctypes.POINTER(ctypes.c_float),
                                              ctypes.POINTER(ctypes.c_int), _vp]),
@@ -407,7 +408,10 @@ def _file_table(files):
 
 def record_write(files, labels=None):
     """One record (bytes) from JPEG files (bytes objects): pcr_record_size + pcr_record_write."""
-    bufs, ptrs, sizes = _file_table(files)
+    return _record_bytes(*_file_table(files), labels).tobytes()
+
+
+def _record_bytes(bufs, ptrs, sizes, labels):
     total, G = ctypes.c_uint64(0), ctypes.c_uint32(0)
     _check(lib().pcr_record_size(ptrs, sizes, len(bufs), ctypes.byref(total), ctypes.byref(G)), "pcr_record_size")
     out = np.empty(int(total.value), np.uint8)
@@ -417,7 +421,7 @@ def record_write(files, labels=None):
     _check(lib().pcr_record_write(ptrs, sizes, lab.ctypes.data_as(_vp) if lab is not None else None, len(bufs), out.ctypes.data_as(_vp),
                                   out.size, ctypes.byref(written)), "pcr_record_write")
     assert written.value == out.size
-    return out.tobytes()
+    return out
 
 
 def record_write_indexed(files, labels=None, entry_interval=128):
@@ -485,15 +489,21 @@ def transcode_files(files, device=0, threads=None, restart_interval=0, device_co
     """The paper's encoding step for a list of JPEG files (baseline or progressive): their coefficients are decoded
     and the symbols of the new scans counted on the device, the progressive files written on the host.  Returns the
     progressive files; record_write() groups them."""
-    rec = record_write(files)
-    with pcr_open(rec, device) as r:
-        lay = r.coef_layout()
-        hist = r.symbol_histograms(restart_interval).cpu().numpy() if device_counts else None
-        coef = r.decode_coefficients(r.G).cpu().numpy()
-    from concurrent.futures import ThreadPoolExecutor                 # (the C call releases the interpreter lock)
-    with ThreadPoolExecutor(threads or min(16, os.cpu_count() or 1)) as ex:
-        return list(ex.map(lambda i: transcode_progressive(files[i], coef[int(lay[i]):int(lay[i + 1])], restart_interval,
-                                                           None if hist is None else hist[i]), range(len(files))))
+    import torch
+    bufs, ptrs, sizes = _file_table(files)
+    off = np.concatenate([[0], np.cumsum([b.size + b.size // 2 + 4096 for b in bufs])]).astype(np.uint64)
+    written = np.zeros(len(bufs), np.uint64)
+    with pcr_open(_record_bytes(bufs, ptrs, sizes, None), device) as r:
+        for _ in range(2):
+            out = np.empty(int(off[-1]), np.uint8)
+            rc = lib().pcr_transcode_batch(r._h, ptrs, sizes, len(bufs), restart_interval, int(device_counts), threads or min(16, os.cpu_count() or 1),
+                                           out.ctypes.data_as(_vp), off.ctypes.data_as(_vp), written.ctypes.data_as(_vp),
+                                           torch.cuda.current_stream(device).cuda_stream)
+            if rc != E_RANGE:
+                break
+            off = np.concatenate([[0], np.cumsum(written)]).astype(np.uint64)
+    _check(rc, "pcr_transcode_batch")
+    return [out[int(a):int(a) + int(w)].tobytes() for a, w in zip(off, written)]
 
 
 class Loader:

@@ -12,6 +12,9 @@
 #include <cstring>
 #include <thread>
 #include <vector>
+#if defined(__SSE2__) && !defined(__HIP_DEVICE_COMPILE__)
+#include <emmintrin.h>
+#endif
 
 #include "pcr_format.h"
 #include "pcr_entropy.h"
@@ -129,9 +132,9 @@ struct BitCursor {
     const uint8_t* d; uint64_t nbits, pos; bool bad;
     // the 32 bits at the cursor (the buffer is padded beyond its end)
     uint32_t peek() const {
-        const uint8_t* p = d + (pos >> 3);
-        const uint64_t v = ((uint64_t)p[0] << 32) | ((uint64_t)p[1] << 24) | ((uint64_t)p[2] << 16) | ((uint64_t)p[3] << 8) | p[4];
-        return (uint32_t)(v >> (8 - (pos & 7)));
+        uint64_t v;
+        memcpy(&v, d + (pos >> 3), 8);
+        return (uint32_t)(__builtin_bswap64(v) << (pos & 7) >> 32);
     }
     void skip(uint32_t n) { pos += n; if (pos > nbits) bad = true; }
     uint32_t take(uint32_t n) { const uint32_t v = n ? peek() >> (32 - n) : 0; skip(n); return v; }
@@ -142,8 +145,10 @@ struct BitCursor {
 inline void unstuff_scan(const uint8_t* src, uint32_t L, std::vector<uint8_t>* out, std::vector<uint32_t>* starts) {
     out->clear(); starts->assign(1, 0);
     for (uint32_t q = 0; q < L; q++) {
-        const uint8_t cur = src[q];
-        if (cur != 0xFF) { out->push_back(cur); continue; }
+        const void* ff = memchr(src + q, 0xFF, L - q);
+        const uint32_t plain = ff ? (uint32_t)((const uint8_t*)ff - (src + q)) : L - q;
+        out->insert(out->end(), src + q, src + q + plain);
+        q += plain;
         if (q + 1 >= L) break;
         const uint8_t nx = src[q + 1];
         if (nx == 0x00) { out->push_back(0xFF); q++; }
@@ -254,11 +259,11 @@ inline int find_entry_points(const uint8_t* file, const uint64_t* ends, uint32_t
                             if (sz > 1) { b.bad = true; break; }
                             if (sz == 0 && r < 15) { eobrun = (1u << r) + b.take(r); break; }   // (counts this block)
                             if (sz) b.skip(1);                       // the sign
-                            while (k <= sd.Se) {                     // over r zeros; a correction bit at every non-zero on the way
-                                if ((h >> k) & 1) b.skip(1);
-                                else { if (r == 0) break; r--; }
-                                k++;
-                            }
+                            const uint64_t from = band & ~((1ull << k) - 1);
+                            uint64_t zeros = ~h & from;              // over r zeros; a correction bit at every non-zero on the way
+                            for (; r && zeros; r--) zeros &= zeros - 1;
+                            k = zeros ? __builtin_ctzll(zeros) : (int)sd.Se + 1;
+                            b.skip((uint32_t)__builtin_popcountll(h & from & (k < 64 ? (1ull << k) - 1 : ~0ull)));
                             if (sz) { if (k > sd.Se) { b.bad = true; break; } h |= 1ull << k; }
                             k++;
                         }
@@ -369,12 +374,20 @@ inline void build_table(const uint32_t freq_in[256], HuffSpec* H) {
     for (int i = 0; i < 256; i++) freq[i] = (long)freq_in[i];
     freq[256] = 1;
     for (int i = 0; i < 257; i++) { codesize[i] = 0; others[i] = -1; }
-    for (;;) {
-        int c1 = -1, c2 = -1;
-        for (int i = 0; i < 257; i++) if (freq[i] > 0 && (c1 < 0 || freq[i] <= freq[c1])) c1 = i;      // least, ties: the larger index
-        for (int i = 0; i < 257; i++) if (freq[i] > 0 && i != c1 && (c2 < 0 || freq[i] <= freq[c2])) c2 = i;
-        if (c2 < 0) break;
-        freq[c1] += freq[c2]; freq[c2] = 0;
+    // The symbols that occur, in order; one pass finds the two least (ties: the larger index), the second of which then
+    // leaves the list.
+    int live[257], nlive = 0;
+    for (int i = 0; i < 257; i++) if (freq[i] > 0) live[nlive++] = i;
+    while (nlive > 1) {
+        int a1 = -1, a2 = -1;
+        for (int e = 0; e < nlive; e++) {
+            if (a1 < 0 || freq[live[e]] <= freq[live[a1]]) { a2 = a1; a1 = e; }
+            else if (a2 < 0 || freq[live[e]] <= freq[live[a2]]) a2 = e;
+        }
+        const int c1 = live[a1], c2 = live[a2];
+        freq[c1] += freq[c2];
+        for (int e = a2; e + 1 < nlive; e++) live[e] = live[e + 1];
+        nlive--;
         for (int v = c1;; v = others[v]) { codesize[v]++; if (others[v] < 0) { others[v] = c2; break; } }
         for (int v = c2; v >= 0; v = others[v]) codesize[v]++;
     }
@@ -405,24 +418,80 @@ inline void build_table(const uint32_t freq_in[256], HuffSpec* H) {
     }
 }
 
+// Bits into bytes, four at a time (one by one where a byte of the four is 0xFF and takes a zero behind it).
 class BitWriter {
 public:
-    explicit BitWriter(std::vector<uint8_t>* out) : out_(out) {}
-    void put(uint32_t bits, int n) {
-        if (n == 0) return;
-        acc_ = (acc_ << n) | (bits & ((1u << n) - 1u)); have_ += n;
-        while (have_ >= 8) {
-            const uint8_t b = (uint8_t)(acc_ >> (have_ - 8));
-            out_->push_back(b);
-            if (b == 0xFF) out_->push_back(0x00);
-            have_ -= 8;
+    explicit BitWriter(std::vector<uint8_t>* out) : out_(out), pos_(out->size()) {}
+    void put(uint32_t bits, int n) {                           // n <= 32
+        acc_ = (acc_ << n) | (bits & (uint32_t)((1ull << n) - 1u)); have_ += n;
+        if (have_ < 32) return;
+        const uint32_t w = (uint32_t)(acc_ >> (have_ - 32));
+        have_ -= 32;
+        room(8);
+        if (((~w - 0x01010101u) & w & 0x80808080u) == 0) {     // no byte is 0xFF
+            uint8_t* p = out_->data() + pos_;
+            p[0] = (uint8_t)(w >> 24); p[1] = (uint8_t)(w >> 16); p[2] = (uint8_t)(w >> 8); p[3] = (uint8_t)w;
+            pos_ += 4;
+        } else for (int s = 24; s >= 0; s -= 8) byte((uint8_t)(w >> s));
+    }
+    void finish() {                                            // pad with 1-bits
+        const int pad = (8 - have_ % 8) % 8;
+        acc_ = (acc_ << pad) | ((1u << pad) - 1u); have_ += pad;
+        room(16);
+        for (; have_ > 0; have_ -= 8) byte((uint8_t)(acc_ >> (have_ - 8)));
+        have_ = 0;
+        out_->resize(pos_);
+    }
+    void marker(uint8_t m) { finish(); out_->push_back(0xFF); out_->push_back(m); pos_ = out_->size(); }
+private:
+    void room(size_t n) { if (out_->size() - pos_ < n) out_->resize(out_->size() + out_->size() / 2 + 4096); }
+    void byte(uint8_t b) { (*out_)[pos_++] = b; if (b == 0xFF) (*out_)[pos_++] = 0x00; }
+    std::vector<uint8_t>* out_; size_t pos_;                   // (the vector is longer than what is written, until finish())
+    uint64_t acc_ = 0; int have_ = 0;
+};
+
+// Which positions of a block (bit k: zig-zag position k) are not zero after the point transform by 0, 1 and 2 bits: what
+// the coders below walk over instead of 64 coefficients per block and scan.
+struct BlockMasks {
+    std::vector<uint64_t> nz[3];
+    void fill(const int16_t* plane, size_t blocks) {
+        // the order of a mask's bits is changed eight of them at a time
+        static const std::vector<uint64_t> order = [] {
+            std::vector<uint64_t> t(8 * 256, 0);
+            const ZigzagTable zz;
+            for (int k = 0; k < 64; k++)
+                for (int v = 0; v < 256; v++) if (v >> (zz.natural[k] & 7) & 1) t[(size_t)(zz.natural[k] >> 3) * 256 + v] |= 1ull << k;
+            return t;
+        }();
+        for (auto& m : nz) m.resize(blocks);
+        for (size_t b = 0; b < blocks; b++) {
+            uint64_t flat[3];
+            natural_masks(plane + b * 64, flat);
+            for (int s = 0; s < 3; s++) {
+                uint64_t m = 0;
+                for (int r = 0; r < 8; r++) m |= order[(size_t)r * 256 + (flat[s] >> (8 * r) & 255)];
+                nz[s][b] = m;
+            }
         }
     }
-    void finish() { if (have_) put((1u << (8 - have_)) - 1u, 8 - have_); }      // pad with 1-bits
-    void marker(uint8_t m) { finish(); out_->push_back(0xFF); out_->push_back(m); }
-private:
-    std::vector<uint8_t>* out_;
-    uint64_t acc_ = 0; int have_ = 0;
+    static void natural_masks(const int16_t* c, uint64_t flat[3]) {
+        flat[0] = flat[1] = flat[2] = 0;
+#if defined(__SSE2__) && !defined(__HIP_DEVICE_COMPILE__)
+        const __m128i zero = _mm_setzero_si128(), one = _mm_set1_epi16(1), three = _mm_set1_epi16(3);
+        for (int q = 0; q < 4; q++) {
+            __m128i a = _mm_loadu_si128((const __m128i*)(c + 16 * q)), b = _mm_loadu_si128((const __m128i*)(c + 16 * q + 8));
+            a = _mm_max_epi16(a, _mm_subs_epi16(zero, a)); b = _mm_max_epi16(b, _mm_subs_epi16(zero, b));
+            flat[0] |= (uint64_t)(uint32_t)_mm_movemask_epi8(_mm_packs_epi16(_mm_cmpgt_epi16(a, zero), _mm_cmpgt_epi16(b, zero))) << (16 * q);
+            flat[1] |= (uint64_t)(uint32_t)_mm_movemask_epi8(_mm_packs_epi16(_mm_cmpgt_epi16(a, one), _mm_cmpgt_epi16(b, one))) << (16 * q);
+            flat[2] |= (uint64_t)(uint32_t)_mm_movemask_epi8(_mm_packs_epi16(_mm_cmpgt_epi16(a, three), _mm_cmpgt_epi16(b, three))) << (16 * q);
+        }
+#else
+        for (int k = 0; k < 64; k++) {
+            const int mag = c[k] < 0 ? -(int)c[k] : c[k];
+            flat[0] |= (uint64_t)(mag > 0) << k; flat[1] |= (uint64_t)(mag > 1) << k; flat[2] |= (uint64_t)(mag > 3) << k;
+        }
+#endif
+    }
 };
 
 struct Frame {
@@ -430,54 +499,67 @@ struct Frame {
     int hs[kMaxComp], vs[kMaxComp], tq[kMaxComp], cid[kMaxComp];
     int bw[kMaxComp], bh[kMaxComp], cw[kMaxComp], ch[kMaxComp], mcux, mcuy;
     const int16_t* plane[kMaxComp];                            // [bh][bw][64], natural order inside a block
+    BlockMasks masks[kMaxComp];
 };
 
 struct ScanSpec { int ns, comp[kMaxComp], Ss, Se, Ah, Al; };
 
-inline int bit_length(int v) { int n = 0; while (v) { n++; v >>= 1; } return n; }
+inline int bit_length(int v) { return v ? 32 - __builtin_clz((unsigned)v) : 0; }
 
-class ScanCoder {
+// Where a scan's symbols go: a list of tokens, or, with the tables known beforehand, straight into the file.
+class TokenSink {
+public:
+    std::vector<Token> tokens;
+    void symbol(uint8_t slot, uint8_t sym, int nbits, uint32_t bits) { tokens.push_back(Token{slot, sym, (uint8_t)nbits, (uint16_t)(bits & 0xFFFFu)}); }
+    void raw(uint64_t bits, int n) {
+        while (n > 0) { const int take = n < 16 ? n : 16; symbol(kRawBits, 0, take, (uint32_t)(bits >> (n - take)) & ((1u << take) - 1u)); n -= take; }
+    }
+    void restart(uint8_t m) { tokens.push_back(Token{kRestartMark, m, 0, 0}); }
+};
+class FileSink {
+public:
+    FileSink(BitWriter* w, const HuffSpec* H) : w_(w), H_(H) {}
+    bool unknown = false;                                      // a symbol the tables hold no code for
+    void symbol(uint8_t slot, uint8_t sym, int nbits, uint32_t bits) {
+        const int size = H_[slot].size[sym];
+        unknown = unknown || size == 0;
+        w_->put((uint32_t)H_[slot].code[sym] << nbits | (bits & ((1u << nbits) - 1u)), size + nbits);     // (16 + 16 bits at most)
+    }
+    void raw(uint64_t bits, int n) {
+        if (n > 32) { w_->put((uint32_t)(bits >> (n - 32)), 32); n -= 32; }
+        w_->put((uint32_t)bits, n);
+    }
+    void restart(uint8_t m) { w_->marker((uint8_t)(0xD0 + m)); }
+private:
+    BitWriter* w_; const HuffSpec* H_;
+};
+
+template <class Sink> class ScanCoder {
 public:
     // restart_mcus: MCUs of this scan per restart interval (0: no restart markers)
-    ScanCoder(const Frame& F, const ScanSpec& S, uint32_t restart_mcus) : F_(F), S_(S), ri_(restart_mcus) {}
-    std::vector<Token> tokens;
-
-    void run() {
-        size_t blocks = 0;
-        for (int j = 0; j < S_.ns; j++) blocks += (size_t)F_.bw[S_.comp[j]] * F_.bh[S_.comp[j]];
-        tokens.reserve(blocks * (S_.Ss == 0 ? 1 : 12));
-        if (S_.Ss == 0) dc_scan(); else ac_scan();
-    }
+    ScanCoder(const Frame& F, const ScanSpec& S, uint32_t restart_mcus, Sink* sink) : F_(F), S_(S), sink_(*sink), ri_(restart_mcus) {}
+    void run() { if (S_.Ss == 0) dc_scan(); else ac_scan(); }
 
 private:
-    const Frame& F_; const ScanSpec& S_;
+    const Frame& F_; const ScanSpec& S_; Sink& sink_;
     uint32_t ri_, mcu_ = 0, marks_ = 0;                        // restart interval, MCUs begun, markers written
     int pred_[kMaxComp] = {0, 0, 0};                           // DC predictions
     // end-of-band run shared by the blocks of an AC scan, and the correction bits that wait behind it
+    struct Bits { uint64_t v; int n; };
     uint32_t eobrun_ = 0;
-    std::vector<uint8_t> pending_;
-    std::vector<uint8_t> corr_;                                // correction bits met since the last symbol of the current block
-
-    void push(uint8_t slot, uint8_t sym, int nbits, uint32_t bits) { tokens.push_back(Token{slot, sym, (uint8_t)nbits, (uint16_t)(bits & 0xFFFFu)}); }
-    void push_bits(const std::vector<uint8_t>& b) {
-        size_t i = 0;
-        while (i < b.size()) {
-            uint32_t v = 0; int n = 0;
-            while (n < 16 && i < b.size()) { v = (v << 1) | b[i++]; n++; }
-            push(kRawBits, 0, n, v);
-        }
-    }
-    const int16_t* block(int c, int row, int col) const { return F_.plane[c] + ((size_t)row * F_.bw[c] + col) * 64; }
+    std::vector<Bits> pending_;
+    const ZigzagTable zz_;
 
     // A restart interval ends: whatever is pending goes out, a marker follows, predictions start again.
     void begin_mcu() {
         if (ri_ && mcu_ && mcu_ % ri_ == 0) {
             flush_eobrun();
-            push(kRestartMark, (uint8_t)(marks_++ & 7), 0, 0);
+            sink_.restart((uint8_t)(marks_++ & 7));
             pred_[0] = pred_[1] = pred_[2] = 0;
         }
         mcu_++;
     }
+    // fn(component of the scan, component, number of the block in its plane)
     template <class Fn> void for_each_block(Fn fn) {
         if (S_.ns > 1) {
             for (int my = 0; my < F_.mcuy; my++) for (int mx = 0; mx < F_.mcux; mx++) {
@@ -485,24 +567,24 @@ private:
                 for (int j = 0; j < S_.ns; j++) {
                     const int c = S_.comp[j];
                     for (int by = 0; by < F_.vs[c]; by++) for (int bx = 0; bx < F_.hs[c]; bx++)
-                        fn(j, c, block(c, my * F_.vs[c] + by, mx * F_.hs[c] + bx));
+                        fn(j, c, (size_t)(my * F_.vs[c] + by) * F_.bw[c] + (size_t)(mx * F_.hs[c] + bx));
                 }
             }
         } else {
             const int c = S_.comp[0];
-            for (int row = 0; row < F_.ch[c]; row++) for (int col = 0; col < F_.cw[c]; col++) { begin_mcu(); fn(0, c, block(c, row, col)); }
+            for (int row = 0; row < F_.ch[c]; row++) for (int col = 0; col < F_.cw[c]; col++) { begin_mcu(); fn(0, c, (size_t)row * F_.bw[c] + col); }
         }
     }
 
     void dc_scan() {
-        for_each_block([&](int j, int c, const int16_t* b) {
-            const int v = (int)b[0] >> S_.Al;                  // arithmetic shift: the point transform of DC
+        for_each_block([&](int j, int c, size_t block) {
+            const int v = (int)F_.plane[c][block * 64] >> S_.Al;      // arithmetic shift: the point transform of DC
             if (S_.Ah == 0) {
                 int diff = v - pred_[c]; pred_[c] = v;
                 const int nb = bit_length(diff < 0 ? -diff : diff);
-                push((uint8_t)(j == 0 ? 0 : 1), (uint8_t)nb, nb, (uint32_t)(diff < 0 ? diff - 1 : diff));
+                sink_.symbol((uint8_t)(j == 0 ? 0 : 1), (uint8_t)nb, nb, (uint32_t)(diff < 0 ? diff - 1 : diff));
             } else {
-                push(kRawBits, 0, 1, (uint32_t)(v & 1));
+                sink_.raw((uint64_t)(v & 1), 1);
             }
         });
     }
@@ -510,63 +592,70 @@ private:
     void flush_eobrun() {
         if (eobrun_ > 0) {
             const int n = bit_length((int)eobrun_) - 1;
-            push(0, (uint8_t)(n << 4), n, eobrun_ - (1u << n));
+            sink_.symbol(0, (uint8_t)(n << 4), n, eobrun_ - (1u << n));
             eobrun_ = 0;
         }
-        if (!pending_.empty()) { push_bits(pending_); pending_.clear(); }
+        for (const Bits& b : pending_) sink_.raw(b.v, b.n);
+        pending_.clear();
     }
 
     void ac_scan() {
-        ZigzagTable zz;
-        for_each_block([&](int, int, const int16_t* b) {
-            if (S_.Ah == 0) ac_first_block(b, zz); else ac_refine_block(b, zz);
+        const uint64_t band = (S_.Se >= 63 ? ~0ull : (1ull << (S_.Se + 1)) - 1) & ~((1ull << S_.Ss) - 1);
+        for_each_block([&](int, int c, size_t block) {
+            const int16_t* b = F_.plane[c] + block * 64;
+            const uint64_t here = F_.masks[c].nz[S_.Al][block] & band;
+            if (S_.Ah == 0) ac_first_block(b, here); else ac_refine_block(b, here, F_.masks[c].nz[S_.Al + 1][block]);
         });
         flush_eobrun();
     }
 
-    void ac_first_block(const int16_t* b, const ZigzagTable& zz) {
-        int run = 0;
-        for (int k = S_.Ss; k <= S_.Se; k++) {
-            const int c = b[zz.natural[k]];
+    void ac_first_block(const int16_t* b, uint64_t m) {
+        int prev = S_.Ss - 1;
+        if (m) flush_eobrun();
+        for (; m; m &= m - 1) {
+            const int k = __builtin_ctzll(m), c = b[zz_.natural[k]];
             const int mag = (c < 0 ? -c : c) >> S_.Al;         // magnitudes are shifted, not the signed value
-            if (mag == 0) { run++; continue; }
-            flush_eobrun();
-            while (run > 15) { push(0, 0xF0, 0, 0); run -= 16; }
+            int run = k - prev - 1;
+            prev = k;
+            while (run > 15) { sink_.symbol(0, 0xF0, 0, 0); run -= 16; }
             const int nb = bit_length(mag);
-            push(0, (uint8_t)((run << 4) | nb), nb, (uint32_t)(c < 0 ? ~mag : mag));
-            run = 0;
+            sink_.symbol(0, (uint8_t)((run << 4) | nb), nb, (uint32_t)(c < 0 ? ~mag : mag));
         }
-        if (run > 0) { if (++eobrun_ == 0x7FFF) flush_eobrun(); }
+        if (prev < S_.Se) { if (++eobrun_ == 0x7FFF) flush_eobrun(); }
     }
 
-    void ac_refine_block(const int16_t* b, const ZigzagTable& zz) {
-        int mag[64];
-        int last_new = -1;                                     // last position that becomes non-zero in this scan
-        for (int k = S_.Ss; k <= S_.Se; k++) {
-            const int c = b[zz.natural[k]];
-            mag[k] = (c < 0 ? -c : c) >> S_.Al;
-            if (mag[k] == 1) last_new = k;
-        }
-        int run = 0;
-        std::vector<uint8_t>& corr = corr_;
-        corr.clear();
-        for (int k = S_.Ss; k <= S_.Se; k++) {
-            if (mag[k] == 0) { run++; continue; }
+    // m: positions of the band that are not zero; known: those that were not zero before this scan
+    void ac_refine_block(const int16_t* b, uint64_t m, uint64_t known) {
+        const uint64_t fresh = m & ~known;
+        const int last_new = fresh ? 63 - __builtin_clzll(fresh) : -1;   // last position that becomes non-zero in this scan
+        int run = 0, prev = S_.Ss - 1;
+        Bits corr{0, 0};                                       // correction bits met since the last symbol
+        for (; m; m &= m - 1) {
+            const int k = __builtin_ctzll(m), c = b[zz_.natural[k]];
+            run += k - prev - 1;
+            prev = k;
             while (run > 15 && k <= last_new) {                // sixteen zeros, only where a new coefficient still follows
                 flush_eobrun();
-                push(0, 0xF0, 0, 0);
+                sink_.symbol(0, 0xF0, 0, 0);
                 run -= 16;
-                push_bits(corr); corr.clear();
+                sink_.raw(corr.v, corr.n); corr = Bits{0, 0};
             }
-            if (mag[k] > 1) { corr.push_back((uint8_t)(mag[k] & 1)); continue; }     // known already: one more bit of it
+            if (known >> k & 1) {                              // one more bit of it
+                corr.v = corr.v << 1 | (uint64_t)(((c < 0 ? -c : c) >> S_.Al) & 1);
+                corr.n++;
+                continue;
+            }
             flush_eobrun();
-            push(0, (uint8_t)((run << 4) | 1), 1, b[zz.natural[k]] < 0 ? 0u : 1u);
-            push_bits(corr); corr.clear();
+            sink_.symbol(0, (uint8_t)((run << 4) | 1), 1, c < 0 ? 0u : 1u);
+            sink_.raw(corr.v, corr.n); corr = Bits{0, 0};
             run = 0;
         }
-        if (run > 0 || !corr.empty()) {
+        if (run + (S_.Se - prev) > 0 || corr.n) {
             eobrun_++;
-            pending_.insert(pending_.end(), corr.begin(), corr.end());
+            if (corr.n) {
+                if (!pending_.empty() && pending_.back().n + corr.n <= 64) pending_.back() = Bits{pending_.back().v << corr.n | corr.v, pending_.back().n + corr.n};
+                else pending_.push_back(corr);
+            }
             if (eobrun_ == 0x7FFF) flush_eobrun();
         }
     }
@@ -625,6 +714,7 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
         need += (size_t)img.bw[c] * img.bh[c] * 64;
     }
     if (need != coef_count) return kERange;
+    for (int c = 0; c < img.nc; c++) F.masks[c].fill(F.plane[c], (size_t)img.bw[c] * img.bh[c]);
     std::vector<uint8_t>& o = *out;
     o.push_back(0xFF); o.push_back(0xD8);
     bool done[4] = {false, false, false, false};
@@ -649,23 +739,24 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
     int scan_index = -1;
     for (const ScanSpec& S : default_script(img.nc)) {
         scan_index++;
-        ScanCoder coder(F, S, restart_interval);
-        coder.run();
+        TokenSink list;                                            // (only where the symbols are counted here)
+        if (!counts) ScanCoder<TokenSink>(F, S, restart_interval, &list).run();
         uint32_t freq[2][256];
         memset(freq, 0, sizeof freq);
         bool used[2] = {false, false};
         if (counts) {
             memcpy(freq, counts + (size_t)scan_index * kHistPerScan, sizeof freq);
             for (int s2 = 0; s2 < 2; s2++) for (int y = 0; y < 256; y++) if (freq[s2][y]) used[s2] = true;
-            // (a token whose symbol the counts do not hold would get no code: refuse counts that do not fit the coefficients)
-            for (const Token& t : coder.tokens) if (t.slot < kRawBits && freq[t.slot][t.sym] == 0) return kEFormat;
         } else {
-            for (const Token& t : coder.tokens) if (t.slot < kRawBits) { freq[t.slot][t.sym]++; used[t.slot] = true; }
+            for (const Token& t : list.tokens) if (t.slot < kRawBits) { freq[t.slot][t.sym]++; used[t.slot] = true; }
         }
         if (counts_out) memcpy(counts_out + (size_t)scan_index * kHistPerScan, freq, sizeof freq);
         HuffSpec H[2];
         const int cls = S.Ss == 0 ? 0 : 1;
-        for (int s = 0; s < 2; s++) if (used[s]) { build_table(freq[s], &H[s]); write_dht(&o, cls, s, H[s]); }
+        for (int s = 0; s < 2; s++) {
+            if (used[s]) { build_table(freq[s], &H[s]); write_dht(&o, cls, s, H[s]); }
+            else memset(H[s].size, 0, sizeof H[s].size);
+        }
         o.push_back(0xFF); o.push_back(0xDA);
         put_be16(&o, (uint32_t)(6 + 2 * S.ns));
         o.push_back((uint8_t)S.ns);
@@ -676,10 +767,16 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
         }
         o.push_back((uint8_t)S.Ss); o.push_back((uint8_t)S.Se); o.push_back((uint8_t)((S.Ah << 4) | S.Al));
         BitWriter bw(&o);
-        for (const Token& t : coder.tokens) {
-            if (t.slot == kRestartMark) { bw.marker((uint8_t)(0xD0 + t.sym)); continue; }
-            if (t.slot < kRawBits) bw.put(H[t.slot].code[t.sym], H[t.slot].size[t.sym]);
-            bw.put(t.bits, t.nbits);
+        FileSink file(&bw, H);
+        if (counts) {
+            ScanCoder<FileSink>(F, S, restart_interval, &file).run();
+            if (file.unknown) return kEFormat;                     // the counts do not fit the coefficients
+        } else {
+            for (const Token& t : list.tokens) {
+                if (t.slot == kRestartMark) file.restart(t.sym);
+                else if (t.slot == kRawBits) file.raw(t.bits, t.nbits);
+                else file.symbol(t.slot, t.sym, t.nbits, t.bits);
+            }
         }
         bw.finish();
     }

@@ -1557,6 +1557,81 @@ int pcr_transcode_symbol_counts(const void* src_jpeg, size_t src_bytes, const in
     return enc::transcode_progressive((const uint8_t*)src_jpeg, src_bytes, coef, coef_count, restart_interval, nullptr, nullptr, counts);
 }
 
+// The batch of pcr_transcode_progressive(_counted) for the files a record was made of: one decode for coefficients and
+// counts, one copy of both to pinned memory (30 MB of coefficients took 10 ms through pageable memory), the files coded by
+// several threads straight from there.
+int pcr_transcode_batch(pcr_record* r, const void* const* files, const size_t* sizes, uint32_t n, uint32_t restart_interval, int device_counts, int threads,
+                        void* out, const uint64_t* out_off, uint64_t* written, void* stream) {
+    if (!r || !files || !sizes || !out || !out_off || !written || n != r->hdr.n || threads < 1) return PCR_E_ARG;
+    if (restart_interval > 65535) return PCR_E_RANGE;
+    const int k = (int)r->hdr.k_avail;
+    int rc = check_scan_group(r, k);
+    if (rc) return rc;
+    HIP_TRY(hipSetDevice(r->device));
+    hipStream_t s = (hipStream_t)stream;
+    Plan* plan = nullptr;
+    r->resident_k = 0;                                       // the planes are refined in place, as for the coefficient export
+    rc = run_entropy_stages(r, 0, k, s, true, &plan);
+    if (rc) return rc;
+    call_end(r);
+    // Images in groups of about kTranscodePinned bytes of coefficients: what is pinned is bounded, except by a single image.
+    constexpr size_t kTranscodePinned = 64u << 20;
+    size_t most = 0;
+    std::vector<uint32_t> group(1, 0);
+    for (uint32_t i = 0; i < n; i++) {
+        if (i > group.back() && (r->coef_off[i + 1] - r->coef_off[group.back()]) * sizeof(int16_t) > kTranscodePinned) group.push_back(i);
+        most = std::max<size_t>(most, (r->coef_off[i + 1] - r->coef_off[group.back()]) * sizeof(int16_t));
+    }
+    group.push_back(n);
+    const size_t hist_bytes = device_counts ? (size_t)n * kHistPerImage * sizeof(uint32_t) : 0, hist_at = arena_round(most);
+    uint8_t *host = nullptr, *dev = nullptr;
+    if (hipHostMalloc((void**)&host, hist_at + hist_bytes + 1, hipHostMallocDefault) != hipSuccess ||
+        hipMalloc((void**)&dev, arena_round((size_t)r->coef_off[n] * sizeof(int16_t)) + hist_bytes + 1) != hipSuccess) rc = PCR_E_NOMEM;
+    int16_t* d_coef = reinterpret_cast<int16_t*>(dev);
+    uint32_t* d_hist = reinterpret_cast<uint32_t*>(dev + arena_round((size_t)r->coef_off[n] * sizeof(int16_t)));
+    if (!rc) {
+        hipLaunchKernelGGL(k_export_natural, dim3(2048), dim3(256), 0, s, r->d.coef, d_coef, (size_t)r->coef_off[n]);
+        if (device_counts)
+            hipLaunchKernelGGL(k_symbol_hist, dim3(n, kScriptScansMax), dim3(64), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off, restart_interval, d_hist);
+        if (hipGetLastError() != hipSuccess) rc = PCR_E_DEVICE;
+    }
+    if (!rc && device_counts && hipMemcpyAsync(host + hist_at, d_hist, hist_bytes, hipMemcpyDeviceToHost, s) != hipSuccess) rc = PCR_E_DEVICE;
+    std::vector<int> status(n, PCR_OK);
+    for (size_t e = 0; !rc && e + 1 < group.size(); e++) {
+        const uint32_t first = group[e], last = group[e + 1];
+        const uint64_t at = r->coef_off[first];
+        if (hipMemcpyAsync(host, d_coef + at, (size_t)(r->coef_off[last] - at) * sizeof(int16_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess) { rc = PCR_E_DEVICE; break; }
+        std::atomic<uint32_t> next(first);
+        auto work = [&]() {
+            std::vector<uint8_t> bytes;
+            for (;;) {
+                const uint32_t i = next.fetch_add(1);
+                if (i >= last) break;
+                bytes.clear();
+                const int16_t* coef = reinterpret_cast<const int16_t*>(host) + (r->coef_off[i] - at);
+                const uint32_t* counts = device_counts ? reinterpret_cast<const uint32_t*>(host + hist_at) + (size_t)i * kHistPerImage : nullptr;
+                status[i] = enc::transcode_progressive((const uint8_t*)files[i], sizes[i], coef, (size_t)(r->coef_off[i + 1] - r->coef_off[i]), restart_interval, &bytes, counts);
+                written[i] = bytes.size();
+                if (status[i]) continue;
+                if (bytes.size() > out_off[i + 1] - out_off[i]) status[i] = PCR_E_RANGE;
+                else memcpy((uint8_t*)out + out_off[i], bytes.data(), bytes.size());
+            }
+        };
+        std::vector<std::thread> pool;
+        for (uint32_t t = 1; t < std::min((uint32_t)threads, last - first); t++) pool.emplace_back(work);
+        work();
+        for (auto& t : pool) t.join();
+    }
+    if (rc) (void)hipStreamSynchronize(s);                    // (the buffers go)
+    if (dev) (void)hipFree(dev);
+    if (host) (void)hipHostFree(host);
+    if (rc) { (void)hipGetLastError(); return rc; }
+    for (uint32_t i = 0; i < n; i++) if (status[i] && status[i] != PCR_E_RANGE) return status[i];
+    for (uint32_t i = 0; i < n; i++) if (status[i]) return status[i];
+    return PCR_OK;
+}
+
 int pcr_symbol_histograms(pcr_record* r, uint32_t restart_interval, uint32_t* d_hist, void* stream) {
     if (!r || !d_hist) return PCR_E_ARG;
     if (restart_interval > 65535) return PCR_E_RANGE;
