@@ -1356,6 +1356,9 @@ __global__ void __launch_bounds__(256) k_crop_resize(const uint32_t* __restrict_
 //            then chroma replication + colour + one rounding + store: one lane per group of 12 output bytes (4 RGB
 //            pixels; 8 gray ones) of one pixel row of one MCU, lanes ordered along the image rows, the samples
 //            read from LDS as 16- and 8-byte vectors, the group written with one (possibly unaligned) store.
+// Two pixel rows per lane in phase B (indices, and with 4:2:0 the chroma terms, made once for both), chroma kept around
+// zero and the conversion's own rounding took 1024 photographs from 361 to 275 us (scan group 2) and from 527 to 439
+// (scan group 10: 0.93 GB of coefficients, masks and pixels, 2.1 TB/s; the rest is vector issue).
 // The kernel is bound by memory latency times occupancy, not by arithmetic.  Occupancy is bounded by LDS, which is
 // why the samples go through it in halves (128 bytes per lane at a time: four wavefronts per SIMD instead of two,
 // measured a third faster); and the chain of dependent trips to memory is kept short: the image's descriptor is read
@@ -1412,6 +1415,26 @@ PCR_D float idct_fold(uint32_t k) {
 // (The conversion instruction saturates and is exact on integers, which floor(v + 1/2) is.)
 PCR_D uint32_t put_u8(float v, uint32_t which, uint32_t word) {
     return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_floorf(v + 0.5f), which, word);
+}
+
+// four bytes, each the value rounded to the nearest integer (halves to even: the callers' values are biased) and clamped
+PCR_D uint32_t four_u8(float a, float b, float c, float d) {
+    uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(a, 0, 0);
+    w = __builtin_amdgcn_cvt_pk_u8_f32(b, 1, w); w = __builtin_amdgcn_cvt_pk_u8_f32(c, 2, w);
+    return __builtin_amdgcn_cvt_pk_u8_f32(d, 3, w);
+}
+// The colour conversion of all pixel kernels (the same instructions everywhere, so that the pixels do not depend on which
+// kernel wrote them): luma y with kHalfUp in it, chroma u, v around zero, g: the part of green that is chroma.
+PCR_D float chroma_green(float u, float v) { return __builtin_fmaf(-0.714136f, v, -0.344136f * u); }
+PCR_D void to_rgb(float y, float u, float v, float g, float* r, float* gg, float* b) {
+    *r = __builtin_fmaf(1.402f, v, y); *gg = y + g; *b = __builtin_fmaf(1.772f, u, y);
+}
+// the twelve bytes of four pixels
+PCR_D void rgb_words(const float y[4], const float u[4], const float v[4], const float g[4], uint32_t w[3]) {
+    float r[4], gg[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) to_rgb(y[i], u[i], v[i], g[i], &r[i], &gg[i], &b[i]);
+    w[0] = four_u8(r[0], gg[0], b[0], r[1]); w[1] = four_u8(gg[1], b[1], r[2], gg[2]); w[2] = four_u8(b[2], r[3], gg[3], b[3]);
 }
 
 // a value per component, picked by a per-lane component number out of three wave-uniform ones
@@ -1478,10 +1501,16 @@ PCR_D int pix_dc(const DevRecord& R, const PixBlock& B, int dcv, const ApplyList
         if (rlc->sc[e].Ss == 0 && dc_refinement_bit(R, rlc->sc[e], B.brow, B.bcol, B.hs, B.vs, B.covered)) dcv |= 1 << rlc->sc[e].Al;
     return dcv;
 }
+// What is added to a component's samples, and the range they are clamped to.  Chroma lies around zero.  Luma carries
+// kHalfUp, two units in the last place of a sample: the conversion to bytes rounds halves to even, and so rounds them up.
+// (Adding 1/2 and rounding down were two more instructions per byte, taking 128 from chroma two per pixel.)
+constexpr float kHalfUp = 0x1p-15f;
+struct PixLevel { float shift, lo, hi; };
+PCR_D PixLevel pix_level(bool luma) { return PixLevel{luma ? 128.f + kHalfUp : 0.f, luma ? 0.f : -128.f, luma ? 255.f : 127.f}; }
 // Refinement replay, de-quantisation and the 8x8 inverse transform of the lane's block; the clamped samples are left in
 // F[8 y + x].  qc: the component's folded quantiser steps (zig-zag order); rlc: its refinement scan list.
 template <bool kRefine>
-PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, float F[64]) {
+PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, const PixLevel& L, float F[64]) {
     int ci[64];
 #pragma unroll
     for (int ch = 0; ch < 8; ch++) {
@@ -1522,8 +1551,8 @@ PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8],
         F[zigzag_lookup(4 * k4 + 2)] = (float)ci[4 * k4 + 2] * qq.z; F[zigzag_lookup(4 * k4 + 3)] = (float)ci[4 * k4 + 3] * qq.w;
     }
     // the level shift: the DC term reaches every sample with weight one (its folded factor is exactly 1/8 and the
-    // transforms only add it), so 128 is added to it once instead of to the 64 samples
-    F[0] += 128.f;
+    // transforms only add it), so it is added to that once instead of to the 64 samples
+    F[0] += L.shift;
 #pragma unroll
     for (int r = 0; r < 8; r++)
         idct8_scaled(F[8 * r], F[8 * r + 1], F[8 * r + 2], F[8 * r + 3], F[8 * r + 4], F[8 * r + 5], F[8 * r + 6], F[8 * r + 7]);
@@ -1531,7 +1560,7 @@ PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8],
     for (int x = 0; x < 8; x++)
         idct8_scaled(F[x], F[8 + x], F[16 + x], F[24 + x], F[32 + x], F[40 + x], F[48 + x], F[56 + x]);
 #pragma unroll
-    for (int e = 0; e < 64; e++) F[e] = clamp255(F[e]);
+    for (int e = 0; e < 64; e++) F[e] = __builtin_amdgcn_fmed3f(F[e], L.lo, L.hi);
 }
 // rows y0 .. y0 + kRows - 1 of the block's samples to dst[(y - y0) * row_len + x]
 template <int y0, int kRows>
@@ -1546,7 +1575,7 @@ PCR_D void pix_put_rows(const float F[64], float* dst, uint32_t row_len) {
 template <bool kRefine>
 PCR_D void pix_finish(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, float* dst, uint32_t row_len) {
     float F[64];
-    pix_samples<kRefine>(R, B, v, qc, rlc, F);
+    pix_samples<kRefine>(R, B, v, qc, rlc, pix_level(B.c == 0), F);
     pix_put_rows<0, 8>(F, dst, row_len);
 }
 // Half kHalf (0: upper, 1: lower) of the pixel rows of an MCU: the part of the lane's block that lies in it, to the
@@ -1605,7 +1634,7 @@ PCR_D void store_head(uint8_t* p, uint32_t w0, uint32_t w1, uint32_t w2, uint32_
 }
 
 template <bool kRefine, bool kPlanes>
-__global__ void __launch_bounds__(kPixLanes) k_pixel(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out,
+__global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out,
                                                      const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx,
                                                      const CropBox* __restrict__ boxes) {
     // samples of half the pixel rows of the run: 32 per block
@@ -1614,8 +1643,9 @@ __global__ void __launch_bounds__(kPixLanes) k_pixel(DevRecord R, const PixelTil
     // four banks apart, so that lanes of different components read them without bank conflicts
     __shared__ __attribute__((aligned(16))) float qz[kMaxComp][68];
     __shared__ ApplyList rl[kRefine ? kMaxComp : 1];       // refinement scan lists of the components (n = 0: none)
-    __shared__ uint32_t org[kPixLanes];                    // per MCU of the run: its first pixel, counted in pixels from the image's first (< 2^32)
-    __shared__ uint16_t visw[kPixLanes], vish[kPixLanes];  // ... and how many of its pixel columns / rows lie inside the image
+    // per MCU of the run: its first byte, counted from the first one of the run's first row of MCUs; how many of its pixel
+    // columns and rows lie inside the image (low and high half)
+    __shared__ uint2 place[kPixLanes];
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), mcu0 = uni(tiles[item].mcu0);
@@ -1642,6 +1672,7 @@ __global__ void __launch_bounds__(kPixLanes) k_pixel(DevRecord R, const PixelTil
         }
     }
     const bool dead = uni((uint32_t)(R.status[timg] != kOk)) != 0;
+    const uint32_t row0 = mcu0 / mcux;                      // the run's first row of MCUs
     // ---- phase A, first half: the lane's block and its loads ----
     const uint32_t m = (tid * recip16(bpm)) >> 16, j = tid - m * bpm;
     const bool mine = !dead && m < nm;
@@ -1661,10 +1692,9 @@ __global__ void __launch_bounds__(kPixLanes) k_pixel(DevRecord R, const PixelTil
     pix_quant_table(R, ip, nc, qz, tid, kPixLanes);
     if (tid < nm) {
         const uint32_t M = mcu0 + tid, my = M / mcux, mx = M - my * mcux;
-        org[tid] = my * mcu_px_h * W + mx * mcu_px_w;
         const uint32_t x = mx * mcu_px_w, y = my * mcu_px_h;
-        visw[tid] = (uint16_t)(x >= W ? 0 : (W - x < mcu_px_w ? W - x : mcu_px_w));
-        vish[tid] = (uint16_t)(y >= H ? 0 : (H - y < mcu_px_h ? H - y : mcu_px_h));
+        const uint32_t vw = x >= W ? 0 : (W - x < mcu_px_w ? W - x : mcu_px_w), vh = y >= H ? 0 : (H - y < mcu_px_h ? H - y : mcu_px_h);
+        place[tid] = uint2{((my - row0) * mcu_px_h * W + x) * nc, vw | vh << 16};
     }
     __syncthreads();
     // ---- phase A, second half: the block's samples, in registers ----
@@ -1672,8 +1702,9 @@ __global__ void __launch_bounds__(kPixLanes) k_pixel(DevRecord R, const PixelTil
     const bool flatb = mine && B.zm <= 1;                   // flat: one sample stands for the block
     if (mine) {
         const ApplyList* rlc = &rl[kRefine ? B.c : 0];
-        if (flatb) S[0] = clamp255((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + 128.f);
-        else pix_samples<kRefine>(R, B, v, qz[B.c], rlc, S);
+        const PixLevel L = pix_level(kPlanes || B.c == 0);   // (planes of bytes: every component as it is)
+        if (flatb) S[0] = __builtin_amdgcn_fmed3f((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + L.shift, L.lo, L.hi);
+        else pix_samples<kRefine>(R, B, v, qz[B.c], rlc, L, S);
     }
     if (kPlanes) {
         // Instead of pixels: the lane's block, rounded, into the component's own plane of bytes (`out`: one byte per
@@ -1686,29 +1717,32 @@ __global__ void __launch_bounds__(kPixLanes) k_pixel(DevRecord R, const PixelTil
             for (int y = 0; y < 8; y++) {
                 uint2 w;
                 if (flatb) {
-                    w.x = put_u8(S[0], 0, 0); w.x = put_u8(S[0], 1, w.x); w.x = put_u8(S[0], 2, w.x); w.x = put_u8(S[0], 3, w.x);
-                    w.y = w.x;
+                    w.x = w.y = four_u8(S[0], S[0], S[0], S[0]);
                 } else {
-                    w.x = put_u8(S[8 * y], 0, 0); w.x = put_u8(S[8 * y + 1], 1, w.x); w.x = put_u8(S[8 * y + 2], 2, w.x); w.x = put_u8(S[8 * y + 3], 3, w.x);
-                    w.y = put_u8(S[8 * y + 4], 0, 0); w.y = put_u8(S[8 * y + 5], 1, w.y); w.y = put_u8(S[8 * y + 6], 2, w.y); w.y = put_u8(S[8 * y + 7], 3, w.y);
+                    w.x = four_u8(S[8 * y], S[8 * y + 1], S[8 * y + 2], S[8 * y + 3]);
+                    w.y = four_u8(S[8 * y + 4], S[8 * y + 5], S[8 * y + 6], S[8 * y + 7]);
                 }
                 *reinterpret_cast<uint2*>(pd + (size_t)y * pw) = w;
             }
         }
         return;
     }
-    // ---- phase B: one lane per group of output bytes of one pixel row of one MCU, the upper half of the pixel rows of
-    // the MCUs first, then the lower: the samples of half a run are what the workgroup holds in LDS at a time ----
+    // ---- phase B: one lane per group of output bytes of two pixel rows of one MCU, the upper half of the pixel rows of
+    // the MCUs first, then the lower: the samples of half a run are what the workgroup holds in LDS at a time.  (Two
+    // rows at a time: the indices, and with 4:2:0 the chroma terms, serve both.) ----
     const uint32_t shx0 = G.hs[0] == G.hmax ? 0 : 1, shy0 = G.vs[0] == G.vmax ? 0 : 1;       // sampling factors are 1 or 2
     const uint32_t shx1 = nc > 1 && G.hs[1] != G.hmax, shy1 = nc > 1 && G.vs[1] != G.vmax;
     const uint32_t shx2 = nc > 2 && G.hs[2] != G.hmax, shy2 = nc > 2 && G.vs[2] != G.vmax;
-    const uint32_t ppg = nc == 1 ? 8u : 4u;                 // pixels per group: 8 gray bytes, or 12 bytes of RGB
+    const bool halves = (shx1 & shy1 & shx2 & shy2) && !shx0 && !shy0;                      // 4:2:0
+    const uint32_t ppg = nc == 1 ? 8u : 4u;                 // pixels per group and row: 8 gray bytes, or 12 bytes of RGB
     const uint32_t gpm = mcu_px_w / ppg;                    // groups per pixel row of an MCU: 1, 2 or 4
     const uint32_t lg = gpm == 4 ? 2u : (gpm == 2 ? 1u : 0u);
     const uint32_t half_h = mcu_px_h >> 1;                  // pixel rows of an MCU per half: 4 or 8
-    const uint32_t items = nm * half_h * gpm;
+    const uint32_t items = nm * (half_h >> 1) * gpm;
     const uint32_t rcpn = nm > 1 ? 0xFFFFFFFFu / nm + 1u : 0u;       // q / nm as the high word of q * rcpn: exact while q * nm < 2^32
     const uint32_t mstride = bpm * 32;                      // samples of an MCU in one half
+    uint8_t* const first = out + R.out_off[timg] + (size_t)row0 * mcu_px_h * W * nc;
+    const uint32_t line = W * nc;
     // component c's four samples for pixels x0.. of row ly (counted inside the half) of MCU mm: a flat component has one per block
     auto fetch = [&](uint32_t c, uint32_t mm, uint32_t ly, uint32_t x0, uint32_t shx, uint32_t shy, float s[4]) {
         if (G.flat[c]) {
@@ -1726,50 +1760,70 @@ __global__ void __launch_bounds__(kPixLanes) k_pixel(DevRecord R, const PixelTil
         }
         __syncthreads();
         for (uint32_t it = tid; it < items; it += kPixLanes) {
-            // lanes run along the image rows: group, then MCU, then pixel row
+            // lanes run along the image rows: group, then MCU, then pair of pixel rows
             const uint32_t g = it & (gpm - 1), q = it >> lg;
-            const uint32_t lyh = nm > 1 ? __umulhi(q, rcpn) : q, mm = q - lyh * nm;
-            const uint32_t ly = lyh + half * half_h;        // the pixel row inside the MCU
-            const uint32_t x0 = g * ppg, vw = visw[mm];
-            if (ly >= vish[mm] || x0 >= vw) continue;
-            uint8_t* wp = out + R.out_off[timg] + ((size_t)org[mm] + (size_t)ly * W + x0) * nc;
+            const uint32_t lyp = nm > 1 ? __umulhi(q, rcpn) : q, mm = q - lyp * nm, lyh = 2 * lyp;
+            const uint32_t ly = lyh + half * half_h;        // the first of the two pixel rows inside the MCU
+            const uint2 pl = place[mm];
+            const uint32_t x0 = g * ppg, vw = pl.y & 0xFFFFu, vh = pl.y >> 16;
+            if (ly >= vh || x0 >= vw) continue;
+            uint8_t* const wp = first + (pl.x + ly * line + x0 * nc);
             const uint32_t left = vw - x0;                  // pixels of the group inside the image
+            const bool both = ly + 1 < vh;
             if (nc == 1) {
-                float a[4], bq[4];
-                fetch(0, mm, lyh, x0, 0, 0, a); fetch(0, mm, lyh, x0 + 4, 0, 0, bq);
-                uint32_t w0 = 0, w1 = 0;
-                if (!dead) {
-                    w0 = put_u8(a[0], 0, w0); w0 = put_u8(a[1], 1, w0); w0 = put_u8(a[2], 2, w0); w0 = put_u8(a[3], 3, w0);
-                    w1 = put_u8(bq[0], 0, w1); w1 = put_u8(bq[1], 1, w1); w1 = put_u8(bq[2], 2, w1); w1 = put_u8(bq[3], 3, w1);
-                }
-                if (left >= 8) {
-                    struct __attribute__((packed, aligned(1))) Eight { uint32_t a, b; };
-                    Eight e8; e8.a = w0; e8.b = w1;
-                    *reinterpret_cast<Eight*>(wp) = e8;
-                } else {
-                    store_head(wp, w0, w1, 0u, left);
+#pragma unroll
+                for (uint32_t row = 0; row < 2; row++) {
+                    float a[4], bq[4];
+                    fetch(0, mm, lyh + row, x0, 0, 0, a); fetch(0, mm, lyh + row, x0 + 4, 0, 0, bq);
+                    uint32_t w0 = 0, w1 = 0;
+                    if (!dead) { w0 = four_u8(a[0], a[1], a[2], a[3]); w1 = four_u8(bq[0], bq[1], bq[2], bq[3]); }
+                    if (row && !both) continue;
+                    if (left >= 8) {
+                        struct __attribute__((packed, aligned(1))) Eight { uint32_t a, b; };
+                        Eight e8; e8.a = w0; e8.b = w1;
+                        *reinterpret_cast<Eight*>(wp + row * line) = e8;
+                    } else {
+                        store_head(wp + row * line, w0, w1, 0u, left);
+                    }
                 }
             } else {
-                float ys[4], cb[4], cr[4];
-                uint32_t w0 = 0, w1 = 0, w2 = 0;
-                if (!dead) {
-                    fetch(0, mm, lyh, x0, shx0, shy0, ys); fetch(1, mm, lyh, x0, shx1, shy1, cb); fetch(2, mm, lyh, x0, shx2, shy2, cr);
-                    float r[4], gg[4], bb[4];
-#pragma unroll
-                    for (int i = 0; i < 4; i++) {
-                        const float u = cb[i] - 128.f, w = cr[i] - 128.f;
-                        r[i] = ys[i] + 1.402f * w; gg[i] = ys[i] - 0.344136f * u - 0.714136f * w; bb[i] = ys[i] + 1.772f * u;
+                auto store = [&](uint32_t row, const uint32_t w[3]) {
+                    uint8_t* const p = wp + row * line;
+                    if (left >= 4) {
+                        struct __attribute__((packed, aligned(1))) Twelve { uint32_t a, b, c; };
+                        Twelve tw; tw.a = w[0]; tw.b = w[1]; tw.c = w[2];
+                        *reinterpret_cast<Twelve*>(p) = tw;        // one (possibly unaligned) 12-byte store
+                    } else {
+                        store_head(p, w[0], w[1], w[2], left * 3);
                     }
-                    w0 = put_u8(r[0], 0, w0); w0 = put_u8(gg[0], 1, w0); w0 = put_u8(bb[0], 2, w0); w0 = put_u8(r[1], 3, w0);
-                    w1 = put_u8(gg[1], 0, w1); w1 = put_u8(bb[1], 1, w1); w1 = put_u8(r[2], 2, w1); w1 = put_u8(gg[2], 3, w1);
-                    w2 = put_u8(bb[2], 0, w2); w2 = put_u8(r[3], 1, w2); w2 = put_u8(gg[3], 2, w2); w2 = put_u8(bb[3], 3, w2);
-                }
-                if (left >= 4) {
-                    struct __attribute__((packed, aligned(1))) Twelve { uint32_t a, b, c; };
-                    Twelve tw; tw.a = w0; tw.b = w1; tw.c = w2;
-                    *reinterpret_cast<Twelve*>(wp) = tw;           // one (possibly unaligned) 12-byte store
+                };
+                if (dead) {
+                    const uint32_t w[3] = {0, 0, 0};
+                    store(0, w);
+                    if (both) store(1, w);
+                } else if (halves) {                        // two chroma samples for the eight pixels
+                    float cb[4], cr[4];
+                    fetch(1, mm, lyh, x0, 1, 1, cb); fetch(2, mm, lyh, x0, 1, 1, cr);
+                    const float g0 = chroma_green(cb[0], cr[0]), g1 = chroma_green(cb[2], cr[2]);
+                    const float u[4] = {cb[0], cb[0], cb[2], cb[2]}, v[4] = {cr[0], cr[0], cr[2], cr[2]}, gc[4] = {g0, g0, g1, g1};
+#pragma unroll
+                    for (uint32_t row = 0; row < 2; row++) {
+                        if (row && !both) continue;
+                        float ys[4]; uint32_t w[3];
+                        fetch(0, mm, lyh + row, x0, 0, 0, ys);
+                        rgb_words(ys, u, v, gc, w);
+                        store(row, w);
+                    }
                 } else {
-                    store_head(wp, w0, w1, w2, left * 3);
+#pragma unroll 1
+                    for (uint32_t row = 0; row < (both ? 2u : 1u); row++) {
+                        float ys[4], cb[4], cr[4], gc[4]; uint32_t w[3];
+                        fetch(0, mm, lyh + row, x0, shx0, shy0, ys); fetch(1, mm, lyh + row, x0, shx1, shy1, cb); fetch(2, mm, lyh + row, x0, shx2, shy2, cr);
+#pragma unroll
+                        for (int i = 0; i < 4; i++) gc[i] = chroma_green(cb[i], cr[i]);
+                        rgb_words(ys, cb, cr, gc, w);
+                        store(row, w);
+                    }
                 }
             }
         }
@@ -1808,7 +1862,7 @@ PCR_D void flat_cell_words(const DevRecord& R, const ImgDesc& D, const int16_t* 
     uint32_t plane0 = 0;
 #pragma unroll
     for (uint32_t c = 0; c < kMaxComp; c++) {
-        s[c] = 128.f;
+        s[c] = 0.f;
         if (c < D.nc) {
             const uint32_t bcol = (cx * D.hs[c]) >> (D.hmax - 1), brow = (cy * D.vs[c]) >> (D.vmax - 1);      // (sampling factors are 1 or 2)
             // (picked with compares: an index computed at run time would put the whole descriptor into scratch memory)
@@ -1817,14 +1871,16 @@ PCR_D void flat_cell_words(const DevRecord& R, const ImgDesc& D, const int16_t* 
             const uint32_t qprec = tq == 0 ? D.qprec[0] : (tq == 1 ? D.qprec[1] : (tq == 2 ? D.qprec[2] : D.qprec[3]));
             const uint8_t* q = R.rec + qoff;
             const float q0 = (qprec ? (float)ld_be16(q) : (float)q[0]) * 0.125f;
-            s[c] = clamp255((float)dcp[plane0 + brow * D.bw[c] + bcol] * q0 + 128.f);
+            const PixLevel L = pix_level(c == 0);
+            s[c] = __builtin_amdgcn_fmed3f((float)dcp[plane0 + brow * D.bw[c] + bcol] * q0 + L.shift, L.lo, L.hi);
             plane0 += (uint32_t)D.bw[c] * D.bh[c];
         }
     }
-    if (D.nc == 1) { uint32_t g = put_u8(s[0], 0, 0); g |= g << 8; g |= g << 16; *w0 = g; *w1 = g; *w2 = g; }
+    if (D.nc == 1) { uint32_t g = __builtin_amdgcn_cvt_pk_u8_f32(s[0], 0, 0); g |= g << 8; g |= g << 16; *w0 = g; *w1 = g; *w2 = g; }
     else {
-        const float u = s[1] - 128.f, w = s[2] - 128.f;
-        const uint32_t r = put_u8(s[0] + 1.402f * w, 0, 0), gq = put_u8(s[0] - 0.344136f * u - 0.714136f * w, 0, 0), bq = put_u8(s[0] + 1.772f * u, 0, 0);
+        float rf, gf, bf;
+        to_rgb(s[0], s[1], s[2], chroma_green(s[1], s[2]), &rf, &gf, &bf);
+        const uint32_t r = __builtin_amdgcn_cvt_pk_u8_f32(rf, 0, 0), gq = __builtin_amdgcn_cvt_pk_u8_f32(gf, 0, 0), bq = __builtin_amdgcn_cvt_pk_u8_f32(bf, 0, 0);
         *w0 = r | (gq << 8) | (bq << 16) | (r << 24); *w1 = gq | (bq << 8) | (r << 16) | (gq << 24); *w2 = bq | (r << 8) | (gq << 16) | (bq << 24);
     }
     if (dead) { *w0 = 0; *w1 = 0; *w2 = 0; }
@@ -2298,12 +2354,13 @@ struct TailView {
 PCR_D void tail_pixel(const TailView& V, uint32_t x, uint32_t y, float px[3]) {
     if (V.dead) { px[0] = px[1] = px[2] = 0.f; return; }
     const float s0 = V.plane[0][((y >> V.shy[0]) & V.fm[0]) * V.len[0] + ((x >> V.shx[0]) & V.fm[0])];
-    if (V.nc == 1) { px[0] = fminf(fmaxf(__builtin_floorf(s0 + 0.5f), 0.f), 255.f); px[1] = px[2] = 0.f; return; }
-    const float u = V.plane[1][((y >> V.shy[1]) & V.fm[1]) * V.len[1] + ((x >> V.shx[1]) & V.fm[1])] - 128.f;
-    const float w = V.plane[2][((y >> V.shy[2]) & V.fm[2]) * V.len[2] + ((x >> V.shx[2]) & V.fm[2])] - 128.f;
-    px[0] = fminf(fmaxf(__builtin_floorf(s0 + 1.402f * w + 0.5f), 0.f), 255.f);
-    px[1] = fminf(fmaxf(__builtin_floorf(s0 - 0.344136f * u - 0.714136f * w + 0.5f), 0.f), 255.f);
-    px[2] = fminf(fmaxf(__builtin_floorf(s0 + 1.772f * u + 0.5f), 0.f), 255.f);
+    auto level = [](float v) { return __builtin_amdgcn_fmed3f(__builtin_rintf(v), 0.f, 255.f); };
+    if (V.nc == 1) { px[0] = level(s0); px[1] = px[2] = 0.f; return; }
+    const float u = V.plane[1][((y >> V.shy[1]) & V.fm[1]) * V.len[1] + ((x >> V.shx[1]) & V.fm[1])];
+    const float w = V.plane[2][((y >> V.shy[2]) & V.fm[2]) * V.len[2] + ((x >> V.shx[2]) & V.fm[2])];
+    float r, g, b;
+    to_rgb(s0, u, w, chroma_green(u, w), &r, &g, &b);
+    px[0] = level(r); px[1] = level(g); px[2] = level(b);
 }
 
 template <bool kRefine>
@@ -2368,7 +2425,8 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
             const ApplyList* rlc = &rl[kRefine ? B.c : 0];
             const uint32_t row_len = seg_m * B.hs * 8;
             float* dst = tile + seg_m * pick3(B.c, G.rb[0], G.rb[1], G.rb[2]) + by * 8 * row_len + (ml * B.hs + bx) * 8;
-            if (B.zm <= 1) dst[0] = clamp255((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + 128.f);
+            const PixLevel L = pix_level(B.c == 0);
+            if (B.zm <= 1) dst[0] = __builtin_amdgcn_fmed3f((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + L.shift, L.lo, L.hi);
             else pix_finish<kRefine>(R, B, v, qz[B.c], rlc, dst, row_len);
         }
         __syncthreads();
