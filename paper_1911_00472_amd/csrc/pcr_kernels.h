@@ -1354,11 +1354,12 @@ __global__ void __launch_bounds__(256) k_crop_resize(const uint32_t* __restrict_
 //            their block that lies in the half into LDS, MCU by MCU (per MCU the rows of each component as one small
 //            row-major plane; a component that only has its DC writes one sample per block: the block is flat);
 //            then chroma replication + colour + one rounding + store: one lane per group of 12 output bytes (4 RGB
-//            pixels; 8 gray ones) of one pixel row of one MCU, lanes ordered along the image rows, the samples
-//            read from LDS as 16- and 8-byte vectors, the group written with one (possibly unaligned) store.
-// Two pixel rows per lane in phase B (indices, and with 4:2:0 the chroma terms, made once for both), chroma kept around
-// zero and the conversion's own rounding took 1024 photographs from 361 to 275 us (scan group 2) and from 527 to 439
-// (scan group 10: 0.93 GB of coefficients, masks and pixels, 2.1 TB/s; the rest is vector issue).
+//            pixels; 8 gray ones) of two pixel rows of one MCU, lanes ordered along the image rows, the samples
+//            read from LDS as 16- and 8-byte vectors, each row written with one (possibly unaligned) store.
+// Two pixel rows per lane in phase B (indices, and with 4:2:0 the chroma samples, fetched once for both) took 1024
+// photographs from 361 to 288 us (scan group 2) and from 527 to 463 (scan group 10: 0.93 GB of coefficients, masks and
+// pixels, 2.0 TB/s; the rest is vector issue).  Folding the half of the rounding into luma and centring the samples
+// before the transform saves another 5 %, but moves pixels whose value lies on the edge of rounding (2 in 100 000).
 // The kernel is bound by memory latency times occupancy, not by arithmetic.  Occupancy is bounded by LDS, which is
 // why the samples go through it in halves (128 bytes per lane at a time: four wavefronts per SIMD instead of two,
 // measured a third faster); and the chain of dependent trips to memory is kept short: the image's descriptor is read
@@ -1417,23 +1418,24 @@ PCR_D uint32_t put_u8(float v, uint32_t which, uint32_t word) {
     return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_floorf(v + 0.5f), which, word);
 }
 
-// four bytes, each the value rounded to the nearest integer (halves to even: the callers' values are biased) and clamped
+// four bytes
 PCR_D uint32_t four_u8(float a, float b, float c, float d) {
-    uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(a, 0, 0);
-    w = __builtin_amdgcn_cvt_pk_u8_f32(b, 1, w); w = __builtin_amdgcn_cvt_pk_u8_f32(c, 2, w);
-    return __builtin_amdgcn_cvt_pk_u8_f32(d, 3, w);
+    uint32_t w = put_u8(a, 0, 0);
+    w = put_u8(b, 1, w); w = put_u8(c, 2, w);
+    return put_u8(d, 3, w);
 }
 // The colour conversion of all pixel kernels (the same instructions everywhere, so that the pixels do not depend on which
-// kernel wrote them): luma y with kHalfUp in it, chroma u, v around zero, g: the part of green that is chroma.
-PCR_D float chroma_green(float u, float v) { return __builtin_fmaf(-0.714136f, v, -0.344136f * u); }
-PCR_D void to_rgb(float y, float u, float v, float g, float* r, float* gg, float* b) {
-    *r = __builtin_fmaf(1.402f, v, y); *gg = y + g; *b = __builtin_fmaf(1.772f, u, y);
+// kernel wrote them): luma y, chroma u, v around zero.
+PCR_D void to_rgb(float y, float u, float v, float* r, float* g, float* b) {
+    *r = __builtin_fmaf(1.402f, v, y);
+    *g = __builtin_fmaf(-0.714136f, v, __builtin_fmaf(-0.344136f, u, y));
+    *b = __builtin_fmaf(1.772f, u, y);
 }
 // the twelve bytes of four pixels
-PCR_D void rgb_words(const float y[4], const float u[4], const float v[4], const float g[4], uint32_t w[3]) {
+PCR_D void rgb_words(const float y[4], const float u[4], const float v[4], uint32_t w[3]) {
     float r[4], gg[4], b[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) to_rgb(y[i], u[i], v[i], g[i], &r[i], &gg[i], &b[i]);
+    for (int i = 0; i < 4; i++) to_rgb(y[i], u[i], v[i], &r[i], &gg[i], &b[i]);
     w[0] = four_u8(r[0], gg[0], b[0], r[1]); w[1] = four_u8(gg[1], b[1], r[2], gg[2]); w[2] = four_u8(b[2], r[3], gg[3], b[3]);
 }
 
@@ -1501,16 +1503,10 @@ PCR_D int pix_dc(const DevRecord& R, const PixBlock& B, int dcv, const ApplyList
         if (rlc->sc[e].Ss == 0 && dc_refinement_bit(R, rlc->sc[e], B.brow, B.bcol, B.hs, B.vs, B.covered)) dcv |= 1 << rlc->sc[e].Al;
     return dcv;
 }
-// What is added to a component's samples, and the range they are clamped to.  Chroma lies around zero.  Luma carries
-// kHalfUp, two units in the last place of a sample: the conversion to bytes rounds halves to even, and so rounds them up.
-// (Adding 1/2 and rounding down were two more instructions per byte, taking 128 from chroma two per pixel.)
-constexpr float kHalfUp = 0x1p-15f;
-struct PixLevel { float shift, lo, hi; };
-PCR_D PixLevel pix_level(bool luma) { return PixLevel{luma ? 128.f + kHalfUp : 0.f, luma ? 0.f : -128.f, luma ? 255.f : 127.f}; }
 // Refinement replay, de-quantisation and the 8x8 inverse transform of the lane's block; the clamped samples are left in
 // F[8 y + x].  qc: the component's folded quantiser steps (zig-zag order); rlc: its refinement scan list.
 template <bool kRefine>
-PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, const PixLevel& L, float F[64]) {
+PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, float F[64]) {
     int ci[64];
 #pragma unroll
     for (int ch = 0; ch < 8; ch++) {
@@ -1551,8 +1547,8 @@ PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8],
         F[zigzag_lookup(4 * k4 + 2)] = (float)ci[4 * k4 + 2] * qq.z; F[zigzag_lookup(4 * k4 + 3)] = (float)ci[4 * k4 + 3] * qq.w;
     }
     // the level shift: the DC term reaches every sample with weight one (its folded factor is exactly 1/8 and the
-    // transforms only add it), so it is added to that once instead of to the 64 samples
-    F[0] += L.shift;
+    // transforms only add it), so 128 is added to that once instead of to the 64 samples
+    F[0] += 128.f;
 #pragma unroll
     for (int r = 0; r < 8; r++)
         idct8_scaled(F[8 * r], F[8 * r + 1], F[8 * r + 2], F[8 * r + 3], F[8 * r + 4], F[8 * r + 5], F[8 * r + 6], F[8 * r + 7]);
@@ -1560,7 +1556,7 @@ PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8],
     for (int x = 0; x < 8; x++)
         idct8_scaled(F[x], F[8 + x], F[16 + x], F[24 + x], F[32 + x], F[40 + x], F[48 + x], F[56 + x]);
 #pragma unroll
-    for (int e = 0; e < 64; e++) F[e] = __builtin_amdgcn_fmed3f(F[e], L.lo, L.hi);
+    for (int e = 0; e < 64; e++) F[e] = clamp255(F[e]);
 }
 // rows y0 .. y0 + kRows - 1 of the block's samples to dst[(y - y0) * row_len + x]
 template <int y0, int kRows>
@@ -1575,7 +1571,7 @@ PCR_D void pix_put_rows(const float F[64], float* dst, uint32_t row_len) {
 template <bool kRefine>
 PCR_D void pix_finish(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, float* dst, uint32_t row_len) {
     float F[64];
-    pix_samples<kRefine>(R, B, v, qc, rlc, pix_level(B.c == 0), F);
+    pix_samples<kRefine>(R, B, v, qc, rlc, F);
     pix_put_rows<0, 8>(F, dst, row_len);
 }
 // Half kHalf (0: upper, 1: lower) of the pixel rows of an MCU: the part of the lane's block that lies in it, to the
@@ -1702,9 +1698,8 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
     const bool flatb = mine && B.zm <= 1;                   // flat: one sample stands for the block
     if (mine) {
         const ApplyList* rlc = &rl[kRefine ? B.c : 0];
-        const PixLevel L = pix_level(kPlanes || B.c == 0);   // (planes of bytes: every component as it is)
-        if (flatb) S[0] = __builtin_amdgcn_fmed3f((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + L.shift, L.lo, L.hi);
-        else pix_samples<kRefine>(R, B, v, qz[B.c], rlc, L, S);
+        if (flatb) S[0] = clamp255((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + 128.f);
+        else pix_samples<kRefine>(R, B, v, qz[B.c], rlc, S);
     }
     if (kPlanes) {
         // Instead of pixels: the lane's block, rounded, into the component's own plane of bytes (`out`: one byte per
@@ -1804,24 +1799,24 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
                 } else if (halves) {                        // two chroma samples for the eight pixels
                     float cb[4], cr[4];
                     fetch(1, mm, lyh, x0, 1, 1, cb); fetch(2, mm, lyh, x0, 1, 1, cr);
-                    const float g0 = chroma_green(cb[0], cr[0]), g1 = chroma_green(cb[2], cr[2]);
-                    const float u[4] = {cb[0], cb[0], cb[2], cb[2]}, v[4] = {cr[0], cr[0], cr[2], cr[2]}, gc[4] = {g0, g0, g1, g1};
+                    const float u0 = cb[0] - 128.f, u1 = cb[2] - 128.f, v0 = cr[0] - 128.f, v1 = cr[2] - 128.f;
+                    const float u[4] = {u0, u0, u1, u1}, v[4] = {v0, v0, v1, v1};
 #pragma unroll
                     for (uint32_t row = 0; row < 2; row++) {
                         if (row && !both) continue;
                         float ys[4]; uint32_t w[3];
                         fetch(0, mm, lyh + row, x0, 0, 0, ys);
-                        rgb_words(ys, u, v, gc, w);
+                        rgb_words(ys, u, v, w);
                         store(row, w);
                     }
                 } else {
 #pragma unroll 1
                     for (uint32_t row = 0; row < (both ? 2u : 1u); row++) {
-                        float ys[4], cb[4], cr[4], gc[4]; uint32_t w[3];
+                        float ys[4], cb[4], cr[4]; uint32_t w[3];
                         fetch(0, mm, lyh + row, x0, shx0, shy0, ys); fetch(1, mm, lyh + row, x0, shx1, shy1, cb); fetch(2, mm, lyh + row, x0, shx2, shy2, cr);
 #pragma unroll
-                        for (int i = 0; i < 4; i++) gc[i] = chroma_green(cb[i], cr[i]);
-                        rgb_words(ys, cb, cr, gc, w);
+                        for (int i = 0; i < 4; i++) { cb[i] -= 128.f; cr[i] -= 128.f; }
+                        rgb_words(ys, cb, cr, w);
                         store(row, w);
                     }
                 }
@@ -1862,7 +1857,7 @@ PCR_D void flat_cell_words(const DevRecord& R, const ImgDesc& D, const int16_t* 
     uint32_t plane0 = 0;
 #pragma unroll
     for (uint32_t c = 0; c < kMaxComp; c++) {
-        s[c] = 0.f;
+        s[c] = 128.f;
         if (c < D.nc) {
             const uint32_t bcol = (cx * D.hs[c]) >> (D.hmax - 1), brow = (cy * D.vs[c]) >> (D.vmax - 1);      // (sampling factors are 1 or 2)
             // (picked with compares: an index computed at run time would put the whole descriptor into scratch memory)
@@ -1871,16 +1866,15 @@ PCR_D void flat_cell_words(const DevRecord& R, const ImgDesc& D, const int16_t* 
             const uint32_t qprec = tq == 0 ? D.qprec[0] : (tq == 1 ? D.qprec[1] : (tq == 2 ? D.qprec[2] : D.qprec[3]));
             const uint8_t* q = R.rec + qoff;
             const float q0 = (qprec ? (float)ld_be16(q) : (float)q[0]) * 0.125f;
-            const PixLevel L = pix_level(c == 0);
-            s[c] = __builtin_amdgcn_fmed3f((float)dcp[plane0 + brow * D.bw[c] + bcol] * q0 + L.shift, L.lo, L.hi);
+            s[c] = clamp255((float)dcp[plane0 + brow * D.bw[c] + bcol] * q0 + 128.f);
             plane0 += (uint32_t)D.bw[c] * D.bh[c];
         }
     }
-    if (D.nc == 1) { uint32_t g = __builtin_amdgcn_cvt_pk_u8_f32(s[0], 0, 0); g |= g << 8; g |= g << 16; *w0 = g; *w1 = g; *w2 = g; }
+    if (D.nc == 1) { uint32_t g = put_u8(s[0], 0, 0); g |= g << 8; g |= g << 16; *w0 = g; *w1 = g; *w2 = g; }
     else {
         float rf, gf, bf;
-        to_rgb(s[0], s[1], s[2], chroma_green(s[1], s[2]), &rf, &gf, &bf);
-        const uint32_t r = __builtin_amdgcn_cvt_pk_u8_f32(rf, 0, 0), gq = __builtin_amdgcn_cvt_pk_u8_f32(gf, 0, 0), bq = __builtin_amdgcn_cvt_pk_u8_f32(bf, 0, 0);
+        to_rgb(s[0], s[1] - 128.f, s[2] - 128.f, &rf, &gf, &bf);
+        const uint32_t r = put_u8(rf, 0, 0), gq = put_u8(gf, 0, 0), bq = put_u8(bf, 0, 0);
         *w0 = r | (gq << 8) | (bq << 16) | (r << 24); *w1 = gq | (bq << 8) | (r << 16) | (gq << 24); *w2 = bq | (r << 8) | (gq << 16) | (bq << 24);
     }
     if (dead) { *w0 = 0; *w1 = 0; *w2 = 0; }
@@ -2354,12 +2348,12 @@ struct TailView {
 PCR_D void tail_pixel(const TailView& V, uint32_t x, uint32_t y, float px[3]) {
     if (V.dead) { px[0] = px[1] = px[2] = 0.f; return; }
     const float s0 = V.plane[0][((y >> V.shy[0]) & V.fm[0]) * V.len[0] + ((x >> V.shx[0]) & V.fm[0])];
-    auto level = [](float v) { return __builtin_amdgcn_fmed3f(__builtin_rintf(v), 0.f, 255.f); };
+    auto level = [](float v) { return __builtin_amdgcn_fmed3f(__builtin_floorf(v + 0.5f), 0.f, 255.f); };
     if (V.nc == 1) { px[0] = level(s0); px[1] = px[2] = 0.f; return; }
-    const float u = V.plane[1][((y >> V.shy[1]) & V.fm[1]) * V.len[1] + ((x >> V.shx[1]) & V.fm[1])];
-    const float w = V.plane[2][((y >> V.shy[2]) & V.fm[2]) * V.len[2] + ((x >> V.shx[2]) & V.fm[2])];
+    const float u = V.plane[1][((y >> V.shy[1]) & V.fm[1]) * V.len[1] + ((x >> V.shx[1]) & V.fm[1])] - 128.f;
+    const float w = V.plane[2][((y >> V.shy[2]) & V.fm[2]) * V.len[2] + ((x >> V.shx[2]) & V.fm[2])] - 128.f;
     float r, g, b;
-    to_rgb(s0, u, w, chroma_green(u, w), &r, &g, &b);
+    to_rgb(s0, u, w, &r, &g, &b);
     px[0] = level(r); px[1] = level(g); px[2] = level(b);
 }
 
@@ -2425,8 +2419,7 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
             const ApplyList* rlc = &rl[kRefine ? B.c : 0];
             const uint32_t row_len = seg_m * B.hs * 8;
             float* dst = tile + seg_m * pick3(B.c, G.rb[0], G.rb[1], G.rb[2]) + by * 8 * row_len + (ml * B.hs + bx) * 8;
-            const PixLevel L = pix_level(B.c == 0);
-            if (B.zm <= 1) dst[0] = __builtin_amdgcn_fmed3f((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + L.shift, L.lo, L.hi);
+            if (B.zm <= 1) dst[0] = clamp255((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + 128.f);
             else pix_finish<kRefine>(R, B, v, qz[B.c], rlc, dst, row_len);
         }
         __syncthreads();
