@@ -16,6 +16,7 @@
 #include <hip/hip_fp16.h>
 #include "pcr_common.h"
 #include "pcr_format.h"
+#include "pcr_chains.h"
 #include "pcr_entropy.h"
 #include "pcr_lanes.h"
 #include "pcr_pixel.h"
@@ -739,7 +740,6 @@ PCR_D uint32_t lane_table_slot(const DevRecord& R, const LaneJob& job, uint32_t 
 // on one compute unit and share its vector cache: no more than the order of the operations is needed to see them).  A
 // wavefront waits only for wavefronts before it in the chain, and every wavefront ends by releasing all of its blocks,
 // whatever became of its unit: every wait ends.
-constexpr uint32_t kChainWaves = 8;
 struct UnitChain { uint32_t first, count; uint64_t waits; };     // units [first, first + count), a wavefront each; byte w of waits: the earlier wavefronts that wavefront w follows
 
 struct ChainGate {

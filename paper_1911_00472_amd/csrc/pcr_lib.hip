@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/pcr.h"
+#include "pcr_chains.h"
 #include "pcr_kernels.h"
 #include "pcr_sequential.h"
 #include "pcr_hist.h"
@@ -222,24 +223,12 @@ struct pcr_record {
 
 namespace {
 
-// level[g] = 1 + max level of an earlier scan that shares a component and overlaps in band
 void compute_levels(pcr_record* r) {
     const uint32_t n = r->hdr.n, G = r->hdr.G;
     r->level.assign((size_t)n * G, 0);
     r->max_level = 0;
-    for (uint32_t i = 0; i < n; i++) {
-        const ScanDesc* s = &r->scan[(size_t)i * G];
-        for (uint32_t g = 0; g < r->img[i].nscans; g++) {
-            uint32_t lv = 1;
-            for (uint32_t q = 0; q < g; q++) {
-                bool share = false;
-                for (int a = 0; a < s[g].ns; a++) for (int b = 0; b < s[q].ns; b++) if (s[g].comp[a] == s[q].comp[b]) share = true;
-                if (share && s[q].Ss <= s[g].Se && s[g].Ss <= s[q].Se) lv = std::max<uint32_t>(lv, r->level[(size_t)i * G + q] + 1u);
-            }
-            r->level[(size_t)i * G + g] = (uint8_t)lv;
-            r->max_level = std::max(r->max_level, lv);
-        }
-    }
+    for (uint32_t i = 0; i < n; i++)
+        r->max_level = std::max(r->max_level, scan_levels(&r->scan[(size_t)i * G], r->img[i].nscans, &r->level[(size_t)i * G]));
 }
 
 // The work lists of the per-block kernels of refinement scans.
@@ -260,83 +249,31 @@ void refine_tiles(const pcr_record* r, const std::vector<RefineScan>& rl, LevelL
     if (ll->n_cov_tiles) up->add(&ll->d_cov_tiles, cov_tiles);
 }
 
-// Scans whose units can be decoded by the wavefronts of one workgroup in step (k_decode_waves): AC scans of one component
-// in file order.  Interval j of each of them has to cover the same blocks, so restart intervals must agree; entry points,
-// which every scan has at places of its own, rule it out where one of the scans builds on another.
-struct ChainSet {
-    struct Chain { uint32_t img, cost, units, count, scan[kChainWaves]; uint64_t waits; };      // units: intervals; count: scans
-    std::vector<Chain> ac, dc;
-    bool ordered = false;                                     // some scan builds on another one of the call
-    bool possible = true;
-};
-void chain_scans(const pcr_record* r, uint32_t i, const std::vector<uint32_t>& scans, ChainSet* C) {
-    const uint32_t G = r->hdr.G;
-    auto at = [&](uint32_t g) -> const ScanDesc& { return r->scan[(size_t)i * G + g]; };
-    auto units = [&](uint32_t g) { return r->slot_cnt[(size_t)i * G + g]; };
-    auto cost = [&](uint32_t g) { return at(g).data_len / std::max(1u, units(g)) * (at(g).Ah ? 2u : 1u); };   // (a byte of a refinement scan takes a wavefront about twice as long)
-    std::vector<uint32_t> waits(scans.size(), 0);
-    bool ordered = false, same = scans.size() <= kChainWaves;
-    for (size_t a = 0; a < scans.size(); a++) {
-        const ScanDesc& A = at(scans[a]);
-        if (a > 0) same = same && A.ri == at(scans[0]).ri && units(scans[a]) == units(scans[0]) && r->ent_off_h[(size_t)i * G + scans[a]] == 0 && r->ent_off_h[(size_t)i * G + scans[0]] == 0;
-        for (size_t b = 0; b < a; b++) {
-            const ScanDesc& B = at(scans[b]);
-            if (B.Ss <= A.Se && A.Ss <= B.Se) { ordered = true; if (b < 32) waits[a] |= 1u << b; }
-        }
-    }
-    if (!ordered) {
-        for (uint32_t g : scans) { ChainSet::Chain c{i, cost(g), units(g), 1, {g}, 0}; C->ac.push_back(c); }
-        return;
-    }
-    C->ordered = true;
-    if (!same) { C->possible = false; return; }
-    ChainSet::Chain c{i, 0, units(scans[0]), (uint32_t)scans.size(), {}, 0};
-    for (size_t a = 0; a < scans.size(); a++) {
-        c.scan[a] = scans[a]; c.cost = std::max(c.cost, cost(scans[a]));
-        c.waits |= (uint64_t)waits[a] << (8 * a);
-    }
-    C->ac.push_back(c);
-}
-
 // The chains of a plan (once, when a call first wants them).
 int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
     if (plan->chains_built) return PCR_OK;
     const uint32_t n = r->hdr.n, G = r->hdr.G;
     ChainSet chains;
-    std::vector<uint32_t> comp_scans[kMaxComp];
     std::vector<RefineScan> refined;
-    auto alone = [&](uint32_t i, uint32_t g) {
-        const size_t ig = (size_t)i * G + g;
-        return ChainSet::Chain{i, r->scan[ig].data_len / std::max(1u, r->slot_cnt[ig]), r->slot_cnt[ig], 1, {g}, 0};
-    };
-    for (uint32_t i = 0; i < n; i++) {
-        for (auto& v : comp_scans) v.clear();
-        for (uint32_t g = (uint32_t)k0; g < std::min<uint32_t>(r->img[i].nscans, (uint32_t)k); g++) {
-            const ScanDesc& sd = r->scan[(size_t)i * G + g];
-            if (is_sequential_scan(sd)) chains.possible = false;
-            else if (sd.Ss > 0) { comp_scans[sd.comp[0]].push_back(g); if (sd.Ah > 0) refined.push_back(RefineScan{i, g}); }
-            else if (sd.Ah == 0) chains.dc.push_back(alone(i, g));
-        }
-        for (const auto& v : comp_scans) if (!v.empty()) chain_scans(r, i, v, &chains);
+    for (uint32_t i = 0; i < n && chains.possible; i++) {
+        const uint32_t upto = std::min<uint32_t>(r->img[i].nscans, (uint32_t)k);
+        const size_t at = (size_t)i * G;
+        chains.add(i, &r->scan[at], &r->slot_cnt[at], &r->ent_off_h[at], (uint32_t)k0, upto);
+        for (uint32_t g = (uint32_t)k0; g < upto; g++) if (r->scan[at + g].Ss > 0 && r->scan[at + g].Ah > 0) refined.push_back(RefineScan{i, g});
     }
-    // A launch for all scans where they can keep in step; otherwise the first scans alone share one, those of level 1,
-    // which wait for nothing (the refinement scans follow level by level).
     const bool in_step = chains.possible;
-    if (!in_step) {
-        chains.ac.clear(); chains.dc.clear(); refined.clear();
-        for (uint32_t i = 0; i < n; i++)
-            for (uint32_t g = (uint32_t)k0; g < std::min<uint32_t>(r->img[i].nscans, (uint32_t)k); g++) {
-                const size_t ig = (size_t)i * G + g;
-                const ScanDesc& sd = r->scan[ig];
-                if (is_sequential_scan(sd) || sd.Ah > 0 || r->level[ig] != 1) continue;
-                (sd.Ss > 0 ? chains.ac : chains.dc).push_back(alone(i, g));
-            }
+    if (!in_step) {                                          // the refinement scans follow level by level
+        chains = ChainSet(); refined.clear();
+        for (uint32_t i = 0; i < n; i++) {
+            const size_t at = (size_t)i * G;
+            chains.add_level_one(i, &r->scan[at], &r->level[at], &r->slot_cnt[at], (uint32_t)k0, std::min<uint32_t>(r->img[i].nscans, (uint32_t)k));
+        }
     }
     for (LevelList& l : plan->levels) l.chained = l.kind != kSequential && (in_step || (l.kind != kAcRefine && l.level == 0));
     std::vector<Unit> units; std::vector<UnitChain> list;
     for (auto* set : {&chains.ac, &chains.dc}) {
-        std::stable_sort(set->begin(), set->end(), [](const ChainSet::Chain& a, const ChainSet::Chain& b) { return a.cost > b.cost; });     // the longest first
-        for (const ChainSet::Chain& c : *set) {
+        std::stable_sort(set->begin(), set->end(), [](const ScanChain& a, const ScanChain& b) { return a.cost > b.cost; });     // the longest first
+        for (const ScanChain& c : *set) {
             plan->chain_waves = std::max(plan->chain_waves, c.count);
             for (uint32_t j = 0; j < c.units; j++) {
                 list.push_back(UnitChain{(uint32_t)units.size(), c.count, c.waits});

@@ -1,0 +1,42 @@
+// CPU build of the planning of launches that decode several scans side by side (pcr_chains.h).  Test-only.
+#include <cstring>
+#include <vector>
+#include "../../paper_1911_00472_amd/csrc/pcr_chains.h"
+
+using namespace pcr;
+
+// Scans k0 .. k - 1 of an image, `count` scans in all; row g of scans: components (a bit each), Ss, Se, Ah, Al, restart
+// interval, units, entry points.  Row g of out: the launch that decodes the scan (0: the chains, 1 + level: a launch of
+// its level after them, -1: none), its chain (AC: from 0 on, DC: from 1000 on), its place in the chain, the places of the
+// scans of the chain that it waits for (a bit each).  Returns whether all scans of the call keep in step.
+extern "C" int chain_plan(const int* scans, int count, int k0, int k, int* out) {
+    std::vector<ScanDesc> s((size_t)count);
+    std::vector<uint32_t> units((size_t)count), entries((size_t)count);
+    for (int g = 0; g < count; g++) {
+        const int* p = scans + 8 * g;
+        memset(&s[g], 0, sizeof(ScanDesc));
+        for (int c = 0; c < kMaxComp; c++) if (p[0] >> c & 1) s[g].comp[s[g].ns++] = (uint8_t)c;
+        s[g].Ss = (uint8_t)p[1]; s[g].Se = (uint8_t)p[2]; s[g].Ah = (uint8_t)p[3]; s[g].Al = (uint8_t)p[4]; s[g].ri = (uint16_t)p[5];
+        s[g].data_len = 1000u + 10u * (uint32_t)g;
+        units[g] = (uint32_t)p[6]; entries[g] = (uint32_t)p[7];
+    }
+    std::vector<uint8_t> level((size_t)count);
+    scan_levels(s.data(), (uint32_t)count, level.data());
+    ChainSet set;
+    set.add(0, s.data(), units.data(), entries.data(), (uint32_t)k0, (uint32_t)k);
+    const int in_step = set.possible;
+    if (!in_step) { set = ChainSet(); set.add_level_one(0, s.data(), level.data(), units.data(), (uint32_t)k0, (uint32_t)k); }
+    for (int g = 0; g < count; g++) {
+        const bool serial = g >= k0 && g < k && !(s[g].Ss == 0 && s[g].Ah > 0);       // (DC refinement scans are read in place)
+        out[4 * g] = serial ? 1 + level[g] : -1; out[4 * g + 1] = out[4 * g + 2] = -1; out[4 * g + 3] = 0;
+    }
+    for (int kind = 0; kind < 2; kind++) {
+        const auto& list = kind ? set.dc : set.ac;
+        for (size_t c = 0; c < list.size(); c++)
+            for (uint32_t a = 0; a < list[c].count; a++) {
+                int* o = out + 4 * list[c].scan[a];
+                o[0] = 0; o[1] = (int)c + 1000 * kind; o[2] = (int)a; o[3] = (int)(list[c].waits >> (8 * a) & 255u);
+            }
+    }
+    return in_step;
+}
