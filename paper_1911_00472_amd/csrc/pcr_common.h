@@ -139,4 +139,18 @@ typedef const uint32_t* StreamPtr;
 #endif
 PCR_HD StreamPtr stream_ptr(const uint32_t* p) { return (StreamPtr)p; }
 
+// Workgroups that clear memory among others of the same launch.  They come in rows of kDies consecutive ones, every
+// `period`-th row, so that each of the chip's dies (which take workgroups in turn by their index) gets the same number of
+// them and they run beside the others from the launch's start to its end.
+constexpr uint32_t kDies = 8;
+struct FillTurn { bool fills; uint32_t index; };               // index: among the workgroups that fill, or among the others
+PCR_HD uint32_t fill_rows(uint32_t groups) { return (groups + kDies - 1) / kDies; }
+PCR_HD uint32_t fill_period(uint32_t others, uint32_t rows) { return rows ? (others / kDies + rows) / rows : 1u; }
+// Workgroup b of others + rows * kDies.
+PCR_HD FillTurn fill_turn(uint32_t b, uint32_t rows, uint32_t period) {
+    const uint32_t past = (b / kDies + 1) / period;            // filling rows up to b's, itself included
+    const bool fills = past <= rows && past * period == b / kDies + 1 && rows > 0;
+    return FillTurn{fills, fills ? (past - 1) * kDies + b % kDies : b - kDies * (past < rows ? past : rows)};
+}
+
 }  // namespace pcr

@@ -38,7 +38,7 @@ PCR_D void short_kernel_priority() { __builtin_amdgcn_s_setprio(3); }
 // take item xcd_major(blockIdx.x, gridDim.x) instead of item blockIdx.x: every die then works through one contiguous
 // eighth of the list, so the cache lines two neighbours share are completed in one L2 instead of being written back
 // in parts from two.
-constexpr uint32_t kXcds = 8;
+constexpr uint32_t kXcds = kDies;
 PCR_D uint32_t xcd_major(uint32_t b, uint32_t n) {
     const uint32_t q = n / kXcds, r = n - q * kXcds, x = b % kXcds, i = b / kXcds;
     return x * q + (x < r ? x : r) + i;
@@ -363,7 +363,7 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
 // --------------------------------------------------------------------------------------
 constexpr uint32_t kUnstuffWaves = 4, kUnstuffStep = 1024;
 constexpr int kMaxFills = 3;
-struct FillList { uint4* p[kMaxFills]; size_t n16[kMaxFills]; uint32_t groups; };      // 16-byte pieces; workgroups that share the work
+struct FillList { uint4* p[kMaxFills]; size_t n16[kMaxFills]; uint32_t rows; };        // 16-byte pieces; rows of workgroups that share the work
 
 // 0x80 in every byte of the result whose byte in x is zero (exact, no carries between bytes)
 PCR_D uint64_t zero_bytes(uint64_t x) {
@@ -531,22 +531,24 @@ PCR_D void unstuff_scan(const DevRecord& R, uint32_t i, uint32_t g, uint8_t* buf
     }
 }
 
-// Workgroups [0, P.first[P.count] + F.groups): every period-th one (until F.groups of them) fills, the others unstuff.
+// Workgroups [0, P.first[P.count] + kDies * F.rows): fill_turn says which of them fill, the others unstuff.  (Every second
+// or fourth single workgroup, as before, put the whole fill on four or two of the eight dies: 202 and 214 us for 1024
+// photographs at scan groups 9 and 10, of which the 0.5 GB fill is the larger part, against 118 and 131.)
 __global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period) {
     __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffWaves * (kUnstuffStep + 32)];
     __shared__ uint32_t tot[kUnstuffWaves];
     short_kernel_priority();
-    const uint32_t b = blockIdx.x, tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
-    const uint32_t fills = F.groups == 0 ? 0u : ((b + 1) / period < F.groups ? (b + 1) / period : F.groups);   // filling workgroups up to this one, itself included
-    if (F.groups && (b + 1) % period == 0 && (b + 1) / period <= F.groups) {
+    const uint32_t tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
+    const FillTurn turn = fill_turn(blockIdx.x, F.rows, period);
+    if (turn.fills) {
         for (int f = 0; f < kMaxFills; f++) {
             uint4* p = F.p[f];
-            const size_t n16 = F.n16[f], stride = (size_t)F.groups * 256;
-            for (size_t e = (size_t)(fills - 1) * 256 + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
+            const size_t n16 = F.n16[f], stride = (size_t)F.rows * kDies * 256;
+            for (size_t e = (size_t)turn.index * 256 + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
         }
         return;
     }
-    const uint32_t u = b - fills;
+    const uint32_t u = turn.index;
     uint32_t e = 0;
     while (e + 1 < P.count && u >= P.first[e + 1]) e++;
     if (e >= P.count) return;

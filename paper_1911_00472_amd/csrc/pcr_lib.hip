@@ -504,9 +504,9 @@ void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bo
     hipLaunchKernelGGL(k_headers, dim3(n), dim3(kHeaderLanes), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
 }
 
-// Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, the filling
-// workgroups spread evenly between the others so that they run beside them all the way (as many as unstuff at most, or they
-// would go ahead of them; 1024 where that is more: there is room for all at once).
+// Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, rows of filling
+// workgroups spread evenly between the others (fill_turn) so that they run beside them all the way (as many as unstuff at
+// most, or they would go ahead of them; 1024 where that is more: there is room for all at once).
 void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, hipStream_t s) {
     const uint32_t n = r->hdr.n, count = k - k0;
     UnstuffPlan P{};
@@ -529,10 +529,10 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, hipSt
     P.first[count] = groups;
     size_t pieces = 0;
     for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
-    fill.groups = (uint32_t)std::min<size_t>((pieces + 2047) / 2048, std::min<size_t>(2048, std::max<size_t>(groups, 1024)));     // (eight pieces per lane at least)
-    const uint32_t total = groups + fill.groups;
+    fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 2047) / 2048, std::min<size_t>(2048, std::max<size_t>(groups, 1024))));   // (eight pieces per lane, but for the last row)
+    const uint32_t total = groups + kDies * fill.rows;
     if (total == 0) return;
-    hipLaunchKernelGGL(k_unstuff, dim3(total), dim3(64 * kUnstuffWaves), 0, s, r->d, P, fill, fill.groups ? total / fill.groups : 1u);
+    hipLaunchKernelGGL(k_unstuff, dim3(total), dim3(64 * kUnstuffWaves), 0, s, r->d, P, fill, fill_period(groups, fill.rows));
 }
 
 // Steps 1-5 of the path (index .. entropy decode + refinement) for scans 1..k.
