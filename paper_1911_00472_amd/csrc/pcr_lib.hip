@@ -93,13 +93,16 @@ template <class T> int arena_alloc(Arena* a, T** p, size_t count) {
     *p = reinterpret_cast<T*>(q);
     return PCR_OK;
 }
-// Host memory in which tables are put together before they go to the device (pinned where the owner re-uses it).
+// Host memory in which tables are put together before they go to the device.  Pinned where its owner binds record after
+// record (a loader's slots), and kept there; elsewhere pageable, and given back once the tables are on the device.
 struct HostBlock {
     uint8_t* p = nullptr; size_t cap = 0; bool pinned = false;
     void release() { if (p) { if (pinned) (void)hipHostFree(p); else free(p); } p = nullptr; cap = 0; }
-    int reserve(size_t bytes, size_t keep) {
+    void done() { if (!pinned) release(); }
+    // Room for `bytes`, of which the first `keep` are in use; `exact`: and no more is to be expected.
+    int reserve(size_t bytes, size_t keep, bool exact = false) {
         if (bytes <= cap) return PCR_OK;
-        const size_t want = std::max<size_t>(bytes + bytes / 2, 1u << 16);
+        const size_t want = exact && !pinned ? bytes : std::max<size_t>(bytes + bytes / 2, 1u << 16);
         uint8_t* q = nullptr;
         if (pinned) { if (hipHostMalloc((void**)&q, want, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); return PCR_E_NOMEM; } }
         else if (!(q = (uint8_t*)malloc(want))) return PCR_E_NOMEM;
@@ -129,6 +132,9 @@ class Uploads {
     }
 public:
     Uploads(Arena* a, HostBlock* h) : a_(a), h_(h) {}
+    // About so many bytes are to come: the block grows once instead of with every table that does not fit (each time
+    // copying what it holds into pages that have to be mapped first).
+    void expect(size_t bytes) { if (!rc_) rc_ = h_->reserve(used_ + bytes, used_, true); }
     // Room for `count` entries, to be filled in before anything else is added (null: out of memory, as the flush will say).
     // *p is set by the flush.
     template <class T> T* make(T** p, size_t count) {
@@ -147,11 +153,12 @@ public:
     }
     int flush() {
         uint8_t* base = nullptr;
-        if (items_.empty() && !rc_) return PCR_OK;
+        if (items_.empty() && !rc_) { h_->done(); return PCR_OK; }
         const size_t bytes = used_;
-        const int rc = place(&base); used_ = 0;
-        if (rc) return rc;
-        return hipMemcpy(base, h_->p, bytes, hipMemcpyHostToDevice) == hipSuccess ? PCR_OK : PCR_E_DEVICE;
+        int rc = place(&base); used_ = 0;
+        if (!rc && hipMemcpy(base, h_->p, bytes, hipMemcpyHostToDevice) != hipSuccess) rc = PCR_E_DEVICE;
+        h_->done();
+        return rc;
     }
     int flush_on(hipStream_t s) {
         uint8_t* base = nullptr;
@@ -305,6 +312,8 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     std::vector<std::vector<Run>> runs((size_t)r->max_level * kNumKinds);
     std::vector<std::vector<RefineScan>> rlists(r->max_level);
     std::vector<ApplyUnit> apply; uint32_t max_blk = 0;
+    // (what the tables below take: every list is rounded up to kArenaAlign, jobs are one per window of scans at least)
+    size_t plan_bytes = runs.size() * 6 * kArenaAlign + 2 * kArenaAlign + (size_t)n * kMaxComp * (sizeof(ApplyUnit) + sizeof(int32_t));
     for (uint32_t i = 0; i < n; i++) {
         const uint32_t upto = std::min<uint32_t>(r->img[i].nscans, (uint32_t)k);
         bool refine[kMaxComp] = {false, false, false};
@@ -319,10 +328,15 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             if (g < (uint32_t)k0) continue;                    // decoded by an earlier call
             if (sd.Ss == 0 && sd.Ah > 0) continue;             // DC refinement has no serial decode
             const int kind = seq ? kSequential : (sd.Ss == 0 ? kDcFirst : (sd.Ah == 0 ? kAcFirst : kAcRefine));
-            if (kind == kAcRefine) rlists[r->level[ig] - 1].push_back(RefineScan{i, g});
             const uint32_t cnt = r->slot_cnt[ig];
+            if (kind == kAcRefine) {
+                rlists[r->level[ig] - 1].push_back(RefineScan{i, g});
+                const int c = sd.comp[0];
+                plan_bytes += sizeof(RefineScan) + 2 * sizeof(RefineTile) * (((uint32_t)r->img[i].bw[c] * r->img[i].bh[c] + 255) / 256);
+            }
             const size_t li = (size_t)(r->level[ig] - 1) * kNumKinds + kind;
             if (cnt) runs[li].push_back(Run{i, g, cnt, sd.data_len / cnt});
+            plan_bytes += cnt * sizeof(Unit) + (cnt / kEntropyLanes + 1) * sizeof(LaneJob);
         }
         if (have_dc != (1u << r->img[i].nc) - 1u) plan.dc_complete = false;
         for (int c = 0; c < r->img[i].nc; c++) if (refine[c]) {
@@ -331,6 +345,7 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         }
     }
     Uploads up(&r->big, &r->stage);
+    up.expect(plan_bytes);
     plan.levels.reserve(runs.size());                                // (the uploads keep pointers to its members)
     std::vector<uint64_t> order;
     for (size_t li = 0; li < runs.size(); li++) {
@@ -884,6 +899,7 @@ int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out)
     if (!rc) measure_units(r, bytes, nbytes);
     if (!rc && hipStreamSynchronize(nullptr) != hipSuccess) rc = PCR_E_DEVICE;
     if (rc) { (void)hipGetLastError(); pcr_close(r); return rc; }
+    r->stage.done();
     *out = r;
     return PCR_OK;
 }
@@ -900,6 +916,7 @@ static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, const 
     r->d_tail_tiles = nullptr; r->n_tail_tiles = 0; r->d_edge = nullptr; r->d_edge_off = nullptr; r->d_mcu_px_h = nullptr;
     int rc = bind_bytes(r, d_bytes, nbytes, host, s);
     if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = PCR_E_DEVICE;
+    r->stage.done();
     if (rc) { (void)hipGetLastError(); r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0; }
     return rc;
 }
