@@ -911,13 +911,18 @@ int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out)
 // handle holds no record (pcr_close is all that may follow).
 static int bind_bytes(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s);
 static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s) {
-    r->plans.clear(); r->resident_k = 0; r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0;
+    auto holds_nothing = [&]() {                             // until the bind succeeds: no images, and layouts of no images
+        r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0;
+        r->out_off.assign(1, 0); r->coef_off.assign(1, 0);
+    };
+    r->plans.clear(); r->resident_k = 0;
+    holds_nothing();
     r->d_dims = nullptr; r->d_ssim_part = nullptr; r->d_planes = nullptr;
     r->d_tail_tiles = nullptr; r->n_tail_tiles = 0; r->d_edge = nullptr; r->d_edge_off = nullptr; r->d_mcu_px_h = nullptr;
     int rc = bind_bytes(r, d_bytes, nbytes, host, s);
     if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = PCR_E_DEVICE;
     r->stage.done();
-    if (rc) { (void)hipGetLastError(); r->hdr = RecordHeader{}; r->n_tiles = 0; r->n_flat_tiles = 0; r->n_flat_rows = 0; }
+    if (rc) { (void)hipGetLastError(); holds_nothing(); }
     return rc;
 }
 static int bind_bytes(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s) {
