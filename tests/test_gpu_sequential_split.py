@@ -75,3 +75,8 @@ def test_damaged_data_flag_their_image_only():
             want, _, _ = oracle.decode_record_image(bytes(bad), 2, 1)
             assert np.array_equal(coef[int(clay[2]):int(clay[3])], want), name
     assert flagged >= 2
+
+
+@pytest.mark.parametrize("quality,noise,sub,side", [(97, 16.0, 2, 240), (100, 40.0, 1, 240), (100, 8.0, 2, 120), (100, 40.0, 2, 800), (97, 16.0, 1, 120)])
+def test_high_qualities_at_which_the_rounds_are_given_up_early_or_go_on_to_the_end(quality, noise, sub, side):
+    _check([pcrgen.encode_pixels(pcrgen.synth(3 + i, 2, side, side, 3, noise), sub, sub, quality, "sequential") for i in range(2)])
