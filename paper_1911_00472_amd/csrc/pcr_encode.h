@@ -11,7 +11,6 @@
 #include <atomic>
 #include <cstring>
 #include <exception>
-#include <functional>
 #include <new>
 #include <thread>
 #include <vector>
@@ -27,15 +26,18 @@ namespace pcr {
 namespace enc {
 
 // work() on `count` threads, this one among them; on as many as the system gives where it gives fewer.  work takes what
-// there is to do piece by piece and does not throw.
-template <class F> void on_threads(uint32_t count, const F& work) {
+// there is to do piece by piece.  Returns whether there was memory for all of it.
+template <class F> bool on_threads(uint32_t count, const F& work) {
+    std::atomic<bool> enough(true);
+    auto run = [&]() { try { work(); } catch (const std::bad_alloc&) { enough = false; } };
     std::vector<std::thread> pool;
     try {
         pool.reserve(count);
-        for (uint32_t t = 1; t < count; t++) pool.emplace_back(std::cref(work));
+        for (uint32_t t = 1; t < count; t++) pool.emplace_back(run);
     } catch (const std::exception&) {}                         // (no more threads, or no memory for their table)
-    work();
+    run();
     for (auto& t : pool) t.join();
+    return enough;
 }
 
 // ---- scan splitter --------------------------------------------------------------------------------------
@@ -308,19 +310,15 @@ inline int plan_record_indexed(const void* const* files, const size_t* sizes, ui
     Q->interval = interval;
     Q->ent.assign((size_t)n * kMaxScansPerFile, std::vector<EntryPoint>());
     std::atomic<uint32_t> next(0);
-    std::atomic<bool> no_memory(false);
     auto work = [&]() {
         for (;;) {
             const uint32_t i = next.fetch_add(1);
             if (i >= n) break;
-            try {
-                (void)find_entry_points((const uint8_t*)files[i], &Q->P.ends[(size_t)i * kMaxScansPerFile], Q->P.nscans[i], interval,
-                                        &Q->ent[(size_t)i * kMaxScansPerFile]);   // (a file the walk refuses simply has no entries)
-            } catch (const std::bad_alloc&) { no_memory = true; }
+            (void)find_entry_points((const uint8_t*)files[i], &Q->P.ends[(size_t)i * kMaxScansPerFile], Q->P.nscans[i], interval,
+                                    &Q->ent[(size_t)i * kMaxScansPerFile]);   // (a file the walk refuses simply has no entries)
         }
     };
-    on_threads(std::max(1u, std::min({16u, std::thread::hardware_concurrency(), n})), work);
-    if (no_memory) return kENoMem;
+    if (!on_threads(std::max(1u, std::min({16u, std::thread::hardware_concurrency(), n})), work)) return kENoMem;
     uint64_t entry_bytes_total = 0;
     for (const auto& e : Q->ent) entry_bytes_total += e.size() * (uint64_t)((!e.empty() && e[0].zero) ? kEntryBytesShort : kEntryBytes);
     const uint64_t raw = hdr_ecount_pos(n, Q->P.G, Q->P.G, 0);

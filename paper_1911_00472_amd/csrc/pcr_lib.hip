@@ -1570,16 +1570,14 @@ int pcr_transcode_batch(pcr_record* r, const void* const* files, const size_t* s
                 bytes.clear();
                 const int16_t* coef = reinterpret_cast<const int16_t*>(host) + (r->coef_off[i] - at);
                 const uint32_t* counts = device_counts ? reinterpret_cast<const uint32_t*>(host + hist_at) + (size_t)i * kHistPerImage : nullptr;
-                try {
-                    status[i] = enc::transcode_progressive((const uint8_t*)files[i], sizes[i], coef, (size_t)(r->coef_off[i + 1] - r->coef_off[i]), restart_interval, &bytes, counts);
-                } catch (const std::bad_alloc&) { status[i] = PCR_E_NOMEM; }
+                status[i] = enc::transcode_progressive((const uint8_t*)files[i], sizes[i], coef, (size_t)(r->coef_off[i + 1] - r->coef_off[i]), restart_interval, &bytes, counts);
                 written[i] = bytes.size();
                 if (status[i]) continue;
                 if (bytes.size() > out_off[i + 1] - out_off[i]) status[i] = PCR_E_RANGE;
                 else memcpy((uint8_t*)out + out_off[i], bytes.data(), bytes.size());
             }
         };
-        enc::on_threads(std::min((uint32_t)threads, last - first), work);
+        if (!enc::on_threads(std::min((uint32_t)threads, last - first), work)) rc = PCR_E_NOMEM;
     }
     if (rc) (void)hipStreamSynchronize(s);                    // (the buffers go)
     if (dev) (void)hipFree(dev);
