@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -39,6 +40,7 @@ struct LevelList {
     RefineTile* d_cov_tiles = nullptr; uint32_t n_cov_tiles = 0;                  // k_refine_deal, k_refine_blocks: chunks of the blocks the images cover
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
     uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units k_sequential_split has dealt with
+    uint32_t n_long = 0; uint64_t long_bytes = 0; bool subsampled = false;        // ... how many those are, their bytes, whether some have MCUs of several blocks per component
     bool chained = false;                                                        // the plan's chains hold these units too
 };
 
@@ -402,8 +404,14 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             ll.n_jobs = (uint32_t)jobs.size();
             up.add(&ll.d_jobs, jobs);
         }
-        if (ll.kind == kSequential && (uint64_t)rn[0].bytes * 8 >= kSplitLeastBits) {       // (the longest on average come first)
-            const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc;
+        if (ll.kind == kSequential) {
+            for (const Run& q : rn) {
+                if ((uint64_t)q.bytes * 8 < kSplitLeastBits) break;          // (the longest on average come first)
+                const ScanDesc& sd = r->scan[(size_t)q.img * G + q.scan];
+                ll.n_long += q.count; ll.long_bytes += (uint64_t)q.bytes * q.count;
+                for (int j = 0; j < sd.ns && sd.ns > 1; j++) ll.subsampled = ll.subsampled || r->img[q.img].hs[sd.comp[j]] > 1 || r->img[q.img].vs[sd.comp[j]] > 1;
+            }
+            if (ll.n_long) { const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc; }
         }
         if (ll.kind == kAcRefine) {
             const auto& rl = rlists[li / kNumKinds];
@@ -509,6 +517,29 @@ bool dc_lanes_pay(const pcr_record* r, const LevelList& l) {
     return g_open_records.load(std::memory_order_relaxed) > 1 && l.n >= kDcLanesMinUnits;
 }
 
+// Many lanes per long sequential scan, or one wavefront?  k_sequential_split has room for one scan per compute unit (150 KB
+// of LDS), 256 at a time, and spends up to three times the work; k_sequential takes as long as its longest scan until some
+// thousand of them fill the scalar units.  Measured (ms for n files, k_sequential / k_sequential_split):
+//                        n = 64         512           1024          2048          4096
+//   4:2:0, 110 KB    11.3 / 2.1    11.5 / 3.9    12.6 / 7.5    15.7 / 12.7   23.3 / 24.9
+//   4:2:0, 29 KB      3.0 / 1.5     3.1 / 2.8     3.5 / 4.8     4.4 / 8.6     6.4 / 16.8
+//   4:2:0, 11 KB      1.2 / 1.5     1.3 / 2.3     1.4 / 3.7     1.8 / 6.4     2.6 / 12.2
+//   4:4:4, 110 KB    11.9 / 1.2    12.1 / 2.1    13.7 / 4.0    17.1 / 7.4    24.9 / 14.0
+//   4:4:4, 13 KB      1.5 / 0.6     1.6 / 1.0     1.8 / 1.7     2.2 / 3.1     3.2 / 6.1
+//   gray, 146 KB     13.3 / 1.0    13.6 / 2.0    15.3 / 3.7    19.2 / 6.8    28.2 / 13.0
+//   gray, 17 KB       1.7 / 0.5     1.7 / 0.8     2.0 / 1.4     2.5 / 2.6     3.6 / 5.0
+// The two lines below follow these figures (in us; kb: the mean of the long scans).  A record decoded beside others shares
+// the compute units with them; the records the process has open (four at most count) are taken as the sign of it, as by
+// lanes_pay.  (Without this choice 4096 baseline photographs in four records took 29.1 ms instead of 23.2.)
+bool split_pays(const LevelList& l) {
+    if (l.n_long == 0) return false;
+    const float n = (float)l.n_long * (float)std::min(4, std::max(1, g_open_records.load(std::memory_order_relaxed)));
+    const float kb = (float)l.long_bytes / (float)l.n_long / 1000.f, turns = std::ceil(n / 256.f);
+    const float split = l.subsampled ? 550.f + turns * (850.f + 6.f * kb) : 150.f + turns * (260.f + 4.5f * kb);
+    const float sequential = 102.f * kb * std::max(1.f, 0.72f + n / 3072.f);
+    return split < sequential;
+}
+
 // Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
 // regions in the same kernel: a launch costs about as much as k_index runs, and a workgroup of k_headers sums at most
 // kOwnIndexImages lengths per scan group.
@@ -572,7 +603,8 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         if (l.kind == kDcFirst) {
             by_lanes[li] = dc_lanes_pay(r, l) ? 1 : 0;
             if (!by_lanes[li]) dc_tables = true;
-        } else if (l.kind != kSequential) {
+        } else if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
+        else {
             by_lanes[li] = lanes_pay(r, l) ? 1 : 0;
             if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
         }
@@ -629,8 +661,8 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
             mark(r, PCR_STAGE_DC_FIRST, s);
         }
         else if (l.kind == kSequential) {
-            if (l.d_done) hipLaunchKernelGGL(k_sequential_split, dim3(l.n), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
-            hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, (const uint32_t*)l.d_done, c32);
+            if (by_lanes[li]) hipLaunchKernelGGL(k_sequential_split, dim3(l.n), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
+            hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, by_lanes[li] ? (const uint32_t*)l.d_done : (const uint32_t*)nullptr, c32);
             mark(r, PCR_STAGE_SEQUENTIAL, s);
         }
         else if (l.kind == kAcFirst) {

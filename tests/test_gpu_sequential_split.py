@@ -80,3 +80,21 @@ def test_damaged_data_flag_their_image_only():
 @pytest.mark.parametrize("quality,noise,sub,side", [(97, 16.0, 2, 240), (100, 40.0, 1, 240), (100, 8.0, 2, 120), (100, 40.0, 2, 800), (97, 16.0, 1, 120)])
 def test_high_qualities_at_which_the_rounds_are_given_up_early_or_go_on_to_the_end(quality, noise, sub, side):
     _check([pcrgen.encode_pixels(pcrgen.synth(3 + i, 2, side, side, 3, noise), sub, sub, quality, "sequential") for i in range(2)])
+
+
+@pytest.mark.parametrize("others", [0, 3])
+def test_more_long_scans_than_the_split_pays_for(others):
+    """Too many files at a time for a workgroup each (alone from some 700 of this size on, sooner beside other records that
+    are open): the one-wavefront decoder takes them all, with the same coefficients."""
+    distinct = [pcrgen.encode_pixels(pcrgen.synth(60 + i, 2, 130 + i, 121, 3, 18.0), 2, 2, 92, "sequential", restart=0) for i in range(8)]
+    assert min(map(len, distinct)) * 8 > 65536
+    open_beside = [pkg.pcr_open(pcrgen.write_record(distinct), 0) for _ in range(others)]
+    for n in (8, 250, 1100):
+        rec = pcrgen.write_record([distinct[i % 8] for i in range(n)])
+        coef, lay, st, _, _ = _coefficients(rec)
+        assert (st == 0).all()
+        want = [oracle.decode_record_image(rec, i, 1)[0] for i in range(8)]
+        for i in range(n):
+            assert np.array_equal(coef[int(lay[i]):int(lay[i + 1])], want[i % 8]), (n, i)
+    for r in open_beside:
+        r.close()
