@@ -136,7 +136,10 @@ __global__ void __launch_bounds__(256) k_index(DevRecord R, uint32_t kmax) {
 //      interval a scan takes over from earlier regions are found with ballots over the lanes;
 //   4. one wavefront per scan builds the scan's tables from its definition, every lane its share of the entries.
 // One lane per image for all of this, with the tables in a kernel of their own, took 125 + 81 us for 1024 images of
-// 10 scans; see the design notes for what this takes.
+// 10 scans; this takes 47 (8 for k_index ahead of it), bound by the chain of dependent LDS reads of the walk.
+// Workgroups have a wavefront per scan group, kHeaderWaves at most: with eight of them at every scan group, of which seven
+// had nothing to do at scan group 1, the kernel stood in the way of the pixel writers of other records (four records
+// in flight, ms per step at scan groups 1 and 2: 0.745 and 2.18, now 0.675 and 2.08; alone nothing changes).
 // keep_status: a fidelity upgrade builds on planes decoded earlier; an image those calls found damaged stays so.
 // tables from scan k0 on are built (none: k0 = kmax); dc_too = 0: the DC first scans of this call are all decoded by
 // k_dc_first_lanes, which builds its own tables.
@@ -227,13 +230,13 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
     __shared__ ImgDesc s_img;
     __shared__ CanonCode s_code[kHeaderWaves];
     short_kernel_priority();
-    const uint32_t i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lanes = blockDim.x, waves = lanes >> 6;
     const uint32_t n = R.n, nsc = R.nscans[i];
     uint32_t upto = nsc < kmax ? nsc : kmax;
     if (upto > kMaxGroups) upto = kMaxGroups;               // (cannot happen: the header check refuses such records)
     // ---- where the regions lie ----
     if (own_index) {
-        for (uint32_t g = wave; g < upto; g += kHeaderWaves) {
+        for (uint32_t g = wave; g < upto; g += waves) {
             uint32_t before = 0;
             for (uint32_t j = lane; j < i; j += 64) before += R.len[(size_t)g * n + j];
 #pragma unroll
@@ -244,14 +247,14 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
             }
         }
     } else if (tid < upto) { s_off[tid] = R.off[(size_t)tid * n + i]; s_len[tid] = R.len[(size_t)tid * n + i]; }
-    for (uint32_t e = tid; e < sizeof(ScanDesc) * kMaxGroups / 4; e += kHeaderLanes) reinterpret_cast<uint32_t*>(s_scan)[e] = 0;
-    for (uint32_t e = tid; e < sizeof(ImgDesc) / 4; e += kHeaderLanes) reinterpret_cast<uint32_t*>(&s_img)[e] = 0;
+    for (uint32_t e = tid; e < sizeof(ScanDesc) / 4 * upto; e += lanes) reinterpret_cast<uint32_t*>(s_scan)[e] = 0;
+    for (uint32_t e = tid; e < sizeof(ImgDesc) / 4; e += lanes) reinterpret_cast<uint32_t*>(&s_img)[e] = 0;
     __syncthreads();
     // ---- their first bytes ----
     uint32_t window = upto ? (kHeaderStage / upto) & ~15u : 0u;
     if (window > kHeaderWindow) window = kHeaderWindow;
     const uint32_t pieces = window >> 4;                     // 16-byte pieces per region
-    for (uint32_t e = tid; e < pieces * upto; e += kHeaderLanes) {
+    for (uint32_t e = tid; e < pieces * upto; e += lanes) {
         const uint32_t g = e / pieces, o = (e - g * pieces) * 16, L = s_len[g];
         if (o >= L) continue;
         const uint8_t* src = R.rec + s_off[g] + o;
@@ -318,14 +321,14 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
     {
         uint32_t* dst = reinterpret_cast<uint32_t*>(&R.scan[(size_t)i * R.G]);
         static_assert(sizeof(ScanDesc) % 4 == 0, "ScanDesc is copied as dwords");
-        for (uint32_t e = tid; e < sizeof(ScanDesc) / 4 * upto; e += kHeaderLanes) dst[e] = reinterpret_cast<const uint32_t*>(s_scan)[e];
+        for (uint32_t e = tid; e < sizeof(ScanDesc) / 4 * upto; e += lanes) dst[e] = reinterpret_cast<const uint32_t*>(s_scan)[e];
         uint32_t* di = reinterpret_cast<uint32_t*>(&R.img[i]);
-        for (uint32_t e = tid; e < sizeof(ImgDesc) / 4; e += kHeaderLanes) di[e] = reinterpret_cast<const uint32_t*>(&s_img)[e];
+        for (uint32_t e = tid; e < sizeof(ImgDesc) / 4; e += lanes) di[e] = reinterpret_cast<const uint32_t*>(&s_img)[e];
     }
     if (s_img.status != kOk) return;
     // ---- the tables ----
     CanonCode* code = &s_code[wave];
-    for (uint32_t g = k0 + wave; g < upto; g += kHeaderWaves) {
+    for (uint32_t g = k0 + wave; g < upto; g += waves) {
         const ScanDesc& sd = s_scan[g];
         const size_t ig = (size_t)i * R.G + g;
         // (a table may have been defined ahead of this scan's own region: in memory then, unless it is region 0)
