@@ -641,12 +641,14 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     mark(r, PCR_STAGE_UNSTUFF, s);
     const uint32_t* c32 = reinterpret_cast<const uint32_t*>(r->d.clean);
     auto waves = [&](const LevelList& l) {
-        hipLaunchKernelGGL(l.kind == kDcFirst ? k_decode_waves<kWavesDc> : k_decode_waves<kWavesAc>, dim3(l.n), dim3(kEntropyLanes), kWaveTabBytes, s, r->d, l.d_units,
+        hipLaunchKernelGGL((l.kind == kDcFirst ? k_decode_waves<kWavesDc, false> : k_decode_waves<kWavesAc, false>), dim3(l.n), dim3(kEntropyLanes), kWaveTabBytes, s, r->d, l.d_units,
                            (const UnitChain*)nullptr, c32, dc_to_planes ? 1u : 0u);
     };
     if (side_by_side) {
-        const uint32_t w = plan->chain_waves;
-        hipLaunchKernelGGL(dc_beside ? k_decode_waves<kWavesDc | kWavesAc> : k_decode_waves<kWavesAc>, dim3(dc_beside ? plan->n_chains : plan->n_ac_chains), dim3(kEntropyLanes * w), w * kWaveTabBytes, s, r->d,
+        const uint32_t w = plan->chain_waves;                // (chains of several scans are those in which some follow others)
+        auto* kernel = w > 1 ? (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, true> : k_decode_waves<kWavesAc, true>)
+                             : (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, false> : k_decode_waves<kWavesAc, false>);
+        hipLaunchKernelGGL(kernel, dim3(dc_beside ? plan->n_chains : plan->n_ac_chains), dim3(kEntropyLanes * w), w * kWaveTabBytes, s, r->d,
                            plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u);
         const LevelList& f = plan->refined;
         if (f.n_cov_tiles) hipLaunchKernelGGL(k_refine_blocks, dim3(f.n_cov_tiles), dim3(256), 0, s, r->d, f.d_refine, f.d_cov_tiles);
