@@ -921,7 +921,9 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_refine_lanes(DevRecord R, 
     staged.put(job, tabs);
     if (!U.ok) return;
     U.tab = reinterpret_cast<const LaneTab*>(&tabs[slot][0]);
-    const int rc = lane_decode_ac_refine(U, R.masks + R.mask_off[key], U.plane_elems >> 6, &rings, &hring, t);
+    uint64_t* recs = R.masks + R.mask_off[key];
+    const int rc = any_lane(lane_mostly_runs(U)) ? lane_decode_ac_refine<true>(U, recs, U.plane_elems >> 6, &rings, &hring, t)
+                                                 : lane_decode_ac_refine<false>(U, recs, U.plane_elems >> 6, &rings, &hring, t);
     if (rc != kOk) R.status[un.img] = rc;
 }
 

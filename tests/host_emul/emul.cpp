@@ -172,7 +172,8 @@ extern "C" int emul_decode_record(const uint8_t* rec, size_t nbytes, int k, int6
                 U.plane = cpl[0]; U.plane_elems = (uint32_t)plane * 64;
                 U.tab = reinterpret_cast<const LaneTab*>(&at); U.ok = true;
                 if (U.mcu0 >= U.mcu1 || U.mcu_w == 0) return kEFormat;
-                rc = sd.Ah == 0 ? lane_decode_ac_first(U, &ring, 0) : lane_decode_ac_refine(U, masks[g].data(), (uint32_t)plane, &ring, &hring, 0);
+                rc = sd.Ah == 0 ? lane_decode_ac_first(U, &ring, 0) : (lane_mostly_runs(U) ? lane_decode_ac_refine<true>(U, masks[g].data(), (uint32_t)plane, &ring, &hring, 0)
+                                                             : lane_decode_ac_refine<false>(U, masks[g].data(), (uint32_t)plane, &ring, &hring, 0));
             } else {
                 AcTab at; actab_build(&at, rec + sd.ac_off); actab_pack(&at, sd.Ah == 0, 0, 1);
                 WindowReader wr; wr.init(reinterpret_cast<const uint32_t*>(clean.data()), byte_off, sub_bits, nbits, pos0, &at, sd.Ah == 0, 0, sd.Ah == 0);

@@ -161,3 +161,33 @@ def test_dc_first_scans_with_a_lane_per_unit_many_small_images_and_damage():
             if i != victim:
                 sl = slice(int(lay[i]), int(lay[i + 1]))
                 assert st[i] == 0 and np.array_equal(pix[sl], good[sl]), (victim, i)
+
+
+def test_refinement_units_that_are_mostly_end_of_band_runs():
+    """Smooth pictures with a few busy blocks: units of thousands of blocks and hardly a symbol take the refinement loop with
+    the short way through runs, alone and in wavefronts with ordinary units; blocks of a run with many corrections included."""
+    rng = np.random.default_rng(8)
+    q = np.ones((2, 64), np.uint16)
+    files = []
+    for n, (busy, w, h) in enumerate([(0.0, 400, 304), (0.002, 400, 304), (0.02, 203, 333), (0.3, 160, 160), (1.0, 88, 80)]):
+        nb = pcrgen.plane_blocks(w, h, 1, 1, 1)[0]
+        c = np.zeros((nb, 64), np.int16)
+        c[:, 0] = rng.integers(-300, 300, nb)
+        hit = rng.random(nb) < busy
+        c[hit] = np.where(rng.random((int(hit.sum()), 64)) < 0.7, rng.integers(-9, 10, (int(hit.sum()), 64)), c[hit])
+        if n in (1, 2):                                       # long history, nothing new: blocks inside runs that carry only corrections
+            dense = rng.random(nb) < 0.05
+            c[dense, 1:] = 8 * rng.choice([-1, 1], (int(dense.sum()), 63))
+        files.append(pcrgen.encode_coefs(c.reshape(-1), w, h, 1, 1, 1, q, [(1, 0, 0, 0, 0, 0, 0, 0), (1, 0, 0, 0, 1, 63, 0, 2), (1, 0, 0, 0, 1, 63, 2, 1), (1, 0, 0, 0, 1, 63, 1, 0)], 0))
+    files = files * 3
+    for rec in (pkg.record_write_indexed(files, None, 16), pkg.record_write_indexed(files, None, 1000)):
+        with pkg.pcr_open(rec, 0) as r:
+            r.set_lane_decoders(1)
+            for k in range(2, r.G + 1):
+                got = r.decode_coefficients(k).cpu().numpy()
+                lay = r.coef_layout()
+                if k > 2:
+                    assert r.last_decoder_shapes()[0] > 0
+                for i in range(len(files)):
+                    want, _, _ = oracle.decode_record_image(rec, i, k)
+                    assert np.array_equal(got[int(lay[i]):int(lay[i + 1])], want), (i, k)
