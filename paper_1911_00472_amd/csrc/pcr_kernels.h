@@ -139,7 +139,8 @@ __global__ void __launch_bounds__(256) k_index(DevRecord R, uint32_t kmax) {
 // 10 scans; this takes 47 (8 for k_index ahead of it), bound by the chain of dependent LDS reads of the walk.
 // Workgroups have a wavefront per scan group, kHeaderWaves at most: with eight of them at every scan group, of which seven
 // had nothing to do at scan group 1, the kernel stood in the way of the pixel writers of other records (four records
-// in flight, ms per step at scan groups 1 and 2: 0.745 and 2.18, now 0.675 and 2.08; alone nothing changes).
+// in flight, ms per step at scan groups 1 and 2: 0.745 and 2.18, now 0.675 and 2.08; alone nothing changes).  Records
+// small enough for own_index leave the chip empty anyway and keep the eight, which sum the lengths.
 // keep_status: a fidelity upgrade builds on planes decoded earlier; an image those calls found damaged stays so.
 // tables from scan k0 on are built (none: k0 = kmax); dc_too = 0: the DC first scans of this call are all decoded by
 // k_dc_first_lanes, which builds its own tables.

@@ -547,7 +547,7 @@ void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bo
     const uint32_t n = r->hdr.n;
     const bool own = n <= kOwnIndexImages;
     if (!own) hipLaunchKernelGGL(k_index, dim3(k), dim3(256), 0, s, r->d, k);
-    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * std::min<uint32_t>(k, kHeaderWaves)), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
+    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * (own ? kHeaderWaves : std::min<uint32_t>(k, kHeaderWaves))), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
 }
 
 // Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, rows of filling
