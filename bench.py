@@ -52,11 +52,11 @@ VALU_PEAK_TLANEOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # vector ALU: 256 CUs x 4 SIM
 # the counters were taken: an entry is removed (-> null in the output) whenever its kernel changes.
 PMC = {
     # mean of the two launches of one decode (profiles/decode_kernels_imagenet_like_k10_counters.md)
-    "ac_refine_lanes": {"salu": 36.4e6, "valu": 160.6e6, "fetch_bytes": 499.5e6, "write_bytes": 324.6e6,
+    "ac_refine_lanes": {"salu": 5.9e6, "valu": 121.9e6, "fetch_bytes": 436.7e6, "write_bytes": 247.6e6,
                         "source": "profiles/decode_kernels_imagenet_like_k10_counters.md (SQ_INSTS_SALU, SQ_INSTS_VALU, FETCH_SIZE x 2.0, WRITE_SIZE x 1.0)"},
 }
 # all kernels of that decode, same counter run
-RECORD0_INSTS = {"scalar": 228.5e6, "vector": 764.3e6, "source": "profiles/decode_kernels_imagenet_like_k10_counters.md (whole decode)"}
+RECORD0_INSTS = {"scalar": 105.8e6, "vector": 633.1e6, "source": "profiles/decode_kernels_imagenet_like_k10_counters.md (whole decode)"}
 
 # The work of one Huffman-coded symbol, at the very least.
 # One wavefront per unit (pcr_entropy.h): the serial chain -- fetch the packed word of the current bit offset, test it,
@@ -168,6 +168,7 @@ class Job:
         self.outs = [torch.empty(int(h.output_layout()[-1]), dtype=torch.uint8, device="cuda") for h in self.handles]
         self.streams = [torch.cuda.Stream() for _ in self.handles]          # default priority
         self.n_img = sum(h.n for h in self.handles)
+        self.alone_ms = {}
 
     def step(self, k):
         for h, o, st in zip(self.handles, self.outs, self.streams):
@@ -179,7 +180,9 @@ class Job:
 
     def timed(self, k, steps, warmup, single_steps=10):
         """(mean s per step over `steps` steps in one bracket, [s of single steps], stage times overlapped, stage times
-        of record 0 decoded alone, calls)."""
+        of record 0 decoded alone, calls).  alone_ms[k]: wall time of an ordinary call on record 0 by itself, which is not
+        the sum of its stage times where scans are decoded side by side: with stage timing on, every stage is launched
+        on its own."""
         torch, pkg = self.torch, self.pkg
         for _ in range(warmup):
             self.step(k)
@@ -197,6 +200,13 @@ class Job:
             self.step(k)
             torch.cuda.synchronize()
             singles.append(time.perf_counter() - t)
+        h0, ones = self.handles[0], []
+        for _ in range(5):
+            t = time.perf_counter()
+            h0.decode_batch(k, out=self.outs[0], stream=self.streams[0].cuda_stream)
+            torch.cuda.synchronize()
+            ones.append((time.perf_counter() - t) * 1e3)
+        self.alone_ms[k] = float(np.median(ones))
         # HIP events the library records on each record's own stream around every kernel.  The records of a step
         # overlap, so an interval here also holds the time a kernel spent sharing the GPU with the other records'.
         for h in self.handles:
@@ -211,7 +221,6 @@ class Job:
                 over[n][0] += ms
                 over[n][1] += launches
         # the same with record 0 decoded ALONE: every kernel has the GPU to itself (what rocprofv3 reports as well)
-        h0 = self.handles[0]
         h0.enable_stage_timing(True)
         for _ in range(3):
             h0.decode_batch(k, out=self.outs[0], stream=self.streams[0].cuda_stream)
@@ -631,7 +640,7 @@ def main():
           file=sys.stderr, flush=True)
 
     # The records the library's own writer makes of these files: the same image bytes, plus entry points about every
-    # 128 MCUs of every scan (record version 2), which the decoder uses as it uses restart intervals.  `value` is
+    # 64 MCUs (--entry-interval) of every scan (record version 2), which the decoder uses as it uses restart intervals.  `value` is
     # measured on them; the plain records (no entry points: one serial stream per scan) are timed further down.
     plain_records = records
     per_record = pcrgen.WORKLOADS[name]["per_record"]
@@ -682,6 +691,7 @@ def main():
             "hbm_roofline_frac": ab["path"] / sec / 1e9 / HBM_PEAK_GBS,
             "must_move_floor_GBps": (ab["compressed"] + ab["out"]) / sec / 1e9,
             "compressed_MB": ab["compressed"] / 1e6,
+            "ms_one_record_alone": job.alone_ms[k],
             "stage_ms_one_record_alone": {n: ms / calls for n, (ms, launches) in alone.items() if launches},
             "kernel_ms_per_launch_overlapped": {n: v for n, v in per_launch(over).items() if v},
         }
@@ -764,6 +774,8 @@ def main():
                        if (default_config and RECORD0_INSTS and lane_launches > 0 and wave_launches == 0) else None),
         "ac_decoder_shape": {"lane_per_unit_launches": lane_launches, "wavefront_per_unit_launches": wave_launches},
         "roofline": roofline,
+        "stage_times": "with stage timing on every stage is launched on its own; an ordinary call decodes the scans of records that take the "
+                       "wavefront decoders side by side (plain records, few units), so that stage times describe those launches and not its own",
         "pixel_kernel": pixel_kernel,
         "cpu_baseline": cpu,
         "per_scan_group": report,
@@ -782,7 +794,7 @@ def main():
     for k in ([] if args.only else sorted(set(TABLE_SCAN_GROUPS) & set(scan_groups))):
         psec, psingles, _, palone, pcalls = pjob.timed(k, max(3, args.steps // 2), 2, single_steps=5)
         plain[str(k)] = {"images_per_s": n_img / psec, "ms_per_step": psec * 1e3,
-                         "ms_one_record_alone": sum(ms for ms, _ in palone.values()) / pcalls}
+                         "ms_one_record_alone": pjob.alone_ms[k], "ms_one_record_alone_stage_by_stage": sum(ms for ms, _ in palone.values()) / pcalls}
     pjob.close()
     del pjob
     line["plain_records_without_entry_points"] = plain
