@@ -135,6 +135,8 @@ int pcr_coef_layout(const pcr_record* rec, uint64_t* offsets);
 
 /* Quantised coefficients after scans 1..k (partially refined coefficients are multiples of
  * 2^Al; coefficients not yet received are 0).  d_coef: device, offsets[n] int16 elements.
+ * The coefficients of an image whose entropy-coded data is corrupt are unspecified (its neighbours' are not touched):
+ * how far a decoder follows damaged data differs between the decoders a call may take.
  * Asynchronous on hip_stream. */
 int pcr_decode_coefficients(pcr_record* rec, int k, int16_t* d_coef, void* hip_stream);
 
@@ -143,6 +145,8 @@ int pcr_decode_coefficients(pcr_record* rec, int k, int16_t* d_coef, void* hip_s
  *   out_u8_nhwc   device pointer, layout as pcr_output_layout; out_capacity in bytes
  *   d_status      optional device array of n int32: 0, or a PCR_E_* code for an image whose
  *                 entropy-coded data is corrupt (its pixels are zero-filled)
+ * A first scan that covers coefficients an earlier scan of its component already holds, which T.81 rules out, is decoded
+ * in file order like any other (behind a refinement of them the result is unspecified, but always the same).
  * Runs the whole path on the device: index, marker parsing, unstuffing, progressive Huffman
  * decode of scans 1..k, refinement, de-quantisation, inverse DCT, chroma replication and
  * YCbCr->RGB.  Coefficients not yet received count as zero; no smoothing is applied.
@@ -411,7 +415,8 @@ int pcr_last_decoder_shapes(pcr_record* rec, int* lane_launches, int* wavefront_
 
 /* Stage timing with HIP events recorded on the call's own stream (off by default; switching it on
  * starts a new history).  While it is on, every stage has launches of its own; without it, scans for the wavefront
- * decoders share one launch where they can, whatever their stage.  A stage is one kernel or a short run of kernels:
+ * decoders share one launch where they can, whatever their stage: the times then reported are those of launches that an
+ * ordinary call does not make (512 photographs without entry points: 6.7 ms, stage by stage 15).  A stage is one kernel or a short run of kernels:
  *   INDEX_PARSE    k_index + k_headers               UNSTUFF        k_unstuff + zero fills
  *   DC_FIRST, AC_FIRST, AC_REFINE, REFINE_BLOCKS, SEQUENTIAL     one interval per launch of that kernel (DC_FIRST, AC_FIRST,
  *                  AC_REFINE: of either decoder shape; REFINE_BLOCKS: k_refine_blocks after a wavefront-per-unit launch, k_refine_history

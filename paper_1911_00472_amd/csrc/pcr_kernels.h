@@ -382,6 +382,10 @@ struct __attribute__((packed, aligned(1))) LooseU16 { uint16_t v; };
 
 // What a launch works through: scan groups in order of decreasing length; first[e]: the first unstuffing workgroup of entry
 // e (first[count]: their number); bit e of `wide`: one scan per workgroup, else one per wavefront.
+// kUnstuffWide, in bytes of a group's mean scan; us of the launch with the line at 1024 / 3072 / 6144 / 12288 / never: 1024
+// photographs at scan group 2 89 / 89 / 99 / 99 / 99, 5 109 / 108 / 98 / 98 / 103, 10 143 / 129 / 132 / 132 / 141; 256 pictures
+// of 600 x 450 in 4:4:4 at 5 90 / 90 / 90 / 105 / 152; 128 of 1024 x 1024 at 10 114 / 114 / 131 / 131 / 279; 1024 of 256 x 256 at
+// 5 43 / 31 / 31 / 31 / 31.
 constexpr uint32_t kUnstuffWide = 6144;
 struct UnstuffPlan { uint64_t wide; uint32_t count; uint32_t first[kMaxGroups + 1]; uint8_t group[kMaxGroups]; };
 
