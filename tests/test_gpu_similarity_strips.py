@@ -1,5 +1,5 @@
 """The strips of k_ssim_tiles at their edges: pictures one column and one row short of, at and beyond a strip (54 window
-positions across, 32, 64 or 96 down, groups of four rows), and a record large enough for the tallest strips."""
+positions across, 32, 64 or 128 down, groups of four rows), and a record large enough for the tallest strips."""
 import numpy as np
 import pytest
 
@@ -27,3 +27,17 @@ def test_strip_edges(C, copies):
         got = r.msssim_batch(r.decode_batch(2), r.decode_batch(r.G)).cpu().numpy().reshape(copies, -1)
     assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
     assert np.abs(got[0] - np.array(want)).max() <= TOL, (got[0], want)
+
+
+@pytest.mark.parametrize("w,h,C,sub,copies", [(11, 11, 3, 1, 1), (12, 11, 3, 2, 1), (22, 22, 3, 1, 1), (23, 24, 3, 2, 1), (11, 12, 1, 1, 1), (64, 137, 3, 2, 1),
+                                              (65, 138, 3, 2, 5600), (64, 139, 3, 2, 5600), (23, 149, 3, 1, 8200)])
+def test_blocks_at_both_ends_of_the_buffer(w, h, C, sub, copies):
+    """Three and six bytes are loaded with the byte or two ahead of them, except at the buffer's first block; two rows of
+    pixels are in flight; strips of 128 rows (many pictures) end one row short of, at and beyond a picture."""
+    import torch
+    rec = pcrgen.write_record([pcrgen.make_jpeg(811, 2, w, h, C, 11.0, sub, sub, 88)] * copies)
+    a, b = (oracle.decode_record_image(rec, 0, k)[1] for k in (2, oracle.record_header(rec)["G"]))
+    with pkg.Record(rec) as r:
+        got = r.msssim_batch(r.decode_batch(2), r.decode_batch(r.G)).cpu().numpy()
+    assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
+    assert abs(got[0] - oracle.msssim(a, b)) <= TOL
