@@ -1177,7 +1177,7 @@ __global__ void __launch_bounds__(256) k_refine_blocks(DevRecord R, const Refine
 // scans of the component in file order, DC refinement scans) into a compact list; k_apply then
 // runs one lane per coefficient, a workgroup covering kApplyChunk consecutive coefficients.
 struct ApplyScan { uint64_t mask_off; uint32_t slot; uint32_t data_base; uint32_t mcu_w; uint16_t ri; uint8_t Ss, Se, Ah, Al, ns, before, bpm, pad[3]; };
-struct ApplyList { uint32_t n; uint32_t pad; ApplyScan sc[kApplyMaxScans]; };
+struct ApplyList { uint32_t n, nac; ApplyScan sc[kApplyMaxScans]; };       // AC scans first (nac of them), then DC scans; both in file order
 constexpr uint32_t kApplyChunk = 4096;
 
 // DC refinement of the block at (row, col) of a component with sampling hs x vs: the block's bit sits at
@@ -1193,36 +1193,47 @@ PCR_D uint32_t dc_refinement_bit(const DevRecord& R, const ApplyScan& S, uint32_
     return (uint32_t)dc_refine_bit(words, R.ivl_start[S.slot + ivl], bit);
 }
 
-__global__ void __launch_bounds__(64) k_apply_prep(DevRecord R, const ApplyUnit* __restrict__ au, uint32_t nau, uint32_t kmax, ApplyList* lists) {
-    const uint32_t u = blockIdx.x * 64 + threadIdx.x;
+// A wavefront per (image, component), a lane per scan: the loads of all scans are under way together.  (A lane per image
+// and component walking its scans took 9.4 us for 1024 images, nearly all of it waiting for one load after another.)
+constexpr int kApplyPrepWaves = 4;
+__global__ void __launch_bounds__(64 * kApplyPrepWaves) k_apply_prep(DevRecord R, const ApplyUnit* __restrict__ au, uint32_t nau, uint32_t kmax, ApplyList* lists) {
+    const uint32_t u = blockIdx.x * kApplyPrepWaves + uni(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     if (u >= nau) return;
     const ApplyUnit a = au[u];
     const ImgDesc* img = &R.img[a.img];
-    const int c = a.comp;
+    const uint32_t c = a.comp;
     ApplyList* L = &lists[u];
-    uint32_t n = 0;
     const uint32_t upto = img->nscans < kmax ? img->nscans : kmax;
-    for (uint32_t g = 0; g < upto && n < kApplyMaxScans; g++) {
-        const size_t ig = (size_t)a.img * R.G + g;
-        const ScanDesc* sd = &R.scan[ig];
-        ApplyScan e;
-        e.Ss = sd->Ss; e.Se = sd->Se; e.Ah = sd->Ah; e.Al = sd->Al; e.ns = sd->ns; e.ri = sd->ri; e.mcu_w = sd->mcu_w;
-        e.mask_off = R.mask_off[ig]; e.slot = R.slot_base[ig]; e.data_base = clean_base(sd->data_off);
-        e.before = 0; e.bpm = 0; e.pad[0] = e.pad[1] = e.pad[2] = 0;
-        if (sd->Ss == 0) {
-            if (sd->Ah == 0) continue;
-            int j = -1; uint32_t before = 0, bpm = 0;
-            for (int q = 0; q < sd->ns; q++) {
-                const int cq = sd->comp[q];
-                if (cq == c) { j = q; before = bpm; }
-                bpm += sd->ns > 1 ? (uint32_t)img->hs[cq] * img->vs[cq] : 1;
+    uint32_t n = 0;
+    for (uint32_t dc = 0; dc < 2; dc++) {                    // (AC first scans are in the planes already)
+        for (uint32_t g0 = 0; g0 < upto; g0 += 64) {
+            const uint32_t g = g0 + lane;
+            const size_t ig = (size_t)a.img * R.G + (g < upto ? g : 0u);
+            const ScanDesc sd = R.scan[ig];
+            ApplyScan e;
+            e.Ss = sd.Ss; e.Se = sd.Se; e.Ah = sd.Ah; e.Al = sd.Al; e.ns = sd.ns; e.ri = sd.ri; e.mcu_w = sd.mcu_w;
+            e.mask_off = R.mask_off[ig]; e.slot = R.slot_base[ig]; e.data_base = clean_base(sd.data_off);
+            e.before = 0; e.bpm = 0; e.pad[0] = e.pad[1] = e.pad[2] = 0;
+            bool has = false;
+            uint32_t before = 0, bpm = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < (uint32_t)kMaxComp; q++) {
+                if (q >= sd.ns) continue;
+                const uint32_t cq = sd.comp[q];
+                if (cq == c) { has = true; before = bpm; }
+                bpm += sd.ns > 1 ? (uint32_t)img->hs[cq] * img->vs[cq] : 1u;
             }
-            if (j < 0) continue;
-            e.before = (uint8_t)before; e.bpm = (uint8_t)bpm;
-        } else if (sd->comp[0] != c || sd->Ah == 0) continue;  // AC first scans are in the planes already
-        L->sc[n++] = e;
+            if (dc) { e.before = (uint8_t)before; e.bpm = (uint8_t)bpm; } else has = sd.comp[0] == c;
+            const bool take = g < upto && sd.Ah != 0 && (sd.Ss == 0 ? 1u : 0u) == dc && has;
+            const uint64_t all = __builtin_amdgcn_ballot_w64(take);
+            const uint32_t at = n + (uint32_t)__builtin_popcountll(all & ((1ull << lane) - 1u));
+            if (take && at < (uint32_t)kApplyMaxScans) L->sc[at] = e;
+            n += (uint32_t)__builtin_popcountll(all);
+        }
+        n = n < (uint32_t)kApplyMaxScans ? n : (uint32_t)kApplyMaxScans;
+        if (!dc && lane == 0) L->nac = n;
     }
-    L->n = n;
+    if (lane == 0) L->n = n;
 }
 
 __global__ void __launch_bounds__(256) k_apply(DevRecord R, const ApplyUnit* __restrict__ au, const ApplyList* __restrict__ lists) {
@@ -1395,6 +1406,7 @@ __global__ void __launch_bounds__(256) k_crop_resize(const uint32_t* __restrict_
 constexpr int kPixLanes = 128;             // blocks per workgroup (the samples of half a run take kPixLanes * 128 bytes of LDS)
 
 struct PixelTile { uint32_t img; uint32_t mcu0; };          // first MCU of the run
+typedef short short2v __attribute__((ext_vector_type(2)));
 typedef short short8 __attribute__((ext_vector_type(8)));
 
 // w / d as (w * recip16(d)) >> 16, exact while w * d < 65536
@@ -1405,7 +1417,17 @@ PCR_HD uint32_t blocks_per_mcu(const ImgDesc& d) {
     for (int c = 0; c < d.nc; c++) b += (uint32_t)d.hs[c] * d.vs[c];
     return b;
 }
-PCR_HD uint32_t pixel_mcus_per_tile(const ImgDesc& d) { return (uint32_t)kPixLanes / blocks_per_mcu(d); }   // >= 10: an MCU has at most 12 blocks
+// Samples of an MCU in LDS: 32 per block for half of its pixel rows, and some that stay empty.  A wavefront converts a
+// pixel row of several MCUs at a time, each lane sixteen bytes of it; with nothing between the MCUs their rows lie a
+// multiple of 256 bytes apart, on the same banks.  groups: lanes per pixel row of an MCU.
+PCR_HD uint32_t pixel_mcu_samples(uint32_t bpm, uint32_t groups) { return bpm * 32 + 4 * groups; }
+PCR_HD uint32_t pixel_row_groups(uint32_t nc, uint32_t hmax) { return 8 * hmax / (nc == 1 ? 8u : 4u); }
+constexpr uint32_t kPixSamples = 4368;     // what a workgroup holds: 21 MCUs of 4:2:0, 42 of 4:4:4, 121 gray ones (eight workgroups to a compute unit)
+PCR_HD uint32_t pixel_mcus(uint32_t bpm, uint32_t groups) {
+    const uint32_t by_lanes = (uint32_t)kPixLanes / bpm, by_lds = kPixSamples / pixel_mcu_samples(bpm, groups);
+    return by_lanes < by_lds ? by_lanes : by_lds;
+}
+PCR_HD uint32_t pixel_mcus_per_tile(const ImgDesc& d) { return pixel_mcus(blocks_per_mcu(d), pixel_row_groups(d.nc, d.hmax)); }   // >= 10: an MCU has at most 12 blocks
 
 // 8-point inverse transform with the constant factors taken out: in[u] must already carry the 1/2 of the pass and,
 // for u = 0 and 4, cos(pi/4).  out[x] = sum_u in'[u] cos((2x+1) u pi / 16).
@@ -1422,13 +1444,18 @@ PCR_D void idct8_scaled(float& x0, float& x1, float& x2, float& x3, float& x4, f
     x0 = e0 + o0; x7 = e0 - o0; x1 = e1 + o1; x6 = e1 - o1;
     x2 = e2 + o2; x5 = e2 - o2; x3 = e3 + o3; x4 = e3 - o3;
 }
-// the factor folded into the quantiser step of zig-zag position k: 1/2 per pass, cos(pi/4) for row or column 0 and 4
-PCR_D float idct_fold(uint32_t k) {
-    const uint32_t p = zigzag_lookup(k), u = p & 7, v = p >> 3;
-    const float c4 = 0.70710678118654752440f;
-    const bool a = (u & 3) == 0, b = (v & 3) == 0;
-    return a && b ? 0.125f : (a || b ? 0.25f * c4 : 0.25f);            // (cos(pi/4) squared is exactly 1/2: a block with only its DC is exactly DC x step / 8)
-}
+// The factor folded into the quantiser step of zig-zag position k: 1/2 per pass, cos(pi/4) for row or column 0 and 4.
+// Bit k of the words: positions with row and column 0 or 4, and those with one of them.
+struct PixFolds {
+    uint64_t both, once;
+    constexpr PixFolds() : both(0), once(0) {
+        for (int k = 0; k < 64; k++) {
+            const uint32_t p = (uint32_t)zigzag_natural(k), u = p & 7, v = p >> 3;
+            const bool a = (u & 3) == 0, b = (v & 3) == 0;
+            if (a && b) both |= 1ull << k; else if (a || b) once |= 1ull << k;
+        }
+    }
+};
 
 // byte `which` of `word` := v rounded half up and clamped to [0, 255] (v is finite); the other bytes are kept.
 // (The conversion instruction saturates and is exact on integers, which floor(v + 1/2) is.)
@@ -1436,11 +1463,16 @@ PCR_D uint32_t put_u8(float v, uint32_t which, uint32_t word) {
     return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_floorf(v + 0.5f), which, word);
 }
 
-// four bytes
+// Four values rounded half up and clamped to [0, 255], as bytes.  The conversion instruction rounds as the mode register
+// says; turned to downwards for it (and back to nearest behind it) it saves every byte its floor.
+#define PCR_ROUND_DOWN "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 2\n\t"
+#define PCR_ROUND_NEAREST "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 0"
 PCR_D uint32_t four_u8(float a, float b, float c, float d) {
-    uint32_t w = put_u8(a, 0, 0);
-    w = put_u8(b, 1, w); w = put_u8(c, 2, w);
-    return put_u8(d, 3, w);
+    uint32_t w;
+    asm(PCR_ROUND_DOWN
+        "v_cvt_pk_u8_f32 %0, %1, 0, 0\n\tv_cvt_pk_u8_f32 %0, %2, 1, %0\n\tv_cvt_pk_u8_f32 %0, %3, 2, %0\n\tv_cvt_pk_u8_f32 %0, %4, 3, %0\n\t"
+        PCR_ROUND_NEAREST : "=&v"(w) : "v"(a + 0.5f), "v"(b + 0.5f), "v"(c + 0.5f), "v"(d + 0.5f));
+    return w;
 }
 // The colour conversion of all pixel kernels (the same instructions everywhere, so that the pixels do not depend on which
 // kernel wrote them): luma y, chroma u, v around zero.
@@ -1451,14 +1483,41 @@ PCR_D void to_rgb(float y, float u, float v, float* r, float* g, float* b) {
 }
 // the twelve bytes of four pixels
 PCR_D void rgb_words(const float y[4], const float u[4], const float v[4], uint32_t w[3]) {
-    float r[4], gg[4], b[4];
+    float r[4], g[4], b[4];
 #pragma unroll
-    for (int i = 0; i < 4; i++) to_rgb(y[i], u[i], v[i], &r[i], &gg[i], &b[i]);
-    w[0] = four_u8(r[0], gg[0], b[0], r[1]); w[1] = four_u8(gg[1], b[1], r[2], gg[2]); w[2] = four_u8(b[2], r[3], gg[3], b[3]);
+    for (int i = 0; i < 4; i++) { to_rgb(y[i], u[i], v[i], &r[i], &g[i], &b[i]); r[i] += 0.5f; g[i] += 0.5f; b[i] += 0.5f; }
+    asm(PCR_ROUND_DOWN
+        "v_cvt_pk_u8_f32 %0, %3, 0, 0\n\tv_cvt_pk_u8_f32 %1, %7, 0, 0\n\tv_cvt_pk_u8_f32 %2, %11, 0, 0\n\t"
+        "v_cvt_pk_u8_f32 %0, %4, 1, %0\n\tv_cvt_pk_u8_f32 %1, %8, 1, %1\n\tv_cvt_pk_u8_f32 %2, %12, 1, %2\n\t"
+        "v_cvt_pk_u8_f32 %0, %5, 2, %0\n\tv_cvt_pk_u8_f32 %1, %9, 2, %1\n\tv_cvt_pk_u8_f32 %2, %13, 2, %2\n\t"
+        "v_cvt_pk_u8_f32 %0, %6, 3, %0\n\tv_cvt_pk_u8_f32 %1, %10, 3, %1\n\tv_cvt_pk_u8_f32 %2, %14, 3, %2\n\t"
+        PCR_ROUND_NEAREST
+        : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2])
+        : "v"(r[0]), "v"(g[0]), "v"(b[0]), "v"(r[1]), "v"(g[1]), "v"(b[1]), "v"(r[2]), "v"(g[2]), "v"(b[2]), "v"(r[3]), "v"(g[3]), "v"(b[3]));
 }
 
 // a value per component, picked by a per-lane component number out of three wave-uniform ones
 PCR_D uint32_t pick3(uint32_t c, uint32_t a0, uint32_t a1, uint32_t a2) { return c == 0 ? a0 : (c == 1 ? a1 : a2); }
+
+// What earlier kernels wrote and this one only reads, at a wave-uniform address: a scalar load, which arrives in scalar
+// registers and does not stand in the way of the loads behind it.
+template <class T> PCR_D T load_const(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
+// an image's descriptor through a wave-uniform pointer, as dwords
+PCR_D void load_desc(const ImgDesc* ip, ImgDesc* D) {
+    const __attribute__((address_space(4))) uint32_t* src = (const __attribute__((address_space(4))) uint32_t*)ip;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(D);
+#pragma unroll
+    for (uint32_t e = 0; e < sizeof(ImgDesc) / 4; e++) dst[e] = src[e];
+}
+// Where this stands its arguments have been loaded: loads that depend on nothing but the image's number are then under
+// way together.  (The compiler moves each to its first use, behind the branches, and waits for one after the other.)
+PCR_D void wanted_now(uint32_t a) { asm volatile("" :: "s"(a)); }
+PCR_D void wanted_now(uint64_t a) { asm volatile("" :: "s"(a)); }
+PCR_D void wanted_now(const ImgDesc& D) {
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(&D);
+#pragma unroll
+    for (uint32_t e = 0; e < sizeof(ImgDesc) / 4; e++) wanted_now(w[e]);
+}
 
 // What the pixel kernels need to know about an image, all wave-uniform (read through a wave-uniform pointer, so
 // with scalar loads): sampling, blocks per MCU, where a component's samples start inside an MCU's part of the
@@ -1468,7 +1527,8 @@ struct PixGeom {
     uint32_t hs[kMaxComp], vs[kMaxComp], nbl[kMaxComp], rb[kMaxComp], rs[kMaxComp], plane0[kMaxComp], npl[kMaxComp], bw[kMaxComp], zmx[kMaxComp], cw[kMaxComp], ch[kMaxComp];
     bool flat[kMaxComp];
 };
-PCR_D void pix_geom(const ImgDesc* ip, PixGeom* g) {
+PCR_D void pix_geom(const ImgDesc& D, PixGeom* g) {
+    const ImgDesc* ip = &D;
     g->nc = ip->nc; g->W = ip->W; g->H = ip->H; g->hmax = ip->hmax; g->vmax = ip->vmax; g->mcux = ip->mcux; g->mcuy = ip->mcuy;
     uint32_t bpm = 0, p0 = 0;
 #pragma unroll
@@ -1488,7 +1548,7 @@ PCR_D void pix_geom(const ImgDesc* ip, PixGeom* g) {
 // The lane's block: component c, block (brow, bcol) of the component's plane.
 struct PixBlock { uint32_t c, hs, vs, brow, bcol, b, zm, nblk; const int16_t* coef; const int16_t* dc; bool covered; };   // nblk: blocks of the component's plane;   // dc: the block's entry of the compact DC copy
 // j: number of the block inside its MCU (components one after the other, each vs rows of hs blocks); (my, mx): the MCU
-PCR_D void pix_block(const DevRecord& R, const PixGeom& G, uint32_t img, uint32_t j, uint32_t my, uint32_t mx, PixBlock* B, uint32_t* by_out, uint32_t* bx_out) {
+PCR_D void pix_block(const DevRecord& R, const PixGeom& G, uint64_t coef0, uint32_t j, uint32_t my, uint32_t mx, PixBlock* B, uint32_t* by_out, uint32_t* bx_out) {
     const uint32_t c = j < G.nbl[0] ? 0u : (j < G.nbl[0] + G.nbl[1] ? 1u : 2u);
     const uint32_t jj = j - pick3(c, 0u, G.nbl[0], G.nbl[0] + G.nbl[1]);
     B->c = c; B->hs = pick3(c, G.hs[0], G.hs[1], G.hs[2]); B->vs = pick3(c, G.vs[0], G.vs[1], G.vs[2]);
@@ -1497,72 +1557,100 @@ PCR_D void pix_block(const DevRecord& R, const PixGeom& G, uint32_t img, uint32_
     B->b = B->brow * pick3(c, G.bw[0], G.bw[1], G.bw[2]) + B->bcol;
     B->zm = pick3(c, G.zmx[0], G.zmx[1], G.zmx[2]);
     B->nblk = pick3(c, G.npl[0], G.npl[1], G.npl[2]);
-    B->coef = R.coef + R.coef_off[img] + ((size_t)pick3(c, G.plane0[0], G.plane0[1], G.plane0[2]) + B->b) * 64;
-    B->dc = R.dc + (R.coef_off[img] >> 6) + pick3(c, G.plane0[0], G.plane0[1], G.plane0[2]) + B->b;
+    B->coef = R.coef + coef0 + ((size_t)pick3(c, G.plane0[0], G.plane0[1], G.plane0[2]) + B->b) * 64;
+    B->dc = R.dc + (coef0 >> 6) + pick3(c, G.plane0[0], G.plane0[1], G.plane0[2]) + B->b;
     B->covered = B->brow < pick3(c, G.ch[0], G.ch[1], G.ch[2]) && B->bcol < pick3(c, G.cw[0], G.cw[1], G.cw[2]);
     *by_out = by; *bx_out = bx;
 }
-// the block's coefficients as they lie in memory (zig-zag order), chunks beyond zm left zero; the DC coefficient comes
-// from the compact copy (the planes hold it only for the coefficient export)
-PCR_D void pix_load(const PixBlock& B, short8 v[8]) {
+// The block's coefficients as they lie in memory (zig-zag order, two to a word), chunks beyond zm left zero; returns the
+// DC coefficient, which comes from the compact copy (the planes hold it only for the coefficient export) and is put in its
+// place when the loads have arrived (pix_samples): here it would have the lane wait for them.
+PCR_D int16_t pix_load(const PixBlock& B, uint4 v[8]) {
     const int16_t dc = *B.dc;
 #pragma unroll
     for (int ch = 0; ch < 8; ch++) {
-        v[ch] = short8{0, 0, 0, 0, 0, 0, 0, 0};
-        if ((uint32_t)ch * 8 < B.zm) v[ch] = *reinterpret_cast<const short8*>(B.coef + ch * 8);
+        v[ch] = uint4{0, 0, 0, 0};
+        if (B.zm > 1 && (uint32_t)ch * 8 < B.zm) v[ch] = *reinterpret_cast<const uint4*>(B.coef + ch * 8);
     }
-    v[0][0] = dc;
+    return dc;
 }
 // DC of the block after the component's DC refinement scans
 template <bool kRefine>
 PCR_D int pix_dc(const DevRecord& R, const PixBlock& B, int dcv, const ApplyList* rlc) {
     const uint32_t nref = kRefine ? rlc->n : 0;
-    for (uint32_t e = 0; e < nref; e++)
-        if (rlc->sc[e].Ss == 0 && dc_refinement_bit(R, rlc->sc[e], B.brow, B.bcol, B.hs, B.vs, B.covered)) dcv |= 1 << rlc->sc[e].Al;
+    for (uint32_t e = kRefine ? rlc->nac : 0u; e < nref; e++)
+        if (dc_refinement_bit(R, rlc->sc[e], B.brow, B.bcol, B.hs, B.vs, B.covered)) dcv |= 1 << rlc->sc[e].Al;
     return dcv;
+}
+// One or two refinement passes over the block's coefficients, two coefficients to a word.  A position either grows (it
+// was non-zero: + 2^Al with its own sign) or is new (it was zero: +- 2^Al by the sign its pass gave) or stays: one step
+// with one sign, taken from the coefficient or from the pass.  lo: the positions that change in the pass at bit Al, hi:
+// those of the pass before it at bit Al + 1 (or none): a position new in that pass may grow in this one and does so with
+// the same sign, so both passes are one step of 0 .. 3 times 2^Al.  neg: the new positions that are negative, of both.
+// Sixteen positions at a time are laid out so that a shift puts an even and an odd one into the two halves of a word:
+// six instructions for two coefficients and both passes (ten per coefficient one by one).
+PCR_D uint32_t pair_mad(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2v, a) * __builtin_bit_cast(short2v, b) + __builtin_bit_cast(short2v, c));
+}
+PCR_D uint32_t pair_sign(uint32_t a) { return __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2v, a) >> (short)15); }
+PCR_D void pix_refine(uint32_t cw[32], uint64_t neg, uint64_t hi, uint64_t lo, uint32_t Al) {
+    const uint32_t one = 0x00010001u << Al, above = ((0xFFFEu << Al) & 0xFFFFu) * 0x00010001u;     // 2^Al, and -2^(Al+1), in both halves
+#pragma unroll
+    for (int g = 0; g < 4; g++) {
+        auto spread = [g](uint64_t m) {                       // bit p of the sixteen: at p, and at p + 15
+            const uint32_t w = g < 2 ? (uint32_t)m : (uint32_t)(m >> 32), h = (g & 1) ? w >> 16 : w & 0xFFFFu;
+            return h | (h << 15);
+        };
+        const uint32_t n = spread(neg), m = (spread(lo) & 0x55555555u) | ((spread(hi) & 0x55555555u) << 1);
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            uint32_t& c = cw[8 * g + j];
+            const uint32_t step = (pair_sign((n << (15 - 2 * j)) | c) & above) | one;
+            c = pair_mad((m >> (2 * j)) & 0x00030003u, step, c);
+        }
+    }
 }
 // Refinement replay, de-quantisation and the 8x8 inverse transform of the lane's block; the clamped samples are left in
 // F[8 y + x].  qc: the component's folded quantiser steps (zig-zag order); rlc: its refinement scan list.
 template <bool kRefine>
-PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, float F[64]) {
-    int ci[64];
+PCR_D void pix_samples(const DevRecord& R, const PixBlock& B, const uint4 v[8], int16_t dc, const float* qc, const ApplyList* rlc, float F[64]) {
+    uint32_t cw[32];
 #pragma unroll
-    for (int ch = 0; ch < 8; ch++) {
-#pragma unroll
-        for (int q = 0; q < 8; q++) ci[ch * 8 + q] = v[ch][q];
-    }
-    const uint32_t nref = kRefine ? rlc->n : 0;
-    for (uint32_t e = 0; e < nref; e++) {
-        const ApplyScan& S = rlc->sc[e];
-        if (S.Ss == 0) {
-            if (dc_refinement_bit(R, S, B.brow, B.bcol, B.hs, B.vs, B.covered)) ci[0] |= 1 << S.Al;
-        } else if (B.covered) {
-            // the three words of the block's record: positions that become non-zero, their signs, positions
-            // whose magnitude grows (all inside the scan's band)
-            const uint64_t* rec = R.masks + S.mask_off;
-            const ulonglong2 ns = *reinterpret_cast<const ulonglong2*>(rec + ref_word(kRefNz, B.b, B.nblk));
-            const uint64_t nzm = ns.x, sgm = ns.y, plm = rec[ref_word(kRefPlus, B.b, B.nblk)];
-            // A position either grows (it was non-zero: + 2^Al with its own sign) or is new (it was zero: +- 2^Al by the
-            // sign bit) or stays: one step with one sign, taken from the coefficient or from the record.
-            const uint64_t anym = nzm | plm, negm = nzm & ~sgm;
-            const int p1 = 1 << S.Al, above = -2 * p1;       // (above: the bits over bit Al)
-#pragma unroll
-            for (int k = 1; k < 64; k++) {
-                const uint32_t anw = k < 32 ? (uint32_t)anym : (uint32_t)(anym >> 32), ngw = k < 32 ? (uint32_t)negm : (uint32_t)(negm >> 32);
-                const int bit = k & 31;
-                const int neg = (ci[k] | (int)(ngw << (31 - bit))) >> 31;   // all ones where the step is negative
-                const int step = (neg & above) | p1;                        // -2^Al or 2^Al
-                // ... taken where the coefficient changes: bit x step + coefficient in one instruction (written out: the
-                // compiler turns a product with a single bit into a mask, an `and` and an addition)
-                asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(ci[k]) : "v"((anw >> bit) & 1u), "v"(step), "v"(ci[k]));
-            }
+    for (int ch = 0; ch < 8; ch++) { cw[4 * ch] = v[ch].x; cw[4 * ch + 1] = v[ch].y; cw[4 * ch + 2] = v[ch].z; cw[4 * ch + 3] = v[ch].w; }
+    cw[0] = (cw[0] & 0xFFFF0000u) | (uint16_t)dc;
+    if (kRefine) {
+        const uint32_t nref = rlc->n, nac = B.covered ? rlc->nac : 0u;
+        // A pass's part of the block's record: positions that become non-zero and their signs, positions whose magnitude
+        // grows (all inside the scan's band).  Those of the first two passes are under way together, the DC bits beside them.
+        auto pass = [&](uint32_t e, ulonglong2* ns, uint64_t* pl) {
+            const uint64_t* rec = R.masks + rlc->sc[e].mask_off;
+            *ns = *reinterpret_cast<const ulonglong2*>(rec + ref_word(kRefNz, B.b, B.nblk));
+            *pl = rec[ref_word(kRefPlus, B.b, B.nblk)];
+        };
+        ulonglong2 ns0{0, 0}, ns1{0, 0};
+        uint64_t pl0 = 0, pl1 = 0;
+        if (nac > 0) pass(0, &ns0, &pl0);
+        if (nac > 1) pass(1, &ns1, &pl1);
+        for (uint32_t e = rlc->nac; e < nref; e++)
+            if (dc_refinement_bit(R, rlc->sc[e], B.brow, B.bcol, B.hs, B.vs, B.covered)) cw[0] |= (1u << rlc->sc[e].Al) & 0xFFFFu;
+        // the passes gathered and not made yet: usual scripts refine bit by bit, and the last two are made together
+        uint64_t neg = ns0.x & ~ns0.y, hi = 0, lo = ns0.x | pl0;
+        uint32_t al = nac > 0 ? rlc->sc[0].Al : 0u, passes = nac > 0 ? 1u : 0u;
+        for (uint32_t e = 1; e < nac; e++) {
+            if (e > 1) pass(e, &ns1, &pl1);
+            const uint32_t Al = rlc->sc[e].Al;
+            const bool joins = passes == 1 && Al + 1u == al;
+            if (passes != 0 && !joins) { pix_refine(cw, neg, hi, lo, al); neg = 0; passes = 0; }
+            hi = joins ? lo : 0; lo = ns1.x | pl1; neg |= ns1.x & ~ns1.y; al = Al; passes++;
         }
+        if (passes != 0) pix_refine(cw, neg, hi, lo, al);
     }
+    auto coef = [&](int k) { return (float)(int)(int16_t)(uint16_t)(cw[k >> 1] >> (16 * (k & 1))); };
 #pragma unroll
     for (int k4 = 0; k4 < 16; k4++) {                        // natural order: F[8 v + u]
         const float4 qq = *reinterpret_cast<const float4*>(qc + 4 * k4);
-        F[zigzag_lookup(4 * k4)] = (float)ci[4 * k4] * qq.x; F[zigzag_lookup(4 * k4 + 1)] = (float)ci[4 * k4 + 1] * qq.y;
-        F[zigzag_lookup(4 * k4 + 2)] = (float)ci[4 * k4 + 2] * qq.z; F[zigzag_lookup(4 * k4 + 3)] = (float)ci[4 * k4 + 3] * qq.w;
+        F[zigzag_lookup(4 * k4)] = coef(4 * k4) * qq.x; F[zigzag_lookup(4 * k4 + 1)] = coef(4 * k4 + 1) * qq.y;
+        F[zigzag_lookup(4 * k4 + 2)] = coef(4 * k4 + 2) * qq.z; F[zigzag_lookup(4 * k4 + 3)] = coef(4 * k4 + 3) * qq.w;
     }
     // the level shift: the DC term reaches every sample with weight one (its folded factor is exactly 1/8 and the
     // transforms only add it), so 128 is added to that once instead of to the 64 samples
@@ -1587,9 +1675,9 @@ PCR_D void pix_put_rows(const float F[64], float* dst, uint32_t row_len) {
 }
 // the same, with the whole block stored to dst[y * row_len + x]
 template <bool kRefine>
-PCR_D void pix_finish(const DevRecord& R, const PixBlock& B, const short8 v[8], const float* qc, const ApplyList* rlc, float* dst, uint32_t row_len) {
+PCR_D void pix_finish(const DevRecord& R, const PixBlock& B, const uint4 v[8], int16_t dc, const float* qc, const ApplyList* rlc, float* dst, uint32_t row_len) {
     float F[64];
-    pix_samples<kRefine>(R, B, v, qc, rlc, F);
+    pix_samples<kRefine>(R, B, v, dc, qc, rlc, F);
     pix_put_rows<0, 8>(F, dst, row_len);
 }
 // Half kHalf (0: upper, 1: lower) of the pixel rows of an MCU: the part of the lane's block that lies in it, to the
@@ -1605,24 +1693,59 @@ PCR_D void pix_put_half(const float F[64], bool flat, uint32_t vs, uint32_t by, 
         if (flat) dst[0] = F[0]; else pix_put_rows<4 * kHalf, 4>(F, dst, row_len);
     }
 }
-// the component's folded quantiser steps into LDS; every lane of the workgroup calls it
-PCR_D void pix_quant_table(const DevRecord& R, const ImgDesc* ip, uint32_t nc, float (*qz)[68], uint32_t tid, uint32_t nthreads) {
-    for (uint32_t e = tid; e < nc * 64; e += nthreads) {
-        const uint32_t c = e >> 6, k = e & 63;
-        const uint32_t tq = ip->tq[c];
-        const uint8_t* q = R.rec + ip->qoff[tq];
-        qz[c][k] = (ip->qprec[tq] ? (float)ld_be16(q + 2 * k) : (float)q[k]) * idct_fold(k);
+// The components' folded quantiser steps into LDS; every lane of the workgroup (of two wavefronts or more) calls it.  The
+// loads of all components are under way together, and where they lie is known from the descriptor in registers: a chain of
+// loads that each wait for the one before is what a kernel of short workgroups waits for most.
+struct PixQuant { uint32_t off[kMaxComp], wide[kMaxComp]; };
+PCR_D void pix_quant_where(const ImgDesc* ip, const ImgDesc& D, PixQuant* Q) {
+    const uint32_t prec = (uint32_t)D.qprec[0] | (uint32_t)D.qprec[1] << 8 | (uint32_t)D.qprec[2] << 16 | (uint32_t)D.qprec[3] << 24;
+#pragma unroll
+    for (uint32_t c = 0; c < kMaxComp; c++) {
+        const uint32_t tq = D.tq[c] & 3u;
+        Q->off[c] = load_const(&ip->qoff[tq]);               // (from memory: indexed in registers, the descriptor would go to scratch memory)
+        Q->wide[c] = (prec >> (8 * tq)) & 255u;
     }
 }
-// the refinement scan lists of the image's components into LDS
+struct PixSteps { uint32_t hi[2], lo[2]; };                  // a step's bytes as loaded (an 8-bit one twice): of component `wave`, and of component 2
+PCR_D void pix_quant_load(const DevRecord& R, const PixQuant& Q, uint32_t nc, uint32_t tid, PixSteps* S) {
+    const uint32_t wave = uni(tid >> 6), k = tid & 63u;
+#pragma unroll
+    for (uint32_t j = 0; j < 2; j++) {                        // (no branch: the loads would be waited for at its end)
+        const uint32_t c = j == 1 ? 2u : wave, d = c < nc ? c : 0u;
+        const uint32_t wide = pick3(d, Q.wide[0], Q.wide[1], Q.wide[2]) ? 1u : 0u;
+        const uint8_t* q = R.rec + pick3(d, Q.off[0], Q.off[1], Q.off[2]) + (k << wide);
+        S->hi[j] = q[0]; S->lo[j] = q[wide];
+    }
+}
+PCR_D void pix_quant_table(const PixQuant& Q, const PixSteps& S, uint32_t nc, float (*qz)[68], uint32_t tid, uint32_t nthreads) {
+    const uint32_t wave = uni(tid >> 6), k = tid & 63u;
+    // Which positions have the transform's cos(pi/4) folded in twice and once: bit k of the words.
+    constexpr PixFolds folds{};
+    const uint64_t both = folds.both >> k, once = folds.once >> k;
+    const float f = (both & 1u) ? 0.125f : ((once & 1u) ? 0.25f * 0.70710678118654752440f : 0.25f);   // (cos(pi/4) squared is exactly 1/2: a block with only its DC is exactly DC x step / 8)
+    auto step = [&](uint32_t c, uint32_t j) { return (float)(pick3(c, Q.wide[0], Q.wide[1], Q.wide[2]) ? S.hi[j] << 8 | S.lo[j] : S.hi[j]) * f; };
+    if (wave < nc) qz[wave][k] = step(wave, 0);
+    if (nthreads == 128 && wave == 0 && nc > 2) qz[2][k] = step(2, 1);    // (two wavefronts: the first has component 2 as well)
+}
+// the refinement scan lists of the image's components into LDS (all of them under way together)
 PCR_D void pix_lists(const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx, uint32_t img, uint32_t nc, ApplyList* rl, uint32_t tid, uint32_t nthreads) {
-    for (uint32_t c = 0; c < nc; c++) {
-        const int32_t li = list_idx ? list_idx[img * kMaxComp + c] : -1;
+    constexpr uint32_t kWords = sizeof(ApplyList) / 4;
+    const int32_t* at = list_idx + img * kMaxComp;
+    const int32_t l0 = at[0], l1 = at[1], l2 = at[2];
+    uint32_t w[kMaxComp], x[kMaxComp];
+    static_assert(kWords > 128 && kWords <= 256, "two words per lane of 128");
+    const uint32_t e0 = tid, e1 = tid + 128;
+#pragma unroll
+    for (uint32_t c = 0; c < kMaxComp; c++) {
+        const int32_t li = c == 0 ? l0 : (c == 1 ? l1 : l2);
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(&lists[li]);
+        w[c] = x[c] = 0;                                     // (n = 0 where there is none)
+        if (c < nc && li >= 0) { if (e0 < 128) w[c] = src[e0]; if (e1 < kWords) x[c] = src[e1]; }
+    }
+#pragma unroll
+    for (uint32_t c = 0; c < kMaxComp; c++) {
         uint32_t* dst = reinterpret_cast<uint32_t*>(&rl[c]);
-        if (li >= 0) {
-            const uint32_t* src = reinterpret_cast<const uint32_t*>(&lists[li]);
-            for (uint32_t e = tid; e < sizeof(ApplyList) / 4; e += nthreads) dst[e] = src[e];
-        } else if (tid == 0) dst[0] = 0;                    // n = 0
+        if (c < nc) { if (e0 < 128) dst[e0] = w[c]; if (e1 < kWords) dst[e1] = x[c]; }
     }
 }
 
@@ -1652,25 +1775,40 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
                                                      const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx,
                                                      const CropBox* __restrict__ boxes) {
     // samples of half the pixel rows of the run: 32 per block
-    __shared__ __attribute__((aligned(16))) float tile[kPixLanes * 32];
+    __shared__ __attribute__((aligned(16))) float tile[kPixSamples];
     // quantiser steps in zig-zag order times the folded transform factors; the rows of the three components start
     // four banks apart, so that lanes of different components read them without bank conflicts
     __shared__ __attribute__((aligned(16))) float qz[kMaxComp][68];
     __shared__ ApplyList rl[kRefine ? kMaxComp : 1];       // refinement scan lists of the components (n = 0: none)
-    // per MCU of the run: its first byte, counted from the first one of the run's first row of MCUs; how many of its pixel
-    // columns and rows lie inside the image (low and high half)
-    __shared__ uint2 place[kPixLanes];
+    // per MCU of the run: how many of its pixel columns and rows lie inside the image, less one (four bits each), and its
+    // first byte, counted from the first one of the run's first row of MCUs (below 2^23: at most 2 x 16 rows of 65535 pixels
+    // of a wide image, or what 121 MCUs hold)
+    __shared__ uint32_t place[kPixLanes];
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), mcu0 = uni(tiles[item].mcu0);
     const uint32_t tid = threadIdx.x;
-    const ImgDesc* ip = R.img + timg;
+    // Everything the run needs to know of its image, asked for at once, and the quantiser steps, the block's coefficients and
+    // the lists behind it: three round trips to memory ahead of the transform where there were eight, one after the other,
+    // half of a workgroup's time (measured: 53 % of the wavefronts' cycles waiting, now 39).  With the rows of the MCUs apart
+    // in LDS (pixel_mcu_samples) and both refinement passes at once (pix_refine), us alone: 1024 x 256 x 256 at scan group 5
+    // 137 -> 115, 128 x 1024 x 1024 310 -> 191, 256 x 600 x 450 4:4:4 at scan group 10 356 -> 219, 1024 photographs 460 -> 317.
+    ImgDesc D;
+    load_desc(R.img + timg, &D);
+    const bool dead = load_const(&R.status[timg]) != kOk;
+    const uint64_t coef0 = load_const(&R.coef_off[timg]), out0 = load_const(&R.out_off[timg]);
+    wanted_now(D); wanted_now((uint32_t)dead); wanted_now(coef0); wanted_now(out0);
     PixGeom G;
-    pix_geom(ip, &G);
+    pix_geom(D, &G);
+    PixQuant Q;
+    pix_quant_where(R.img + timg, D, &Q);
+#pragma unroll
+    for (uint32_t c = 0; c < kMaxComp; c++) wanted_now(Q.off[c]);
     const uint32_t nc = G.nc, W = G.W, H = G.H, mcux = G.mcux, bpm = G.bpm;
     const uint32_t mcu_px_w = 8 * G.hmax, mcu_px_h = 8 * G.vmax;
     if (bpm == 0 || bpm > 12) return;                       // (cannot happen for an image the parser accepted)
-    const uint32_t per = (uint32_t)kPixLanes / bpm;
+    const uint32_t gpm = pixel_row_groups(nc, G.hmax);      // groups per pixel row of an MCU: 1, 2 or 4
+    const uint32_t per = pixel_mcus(bpm, gpm);
     const uint32_t total = mcux * G.mcuy;
     if (mcu0 >= total) return;
     const uint32_t nm = total - mcu0 < per ? total - mcu0 : per;      // MCUs of this run
@@ -1685,30 +1823,29 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
             if ((int)(c0 * mcu_px_w) >= b.x0 + b.w || (int)((c0 + nm) * mcu_px_w) <= b.x0) return;
         }
     }
-    const bool dead = uni((uint32_t)(R.status[timg] != kOk)) != 0;
     const uint32_t row0 = mcu0 / mcux;                      // the run's first row of MCUs
-    // ---- phase A, first half: the lane's block and its loads ----
+    // ---- phase A, first half: the quantiser steps, the lane's block and its loads ----
+    PixSteps steps;
+    pix_quant_load(R, Q, nc, tid, &steps);
     const uint32_t m = (tid * recip16(bpm)) >> 16, j = tid - m * bpm;
     const bool mine = !dead && m < nm;
     PixBlock B;
     uint32_t by = 0, bx = 0;
-    short8 v[8];
+    uint4 v[8];
+    int16_t dc = 0;
     if (mine) {
         const uint32_t M = mcu0 + m, my = M / mcux, mx = M - my * mcux;
-        pix_block(R, G, timg, j, my, mx, &B, &by, &bx);
-        if (B.zm <= 1) {
-            v[0] = short8{0, 0, 0, 0, 0, 0, 0, 0};
-            v[0][0] = *B.dc;
-        } else pix_load(B, v);
+        pix_block(R, G, coef0, j, my, mx, &B, &by, &bx);
+        dc = pix_load(B, v);
     }
     // ---- prologue tables (the loads above are under way meanwhile) ----
     if (kRefine) pix_lists(lists, list_idx, timg, nc, rl, tid, kPixLanes);
-    pix_quant_table(R, ip, nc, qz, tid, kPixLanes);
+    pix_quant_table(Q, steps, nc, qz, tid, kPixLanes);
     if (tid < nm) {
         const uint32_t M = mcu0 + tid, my = M / mcux, mx = M - my * mcux;
         const uint32_t x = mx * mcu_px_w, y = my * mcu_px_h;
-        const uint32_t vw = x >= W ? 0 : (W - x < mcu_px_w ? W - x : mcu_px_w), vh = y >= H ? 0 : (H - y < mcu_px_h ? H - y : mcu_px_h);
-        place[tid] = uint2{((my - row0) * mcu_px_h * W + x) * nc, vw | vh << 16};
+        const uint32_t vw = W - x < mcu_px_w ? W - x : mcu_px_w, vh = H - y < mcu_px_h ? H - y : mcu_px_h;      // (every MCU holds a pixel)
+        place[tid] = (vw - 1u) | (vh - 1u) << 4 | ((my - row0) * mcu_px_h * W + x) * nc << 8;
     }
     __syncthreads();
     // ---- phase A, second half: the block's samples, in registers ----
@@ -1716,8 +1853,9 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
     const bool flatb = mine && B.zm <= 1;                   // flat: one sample stands for the block
     if (mine) {
         const ApplyList* rlc = &rl[kRefine ? B.c : 0];
-        if (flatb) S[0] = clamp255((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + 128.f);
-        else pix_samples<kRefine>(R, B, v, qz[B.c], rlc, S);
+        asm volatile("" : "+v"(dc), "+v"(v[0].x));            // (or what is done with them, and the wait for the loads, comes right behind the loads)
+        if (flatb) S[0] = clamp255((float)pix_dc<kRefine>(R, B, dc, rlc) * qz[B.c][0] + 128.f);
+        else pix_samples<kRefine>(R, B, v, dc, qz[B.c], rlc, S);
     }
     if (kPlanes) {
         // Instead of pixels: the lane's block, rounded, into the component's own plane of bytes (`out`: one byte per
@@ -1725,7 +1863,7 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
         // for k_triangle_rgb.  A damaged image's planes are left alone; that kernel writes its pixels as zeros.
         if (mine) {
             const uint32_t pw = pick3(B.c, G.bw[0], G.bw[1], G.bw[2]) * 8;
-            uint8_t* pd = out + R.coef_off[timg] + (size_t)pick3(B.c, G.plane0[0], G.plane0[1], G.plane0[2]) * 64 + (size_t)(B.brow * 8) * pw + B.bcol * 8;
+            uint8_t* pd = out + coef0 + (size_t)pick3(B.c, G.plane0[0], G.plane0[1], G.plane0[2]) * 64 + (size_t)(B.brow * 8) * pw + B.bcol * 8;
 #pragma unroll
             for (int y = 0; y < 8; y++) {
                 uint2 w;
@@ -1748,13 +1886,12 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
     const uint32_t shx2 = nc > 2 && G.hs[2] != G.hmax, shy2 = nc > 2 && G.vs[2] != G.vmax;
     const bool halves = (shx1 & shy1 & shx2 & shy2) && !shx0 && !shy0;                      // 4:2:0
     const uint32_t ppg = nc == 1 ? 8u : 4u;                 // pixels per group and row: 8 gray bytes, or 12 bytes of RGB
-    const uint32_t gpm = mcu_px_w / ppg;                    // groups per pixel row of an MCU: 1, 2 or 4
     const uint32_t lg = gpm == 4 ? 2u : (gpm == 2 ? 1u : 0u);
     const uint32_t half_h = mcu_px_h >> 1;                  // pixel rows of an MCU per half: 4 or 8
     const uint32_t items = nm * (half_h >> 1) * gpm;
     const uint32_t rcpn = nm > 1 ? 0xFFFFFFFFu / nm + 1u : 0u;       // q / nm as the high word of q * rcpn: exact while q * nm < 2^32
-    const uint32_t mstride = bpm * 32;                      // samples of an MCU in one half
-    uint8_t* const first = out + R.out_off[timg] + (size_t)row0 * mcu_px_h * W * nc;
+    const uint32_t mstride = pixel_mcu_samples(bpm, gpm);
+    uint8_t* const first = out + out0 + (size_t)row0 * mcu_px_h * W * nc;
     const uint32_t line = W * nc;
     // component c's four samples for pixels x0.. of row ly (counted inside the half) of MCU mm: a flat component has one per block
     auto fetch = [&](uint32_t c, uint32_t mm, uint32_t ly, uint32_t x0, uint32_t shx, uint32_t shy, float s[4]) {
@@ -1777,10 +1914,10 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
             const uint32_t g = it & (gpm - 1), q = it >> lg;
             const uint32_t lyp = nm > 1 ? __umulhi(q, rcpn) : q, mm = q - lyp * nm, lyh = 2 * lyp;
             const uint32_t ly = lyh + half * half_h;        // the first of the two pixel rows inside the MCU
-            const uint2 pl = place[mm];
-            const uint32_t x0 = g * ppg, vw = pl.y & 0xFFFFu, vh = pl.y >> 16;
+            const uint32_t pl = place[mm];
+            const uint32_t x0 = g * ppg, vw = (pl & 15u) + 1u, vh = ((pl >> 4) & 15u) + 1u;
             if (ly >= vh || x0 >= vw) continue;
-            uint8_t* const wp = first + (pl.x + ly * line + x0 * nc);
+            uint8_t* const wp = first + ((pl >> 8) + ly * line + x0 * nc);
             const uint32_t left = vw - x0;                  // pixels of the group inside the image
             const bool both = ly + 1 < vh;
             if (nc == 1) {
@@ -1855,13 +1992,6 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
 constexpr int kFlatLanes = 256;
 PCR_HD uint32_t flat_cells(uint32_t W, uint32_t H) { return ((W + 7) >> 3) * ((H + 7) >> 3); }
 
-// an image's descriptor through a wave-uniform pointer, as dwords
-PCR_D void load_desc(const ImgDesc* ip, ImgDesc* D) {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(ip);
-    uint32_t* dst = reinterpret_cast<uint32_t*>(D);
-#pragma unroll
-    for (uint32_t e = 0; e < sizeof(ImgDesc) / 4; e++) dst[e] = src[e];
-}
 // only DCs decoded for every component?  (the host launches the flat kernels only for such decodes)
 PCR_D bool flat_image(const ImgDesc& D) {
     bool ok = D.nc == 1 || D.nc == 3;
@@ -1888,12 +2018,12 @@ PCR_D void flat_cell_words(const DevRecord& R, const ImgDesc& D, const int16_t* 
             plane0 += (uint32_t)D.bw[c] * D.bh[c];
         }
     }
-    if (D.nc == 1) { uint32_t g = put_u8(s[0], 0, 0); g |= g << 8; g |= g << 16; *w0 = g; *w1 = g; *w2 = g; }
+    if (D.nc == 1) { const uint32_t g = four_u8(s[0], s[0], s[0], s[0]); *w0 = g; *w1 = g; *w2 = g; }
     else {
         float rf, gf, bf;
         to_rgb(s[0], s[1] - 128.f, s[2] - 128.f, &rf, &gf, &bf);
-        const uint32_t r = put_u8(rf, 0, 0), gq = put_u8(gf, 0, 0), bq = put_u8(bf, 0, 0);
-        *w0 = r | (gq << 8) | (bq << 16) | (r << 24); *w1 = gq | (bq << 8) | (r << 16) | (gq << 24); *w2 = bq | (r << 8) | (gq << 16) | (bq << 24);
+        const uint32_t w = four_u8(rf, gf, bf, rf);
+        *w0 = w; *w1 = __builtin_amdgcn_perm(w, w, 0x01000201u); *w2 = __builtin_amdgcn_perm(w, w, 0x02010002u);
     }
     if (dead) { *w0 = 0; *w1 = 0; *w2 = 0; }
 }
@@ -2387,9 +2517,15 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), mcu0 = uni(tiles[item].mcu0);
     const uint32_t tid = threadIdx.x;
-    const ImgDesc* ip = R.img + timg;
+    ImgDesc D;
+    load_desc(R.img + timg, &D);
+    const bool dead = load_const(&R.status[timg]) != kOk;
+    const uint64_t coef0 = load_const(&R.coef_off[timg]), edge0 = load_const(&edge_off[timg]);
+    wanted_now(D); wanted_now((uint32_t)dead); wanted_now(coef0); wanted_now(edge0);
     PixGeom G;
-    pix_geom(ip, &G);
+    pix_geom(D, &G);
+    PixQuant Q;
+    pix_quant_where(R.img + timg, D, &Q);
     const uint32_t nc = G.nc, W = G.W, H = G.H, mcux = G.mcux, bpm = G.bpm;
     const uint32_t mcu_px_w = 8 * G.hmax, mcu_px_h = 8 * G.vmax;
     const uint32_t seg_m = min((uint32_t)kTailLanes / max(bpm, 1u), mcux);   // MCUs one pass holds in LDS
@@ -2399,10 +2535,21 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
     const CropBox b = clamp_box(boxes[timg], (int)W, (int)H);
     if ((int)ylo >= b.y0 + b.h || (int)yhi <= b.y0) return;
     const uint32_t mc0 = (uint32_t)b.x0 / mcu_px_w, mc1 = (uint32_t)(b.x0 + b.w - 1) / mcu_px_w;   // MCUs the box touches
-    const bool dead = uni((uint32_t)(R.status[timg] != kOk)) != 0;
     const uint32_t ml = (tid * recip16(bpm)) >> 16, j = tid - ml * bpm;   // MCU within the pass, block within the MCU
+    // the loads of the first pass; those of each further one set out ahead of the tail of the pass before it
+    PixSteps steps;
+    pix_quant_load(R, Q, nc, tid, &steps);
+    PixBlock B;
+    uint32_t by = 0, bx = 0;
+    uint4 v[8];
+    int16_t dc = 0;
+    auto mine_at = [&](uint32_t s0) { return !dead && ml < seg_m && s0 + ml <= min(s0 + seg_m - 1, mc1); };
+    if (mine_at(mc0)) {
+        pix_block(R, G, coef0, j, my, mc0 + ml, &B, &by, &bx);
+        dc = pix_load(B, v);
+    }
     if (kRefine) pix_lists(lists, list_idx, timg, nc, rl, tid, kTailLanes);
-    pix_quant_table(R, ip, nc, qz, tid, kTailLanes);
+    pix_quant_table(Q, steps, nc, qz, tid, kTailLanes);
     if (tid == 0) { row_lo = 0xFFFFFFFFu; row_hi = 0; }
     __syncthreads();
     // output rows both of whose source rows lie in [ylo, yhi): they form one interval
@@ -2425,20 +2572,17 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
     for (uint32_t s0 = mc0;; s0 += seg_m - 1) {
         const uint32_t s1 = min(s0 + seg_m - 1, mc1);                   // last MCU decoded in this pass
         const bool last = s1 == mc1;
-        const uint32_t m = s0 + ml;
-        const bool mine = !dead && ml < seg_m && m <= s1;
-        PixBlock B;
-        uint32_t by = 0, bx = 0;
-        short8 v[8];
-        if (mine) {
-            pix_block(R, G, timg, j, my, m, &B, &by, &bx);
-            if (B.zm <= 1) { v[0] = short8{0, 0, 0, 0, 0, 0, 0, 0}; v[0][0] = *B.dc; }
-            else pix_load(B, v);
+        if (mine_at(s0)) {
+            asm volatile("" : "+v"(dc), "+v"(v[0].x));        // (see k_pixel)
             const ApplyList* rlc = &rl[kRefine ? B.c : 0];
             const uint32_t row_len = seg_m * B.hs * 8;
             float* dst = tile + seg_m * pick3(B.c, G.rb[0], G.rb[1], G.rb[2]) + by * 8 * row_len + (ml * B.hs + bx) * 8;
-            if (B.zm <= 1) dst[0] = clamp255((float)pix_dc<kRefine>(R, B, v[0][0], rlc) * qz[B.c][0] + 128.f);
-            else pix_finish<kRefine>(R, B, v, qz[B.c], rlc, dst, row_len);
+            if (B.zm <= 1) dst[0] = clamp255((float)pix_dc<kRefine>(R, B, dc, rlc) * qz[B.c][0] + 128.f);
+            else pix_finish<kRefine>(R, B, v, dc, qz[B.c], rlc, dst, row_len);
+        }
+        if (!last && mine_at(s1)) {
+            pix_block(R, G, coef0, j, my, s1 + ml, &B, &by, &bx);
+            dc = pix_load(B, v);
         }
         __syncthreads();
         const uint32_t xorg = s0 * mcu_px_w;                            // image column of the pass's first sample
@@ -2446,7 +2590,7 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
         const uint32_t xe = last ? (uint32_t)(b.x0 + b.w) : s1 * mcu_px_w;
         // the first and the last pixel row, for the output rows that need a neighbouring MCU row as well
         {
-            uint8_t* e = edge + edge_off[timg] + (size_t)(2 * my) * W * nc;
+            uint8_t* e = edge + edge0 + (size_t)(2 * my) * W * nc;
             const uint32_t span = xe - xs;
             for (uint32_t it = tid; it < 2 * span; it += kTailLanes) {
                 const uint32_t which = it >= span, x = xs + (which ? it - span : it);

@@ -688,7 +688,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         }
     }
     if (plan->n_apply) {
-        hipLaunchKernelGGL(k_apply_prep, dim3((plan->n_apply + 63) / 64), dim3(64), 0, s, r->d, plan->d_apply, plan->n_apply, (uint32_t)k, plan->d_apply_lists);
+        hipLaunchKernelGGL(k_apply_prep, dim3((plan->n_apply + kApplyPrepWaves - 1) / kApplyPrepWaves), dim3(64 * kApplyPrepWaves), 0, s, r->d, plan->d_apply, plan->n_apply, (uint32_t)k, plan->d_apply_lists);
         if (refine_in_memory)
             hipLaunchKernelGGL(k_apply, dim3(plan->apply_grid_x, plan->n_apply), dim3(256), 0, s, r->d, plan->d_apply, plan->d_apply_lists);
     }
