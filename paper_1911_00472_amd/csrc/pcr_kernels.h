@@ -654,46 +654,106 @@ PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __rest
     L->ok = true;
 }
 
-PCR_D uint32_t lane_le32(const uint8_t* p) { return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24); }
+// What earlier kernels wrote and this one only reads, at a wave-uniform address: a scalar load, which arrives in scalar
+// registers and does not stand in the way of the loads behind it.
+template <class T> PCR_D T load_const(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
+// Where this stands its arguments have been loaded: loads that depend on nothing but the image's number are then under
+// way together.  (The compiler moves each to its first use, behind the branches, and waits for one after the other.)
+PCR_D void wanted_now(uint32_t a) { asm volatile("" :: "s"(a)); }
+PCR_D void wanted_now(uint64_t a) { asm volatile("" :: "s"(a)); }
+// The same in vector registers; a descriptor as its words (loaded whole: the loads of single members end up behind the
+// branches that use them).
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+PCR_D void arrived(uint32_t a) { asm volatile("" :: "v"(a)); }
+PCR_D void arrived(uint64_t a) { asm volatile("" :: "v"(a)); }
+template <class T> struct DescWords {
+    static constexpr uint32_t kQuads = sizeof(T) / 16, kRest = sizeof(T) / 4 - 4 * kQuads;
+    uint4v q[kQuads]; uint32_t r[kRest ? kRest : 1];
+    PCR_D void load(const T* p) {
+        struct __attribute__((packed, aligned(4))) Quad { uint4v v; };
+#pragma unroll
+        for (uint32_t e = 0; e < kQuads; e++) q[e] = reinterpret_cast<const Quad*>(p)[e].v;
+#pragma unroll
+        for (uint32_t e = 0; e < kRest; e++) r[e] = reinterpret_cast<const uint32_t*>(p)[4 * kQuads + e];
+    }
+    PCR_D void here() const {
+#pragma unroll
+        for (uint32_t e = 0; e < kQuads; e++) asm volatile("" :: "v"(q[e]));
+#pragma unroll
+        for (uint32_t e = 0; e < kRest; e++) asm volatile("" :: "v"(r[e]));
+    }
+    // the member of `bytes` bytes at offset off (constants, after inlining)
+    PCR_D uint32_t at(size_t off, uint32_t bytes) const {
+        const uint32_t e = (uint32_t)off / 4, w = e < 4 * kQuads ? q[e / 4][e % 4] : r[e - 4 * kQuads];
+        return bytes == 4 ? w : (w >> (8 * (off % 4))) & ((1u << (8 * bytes)) - 1u);
+    }
+};
+#define PCR_MEMBER(D, T, m, i) ((D).at(offsetof(T, m) + (i) * sizeof(((T*)0)->m[0]), sizeof(((T*)0)->m[0])))
+#define PCR_FIELD(D, T, m) ((D).at(offsetof(T, m), sizeof(((T*)0)->m)))
+
+// What the set-up of a unit reads, in two rounds of loads that depend on nothing but the unit and on the first round: loads
+// that are each behind a check of the one before cost a trip to memory each, eight or nine of them ahead of a lane's first
+// symbol.  (Every address is inside its buffer whatever the descriptors say; the checks come afterwards.)
+struct LaneUnitInfo {
+    DescWords<ImgDesc> img; DescWords<ScanDesc> sd;
+    bool ok, entries;                                         // the unit can be decoded, as far as these tell; it runs from one entry point to another
+    uint32_t ns, Ss, Se, Ah, Al, mcu_w;
+    uint64_t coef0;
+    uint32_t m0, m1, b0, b1;                                  // its MCUs, its bits in the scan's unstuffed data
+    uint64_t preds;                                           // DC predictions of the entry point it starts at, or zeros
+    PCR_D uint32_t bw(uint32_t c) const { return pick(c, PCR_MEMBER(img, ImgDesc, bw, 0), PCR_MEMBER(img, ImgDesc, bw, 1), PCR_MEMBER(img, ImgDesc, bw, 2)); }
+    PCR_D uint32_t bh(uint32_t c) const { return pick(c, PCR_MEMBER(img, ImgDesc, bh, 0), PCR_MEMBER(img, ImgDesc, bh, 1), PCR_MEMBER(img, ImgDesc, bh, 2)); }
+    PCR_D uint32_t hs(uint32_t c) const { return pick(c, PCR_MEMBER(img, ImgDesc, hs, 0), PCR_MEMBER(img, ImgDesc, hs, 1), PCR_MEMBER(img, ImgDesc, hs, 2)); }
+    PCR_D uint32_t vs(uint32_t c) const { return pick(c, PCR_MEMBER(img, ImgDesc, vs, 0), PCR_MEMBER(img, ImgDesc, vs, 1), PCR_MEMBER(img, ImgDesc, vs, 2)); }
+    PCR_D uint32_t nblk(uint32_t c) const { return c < PCR_FIELD(img, ImgDesc, nc) ? bw(c) * bh(c) : 0u; }
+    PCR_D uint32_t before(uint32_t c) const { return (c > 0 ? nblk(0) : 0u) + (c > 1 ? nblk(1) : 0u); }      // blocks of the planes ahead of it
+    PCR_D static uint32_t pick(uint32_t c, uint32_t a0, uint32_t a1, uint32_t a2) { return c == 0 ? a0 : (c == 1 ? a1 : a2); }
+};
+PCR_D uint64_t loose64(const uint8_t* p) { return reinterpret_cast<const LooseU64*>(p)->v; }
+PCR_D __attribute__((always_inline)) void lane_unit_info(const DevRecord& R, const Unit& un, LaneUnitInfo* I) {
+    const size_t ig = (size_t)un.img * R.G + un.scan;
+    auto in_record = [&](uint64_t at, uint32_t bytes) { return R.rec + (at + bytes <= R.nbytes ? at : R.nbytes - bytes); };   // (a record has more than 24 bytes)
+    // first round
+    I->img.load(&R.img[un.img]); I->sd.load(&R.scan[ig]);
+    const uint32_t status = (uint32_t)R.status[un.img], sc = R.slot_cnt[ig], ent = R.ent_off[ig];
+    const uint32_t field = reinterpret_cast<const LooseU16*>(in_record(hdr_ecount_pos(R.n, R.G, un.scan, un.img), 2))->v;
+    const uint32_t i0 = R.ivl_start[un.slot + un.interval], i1 = R.ivl_start[un.slot + un.interval + 1];
+    I->coef0 = R.coef_off[un.img];
+    I->img.here(); I->sd.here(); arrived(status); arrived(sc); arrived(ent); arrived(field); arrived(i0); arrived(i1); arrived(I->coef0);
+    I->ns = PCR_FIELD(I->sd, ScanDesc, ns); I->Ss = PCR_FIELD(I->sd, ScanDesc, Ss); I->Se = PCR_FIELD(I->sd, ScanDesc, Se);
+    I->Ah = PCR_FIELD(I->sd, ScanDesc, Ah); I->Al = PCR_FIELD(I->sd, ScanDesc, Al); I->mcu_w = PCR_FIELD(I->sd, ScanDesc, mcu_w);
+    const uint32_t mcus = PCR_FIELD(I->sd, ScanDesc, mcus), ri = PCR_FIELD(I->sd, ScanDesc, ri);
+    I->entries = ri == 0 && sc > 1;
+    // second round: the scan's end, the entry points ahead of and behind the unit
+    const uint32_t stride = entry_stride(field);
+    const uint64_t e = (uint64_t)ent + (uint64_t)stride * un.interval;
+    const bool first = un.interval == 0, last = un.interval + 1 >= sc;
+    const uint64_t ahead = I->entries && !first ? e - stride : 0;
+    const uint8_t *pa = in_record(ahead, 8), *pp = in_record(ahead + 8, 8), *pb = in_record(I->entries && !last ? e : 0, 8);
+    const uint32_t total = R.ivl_start[un.slot + (I->entries ? sc : 0u)] * 8;
+    const uint64_t ea = loose64(pa), eb = loose64(pb), ep = loose64(pp);
+    arrived(total); arrived(ea); arrived(eb); arrived(ep);
+    const uint32_t r0 = ri ? un.interval * ri : 0u, r1 = ri ? (r0 + ri < mcus ? r0 + ri : mcus) : mcus;
+    I->m0 = I->entries ? (first ? 0u : (uint32_t)ea) : r0; I->m1 = I->entries && !last ? (uint32_t)eb : (I->entries ? mcus : r1);
+    I->b0 = I->entries ? (first ? 0u : (uint32_t)(ea >> 32)) : i0 * 8; I->b1 = I->entries ? (last ? total : (uint32_t)(eb >> 32)) : (i1 > i0 ? i1 : i0) * 8;
+    I->preds = !I->entries || first || stride != kEntryBytes ? 0u : ep;
+    I->ok = status == (uint32_t)kOk && un.scan < PCR_FIELD(I->img, ImgDesc, nscans) && PCR_FIELD(I->sd, ScanDesc, valid) != 0 && I->mcu_w != 0 && (I->entries || I->m0 < mcus);
+    if (I->ok && I->entries && !(I->m0 < I->m1 && I->m1 <= mcus && I->b0 <= I->b1 && I->b1 <= total)) { R.status[un.img] = kEFormat; I->ok = false; }   // entries out of order or out of range
+}
 
 // The same checks and ranges as unit_setup (pcr_kernels.h), without the assumption that the unit is wave-uniform.
 PCR_D void lane_unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __restrict__ clean32, LaneUnit* U) {
-    U->ok = false;
-    const ImgDesc* img = &R.img[un.img];
-    if (R.status[un.img] != kOk || un.scan >= img->nscans) return;
-    const size_t ig = (size_t)un.img * R.G + un.scan;
-    const ScanDesc* sd = &R.scan[ig];
-    if (!sd->valid || sd->ns != 1 || sd->Ss == 0) return;
-    const uint32_t sb = R.slot_base[ig], sc = R.slot_cnt[ig];
-    const uint32_t ri = sd->ri, mcus = sd->mcus;
-    if (ri == 0 && sc > 1) {
-        const uint32_t stride = entry_stride(ld_le16(R.rec + hdr_ecount_pos(R.n, R.G, un.scan, un.img)));
-        const uint8_t* e = R.rec + R.ent_off[ig] + (size_t)stride * un.interval;
-        const uint32_t total = R.ivl_start[sb + sc] * 8;
-        uint32_t m0 = 0, b0 = 0, m1 = mcus, b1 = total;
-        if (un.interval > 0) { m0 = lane_le32(e - stride); b0 = lane_le32(e - stride + 4); }
-        if (un.interval + 1 < sc) { m1 = lane_le32(e); b1 = lane_le32(e + 4); }
-        if (!(m0 < m1 && m1 <= mcus && b0 <= b1 && b1 <= total)) { R.status[un.img] = kEFormat; return; }
-        U->mcu0 = m0; U->mcu1 = m1; U->bit0 = b0; U->bit1 = b1;
-    } else {
-        const uint32_t b0 = R.ivl_start[sb + un.interval], b1 = R.ivl_start[sb + un.interval + 1];
-        U->mcu0 = ri ? un.interval * ri : 0;
-        U->mcu1 = ri ? (U->mcu0 + ri < mcus ? U->mcu0 + ri : mcus) : mcus;
-        if (U->mcu0 >= mcus) return;
-        U->bit0 = b0 * 8; U->bit1 = (b1 > b0 ? b1 : b0) * 8;
-    }
-    U->mcu_w = sd->mcu_w;
-    if (U->mcu_w == 0) return;
-    U->Ss = sd->Ss; U->Se = sd->Se; U->Al = sd->Al;
-    const uint32_t c = sd->comp[0];
-    size_t po = 0;
-    for (uint32_t q = 0; q < c && q < kMaxComp; q++) po += (size_t)img->bw[q] * img->bh[q] * 64;
-    U->bw = img->bw[c];
-    U->plane = R.coef + R.coef_off[un.img] + po;
-    U->plane_elems = (uint32_t)img->bw[c] * img->bh[c] * 64;
-    U->words = clean32 + (clean_base(sd->data_off) >> 2);
+    LaneUnitInfo I;
+    lane_unit_info(R, un, &I);
+    U->ok = I.ok && I.ns == 1 && I.Ss != 0;
+    const uint32_t c = PCR_MEMBER(I.sd, ScanDesc, comp, 0);
+    U->mcu0 = I.m0; U->mcu1 = I.m1; U->bit0 = I.b0; U->bit1 = I.b1; U->mcu_w = I.mcu_w;
+    U->Ss = I.Ss; U->Se = I.Se; U->Al = I.Al;
+    U->bw = I.bw(c);
+    U->plane_elems = U->bw * I.bh(c) * 64;
+    U->plane = R.coef + I.coef0 + (size_t)I.before(c) * 64;
+    U->words = clean32 + (clean_base(PCR_FIELD(I.sd, ScanDesc, data_off)) >> 2);
     U->tab = nullptr;                                         // (the kernel points it at the job's copy in LDS)
-    U->ok = true;
 }
 
 // One job of a lane-per-unit kernel: units [first, first + count) of the launch's list, count <= 64, and the scans they
@@ -701,36 +761,36 @@ PCR_D void lane_unit_setup(const DevRecord& R, const Unit& un, const uint32_t* _
 constexpr int kLaneTabs = 8;
 struct LaneJob { uint32_t first, count, ntab; uint32_t key[kLaneTabs]; };
 
-// The AC tables of a job on their way into LDS: fetch with every lane of the wavefront, put once the loads may be waited for
-// (the pieces of all tables are under way together, and the set-up of the units beside them).
-struct LaneTables {
-    uint4 v[kLaneTabs], w[kLaneTabs];
-    PCR_D void fetch(const DevRecord& R, const LaneJob& job) {
-        const uint32_t t = threadIdx.x;
-        static_assert(kLaneTabPieces > kEntropyLanes && kLaneTabPieces <= 2 * kEntropyLanes, "two pieces per lane");
+// The AC tables of a job on their way into LDS, straight from memory: bring with every lane of the wavefront, have once
+// they are needed (the set-up of the units goes on beside them).  Where the tables lie is read first, for all at once: with
+// each table behind its own index and its own branch the eight of a job were eight trips to memory one after the other.
+PCR_D void lane_tables_bring(const DevRecord& R, const LaneJob& job, const Unit& un, uint4 (*tabs)[kLaneTabPieces]) {
+    const uint32_t t = threadIdx.x;
+    static_assert(kLaneTabPieces > kEntropyLanes && kLaneTabPieces <= 2 * kEntropyLanes, "two pieces per lane");
+    uint32_t at[kLaneTabs];
 #pragma unroll
-        for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) {
-            const uint32_t k = job.key[sl];
-            v[sl] = w[sl] = uint4{0, 0, 0, 0};
-            if (sl < job.ntab && k < R.n * R.G) {             // (the same for all lanes)
-                const uint4* src = reinterpret_cast<const uint4*>(&R.tabs[R.tab_idx[k]]);
-                v[sl] = src[t];
-                if (t < kLaneTabPieces - kEntropyLanes) w[sl] = src[kEntropyLanes + t];
-            }
-        }
+    for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) {
+        const uint32_t k = job.key[sl < job.ntab ? sl : 0u];
+        at[sl] = load_const(&R.tab_idx[k < R.n * R.G ? k : 0u]);
     }
-    PCR_D void put(const LaneJob& job, uint4 (*tabs)[kLaneTabPieces]) const {
-        const uint32_t t = threadIdx.x;
 #pragma unroll
-        for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) {
-            if (sl < job.ntab) {
-                tabs[sl][t] = v[sl];
-                if (t < kLaneTabPieces - kEntropyLanes) tabs[sl][kEntropyLanes + t] = w[sl];
-            }
-        }
-        __syncthreads();
+    for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) wanted_now(at[sl]);
+    arrived(un.img); arrived(un.scan);                        // (the lane's unit, on its way since before: waited for here, not behind the tables)
+    auto to_lds = [](const uint4* from, uint4* to) {          // lane l's piece to to[l]
+        __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)from, (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+    };
+#pragma unroll
+    for (uint32_t sl = 0; sl < (uint32_t)kLaneTabs; sl++) {
+        if (sl >= job.ntab) continue;                         // (the same for all lanes)
+        const uint4* src = reinterpret_cast<const uint4*>(&R.tabs[at[sl]]);
+        to_lds(src + t, &tabs[sl][0]);
+        if (t < kLaneTabPieces - kEntropyLanes) to_lds(src + kEntropyLanes + t, &tabs[sl][kEntropyLanes]);
     }
-};
+}
+PCR_D void lane_tables_have() {
+    __builtin_amdgcn_s_waitcnt(0x0F70);                       // (vmcnt 0)
+    __syncthreads();
+}
 // the slot of the table of scan `key` (>= kLaneTabs: not among the job's -- the host never makes such a job)
 PCR_D uint32_t lane_table_slot(const DevRecord& R, const LaneJob& job, uint32_t key) {
     uint32_t slot = ~0u;
@@ -883,26 +943,28 @@ __global__ void __launch_bounds__(kEntropyLanes * kChainWaves) k_decode_waves(De
 // units of one scan lie together).  The tables (built by k_headers) are copied into LDS first: every lane looks
 // its codes up in its own table, and 64 scattered reads of memory per symbol would bound the kernel by the rate at
 // which the memory pipeline takes requests.
-__global__ void __launch_bounds__(kEntropyLanes) k_ac_first_lanes(DevRecord R, const Unit* __restrict__ units, const LaneJob* __restrict__ jobs,
-        const uint32_t* __restrict__ clean32) {
-    __shared__ uint4 tabs[kLaneTabs][kLaneTabPieces];
-    __shared__ LaneRing rings;
-    const LaneJob job = jobs[blockIdx.x];
+PCR_D __attribute__((always_inline)) void ac_first_job(const DevRecord& R, const Unit* __restrict__ units, const LaneJob& job, const uint32_t* __restrict__ clean32,
+        uint4 (*tabs)[kLaneTabPieces], LaneRing* rings) {
     const uint32_t t = threadIdx.x;
     const bool mine = t < job.count;
-    Unit un = units[job.first + (mine ? t : 0u)];
+    const Unit un = units[job.first + (mine ? t : 0u)];
     const uint32_t key = un.img * R.G + un.scan;
-    LaneTables staged;
-    staged.fetch(R, job);
+    lane_tables_bring(R, job, un, tabs);
     const uint32_t slot = lane_table_slot(R, job, key);
     LaneUnit U;
     U.ok = false;
     if (mine && slot < (uint32_t)kLaneTabs) lane_unit_setup(R, un, clean32, &U);
-    staged.put(job, tabs);
+    lane_tables_have();
     if (!U.ok) return;
     U.tab = reinterpret_cast<const LaneTab*>(&tabs[slot][0]);
-    const int rc = lane_decode_ac_first(U, &rings, t);
+    const int rc = lane_decode_ac_first(U, rings, t);
     if (rc != kOk) R.status[un.img] = rc;
+}
+__global__ void __launch_bounds__(kEntropyLanes) k_ac_first_lanes(DevRecord R, const Unit* __restrict__ units, const LaneJob* __restrict__ jobs,
+        const uint32_t* __restrict__ clean32) {
+    __shared__ uint4 tabs[kLaneTabs][kLaneTabPieces];
+    __shared__ LaneRing rings;
+    ac_first_job(R, units, jobs[blockIdx.x], clean32, tabs, &rings);
 }
 
 // AC refinement scans with one lane per unit: as k_ac_first_lanes.  k_refine_history must have run for the scans of the
@@ -917,13 +979,12 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_refine_lanes(DevRecord R, 
     const bool mine = t < job.count;
     Unit un = units[job.first + (mine ? t : 0u)];
     const uint32_t key = un.img * R.G + un.scan;
-    LaneTables staged;
-    staged.fetch(R, job);
+    lane_tables_bring(R, job, un, tabs);
     const uint32_t slot = lane_table_slot(R, job, key);
     LaneUnit U;
     U.ok = false;
     if (mine && slot < (uint32_t)kLaneTabs) lane_unit_setup(R, un, clean32, &U);
-    staged.put(job, tabs);
+    lane_tables_have();
     if (!U.ok) return;
     U.tab = reinterpret_cast<const LaneTab*>(&tabs[slot][0]);
     uint64_t* recs = R.masks + R.mask_off[key];
@@ -936,70 +997,57 @@ __global__ void __launch_bounds__(kEntropyLanes) k_ac_refine_lanes(DevRecord R, 
 // per wavefront, whatever images they belong to -- every lane builds its own small tables.  The checks and ranges are
 // those of unit_setup.
 PCR_D __attribute__((always_inline)) void lane_dc_unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __restrict__ clean32, uint32_t to_planes, LaneDcUnit* U) {
-    U->ok = false;
-    const ImgDesc* img = &R.img[un.img];
-    if (R.status[un.img] != kOk || un.scan >= img->nscans) return;
-    const size_t ig = (size_t)un.img * R.G + un.scan;
-    const ScanDesc* sd = &R.scan[ig];
-    if (!sd->valid || sd->Ss != 0 || sd->Ah != 0 || !img->progressive || sd->ns < 1 || sd->ns > kMaxComp) return;
-    const uint32_t sb = R.slot_base[ig], sc = R.slot_cnt[ig];
-    const uint32_t ri = sd->ri, mcus = sd->mcus;
-    U->pred0 = U->pred1 = U->pred2 = 0;
-    if (ri == 0 && sc > 1) {
-        const uint32_t stride = entry_stride(ld_le16(R.rec + hdr_ecount_pos(R.n, R.G, un.scan, un.img)));
-        const uint8_t* e = R.rec + R.ent_off[ig] + (size_t)stride * un.interval;
-        const uint32_t total = R.ivl_start[sb + sc] * 8;
-        uint32_t m0 = 0, b0 = 0, m1 = mcus, b1 = total;
-        if (un.interval > 0) {
-            const uint8_t* p = e - stride;
-            m0 = lane_le32(p); b0 = lane_le32(p + 4);
-            if (stride == kEntryBytes) { U->pred0 = (int)(int16_t)ld_le16(p + 8); U->pred1 = (int)(int16_t)ld_le16(p + 10); U->pred2 = (int)(int16_t)ld_le16(p + 12); }
-        }
-        if (un.interval + 1 < sc) { m1 = lane_le32(e); b1 = lane_le32(e + 4); }
-        if (!(m0 < m1 && m1 <= mcus && b0 <= b1 && b1 <= total)) { R.status[un.img] = kEFormat; return; }
-        U->mcu0 = m0; U->mcu1 = m1; U->bit0 = b0; U->bit1 = b1;
-    } else {
-        const uint32_t b0 = R.ivl_start[sb + un.interval], b1 = R.ivl_start[sb + un.interval + 1];
-        U->mcu0 = ri ? un.interval * ri : 0;
-        U->mcu1 = ri ? (U->mcu0 + ri < mcus ? U->mcu0 + ri : mcus) : mcus;
-        if (U->mcu0 >= mcus) return;
-        U->bit0 = b0 * 8; U->bit1 = (b1 > b0 ? b1 : b0) * 8;
-    }
-    U->mcu_w = sd->mcu_w;
-    if (U->mcu_w == 0) return;
-    U->ns = sd->ns; U->Al = sd->Al;
-    const uint32_t nb0 = (uint32_t)img->bw[0] * img->bh[0], nb1 = img->nc > 1 ? (uint32_t)img->bw[1] * img->bh[1] : 0u, nb2 = img->nc > 2 ? (uint32_t)img->bw[2] * img->bh[2] : 0u;
-    const bool one = sd->ns == 1;                               // a scan of one component goes block by block
+    LaneUnitInfo I;
+    lane_unit_info(R, un, &I);
+    U->ok = I.ok && I.Ss == 0 && I.Ah == 0 && PCR_FIELD(I.img, ImgDesc, progressive) != 0 && I.ns >= 1 && I.ns <= (uint32_t)kMaxComp;
+    U->pred0 = (int)(int16_t)I.preds; U->pred1 = (int)(int16_t)(I.preds >> 16); U->pred2 = (int)(int16_t)(I.preds >> 32);
+    U->mcu0 = I.m0; U->mcu1 = I.m1; U->bit0 = I.b0; U->bit1 = I.b1; U->mcu_w = I.mcu_w;
+    U->ns = I.ns; U->Al = I.Al;
+    const bool one = I.ns == 1;                                 // a scan of one component goes block by block
     // scan component j is component c of the image (sampling factors are 1 or 2: the parser refuses anything else)
-    auto component = [&](int j, uint32_t* hs, uint32_t* vs, uint32_t* bw, uint32_t* pblk, const uint8_t** def) {
-        const int c = j < sd->ns ? (int)sd->comp[j] : 0;
-        *hs = one ? 1u : (uint32_t)img->hs[c]; *vs = one ? 1u : (uint32_t)img->vs[c]; *bw = img->bw[c];
-        *pblk = c == 0 ? 0u : (c == 1 ? nb0 : nb0 + nb1);
-        *def = R.rec + sd->dc_off[j < sd->ns ? j : 0];
+    auto component = [&](uint32_t j, uint32_t comp, uint32_t dc_off, uint32_t* hs, uint32_t* vs, uint32_t* bw, uint32_t* pblk, const uint8_t** def) {
+        const uint32_t c = j < I.ns ? comp : 0u;
+        *hs = one ? 1u : I.hs(c); *vs = one ? 1u : I.vs(c); *bw = I.bw(c);
+        *pblk = I.before(c);
+        *def = R.rec + (j < I.ns ? dc_off : PCR_MEMBER(I.sd, ScanDesc, dc_off, 0));
     };
-    component(0, &U->hs0, &U->vs0, &U->bw0, &U->pblk0, &U->def0);
-    component(1, &U->hs1, &U->vs1, &U->bw1, &U->pblk1, &U->def1);
-    component(2, &U->hs2, &U->vs2, &U->bw2, &U->pblk2, &U->def2);
-    U->nblocks = nb0 + nb1 + nb2;
-    U->dense = R.dc + (R.coef_off[un.img] >> 6);
-    U->planes = to_planes ? R.coef + R.coef_off[un.img] : nullptr;
-    U->words = clean32 + (clean_base(sd->data_off) >> 2);
-    U->ok = true;
+    component(0, PCR_MEMBER(I.sd, ScanDesc, comp, 0), PCR_MEMBER(I.sd, ScanDesc, dc_off, 0), &U->hs0, &U->vs0, &U->bw0, &U->pblk0, &U->def0);
+    component(1, PCR_MEMBER(I.sd, ScanDesc, comp, 1), PCR_MEMBER(I.sd, ScanDesc, dc_off, 1), &U->hs1, &U->vs1, &U->bw1, &U->pblk1, &U->def1);
+    component(2, PCR_MEMBER(I.sd, ScanDesc, comp, 2), PCR_MEMBER(I.sd, ScanDesc, dc_off, 2), &U->hs2, &U->vs2, &U->bw2, &U->pblk2, &U->def2);
+    U->end = R.rec + R.nbytes;
+    U->nblocks = I.nblk(0) + I.nblk(1) + I.nblk(2);
+    U->dense = R.dc + (I.coef0 >> 6);
+    U->planes = to_planes ? R.coef + I.coef0 : nullptr;
+    U->words = clean32 + (clean_base(PCR_FIELD(I.sd, ScanDesc, data_off)) >> 2);
 }
 
-__global__ void __launch_bounds__(kEntropyLanes) k_dc_first_lanes(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
-        const uint32_t* __restrict__ clean32, uint32_t to_planes) {
-    __shared__ LaneRing rings;
-    __shared__ LaneDcTabs tabs;
+PCR_D __attribute__((always_inline)) void dc_first_units(const DevRecord& R, const Unit* __restrict__ units, uint32_t nunits, uint32_t block,
+        const uint32_t* __restrict__ clean32, uint32_t to_planes, LaneRing* rings) {
     short_kernel_priority();
-    const uint32_t t = threadIdx.x, u = blockIdx.x * kEntropyLanes + t;
+    const uint32_t t = threadIdx.x, u = block * kEntropyLanes + t;
+    const Unit un = units[u < nunits ? u : 0u];
     LaneDcUnit U;
     U.ok = false;
-    Unit un = units[u < nunits ? u : 0u];
     if (u < nunits) lane_dc_unit_setup(R, un, clean32, to_planes, &U);
     if (!U.ok) return;
-    const int rc = lane_decode_dc_first(U, &rings, &tabs, t);
+    const int rc = lane_decode_dc_first(U, rings, t);
     if (rc != kOk) R.status[un.img] = rc;
+}
+__global__ void __launch_bounds__(kEntropyLanes, 4) k_dc_first_lanes(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
+        const uint32_t* __restrict__ clean32, uint32_t to_planes) {
+    __shared__ LaneRing rings;
+    dc_first_units(R, units, nunits, blockIdx.x, clean32, to_planes, &rings);
+}
+// DC and AC first scans of one level in one launch: the first dc_blocks workgroups are k_dc_first_lanes', the others
+// k_ac_first_lanes'.  Both take as long as their longest unit and leave most of the chip idle meanwhile; one behind the
+// other they took the sum: 1024 x 256 x 256 at scan group 5 62 us for the DC scans by wavefronts + 82, 1024 photographs
+// at 2 136 + 108.  (Kept on their own where stages are timed, and for calls with only one of the two.)
+__global__ void __launch_bounds__(kEntropyLanes, 4) k_first_lanes(DevRecord R, const Unit* __restrict__ dc_units, uint32_t n_dc, uint32_t dc_blocks,
+        const Unit* __restrict__ ac_units, const LaneJob* __restrict__ jobs, const uint32_t* __restrict__ clean32, uint32_t to_planes) {
+    __shared__ uint4 tabs[kLaneTabs][kLaneTabPieces];
+    __shared__ LaneRing rings;
+    if (blockIdx.x < dc_blocks) dc_first_units(R, dc_units, n_dc, blockIdx.x, clean32, to_planes, &rings);
+    else ac_first_job(R, ac_units, jobs[blockIdx.x - dc_blocks], clean32, tabs, &rings);
 }
 
 // Sequential (baseline) scans: the DC and AC tables of every scan component, once per distinct table.  done (may be null): the
@@ -1499,9 +1547,6 @@ PCR_D void rgb_words(const float y[4], const float u[4], const float v[4], uint3
 // a value per component, picked by a per-lane component number out of three wave-uniform ones
 PCR_D uint32_t pick3(uint32_t c, uint32_t a0, uint32_t a1, uint32_t a2) { return c == 0 ? a0 : (c == 1 ? a1 : a2); }
 
-// What earlier kernels wrote and this one only reads, at a wave-uniform address: a scalar load, which arrives in scalar
-// registers and does not stand in the way of the loads behind it.
-template <class T> PCR_D T load_const(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
 // an image's descriptor through a wave-uniform pointer, as dwords
 PCR_D void load_desc(const ImgDesc* ip, ImgDesc* D) {
     const __attribute__((address_space(4))) uint32_t* src = (const __attribute__((address_space(4))) uint32_t*)ip;
@@ -1509,10 +1554,6 @@ PCR_D void load_desc(const ImgDesc* ip, ImgDesc* D) {
 #pragma unroll
     for (uint32_t e = 0; e < sizeof(ImgDesc) / 4; e++) dst[e] = src[e];
 }
-// Where this stands its arguments have been loaded: loads that depend on nothing but the image's number are then under
-// way together.  (The compiler moves each to its first use, behind the branches, and waits for one after the other.)
-PCR_D void wanted_now(uint32_t a) { asm volatile("" :: "s"(a)); }
-PCR_D void wanted_now(uint64_t a) { asm volatile("" :: "s"(a)); }
 PCR_D void wanted_now(const ImgDesc& D) {
     const uint32_t* w = reinterpret_cast<const uint32_t*>(&D);
 #pragma unroll

@@ -294,29 +294,26 @@ PCR_HD int lane_decode_ac_first(const LaneUnit& U, LaneRing* rings, uint32_t lan
 // ---------------------------------------------------------------------------------------
 // DC first scan of one unit (interleaved: up to three components, their blocks MCU by MCU; or one component, block by
 // block over the blocks that cover its samples).  A unit's lanes belong to different images, each with its own two or
-// three small tables, so the tables do not go through the job mechanism of the AC kernels: every lane makes its own,
-// in LDS, in a form that needs no look-up memory worth the name -- the first sixteen codes of the table (more are no
-// DC categories; the wavefront decoders drop them the same way) in code order, each as its left-aligned 16-bit value.
-// Canonical codes in that form are increasing, so the code at the head of a 16-bit window w is the last one that is
-// <= w: the lane counts them.  One symbol -- one block -- per trip.
+// three small tables, so the tables do not go through the job mechanism of the AC kernels: every lane keeps its own in
+// registers, in a form that needs no look-up -- the first sixteen codes of the table (more are no DC categories; the
+// wavefront decoders drop them the same way) in code order, each as its left-aligned 16-bit value.  Canonical codes in
+// that form are increasing, so the code at the head of a 16-bit window w is the last one that is <= w: the lane counts
+// them, two to an instruction.  One symbol -- one block -- per trip.
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t kLaneDcCodes = 16;
-struct LaneDcTab {                                            // 80 bytes: read as 16-byte vectors, and five of them apart keeps 8 lanes on 32 banks
-    uint16_t lim[kLaneDcCodes];                               // left-aligned code of entry i; 0xFFFF where there is none (no code is all ones)
-    uint32_t len[2], cat[2];                                  // 4 bits per entry: code length - 1, category (entry i: bits 4 (i & 7) of word i >> 3)
-    uint32_t n;                                               // entries
-    uint32_t end;                                             // first left-aligned value that is no code of the (truncated) table
-    uint32_t pad[6];
+struct LaneDcCodes {
+    uint32_t lim[kLaneDcCodes / 2];                           // left-aligned code of entry i: half i & 1 of word i >> 1; 0xFFFF where there is none (no code is all ones)
+    uint64_t len, cat;                                        // 4 bits per entry: code length - 1, category
+    uint32_t end;                                             // first left-aligned value that is no code of the (truncated) table; 0xFFFF at most
 };
-static_assert(sizeof(LaneDcTab) == 80, "LaneDcTab layout");
-struct LaneDcTabs { LaneDcTab t[kMaxComp][64]; };            // [scan component][lane]
+// A definition as it is read: sixteen counts and the first sixteen symbols.
+struct LaneDcDef { uint32_t w[8]; uint32_t ahead; };         // (the first `ahead` bytes are not its own)
 
 struct LaneDcUnit {
     const uint32_t* words; uint32_t bit0, bit1;               // as LaneUnit
     uint32_t mcu0, mcu1, mcu_w;
     uint32_t ns;                                              // components of the scan
-    // per scan component 0, 1, 2 (single members, no arrays: a member picked by a run-time component number must be a
-    // select between registers, and from an array the compiler makes it a load from a selected address in scratch memory):
+    // per scan component 0, 1, 2:
     uint32_t hs0, hs1, hs2, vs0, vs1, vs2;                    // blocks per MCU (1 x 1 if ns == 1)
     uint32_t bw0, bw1, bw2;                                   // blocks per row of the component's plane
     uint32_t pblk0, pblk1, pblk2;                             // first block of its plane in the image's coefficient buffer
@@ -326,111 +323,153 @@ struct LaneDcUnit {
     int16_t* planes;                                          // the image's coefficient buffer (element 0 of every block), or null
     uint32_t nblocks;                                         // blocks of that buffer
     const uint8_t *def0, *def1, *def2;                        // each scan component's table definition: 16 counts, then the symbols in code order
+    const uint8_t* end;                                       // end of the bytes the definitions lie in
     bool ok;
 };
 
-// The table of a definition (call per lane; t is the lane's own).
-PCR_HD __attribute__((always_inline)) void lane_dctab_build(LaneDcTab* t, const uint8_t* bits_vals) {
-    for (uint32_t i = 0; i < kLaneDcCodes; i++) t->lim[i] = 0xFFFFu;
-    uint32_t code = 0, k = 0, n = 0, end = 0, len0 = 0, len1 = 0, cat0 = 0, cat1 = 0;
-    for (uint32_t L = 1; L <= 16; L++) {
-        const uint32_t cnt = bits_vals[L - 1];
-        for (uint32_t j = 0; j < cnt; j++) {
-            const uint32_t left = code << (16 - L);
-            if (k < kLaneDcCodes && left < 0xFFFFu) {
-                t->lim[k] = (uint16_t)left;
-                const uint32_t sh = 4u * (k & 7u), c = bits_vals[16 + k] & 15u;
-                if (k < 8) { len0 |= (L - 1u) << sh; cat0 |= c << sh; } else { len1 |= (L - 1u) << sh; cat1 |= c << sh; }
-                end = left + (1u << (16 - L));
-                n = k + 1;
-            }
-            code++; k++;
-        }
-        code <<= 1;
+// The definition at d (call per lane, for all tables before any is used: the loads are then under way together).  The 32
+// bytes are read whatever the definition's length, at the very end of the record (end) from as much ahead of it as is
+// missing behind it; a record has more than 32 bytes.
+PCR_HD void lane_dc_def(LaneDcDef* D, const uint8_t* d, const uint8_t* end) {
+    const uint64_t behind = (uint64_t)(end - d);
+    uint32_t ahead = behind >= 32 ? 0u : 32u - (uint32_t)behind;
+    struct __attribute__((packed, aligned(1))) Loose { uint4 a, b; };
+    const Loose v = *reinterpret_cast<const Loose*>(d - ahead);
+    D->w[0] = v.a.x; D->w[1] = v.a.y; D->w[2] = v.a.z; D->w[3] = v.a.w; D->w[4] = v.b.x; D->w[5] = v.b.y; D->w[6] = v.b.z; D->w[7] = v.b.w;
+    D->ahead = ahead;
+}
+
+// The table of a definition.  Sixteen entries are pushed in at the top of each member and the definition's bytes taken from
+// the bottom of its words, so that no register is indexed.
+PCR_HD void lane_dc_codes(LaneDcCodes* T, LaneDcDef D) {
+    auto down = [](uint32_t* w, int n) {                      // n words, one byte down
+        for (int q = 0; q + 1 < n; q++) w[q] = (w[q] >> 8) | (w[q + 1] << 24);
+        w[n - 1] >>= 8;
+    };
+    while (PCR_RARELY(D.ahead != 0)) if (D.ahead != 0) { down(D.w, 8); D.ahead--; }
+    uint32_t L = 0, code = 0, rem = 0, end = 0;
+    uint64_t len = 0, cat = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kLaneDcCodes / 2; q++) T->lim[q] = 0;
+#pragma unroll 1
+    for (uint32_t i = 0; i < kLaneDcCodes; i++) {
+#pragma unroll 1
+        while (rem == 0 && L < 16) { L++; code <<= 1; rem = D.w[0] & 255u; down(D.w, 4); }
+        const uint32_t left = code << (16u - L);
+        const bool is = rem != 0 && left < 0xFFFFu;
+#pragma unroll
+        for (uint32_t q = 0; q + 1 < kLaneDcCodes / 2; q++) T->lim[q] = (T->lim[q] >> 16) | (T->lim[q + 1] << 16);
+        T->lim[kLaneDcCodes / 2 - 1] = (T->lim[kLaneDcCodes / 2 - 1] >> 16) | (is ? left << 16 : 0xFFFF0000u);
+        len = (len >> 4) | (uint64_t)((L - 1u) & 15u) << 60; cat = (cat >> 4) | (uint64_t)(D.w[4] & 15u) << 60;
+        down(D.w + 4, 4);
+        end = is ? left + (1u << (16u - L)) : end;
+        code += rem != 0 ? 1u : 0u; rem -= rem != 0 ? 1u : 0u;
     }
-    t->len[0] = len0; t->len[1] = len1; t->cat[0] = cat0; t->cat[1] = cat1; t->n = n;
-    t->end = end > 0x10000u ? 0x10000u : end;
+    T->len = len; T->cat = cat; T->end = end < 0xFFFFu ? end : 0xFFFFu;
 }
 
-// v, as a value in a vector register whose origin the compiler does not look behind (see lane_decode_dc_first)
-PCR_HD uint32_t lane_value(uint32_t v) {
+// entries above w (of sixteen)
+PCR_HD uint32_t lane_dc_above(const LaneDcCodes& T, uint32_t w) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm("" : "+v"(v));
+    // (written out: the compiler makes sixteen comparisons and selects of it)
+    const uint32_t ww = w | (w << 16);
+    auto above = [&](uint32_t q) {
+        uint32_t r;
+        asm("v_pk_sub_u16 %0, %1, %2 clamp\n\tv_pk_min_u16 %0, %0, 1 op_sel_hi:[1,0]" : "=v"(r) : "v"(T.lim[q]), "v"(ww));
+        return r;
+    };
+    const uint32_t a = ((above(0) + above(1)) + (above(2) + above(3))) + ((above(4) + above(5)) + (above(6) + above(7)));    // (halves below 9: no carry)
+    return (a & 0xFFFFu) + (a >> 16);
+#else
+    uint32_t n = 0;
+    for (uint32_t q = 0; q < 8; q++) n += ((T.lim[q] & 0xFFFFu) > w ? 1u : 0u) + ((T.lim[q] >> 16) > w ? 1u : 0u);
+    return n;
 #endif
-    return v;
 }
 
-PCR_HD __attribute__((always_inline)) int lane_decode_dc_first(const LaneDcUnit& U, LaneRing* rings, LaneDcTabs* tabs, uint32_t lane) {
-    // The per-component members as plain values: picked by a run-time component number straight from U, the compiler
-    // picks the member's address instead and loads from it, which puts the whole of U into scratch memory.
-    const uint32_t hs0 = lane_value(U.hs0), hs1 = lane_value(U.hs1), hs2 = lane_value(U.hs2);
-    const uint32_t vs0 = lane_value(U.vs0), vs1 = lane_value(U.vs1), vs2 = lane_value(U.vs2);
-    const uint32_t bw0 = lane_value(U.bw0), bw1 = lane_value(U.bw1), bw2 = lane_value(U.bw2);
-    const uint32_t pb0 = lane_value(U.pblk0), pb1 = lane_value(U.pblk1), pb2 = lane_value(U.pblk2);
+// one symbol: the DC difference at the head of the stream; `bad` gets its sign where there is no code, or no bits
+PCR_HD int lane_dc_symbol(LaneStream* st, const LaneDcCodes& T, uint32_t* bad) {
+    const uint32_t win = st->window(), w16 = win >> 16;
+    const uint32_t sh = 4u * (15u - lane_dc_above(T, w16)) & 63u;
+    const uint32_t len = ((uint32_t)(T.len >> sh) & 15u) + 1u, s = (uint32_t)(T.cat >> sh) & 15u;
+    st->consume(len + s);
+    const uint32_t x = win << len, extra = bit_range(x, 32u - s, s), neg = ~sign_mask(x) & ((1u << s) - 1u);
+    *bad |= (T.end - 1u - w16) | st->beyond();
+    return (int)(extra - neg);
+}
+
+// lanes whose value equals that of the first lane still in the branch
+PCR_HD bool as_first(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return v == (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+#else
+    (void)v;
+    return true;
+#endif
+}
+PCR_HD uint32_t of_first(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+#else
+    return v;
+#endif
+}
+
+// Bound by the latency of one symbol after another: about 330 cycles each, of 46 instructions.  1024 photographs (entry
+// points every 64 MCUs) take 55 us; 100 before, when the tables lay in LDS, were read definition byte by byte, and every
+// symbol picked its component's members with selects (1250 cycles, 110 instructions).
+// The lanes of a wavefront go MCU by MCU, block by block, in step, so which component a block belongs to is the same for
+// all of them and costs nothing: lanes whose MCUs look different (another sub-sampling, in another image) go after each
+// other.
+PCR_HD __attribute__((always_inline)) int lane_decode_dc_first(const LaneDcUnit& U, LaneRing* rings, uint32_t lane) {
+    LaneDcDef d0, d1, d2;
+    lane_dc_def(&d0, U.def0, U.end); lane_dc_def(&d1, U.def1, U.end); lane_dc_def(&d2, U.def2, U.end);
     LaneStream st;
     st.init(U.words, U.bit0, U.bit1, rings, lane);
-    static_assert(kMaxComp == 3, "the components are spelled out (an array indexed in a loop ends up in scratch memory)");
-    lane_dctab_build(&tabs->t[0][lane], U.def0);
-    if (U.ns > 1) lane_dctab_build(&tabs->t[1][lane], U.def1);
-    if (U.ns > 2) lane_dctab_build(&tabs->t[2][lane], U.def2);
-    const uint32_t n0 = hs0 * vs0, n01 = n0 + (U.ns > 1 ? hs1 * vs1 : 0u);
-    const uint32_t bpm = n01 + (U.ns > 2 ? hs2 * vs2 : 0u);
+    LaneDcCodes t0, t1, t2;
+    lane_dc_codes(&t0, d0); lane_dc_codes(&t1, d1); lane_dc_codes(&t2, d2);
     uint32_t left = U.mcu1 - U.mcu0;                          // MCUs not finished yet
-    uint32_t my = U.mcu0 / U.mcu_w, mx = U.mcu0 - my * U.mcu_w, j = 0;
+    const uint32_t my = U.mcu0 / U.mcu_w;
+    uint32_t in_row = U.mcu_w - (U.mcu0 - my * U.mcu_w);      // MCUs left in the row (the current one included)
+    // every block lies inside the buffer if those of the last row do
+    const uint32_t last_row = (U.mcu1 - 1u) / U.mcu_w;
+    auto inside = [&](uint32_t pblk, uint32_t hs, uint32_t vs, uint32_t bw) { return (uint64_t)pblk + ((uint64_t)last_row * vs + vs - 1u) * bw + (uint64_t)U.mcu_w * hs <= U.nblocks; };
+    if (U.mcu0 >= U.mcu1 || !inside(U.pblk0, U.hs0, U.vs0, U.bw0) || !inside(U.pblk1, U.hs1, U.vs1, U.bw1) || !inside(U.pblk2, U.hs2, U.vs2, U.bw2)) return kEFormat;
+    const uint32_t mx = U.mcu0 - my * U.mcu_w;
+    uint32_t b0 = U.pblk0 + my * U.vs0 * U.bw0 + mx * U.hs0, b1 = U.pblk1 + my * U.vs1 * U.bw1 + mx * U.hs1, b2 = U.pblk2 + my * U.vs2 * U.bw2 + mx * U.hs2;   // the MCU's first block of each component
+    const uint32_t skip0 = U.vs0 * U.bw0 - U.mcu_w * U.hs0, skip1 = U.vs1 * U.bw1 - U.mcu_w * U.hs1, skip2 = U.vs2 * U.bw2 - U.mcu_w * U.hs2;
+    const uint32_t shape = U.ns | U.hs0 << 4 | U.vs0 << 8 | U.hs1 << 12 | U.vs1 << 16 | U.hs2 << 20 | U.vs2 << 24;
     int pred0 = U.pred0, pred1 = U.pred1, pred2 = U.pred2;
-    uint32_t bad = 0, low = st.low_water(1);
-    while (left != 0) {
-        if (PCR_RARELY((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(1); }
-        const uint32_t win = st.window(), w16 = win >> 16;
-        // the block: component c of the scan, block (by, bx) of its part of the MCU (sampling factors are 1 or 2)
-        const uint32_t c = (j >= n0 ? 1u : 0u) + (j >= n01 ? 1u : 0u);
-        const uint32_t jj = j - (c == 0 ? 0u : (c == 1 ? n0 : n01));
-        const uint32_t hs = c == 0 ? hs0 : (c == 1 ? hs1 : hs2), vs = c == 0 ? vs0 : (c == 1 ? vs1 : vs2);
-        const uint32_t bw = c == 0 ? bw0 : (c == 1 ? bw1 : bw2), p0 = c == 0 ? pb0 : (c == 1 ? pb1 : pb2);
-        const uint32_t bx = jj & (hs - 1u), by = jj >> (hs - 1u);
-        const uint32_t blk = p0 + (my * vs + by) * bw + mx * hs + bx;
-        // the code: the last of the table's that is not above the window
-        const LaneDcTab* T = &tabs->t[c][lane];
-        // (three 16-byte reads that do not wait for the window: limits, limits, lengths and categories; then no further
-        // trip to LDS stands between the window and the symbol)
-        const uint4 la = *reinterpret_cast<const uint4*>(&T->lim[0]), lb = *reinterpret_cast<const uint4*>(&T->lim[8]);
-        const uint4 lc = *reinterpret_cast<const uint4*>(&T->len[0]);
-        const uint2 ne = *reinterpret_cast<const uint2*>(&T->n);
-        const uint32_t lw[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
-        uint32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0;              // (four sums: no chain of sixteen additions)
-#pragma unroll
-        for (int q = 0; q < 8; q += 2) {
-            c0 += (lw[q] & 0xFFFFu) <= w16 ? 1u : 0u; c1 += (lw[q] >> 16) <= w16 ? 1u : 0u;
-            c2 += (lw[q + 1] & 0xFFFFu) <= w16 ? 1u : 0u; c3 += (lw[q + 1] >> 16) <= w16 ? 1u : 0u;
+    uint32_t bad = 0;
+    bool done = false;
+    while (!done) {
+        if (!as_first(shape)) continue;                       // (another turn)
+        const uint32_t sh = of_first(shape), ns = sh & 15u;
+        uint32_t low = st.low_water(1);                       // (a symbol takes one word at most)
+        auto blocks = [&](const LaneDcCodes& T, uint32_t hs, uint32_t vs, uint32_t bw, uint32_t b, int* pred) {
+            for (uint32_t y = 0; y < vs; y++)
+                for (uint32_t x = 0; x < hs; x++) {
+                    if (PCR_RARELY((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(1); }
+                    *pred += lane_dc_symbol(&st, T, &bad);
+                    const int16_t v = (int16_t)((uint32_t)*pred << U.Al);
+                    const uint32_t blk = b + y * bw + x;
+                    U.dense[blk] = v;
+                    if (U.planes) U.planes[(size_t)blk * 64] = v;
+                }
+        };
+        while (left != 0) {
+            blocks(t0, (sh >> 4) & 15u, (sh >> 8) & 15u, U.bw0, b0, &pred0);
+            if (ns > 1) blocks(t1, (sh >> 12) & 15u, (sh >> 16) & 15u, U.bw1, b1, &pred1);
+            if (ns > 2) blocks(t2, (sh >> 20) & 15u, (sh >> 24) & 15u, U.bw2, b2, &pred2);
+            left--;
+            if ((int)bad < 0) left = 0;                       // stop at the first damaged MCU
+            b0 += U.hs0; b1 += U.hs1; b2 += U.hs2; in_row--;
+            const uint32_t wrap = sign_mask(in_row - 1u);
+            b0 += wrap & skip0; b1 += wrap & skip1; b2 += wrap & skip2; in_row += wrap & U.mcu_w;
         }
-        const uint32_t cnt = (c0 + c1) + (c2 + c3);           // codes at or below the window: the last of them is the one
-        const uint32_t idx = (cnt - 1u) & 15u, sh = 4u * (idx & 7u);
-        const bool code_ok = cnt != 0 && cnt <= ne.x && w16 < ne.y;
-        const uint32_t len = code_ok ? (((idx < 8 ? lc.x : lc.y) >> sh) & 15u) + 1u : 1u, s = code_ok ? ((idx < 8 ? lc.z : lc.w) >> sh) & 15u : 0u;
-        const uint32_t extra = ((win << len) >> 1) >> (31u - s);
-        const int diff = extend(extra, (int)s);
-        st.consume(len + s);
-        bad |= code_ok ? 0u : 1u;
-        bad |= st.beyond() >> 31;                             // never walk beyond the unit's data
-        int pred = c == 0 ? pred0 : (c == 1 ? pred1 : pred2);
-        pred += diff;
-        pred0 = c == 0 ? pred : pred0; pred1 = c == 1 ? pred : pred1; pred2 = c == 2 ? pred : pred2;
-        if (!bad && blk < U.nblocks) {
-            const int16_t v = (int16_t)(pred * (1 << U.Al));
-            U.dense[blk] = v;
-            if (U.planes) U.planes[(size_t)blk * 64] = v;
-        }
-        // on to the next block, MCU, row of MCUs
-        j++;
-        const bool mcu_done = j == bpm;
-        j = mcu_done ? 0u : j;
-        mx += mcu_done ? 1u : 0u;
-        const bool row_done = mx == U.mcu_w;
-        mx = row_done ? 0u : mx; my += row_done ? 1u : 0u;
-        left -= mcu_done ? 1u : 0u;
-        if (bad) left = 0;                                    // stop at the first damaged block
+        done = true;
     }
-    return bad ? kEFormat : kOk;
+    return (int)bad < 0 ? kEFormat : kOk;
 }
 
 // ---------------------------------------------------------------------------------------

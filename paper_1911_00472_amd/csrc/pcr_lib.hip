@@ -507,14 +507,15 @@ bool lanes_pay(const pcr_record* r, const LevelList& l) {
     return l.n >= least && l.n >= 32u * l.n_jobs;            // (jobs half full at least: few tables per 64 units)
 }
 
-// The same question for a launch of DC first scans.  A lane decodes a DC symbol with a fifth of the instructions a
-// wavefront spends on it, but a launch of lanes takes as long as one unit, however few there are: it pays when the
-// wavefront decoders of several records would queue for the scalar units.
-constexpr uint32_t kDcLanesMinUnits = 4096;
+// The same question for a launch of DC first scans by themselves (beside AC first scans by lanes they cost nothing, see
+// with_ac).  A lane decodes a DC symbol with a fifth of the instructions a wavefront spends on it, but a launch of lanes
+// takes as long as one unit, however few there are.  Measured, scan group 1 of one record, an entry every 64 MCUs, us a call by
+// lanes / by wavefronts: 256 x 256 in 4:2:0, 1024 units 88 / 73, 2048 98 / 97, 4096 118 / 138; 400 x 400 in 4:2:0, 1280
+// units 91 / 80, 2560 101 / 104, 10240 188 / 269; 600 x 450 in 4:4:4, 1072 units 69 / 64, 4288 76 / 93, 17152 105 / 205.
+constexpr uint32_t kDcLanesMinUnits = 2048;
 bool dc_lanes_pay(const pcr_record* r, const LevelList& l) {
     if (r->lane_mode < 0) return false;
-    if (r->lane_mode > 0) return l.n >= (uint32_t)kEntropyLanes;
-    return g_open_records.load(std::memory_order_relaxed) > 1 && l.n >= kDcLanesMinUnits;
+    return l.n >= (r->lane_mode > 0 ? (uint32_t)kEntropyLanes : kDcLanesMinUnits);
 }
 
 // Many lanes per long sequential scan, or one wavefront?  k_sequential_split has room for one scan per compute unit (150 KB
@@ -600,14 +601,22 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     r->last_lane_launches = r->last_wave_launches = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
-        if (l.kind == kDcFirst) {
-            by_lanes[li] = dc_lanes_pay(r, l) ? 1 : 0;
-            if (!by_lanes[li]) dc_tables = true;
-        } else if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
+        if (l.kind == kDcFirst) by_lanes[li] = dc_lanes_pay(r, l) ? 1 : 0;
+        else if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
         else {
             by_lanes[li] = lanes_pay(r, l) ? 1 : 0;
             if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
         }
+    }
+    // Beside AC first scans that go to the lanes the DC first scans of the same level go there too, in the same launch.
+    auto with_ac = [&](size_t li) {
+        return plan->levels[li].kind == kDcFirst && li + 1 < plan->levels.size() && plan->levels[li + 1].kind == kAcFirst && plan->levels[li + 1].level == plan->levels[li].level &&
+               by_lanes[li + 1] != 0;
+    };
+    for (size_t li = 0; li < plan->levels.size(); li++) {
+        if (plan->levels[li].kind != kDcFirst) continue;
+        if (with_ac(li)) by_lanes[li] = 1;
+        if (!by_lanes[li]) dc_tables = true;
     }
     // Scans side by side where the AC scans are for the wavefront decoders (DC first scans may go to the lanes by themselves);
     // with stage timing on, whose intervals are those of single stages, one after the other.
@@ -657,7 +666,12 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         auto& l = plan->levels[li];
         if (side_by_side && l.chained && (l.kind != kDcFirst || dc_beside)) continue;
         const dim3 block(kEntropyLanes);
-        if (l.kind == kDcFirst) {
+        if (with_ac(li) && !r->timing) {                     // (timed, each stage has a launch, and an interval, of its own)
+            const auto& ac = plan->levels[++li];
+            const uint32_t dc_blocks = (l.n + kEntropyLanes - 1) / kEntropyLanes;
+            hipLaunchKernelGGL(k_first_lanes, dim3(dc_blocks + ac.n_jobs), block, 0, s, r->d, l.d_units, l.n, dc_blocks, ac.d_units, ac.d_jobs, c32, dc_to_planes ? 1u : 0u);
+        }
+        else if (l.kind == kDcFirst) {
             if (by_lanes[li]) hipLaunchKernelGGL(k_dc_first_lanes, dim3((l.n + kEntropyLanes - 1) / kEntropyLanes), block, 0, s, r->d, l.d_units, l.n, c32, dc_to_planes ? 1u : 0u);
             else waves(l);
             mark(r, PCR_STAGE_DC_FIRST, s);

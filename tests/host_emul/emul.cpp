@@ -135,7 +135,7 @@ extern "C" int emul_decode_record(const uint8_t* rec, size_t nbytes, int k, int6
                 rc = decode_sequential(&sw, ls, tb, &ssink);
             } else if (sd.Ss == 0 && by_lane && img.progressive && sd.Ah == 0) {
                 // the DC first scan with the lane decoder: the unit set up as k_dc_first_lanes sets it up
-                static LaneRing ring; static LaneDcTabs dtabs;
+                static LaneRing ring;
                 std::vector<int16_t> dense(coef.size() / 64 + 1, 0);
                 LaneDcUnit U;
                 U.words = reinterpret_cast<const uint32_t*>(clean.data());
@@ -153,8 +153,8 @@ extern "C" int emul_decode_record(const uint8_t* rec, size_t nbytes, int k, int6
                 U.def0 = defv[0]; U.def1 = defv[1]; U.def2 = defv[2];
                 U.pred0 = ls.pred[0]; U.pred1 = ls.pred[1]; U.pred2 = ls.pred[2];
                 U.dense = dense.data(); U.planes = coef.data(); U.nblocks = (uint32_t)(coef.size() / 64);
-                U.ok = true;
-                rc = lane_decode_dc_first(U, &ring, &dtabs, 0);
+                U.end = rec + nbytes; U.ok = true;
+                rc = lane_decode_dc_first(U, &ring, 0);
             } else if (sd.Ss == 0) {
                 std::vector<DcTab> dt(3);
                 for (int q = 0; q < sd.ns; q++) dctab_build(&dt[q], rec + sd.dc_off[q]);

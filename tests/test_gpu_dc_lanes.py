@@ -1,0 +1,56 @@
+"""DC first scans with a lane per unit where the lanes of a wavefront differ or run out: MCUs of every shape in one
+wavefront, units of one block, tables that end where the record ends (their 32 bytes are then read from ahead of them), sixteen
+codes and one; alone and in the launch of the AC first scans."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1911_00472_amd as pkg
+import pcrgen
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(rec, k, lanes=1):
+    with pkg.pcr_open(rec, 0) as r:
+        r.set_lane_decoders(lanes)
+        got, lay = r.decode_coefficients(k).cpu().numpy(), r.coef_layout()
+        pix, play = r.decode_batch(k).cpu().numpy(), r.output_layout()
+        for i in range(r.n):
+            want, p, _ = oracle.decode_record_image(rec, i, k)
+            assert np.array_equal(got[int(lay[i]):int(lay[i + 1])], want), (i, k)
+            assert np.abs(pix[int(play[i]):int(play[i + 1])].reshape(p.shape).astype(int) - p).max() <= 1, (i, k)
+
+
+@pytest.mark.parametrize("interval", [1, 5, 64])
+@pytest.mark.parametrize("k", [1, 2, 5])
+def test_every_shape_in_one_wavefront(interval, k):
+    files = []
+    for i in range(24):
+        hs, vs = ((2, 2), (1, 1), (2, 1), (1, 2))[i % 4]
+        w, h = 8 + 23 * (i % 5), 9 + 17 * (i % 7)
+        files.append(pcrgen.encode_pixels(pcrgen.synth(60 + i, i % 3, w, h, 3, 4.0 + i), hs, vs, 70 + i))
+    _check(pkg.record_write_indexed(files, None, interval), k)
+
+
+@pytest.mark.parametrize("count", [64, 65, 127, 200])
+def test_tables_at_the_very_end_of_the_record(count):
+    """Gray pictures of one block, the record cut behind its first scan group: the last table has fewer than 32 bytes."""
+    files = [pcrgen.encode_pixels(pcrgen.synth(9 + i, i % 3, 8, 8, 1, 2.0), 1, 1, 60) for i in range(count)]
+    rec = pcrgen.write_record(files)
+    ends = oracle.record_index(rec)[4]
+    _check(rec[:int(ends[0])], 1)
+
+
+def test_many_categories():
+    """Differences of every size: tables of all the codes a picture can need, beside tables of a single one."""
+    q = np.ones((2, 64), np.uint16)
+    rng = np.random.default_rng(3)
+    files = []
+    for i in range(80):
+        c = np.zeros((pcrgen.plane_blocks(64, 56, 1, 1, 1)[0], 64), np.int16)
+        if i % 3:
+            c[:, 0] = rng.choice([-1023, -512, -255, -128, -60, -30, -9, -4, -2, 0, 1, 3, 7, 15, 31, 100, 500, 1000], len(c))
+        files.append(pcrgen.encode_coefs(c.reshape(-1), 64, 56, 1, 1, 1, q, [(1, 0, 0, 0, 0, 0, 0, 0), (1, 0, 0, 0, 1, 63, 0, 0)], 0))
+    _check(pkg.record_write_indexed(files, None, 7), 1)
+    _check(pkg.record_write_indexed(files, None, 7), 2)
