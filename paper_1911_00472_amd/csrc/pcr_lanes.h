@@ -215,7 +215,9 @@ struct LaneLookup {
         }
         return e;
     }
-    // A code neither look-up resolves: limit[L - 8] is the first left-aligned 16-bit value that is not a code of length <= L,
+    // A decoder reads the entry of the next symbol as soon as it knows where that begins, does the rest of this symbol's work
+    // while LDS answers, and looks at it then; 0 is for by_limits.
+    // A code neither look-up knows (kCodeBad if there is no such code): limit[L - 8] is the first left-aligned 16-bit value that is not a code of length <= L,
     // so the length is 9 + the number of limits at or below the code.
     PCR_HD uint32_t by_limits(uint32_t c16) const {
         uint32_t L = 9, below = lim8;
@@ -259,8 +261,24 @@ PCR_HD int lane_decode_ac_first(const LaneUnit& U, LaneRing* rings, uint32_t lan
     uint32_t low = st.low_water(1);                           // (a trip takes one word at most)
     uint32_t next_win = st.window(), next_e = code.entry(next_win);
     while (left != 0) {
-        if (PCR_RARELY((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(1); }
-        const uint32_t win = next_win, e = code.resolve(next_e, win), nx = e & 15u;
+        const uint32_t win = next_win;
+        uint32_t e = next_e;
+        // What is rare -- a ring about to run dry, a code the look-up does not know, a row of blocks at its end -- is asked in
+        // one test: a comparison and the branch on it take a wavefront some 37 cycles, as much as four dependent instructions.
+        if (PCR_RARELY((int)((st.n - low) | (e - 1u) | (uint32_t)(in_row - 1)) < 0)) {
+            if (any_lane((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(1); }
+            if (e == 0) e = code.by_limits(win >> 16);
+            if (in_row <= 0) {                                // on to the next row of blocks
+                if (in_row <= -(int)mcu_w) {                  // an end-of-band run over more than one row
+                    uint32_t q = (uint32_t)((float)(-in_row) * rcp_w);      // rows passed, estimated: off by less than 1 + blocks / 2^22
+                    const uint32_t margin = 1u + ((uint32_t)-in_row >> 22);
+                    q = q > margin ? q - margin : 0;          // never too high; the loop adds what is missing
+                    in_row += (int)(q * mcu_w); base += q * row_skip;
+                }
+                while (in_row <= 0) { in_row += (int)mcu_w; base += row_skip; }
+            }
+        }
+        const uint32_t nx = e & 15u;
         st.consume(bit_range(e, 8, 5) + nx);
         next_win = st.window(); next_e = code.entry(next_win);
         const uint32_t x = win << ((e >> 8) & 31u), extra = bit_range(x, 32u - nx, nx);   // the appended bits: the value, or the length of an end-of-band run
@@ -278,15 +296,6 @@ PCR_HD int lane_decode_ac_first(const LaneUnit& U, LaneRing* rings, uint32_t lan
         adv = (adv < left ? adv : left) & done;
         k = by_mask(done, Ss, at + 1u);
         left -= adv; base += adv * 64; in_row -= (int)adv;
-        if (PCR_RARELY(in_row <= 0)) {                          // on to the next row of blocks
-            if (in_row <= -(int)mcu_w) {                      // an end-of-band run over more than one row
-                uint32_t q = (uint32_t)((float)(-in_row) * rcp_w);      // rows passed, estimated: off by less than 1 + blocks / 2^22
-                const uint32_t margin = 1u + ((uint32_t)-in_row >> 22);
-                q = q > margin ? q - margin : 0;              // never too high; the loop adds what is missing
-                in_row += (int)(q * mcu_w); base += q * row_skip;
-            }
-            while (in_row <= 0) { in_row += (int)mcu_w; base += row_skip; }
-        }
     }
     return (int)bad < 0 ? kEFormat : kOk;
 }
@@ -522,7 +531,7 @@ PCR_HD int lane_decode_ac_refine(const LaneUnit& U, uint64_t* recs, uint32_t nbl
     LaneLookup code;
     code.init(U.tab);
     const uint32_t Ss = U.Ss, band = U.Se - U.Ss + 1u, mcu_w = U.mcu_w, row_skip = U.bw - mcu_w;
-    const uint32_t to_place = 64u - band;                     // from the top of a word down to its bottom, once the whole band has passed
+    const uint32_t to_place = 63u - U.Se;                     // from the top of a word down to its bottom, once the whole band has passed
     uint32_t left = U.mcu1 - U.mcu0;                          // blocks of the unit not finished yet (the current one included)
     const uint32_t row0 = U.mcu0 / mcu_w, col0 = U.mcu0 - row0 * mcu_w;
     uint32_t blk = row0 * U.bw + col0, in_row = mcu_w - col0; // the current block; blocks left in its row (itself included)
@@ -648,7 +657,7 @@ PCR_HD int lane_decode_ac_refine(const LaneUnit& U, uint64_t* recs, uint32_t nbl
         newm = (newm >> on) | ((uint64_t)hit << 32); sgn = (sgn >> on) | ((uint64_t)(hit & x) << 32);
         rem -= on;
         if (rem == 0) {                                       // the block is complete
-            newm = (newm >> to_place) << Ss; sgn = (sgn >> to_place) << Ss;
+            newm >>= to_place; sgn >>= to_place;
             block_done();
         }
     }
