@@ -207,7 +207,9 @@ PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t l
     for (uint32_t e = lane; e < 128; e += 64) {
         const uint32_t c16 = lim8 + (e << sh2);
         const uint32_t f = c16 < 65536u ? canon_find<9, 16>(c, c16) : 0u;
-        t->lut2[e] = (uint16_t)((f && 16u - (f >> 8) >= sh2) ? code_entry(f >> 8, c->vals[f & 255u]) : 0u);
+        const uint32_t v = (f && 16u - (f >> 8) >= sh2) ? (f & 0xFF00u) | c->vals[f & 255u] : 0u;
+        t->lut2[e] = (uint16_t)(v ? code_entry(v >> 8, v & 255u) : 0u);
+        t->lutp[256 + e] = packed_entry(v, first);
     }
     if (lane < 9) t->limit[lane] = c->lim[8 + lane];
     if (lane < 8) t->valptr[lane] = (uint16_t)c->first[9 + lane];
@@ -894,6 +896,8 @@ PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab*
 #pragma unroll
     for (int q = 0; q < kMaxHist; q++) hp.p[q] = R.masks + uni((uint64_t)R.mask_off[(size_t)un.img * R.G + sd->hist[q < hp.n ? q : 0]]);
     hp.n = uni(hp.n);
+    hp.some = hp.n > 0 ? ~0ull : 0ull;
+    if (hp.n == 0) hp.p[0] = reinterpret_cast<const uint64_t*>(hp.coef);   // (16 bytes a block are read of its 128)
     wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, false, lane, false);
     return skim_ac_refine(&wr, L.ls, hp, R.masks + uni((uint64_t)R.mask_off[ig]), L.plane_elems[0] >> 6, gate);
 }
@@ -1196,7 +1200,7 @@ __global__ void __launch_bounds__(256) k_refine_blocks(DevRecord R, const Refine
     {
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.tabs[R.tab_idx[ig]]);
         uint32_t* dst = reinterpret_cast<uint32_t*>(&tab);
-        for (uint32_t e = threadIdx.x; e < sizeof(AcTab) / 4; e += 256) dst[e] = src[e];
+        for (uint32_t e = threadIdx.x; e < offsetof(AcTab, lutp) / 4; e += 256) dst[e] = src[e];   // (what ac_code reads)
     }
     __syncthreads();
     const uint32_t b = tile.chunk * 256 + threadIdx.x;
