@@ -712,7 +712,7 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
     ScanDesc first; memset(&first, 0, sizeof first);
     RegionWalk w;
     int rc = walk_region(src, 0, (uint32_t)src_bytes, 0, &w, &img);                   // up to the first scan header
-    if (rc == kOk) rc = resolve_scan(src, w, (uint32_t)src_bytes, w.dht, w.ri >= 0 ? (uint32_t)w.ri : 0u, &img, &first);
+    if (rc == kOk) rc = resolve_scan(w, (uint32_t)src_bytes, w.dht, w.ri >= 0 ? (uint32_t)w.ri : 0u, &img, &first);
     if (rc == kOk) rc = scan_history(&first, 0);
     for (int t = 0; t < 4; t++) { img.qoff[t] = w.qoff[t]; img.qprec[t] = w.qprec[t]; }
     if (rc != kOk) return rc;

@@ -78,7 +78,9 @@ PCR_HD int parse_record_header(const uint8_t* bytes, uint64_t nbytes, RecordHead
 // entropy-coded data) and fills the image and scan descriptors.
 //   rec      record bytes: a pointer, or on the device anything indexed by record offset (HeaderBytes)
 //   off,len  index tables [G][n] (absolute offsets / lengths of the regions)
-// Every read is bounds-checked against the region it belongs to.
+// Every read is bounds-checked against the region it belongs to.  Bytes are taken twenty-four at a time (bytes24), enough
+// for a segment's marker and length with what is looked at of its payload, at one place in the code: on the device
+// code that runs once costs what it takes to fetch it, and a chain of byte reads would be as slow.
 // The walk over a region's segments (walk_region) needs nothing from other regions; what a scan takes over from
 // earlier ones -- tables in force, restart interval, the scans it refines -- is put together afterwards
 // (resolve_scan, scan_history).  The host goes through an image's regions one by one (parse_image), the device
@@ -88,23 +90,44 @@ struct RegionWalk {
     uint32_t dht[8];                       // offset of BITS of the table this region last defines for class * 4 + id (0: none)
     uint32_t qoff[4]; uint8_t qprec[4];    // the same for quantisation tables
     uint32_t sos, sos_end;                 // payload of the scan header; entropy-coded data starts at sos_end
+    uint64_t sos_head[2];                  // its first sixteen bytes
     int32_t ri;                            // restart interval defined here, -1: none
 };
 
+// Bytes p .. p + 23, little endian; what lies at `end` or behind it says nothing.
+PCR_HD void bytes24(const uint8_t* rec, uint32_t p, uint32_t end, uint64_t v[3]) {
+    v[0] = v[1] = v[2] = 0;
+    for (uint32_t b = 0; b < 24; b++) if (b < end - p) v[b >> 3] |= (uint64_t)rec[p + b] << (8 * (b & 7));
+}
+PCR_HD uint32_t byte_of(uint64_t v, uint32_t b) { return (uint32_t)(v >> (8 * b)) & 255u; }
+// sum of the eight bytes
+PCR_HD uint32_t sum_bytes(uint64_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_sad_u8((uint32_t)v, 0u, __builtin_amdgcn_sad_u8((uint32_t)(v >> 32), 0u, 0u));
+#else
+    uint32_t t = 0;
+    for (uint32_t b = 0; b < 8; b++) t += byte_of(v, b);
+    return t;
+#endif
+}
+
 PCR_HD void setup_geometry(ImgDesc* d) {
+    const int nc = uni((int)d->nc);
     d->hmax = 1; d->vmax = 1;
-    for (int c = 0; c < d->nc; c++) { if (d->hs[c] > d->hmax) d->hmax = d->hs[c]; if (d->vs[c] > d->vmax) d->vmax = d->vs[c]; }
-    d->mcux = (uint16_t)((d->W + 8 * d->hmax - 1) / (8 * d->hmax));
-    d->mcuy = (uint16_t)((d->H + 8 * d->vmax - 1) / (8 * d->vmax));
-    for (int c = 0; c < d->nc; c++) {
+    for (int c = 0; c < nc; c++) { if (d->hs[c] > d->hmax) d->hmax = d->hs[c]; if (d->vs[c] > d->vmax) d->vmax = d->vs[c]; }
+    const uint32_t hsh = d->hmax - 1u, vsh = d->vmax - 1u;     // (factors are 1 or 2: shifts)
+    d->mcux = (uint16_t)((d->W + (8u << hsh) - 1) >> (3 + hsh));
+    d->mcuy = (uint16_t)((d->H + (8u << vsh) - 1) >> (3 + vsh));
+    for (int c = 0; c < nc; c++) {
         d->bw[c] = (uint16_t)(d->mcux * d->hs[c]); d->bh[c] = (uint16_t)(d->mcuy * d->vs[c]);
-        uint32_t xc = ((uint32_t)d->W * d->hs[c] + d->hmax - 1) / d->hmax, yc = ((uint32_t)d->H * d->vs[c] + d->vmax - 1) / d->vmax;
+        uint32_t xc = ((uint32_t)d->W * d->hs[c] + hsh) >> hsh, yc = ((uint32_t)d->H * d->vs[c] + vsh) >> vsh;
         d->cw[c] = (uint16_t)((xc + 7) / 8); d->ch[c] = (uint16_t)((yc + 7) / 8);
     }
 }
 
 // The segments of region g up to its scan header.  The frame header goes into *img (region 0 must hold it, later
-// regions must not).
+// regions must not).  On the device a wavefront walks a region: what bytes24 returns is the same in all lanes and known to
+// be (uni), so that all of this is scalar code, and *w and *img lie in LDS.
 template <class Bytes>
 PCR_HD int walk_region(const Bytes& rec, uint32_t p, uint32_t end, uint32_t g, RegionWalk* w, ImgDesc* img) {
     for (int t = 0; t < 8; t++) w->dht[t] = 0;
@@ -115,84 +138,104 @@ PCR_HD int walk_region(const Bytes& rec, uint32_t p, uint32_t end, uint32_t g, R
         if (end - p < 2 || rec[p] != 0xFF || rec[p + 1] != 0xD8) return kEFormat;
         p += 2;
     }
-    while (true) {
-        if (end - p < 4) return kEFormat;
-        if (rec[p] != 0xFF) return kEFormat;
-        uint32_t m = rec[p + 1];
-        if (m == 0xFF) { p++; continue; }
-        uint32_t L = ((uint32_t)rec[p + 2] << 8) | rec[p + 3];
-        if (L < 2 || L + 2 > end - p) return kEFormat;
-        uint32_t s = p + 4, se = p + 2 + L;
-        p = se;
+    uint32_t m = 0, s = 0, se = 0;                           // the segment's marker, what is left of its payload
+    while (true) {                                           // one turn per segment, or per table of a segment that holds several
+        const bool fresh = s >= se;
+        if (fresh && end - p < 4) return kEFormat;
+        uint64_t v[3];
+        bytes24(rec, fresh ? p : s, end, v);
+        if (fresh) {
+            if (byte_of(v[0], 0) != 0xFF) return kEFormat;
+            m = byte_of(v[0], 1);
+            if (m == 0xFF) { p++; continue; }
+            const uint32_t L = (byte_of(v[0], 2) << 8) | byte_of(v[0], 3);
+            if (L < 2 || L + 2 > end - p) return kEFormat;
+            s = p + 4; se = p + 2 + L;
+            p = se;
+            v[0] = (v[0] >> 32) | (v[1] << 32); v[1] = (v[1] >> 32) | (v[2] << 32); v[2] >>= 32;
+        }
+        const uint32_t first = byte_of(v[0], 0), left = se - s;
         if (m == 0xDB) {
-            while (s < se) {
-                uint32_t pq = rec[s] >> 4, tq = rec[s] & 15; s++;
-                if (tq > 3 || pq > 1 || se - s < 64 * (pq + 1)) return kEFormat;
-                // (selects over the four slots: an index would put the array into scratch memory on the device)
-                for (uint32_t t = 0; t < 4; t++) if (t == tq) { w->qoff[t] = s; w->qprec[t] = (uint8_t)pq; }
-                s += 64 * (pq + 1);
-            }
+            if (left == 0) continue;
+            const uint32_t pq = first >> 4, tq = first & 15;
+            if (tq > 3 || pq > 1 || left - 1 < 64 * (pq + 1)) return kEFormat;
+            w->qoff[tq] = s + 1; w->qprec[tq] = (uint8_t)pq;
+            s += 1 + 64 * (pq + 1);
+        } else if (m == 0xC4) {
+            if (left == 0) continue;
+            const uint32_t tc = first >> 4, th = first & 15;
+            if (tc > 1 || th > 3 || left < 17) return kEFormat;
+            const uint32_t nv = sum_bytes(v[0] >> 8) + sum_bytes(v[1]) + byte_of(v[2], 0);
+            if (nv > 256 || left - 17 < nv) return kEFormat;
+            w->dht[tc * 4 + th] = s + 1;
+            s += 17 + nv;
         } else if (m == 0xC0 || m == 0xC1 || m == 0xC2) {
-            if (have_frame || se - s < 6) return kEFormat;
-            if (rec[s] != 8) return kEUnsupported;
+            if (have_frame || left < 6) return kEFormat;
+            if (first != 8) return kEUnsupported;
+            const uint32_t nc = byte_of(v[0], 5);
             img->progressive = (m == 0xC2);
-            img->H = (uint16_t)(((uint32_t)rec[s + 1] << 8) | rec[s + 2]); img->W = (uint16_t)(((uint32_t)rec[s + 3] << 8) | rec[s + 4]); img->nc = rec[s + 5];
+            img->H = (uint16_t)((byte_of(v[0], 1) << 8) | byte_of(v[0], 2)); img->W = (uint16_t)((byte_of(v[0], 3) << 8) | byte_of(v[0], 4)); img->nc = (uint8_t)nc;
             if (img->H == 0 || img->W == 0) return kEUnsupported;
-            if (img->nc != 1 && img->nc != 3) return kEUnsupported;
-            if (se - s < 6u + 3u * img->nc) return kEFormat;
-            for (int c = 0; c < img->nc; c++) {
-                img->cid[c] = rec[s + 6 + 3 * c]; img->hs[c] = rec[s + 7 + 3 * c] >> 4; img->vs[c] = rec[s + 7 + 3 * c] & 15; img->tq[c] = rec[s + 8 + 3 * c];
-                if (img->hs[c] < 1 || img->hs[c] > 2 || img->vs[c] < 1 || img->vs[c] > 2 || img->tq[c] > 3) return kEUnsupported;
+            if (nc != 1 && nc != 3) return kEUnsupported;
+            if (left < 6u + 3u * nc) return kEFormat;
+            const uint64_t comps[3] = {(v[0] >> 48) | (v[1] << 16), v[1] >> 8, v[1] >> 32};      // three bytes each
+            for (uint32_t c = 0; c < (uint32_t)kMaxComp; c++) {
+                if (c >= nc) continue;
+                const uint32_t h = byte_of(comps[c], 1) >> 4, vs = byte_of(comps[c], 1) & 15, tq = byte_of(comps[c], 2);
+                img->cid[c] = (uint8_t)byte_of(comps[c], 0); img->hs[c] = (uint8_t)h; img->vs[c] = (uint8_t)vs; img->tq[c] = (uint8_t)tq;
+                if (h < 1 || h > 2 || vs < 1 || vs > 2 || tq > 3) return kEUnsupported;
             }
-            if (img->nc == 1) { img->hs[0] = 1; img->vs[0] = 1; }
+            if (nc == 1) { img->hs[0] = 1; img->vs[0] = 1; }
             setup_geometry(img);
             have_frame = true;
-        } else if ((m >= 0xC3 && m <= 0xCF && m != 0xC4 && m != 0xC8 && m != 0xCC) || m == 0xDC) {
+            s = se;
+        } else if ((m >= 0xC3 && m <= 0xCF && m != 0xC8 && m != 0xCC) || m == 0xDC) {
             return kEUnsupported;                  // lossless, hierarchical, arithmetic coding, DNL
-        } else if (m == 0xC4) {
-            while (s < se) {
-                uint32_t tc = rec[s] >> 4, th = rec[s] & 15;
-                if (tc > 1 || th > 3 || se - s < 17) return kEFormat;
-                uint32_t nv = 0; for (int i = 0; i < 16; i++) nv += rec[s + 1 + i];
-                if (nv > 256 || se - s < 17 + nv) return kEFormat;
-                for (uint32_t t = 0; t < 8; t++) if (t == tc * 4 + th) w->dht[t] = s + 1;
-                s += 17 + nv;
-            }
         } else if (m == 0xDD) {
-            if (se - s < 2) return kEFormat;
-            w->ri = (int32_t)(((uint32_t)rec[s] << 8) | rec[s + 1]);
+            if (left < 2) return kEFormat;
+            w->ri = (int32_t)((first << 8) | byte_of(v[0], 1));
+            s = se;
         } else if (m == 0xDA) {
-            if (!have_frame || se - s < 1) return kEFormat;
+            if (!have_frame || left < 1) return kEFormat;
             w->sos = s; w->sos_end = se;
+            w->sos_head[0] = v[0]; w->sos_head[1] = v[1];
             return kOk;
+        } else {
+            s = se;                                // APPn, COM, anything else with a length: skipped
         }
-        // APPn, COM, anything else with a length: skipped
     }
 }
 
 // The descriptor of a scan from its header: dht, ri: the tables and the restart interval in force; end: of its region.
-template <class Bytes>
-PCR_HD int resolve_scan(const Bytes& rec, const RegionWalk& w, uint32_t end, const uint32_t dht[8], uint32_t ri, const ImgDesc* img, ScanDesc* sd) {
-    const uint32_t s = w.sos, se = w.sos_end, ns = rec[s];
-    if (ns < 1 || ns > img->nc || se - s < 1 + 2 * ns + 3) return kEFormat;
+PCR_HD int resolve_scan(const RegionWalk& w, uint32_t end, const uint32_t dht[8], uint32_t ri, const ImgDesc* img, ScanDesc* sd) {
+    const uint32_t s = uni(w.sos), se = uni(w.sos_end), nc = uni((uint32_t)img->nc), progressive = uni((uint32_t)img->progressive);
+    const uint64_t h0 = uni(w.sos_head[0]), h1 = uni(w.sos_head[1]);
+    uint32_t cid[kMaxComp];
+    for (int q = 0; q < kMaxComp; q++) cid[q] = uni((uint32_t)img->cid[q]);
+    const uint32_t ns = byte_of(h0, 0);
+    if (ns < 1 || ns > nc || se - s < 1 + 2 * ns + 3) return kEFormat;
     sd->ns = (uint8_t)ns;
     uint32_t dc_def[kMaxComp] = {0, 0, 0}, ac_def[kMaxComp] = {0, 0, 0};           // the tables the components name
+    uint32_t comp0 = 0;
     for (uint32_t j = 0; j < (uint32_t)kMaxComp; j++) {
         if (j >= ns) continue;
         int c = -1;
-        for (int q = 0; q < kMaxComp; q++) if (q < img->nc && img->cid[q] == rec[s + 1 + 2 * j]) c = q;
+        for (int q = 0; q < kMaxComp; q++) if (q < (int)nc && cid[q] == byte_of(h0, 1 + 2 * j)) c = q;
         if (c < 0) return kEFormat;
-        const uint32_t td = rec[s + 2 + 2 * j] >> 4, ta = rec[s + 2 + 2 * j] & 15;
+        const uint32_t td = byte_of(h0, 2 + 2 * j) >> 4, ta = byte_of(h0, 2 + 2 * j) & 15;
         sd->comp[j] = (uint8_t)c;
+        if (j == 0) comp0 = (uint32_t)c;
         if (td > 3 || ta > 3) return kEFormat;
         for (uint32_t t = 0; t < 4; t++) { dc_def[j] = t == td ? dht[t] : dc_def[j]; ac_def[j] = t == ta ? dht[4 + t] : ac_def[j]; }
     }
-    sd->Ss = rec[s + 1 + 2 * ns]; sd->Se = rec[s + 2 + 2 * ns]; sd->Ah = rec[s + 3 + 2 * ns] >> 4; sd->Al = rec[s + 3 + 2 * ns] & 15;
+    const uint64_t band = ns == 1 ? h0 >> 24 : ns == 2 ? h0 >> 40 : (h0 >> 56) | (h1 << 8);      // behind the components: Ss, Se, Ah and Al
+    const uint32_t Ss = byte_of(band, 0), Se = byte_of(band, 1), Ah = byte_of(band, 2) >> 4, Al = byte_of(band, 2) & 15;
+    sd->Ss = (uint8_t)Ss; sd->Se = (uint8_t)Se; sd->Ah = (uint8_t)Ah; sd->Al = (uint8_t)Al;
     for (int j = 0; j < kMaxComp; j++) sd->ac_offc[j] = 0;
-    if (!img->progressive) {
+    if (!progressive) {
         // Sequential (baseline) file, the format a record of non-progressive images holds (one scan group, or
         // one per component): the scan header must say "all 64 coefficients, full precision".
-        if (sd->Ss != 0 || sd->Se != 63 || sd->Ah != 0 || sd->Al != 0) return kEFormat;
+        if (Ss != 0 || Se != 63 || Ah != 0 || Al != 0) return kEFormat;
         for (uint32_t j = 0; j < (uint32_t)kMaxComp; j++) {
             if (j >= ns) continue;
             if (!dc_def[j] || !ac_def[j]) return kEFormat;
@@ -200,19 +243,19 @@ PCR_HD int resolve_scan(const Bytes& rec, const RegionWalk& w, uint32_t end, con
         }
         sd->ac_off = ac_def[0];
     } else {
-        if (sd->Ss > sd->Se || sd->Se > 63 || (sd->Ss == 0 && sd->Se != 0) || (sd->Ss > 0 && ns != 1) || sd->Al > 13) return kEFormat;
-        if (sd->Ah != 0 && sd->Ah != sd->Al + 1) return kEFormat;
+        if (Ss > Se || Se > 63 || (Ss == 0 && Se != 0) || (Ss > 0 && ns != 1) || Al > 13) return kEFormat;
+        if (Ah != 0 && Ah != Al + 1) return kEFormat;
         for (uint32_t j = 0; j < (uint32_t)kMaxComp; j++) {
             if (j >= ns) continue;
             sd->dc_off[j] = 0;
-            if (sd->Ss == 0 && sd->Ah == 0) { if (!dc_def[j]) return kEFormat; sd->dc_off[j] = dc_def[j]; }
+            if (Ss == 0 && Ah == 0) { if (!dc_def[j]) return kEFormat; sd->dc_off[j] = dc_def[j]; }
         }
         sd->ac_off = 0;
-        if (sd->Ss > 0) { if (!ac_def[0]) return kEFormat; sd->ac_off = ac_def[0]; }
+        if (Ss > 0) { if (!ac_def[0]) return kEFormat; sd->ac_off = ac_def[0]; }
     }
     sd->ri = (uint16_t)ri;
     if (ns > 1) { sd->mcu_w = img->mcux; sd->mcus = (uint32_t)img->mcux * img->mcuy; }
-    else { sd->mcu_w = img->cw[sd->comp[0]]; sd->mcus = (uint32_t)img->cw[sd->comp[0]] * img->ch[sd->comp[0]]; }
+    else { sd->mcu_w = img->cw[comp0]; sd->mcus = (uint32_t)img->cw[comp0] * img->ch[comp0]; }
     sd->data_off = se; sd->data_len = end - se;
     return kOk;
 }
@@ -273,7 +316,7 @@ PCR_HD void parse_image(const uint8_t* rec, const uint32_t* off, const uint32_t*
             for (int t = 0; t < 8; t++) if (w.dht[t]) dht[t] = w.dht[t];
             for (int t = 0; t < 4; t++) if (w.qoff[t]) { img->qoff[t] = w.qoff[t]; img->qprec[t] = w.qprec[t]; }
             if (w.ri >= 0) ri = (uint32_t)w.ri;
-            rc = resolve_scan(rec, w, p + L, dht, ri, img, &scans[g]);
+            rc = resolve_scan(w, p + L, dht, ri, img, &scans[g]);
         }
         if (rc == kOk) rc = scan_history(scans, g);
         if (rc != kOk) { img->status = rc; return; }

@@ -130,13 +130,18 @@ __global__ void __launch_bounds__(256) k_index(DevRecord R, uint32_t kmax) {
 // k_headers: the marker segments of one image per workgroup, and the Huffman tables of its scans.
 //   1. where the regions of scan groups 0 .. kmax-1 lie: the offsets k_index left, or (own_index, small records, one
 //      launch fewer) the sum of the lengths ahead of the image's, taken here;
-//   2. the first bytes of every region into LDS, all of them at once -- a walk over marker segments is a chain of byte
+//   2. the first bytes of every region into LDS, all of them at once -- a walk over marker segments is a chain of
 //      reads that depend on one another, and from memory each of them is a trip of a microsecond;
-//   3. one LANE PER REGION walks its segments (walk_region) and reads its scan header; the tables and the restart
-//      interval a scan takes over from earlier regions are found with ballots over the lanes;
-//   4. one wavefront per scan builds the scan's tables from its definition, every lane its share of the entries.
-// One lane per image for all of this, with the tables in a kernel of their own, took 125 + 81 us for 1024 images of
-// 10 scans; this takes 47 (8 for k_index ahead of it), bound by the chain of dependent LDS reads of the walk.
+//   3. one WAVEFRONT PER REGION walks its segments (walk_region), then reads its scan header (resolve_scan) with the tables
+//      and the restart interval in force, which ballots over the regions find;
+//   4. one wavefront puts together which scans refine which (the scans' headers handed round its lanes) and checks the image;
+//   5. one wavefront per TABLE builds it from its definition, every lane its share of the entries.
+// What bounds it is code that runs once: a workgroup passes through all of it, from a cold instruction cache, and each
+// branch that lanes take differently costs its mask arithmetic.  So the walk is scalar code with one place that reads (24
+// bytes at a time); with a lane per region, byte reads and the parse's state in vector registers the walk was 28 000 cycles
+// of the 94 000 a workgroup of ten scans took, the search for the scans refined 22 000 and the tables, dealt out by scan, 28 000;
+// now 18 000, 6 000 and 12 000.  us for 64 gray pictures of 6 scans 22.8 -> 16.2, small ragged ones of 10 scans 43.0 -> 26.6,
+// 1024 of 256 x 256 at scan group 5 38.5 -> 27.2 (k_index: 8 more), 512 photographs of 10 scans 48.9 -> 30.8.
 // Workgroups have a wavefront per scan group, kHeaderWaves at most: with eight of them at every scan group, of which seven
 // had nothing to do at scan group 1, the kernel stood in the way of the pixel writers of other records (four records
 // in flight, ms per step at scan groups 1 and 2: 0.745 and 2.18, now 0.675 and 2.08; alone nothing changes).  Records
@@ -156,9 +161,30 @@ constexpr uint32_t kOwnIndexImages = 512;                  // own_index up to th
 typedef const __attribute__((address_space(3))) uint8_t* LdsBytes;
 typedef const __attribute__((address_space(1))) uint8_t* GlobalBytes;
 struct HeaderBytes {
-    GlobalBytes rec; LdsBytes lds; uint32_t base, count;
+    GlobalBytes rec; LdsBytes lds; uint32_t base, count, room;   // room: bytes of the window, of which `count` are staged
     PCR_D uint8_t operator[](uint32_t p) const { const uint32_t o = p - base; return o < count ? lds[o] : rec[p]; }
 };
+// (Called with a wavefront, all lanes the same.  end: of the region the window is the head of.  The window starts on 16 bytes, and four bytes behind it may be read.)
+PCR_D void bytes24(const HeaderBytes& b, uint32_t p, uint32_t end, uint64_t v[3]) {
+    const uint32_t o = p - b.base;
+    uint32_t w[6] = {0, 0, 0, 0, 0, 0};
+    if (o + 24 <= b.room) {
+        typedef const __attribute__((address_space(3))) uint32_t* LdsWords;
+        const LdsWords at = (LdsWords)(b.lds + (o & ~3u));
+#pragma unroll
+        for (int t = 0; t < 6; t++) w[t] = __builtin_amdgcn_alignbyte(at[t + 1], at[t], o & 3);
+    } else {
+#pragma unroll 1
+        for (uint32_t t = 0; t < 24; t++) {
+            const uint32_t x = t < end - p ? b.rec[p + t] : 0u;
+#pragma unroll
+            for (int q = 0; q < 5; q++) w[q] = __builtin_amdgcn_alignbyte(w[q + 1], w[q], 1);
+            w[5] = (w[5] >> 8) | (x << 24);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; t++) v[t] = ((uint64_t)uni(w[2 * t + 1]) << 32) | uni(w[2 * t]);
+}
 
 // A canonical code's lengths, for building look-ups entry by entry: lim[L] = first left-aligned 16-bit value that is not
 // a code of length <= L (so codes of length L occupy lim[L-1] .. lim[L]), first[L] = index of the first code of length L.
@@ -169,16 +195,9 @@ PCR_D void canon_build(CanonCode* c, const HeaderBytes& def, uint32_t at, uint32
     const uint32_t mine = lane < 16 ? def[at + lane] : 0u;
     const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)lanes_prefix_sum(mine), 15);       // symbols in all
     for (uint32_t i = lane; i < 256; i += 64) c->vals[i] = i < k ? def[at + 16 + i] : (uint8_t)0;
-    uint32_t code = 0, lim = 0, first = 0;                    // of this lane's length (lane 0: length 1), put together by going down the lengths
-#pragma unroll
-    for (uint32_t L = 1; L <= 16; L++) {
-        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(L - 1));
-        code += cnt;
-        const uint64_t t = (uint64_t)code << (16 - L);
-        if (lane == L - 1) lim = t > 65536 ? 65536u : (uint32_t)t;
-        code <<= 1;
-    }
-    first = lanes_prefix_sum(mine) - mine;
+    // the codes of a length end, left-aligned, where those of all lengths up to it together do
+    const uint32_t ends = lanes_prefix_sum(lane < 16 ? mine << (15 - lane) : 0u), lim = ends > 65536u ? 65536u : ends;
+    const uint32_t first = lanes_prefix_sum(mine) - mine;
     if (lane < 16) { c->lim[lane + 1] = lim; c->first[lane + 1] = first; }
     if (lane == 16) c->lim[0] = 0;
 }
@@ -227,11 +246,15 @@ PCR_D void dctab_build_wave(DcTab* t, const CanonCode* c, uint32_t lane) {
 }
 
 __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32_t kmax, uint32_t keep_status, uint32_t own_index, uint32_t k0, uint32_t dc_too) {
-    __shared__ __attribute__((aligned(16))) uint8_t stage[kHeaderStage];
+    __shared__ __attribute__((aligned(16))) uint8_t stage[kHeaderStage + 16];
     __shared__ uint32_t s_off[kMaxGroups], s_len[kMaxGroups];
     __shared__ ScanDesc s_scan[kMaxGroups];
+    __shared__ RegionWalk s_walk[kMaxGroups];
+    __shared__ int s_rc[kMaxGroups];
     __shared__ ImgDesc s_img;
     __shared__ CanonCode s_code[kHeaderWaves];
+    __shared__ uint16_t s_job[kMaxGroups * kMaxComp];        // tables to build: scan group | component of the scan << 8
+    __shared__ uint32_t s_njobs;
     short_kernel_priority();
     const uint32_t i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lanes = blockDim.x, waves = lanes >> 6;
     const uint32_t n = R.n, nsc = R.nscans[i];
@@ -239,15 +262,18 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
     if (upto > kMaxGroups) upto = kMaxGroups;               // (cannot happen: the header check refuses such records)
     // ---- where the regions lie ----
     if (own_index) {
-        for (uint32_t g = wave; g < upto; g += waves) {
-            uint32_t before = 0;
-            for (uint32_t j = lane; j < i; j += 64) before += R.len[(size_t)g * n + j];
+        for (uint32_t g = wave; g < upto; g += waves) {      // (all of a group's loads at once: kOwnIndexImages / 64 lengths per lane)
+            const uint32_t* len = R.len + (size_t)g * n;
+            const uint64_t start = ld_le64(R.rec + (g == 0 ? 16 : hdr_group_end_pos(g - 1)));
+            const uint32_t mine = len[i];
+            uint32_t t[kOwnIndexImages / 64], before = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < kOwnIndexImages / 64; j++) t[j] = len[64 * j + lane < i ? 64 * j + lane : i];
+#pragma unroll
+            for (uint32_t j = 0; j < kOwnIndexImages / 64; j++) before += 64 * j + lane < i ? t[j] : 0u;
 #pragma unroll
             for (int d = 32; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d);
-            if (lane == 0) {
-                const uint32_t start = g == 0 ? (uint32_t)ld_le64(R.rec + 16) : (uint32_t)ld_le64(R.rec + hdr_group_end_pos(g - 1));
-                s_off[g] = start + before; s_len[g] = R.len[(size_t)g * n + i];
-            }
+            if (lane == 0) { s_off[g] = (uint32_t)start + before; s_len[g] = mine; }
         }
     } else if (tid < upto) { s_off[tid] = R.off[(size_t)tid * n + i]; s_len[tid] = R.len[(size_t)tid * n + i]; }
     for (uint32_t e = tid; e < sizeof(ScanDesc) / 4 * upto; e += lanes) reinterpret_cast<uint32_t*>(s_scan)[e] = 0;
@@ -269,52 +295,113 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
         } else for (uint32_t b = 0; b < L - o; b++) dst[b] = src[b];
     }
     __syncthreads();
-    auto bytes_of = [&](uint32_t g) { return HeaderBytes{(GlobalBytes)R.rec, (LdsBytes)(stage + g * window), s_off[g], s_len[g] < window ? s_len[g] : window}; };
-    // ---- the walk: lane g of the first wavefront takes region g ----
-    RegionWalk w{};
-    int rc = kOk;
-    if (wave == 0) {
-        const uint32_t g = lane;
-        if (g < upto) rc = walk_region(bytes_of(g), s_off[g], s_off[g] + s_len[g], g, &w, &s_img);
-#pragma unroll
-        for (int t = 0; t < 4; t++) {
-            const uint64_t m = __ballot(g < upto && w.qoff[t] != 0);
-            const int last = m ? 63 - __builtin_clzll(m) : 0;
-            const uint32_t qo = (uint32_t)__shfl((int)w.qoff[t], last), qp = (uint32_t)__shfl((int)w.qprec[t], last);
-            if (lane == 0) { s_img.qoff[t] = m ? qo : 0u; s_img.qprec[t] = (uint8_t)(m ? qp : 0u); }
-        }
+    auto bytes_of = [&](uint32_t g) {
+        const uint32_t len = uni(s_len[g]);
+        return HeaderBytes{(GlobalBytes)R.rec, (LdsBytes)(stage + g * window), uni(s_off[g]), len < window ? len : window, window};
+    };
+    // ---- the walk, a wavefront per region ----
+    for (uint32_t g = wave; g < upto; g += waves) {
+        const uint32_t at = uni(s_off[g]), end = at + uni(s_len[g]);
+        const int rc = walk_region(bytes_of(g), at, end, g, &s_walk[g], &s_img);
+        if (lane == 0) s_rc[g] = rc;
+    }
+    __syncthreads();
+    for (uint32_t g = wave; g < upto; g += waves) {
         // what is in force at the scan: the last definition in this region or an earlier one
-        const uint64_t upto_me = g >= 63 ? ~0ull : (2ull << g) - 1;
+        const RegionWalk& w = s_walk[lane < upto ? lane : 0];
+        uint32_t dht[8], ri;
 #pragma unroll
         for (int t = 0; t < 8; t++) {
-            const uint64_t m = __ballot(g < upto && w.dht[t] != 0) & upto_me;
-            const uint32_t v = (uint32_t)__shfl((int)w.dht[t], m ? 63 - __builtin_clzll(m) : 0);
-            w.dht[t] = m ? v : 0u;
+            const uint32_t def = w.dht[t];
+            const uint64_t m = __ballot(lane <= g && def != 0);
+            dht[t] = m ? (uint32_t)__builtin_amdgcn_readlane((int)def, 63 - __builtin_clzll(m)) : 0u;
         }
         {
-            const uint64_t m = __ballot(g < upto && w.ri >= 0) & upto_me;
-            const int v = __shfl(w.ri, m ? 63 - __builtin_clzll(m) : 0);
-            w.ri = m ? v : 0;
+            const int def = w.ri;
+            const uint64_t m = __ballot(lane <= g && def >= 0);
+            ri = m ? (uint32_t)__builtin_amdgcn_readlane(def, 63 - __builtin_clzll(m)) : 0u;
+        }
+        const int walked = uni(s_rc[g]);
+        if (walked == kOk) {
+            const int rc = resolve_scan(s_walk[g], uni(s_off[g]) + uni(s_len[g]), dht, ri, &s_img, &s_scan[g]);
+            if (lane == 0) s_rc[g] = rc;
         }
     }
-    __syncthreads();                                        // (the frame header is lane 0's)
-    if (wave == 0 && lane < upto && rc == kOk) rc = resolve_scan(bytes_of(lane), w, s_off[lane] + s_len[lane], w.dht, (uint32_t)w.ri, &s_img, &s_scan[lane]);
+    if (wave == waves - 1) {                                 // quantisation tables: the last definition of all
+        const RegionWalk& w = s_walk[lane < upto ? lane : 0];
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const uint32_t off = w.qoff[t], prec = w.qprec[t];
+            const uint64_t m = __ballot(lane < upto && off != 0);
+            const int last = m ? 63 - __builtin_clzll(m) : 0;
+            const uint32_t qo = (uint32_t)__builtin_amdgcn_readlane((int)off, last), qp = (uint32_t)__builtin_amdgcn_readlane((int)prec, last);
+            if (lane == 0) { s_img.qoff[t] = m ? qo : 0u; s_img.qprec[t] = (uint8_t)(m ? qp : 0u); }
+        }
+    }
     __syncthreads();
     if (wave == 0) {
-        if (lane < upto && rc == kOk) rc = scan_history(s_scan, lane);
+        int rc = lane < upto ? s_rc[lane] : kOk;
+        // scan_history, the reach of the components and check_image, every scan's header handed round the lanes
+        ScanDesc* sd = &s_scan[lane < upto ? lane : 0];
+        const uint32_t ns = sd->ns, Ss = sd->Ss, Se = sd->Se, comp = sd->comp[0];
+        uint32_t key = Ss | (Se << 6) | (sd->Ah ? 1u << 12 : 0u) | (comp << 13);
+#pragma unroll
+        for (uint32_t j = 0; j < (uint32_t)kMaxComp; j++) if (j < ns) key += 1u << (15 + 2 * sd->comp[j]);     // how often the scan names each component
+        uint64_t hist = 0;
+        uint32_t nhist = 0, has_first = 0, over = 0;
+        const bool refines = Ss > 0 && sd->Ah > 0;
+        for (uint32_t q = 0; q + 1 < upto; q++) {
+            const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)key, (int)q);
+            if ((k & 63) == 0) continue;
+            const bool of = refines && q < lane && ((k >> 13) & 3) == comp && (k & 63) <= Se && Ss <= ((k >> 6) & 63);
+            if ((k & (1u << 12)) == 0) has_first |= of ? 1u : 0u;
+            else if (of) {
+                if (nhist >= (uint32_t)kMaxHist) over = 1;
+                else { hist |= (uint64_t)q << (8 * nhist); nhist++; }
+            }
+        }
+        if (lane < upto && rc == kOk) {
+            sd->nhist = (uint8_t)nhist;
+#pragma unroll
+            for (int t = 0; t < kMaxHist; t++) if ((uint32_t)t < nhist) sd->hist[t] = (uint8_t)(hist >> (8 * t));
+            rc = over ? kEUnsupported : (refines && !has_first ? kEFormat : kOk);
+            if (rc == kOk) sd->valid = 1;
+        }
         const uint64_t bad = __ballot(lane < upto && rc != kOk);
         const uint32_t good = bad ? (uint32_t)__builtin_ctzll(bad) : upto;            // scans ahead of the first damaged region
         const int first_rc = __shfl(rc, bad ? (int)good : 0);
-        if (lane < (uint32_t)kMaxComp) {                                              // per component: how far its scans reach
-            uint32_t z = 0;
-            for (uint32_t g = 0; g < good; g++)
-                for (uint32_t j = 0; j < s_scan[g].ns; j++)
-                    if (s_scan[g].comp[j] == lane && s_scan[g].Se + 1u > z) z = s_scan[g].Se + 1u;
-            s_img.zmax[lane] = (uint8_t)z;
+        uint32_t reach[kMaxComp] = {0, 0, 0}, nref[kMaxComp] = {0, 0, 0};             // per component: how far its scans reach, how many refine it
+        for (uint32_t q = 0; q < good; q++) {
+            const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)key, (int)q), z = ((k >> 6) & 63) + 1;
+#pragma unroll
+            for (int c = 0; c < kMaxComp; c++) {
+                const uint32_t named = (k >> (15 + 2 * c)) & 3;
+                if (named && z > reach[c]) reach[c] = z;
+                if (k & (1u << 12)) nref[c] += named;
+            }
         }
-        if (lane == 0) s_img.nscans = good;
+        if (lane == 0) {
+#pragma unroll
+            for (int c = 0; c < kMaxComp; c++) s_img.zmax[c] = (uint8_t)reach[c];
+            s_img.nscans = good;
+        }
+        {
+            const uint32_t jobs = lane < k0 || lane >= upto ? 0u : Ss > 0 ? 1u : (dc_too && sd->Ah == 0 && s_img.progressive) ? ns : 0u;
+            const uint32_t end = lanes_prefix_sum(jobs);
+            for (uint32_t j = 0; j < jobs; j++) s_job[end - jobs + j] = (uint16_t)(lane | (j << 8));
+            if (lane == 63) s_njobs = end;
+        }
         if (lane >= good && lane < upto) s_scan[lane].valid = 0;
-        const int st = bad ? first_rc : check_image(&s_img, s_scan);
+        int st = bad ? first_rc : kOk;
+        if (!bad) {                                          // (as check_image)
+            if (good == 0) st = kEFormat;
+            else {
+#pragma unroll
+                for (int c = 0; c < kMaxComp; c++) if (st == kOk && c < s_img.nc && nref[c] > (uint32_t)kApplyMaxScans) st = kEUnsupported;
+#pragma unroll
+                for (int c = 0; c < kMaxComp; c++) if (st == kOk && c < s_img.nc && !s_img.qoff[s_img.tq[c]]) st = kEFormat;
+            }
+        }
         if (lane == 0) {
             s_img.status = st;
             if (!(keep_status && R.status[i] != kOk)) R.status[i] = st;
@@ -331,22 +418,16 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
     if (s_img.status != kOk) return;
     // ---- the tables ----
     CanonCode* code = &s_code[wave];
-    for (uint32_t g = k0 + wave; g < upto; g += waves) {
+    const uint32_t njobs = s_njobs;
+    for (uint32_t job = wave; job < njobs; job += waves) {
+        const uint32_t g = s_job[job] & 255u, j = s_job[job] >> 8;
         const ScanDesc& sd = s_scan[g];
         const size_t ig = (size_t)i * R.G + g;
         // (a table may have been defined ahead of this scan's own region: in memory then, unless it is region 0)
-        if (sd.Ss > 0) {
-            canon_build(code, bytes_of(g), sd.ac_off, lane);
-            wave_sync();
-            actab_build_wave(&R.tabs[R.tab_idx[ig]], code, sd.Ah == 0, lane);
-        } else if (dc_too && sd.Ah == 0 && s_img.progressive) {
-            for (uint32_t j = 0; j < sd.ns; j++) {
-                canon_build(code, bytes_of(g), sd.dc_off[j], lane);
-                wave_sync();
-                dctab_build_wave(&R.dctabs[R.dctab_idx[ig] + j], code, lane);
-                wave_sync();
-            }
-        }
+        canon_build(code, bytes_of(g), sd.Ss > 0 ? sd.ac_off : sd.dc_off[j], lane);
+        wave_sync();
+        if (sd.Ss > 0) actab_build_wave(&R.tabs[R.tab_idx[ig]], code, sd.Ah == 0, lane);
+        else dctab_build_wave(&R.dctabs[R.dctab_idx[ig] + j], code, lane);
         wave_sync();
     }
 }

@@ -93,3 +93,28 @@ def test_damaged_headers_flag_their_image_only():
                 assert np.array_equal(part, want[int(lay[i]):int(lay[i + 1])]), (g, at, i)
             elif g > 0:                                        # (without a frame header there is nothing to fill)
                 assert not part.any(), (g, at)
+
+
+@pytest.mark.parametrize("start", [936, 952, 968, 984, 1000])
+def test_segments_across_the_end_of_the_staged_window(start):
+    """Comments of sixteen lengths in a row ahead of the tables and ahead of a later scan: every segment behind them begins at every
+    offset from the end of the staged bytes, and is read half from them and half from memory."""
+    files = []
+    for comment in range(start, start + 16):
+        base = pcrgen.make_jpeg(5, 1, 23, 17, 3, 8.0, 2, 1, 90)
+        seg = b"\xff\xfe" + (comment + 2).to_bytes(2, "big") + bytes((5 * j) & 0x7F for j in range(comment))
+        ends = pcrgen.split_scans(base)
+        at = base.index(b"\xff\xc2")
+        files.append(base[:at] + seg + base[at:])
+        files.append(base[:ends[2]] + seg + base[ends[2]:])
+    _same(pcrgen.write_record(files))
+
+
+def test_a_refinement_that_builds_on_as_many_scans_as_can_be():
+    """Six earlier refinements of a band, the most a scan may build on, and bands that overlap some of them."""
+    dc, whole = (1, 0, 0, 0, 0, 0, 0, 0), [(1, 0, 0, 0, 1, 63, 0, 7)] + [(1, 0, 0, 0, 1, 63, a, a - 1) for a in range(7, 0, -1)]
+    parts = [(1, 0, 0, 0, 1, 20, 0, 3), (1, 0, 0, 0, 21, 63, 0, 3)] + [(1, 0, 0, 0, lo, hi, a, a - 1) for a in (3, 2) for lo, hi in ((1, 9), (10, 30), (31, 63))]
+    parts += [(1, 0, 0, 0, 1, 63, 1, 0)]
+    files = [pcrgen.encode_pixels(pcrgen.synth(7 + i, 1, 40 + i, 33, 1, 25.0), 1, 1, 95, [dc] + s) for i, s in enumerate((whole, parts))]
+    for f in files:
+        _same(pcrgen.write_record([f]))
