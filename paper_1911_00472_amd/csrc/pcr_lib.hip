@@ -1599,7 +1599,7 @@ int pcr_transcode_batch(pcr_record* r, const void* const* files, const size_t* s
     if (!rc) {
         hipLaunchKernelGGL(k_export_natural, dim3(2048), dim3(256), 0, s, r->d.coef, d_coef, (size_t)r->coef_off[n]);
         if (device_counts)
-            hipLaunchKernelGGL(k_symbol_hist, dim3(n, kScriptScansMax), dim3(64), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off, restart_interval, d_hist);
+            hipLaunchKernelGGL(k_symbol_hist, dim3(n, kScriptScansMax), dim3(kHistLanes), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off, restart_interval, d_hist);
         if (hipGetLastError() != hipSuccess) rc = PCR_E_DEVICE;
     }
     if (!rc && device_counts && hipMemcpyAsync(host + hist_at, d_hist, hist_bytes, hipMemcpyDeviceToHost, s) != hipSuccess) rc = PCR_E_DEVICE;
@@ -1650,7 +1650,7 @@ int pcr_symbol_histograms(pcr_record* r, uint32_t restart_interval, uint32_t* d_
     if (rc) return rc;
     call_end(r);
     static_assert(PCR_HIST_ENTRIES == kHistPerImage, "header and kernel agree on the layout of the counts");
-    hipLaunchKernelGGL(k_symbol_hist, dim3(r->hdr.n, kScriptScansMax), dim3(64), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off,
+    hipLaunchKernelGGL(k_symbol_hist, dim3(r->hdr.n, kScriptScansMax), dim3(kHistLanes), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off,
                        restart_interval, d_hist);
     if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
     return PCR_OK;
