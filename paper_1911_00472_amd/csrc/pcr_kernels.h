@@ -744,6 +744,24 @@ template <class T> PCR_D T load_const(const T* p) { return *(const __attribute__
 // way together.  (The compiler moves each to its first use, behind the branches, and waits for one after the other.)
 PCR_D void wanted_now(uint32_t a) { asm volatile("" :: "s"(a)); }
 PCR_D void wanted_now(uint64_t a) { asm volatile("" :: "s"(a)); }
+// a value per component, picked by a component number (per lane or wave-uniform) out of three wave-uniform ones
+PCR_D uint32_t pick3(uint32_t c, uint32_t a0, uint32_t a1, uint32_t a2) { return c == 0 ? a0 : (c == 1 ? a1 : a2); }
+
+// a descriptor through a wave-uniform pointer, as dwords
+template <class T> PCR_D void load_desc(const T* ip, T* D) {
+    const __attribute__((address_space(4))) uint32_t* src = (const __attribute__((address_space(4))) uint32_t*)ip;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(D);
+#pragma unroll
+    for (uint32_t e = 0; e < sizeof(T) / 4; e++) dst[e] = src[e];
+}
+template <class T> PCR_D void desc_wanted_now(const T& D) {
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(&D);
+#pragma unroll
+    for (uint32_t e = 0; e < sizeof(T) / 4; e++) wanted_now(w[e]);
+}
+PCR_D void wanted_now(const ImgDesc& D) { desc_wanted_now(D); }
+PCR_D void wanted_now(const ScanDesc& D) { desc_wanted_now(D); }
+
 // The same in vector registers; a descriptor as its words (loaded whole: the loads of single members end up behind the
 // branches that use them).
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
@@ -1192,18 +1210,37 @@ struct RefineTile { uint32_t entry; uint32_t chunk; };
 // when the scan starts: what the AC first scans left in the coefficient plane, and what earlier refinement scans of the
 // band added (their kRefNz words).  k_refine_deal: the correction bits the decoder left in reading order go to the
 // history positions they belong to (kRefPlus as every consumer reads it).
-PCR_D bool refine_block_of_lane(const DevRecord& R, const RefineScan& a, uint32_t chunk, size_t* ig_out, uint32_t* blk_out, uint32_t* plane_out) {
-    if (R.status[a.img] != kOk) return false;
-    const ImgDesc* img = &R.img[a.img];
-    const size_t ig = (size_t)a.img * R.G + a.scan;
-    const int c = R.scan[ig].comp[0];
-    const uint32_t cw = img->cw[c], ncov = cw * img->ch[c];
-    const uint32_t b = chunk * 256 + threadIdx.x;
-    if (b >= ncov) return false;
-    const uint32_t bw = img->bw[c];
-    *ig_out = ig; *blk_out = (b / cw) * bw + (b % cw); *plane_out = bw * img->bh[c];
-    return true;
+// Where the work of a tile lies: its entry, then everything that depends on the image and the scan alone in ONE round of scalar
+// loads.  (Read where it was used, each member behind the branch before it, a workgroup waited five times in a row before
+// its first word of the records.  1024 photographs, four records in flight, and 256 of 600 x 450, us per launch: k_refine_history 177 ->
+// 137 and 59 -> 52, k_refine_deal 73 -> 69 and 22 -> 21.)
+struct RefinePlace {
+    ImgDesc D; ScanDesc S;
+    uint32_t img, chunk, status, tab, slot, cw, ncov, bw, plane;
+    size_t ig;
+    uint64_t mask, coef;
+};
+PCR_D void refine_place(const DevRecord& R, const RefineScan* rs, const RefineTile* tiles, RefinePlace* P) {
+    const uint64_t tile = load_const(reinterpret_cast<const uint64_t*>(tiles) + blockIdx.x);
+    const uint64_t a = load_const(reinterpret_cast<const uint64_t*>(rs) + (uint32_t)tile);
+    P->chunk = (uint32_t)(tile >> 32);
+    P->img = (uint32_t)a;
+    P->ig = (size_t)P->img * R.G + (uint32_t)(a >> 32);
+    load_desc(R.img + P->img, &P->D);
+    load_desc(R.scan + P->ig, &P->S);
+    P->status = (uint32_t)load_const(&R.status[P->img]);
+    P->tab = load_const(&R.tab_idx[P->ig]);
+    P->slot = load_const(&R.slot_base[P->ig]);
+    P->mask = load_const(&R.mask_off[P->ig]);
+    P->coef = load_const(&R.coef_off[P->img]);
+    wanted_now(P->D); wanted_now(P->S); wanted_now(P->status); wanted_now(P->tab); wanted_now(P->slot); wanted_now(P->mask); wanted_now(P->coef);
+    const uint32_t c = P->S.comp[0];
+    P->cw = pick3(c, P->D.cw[0], P->D.cw[1], P->D.cw[2]);
+    P->ncov = P->cw * pick3(c, P->D.ch[0], P->D.ch[1], P->D.ch[2]);
+    P->bw = pick3(c, P->D.bw[0], P->D.bw[1], P->D.bw[2]);
+    P->plane = P->bw * pick3(c, P->D.bh[0], P->D.bh[1], P->D.bh[2]);
 }
+static_assert(sizeof(RefineTile) == 8 && offsetof(RefineTile, entry) == 0 && sizeof(RefineScan) == 8 && offsetof(RefineScan, img) == 0, "taken as 64-bit words");
 // k_refine_history works through the padded plane (blocks the image does not cover included: they hold zeros), 64
 // consecutive blocks -- 8 KB of coefficients -- per wavefront: lane i of step j loads 16-byte chunk 64 j + i of them, so
 // that every load instruction reads one contiguous kilobyte, turns its eight coefficients into eight mask bits, and leaves
@@ -1211,30 +1248,36 @@ PCR_D bool refine_block_of_lane(const DevRecord& R, const RefineScan& a, uint32_
 __global__ void __launch_bounds__(256) k_refine_history(DevRecord R, const RefineScan* __restrict__ rs, const RefineTile* __restrict__ tiles) {
     __shared__ __attribute__((aligned(8))) uint8_t bytes[4][64 * 8];
     short_kernel_priority();
-    const RefineTile tile = tiles[blockIdx.x];
-    const RefineScan a = rs[tile.entry];
-    if (R.status[a.img] != kOk) return;
-    const ImgDesc* img = &R.img[a.img];
-    const size_t ig = (size_t)a.img * R.G + a.scan;
-    const ScanDesc* sd = &R.scan[ig];
-    const int c = sd->comp[0];
-    const uint32_t plane = (uint32_t)img->bw[c] * img->bh[c];
-    if (tile.chunk * 256 >= plane) return;
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t blk0 = tile.chunk * 256 + wave * 64, blk = blk0 + lane;
+    RefinePlace P;
+    refine_place(R, rs, tiles, &P);
+    if (P.status != (uint32_t)kOk || P.chunk * 256 >= P.plane) return;
+    const uint32_t plane = P.plane, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const uint32_t blk0 = P.chunk * 256 + wave * 64, blk = blk0 + lane;
+    const uint32_t nhist = P.S.nhist < kMaxHist ? P.S.nhist : kMaxHist;
+    uint64_t from[kMaxHist];                                  // the records of the scans this one builds on
+    uint32_t band0;                                           // first and last position of the first of them
+    {
+        const size_t i0 = (size_t)P.img * R.G;
+#pragma unroll
+        for (uint32_t q = 0; q < (uint32_t)kMaxHist; q++) from[q] = load_const(&R.mask_off[i0 + (q < nhist ? P.S.hist[q] : 0u)]);
+        static_assert(offsetof(ScanDesc, Ss) % 4 == 2 && offsetof(ScanDesc, Se) == offsetof(ScanDesc, Ss) + 1, "the upper half of a word");
+        band0 = load_const(reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(&R.scan[i0 + (nhist ? P.S.hist[0] : 0u)]) + (offsetof(ScanDesc, Ss) & ~3u))) >> 16;
+#pragma unroll
+        for (uint32_t q = 0; q < (uint32_t)kMaxHist; q++) wanted_now(from[q]);
+        wanted_now(band0);
+    }
     uint64_t m = 0;
     // An earlier refinement scan of the very same band has this word already: what it started from and what it added
     // are what this scan starts from (16 bytes per block instead of the block's 128 bytes of coefficients).
-    const ScanDesc* first = sd->nhist ? &R.scan[(size_t)a.img * R.G + sd->hist[0]] : sd;
-    const bool from_records = sd->nhist && first->Ss == sd->Ss && first->Se == sd->Se;
+    const bool from_records = nhist && band0 == (P.S.Ss | ((uint32_t)P.S.Se << 8));
     if (from_records) {
-        if (blk < plane) m = R.masks[R.mask_off[(size_t)a.img * R.G + sd->hist[0]] + ref_word(kRefHist, blk, plane)];
+        if (blk < plane) m = R.masks[from[0] + ref_word(kRefHist, blk, plane)];
     } else {
-        size_t po = 0;
-        for (int q = 0; q < c; q++) po += (size_t)img->bw[q] * img->bh[q] * 64;
-        const uint4* src = reinterpret_cast<const uint4*>(R.coef + R.coef_off[a.img] + po) + (size_t)blk0 * 8;
+        const uint32_t c = P.S.comp[0], n0 = (uint32_t)P.D.bw[0] * P.D.bh[0], n1 = (uint32_t)P.D.bw[1] * P.D.bh[1];
+        const size_t po = (size_t)(c > 0 ? n0 : 0u) * 64 + (size_t)(c > 1 ? n1 : 0u) * 64;
+        const uint4* src = reinterpret_cast<const uint4*>(R.coef + P.coef + po) + (size_t)blk0 * 8;
         const uint32_t chunk = lane & 7u;                     // (the same in every step: 64 is a multiple of 8)
-        const bool wanted = chunk >= (uint32_t)(sd->Ss >> 3) && chunk <= (uint32_t)(sd->Se >> 3);
+        const bool wanted = chunk >= (uint32_t)(P.S.Ss >> 3) && chunk <= (uint32_t)(P.S.Se >> 3);
 #pragma unroll
         for (uint32_t j = 0; j < 8; j++) {
             const uint32_t e = j * 64 + lane;                 // chunk e & 7 of block blk0 + (e >> 3)
@@ -1251,50 +1294,45 @@ __global__ void __launch_bounds__(256) k_refine_history(DevRecord R, const Refin
     __syncthreads();
     if (blk >= plane) return;
     if (!from_records) m = *reinterpret_cast<const uint64_t*>(&bytes[wave][lane * 8]);
-    for (uint32_t q = 0; q < sd->nhist && q < (uint32_t)kMaxHist; q++)
-        m |= R.masks[R.mask_off[(size_t)a.img * R.G + sd->hist[q]] + ref_word(kRefNz, blk, plane)];
-    R.masks[R.mask_off[ig] + ref_word(kRefHist, blk, plane)] = m & band_mask(sd->Ss, sd->Se);
+#pragma unroll
+    for (uint32_t q = 0; q < (uint32_t)kMaxHist; q++) if (q < nhist) m |= R.masks[from[q] + ref_word(kRefNz, blk, plane)];
+    R.masks[P.mask + ref_word(kRefHist, blk, plane)] = m & band_mask(P.S.Ss, P.S.Se);
 }
 // grid: one workgroup per tile (chunks of the blocks the image covers)
 __global__ void __launch_bounds__(256) k_refine_deal(DevRecord R, const RefineScan* __restrict__ rs, const RefineTile* __restrict__ tiles) {
     short_kernel_priority();
-    const RefineTile tile = tiles[blockIdx.x];
-    const RefineScan a = rs[tile.entry];
-    size_t ig; uint32_t blk, plane;
-    if (!refine_block_of_lane(R, a, tile.chunk, &ig, &blk, &plane)) return;
-    uint64_t* rec = R.masks + R.mask_off[ig];
+    RefinePlace P;
+    refine_place(R, rs, tiles, &P);
+    const uint32_t b = P.chunk * 256 + threadIdx.x, plane = P.plane;
+    if (P.status != (uint32_t)kOk || b >= P.ncov) return;
+    const uint32_t blk = (b / P.cw) * P.bw + (b % P.cw);
+    uint64_t* rec = R.masks + P.mask;
     rec[ref_word(kRefPlus, blk, plane)] = deal_bits(rec[ref_word(kRefPlus, blk, plane)], rec[ref_word(kRefHist, blk, plane)]);
 }
 
 __global__ void __launch_bounds__(256) k_refine_blocks(DevRecord R, const RefineScan* __restrict__ rs, const RefineTile* __restrict__ tiles) {
-    __shared__ AcTab tab;
+    __shared__ __attribute__((aligned(16))) AcTab tab;
     short_kernel_priority();
-    const RefineTile tile = tiles[blockIdx.x];
-    const RefineScan a = rs[tile.entry];
-    if (R.status[a.img] != kOk) return;
-    const ImgDesc* img = &R.img[a.img];
-    const size_t ig = (size_t)a.img * R.G + a.scan;
-    const ScanDesc* sd = &R.scan[ig];
-    const int c = sd->comp[0];
-    const uint32_t cw = img->cw[c], ncov = cw * img->ch[c];
-    if (tile.chunk * 256 >= ncov) return;
+    RefinePlace P;
+    refine_place(R, rs, tiles, &P);
+    if (P.status != (uint32_t)kOk || P.chunk * 256 >= P.ncov) return;
+    const uint32_t b = P.chunk * 256 + threadIdx.x, at = b < P.ncov ? b : P.ncov - 1;
+    const size_t blk = (size_t)(at / P.cw) * P.bw + (at % P.cw), plane = P.plane;
+    uint64_t* rec = R.masks + P.mask;
+    // (the block's words and its unit's start are on their way while the table is)
+    const uint64_t h = rec[ref_word(kRefHist, blk, plane)], st = rec[ref_word(kRefStart, blk, plane)], newm = rec[ref_word(kRefNz, blk, plane)];   // (h: the history phase 1 worked on)
+    const uint32_t start = R.ivl_start[P.slot + (P.S.ri ? at / P.S.ri : 0)];
     {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(&R.tabs[R.tab_idx[ig]]);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(&tab);
-        for (uint32_t e = threadIdx.x; e < offsetof(AcTab, lutp) / 4; e += 256) dst[e] = src[e];   // (what ac_code reads)
+        constexpr uint32_t kPieces = offsetof(AcTab, lutp) / 16;                     // (what ac_code reads)
+        const uint4* src = reinterpret_cast<const uint4*>(&R.tabs[P.tab]);
+        if (threadIdx.x < kPieces) reinterpret_cast<uint4*>(&tab)[threadIdx.x] = src[threadIdx.x];
     }
+    arrived(h); arrived(st); arrived(newm); arrived(start);
     __syncthreads();
-    const uint32_t b = tile.chunk * 256 + threadIdx.x;
-    if (b >= ncov) return;
-    const uint32_t bw = img->bw[c];
-    const size_t blk = (size_t)(b / cw) * bw + (b % cw);
-    const size_t plane = (size_t)bw * img->bh[c];
-    uint64_t* rec = R.masks + R.mask_off[ig];
-    const uint64_t h = rec[ref_word(kRefHist, blk, plane)];  // the history phase 1 worked on
-    const uint32_t ivl = sd->ri ? b / sd->ri : 0;
-    const uint32_t* words = reinterpret_cast<const uint32_t*>(R.clean + clean_base(sd->data_off));
+    if (b >= P.ncov) return;
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(R.clean + clean_base(P.S.data_off));
     uint64_t sgn, plus;
-    refine_block(words, R.ivl_start[R.slot_base[ig] + ivl], rec[ref_word(kRefStart, blk, plane)], &tab, h, rec[ref_word(kRefNz, blk, plane)], sd->Ss, sd->Se, &sgn, &plus);
+    refine_block(words, start, st, &tab, h, newm, P.S.Ss, P.S.Se, &sgn, &plus);
     rec[ref_word(kRefSign, blk, plane)] = sgn; rec[ref_word(kRefPlus, blk, plane)] = plus;
 }
 
@@ -1627,22 +1665,6 @@ PCR_D void rgb_words(const float y[4], const float u[4], const float v[4], uint3
         PCR_ROUND_NEAREST
         : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2])
         : "v"(r[0]), "v"(g[0]), "v"(b[0]), "v"(r[1]), "v"(g[1]), "v"(b[1]), "v"(r[2]), "v"(g[2]), "v"(b[2]), "v"(r[3]), "v"(g[3]), "v"(b[3]));
-}
-
-// a value per component, picked by a per-lane component number out of three wave-uniform ones
-PCR_D uint32_t pick3(uint32_t c, uint32_t a0, uint32_t a1, uint32_t a2) { return c == 0 ? a0 : (c == 1 ? a1 : a2); }
-
-// an image's descriptor through a wave-uniform pointer, as dwords
-PCR_D void load_desc(const ImgDesc* ip, ImgDesc* D) {
-    const __attribute__((address_space(4))) uint32_t* src = (const __attribute__((address_space(4))) uint32_t*)ip;
-    uint32_t* dst = reinterpret_cast<uint32_t*>(D);
-#pragma unroll
-    for (uint32_t e = 0; e < sizeof(ImgDesc) / 4; e++) dst[e] = src[e];
-}
-PCR_D void wanted_now(const ImgDesc& D) {
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(&D);
-#pragma unroll
-    for (uint32_t e = 0; e < sizeof(ImgDesc) / 4; e++) wanted_now(w[e]);
 }
 
 // What the pixel kernels need to know about an image, all wave-uniform (read through a wave-uniform pointer, so
