@@ -84,7 +84,7 @@ PCR_HD int parse_record_header(const uint8_t* bytes, uint64_t nbytes, RecordHead
 // The walk over a region's segments (walk_region) needs nothing from other regions; what a scan takes over from
 // earlier ones -- tables in force, restart interval, the scans it refines -- is put together afterwards
 // (resolve_scan, scan_history).  The host goes through an image's regions one by one (parse_image), the device
-// walks all of them at once, one lane each (k_headers).
+// walks all of them at once, a wavefront each (k_headers).
 // ---------------------------------------------------------------------------------------
 struct RegionWalk {
     uint32_t dht[8];                       // offset of BITS of the table this region last defines for class * 4 + id (0: none)
@@ -97,6 +97,7 @@ struct RegionWalk {
 // Bytes p .. p + 23, little endian; what lies at `end` or behind it says nothing.
 PCR_HD void bytes24(const uint8_t* rec, uint32_t p, uint32_t end, uint64_t v[3]) {
     v[0] = v[1] = v[2] = 0;
+    if (end - p >= 24) { __builtin_memcpy(v, rec + p, 24); return; }
     for (uint32_t b = 0; b < 24; b++) if (b < end - p) v[b >> 3] |= (uint64_t)rec[p + b] << (8 * (b & 7));
 }
 PCR_HD uint32_t byte_of(uint64_t v, uint32_t b) { return (uint32_t)(v >> (8 * b)) & 255u; }
