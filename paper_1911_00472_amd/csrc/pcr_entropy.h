@@ -304,64 +304,102 @@ __device__ inline void write_lane(uint32_t& v, uint32_t value, uint32_t lane) {
 }
 #endif
 
+// On the device the stream comes through LDS: kStageWords of it at a time, the next ones under way in registers meanwhile, and
+// every lane reads the two words its 32 bits lie in a window ahead.  A window then costs one read and one shift of a lane where
+// three scalar words were handed on, two more fetched -- a scalar load comes back with the wait for the look-up -- and the lanes'
+// bits picked from them: a gray scan of 92 000 coefficients 4.00 -> 3.62 ms, its refinements 4.60 -> 4.43 and 3.99 -> 3.83 ms,
+// plain photographs at scan group 10 5.66 -> 5.42 ms.  (The same feed from a vector register, words picked by scalar reads across
+// lanes, was slower than the scalar loads.)
+constexpr uint32_t kStageWords = 128, kStageWindows = (kStageWords - 2) / 2;
 struct WindowReader {
-    StreamPtr p;                // words after n1
     const AcTab* tab;
     uint32_t lim8, sh2;         // of tab (see packed_index)
-    uint32_t w0, w1, w2, n0, n1;
     uint32_t o;                 // offset of the next unread bit inside the window (may run past 63 until normalised)
     uint32_t wbase;             // bits of the stream before the window
     uint32_t mis_bits, total_bits;
     uint32_t lane;              // this lane's offset (device); unused on the host
     uint32_t vinfo;             // this lane's packed word (device)
     uint32_t vstep;             // ... and what it moves the decoder on by, as the symbol loops add it up (see first_step, refine_step)
-    const uint32_t* g;          // p again, for the vector memory path
-    uint32_t vnext;             // device: even lanes p[0], odd lanes p[1], fetched one window ahead (see slide)
     bool first;
-    bool vfeed;                 // fetch the stream through the vector memory path (see fetch_next)
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef __attribute__((address_space(3))) uint32_t* LdsWords;
+    LdsWords stage;             // kStageWords words
+    const uint32_t* g;          // the stream
+    uint32_t at, last;          // word of the stream the staged ones begin at; last word that is read
+    uint32_t left;              // windows of the stage whose words have not been read yet
+    uint32_t vwin;              // this lane's 32 bits
+    uint32_t vp0, vp1;          // the two words of the next window's
+    LdsWords vat;               // where those of the one after it lie in the stage
+    uint32_t va, vb;            // the next words of the stream, on their way
+#else
+    StreamPtr p;                // words after n1
+    uint32_t w0, w1, w2, n0, n1;
+#endif
 
     // The unit starts sub_bits (0..7) bits into byte byte_off of the segment and holds nbits bits counted from that
     // byte's first bit; pos0: what position() reports for the byte's first bit (0: positions relative to the unit's
     // first byte, as for restart intervals; byte_off * 8: positions in the scan, as for units that start at entry points).
     PCR_HD void init(const uint32_t* words, uint32_t byte_off, uint32_t sub_bits, uint32_t nbits, uint32_t pos0, const AcTab* t, bool first_scan,
-                     uint32_t lane_id, bool vector_feed) {
-        first = first_scan; lane = lane_id; vfeed = vector_feed;
+                     uint32_t lane_id, uint32_t* lds) {
+        first = first_scan; lane = lane_id;
         take_table(t);
         mis_bits = (byte_off & 3) * 8;
+        o = mis_bits + sub_bits; wbase = pos0; total_bits = pos0 + nbits + mis_bits;
+#if defined(__HIP_DEVICE_COMPILE__)
+        stage = (LdsWords)lds; g = words + (byte_off >> 2);
+        last = ((nbits + mis_bits) >> 5) + 4;
+        at = 0u - 2 * kStageWindows;
+        fetch();
+        restage();
+        ahead(); take(); ahead();
+#else
+        (void)lds;
         p = stream_ptr(words + (byte_off >> 2));
         w0 = p[0]; w1 = p[1]; w2 = p[2]; n0 = p[3]; n1 = p[4]; p += 5;
-        g = words + (byte_off >> 2) + 5;
-        o = mis_bits + sub_bits; wbase = pos0; total_bits = pos0 + nbits + mis_bits;
-        vnext = 0;
-        fetch_next();
+#endif
         fill();
     }
-    // With vfeed the two words after n1 are fetched by the vector unit, one per lane parity, although they are the
-    // same for all lanes: a scalar load is waited for together with the LDS look-up that follows it in fill()
-    // (scalar loads and LDS share a counter and scalar loads return out of order), a window before it is needed.
-    // A decoder that keeps other vector loads in flight (the refinement history) is better off with the scalar
-    // load: the vector counter is in order, and the wait for these words would take the younger loads with it.
-    PCR_HD void fetch_next() {
 #if defined(__HIP_DEVICE_COMPILE__)
-        if (vfeed) vnext = g[lane & 1];
-#endif
+    __device__ void fetch() {                                 // the words behind the stage's windows
+        const uint32_t a = at + 2 * kStageWindows + lane, b = a + 64;
+        va = g[a < last ? a : last]; vb = g[b < last ? b : last];
     }
-    PCR_HD void slide() {                                     // on by 64 bits
-        w0 = w2; w1 = n0; w2 = n1;
-#if defined(__HIP_DEVICE_COMPILE__)
-        if (vfeed) { n0 = (uint32_t)__builtin_amdgcn_readlane((int)vnext, 0); n1 = (uint32_t)__builtin_amdgcn_readlane((int)vnext, 1); }
-        else { n0 = p[0]; n1 = p[1]; }
-#else
-        n0 = p[0]; n1 = p[1];
+    __device__ void restage() {
+        at += 2 * kStageWindows;
+        stage[lane] = va; stage[64 + lane] = vb;
+        // (a lane whose bits are one whole word reads it as the second of the two: the shift below goes from 0 to 31.  Lane 0 then
+        // reads the word ahead of the stage, which is the end of the table, and uses nothing of it.)
+        vat = stage + (int)((lane >> 5) - ((lane & 31) == 0 ? 1 : 0));
+        left = kStageWindows;
+        fetch();
+    }
+    __device__ void ahead() {
+        vp0 = vat[0]; vp1 = vat[1];
+        vat += 2;
+        left = opaque(left - 1);
+        if (__builtin_expect(left == 0, 0)) restage();
+    }
+    __device__ void take() { vwin = __builtin_amdgcn_alignbit(vp0, vp1, 32 - lane); }
+    __device__ void skip(uint32_t n) {                        // n windows nobody asks for
+        while (n) {
+            const uint32_t m = n < left ? n : left;
+            vat += 2 * m; left -= m; n -= m;
+            if (left == 0) restage();
+        }
+    }
 #endif
-        p += 2; g += 2; o -= 64; wbase += 64;
-        fetch_next();
+    PCR_HD uint32_t win_at(uint32_t off) const {              // the 32 bits at an offset of the window
+#if defined(__HIP_DEVICE_COMPILE__)
+        return (uint32_t)__builtin_amdgcn_readlane((int)vwin, (int)off);
+#else
+        return bits_at(w0, w1, w2, (int)off);
+#endif
     }
     PCR_HD void take_table(const AcTab* t) { tab = t; lim8 = uni(t->limit[0]); sh2 = uni(t->sh2); }
     PCR_HD uint32_t word_of(uint32_t win) const { return finish_packed(tab->lutp[packed_index(win, lim8, sh2)], win, first); }
     PCR_HD void fill() {
 #if defined(__HIP_DEVICE_COMPILE__)
-        vinfo = word_of(bits_at(w0, w1, w2, (int)lane));
+        vinfo = word_of(vwin);
         vstep = first ? first_step(vinfo) : refine_step(vinfo);
 #endif
     }
@@ -370,26 +408,38 @@ struct WindowReader {
 #if defined(__HIP_DEVICE_COMPILE__)
         return (uint32_t)__builtin_amdgcn_readlane((int)vinfo, (int)off);
 #else
-        return word_of(bits_at(w0, w1, w2, (int)off));
+        return word_of(win_at(off));
 #endif
     }
     // the same for an offset that lookup() answered with kSymMiss: a code neither look-up resolves, or garbage
     PCR_HD uint32_t resolve(uint32_t off) const {
-        const uint32_t win = bits_at(w0, w1, w2, (int)off);
+        const uint32_t win = win_at(off);
         const uint32_t e = ac_long_code(tab, win);
         return uni(e ? pack_symbol(e, win, first) : kSymInvalid);
     }
     PCR_HD bool exhausted() const { return o >= 64; }         // the next symbol starts beyond the window
     PCR_HD void refill() {
-        do slide(); while (o >= 64);
+#if defined(__HIP_DEVICE_COMPILE__)
+        if (!first && __builtin_expect(o >= 128, 0)) {      // (a first scan moves on by 31 bits at a time)
+            const uint32_t n = (o >> 6) - 1;
+            o -= 64 * n; wbase += 64 * n;
+            skip(n - 1); ahead();
+        }
+        o -= 64; wbase += 64;
+        take();
         fill();
+        ahead();
+#else
+        do { w0 = w2; w1 = n0; w2 = n1; n0 = p[0]; n1 = p[1]; p += 2; o -= 64; wbase += 64; } while (o >= 64);
+        fill();
+#endif
     }
     // Sequential scans switch tables between blocks: the words of the current window are looked up again.
     PCR_HD void use_table(const AcTab* t) { take_table(t); fill(); }
     // Sequential scans: packed DC word (pack_dc) of the symbol at the current position, decoded on the spot;
     // 0 where the bits are no code of the table.
     PCR_HD uint32_t dc_word(const DcTab* t) const {
-        const uint32_t win = bits_at(w0, w1, w2, (int)o);
+        const uint32_t win = win_at(o);
         const uint32_t e = dc_code(t, win);
         return uni(e ? pack_dc(e, win) : 0u);                 // (table reads come back in vector registers)
     }

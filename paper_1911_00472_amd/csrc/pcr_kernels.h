@@ -940,8 +940,8 @@ struct ChainGate {
     }
 };
 
-// What a wavefront keeps in LDS: the AC table of its scan, or the DC tables of its components.
-constexpr uint32_t kWaveTabBytes = sizeof(AcTab);
+// What a wavefront keeps in LDS: the AC table of its scan and the words of the stream it is at, or the DC tables of its components.
+constexpr uint32_t kWaveTabBytes = sizeof(AcTab) + kStageWords * sizeof(uint32_t);
 static_assert(kMaxComp * sizeof(DcTab) <= kWaveTabBytes, "one area serves both");
 
 PCR_D int wave_dc_first(const DevRecord& R, const Unit& un, const UnitSetup& L, DcTab* tabs, uint32_t lane, bool to_planes) {
@@ -983,7 +983,7 @@ PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab*
     wave_sync();
     WindowReader wr;
     if (sd->Ah == 0) {
-        wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, true, lane, true);
+        wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, true, lane, reinterpret_cast<uint32_t*>(tab + 1));
         IndexSink sink;
         sink.init(L.plane[0], L.plane_elems[0], L.ls.Al);
         return decode_ac_first(&wr, L.ls, &sink, gate);
@@ -997,7 +997,7 @@ PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab*
     hp.n = uni(hp.n);
     hp.some = hp.n > 0 ? ~0ull : 0ull;
     if (hp.n == 0) hp.p[0] = reinterpret_cast<const uint64_t*>(hp.coef);   // (16 bytes a block are read of its 128)
-    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, false, lane, false);
+    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, false, lane, reinterpret_cast<uint32_t*>(tab + 1));
     return skim_ac_refine(&wr, L.ls, hp, R.masks + uni((uint64_t)R.mask_off[ig]), L.plane_elems[0] >> 6, gate);
 }
 
@@ -1157,6 +1157,8 @@ __global__ void __launch_bounds__(kEntropyLanes, 4) k_first_lanes(DevRecord R, c
 // units k_sequential_split has dealt with.
 __global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const Unit* __restrict__ units, const uint32_t* __restrict__ done,
         const uint32_t* __restrict__ clean32) {
+    __shared__ uint32_t stage_[1 + kStageWords];            // (a word is read ahead of it)
+    uint32_t* stage = stage_ + 1;
     __shared__ DcTab dtabs[kMaxComp];
     __shared__ AcTab atabs[kMaxComp];
     if (done && done[blockIdx.x]) return;
@@ -1189,7 +1191,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const
     tb.dc[0] = &dtabs[0]; tb.dc[1] = &dtabs[uni(dj1)]; tb.dc[2] = &dtabs[uni(dj2)];
     tb.ac[0] = &atabs[0]; tb.ac[1] = &atabs[uni(aj1)]; tb.ac[2] = &atabs[uni(aj2)];
     WindowReader wr;
-    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tb.ac[0], true, threadIdx.x, true);
+    wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tb.ac[0], true, threadIdx.x, stage);
     IndexSink sink;
     sink.init(L.base, L.base_elems, 0, R.dc + (uni((uint64_t)R.coef_off[un.img]) >> 6));
     const int rc = decode_sequential(&wr, L.ls, tb, &sink);

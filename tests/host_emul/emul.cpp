@@ -130,7 +130,7 @@ extern "C" int emul_decode_record(const uint8_t* rec, size_t nbytes, int k, int6
                 SeqTables tb;
                 for (int q = 0; q < kMaxComp; q++) { tb.dc[q] = &dt[q]; tb.ac[q] = &at[q]; }
                 WindowReader sw;
-                sw.init(reinterpret_cast<const uint32_t*>(clean.data()), byte_off, sub_bits, nbits, pos0, tb.ac[0], true, 0, true);
+                sw.init(reinterpret_cast<const uint32_t*>(clean.data()), byte_off, sub_bits, nbits, pos0, tb.ac[0], true, 0, nullptr);
                 IndexSink ssink; ssink.init(coef.data(), (uint32_t)coef.size(), 0);
                 rc = decode_sequential(&sw, ls, tb, &ssink);
             } else if (sd.Ss == 0 && by_lane && img.progressive && sd.Ah == 0) {
@@ -176,7 +176,7 @@ extern "C" int emul_decode_record(const uint8_t* rec, size_t nbytes, int k, int6
                                                              : lane_decode_ac_refine<false>(U, masks[g].data(), (uint32_t)plane, &ring, &hring, 0));
             } else {
                 AcTab at; actab_build(&at, rec + sd.ac_off); actab_pack(&at, sd.Ah == 0, 0, 1);
-                WindowReader wr; wr.init(reinterpret_cast<const uint32_t*>(clean.data()), byte_off, sub_bits, nbits, pos0, &at, sd.Ah == 0, 0, sd.Ah == 0);
+                WindowReader wr; wr.init(reinterpret_cast<const uint32_t*>(clean.data()), byte_off, sub_bits, nbits, pos0, &at, sd.Ah == 0, 0, nullptr);
                 if (sd.Ah == 0) {
                     IndexSink sink; sink.init(cpl[0], (uint32_t)plane * 64, ls.Al);
                     rc = decode_ac_first(&wr, ls, &sink);
