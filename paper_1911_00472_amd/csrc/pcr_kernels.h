@@ -622,15 +622,72 @@ PCR_D void unstuff_scan(const DevRecord& R, uint32_t i, uint32_t g, uint8_t* buf
     }
 }
 
-// Workgroups [0, P.first[P.count] + kDies * F.rows): fill_turn says which of them fill, the others unstuff.  (Every second
+struct ApplyUnit { uint32_t img; uint32_t comp; };
+struct ApplyScan { uint64_t mask_off; uint32_t slot; uint32_t data_base; uint32_t mcu_w; uint16_t ri; uint8_t Ss, Se, Ah, Al, ns, before, bpm, pad[3]; };
+struct ApplyList { uint32_t n, nac; ApplyScan sc[kApplyMaxScans]; };       // AC scans first (nac of them), then DC scans; both in file order
+// The lists of a call (none: nau = 0), made by the first `groups` workgroups of the unstuffing launch.
+struct ApplyJob { const ApplyUnit* au; ApplyList* lists; uint32_t nau, kmax, groups; };
+
+// Gathers, per (image, component), the scans that matter for refinement (AC scans of the component in file order, DC
+// refinement scans) into a compact list.
+// A wavefront per (image, component), a lane per scan: the loads of all scans are under way together.  (A lane per image
+// and component walking its scans took 9.4 us for 1024 images, nearly all of it waiting for one load after another.)
+constexpr int kApplyPrepWaves = 4;
+static_assert(kApplyPrepWaves == (int)kUnstuffWaves, "they share a launch");
+PCR_D void apply_prep(const DevRecord& R, const ApplyUnit* __restrict__ au, uint32_t nau, uint32_t kmax, ApplyList* lists, uint32_t group) {
+    const uint32_t u = group * kApplyPrepWaves + uni(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    if (u >= nau) return;
+    const ApplyUnit a = au[u];
+    const ImgDesc* img = &R.img[a.img];
+    const uint32_t c = a.comp;
+    ApplyList* L = &lists[u];
+    const uint32_t upto = img->nscans < kmax ? img->nscans : kmax;
+    uint32_t n = 0;
+    for (uint32_t dc = 0; dc < 2; dc++) {                    // (AC first scans are in the planes already)
+        for (uint32_t g0 = 0; g0 < upto; g0 += 64) {
+            const uint32_t g = g0 + lane;
+            const size_t ig = (size_t)a.img * R.G + (g < upto ? g : 0u);
+            const ScanDesc sd = R.scan[ig];
+            ApplyScan e;
+            e.Ss = sd.Ss; e.Se = sd.Se; e.Ah = sd.Ah; e.Al = sd.Al; e.ns = sd.ns; e.ri = sd.ri; e.mcu_w = sd.mcu_w;
+            e.mask_off = R.mask_off[ig]; e.slot = R.slot_base[ig]; e.data_base = clean_base(sd.data_off);
+            e.before = 0; e.bpm = 0; e.pad[0] = e.pad[1] = e.pad[2] = 0;
+            bool has = false;
+            uint32_t before = 0, bpm = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < (uint32_t)kMaxComp; q++) {
+                if (q >= sd.ns) continue;
+                const uint32_t cq = sd.comp[q];
+                if (cq == c) { has = true; before = bpm; }
+                bpm += sd.ns > 1 ? (uint32_t)img->hs[cq] * img->vs[cq] : 1u;
+            }
+            if (dc) { e.before = (uint8_t)before; e.bpm = (uint8_t)bpm; } else has = sd.comp[0] == c;
+            const bool take = g < upto && sd.Ah != 0 && (sd.Ss == 0 ? 1u : 0u) == dc && has;
+            const uint64_t all = __builtin_amdgcn_ballot_w64(take);
+            const uint32_t at = n + (uint32_t)__builtin_popcountll(all & ((1ull << lane) - 1u));
+            if (take && at < (uint32_t)kApplyMaxScans) L->sc[at] = e;
+            n += (uint32_t)__builtin_popcountll(all);
+        }
+        n = n < (uint32_t)kApplyMaxScans ? n : (uint32_t)kApplyMaxScans;
+        if (!dc && lane == 0) L->nac = n;
+    }
+    if (lane == 0) L->n = n;
+}
+// (a launch of its own while stage timing is on)
+__global__ void __launch_bounds__(64 * kApplyPrepWaves) k_apply_prep(DevRecord R, ApplyJob A) { apply_prep(R, A.au, A.nau, A.kmax, A.lists, blockIdx.x); }
+
+// Workgroups [0, A.groups) make the refinement lists: a launch of their own behind the entropy decoders took 5.5 us and the gap to the next
+// (64 gray pictures at scan group 6 186 -> 182 us a call, 256 ragged ones 364 -> 359).  A multiple of kDies, so that the others keep their dies.
+// The other P.first[P.count] + kDies * F.rows: fill_turn says which of them fill, the others unstuff.  (Every second
 // or fourth single workgroup, as before, put the whole fill on four or two of the eight dies: 202 and 214 us for 1024
 // photographs at scan groups 9 and 10, of which the 0.5 GB fill is the larger part, against 118 and 131.)
-__global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period) {
+__global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period, ApplyJob A) {
     __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffWaves * (kUnstuffStep + 32)];
     __shared__ uint32_t tot[kUnstuffWaves];
     short_kernel_priority();
     const uint32_t tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
-    const FillTurn turn = fill_turn(blockIdx.x, F.rows, period);
+    if (blockIdx.x < A.groups) { apply_prep(R, A.au, A.nau, A.kmax, A.lists, blockIdx.x); return; }
+    const FillTurn turn = fill_turn(blockIdx.x - A.groups, F.rows, period);
     if (turn.fills) {
         for (int f = 0; f < kMaxFills; f++) {
             uint4* p = F.p[f];
@@ -1198,7 +1255,6 @@ __global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const
     if (rc != kOk) R.status[un.img] = rc;
 }
 
-struct ApplyUnit { uint32_t img; uint32_t comp; };
 
 // Phase 2 of AC refinement: one lane per block of the scan.
 struct RefineScan { uint32_t img; uint32_t scan; };
@@ -1346,11 +1402,8 @@ __global__ void __launch_bounds__(256) k_refine_blocks(DevRecord R, const Refine
 //   k > 0: replay the AC scans of the component in file order: first scans only extend the
 //          non-zero mask, refinement scans add a correction bit or place a new +-2^Al.
 // --------------------------------------------------------------------------------------
-// k_apply_prep gathers, once per (image, component), the scans that matter for refinement (AC
-// scans of the component in file order, DC refinement scans) into a compact list; k_apply then
+// k_apply_prep (apply_prep) has gathered, per (image, component), the scans that matter for refinement; k_apply then
 // runs one lane per coefficient, a workgroup covering kApplyChunk consecutive coefficients.
-struct ApplyScan { uint64_t mask_off; uint32_t slot; uint32_t data_base; uint32_t mcu_w; uint16_t ri; uint8_t Ss, Se, Ah, Al, ns, before, bpm, pad[3]; };
-struct ApplyList { uint32_t n, nac; ApplyScan sc[kApplyMaxScans]; };       // AC scans first (nac of them), then DC scans; both in file order
 constexpr uint32_t kApplyChunk = 4096;
 
 // DC refinement of the block at (row, col) of a component with sampling hs x vs: the block's bit sits at
@@ -1364,49 +1417,6 @@ PCR_D uint32_t dc_refinement_bit(const DevRecord& R, const ApplyScan& S, uint32_
     const uint32_t bit = (m - ivl * S.ri) * S.bpm + within;
     const uint32_t* words = reinterpret_cast<const uint32_t*>(R.clean + S.data_base);
     return (uint32_t)dc_refine_bit(words, R.ivl_start[S.slot + ivl], bit);
-}
-
-// A wavefront per (image, component), a lane per scan: the loads of all scans are under way together.  (A lane per image
-// and component walking its scans took 9.4 us for 1024 images, nearly all of it waiting for one load after another.)
-constexpr int kApplyPrepWaves = 4;
-__global__ void __launch_bounds__(64 * kApplyPrepWaves) k_apply_prep(DevRecord R, const ApplyUnit* __restrict__ au, uint32_t nau, uint32_t kmax, ApplyList* lists) {
-    const uint32_t u = blockIdx.x * kApplyPrepWaves + uni(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-    if (u >= nau) return;
-    const ApplyUnit a = au[u];
-    const ImgDesc* img = &R.img[a.img];
-    const uint32_t c = a.comp;
-    ApplyList* L = &lists[u];
-    const uint32_t upto = img->nscans < kmax ? img->nscans : kmax;
-    uint32_t n = 0;
-    for (uint32_t dc = 0; dc < 2; dc++) {                    // (AC first scans are in the planes already)
-        for (uint32_t g0 = 0; g0 < upto; g0 += 64) {
-            const uint32_t g = g0 + lane;
-            const size_t ig = (size_t)a.img * R.G + (g < upto ? g : 0u);
-            const ScanDesc sd = R.scan[ig];
-            ApplyScan e;
-            e.Ss = sd.Ss; e.Se = sd.Se; e.Ah = sd.Ah; e.Al = sd.Al; e.ns = sd.ns; e.ri = sd.ri; e.mcu_w = sd.mcu_w;
-            e.mask_off = R.mask_off[ig]; e.slot = R.slot_base[ig]; e.data_base = clean_base(sd.data_off);
-            e.before = 0; e.bpm = 0; e.pad[0] = e.pad[1] = e.pad[2] = 0;
-            bool has = false;
-            uint32_t before = 0, bpm = 0;
-#pragma unroll
-            for (uint32_t q = 0; q < (uint32_t)kMaxComp; q++) {
-                if (q >= sd.ns) continue;
-                const uint32_t cq = sd.comp[q];
-                if (cq == c) { has = true; before = bpm; }
-                bpm += sd.ns > 1 ? (uint32_t)img->hs[cq] * img->vs[cq] : 1u;
-            }
-            if (dc) { e.before = (uint8_t)before; e.bpm = (uint8_t)bpm; } else has = sd.comp[0] == c;
-            const bool take = g < upto && sd.Ah != 0 && (sd.Ss == 0 ? 1u : 0u) == dc && has;
-            const uint64_t all = __builtin_amdgcn_ballot_w64(take);
-            const uint32_t at = n + (uint32_t)__builtin_popcountll(all & ((1ull << lane) - 1u));
-            if (take && at < (uint32_t)kApplyMaxScans) L->sc[at] = e;
-            n += (uint32_t)__builtin_popcountll(all);
-        }
-        n = n < (uint32_t)kApplyMaxScans ? n : (uint32_t)kApplyMaxScans;
-        if (!dc && lane == 0) L->nac = n;
-    }
-    if (lane == 0) L->n = n;
 }
 
 __global__ void __launch_bounds__(256) k_apply(DevRecord R, const ApplyUnit* __restrict__ au, const ApplyList* __restrict__ lists) {

@@ -554,7 +554,7 @@ void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bo
 // Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, rows of filling
 // workgroups spread evenly between the others (fill_turn) so that they run beside them all the way (as many as unstuff at
 // most, or they would go ahead of them; 1024 where that is more: there is room for all at once).
-void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, hipStream_t s) {
+void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, const ApplyJob& lists, hipStream_t s) {
     const uint32_t n = r->hdr.n, count = k - k0;
     UnstuffPlan P{};
     uint64_t mean[kMaxGroups];
@@ -577,9 +577,9 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, hipSt
     size_t pieces = 0;
     for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
     fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 2047) / 2048, std::min<size_t>(2048, std::max<size_t>(groups, 1024))));   // (eight pieces per lane, but for the last row)
-    const uint32_t total = groups + kDies * fill.rows;
+    const uint32_t total = lists.groups + groups + kDies * fill.rows;
     if (total == 0) return;
-    hipLaunchKernelGGL(k_unstuff, dim3(total), dim3(64 * kUnstuffWaves), 0, s, r->d, P, fill, fill_period(groups, fill.rows));
+    hipLaunchKernelGGL(k_unstuff, dim3(total), dim3(64 * kUnstuffWaves), 0, s, r->d, P, fill, fill_period(groups, fill.rows), lists);
 }
 
 // Steps 1-5 of the path (index .. entropy decode + refinement) for scans 1..k.
@@ -646,7 +646,11 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     if (k0 == 0 && !plan->dc_complete) {                     // a component whose DC scan is not among the scans decoded reads as zero
         fill.p[1] = (uint4*)r->d.dc; fill.n16[1] = (r->coef_off[n] / 64 * sizeof(int16_t) + 15) / 16;
     }
-    launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, s);
+    // (with stage timing on the lists are a launch of their own: the stage that uses them is theirs)
+    ApplyJob lists{plan->d_apply, plan->d_apply_lists, plan->n_apply, (uint32_t)k, 0};
+    const uint32_t list_groups = (plan->n_apply + kApplyPrepWaves - 1) / kApplyPrepWaves;
+    if (!r->timing) lists.groups = (list_groups + kDies - 1) / kDies * kDies;
+    launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, lists, s);
     mark(r, PCR_STAGE_UNSTUFF, s);
     const uint32_t* c32 = reinterpret_cast<const uint32_t*>(r->d.clean);
     auto waves = [&](const LevelList& l) {
@@ -702,7 +706,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         }
     }
     if (plan->n_apply) {
-        hipLaunchKernelGGL(k_apply_prep, dim3((plan->n_apply + kApplyPrepWaves - 1) / kApplyPrepWaves), dim3(64 * kApplyPrepWaves), 0, s, r->d, plan->d_apply, plan->n_apply, (uint32_t)k, plan->d_apply_lists);
+        if (!lists.groups) hipLaunchKernelGGL(k_apply_prep, dim3(list_groups), dim3(64 * kApplyPrepWaves), 0, s, r->d, lists);
         if (refine_in_memory)
             hipLaunchKernelGGL(k_apply, dim3(plan->apply_grid_x, plan->n_apply), dim3(256), 0, s, r->d, plan->d_apply, plan->d_apply_lists);
     }
