@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(256) k_index(DevRecord R, uint32_t kmax) {
 
 // --------------------------------------------------------------------------------------
 // k_headers: the marker segments of one image per workgroup, and the Huffman tables of its scans.
-//   1. where the regions of scan groups 0 .. kmax-1 lie: the offsets k_index left, or (own_index, small records, one
+//   1. where the regions of scan groups 0 .. kmax-1 lie: the offsets k_index left, or (own_index, most records, one
 //      launch fewer) the sum of the lengths ahead of the image's, taken here;
 //   2. the first bytes of every region into LDS, all of them at once -- a walk over marker segments is a chain of
 //      reads that depend on one another, and from memory each of them is a trip of a microsecond;
@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(256) k_index(DevRecord R, uint32_t kmax) {
 // bytes at a time); with a lane per region, byte reads and the parse's state in vector registers the walk was 28 000 cycles
 // of the 94 000 a workgroup of ten scans took, the search for the scans refined 22 000 and the tables, dealt out by scan, 28 000;
 // now 18 000, 6 000 and 12 000.  us for 64 gray pictures of 6 scans 22.8 -> 16.2, small ragged ones of 10 scans 43.0 -> 26.6,
-// 1024 of 256 x 256 at scan group 5 38.5 -> 27.2 (k_index: 8 more), 512 photographs of 10 scans 48.9 -> 30.8.
+// 1024 of 256 x 256 at scan group 5 38.5 -> 27.2 (with k_index ahead of it, 8 more), 512 photographs of 10 scans 48.9 -> 30.8.
 // Workgroups have a wavefront per scan group, kHeaderWaves at most: with eight of them at every scan group, of which seven
 // had nothing to do at scan group 1, the kernel stood in the way of the pixel writers of other records (four records
 // in flight, ms per step at scan groups 1 and 2: 0.745 and 2.18, now 0.675 and 2.08; alone nothing changes).  Records
@@ -154,7 +154,11 @@ constexpr int kHeaderWaves = 8, kHeaderLanes = 64 * kHeaderWaves;
 constexpr uint32_t kMaxGroups = 64;                        // (parse_record_header refuses more)
 constexpr uint32_t kHeaderStage = 16384;                   // bytes of LDS for the heads of the regions, shared out evenly
 constexpr uint32_t kHeaderWindow = 1024;                   // ... but at most this much per region (a first region with its tables is 600-700 bytes)
-constexpr uint32_t kOwnIndexImages = 512;                  // own_index up to this many images (a workgroup sums n lengths per scan group)
+constexpr uint32_t kHeaderWideImages = 512;                // kHeaderWaves wavefronts per workgroup whatever the scan group up to this many images
+// own_index up to this many images (a workgroup sums n lengths per scan group), but beyond half of it only where every wavefront
+// has one scan group at most.  us a call with k_index / without: 1024 pictures of 256 x 256 at scan group 5 280 / 273, four records of
+// 1024 photographs at 1 708 / 695, at 10 6022 / 6042.
+constexpr uint32_t kOwnIndexImages = 1024;
 
 // Record bytes by record offset: from the staged window, or (past it: long comments and profiles) from memory.
 // (The address spaces are spelled out: through two generic pointers every read became a flat one.)
@@ -262,15 +266,19 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
     if (upto > kMaxGroups) upto = kMaxGroups;               // (cannot happen: the header check refuses such records)
     // ---- where the regions lie ----
     if (own_index) {
-        for (uint32_t g = wave; g < upto; g += waves) {      // (all of a group's loads at once: kOwnIndexImages / 64 lengths per lane)
+        for (uint32_t g = wave; g < upto; g += waves) {      // (512 of a group's loads at once, eight lengths per lane)
             const uint32_t* len = R.len + (size_t)g * n;
             const uint64_t start = ld_le64(R.rec + (g == 0 ? 16 : hdr_group_end_pos(g - 1)));
             const uint32_t mine = len[i];
-            uint32_t t[kOwnIndexImages / 64], before = 0;
+            constexpr uint32_t kHalf = kOwnIndexImages / 2 / 64;
+            uint32_t before = 0;
+            for (uint32_t first = 0; first < i; first += 64 * kHalf) {
+                uint32_t t[kHalf];
 #pragma unroll
-            for (uint32_t j = 0; j < kOwnIndexImages / 64; j++) t[j] = len[64 * j + lane < i ? 64 * j + lane : i];
+                for (uint32_t j = 0; j < kHalf; j++) { const uint32_t at = first + 64 * j + lane; t[j] = len[at < i ? at : i]; }
 #pragma unroll
-            for (uint32_t j = 0; j < kOwnIndexImages / 64; j++) before += 64 * j + lane < i ? t[j] : 0u;
+                for (uint32_t j = 0; j < kHalf; j++) before += first + 64 * j + lane < i ? t[j] : 0u;
+            }
 #pragma unroll
             for (int d = 32; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d);
             if (lane == 0) { s_off[g] = (uint32_t)start + before; s_len[g] = mine; }

@@ -543,12 +543,12 @@ bool split_pays(const LevelList& l) {
 
 // Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
 // regions in the same kernel: a launch costs about as much as k_index runs, and a workgroup of k_headers sums at most
-// kOwnIndexImages lengths per scan group.
+// kOwnIndexImages lengths per scan group (the line: see there).
 void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bool dc_tables, hipStream_t s) {
     const uint32_t n = r->hdr.n;
-    const bool own = n <= kOwnIndexImages;
+    const bool own = n <= kOwnIndexImages / 2 || (n <= kOwnIndexImages && k <= (uint32_t)kHeaderWaves);
     if (!own) hipLaunchKernelGGL(k_index, dim3(k), dim3(256), 0, s, r->d, k);
-    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * (own ? kHeaderWaves : std::min<uint32_t>(k, kHeaderWaves))), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
+    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * (n <= kHeaderWideImages ? kHeaderWaves : std::min<uint32_t>(k, kHeaderWaves))), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
 }
 
 // Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, rows of filling

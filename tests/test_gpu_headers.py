@@ -118,3 +118,10 @@ def test_a_refinement_that_builds_on_as_many_scans_as_can_be():
     files = [pcrgen.encode_pixels(pcrgen.synth(7 + i, 1, 40 + i, 33, 1, 25.0), 1, 1, 95, [dc] + s) for i, s in enumerate((whole, parts))]
     for f in files:
         _same(pcrgen.write_record([f]))
+
+
+@pytest.mark.parametrize("n", [1024, 1025])
+def test_region_offsets_where_the_parser_sums_them_itself(n):
+    """Up to 1024 images the lengths ahead of a region are summed by the parser for scan groups 1 .. 8, beyond by k_index."""
+    few = [pcrgen.make_jpeg(90 + i, 1, 8 + i, 9, 3, 6.0, 1, 1, 80) for i in range(5)]
+    _same(pcrgen.write_record([few[i % 5] for i in range(n)]), images=sorted({0, 63, 64, 511, 512, 513, 1023, n - 1}))
