@@ -41,6 +41,7 @@ struct LevelList {
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
     uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units k_sequential_split has dealt with
     uint32_t n_long = 0; uint64_t long_bytes = 0; bool subsampled = false;        // ... how many those are, their bytes, whether some have MCUs of several blocks per component
+    uint32_t least_lanes = 0;                                                    // DC first scans: units from which the lanes pay (dc_least_lanes)
     bool chained = false;                                                        // the plan's chains hold these units too
 };
 
@@ -301,6 +302,25 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
     return PCR_OK;
 }
 
+// Units from which a launch of DC first scans goes to the lane decoders, by the mean of their blocks and whether the scans are cut.
+// A lane decodes a DC symbol with a fifth of the instructions a wavefront spends on it, but a launch of lanes takes as long as
+// its longest unit, however few there are, and the wavefronts' time a symbol only grows once they fill the scalar units: short
+// units, most of whose time is set-up, are for the lanes early, long ones late; and lanes of one scan read one set of tables.
+// Scan group 1 of one record, us a call by wavefronts / by lanes at 1024, 2048, 3072, 4096, 6144 units:
+//   an entry every 64 MCUs in 4:2:0 (384 blocks)     73 / 88    97 / 98                 138 / 118
+//   the same in 4:4:4 (192)                          64 / 69                             93 / 76  (1072 and 4288 units)
+//   an entry every 128 MCUs (768), 256 x 256        129 / 161  168 / 177   220 / 210    284 / 250    410 / 331
+//   whole scans of  96 x  96 (216)                   95 / 117  137 / 148   172 / 171    204 / 192    259 / 230
+//                  128 x 128 (384)                  114 / 155  157 / 180   205 / 211    248 / 242    343 / 314
+//                  192 x 192 (864)                  159 / 252  231 / 293   310 / 347    399 / 405    530 / 508
+//                  256 x 256 (1536)                 243 / 407  354 / 473   479 / 557    592 / 625    787 / 770
+//                  400 x 400 (3750)                 507 / 901  738 / 1044  958 / 1172  1191 / 1304
+// (four records in flight: 128 x 128, 1024 units each 288 / 344, 4096 780 / 716; 256 x 256, 2048 units 1079 / 1270.)
+uint32_t dc_least_lanes(uint64_t mean_blocks, bool cut) {
+    if (mean_blocks <= 384) return cut ? 2048 : 4096;
+    return mean_blocks <= 768 && cut ? 3072 : 6144;
+}
+
 // Launch geometry for decoding scan groups k0+1 .. k (k0 = 0: from scratch) and turning groups 1 .. k into pixels.
 int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     const int key = k0 * 256 + k;
@@ -403,6 +423,16 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         if (!jobs.empty()) {
             ll.n_jobs = (uint32_t)jobs.size();
             up.add(&ll.d_jobs, jobs);
+        }
+        if (ll.kind == kDcFirst) {
+            uint64_t blocks = 0;
+            for (const Run& q : rn) {
+                const ScanDesc& sd = r->scan[(size_t)q.img * G + q.scan];
+                uint32_t per_mcu = 0;
+                for (int j = 0; j < sd.ns; j++) per_mcu += sd.ns > 1 ? (uint32_t)r->img[q.img].hs[sd.comp[j]] * r->img[q.img].vs[sd.comp[j]] : 1u;
+                blocks += (uint64_t)sd.mcus * per_mcu;
+            }
+            ll.least_lanes = dc_least_lanes(blocks / ll.n, ll.n >= 2 * rn.size());
         }
         if (ll.kind == kSequential) {
             for (const Run& q : rn) {
@@ -508,14 +538,10 @@ bool lanes_pay(const pcr_record* r, const LevelList& l) {
 }
 
 // The same question for a launch of DC first scans by themselves (beside AC first scans by lanes they cost nothing, see
-// with_ac).  A lane decodes a DC symbol with a fifth of the instructions a wavefront spends on it, but a launch of lanes
-// takes as long as one unit, however few there are.  Measured, scan group 1 of one record, an entry every 64 MCUs, us a call by
-// lanes / by wavefronts: 256 x 256 in 4:2:0, 1024 units 88 / 73, 2048 98 / 97, 4096 118 / 138; 400 x 400 in 4:2:0, 1280
-// units 91 / 80, 2560 101 / 104, 10240 188 / 269; 600 x 450 in 4:4:4, 1072 units 69 / 64, 4288 76 / 93, 17152 105 / 205.
-constexpr uint32_t kDcLanesMinUnits = 2048;
+// with_ac; the line: dc_least_lanes).
 bool dc_lanes_pay(const pcr_record* r, const LevelList& l) {
     if (r->lane_mode < 0) return false;
-    return l.n >= (r->lane_mode > 0 ? (uint32_t)kEntropyLanes : kDcLanesMinUnits);
+    return l.n >= (r->lane_mode > 0 ? (uint32_t)kEntropyLanes : l.least_lanes);
 }
 
 // Many lanes per long sequential scan, or one wavefront?  k_sequential_split has room for one scan per compute unit (150 KB

@@ -54,3 +54,22 @@ def test_many_categories():
         files.append(pcrgen.encode_coefs(c.reshape(-1), 64, 56, 1, 1, 1, q, [(1, 0, 0, 0, 0, 0, 0, 0), (1, 0, 0, 0, 1, 63, 0, 0)], 0))
     _check(pkg.record_write_indexed(files, None, 7), 1)
     _check(pkg.record_write_indexed(files, None, 7), 2)
+
+
+@pytest.mark.parametrize("side, interval, pictures", [
+    (8, 0, 4095), (8, 0, 4096),          # whole scans: short units go to the lanes from 4096 on
+    (24, 1, 511), (24, 1, 512),          # four units a scan: from 2048 on
+    (176, 0, 70)])                       # whole scans of 726 blocks: to the wavefronts
+def test_either_side_of_the_line_between_wavefronts_and_lanes(side, interval, pictures):
+    few = [pcrgen.make_jpeg(70 + i, i % 3, side, side, 3, 6.0, 2, 2, 80) for i in range(5)]
+    files = [few[i % 5] for i in range(pictures)]
+    rec = pkg.record_write_indexed(files, None, interval) if interval else pcrgen.write_record(files)
+    with pkg.pcr_open(rec, 0) as r:
+        by_rule = [r.decode_coefficients(1).cpu().numpy(), r.decode_batch(1).cpu().numpy()]
+        lay = r.coef_layout()
+        for i in (0, 1, 2, 3, 4, pictures - 1):
+            want = oracle.decode_record_image(rec, i, 1)[0]
+            assert np.array_equal(by_rule[0][int(lay[i]):int(lay[i + 1])], want), i
+        for lanes in (1, -1):
+            r.set_lane_decoders(lanes)
+            assert np.array_equal(r.decode_coefficients(1).cpu().numpy(), by_rule[0]) and np.array_equal(r.decode_batch(1).cpu().numpy(), by_rule[1]), lanes
