@@ -311,9 +311,9 @@ PCR_HD int lane_decode_ac_first(const LaneUnit& U, LaneRing* rings, uint32_t lan
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t kLaneDcCodes = 16;
 struct LaneDcCodes {
-    uint32_t lim[kLaneDcCodes / 2];                           // left-aligned code of entry i: half i & 1 of word i >> 1; 0xFFFF where there is none (no code is all ones)
+    uint32_t lim[kLaneDcCodes / 2];                           // left-aligned code of entry i: half i & 1 of word i >> 1; 0xFFFF where there is none (see lane_dc_codes)
     uint64_t len, cat;                                        // 4 bits per entry: code length - 1, category
-    uint32_t end;                                             // first left-aligned value that is no code of the (truncated) table; 0xFFFF at most
+    uint32_t end;                                             // first left-aligned value that is no code of the (truncated) table
 };
 // A definition as it is read: sixteen counts and the first sixteen symbols.
 struct LaneDcDef { uint32_t w[8]; uint32_t ahead; };         // (the first `ahead` bytes are not its own)
@@ -349,14 +349,16 @@ PCR_HD void lane_dc_def(LaneDcDef* D, const uint8_t* d, const uint8_t* end) {
 }
 
 // The table of a definition.  Sixteen entries are pushed in at the top of each member and the definition's bytes taken from
-// the bottom of its words, so that no register is indexed.
+// the bottom of its words, so that no register is indexed.  Entries that are not there count as codes at a window of
+// sixteen ones: a code if the table's last one is all ones (no file should hold such a table, but the wavefront decoders
+// take it), and it is that one then, so they have its length and category.
 PCR_HD void lane_dc_codes(LaneDcCodes* T, LaneDcDef D) {
     auto down = [](uint32_t* w, int n) {                      // n words, one byte down
         for (int q = 0; q + 1 < n; q++) w[q] = (w[q] >> 8) | (w[q + 1] << 24);
         w[n - 1] >>= 8;
     };
     while (PCR_RARELY(D.ahead != 0)) if (D.ahead != 0) { down(D.w, 8); D.ahead--; }
-    uint32_t L = 0, code = 0, rem = 0, end = 0;
+    uint32_t L = 0, code = 0, rem = 0, end = 0, last = 0;     // last: length - 1 and category of the last code so far
     uint64_t len = 0, cat = 0;
 #pragma unroll
     for (uint32_t q = 0; q < kLaneDcCodes / 2; q++) T->lim[q] = 0;
@@ -369,12 +371,13 @@ PCR_HD void lane_dc_codes(LaneDcCodes* T, LaneDcDef D) {
 #pragma unroll
         for (uint32_t q = 0; q + 1 < kLaneDcCodes / 2; q++) T->lim[q] = (T->lim[q] >> 16) | (T->lim[q + 1] << 16);
         T->lim[kLaneDcCodes / 2 - 1] = (T->lim[kLaneDcCodes / 2 - 1] >> 16) | (is ? left << 16 : 0xFFFF0000u);
-        len = (len >> 4) | (uint64_t)((L - 1u) & 15u) << 60; cat = (cat >> 4) | (uint64_t)(D.w[4] & 15u) << 60;
+        last = is ? (L - 1u) | (D.w[4] & 15u) << 4 : last;
+        len = (len >> 4) | (uint64_t)(last & 15u) << 60; cat = (cat >> 4) | (uint64_t)(last >> 4) << 60;
         down(D.w + 4, 4);
         end = is ? left + (1u << (16u - L)) : end;
         code += rem != 0 ? 1u : 0u; rem -= rem != 0 ? 1u : 0u;
     }
-    T->len = len; T->cat = cat; T->end = end < 0xFFFFu ? end : 0xFFFFu;
+    T->len = len; T->cat = cat; T->end = end;
 }
 
 // entries above w (of sixteen)

@@ -12,7 +12,7 @@
 
 using namespace pcr;
 
-// 0: the AC scans go through the one-wavefront-per-unit decoders (pcr_entropy.h); 1: through the one-lane-per-unit
+// 0: the scans go through the one-wavefront-per-unit decoders (pcr_entropy.h); 1: through the one-lane-per-unit
 // decoders (pcr_lanes.h), with what k_refine_history and k_refine_deal do around them done here by plain loops
 static int g_lane_decoders = 0;
 extern "C" void emul_set_lane_decoders(int on) { g_lane_decoders = on; }
@@ -86,7 +86,7 @@ extern "C" int emul_decode_record(const uint8_t* rec, size_t nbytes, int k, int6
         size_t plane = (size_t)img.bw[c0] * img.bh[c0];
         if (sd.Ss > 0 && sd.Ah) masks[g].assign(plane * kRefWords, 0);
         if (sd.Ss == 0 && sd.Ah > 0) continue;                     // DC refinement: applied below, in place
-        const bool by_lane = g_lane_decoders && sd.Ss > 0 && !is_sequential_scan(sd);
+        const bool by_lane = g_lane_decoders && !is_sequential_scan(sd);      // (DC refinement scans have left the loop)
         if (by_lane && sd.Ah) {                                    // (k_refine_history) what is non-zero in the band when the scan starts
             const uint64_t band = band_mask(sd.Ss, sd.Se);
             for (size_t blk = 0; blk < plane; blk++) {

@@ -43,6 +43,59 @@ def planar_sequential(seed, W, H, quality=90, restart=0):
     return out + b"\xff\xd9"
 
 
+def gray_dc_scan(width, height, diffs, counts, symbols, al=0):
+    """A gray progressive file of its DC first scan alone: the differences of its blocks, coded with the Huffman table of
+    these counts and symbols (whether or not a file should hold such a table)."""
+    codes, code, k = {}, 0, 0
+    for L in range(1, 17):
+        for _ in range(counts[L - 1]):
+            codes[symbols[k]] = (code, L)
+            code, k = code + 1, k + 1
+        code <<= 1
+    bits = ""
+    for d in diffs:
+        s = abs(d).bit_length()
+        bits += format(codes[s][0], "0%db" % codes[s][1])
+        if s:
+            bits += format(d if d > 0 else d + (1 << s) - 1, "0%db" % s)
+    bits += "1" * (-len(bits) % 8)
+    data = bytes(int(bits[p:p + 8], 2) for p in range(0, len(bits), 8)).replace(b"\xff", b"\xff\0")
+
+    def segment(m, body):
+        return b"\xff" + bytes([m]) + (len(body) + 2).to_bytes(2, "big") + body
+    frame = b"\x08" + height.to_bytes(2, "big") + width.to_bytes(2, "big") + b"\x01\x01\x11\x00"
+    return (b"\xff\xd8" + segment(0xDB, b"\0" + bytes([1] * 64)) + segment(0xC2, frame) + segment(0xC4, b"\0" + bytes(counts) + bytes(symbols)) +
+            segment(0xDA, bytes([1, 1, 0, 0, 0, al])) + data + b"\xff\xd9")
+
+
+# Counts and symbols of DC tables whose last code is all ones (no file should hold one, but every decoder here takes it),
+# and, for comparison, of some whose last code is not.
+_STEPS = [10, 9, 8, 7, 6, 5, 4, 3, 2, 1, 0]
+DC_TABLES = {
+    "sixteen codes, the last all ones": ([1] * 14 + [2, 0], [15, 14, 13, 12, 11] + _STEPS),
+    "sixteen codes of four bits": ([0, 0, 0, 16] + [0] * 12, [15, 14, 13, 12, 11] + _STEPS),
+    "eleven codes, the last all ones": ([0, 1, 5, 1, 1, 1, 2] + [0] * 9, _STEPS),
+    "two codes": ([2] + [0] * 15, [0, 3]),
+    "eleven codes, none all ones": ([0, 1, 5, 1, 1, 1, 1, 1] + [0] * 8, _STEPS),
+    "a single code": ([1] + [0] * 15, [3]),
+}
+
+
+def dc_table_file(name, seed=5, blocks=(7, 5)):
+    """A file of gray_dc_scan with one of the tables above: differences of every category up to 10 that it has, half of them
+    of the last code's, those mostly with all bits of their values set."""
+    import numpy as np
+    counts, symbols = DC_TABLES[name]
+    rng = np.random.default_rng(seed)
+    diffs, at = [], 0
+    for _ in range(blocks[0] * blocks[1]):
+        s = symbols[-1] if rng.random() < 0.5 else int(rng.choice([v for v in symbols if v <= 10]))
+        mag = (1 << s) - 1 if s == 0 or rng.random() < 0.7 else int(rng.integers(1 << (s - 1), 1 << s))
+        diffs.append(mag if at <= 0 else -mag)
+        at += diffs[-1]
+    return gray_dc_scan(8 * blocks[0], 8 * blocks[1], diffs, counts, symbols)
+
+
 # ---- byte-level variants of an existing file: same picture, other legal spellings of its segments ----
 def _rebuild(segs):
     return b"\xff\xd8" + b"".join(s + d for _, s, d in segs) + b"\xff\xd9"

@@ -11,6 +11,7 @@ import pytest
 
 import oracle
 import pcrgen
+from jpeg_files import DC_TABLES, dc_table_file
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "host_emul", "emul.cpp")
@@ -28,7 +29,7 @@ def emul():
     L.emul_set_lane_decoders.restype = None
 
     def run(rec, i, k, info, lanes=False):
-        """lanes: the AC scans through the one-lane-per-unit decoders (pcr_lanes.h) instead of the one-wavefront-per-unit ones."""
+        """lanes: the scans through the one-lane-per-unit decoders (pcr_lanes.h) instead of the one-wavefront-per-unit ones."""
         L.emul_set_lane_decoders(1 if lanes else 0)
         a = np.frombuffer(rec, np.uint8)
         coef = np.zeros(info.coef_count, np.int16)
@@ -90,7 +91,7 @@ def test_lane_code_matches_oracle_extreme_coefficients(emul, extreme_record):
 
 
 def test_lane_per_unit_decoders_match_oracle(emul, rgb_small, extreme_record):
-    """The second shape of AC decoder (one lane per unit, pcr_lanes.h; on the CPU one lane, plain arrays for its rings in
+    """The second shape of decoder (one lane per unit, pcr_lanes.h; on the CPU one lane, plain arrays for its rings in
     LDS): restart intervals, entry points at three intervals, the deep successive-approximation script, the extreme
     planes, noisy images with long codes."""
     from test_oracle_entropy import DEEP
@@ -134,6 +135,15 @@ def test_lane_code_matches_oracle_baseline_file_with_one_scan_per_component(emul
     rec = pcrgen.write_record(files)
     assert oracle.record_header(rec)["G"] == 3
     _compare(emul, rec, range(len(files)), (1, 2, 3))
+
+
+@pytest.mark.parametrize("name", DC_TABLES)
+def test_both_dc_decoders_take_the_same_tables(emul, name):
+    """A DC table whose last code is all ones is no table a file should hold, but the decoders take it; then both do."""
+    files = [dc_table_file(name, seed, blocks) for seed, blocks in ((1, (7, 5)), (2, (1, 1)), (3, (2, 40)))]
+    rec = pcrgen.write_record(files)
+    for lanes in (False, True):
+        _compare(emul, rec, range(len(files)), (1,), lanes)
 
 
 def _variant_files():

@@ -7,6 +7,7 @@ import pytest
 import oracle
 import paper_1911_00472_amd as pkg
 import pcrgen
+from jpeg_files import DC_TABLES, dc_table_file
 
 pytestmark = pytest.mark.gpu
 
@@ -54,6 +55,15 @@ def test_many_categories():
         files.append(pcrgen.encode_coefs(c.reshape(-1), 64, 56, 1, 1, 1, q, [(1, 0, 0, 0, 0, 0, 0, 0), (1, 0, 0, 0, 1, 63, 0, 0)], 0))
     _check(pkg.record_write_indexed(files, None, 7), 1)
     _check(pkg.record_write_indexed(files, None, 7), 2)
+
+
+@pytest.mark.parametrize("name", DC_TABLES)
+def test_tables_whose_last_code_is_all_ones(name):
+    """Both decoders take the same tables."""
+    files = [dc_table_file(name, seed, blocks) for seed in range(22) for blocks in ((7, 5), (1, 1), (2, 40))]
+    rec = pcrgen.write_record(files)
+    _check(rec, 1, lanes=1)
+    _check(rec, 1, lanes=-1)
 
 
 @pytest.mark.parametrize("side, interval, pictures", [
