@@ -71,6 +71,15 @@ PCR_HD uint32_t ld_le32(const uint8_t* p) { return (uint32_t)p[0] | ((uint32_t)p
 PCR_HD uint64_t ld_le64(const uint8_t* p) { return (uint64_t)ld_le32(p) | ((uint64_t)ld_le32(p + 4) << 32); }
 PCR_HD uint32_t ld_be16(const uint8_t* p) { return ((uint32_t)p[0] << 8) | p[1]; }
 
+#if defined(__HIPCC__)
+// What lanes of a wavefront have written to LDS is there for its other lanes from here on.
+PCR_D void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+#endif
+
 // Tell the compiler a value is the same in every lane of the wavefront (it then lives in a
 // scalar register).  Only used where that is true by construction.
 PCR_HD uint32_t uni(uint32_t v) {

@@ -311,6 +311,60 @@ __device__ inline void write_lane(uint32_t& v, uint32_t value, uint32_t lane) {
 // plain photographs at scan group 10 5.66 -> 5.42 ms.  (The same feed from a vector register, words picked by scalar reads across
 // lanes, was slower than the scalar loads.)
 constexpr uint32_t kStageWords = 128, kStageWindows = (kStageWords - 2) / 2;
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __attribute__((address_space(3))) uint32_t* StageWords;
+#else
+typedef uint32_t* StageWords;
+#endif
+// A lane's part of it.  The words a lane reads are other lanes' writes: put() belongs between two wave_sync (the words read
+// before it have been, those read behind it are the new ones), see WindowReader::restage.  (Tests drive sixty-four of these
+// over one array.)
+struct StagedStream {
+    StageWords stage;           // kStageWords words
+    const uint32_t* g;          // the stream
+    uint32_t lane;
+    uint32_t at, last;          // word of the stream the staged ones begin at; last word that is read
+    uint32_t left;              // windows of the stage whose words have not been read yet
+    uint32_t p0, p1;            // the two words of the window read
+    StageWords from;            // where those of the one after it lie in the stage
+    uint32_t va, vb;            // the next words of the stream, on their way
+    PCR_HD void init(StageWords lds, const uint32_t* words, uint32_t bits, uint32_t lane_id) {
+        stage = lds; g = words; lane = lane_id;
+        last = (bits >> 5) + 4;
+        at = 0u - 2 * kStageWindows;
+        fetch();
+    }
+    PCR_HD void fetch() {                                     // the words behind the stage's windows
+        const uint32_t a = at + 2 * kStageWindows + lane, b = a + 64;
+        va = g[a < last ? a : last]; vb = g[b < last ? b : last];
+    }
+    PCR_HD void put() {
+        at += 2 * kStageWindows;
+        stage[lane] = va; stage[64 + lane] = vb;
+        // (a lane whose bits are one whole word reads it as the second of the two: the shift of window() goes from 0 to 31.  Lane 0
+        // then reads the word ahead of the stage, which is the end of the table, and uses nothing of it.)
+        from = stage + (int)((lane >> 5) - ((lane & 31) == 0 ? 1 : 0));
+        left = kStageWindows;
+        fetch();
+    }
+    PCR_HD void read() {
+        p0 = from[0]; p1 = from[1];
+        from += 2;
+        left = opaque(left - 1);
+    }
+    PCR_HD uint32_t pass(uint32_t n) {                        // over n windows, or to the end of the stage; returns how many are missing
+        const uint32_t m = n < left ? n : left;
+        from += 2 * m; left -= m;
+        return n - m;
+    }
+    PCR_HD uint32_t window() const {                          // this lane's 32 bits
+#if defined(__HIP_DEVICE_COMPILE__)
+        return __builtin_amdgcn_alignbit(p0, p1, 32 - lane);
+#else
+        return (uint32_t)((((uint64_t)p0 << 32) | p1) >> ((32 - lane) & 31));
+#endif
+    }
+};
 struct WindowReader {
     const AcTab* tab;
     uint32_t lim8, sh2;         // of tab (see packed_index)
@@ -322,15 +376,8 @@ struct WindowReader {
     uint32_t vstep;             // ... and what it moves the decoder on by, as the symbol loops add it up (see first_step, refine_step)
     bool first;
 #if defined(__HIP_DEVICE_COMPILE__)
-    typedef __attribute__((address_space(3))) uint32_t* LdsWords;
-    LdsWords stage;             // kStageWords words
-    const uint32_t* g;          // the stream
-    uint32_t at, last;          // word of the stream the staged ones begin at; last word that is read
-    uint32_t left;              // windows of the stage whose words have not been read yet
+    StagedStream feed;          // a window ahead
     uint32_t vwin;              // this lane's 32 bits
-    uint32_t vp0, vp1;          // the two words of the next window's
-    LdsWords vat;               // where those of the one after it lie in the stage
-    uint32_t va, vb;            // the next words of the stream, on their way
 #else
     StreamPtr p;                // words after n1
     uint32_t w0, w1, w2, n0, n1;
@@ -346,10 +393,7 @@ struct WindowReader {
         mis_bits = (byte_off & 3) * 8;
         o = mis_bits + sub_bits; wbase = pos0; total_bits = pos0 + nbits + mis_bits;
 #if defined(__HIP_DEVICE_COMPILE__)
-        stage = (LdsWords)lds; g = words + (byte_off >> 2);
-        last = ((nbits + mis_bits) >> 5) + 4;
-        at = 0u - 2 * kStageWindows;
-        fetch();
+        feed.init((StageWords)lds, words + (byte_off >> 2), nbits + mis_bits, lane_id);
         restage();
         ahead(); take(); ahead();
 #else
@@ -360,31 +404,16 @@ struct WindowReader {
         fill();
     }
 #if defined(__HIP_DEVICE_COMPILE__)
-    __device__ void fetch() {                                 // the words behind the stage's windows
-        const uint32_t a = at + 2 * kStageWindows + lane, b = a + 64;
-        va = g[a < last ? a : last]; vb = g[b < last ? b : last];
-    }
-    __device__ void restage() {
-        at += 2 * kStageWindows;
-        stage[lane] = va; stage[64 + lane] = vb;
-        // (a lane whose bits are one whole word reads it as the second of the two: the shift below goes from 0 to 31.  Lane 0 then
-        // reads the word ahead of the stage, which is the end of the table, and uses nothing of it.)
-        vat = stage + (int)((lane >> 5) - ((lane & 31) == 0 ? 1 : 0));
-        left = kStageWindows;
-        fetch();
-    }
+    __device__ void restage() { wave_sync(); feed.put(); wave_sync(); }
     __device__ void ahead() {
-        vp0 = vat[0]; vp1 = vat[1];
-        vat += 2;
-        left = opaque(left - 1);
-        if (__builtin_expect(left == 0, 0)) restage();
+        feed.read();
+        if (__builtin_expect(feed.left == 0, 0)) restage();
     }
-    __device__ void take() { vwin = __builtin_amdgcn_alignbit(vp0, vp1, 32 - lane); }
+    __device__ void take() { vwin = feed.window(); }
     __device__ void skip(uint32_t n) {                        // n windows nobody asks for
         while (n) {
-            const uint32_t m = n < left ? n : left;
-            vat += 2 * m; left -= m; n -= m;
-            if (left == 0) restage();
+            n = feed.pass(n);
+            if (feed.left == 0) restage();
         }
     }
 #endif

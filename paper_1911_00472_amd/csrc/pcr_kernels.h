@@ -43,12 +43,6 @@ PCR_D uint32_t xcd_major(uint32_t b, uint32_t n) {
     const uint32_t q = n / kXcds, r = n - q * kXcds, x = b % kXcds, i = b / kXcds;
     return x * q + (x < r ? x : r) + i;
 }
-// What lanes of a wavefront have written to LDS is there for its other lanes from here on.
-PCR_D void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 // the value of the lane before this one (lane 0: `first`), and the sum over the lanes up to this one
 PCR_D uint32_t lane_before(uint32_t v, uint32_t first) { return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xF, 0xF, false); }   // wave_shr:1
 PCR_D uint32_t lanes_prefix_sum(uint32_t v) {

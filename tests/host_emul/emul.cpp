@@ -261,3 +261,39 @@ extern "C" int emul_decode_record(const uint8_t* rec, size_t nbytes, int k, int6
     }
     return kOk;
 }
+
+// The staged stream of the wavefront decoders: sixty-four lanes over one stage, each phase for all of them before the next.
+// words: `have` of them readable; the unit's bits end at bit `bits`.  steps: windows to pass over ahead of each window taken.
+// Returns the number of windows in which some lane saw other bits than the stream holds at its offset (words behind the last
+// one that is read repeat it), -1 if a word that is not there was asked for.
+extern "C" int emul_staged_stream(const uint32_t* words, uint32_t have, uint32_t bits, const uint32_t* steps, uint32_t nsteps) {
+    const uint32_t last = (bits >> 5) + 4;
+    if (last >= have) return -1;
+    std::vector<uint32_t> lds(1 + kStageWords, 0xDEADBEEFu);               // (a word is read ahead of the stage)
+    StagedStream lane[64];
+    for (uint32_t l = 0; l < 64; l++) lane[l].init(lds.data() + 1, words, bits, l);
+    auto put = [&]() { for (auto& s : lane) s.put(); };
+    auto word = [&](uint32_t i) { return (uint64_t)words[i < last ? i : last]; };
+    put();
+    int wrong = 0;
+    uint32_t w = 0;
+    for (uint32_t t = 0; t < nsteps; t++) {
+        for (uint32_t n = steps[t]; n;) {
+            uint32_t rest = 0;
+            for (auto& s : lane) rest = s.pass(n);
+            w += n - rest; n = rest;
+            if (lane[0].left == 0) put();
+        }
+        for (auto& s : lane) s.read();
+        if (lane[0].left == 0) put();                                      // (what was read is kept)
+        bool ok = true;
+        for (uint32_t l = 0; l < 64; l++) {
+            const uint32_t i = 2 * w + (l >> 5), sh = l & 31;
+            const uint32_t want = (uint32_t)(((word(i) << 32) | word(i + 1)) >> (32 - sh));
+            ok = ok && lane[l].window() == want && lane[l].left == lane[0].left;
+        }
+        wrong += ok ? 0 : 1;
+        w++;
+    }
+    return wrong;
+}

@@ -40,6 +40,7 @@ def emul():
         assert rc == 0, rc
         assert (W.value, H.value, C.value) == (info.W, info.H, info.nc)
         return coef, pix
+    run.lib = L
     return run
 
 
@@ -135,6 +136,21 @@ def test_lane_code_matches_oracle_baseline_file_with_one_scan_per_component(emul
     rec = pcrgen.write_record(files)
     assert oracle.record_header(rec)["G"] == 3
     _compare(emul, rec, range(len(files)), (1, 2, 3))
+
+
+@pytest.mark.parametrize("bits", [0, 1, 31, 32, 64, 127 * 32, 128 * 32 - 1, 63 * 64, 63 * 64 + 1, 126 * 64, 40000])
+def test_staged_stream_gives_every_lane_its_bits(emul, bits):
+    """The words of the stream as they go through the wavefront decoders' stage: window by window past the unit's end, over
+    single windows and over several stages at once, up to and across their ends."""
+    rng = np.random.default_rng(bits)
+    words = rng.integers(0, 1 << 32, (bits >> 5) + 5, dtype=np.uint32)      # (not one word more than may be read)
+    u32p = ctypes.POINTER(ctypes.c_uint32)
+    windows = bits // 64 + 3
+    plans = [np.zeros(max(windows, 200), np.uint32), rng.integers(0, 4, windows, dtype=np.uint32), rng.integers(0, 200, 60, dtype=np.uint32)]
+    plans += [np.array([first, 0, over, 0, 0, 63, 62, 0, 64, 0], np.uint32) for first in (0, 61, 62, 63) for over in (1, 61, 62, 63, 64, 125, 126, 127, 1000)]
+    for steps in plans:
+        got = emul.lib.emul_staged_stream(words.ctypes.data_as(u32p), len(words), bits, steps.ctypes.data_as(u32p), len(steps))
+        assert got == 0, (bits, steps[:12], got)
 
 
 @pytest.mark.parametrize("name", DC_TABLES)
