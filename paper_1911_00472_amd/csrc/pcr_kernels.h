@@ -1000,8 +1000,8 @@ struct ChainGate {
 };
 
 // What a wavefront keeps in LDS: the AC table of its scan and the words of the stream it is at, or the DC tables of its components.
-constexpr uint32_t kWaveTabBytes = sizeof(AcTab) + kStageWords * sizeof(uint32_t);
-static_assert(kMaxComp * sizeof(DcTab) <= kWaveTabBytes, "one area serves both");
+constexpr uint32_t kWaveTabBytes = sizeof(AcTab) + kStageWords * sizeof(uint32_t), kWaveDcTabBytes = kMaxComp * sizeof(DcTab);
+static_assert(kWaveDcTabBytes <= kWaveTabBytes, "one area serves both");
 
 PCR_D int wave_dc_first(const DevRecord& R, const Unit& un, const UnitSetup& L, DcTab* tabs, uint32_t lane, bool to_planes) {
     dc_kernel_priority();

@@ -679,8 +679,12 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, lists, s);
     mark(r, PCR_STAGE_UNSTUFF, s);
     const uint32_t* c32 = reinterpret_cast<const uint32_t*>(r->d.clean);
+    // (a launch of DC scans alone asks for their tables only: with an AC table's room each, the wavefronts of one record left
+    // fewer to those of the others.  Four records of 1024 pictures of 256 x 256 without entry points at scan group 1:
+    // 715 us a call with room for an AC table and the words of a stream, 655 with room for the DC tables; gray photographs 1470, 1405.)
     auto waves = [&](const LevelList& l) {
-        hipLaunchKernelGGL((l.kind == kDcFirst ? k_decode_waves<kWavesDc, false> : k_decode_waves<kWavesAc, false>), dim3(l.n), dim3(kEntropyLanes), kWaveTabBytes, s, r->d, l.d_units,
+        const bool dc = l.kind == kDcFirst;
+        hipLaunchKernelGGL((dc ? k_decode_waves<kWavesDc, false> : k_decode_waves<kWavesAc, false>), dim3(l.n), dim3(kEntropyLanes), dc ? kWaveDcTabBytes : kWaveTabBytes, s, r->d, l.d_units,
                            (const UnitChain*)nullptr, c32, dc_to_planes ? 1u : 0u);
     };
     if (side_by_side) {
