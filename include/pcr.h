@@ -404,8 +404,10 @@ int pcr_transcode_batch(pcr_record* rec, const void* const* files, const size_t*
  * unit, or every unit a lane (64 units per wavefront).  Lanes need a fifth of the instructions but take longer per unit:
  * they win when the GPU is shared between the decodes of several records, or when a launch has very many units.
  * mode 0 (default): lanes for AC launches of at least 8192 units if the process has more than one record open, of at
- * least 32768 units otherwise, and for launches of DC first scans of at least 4096 units if it has more than one record
- * open; 1: lanes wherever the kernels exist and the record's scans have several units; -1: never.
+ * least 32768 units otherwise.  DC first scans share the launch of AC first scans that go to the lanes; by themselves they go
+ * there from 4096 units on if the process has more than one record open, otherwise from 8192 where wavefronts would decode them
+ * in the launch of the AC scans and from 6144 where not (4096 if they are whole scans of 64 to 384 blocks).
+ * 1: lanes wherever the kernels exist and the record's scans have several units; -1: never.
  * The results are the same bit for bit.  Takes effect from the next decode call.  PCR_E_ARG: null handle or another
  * mode. */
 int pcr_set_lane_decoders(pcr_record* rec, int mode);
@@ -414,9 +416,10 @@ int pcr_set_lane_decoders(pcr_record* rec, int mode);
 int pcr_last_decoder_shapes(pcr_record* rec, int* lane_launches, int* wavefront_launches);
 
 /* Stage timing with HIP events recorded on the call's own stream (off by default; switching it on
- * starts a new history).  While it is on, every stage has launches of its own; without it, scans for the wavefront
- * decoders share one launch where they can, whatever their stage: the times then reported are those of launches that an
- * ordinary call does not make (512 photographs without entry points: 6.7 ms, stage by stage 15).  A stage is one kernel or a short run of kernels:
+ * starts a new history).  While it is on, every stage has launches of its own.  Without it, scans for the wavefront
+ * decoders share one launch where they can, whatever their stage, DC and AC first scans for the lanes share one, and the lists of
+ * REFINE_APPLY are made by the launch that unstuffs: the times reported are those of launches that an ordinary call does not
+ * make (512 photographs without entry points: 6.7 ms, stage by stage 15).  A stage is one kernel or a short run of kernels:
  *   INDEX_PARSE    k_index + k_headers               UNSTUFF        k_unstuff + zero fills
  *   DC_FIRST, AC_FIRST, AC_REFINE, REFINE_BLOCKS, SEQUENTIAL     one interval per launch of that kernel (DC_FIRST, AC_FIRST,
  *                  AC_REFINE: of either decoder shape; REFINE_BLOCKS: k_refine_blocks after a wavefront-per-unit launch, k_refine_history

@@ -1,4 +1,5 @@
-// Which scans of an image may be decoded by one launch, and in what order the others follow.  Host code; needs nothing of HIP.
+// Which scans of an image may be decoded by one launch, and in what order the others follow; and which decoder a launch of DC
+// first scans is for.  Host code; needs nothing of HIP.
 //
 // Two scans of a component whose bands overlap have to be decoded in file order: a refinement scan reads what the scans
 // before it made of a block, and a first scan over coefficients that an earlier scan of the component holds (T.81 rules it
@@ -103,6 +104,58 @@ private:
             c.waits |= (uint64_t)waits[a] << (8 * a);
         }
         ac.push_back(c);
+    }
+};
+
+// A launch of DC first scans, and from how many units on it goes to the lane decoders instead of to a wavefront per unit.
+//
+// A lane decodes a DC symbol with a fifth of the instructions a wavefront spends on it, but a launch of lanes takes as long as
+// its longest unit, however few there are, and the wavefronts' time a symbol only grows once they fill the scalar units.  So
+// the number of units decides, more than their length.  us a call by wavefronts / by lanes, at the units and the blocks per
+// unit that a plan counts (a record written with an entry every 64 MCUs has one every 32 in DC first scans):
+//   scan group 1, one record open                   2048 units   4096         6144         8192
+//     cut into units of   32 blocks (gray)           61 / 69      67 / 71                   72 / 66
+//                         96 (4:4:4)                 78 / 91      88 / 92                  106 / 93
+//                        192 (4:2:0)                 89 / 110    112 / 118    131 / 127    151 / 134
+//                        384                        124 / 155    161 / 171    224 / 214    271 / 237
+//                        768                                     267 / 290    334 / 331    415 / 370
+//                       3072                                     908 / 991   1180 / 1175  1504 / 1333
+//     whole scans of       9 blocks (gray)           81 / 96     112 / 117    149 / 148    190 / 177
+//                         96                        114 / 117    174 / 160    221 / 195    278 / 232
+//                        216                        129 / 140    208 / 196    261 / 233    341 / 289
+//                        384                        165 / 189    235 / 226    331 / 303    444 / 379
+//                        864                        230 / 289    401 / 405    535 / 507    695 / 609
+//                       3750                        743 / 1031  1178 / 1274  1539 / 1528  2006 / 1787
+//   four records open, units of each                2048         3072         4096         6144
+//     cut into units of  192 blocks                 214 / 233                 286 / 229    366 / 273
+//     whole scans of     384                        453 / 472    636 / 599    823 / 724   1188 / 977
+//                        864                        697 / 792    980 / 979   1285 / 1177  1877 / 1563
+//                       1536                       1043 / 1238  1478 / 1506  1912 / 1785
+// Where the AC scans of the call go to the wavefront decoders side by side, DC scans by wavefronts are decoded beside them in the
+// same launch, by lanes behind it:
+//   scan group 2, one record open                   2048         4096         8192        12288
+//     cut into units of  192 blocks                 134 / 177    182 / 210    328 / 325
+//                         96                        105 / 133    126 / 147    169 / 176    223 / 218
+//     whole scans of      96                                     213 / 233    346 / 340
+//                        384                                     416 / 465    737 / 735   1062 / 1017
+//   scan group 5: cut, 192 blocks                   175 / 205    248 / 258
+//                 whole scans of 384                             557 / 570    981 / 959   1453 / 1377
+//   four records open, scan group 2: whole, 384     774 / 863   1402 / 1361  2647 / 2403
+//                                    cut, 96        224 / 272    337 / 336    535 / 472
+struct DcLaunch {
+    uint32_t units = 0, scans = 0;
+    uint64_t blocks = 0;
+    void add(const ImgDesc& img, const ScanDesc& sd, uint32_t n) {
+        uint32_t per_mcu = 0;
+        for (int j = 0; j < sd.ns; j++) per_mcu += sd.ns > 1 ? (uint32_t)img.hs[sd.comp[j]] * img.vs[sd.comp[j]] : 1u;
+        units += n; scans++; blocks += (uint64_t)sd.mcus * per_mcu;
+    }
+    // several: the process has more than one record open; beside: the launch could be part of one of AC scans by wavefronts
+    uint32_t least_lanes(bool several, bool beside) const {
+        if (several) return 4096;
+        if (beside) return 8192;
+        const bool cut = units >= 2 * scans;
+        return !cut && blocks >= 64ull * units && blocks <= 384ull * units ? 4096 : 6144;
     }
 };
 

@@ -41,7 +41,7 @@ struct LevelList {
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
     uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units k_sequential_split has dealt with
     uint32_t n_long = 0; uint64_t long_bytes = 0; bool subsampled = false;        // ... how many those are, their bytes, whether some have MCUs of several blocks per component
-    uint32_t least_lanes = 0;                                                    // DC first scans: units from which the lanes pay (dc_least_lanes)
+    DcLaunch dc;                                                                 // DC first scans: what decides between lanes and wavefronts
     bool chained = false;                                                        // the plan's chains hold these units too
 };
 
@@ -302,25 +302,6 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
     return PCR_OK;
 }
 
-// Units from which a launch of DC first scans goes to the lane decoders, by the mean of their blocks and whether the scans are cut.
-// A lane decodes a DC symbol with a fifth of the instructions a wavefront spends on it, but a launch of lanes takes as long as
-// its longest unit, however few there are, and the wavefronts' time a symbol only grows once they fill the scalar units: short
-// units, most of whose time is set-up, are for the lanes early, long ones late; and lanes of one scan read one set of tables.
-// Scan group 1 of one record, us a call by wavefronts / by lanes at 1024, 2048, 3072, 4096, 6144 units:
-//   an entry every 64 MCUs in 4:2:0 (384 blocks)     73 / 88    97 / 98                 138 / 118
-//   the same in 4:4:4 (192)                          64 / 69                             93 / 76  (1072 and 4288 units)
-//   an entry every 128 MCUs (768), 256 x 256        129 / 161  168 / 177   220 / 210    284 / 250    410 / 331
-//   whole scans of  96 x  96 (216)                   95 / 117  137 / 148   172 / 171    204 / 192    259 / 230
-//                  128 x 128 (384)                  114 / 155  157 / 180   205 / 211    248 / 242    343 / 314
-//                  192 x 192 (864)                  159 / 252  231 / 293   310 / 347    399 / 405    530 / 508
-//                  256 x 256 (1536)                 243 / 407  354 / 473   479 / 557    592 / 625    787 / 770
-//                  400 x 400 (3750)                 507 / 901  738 / 1044  958 / 1172  1191 / 1304
-// (four records in flight: 128 x 128, 1024 units each 288 / 344, 4096 780 / 716; 256 x 256, 2048 units 1079 / 1270.)
-uint32_t dc_least_lanes(uint64_t mean_blocks, bool cut) {
-    if (mean_blocks <= 384) return cut ? 2048 : 4096;
-    return mean_blocks <= 768 && cut ? 3072 : 6144;
-}
-
 // Launch geometry for decoding scan groups k0+1 .. k (k0 = 0: from scratch) and turning groups 1 .. k into pixels.
 int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     const int key = k0 * 256 + k;
@@ -425,14 +406,7 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             up.add(&ll.d_jobs, jobs);
         }
         if (ll.kind == kDcFirst) {
-            uint64_t blocks = 0;
-            for (const Run& q : rn) {
-                const ScanDesc& sd = r->scan[(size_t)q.img * G + q.scan];
-                uint32_t per_mcu = 0;
-                for (int j = 0; j < sd.ns; j++) per_mcu += sd.ns > 1 ? (uint32_t)r->img[q.img].hs[sd.comp[j]] * r->img[q.img].vs[sd.comp[j]] : 1u;
-                blocks += (uint64_t)sd.mcus * per_mcu;
-            }
-            ll.least_lanes = dc_least_lanes(blocks / ll.n, ll.n >= 2 * rn.size());
+            for (const Run& q : rn) ll.dc.add(r->img[q.img], r->scan[(size_t)q.img * G + q.scan], q.count);
         }
         if (ll.kind == kSequential) {
             for (const Run& q : rn) {
@@ -537,11 +511,12 @@ bool lanes_pay(const pcr_record* r, const LevelList& l) {
     return l.n >= least && l.n >= 32u * l.n_jobs;            // (jobs half full at least: few tables per 64 units)
 }
 
-// The same question for a launch of DC first scans by themselves (beside AC first scans by lanes they cost nothing, see
-// with_ac; the line: dc_least_lanes).
-bool dc_lanes_pay(const pcr_record* r, const LevelList& l) {
+// The same question for a launch of DC first scans (with AC first scans by lanes they share a launch, see with_ac; the line:
+// DcLaunch).  beside: the launch could be part of one of AC scans by wavefronts.
+bool dc_lanes_pay(const pcr_record* r, const LevelList& l, bool beside) {
     if (r->lane_mode < 0) return false;
-    return l.n >= (r->lane_mode > 0 ? (uint32_t)kEntropyLanes : l.least_lanes);
+    if (r->lane_mode > 0) return l.n >= (uint32_t)kEntropyLanes;
+    return l.n >= l.dc.least_lanes(g_open_records.load(std::memory_order_relaxed) > 1, beside);
 }
 
 // Many lanes per long sequential scan, or one wavefront?  k_sequential_split has room for one scan per compute unit (150 KB
@@ -619,30 +594,16 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     *plan_out = plan;
     const uint32_t n = r->hdr.n;
     call_begin(r, s);
-    // (the wavefront decoders of DC first scans read pre-built tables, the lane decoder makes its own: when every launch
-    // of DC first scans of this call goes to the lanes their tables are not built, and with DC first scans only, none are)
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
-    bool dc_tables = false;
     std::vector<char> by_lanes(plan->levels.size(), 0);
     r->last_lane_launches = r->last_wave_launches = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
-        if (l.kind == kDcFirst) by_lanes[li] = dc_lanes_pay(r, l) ? 1 : 0;
-        else if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
-        else {
+        if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
+        else if (l.kind != kDcFirst) {
             by_lanes[li] = lanes_pay(r, l) ? 1 : 0;
             if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
         }
-    }
-    // Beside AC first scans that go to the lanes the DC first scans of the same level go there too, in the same launch.
-    auto with_ac = [&](size_t li) {
-        return plan->levels[li].kind == kDcFirst && li + 1 < plan->levels.size() && plan->levels[li + 1].kind == kAcFirst && plan->levels[li + 1].level == plan->levels[li].level &&
-               by_lanes[li + 1] != 0;
-    };
-    for (size_t li = 0; li < plan->levels.size(); li++) {
-        if (plan->levels[li].kind != kDcFirst) continue;
-        if (with_ac(li)) by_lanes[li] = 1;
-        if (!by_lanes[li]) dc_tables = true;
     }
     // Scans side by side where the AC scans are for the wavefront decoders (DC first scans may go to the lanes by themselves);
     // with stage timing on, whose intervals are those of single stages, one after the other.
@@ -653,9 +614,21 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         else if ((rc = build_chains(r, k0, k, plan)) != PCR_OK) return rc;
     }
     side_by_side = side_by_side && plan->n_ac_chains > 0;
-    bool dc_beside = side_by_side;
-    for (size_t li = 0; li < plan->levels.size(); li++)
-        if (plan->levels[li].kind == kDcFirst && (by_lanes[li] || !plan->levels[li].chained)) dc_beside = false;
+    // Beside AC first scans that go to the lanes the DC first scans of the same level go there too, in the same launch.
+    auto with_ac = [&](size_t li) {
+        return plan->levels[li].kind == kDcFirst && li + 1 < plan->levels.size() && plan->levels[li + 1].kind == kAcFirst && plan->levels[li + 1].level == plan->levels[li].level &&
+               by_lanes[li + 1] != 0;
+    };
+    // (the wavefront decoders of DC first scans read pre-built tables, the lane decoder makes its own: when every launch
+    // of DC first scans of this call goes to the lanes their tables are not built, and with DC first scans only, none are)
+    bool dc_tables = false, dc_beside = side_by_side;
+    for (size_t li = 0; li < plan->levels.size(); li++) {
+        const LevelList& l = plan->levels[li];
+        if (l.kind != kDcFirst) continue;
+        by_lanes[li] = with_ac(li) || dc_lanes_pay(r, l, side_by_side && l.chained) ? 1 : 0;
+        if (!by_lanes[li]) dc_tables = true;
+        if (by_lanes[li] || !l.chained) dc_beside = false;
+    }
     launch_headers(r, (uint32_t)k, k0 > 0, dc_tables || plan->has_ac ? (uint32_t)k0 : (uint32_t)k, dc_tables, s);
     mark(r, PCR_STAGE_INDEX_PARSE, s);
     const size_t coef_bytes = r->coef_off[n] * sizeof(int16_t);

@@ -1,4 +1,5 @@
-// CPU build of the planning of launches that decode several scans side by side (pcr_chains.h).  Test-only.
+// CPU build of the planning of launches that decode several scans side by side, and of the choice of decoder for DC first
+// scans (pcr_chains.h).  Test-only.
 #include <cstring>
 #include <vector>
 #include "../../paper_1911_00472_amd/csrc/pcr_chains.h"
@@ -39,4 +40,43 @@ extern "C" int chain_plan(const int* scans, int count, int k0, int k, int* out) 
             }
     }
     return in_step;
+}
+
+// The DC first scans of scan groups 1 .. k of a record, as one launch: units, scans, blocks.
+static int dc_launch(const uint8_t* rec, size_t nbytes, uint32_t k, DcLaunch* L) {
+    RecordHeader h;
+    const int rc = parse_record_header(rec, nbytes, &h);
+    if (rc) return rc;
+    const uint32_t n = h.n, G = h.G;
+    std::vector<uint32_t> off((size_t)G * n), len((size_t)G * n);
+    uint64_t pos = h.header_bytes;
+    for (uint32_t g = 0; g < h.k_avail; g++) {
+        for (uint32_t i = 0; i < n; i++) { off[(size_t)g * n + i] = (uint32_t)pos; pos += len[(size_t)g * n + i] = ld_le32(rec + hdr_len_pos(n, G, g, i)); }
+        pos = ld_le64(rec + hdr_group_end_pos(g));
+    }
+    for (uint32_t i = 0; i < n; i++) {
+        ImgDesc img; std::vector<ScanDesc> sc(G);
+        memset(&img, 0, sizeof img);
+        parse_image(rec, off.data(), len.data(), n, i, ld_le32(rec + hdr_nscans_pos(n, G, i)), k, &img, sc.data());
+        if (img.status) return img.status;
+        for (uint32_t g = 0; g < img.nscans; g++) {
+            const ScanDesc& sd = sc[g];
+            if (sd.Ss != 0 || sd.Ah != 0 || is_sequential_scan(sd)) continue;
+            const uint32_t entries = h.version == 2 && sd.ri == 0 ? entry_count(ld_le16(rec + hdr_ecount_pos(n, G, g, i))) : 0;
+            L->add(img, sd, sd.ri ? (sd.mcus + sd.ri - 1) / sd.ri : 1 + entries);
+        }
+    }
+    return 0;
+}
+extern "C" int dc_launch_of(const uint8_t* rec, size_t nbytes, uint32_t k, uint32_t* out) {
+    DcLaunch L;
+    const int rc = dc_launch(rec, nbytes, k, &L);
+    out[0] = L.units; out[1] = L.scans; out[2] = (uint32_t)L.blocks;
+    return rc;
+}
+// does a launch of so many scans, cut into so many units of so many blocks each, go to the lanes?
+extern "C" int dc_by_lanes(uint32_t scans, uint32_t units, uint32_t blocks, int several, int beside) {
+    DcLaunch L;
+    L.scans = scans; L.units = units; L.blocks = (uint64_t)blocks * units;
+    return units >= L.least_lanes(several != 0, beside != 0);
 }

@@ -23,6 +23,7 @@ def plan(tmp_path_factory):
         out = np.zeros((len(a), 4), np.int32)
         step = lib.chain_plan(a.ctypes.data_as(ctypes.POINTER(ctypes.c_int)), len(a), k0, len(a) if k is None else k, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int)))
         return bool(step), out
+    run.lib = lib
     return run
 
 
@@ -83,3 +84,45 @@ def test_any_sequence_of_scans_is_ordered(plan):
         k0 = rng.randrange(len(scans))
         k = rng.randint(k0 + 1, len(scans))
         _check(scans, plan(scans, k0, k)[1], k0, k)
+
+
+@pytest.mark.parametrize("size, sub, interval, units, blocks", [
+    ((256, 256), 2, 64, 8, 192), ((256, 256), 2, 128, 4, 384), ((600, 450), 1, 64, 134, 4275 * 3 / 134), ((256, 256), 2, 0, 1, 1536), ((45, 30), 2, 1, 6, 6)])
+def test_dc_units_of_a_written_record(plan, size, sub, interval, units, blocks):
+    """What the choice of decoder for DC first scans goes by: their entry points are twice as many as the interval says."""
+    import paper_1911_00472_amd as pkg
+    import pcrgen
+    files = [pcrgen.make_jpeg(40 + i, 1, size[0], size[1], 3, 6.0, sub, sub, 80) for i in range(2)]
+    rec = np.frombuffer(pkg.record_write_indexed(files, None, interval) if interval else pcrgen.write_record(files), np.uint8)
+    out = np.zeros(3, np.uint32)
+    u32p, u8p = ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(ctypes.c_uint8)
+    plan.lib.dc_launch_of.argtypes = [u8p, ctypes.c_size_t, ctypes.c_uint32, u32p]
+    assert plan.lib.dc_launch_of(rec.ctypes.data_as(u8p), len(rec), 2, out.ctypes.data_as(u32p)) == 0
+    assert tuple(out) == (2 * units, 2, 2 * units * blocks)
+
+
+# us a call by wavefronts and by lanes: several records open, beside AC scans by wavefronts, blocks per unit, whole scans,
+# {units of a launch: (wavefronts, lanes)}
+DC_TIMES = [
+    (0, 0, 32, 0, {2048: (61, 69), 4096: (67, 71), 8192: (72, 66)}), (0, 0, 96, 0, {2144: (78, 91), 4288: (88, 92), 8576: (106, 93)}),
+    (0, 0, 192, 0, {2048: (89, 110), 4096: (112, 118), 6144: (131, 127), 8192: (151, 134)}),
+    (0, 0, 384, 0, {2048: (124, 155), 4096: (161, 171), 6144: (224, 214), 8192: (271, 237)}),
+    (0, 0, 3072, 0, {4096: (908, 991), 6144: (1180, 1175), 8192: (1504, 1333)}),
+    (0, 0, 9, 1, {2048: (81, 96), 4096: (112, 117), 6144: (149, 148), 8192: (190, 177)}),
+    (0, 0, 216, 1, {2048: (129, 140), 4096: (208, 196), 6144: (261, 233), 8192: (341, 289)}),
+    (0, 0, 384, 1, {2048: (165, 189), 4096: (235, 226), 6144: (331, 303), 8192: (444, 379)}),
+    (0, 0, 864, 1, {2048: (230, 289), 4096: (401, 405), 6144: (535, 507), 8192: (695, 609)}),
+    (0, 0, 3750, 1, {2048: (743, 1031), 4096: (1178, 1274), 6144: (1539, 1528), 8192: (2006, 1787)}),
+    (1, 0, 192, 0, {2048: (214, 233), 4096: (286, 229), 6144: (366, 273)}), (1, 0, 384, 1, {2048: (453, 472), 4096: (823, 724)}),
+    (1, 0, 1536, 1, {2048: (1043, 1238), 3072: (1478, 1506), 4096: (1912, 1785)}),
+    (0, 1, 192, 0, {2048: (134, 177), 4096: (182, 210), 8192: (328, 325)}), (0, 1, 96, 0, {2144: (105, 133), 4288: (126, 147), 8576: (178, 183), 12864: (223, 218)}),
+    (0, 1, 384, 1, {4096: (416, 465), 8192: (737, 735), 12288: (1062, 1017)}),
+    (1, 1, 384, 1, {2048: (774, 863), 4096: (1402, 1361), 8192: (2647, 2403)}), (1, 1, 96, 0, {2144: (224, 272), 4288: (337, 336), 8576: (535, 472)}),
+]
+
+
+@pytest.mark.parametrize("several, beside, blocks, whole, times", DC_TIMES)
+def test_dc_scans_go_where_they_were_measured_to_be_faster(plan, several, beside, blocks, whole, times):
+    for units, (wavefronts, lanes) in times.items():
+        by_lanes = plan.lib.dc_by_lanes(units if whole else units // 4, units, blocks, several, beside)
+        assert (lanes if by_lanes else wavefronts) <= 1.05 * min(lanes, wavefronts), units

@@ -1,6 +1,8 @@
 """DC first scans with a lane per unit where the lanes of a wavefront differ or run out: MCUs of every shape in one
 wavefront, units of one block, tables that end where the record ends (their 32 bytes are then read from ahead of them), sixteen
 codes and one; alone and in the launch of the AC first scans."""
+import contextlib
+
 import numpy as np
 import pytest
 
@@ -66,20 +68,24 @@ def test_tables_whose_last_code_is_all_ones(name):
     _check(rec, 1, lanes=-1)
 
 
-@pytest.mark.parametrize("side, interval, pictures", [
-    (8, 0, 4095), (8, 0, 4096),          # whole scans: short units go to the lanes from 4096 on
-    (24, 1, 511), (24, 1, 512),          # four units a scan: from 2048 on
-    (176, 0, 70)])                       # whole scans of 726 blocks: to the wavefronts
-def test_either_side_of_the_line_between_wavefronts_and_lanes(side, interval, pictures):
+@pytest.mark.parametrize("side, interval, pictures, k, others", [
+    (64, 0, 4095, 1, 0), (64, 0, 4096, 1, 0),          # whole scans of 96 blocks: to the lanes from 4096 on
+    (24, 1, 1535, 1, 0), (24, 1, 1536, 1, 0),          # four units a scan: from 6144 on
+    (24, 1, 1023, 1, 1), (24, 1, 1024, 1, 1),          # with a second record open: from 4096 on
+    (24, 1, 2047, 2, 0), (24, 1, 2048, 2, 0),          # where they could be beside AC scans by wavefronts: from 8192 on
+    (176, 0, 70, 1, 0)])                               # whole scans of 726 blocks: to the wavefronts
+def test_either_side_of_the_line_between_wavefronts_and_lanes(side, interval, pictures, k, others):
     few = [pcrgen.make_jpeg(70 + i, i % 3, side, side, 3, 6.0, 2, 2, 80) for i in range(5)]
     files = [few[i % 5] for i in range(pictures)]
     rec = pkg.record_write_indexed(files, None, interval) if interval else pcrgen.write_record(files)
-    with pkg.pcr_open(rec, 0) as r:
-        by_rule = [r.decode_coefficients(1).cpu().numpy(), r.decode_batch(1).cpu().numpy()]
+    with contextlib.ExitStack() as open_too, pkg.pcr_open(rec, 0) as r:
+        for _ in range(others):
+            open_too.enter_context(pkg.pcr_open(pcrgen.write_record(few[:1]), 0))
+        by_rule = [r.decode_coefficients(k).cpu().numpy(), r.decode_batch(k).cpu().numpy()]
         lay = r.coef_layout()
         for i in (0, 1, 2, 3, 4, pictures - 1):
-            want = oracle.decode_record_image(rec, i, 1)[0]
+            want = oracle.decode_record_image(rec, i, k)[0]
             assert np.array_equal(by_rule[0][int(lay[i]):int(lay[i + 1])], want), i
         for lanes in (1, -1):
             r.set_lane_decoders(lanes)
-            assert np.array_equal(r.decode_coefficients(1).cpu().numpy(), by_rule[0]) and np.array_equal(r.decode_batch(1).cpu().numpy(), by_rule[1]), lanes
+            assert np.array_equal(r.decode_coefficients(k).cpu().numpy(), by_rule[0]) and np.array_equal(r.decode_batch(k).cpu().numpy(), by_rule[1]), lanes
