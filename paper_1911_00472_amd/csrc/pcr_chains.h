@@ -7,6 +7,7 @@
 #pragma once
 #include <algorithm>
 #include <cstdint>
+#include <utility>
 #include <vector>
 
 #include "pcr_format.h"
@@ -107,56 +108,94 @@ private:
     }
 };
 
-// A launch of DC first scans, and from how many units on it goes to the lane decoders instead of to a wavefront per unit.
+// A launch of DC first scans, and whether it goes to the lane decoders instead of to a wavefront per unit.
 //
 // A lane decodes a DC symbol with a fifth of the instructions a wavefront spends on it, but a launch of lanes takes as long as
 // its longest unit, however few there are, and the wavefronts' time a symbol only grows once they fill the scalar units.  So
-// the number of units decides, more than their length.  us a call by wavefronts / by lanes, at the units and the blocks per
-// unit that a plan counts (a record written with an entry every 64 MCUs has one every 32 in DC first scans):
-//   scan group 1, one record open                   2048 units   4096         6144         8192
+// what decides is the launch's blocks over those of its longest unit: `full`, the number of units where all are alike.  us a call
+// by wavefronts / by lanes (units and blocks as a plan counts them: a record written with an entry every 64 MCUs has one every 32
+// in DC first scans):
+//   scan group 1, one record open; full =           2048         4096         6144         8192
 //     cut into units of   32 blocks (gray)           61 / 69      67 / 71                   72 / 66
 //                         96 (4:4:4)                 78 / 91      88 / 92                  106 / 93
 //                        192 (4:2:0)                 89 / 110    112 / 118    131 / 127    151 / 134
 //                        384                        124 / 155    161 / 171    224 / 214    271 / 237
-//                        768                                     267 / 290    334 / 331    415 / 370
 //                       3072                                     908 / 991   1180 / 1175  1504 / 1333
 //     whole scans of       9 blocks (gray)           81 / 96     112 / 117    149 / 148    190 / 177
-//                         96                        114 / 117    174 / 160    221 / 195    278 / 232
 //                        216                        129 / 140    208 / 196    261 / 233    341 / 289
 //                        384                        165 / 189    235 / 226    331 / 303    444 / 379
 //                        864                        230 / 289    401 / 405    535 / 507    695 / 609
 //                       3750                        743 / 1031  1178 / 1274  1539 / 1528  2006 / 1787
-//   four records open, units of each                2048         3072         4096         6144
-//     cut into units of  192 blocks                 214 / 233                 286 / 229    366 / 273
-//     whole scans of     384                        453 / 472    636 / 599    823 / 724   1188 / 977
-//                        864                        697 / 792    980 / 979   1285 / 1177  1877 / 1563
-//                       1536                       1043 / 1238  1478 / 1506  1912 / 1785
-// Where the AC scans of the call go to the wavefront decoders side by side, DC scans by wavefronts are decoded beside them in the
-// same launch, by lanes behind it:
-//   scan group 2, one record open                   2048         4096         8192        12288
-//     cut into units of  192 blocks                 134 / 177    182 / 210    328 / 325
-//                         96                        105 / 133    126 / 147    169 / 176    223 / 218
-//     whole scans of      96                                     213 / 233    346 / 340
-//                        384                                     416 / 465    737 / 735   1062 / 1017
-//   scan group 5: cut, 192 blocks                   175 / 205    248 / 258
-//                 whole scans of 384                             557 / 570    981 / 959   1453 / 1377
-//   four records open, scan group 2: whole, 384     774 / 863   1402 / 1361  2647 / 2403
-//                                    cut, 96        224 / 272    337 / 336    535 / 472
+//     of many sizes, the longest of  384 blocks     174 / 199    288 / 276    422 / 364                (full: 2012, 4029, 6044)
+//                                   1536            452 / 573    588 / 675    849 / 851                (2793, 3724, 5587)
+//   the same where wavefronts would decode them beside the AC scans of the call, in one launch, and lanes behind it (scan group 2):
+//     cut into units of  192 blocks                 134 / 177    182 / 210                 328 / 325
+//     whole scans of     384                                     416 / 465                 737 / 735
+//     of many sizes, up to 726 blocks                            624 / 704                1154 / 1152  (3978, 7957)
+//   four records open, scan group 1, whole scans; units of each and full: 2048, 2048        4096, 4096          6144, 6144
+//     of 384 blocks                                 453 / 472    823 / 724   1188 / 977
+//     of 1536                                      1043 / 1238  1912 / 1785
+//     of many sizes, up to  384 blocks              295 / 348    547 / 478    767 / 648                (full: 1007, 2012, 3021)
+//                           720                     360 / 513    556 / 659    852 / 795                (734, 1468, 2202)
+//                          1260                     536 / 826    847 / 1058  1339 / 1294               (1061, 2122, 3183)
 struct DcLaunch {
-    uint32_t units = 0, scans = 0;
+    uint32_t units = 0, scans = 0, longest = 0;               // longest: blocks of the longest unit
     uint64_t blocks = 0;
     void add(const ImgDesc& img, const ScanDesc& sd, uint32_t n) {
         uint32_t per_mcu = 0;
         for (int j = 0; j < sd.ns; j++) per_mcu += sd.ns > 1 ? (uint32_t)img.hs[sd.comp[j]] * img.vs[sd.comp[j]] : 1u;
+        if (n == 0) return;
         units += n; scans++; blocks += (uint64_t)sd.mcus * per_mcu;
+        longest = std::max(longest, (sd.mcus + n - 1) / n * per_mcu);
     }
     // several: the process has more than one record open; beside: the launch could be part of one of AC scans by wavefronts
-    uint32_t least_lanes(bool several, bool beside) const {
-        if (several) return 4096;
-        if (beside) return 8192;
+    bool by_lanes(bool several, bool beside) const {
+        const uint64_t full = blocks / std::max(1u, longest);
+        if (several) return units >= 4096 && full >= (longest <= 768 ? 2000u : 3000u);
+        if (beside) return full >= 8192;
         const bool cut = units >= 2 * scans;
-        return !cut && blocks >= 64ull * units && blocks <= 384ull * units ? 4096 : 6144;
+        return full >= (cut || longest < 64 || longest > 768 ? 6144u : longest <= 384 ? 3584u : 4608u);
     }
 };
+
+// The MCUs of a DC scan, as far as lanes that decode them in step have to agree on them.
+inline uint32_t dc_mcu_shape(const ImgDesc& img, const ScanDesc& sd) {
+    uint32_t f[2 * kMaxComp] = {1, 1, 1, 1, 1, 1};
+    for (int j = 0; j < sd.ns && sd.ns > 1; j++) { f[2 * j] = img.hs[sd.comp[j]]; f[2 * j + 1] = img.vs[sd.comp[j]]; }
+    return dc_shape(sd.ns, f[0], f[1], f[2], f[3], f[4], f[5]);
+}
+
+// The units of a launch of DC first scans: run e, of which all MCUs have shape[e], has count[e] units; emit(e, unit) is called for
+// each of them in the order of the launch.  A wavefront of `lanes` lanes takes shapes one after the other, so where there are
+// several no wavefront gets more than one: returns the unit at which each begins, and their number at the end (empty: one
+// shape, a wavefront every `lanes` units).  Otherwise the order is that of the runs.  8192 pictures of 77 to 192 pixels a
+// side in four samplings, whole scans, scan group 1: 1204 us a call with the shapes as they come, 639 when a trip of the lane
+// decoder took a symbol of each lane whatever its shape; now 701 by lanes (and by wavefronts, to which they go).
+template <class Emit>
+std::vector<uint32_t> dc_units_by_shape(const std::vector<uint32_t>& shape, const std::vector<uint32_t>& count, uint32_t lanes, Emit emit) {
+    struct Group { uint32_t shape; std::vector<std::pair<uint32_t, uint32_t>> units; };
+    std::vector<Group> groups;
+    std::vector<uint32_t> starts;
+    const bool one = std::all_of(shape.begin(), shape.end(), [&](uint32_t v) { return v == shape[0]; });
+    if (!one) starts.push_back(0);
+    auto wavefront = [&](Group& g) {
+        if (g.units.empty()) return;
+        for (const auto& u : g.units) emit(u.first, u.second);
+        starts.push_back(starts.back() + (uint32_t)g.units.size());
+        g.units.clear();
+    };
+    for (uint32_t e = 0; e < shape.size(); e++) {
+        if (one) { for (uint32_t j = 0; j < count[e]; j++) emit(e, j); continue; }
+        size_t g = 0;
+        while (g < groups.size() && groups[g].shape != shape[e]) g++;
+        if (g == groups.size()) groups.push_back(Group{shape[e], {}});
+        for (uint32_t j = 0; j < count[e]; j++) {
+            groups[g].units.emplace_back(e, j);
+            if (groups[g].units.size() == lanes) wavefront(groups[g]);
+        }
+    }
+    for (Group& g : groups) wavefront(g);
+    return starts;
+}
 
 }  // namespace pcr

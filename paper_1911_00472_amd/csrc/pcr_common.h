@@ -59,6 +59,10 @@ struct ScanDesc {
 
 // A scan of a sequential (baseline) file carries whole blocks: DC difference, then the AC run/size pairs.
 PCR_HD bool is_sequential_scan(const ScanDesc& sd) { return sd.Ss == 0 && sd.Se == 63; }
+// Components of a DC scan and their blocks in an MCU, four bits each (of components the scan does not have: nothing).
+PCR_HD uint32_t dc_shape(uint32_t ns, uint32_t hs0, uint32_t vs0, uint32_t hs1, uint32_t vs1, uint32_t hs2, uint32_t vs2) {
+    return (ns | hs0 << 4 | vs0 << 8 | hs1 << 12 | vs1 << 16 | hs2 << 20 | vs2 << 24) & ((16u << 8 * ns) - 1u);
+}
 
 struct Unit {                              // one independently decodable piece: a restart interval of a scan
     uint32_t img;

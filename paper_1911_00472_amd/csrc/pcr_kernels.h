@@ -1183,10 +1183,13 @@ PCR_D __attribute__((always_inline)) void lane_dc_unit_setup(const DevRecord& R,
     U->words = clean32 + (clean_base(PCR_FIELD(I.sd, ScanDesc, data_off)) >> 2);
 }
 
-PCR_D __attribute__((always_inline)) void dc_first_units(const DevRecord& R, const Unit* __restrict__ units, uint32_t nunits, uint32_t block,
+// Workgroup `block` of the lanes' DC decoders: units [starts[block], starts[block + 1]) of the launch, or sixty-four after
+// sixty-four where there are no starts.
+PCR_D __attribute__((always_inline)) void dc_first_units(const DevRecord& R, const Unit* __restrict__ units, uint32_t nunits, const uint32_t* __restrict__ starts, uint32_t block,
         const uint32_t* __restrict__ clean32, uint32_t to_planes, LaneRing* rings) {
     short_kernel_priority();
-    const uint32_t t = threadIdx.x, u = block * kEntropyLanes + t;
+    const uint32_t t = threadIdx.x, u = (starts ? load_const(&starts[block]) : block * kEntropyLanes) + t;
+    if (starts) nunits = load_const(&starts[block + 1]);
     const Unit un = units[u < nunits ? u : 0u];
     LaneDcUnit U;
     U.ok = false;
@@ -1196,19 +1199,19 @@ PCR_D __attribute__((always_inline)) void dc_first_units(const DevRecord& R, con
     if (rc != kOk) R.status[un.img] = rc;
 }
 __global__ void __launch_bounds__(kEntropyLanes, 4) k_dc_first_lanes(DevRecord R, const Unit* __restrict__ units, uint32_t nunits,
-        const uint32_t* __restrict__ clean32, uint32_t to_planes) {
+        const uint32_t* __restrict__ starts, const uint32_t* __restrict__ clean32, uint32_t to_planes) {
     __shared__ LaneRing rings;
-    dc_first_units(R, units, nunits, blockIdx.x, clean32, to_planes, &rings);
+    dc_first_units(R, units, nunits, starts, blockIdx.x, clean32, to_planes, &rings);
 }
 // DC and AC first scans of one level in one launch: the first dc_blocks workgroups are k_dc_first_lanes', the others
 // k_ac_first_lanes'.  Both take as long as their longest unit and leave most of the chip idle meanwhile; one behind the
 // other they took the sum: 1024 x 256 x 256 at scan group 5 62 us for the DC scans by wavefronts + 82, 1024 photographs
 // at 2 136 + 108.  (Kept on their own where stages are timed, and for calls with only one of the two.)
-__global__ void __launch_bounds__(kEntropyLanes, 4) k_first_lanes(DevRecord R, const Unit* __restrict__ dc_units, uint32_t n_dc, uint32_t dc_blocks,
+__global__ void __launch_bounds__(kEntropyLanes, 4) k_first_lanes(DevRecord R, const Unit* __restrict__ dc_units, uint32_t n_dc, const uint32_t* __restrict__ dc_starts, uint32_t dc_blocks,
         const Unit* __restrict__ ac_units, const LaneJob* __restrict__ jobs, const uint32_t* __restrict__ clean32, uint32_t to_planes) {
     __shared__ uint4 tabs[kLaneTabs][kLaneTabPieces];
     __shared__ LaneRing rings;
-    if (blockIdx.x < dc_blocks) dc_first_units(R, dc_units, n_dc, blockIdx.x, clean32, to_planes, &rings);
+    if (blockIdx.x < dc_blocks) dc_first_units(R, dc_units, n_dc, dc_starts, blockIdx.x, clean32, to_planes, &rings);
     else ac_first_job(R, ac_units, jobs[blockIdx.x - dc_blocks], clean32, tabs, &rings);
 }
 

@@ -432,7 +432,7 @@ PCR_HD uint32_t of_first(uint32_t v) {
 // symbol picked its component's members with selects (1250 cycles, 110 instructions).
 // The lanes of a wavefront go MCU by MCU, block by block, in step, so which component a block belongs to is the same for
 // all of them and costs nothing: lanes whose MCUs look different (another sub-sampling, in another image) go after each
-// other.
+// other.  (Launches are cut so that none are: dc_units_by_shape.)
 PCR_HD __attribute__((always_inline)) int lane_decode_dc_first(const LaneDcUnit& U, LaneRing* rings, uint32_t lane) {
     LaneDcDef d0, d1, d2;
     lane_dc_def(&d0, U.def0, U.end); lane_dc_def(&d1, U.def1, U.end); lane_dc_def(&d2, U.def2, U.end);
@@ -450,7 +450,7 @@ PCR_HD __attribute__((always_inline)) int lane_decode_dc_first(const LaneDcUnit&
     const uint32_t mx = U.mcu0 - my * U.mcu_w;
     uint32_t b0 = U.pblk0 + my * U.vs0 * U.bw0 + mx * U.hs0, b1 = U.pblk1 + my * U.vs1 * U.bw1 + mx * U.hs1, b2 = U.pblk2 + my * U.vs2 * U.bw2 + mx * U.hs2;   // the MCU's first block of each component
     const uint32_t skip0 = U.vs0 * U.bw0 - U.mcu_w * U.hs0, skip1 = U.vs1 * U.bw1 - U.mcu_w * U.hs1, skip2 = U.vs2 * U.bw2 - U.mcu_w * U.hs2;
-    const uint32_t shape = U.ns | U.hs0 << 4 | U.vs0 << 8 | U.hs1 << 12 | U.vs1 << 16 | U.hs2 << 20 | U.vs2 << 24;
+    const uint32_t shape = dc_shape(U.ns, U.hs0, U.vs0, U.hs1, U.vs1, U.hs2, U.vs2);
     int pred0 = U.pred0, pred1 = U.pred1, pred2 = U.pred2;
     uint32_t bad = 0;
     bool done = false;

@@ -42,6 +42,7 @@ struct LevelList {
     uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units k_sequential_split has dealt with
     uint32_t n_long = 0; uint64_t long_bytes = 0; bool subsampled = false;        // ... how many those are, their bytes, whether some have MCUs of several blocks per component
     DcLaunch dc;                                                                 // DC first scans: what decides between lanes and wavefronts
+    uint32_t* d_dc_starts = nullptr; uint32_t n_dc_waves = 0;                    // ... wavefronts of lanes, and where they begin if their MCUs are of several shapes
     bool chained = false;                                                        // the plan's chains hold these units too
 };
 
@@ -339,7 +340,7 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             }
             const size_t li = (size_t)(r->level[ig] - 1) * kNumKinds + kind;
             if (cnt) runs[li].push_back(Run{i, g, cnt, sd.data_len / cnt});
-            plan_bytes += cnt * sizeof(Unit) + (cnt / kEntropyLanes + 1) * sizeof(LaneJob);
+            plan_bytes += cnt * sizeof(Unit) + (cnt / kEntropyLanes + 1) * sizeof(LaneJob);   // (more than dc_units_by_shape's starts take)
         }
         if (have_dc != (1u << r->img[i].nc) - 1u) plan.dc_complete = false;
         for (int c = 0; c < r->img[i].nc; c++) if (refine[c]) {
@@ -371,7 +372,21 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         static_assert(kLaneTabs <= 8, "three bits tell the scans of a window apart");
         const bool by_length = lanes && !r->unit_bits.empty();
         uint32_t at = 0;
-        for (size_t w0 = 0; w0 < rn.size(); w0 += kLaneTabs) {
+        if (ll.kind == kDcFirst) {
+            std::vector<uint32_t> shape(rn.size()), count(rn.size());
+            for (size_t e = 0; e < rn.size(); e++) {
+                const ImgDesc& im = r->img[rn[e].img];
+                const ScanDesc& sd = r->scan[(size_t)rn[e].img * G + rn[e].scan];
+                ll.dc.add(im, sd, rn[e].count);
+                shape[e] = dc_mcu_shape(im, sd); count[e] = rn[e].count;
+            }
+            const std::vector<uint32_t> starts = dc_units_by_shape(shape, count, kEntropyLanes, [&](uint32_t e, uint32_t j) {
+                units[at++] = Unit{rn[e].img, rn[e].scan, j, r->slot_base[(size_t)rn[e].img * G + rn[e].scan]};
+            });
+            ll.n_dc_waves = starts.empty() ? (ll.n + kEntropyLanes - 1) / kEntropyLanes : (uint32_t)starts.size() - 1;
+            if (!starts.empty()) up.add(&ll.d_dc_starts, starts);
+        }
+        for (size_t w0 = 0; w0 < rn.size() && ll.kind != kDcFirst; w0 += kLaneTabs) {
             const size_t w1 = std::min(rn.size(), w0 + kLaneTabs);
             const uint32_t first = at;
             if (by_length) {
@@ -404,9 +419,6 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         if (!jobs.empty()) {
             ll.n_jobs = (uint32_t)jobs.size();
             up.add(&ll.d_jobs, jobs);
-        }
-        if (ll.kind == kDcFirst) {
-            for (const Run& q : rn) ll.dc.add(r->img[q.img], r->scan[(size_t)q.img * G + q.scan], q.count);
         }
         if (ll.kind == kSequential) {
             for (const Run& q : rn) {
@@ -516,7 +528,7 @@ bool lanes_pay(const pcr_record* r, const LevelList& l) {
 bool dc_lanes_pay(const pcr_record* r, const LevelList& l, bool beside) {
     if (r->lane_mode < 0) return false;
     if (r->lane_mode > 0) return l.n >= (uint32_t)kEntropyLanes;
-    return l.n >= l.dc.least_lanes(g_open_records.load(std::memory_order_relaxed) > 1, beside);
+    return l.dc.by_lanes(g_open_records.load(std::memory_order_relaxed) > 1, beside);
 }
 
 // Many lanes per long sequential scan, or one wavefront?  k_sequential_split has room for one scan per compute unit (150 KB
@@ -675,11 +687,10 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         const dim3 block(kEntropyLanes);
         if (with_ac(li) && !r->timing) {                     // (timed, each stage has a launch, and an interval, of its own)
             const auto& ac = plan->levels[++li];
-            const uint32_t dc_blocks = (l.n + kEntropyLanes - 1) / kEntropyLanes;
-            hipLaunchKernelGGL(k_first_lanes, dim3(dc_blocks + ac.n_jobs), block, 0, s, r->d, l.d_units, l.n, dc_blocks, ac.d_units, ac.d_jobs, c32, dc_to_planes ? 1u : 0u);
+            hipLaunchKernelGGL(k_first_lanes, dim3(l.n_dc_waves + ac.n_jobs), block, 0, s, r->d, l.d_units, l.n, l.d_dc_starts, l.n_dc_waves, ac.d_units, ac.d_jobs, c32, dc_to_planes ? 1u : 0u);
         }
         else if (l.kind == kDcFirst) {
-            if (by_lanes[li]) hipLaunchKernelGGL(k_dc_first_lanes, dim3((l.n + kEntropyLanes - 1) / kEntropyLanes), block, 0, s, r->d, l.d_units, l.n, c32, dc_to_planes ? 1u : 0u);
+            if (by_lanes[li]) hipLaunchKernelGGL(k_dc_first_lanes, dim3(l.n_dc_waves), block, 0, s, r->d, l.d_units, l.n, l.d_dc_starts, c32, dc_to_planes ? 1u : 0u);
             else waves(l);
             mark(r, PCR_STAGE_DC_FIRST, s);
         }

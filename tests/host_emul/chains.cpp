@@ -71,12 +71,27 @@ static int dc_launch(const uint8_t* rec, size_t nbytes, uint32_t k, DcLaunch* L)
 extern "C" int dc_launch_of(const uint8_t* rec, size_t nbytes, uint32_t k, uint32_t* out) {
     DcLaunch L;
     const int rc = dc_launch(rec, nbytes, k, &L);
-    out[0] = L.units; out[1] = L.scans; out[2] = (uint32_t)L.blocks;
+    out[0] = L.units; out[1] = L.scans; out[2] = (uint32_t)L.blocks; out[3] = L.longest;
     return rc;
 }
-// does a launch of so many scans, cut into so many units of so many blocks each, go to the lanes?
-extern "C" int dc_by_lanes(uint32_t scans, uint32_t units, uint32_t blocks, int several, int beside) {
+// does a launch of so many scans, cut into so many units of so many blocks in all, the longest of so many, go to the lanes?
+extern "C" int dc_by_lanes(uint32_t scans, uint32_t units, uint32_t blocks, uint32_t longest, int several, int beside) {
     DcLaunch L;
-    L.scans = scans; L.units = units; L.blocks = (uint64_t)blocks * units;
-    return units >= L.least_lanes(several != 0, beside != 0);
+    L.scans = scans; L.units = units; L.blocks = blocks; L.longest = longest;
+    return L.by_lanes(several != 0, beside != 0);
+}
+
+// order of the units of n runs: out[2 i], out[2 i + 1] = run and number of the i-th; starts: where wavefronts begin; returns how many
+extern "C" int dc_order(const uint32_t* shape, const uint32_t* count, uint32_t n, uint32_t lanes, uint32_t* out, uint32_t* starts) {
+    size_t at = 0;
+    const auto v = dc_units_by_shape(std::vector<uint32_t>(shape, shape + n), std::vector<uint32_t>(count, count + n), lanes, [&](uint32_t e, uint32_t j) { out[at++] = e; out[at++] = j; });
+    std::copy(v.begin(), v.end(), starts);
+    return (int)v.size() - 1;
+}
+extern "C" uint32_t dc_shape_of(uint32_t ns, const uint32_t* comp, const uint32_t* hs, const uint32_t* vs) {
+    ImgDesc img; ScanDesc sd;
+    memset(&img, 0, sizeof img); memset(&sd, 0, sizeof sd);
+    sd.ns = (uint8_t)ns;
+    for (uint32_t c = 0; c < (uint32_t)kMaxComp; c++) { sd.comp[c] = (uint8_t)comp[c]; img.hs[c] = (uint8_t)hs[c]; img.vs[c] = (uint8_t)vs[c]; }
+    return dc_mcu_shape(img, sd);
 }

@@ -86,43 +86,85 @@ def test_any_sequence_of_scans_is_ordered(plan):
         _check(scans, plan(scans, k0, k)[1], k0, k)
 
 
-@pytest.mark.parametrize("size, sub, interval, units, blocks", [
-    ((256, 256), 2, 64, 8, 192), ((256, 256), 2, 128, 4, 384), ((600, 450), 1, 64, 134, 4275 * 3 / 134), ((256, 256), 2, 0, 1, 1536), ((45, 30), 2, 1, 6, 6)])
-def test_dc_units_of_a_written_record(plan, size, sub, interval, units, blocks):
-    """What the choice of decoder for DC first scans goes by: their entry points are twice as many as the interval says."""
+@pytest.mark.parametrize("size, sub, interval, units, blocks, longest", [
+    ((256, 256), 2, 64, 8, 1536, 192), ((256, 256), 2, 128, 4, 1536, 384), ((600, 450), 1, 64, 134, 4275 * 3, 96), ((256, 256), 2, 0, 1, 1536, 1536), ((45, 30), 2, 1, 6, 36, 6),
+    ((200, 136), 2, 32, 8, 117 * 6, 90)])
+def test_dc_units_of_a_written_record(plan, size, sub, interval, units, blocks, longest):
+    """What the choice of decoder for DC first scans goes by: their entry points are twice as many as the interval says.  (The
+    longest unit is taken from the mean of its scan, 117 / 8 MCUs in the last row.)"""
     import paper_1911_00472_amd as pkg
     import pcrgen
     files = [pcrgen.make_jpeg(40 + i, 1, size[0], size[1], 3, 6.0, sub, sub, 80) for i in range(2)]
     rec = np.frombuffer(pkg.record_write_indexed(files, None, interval) if interval else pcrgen.write_record(files), np.uint8)
-    out = np.zeros(3, np.uint32)
+    out = np.zeros(4, np.uint32)
     u32p, u8p = ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(ctypes.c_uint8)
     plan.lib.dc_launch_of.argtypes = [u8p, ctypes.c_size_t, ctypes.c_uint32, u32p]
     assert plan.lib.dc_launch_of(rec.ctypes.data_as(u8p), len(rec), 2, out.ctypes.data_as(u32p)) == 0
-    assert tuple(out) == (2 * units, 2, 2 * units * blocks)
+    assert tuple(out) == (2 * units, 2, 2 * blocks, longest)
 
 
-# us a call by wavefronts and by lanes: several records open, beside AC scans by wavefronts, blocks per unit, whole scans,
-# {units of a launch: (wavefronts, lanes)}
+# us a call by wavefronts and by lanes: several records open, beside AC scans by wavefronts, whole scans, blocks of the longest
+# unit, mean over longest, {units of a launch: (wavefronts, lanes)}
 DC_TIMES = [
-    (0, 0, 32, 0, {2048: (61, 69), 4096: (67, 71), 8192: (72, 66)}), (0, 0, 96, 0, {2144: (78, 91), 4288: (88, 92), 8576: (106, 93)}),
-    (0, 0, 192, 0, {2048: (89, 110), 4096: (112, 118), 6144: (131, 127), 8192: (151, 134)}),
-    (0, 0, 384, 0, {2048: (124, 155), 4096: (161, 171), 6144: (224, 214), 8192: (271, 237)}),
-    (0, 0, 3072, 0, {4096: (908, 991), 6144: (1180, 1175), 8192: (1504, 1333)}),
-    (0, 0, 9, 1, {2048: (81, 96), 4096: (112, 117), 6144: (149, 148), 8192: (190, 177)}),
-    (0, 0, 216, 1, {2048: (129, 140), 4096: (208, 196), 6144: (261, 233), 8192: (341, 289)}),
-    (0, 0, 384, 1, {2048: (165, 189), 4096: (235, 226), 6144: (331, 303), 8192: (444, 379)}),
-    (0, 0, 864, 1, {2048: (230, 289), 4096: (401, 405), 6144: (535, 507), 8192: (695, 609)}),
-    (0, 0, 3750, 1, {2048: (743, 1031), 4096: (1178, 1274), 6144: (1539, 1528), 8192: (2006, 1787)}),
-    (1, 0, 192, 0, {2048: (214, 233), 4096: (286, 229), 6144: (366, 273)}), (1, 0, 384, 1, {2048: (453, 472), 4096: (823, 724)}),
-    (1, 0, 1536, 1, {2048: (1043, 1238), 3072: (1478, 1506), 4096: (1912, 1785)}),
-    (0, 1, 192, 0, {2048: (134, 177), 4096: (182, 210), 8192: (328, 325)}), (0, 1, 96, 0, {2144: (105, 133), 4288: (126, 147), 8576: (178, 183), 12864: (223, 218)}),
-    (0, 1, 384, 1, {4096: (416, 465), 8192: (737, 735), 12288: (1062, 1017)}),
-    (1, 1, 384, 1, {2048: (774, 863), 4096: (1402, 1361), 8192: (2647, 2403)}), (1, 1, 96, 0, {2144: (224, 272), 4288: (337, 336), 8576: (535, 472)}),
+    (0, 0, 0, 32, 1, {2048: (61, 69), 4096: (67, 71), 8192: (72, 66)}), (0, 0, 0, 96, 1, {2144: (78, 91), 4288: (88, 92), 8576: (106, 93)}),
+    (0, 0, 0, 192, 1, {2048: (89, 110), 4096: (112, 118), 6144: (131, 127), 8192: (151, 134)}),
+    (0, 0, 0, 384, 1, {2048: (124, 155), 4096: (161, 171), 6144: (224, 214), 8192: (271, 237)}),
+    (0, 0, 0, 3072, 1, {4096: (908, 991), 6144: (1180, 1175), 8192: (1504, 1333)}),
+    (0, 0, 1, 9, 1, {2048: (81, 96), 4096: (112, 117), 6144: (149, 148), 8192: (190, 177)}),
+    (0, 0, 1, 216, 1, {2048: (129, 140), 4096: (208, 196), 6144: (261, 233), 8192: (341, 289)}),
+    (0, 0, 1, 384, 1, {2048: (165, 189), 3072: (201, 209), 4096: (235, 226), 6144: (331, 303), 8192: (444, 379)}),
+    (0, 0, 1, 864, 1, {2048: (230, 289), 4096: (401, 405), 6144: (535, 507), 8192: (695, 609)}),
+    (0, 0, 1, 3750, 1, {2048: (743, 1031), 4096: (1178, 1274), 6144: (1539, 1528), 8192: (2006, 1787)}),
+    (0, 0, 1, 216, 130 / 216, {4096: (158, 161), 6144: (208, 195), 8192: (267, 233), 12288: (377, 307)}),
+    (0, 0, 1, 384, 188 / 384, {4096: (174, 199), 6144: (227, 235), 8192: (288, 276), 12288: (422, 364)}),
+    (0, 0, 1, 726, 470 / 726, {4096: (243, 281), 6144: (349, 359), 8192: (462, 440), 12288: (682, 590)}),
+    (0, 0, 1, 1536, 698 / 1536, {4096: (341, 489), 8192: (588, 675), 12288: (849, 851)}), (0, 0, 1, 2790, 979 / 2790, {8192: (721, 999), 12288: (984, 1175)}),
+    (1, 0, 0, 192, 1, {2048: (214, 233), 4096: (286, 229), 6144: (366, 273)}), (1, 0, 1, 384, 1, {2048: (453, 472), 4096: (823, 724)}),
+    (1, 0, 1, 1536, 1, {2048: (1043, 1238), 3072: (1478, 1506), 4096: (1912, 1785)}),
+    (1, 0, 1, 384, 188.5 / 384, {1024: (196, 279), 2048: (295, 348), 4096: (547, 478), 6144: (767, 648)}),
+    (1, 0, 1, 720, 258 / 720, {2048: (360, 513), 4096: (556, 659), 6144: (852, 795)}), (1, 0, 1, 1260, 653 / 1260, {2048: (536, 826), 4096: (847, 1058), 6144: (1339, 1294)}),
+    (1, 0, 1, 1944, 1324 / 1944, {2048: (875, 1261), 4096: (1576, 1712)}),
+    (0, 1, 0, 192, 1, {2048: (134, 177), 4096: (182, 210), 8192: (328, 325)}), (0, 1, 0, 96, 1, {2144: (105, 133), 4288: (126, 147), 8576: (178, 183), 12864: (223, 218)}),
+    (0, 1, 1, 384, 1, {4096: (416, 465), 8192: (737, 735), 12288: (1062, 1017)}), (0, 1, 1, 726, 470 / 726, {6144: (624, 704), 12288: (1154, 1152)}),
+    (1, 1, 1, 384, 1, {2048: (774, 863), 4096: (1402, 1361), 8192: (2647, 2403)}), (1, 1, 0, 96, 1, {2144: (224, 272), 4288: (337, 336), 8576: (535, 472)}),
+    (1, 1, 1, 1260, 653 / 1260, {4096: (1789, 1937), 6144: (2576, 2562)}),
 ]
 
 
-@pytest.mark.parametrize("several, beside, blocks, whole, times", DC_TIMES)
-def test_dc_scans_go_where_they_were_measured_to_be_faster(plan, several, beside, blocks, whole, times):
+@pytest.mark.parametrize("several, beside, whole, longest, mean, times", DC_TIMES)
+def test_dc_scans_go_where_they_were_measured_to_be_faster(plan, several, beside, whole, longest, mean, times):
     for units, (wavefronts, lanes) in times.items():
-        by_lanes = plan.lib.dc_by_lanes(units if whole else units // 4, units, blocks, several, beside)
+        by_lanes = plan.lib.dc_by_lanes(units if whole else units // 4, units, round(units * longest * mean), longest, several, beside)
         assert (lanes if by_lanes else wavefronts) <= 1.05 * min(lanes, wavefronts), units
+
+
+@pytest.mark.parametrize("shapes, most", [(1, 9), (2, 1), (3, 200), (4, 9)])
+def test_no_wavefront_has_dc_units_of_several_shapes(plan, shapes, most):
+    """Sixty-four units to a wavefront, but for the last of each shape; units of a shape keep their order."""
+    rng = np.random.default_rng(shapes)
+    shape, count = rng.integers(0, shapes, 300, dtype=np.uint32), rng.integers(1, most + 1, 300, dtype=np.uint32)
+    total = int(count.sum())
+    out, starts = np.zeros((total, 2), np.uint32), np.zeros(total + 1, np.uint32)
+    u32p = ctypes.POINTER(ctypes.c_uint32)
+    waves = plan.lib.dc_order(shape.ctypes.data_as(u32p), count.ctypes.data_as(u32p), len(shape), 64, out.ctypes.data_as(u32p), starts.ctypes.data_as(u32p))
+    want = [(e, j) for e in range(len(shape)) for j in range(count[e])]
+    if shapes == 1:
+        assert waves == -1 and [tuple(u) for u in out] == want
+        return
+    assert sorted(map(tuple, out)) == want
+    for v in range(shapes):
+        assert [tuple(u) for u in out if shape[u[0]] == v] == [u for u in want if shape[u[0]] == v]
+    assert starts[0] == 0 and starts[waves] == total and waves <= total // 64 + shapes
+    for a, b in zip(starts[:waves], starts[1:waves + 1]):
+        assert a < b <= a + 64 and len(set(shape[out[a:b, 0]])) == 1
+
+
+def test_a_dc_scan_s_shape_is_of_its_own_components(plan):
+    """Two files whose scan of two components is decoded alike have the same shape, whatever the third component is."""
+    def of(ns, comp, hs, vs):
+        a = [np.array(v, np.uint32) for v in (comp, hs, vs)]
+        return plan.lib.dc_shape_of(ns, *[v.ctypes.data_as(ctypes.POINTER(ctypes.c_uint32)) for v in a])
+    assert of(2, (1, 2, 0), (2, 1, 1), (2, 1, 1)) == of(2, (1, 2, 0), (1, 1, 1), (1, 1, 1))
+    assert of(1, (0, 0, 0), (2, 1, 1), (2, 1, 1)) == of(1, (2, 0, 0), (1, 1, 1), (1, 1, 1))
+    assert of(3, (0, 1, 2), (2, 1, 1), (2, 1, 1)) != of(3, (0, 1, 2), (2, 1, 1), (1, 1, 1))
+    assert of(2, (0, 1, 0), (2, 1, 1), (2, 1, 1)) != of(2, (0, 1, 0), (1, 1, 1), (1, 1, 1))

@@ -36,6 +36,18 @@ def test_every_shape_in_one_wavefront(interval, k):
     _check(pkg.record_write_indexed(files, None, interval), k)
 
 
+def test_wavefronts_of_one_shape_and_some_of_several():
+    """More than sixty-four units of each shape, and some left over of each; the order is the wavefront decoders' too."""
+    files = []
+    for i in range(75):
+        hs, vs = ((2, 2), (1, 1), (2, 1), (1, 2))[i % 4]
+        files.append(pcrgen.encode_pixels(pcrgen.synth(90 + i, i % 3, 30 + 5 * (i % 9), 20 + 9 * (i % 6), 3, 3.0 + i % 7), hs, vs, 70 + i % 20))
+    rec = pkg.record_write_indexed(files, None, 2)
+    for k in (1, 2):
+        _check(rec, k)
+    _check(rec, 1, lanes=-1)
+
+
 @pytest.mark.parametrize("count", [64, 65, 127, 200])
 def test_tables_at_the_very_end_of_the_record(count):
     """Gray pictures of one block, the record cut behind its first scan group: the last table has fewer than 32 bytes."""
@@ -69,7 +81,7 @@ def test_tables_whose_last_code_is_all_ones(name):
 
 
 @pytest.mark.parametrize("side, interval, pictures, k, others", [
-    (64, 0, 4095, 1, 0), (64, 0, 4096, 1, 0),          # whole scans of 96 blocks: to the lanes from 4096 on
+    (64, 0, 3583, 1, 0), (64, 0, 3584, 1, 0),          # whole scans of 96 blocks: to the lanes from 3584 on
     (24, 1, 1535, 1, 0), (24, 1, 1536, 1, 0),          # four units a scan: from 6144 on
     (24, 1, 1023, 1, 1), (24, 1, 1024, 1, 1),          # with a second record open: from 4096 on
     (24, 1, 2047, 2, 0), (24, 1, 2048, 2, 0),          # where they could be beside AC scans by wavefronts: from 8192 on
