@@ -205,7 +205,8 @@ struct LaneLookup {
         return reinterpret_cast<const uint16_t*>(tab)[i];
     }
     // ... and what to make of it: kCodeBad if there is no such code.  A decoder reads the entry of the next symbol as soon
-    // as it knows where that begins, does the rest of this symbol's work while LDS answers, and looks at it then.
+    // as it knows where that begins, does the rest of this symbol's work while LDS answers, and looks at it then; an entry of
+    // 0 is for by_limits.
     PCR_HD uint32_t resolve(uint32_t e, uint32_t win) const {
         if (PCR_RARELY(e == 0)) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -215,10 +216,8 @@ struct LaneLookup {
         }
         return e;
     }
-    // A decoder reads the entry of the next symbol as soon as it knows where that begins, does the rest of this symbol's work
-    // while LDS answers, and looks at it then; 0 is for by_limits.
-    // A code neither look-up knows (kCodeBad if there is no such code): limit[L - 8] is the first left-aligned 16-bit value that is not a code of length <= L,
-    // so the length is 9 + the number of limits at or below the code.
+    // A code neither look-up knows (kCodeBad if there is no such code): limit[L - 8] is the first left-aligned 16-bit value that
+    // is not a code of length <= L, so the length is 9 + the number of limits at or below the code.
     PCR_HD uint32_t by_limits(uint32_t c16) const {
         uint32_t L = 9, below = lim8;
 #pragma unroll
@@ -351,14 +350,14 @@ PCR_HD void lane_dc_def(LaneDcDef* D, const uint8_t* d, const uint8_t* end) {
 // The table of a definition.  Sixteen entries are pushed in at the top of each member and the definition's bytes taken from
 // the bottom of its words, so that no register is indexed.  Entries that are not there count as codes at a window of
 // sixteen ones: a code if the table's last one is all ones (no file should hold such a table, but the wavefront decoders
-// take it), and it is that one then, so they have its length and category.
+// take it).  It is that one then, and all sixteen entries count, so the last of them has its length and category.
 PCR_HD void lane_dc_codes(LaneDcCodes* T, LaneDcDef D) {
     auto down = [](uint32_t* w, int n) {                      // n words, one byte down
         for (int q = 0; q + 1 < n; q++) w[q] = (w[q] >> 8) | (w[q + 1] << 24);
         w[n - 1] >>= 8;
     };
     while (PCR_RARELY(D.ahead != 0)) if (D.ahead != 0) { down(D.w, 8); D.ahead--; }
-    uint32_t L = 0, code = 0, rem = 0, end = 0, last = 0;     // last: length - 1 and category of the last code so far
+    uint32_t L = 0, code = 0, rem = 0, end = 0, n = 0;
     uint64_t len = 0, cat = 0;
 #pragma unroll
     for (uint32_t q = 0; q < kLaneDcCodes / 2; q++) T->lim[q] = 0;
@@ -371,13 +370,14 @@ PCR_HD void lane_dc_codes(LaneDcCodes* T, LaneDcDef D) {
 #pragma unroll
         for (uint32_t q = 0; q + 1 < kLaneDcCodes / 2; q++) T->lim[q] = (T->lim[q] >> 16) | (T->lim[q + 1] << 16);
         T->lim[kLaneDcCodes / 2 - 1] = (T->lim[kLaneDcCodes / 2 - 1] >> 16) | (is ? left << 16 : 0xFFFF0000u);
-        last = is ? (L - 1u) | (D.w[4] & 15u) << 4 : last;
-        len = (len >> 4) | (uint64_t)(last & 15u) << 60; cat = (cat >> 4) | (uint64_t)(last >> 4) << 60;
+        n += is ? 1u : 0u;
+        len = (len >> 4) | (uint64_t)((L - 1u) & 15u) << 60; cat = (cat >> 4) | (uint64_t)(D.w[4] & 15u) << 60;
         down(D.w + 4, 4);
         end = is ? left + (1u << (16u - L)) : end;
         code += rem != 0 ? 1u : 0u; rem -= rem != 0 ? 1u : 0u;
     }
-    T->len = len; T->cat = cat; T->end = end;
+    const uint32_t sh = 4u * (n - 1u) & 63u;                  // the last code's
+    T->len = (len & ~0ull >> 4) | (len >> sh) << 60; T->cat = (cat & ~0ull >> 4) | (cat >> sh) << 60; T->end = end;
 }
 
 // entries above w (of sixteen)
