@@ -150,8 +150,9 @@ constexpr uint32_t kHeaderStage = 16384;                   // bytes of LDS for t
 constexpr uint32_t kHeaderWindow = 1024;                   // ... but at most this much per region (a first region with its tables is 600-700 bytes)
 constexpr uint32_t kHeaderWideImages = 512;                // kHeaderWaves wavefronts per workgroup whatever the scan group up to this many images
 // own_index up to this many images (a workgroup sums n lengths per scan group), but beyond half of it only where every wavefront
-// has one scan group at most.  us a call with k_index / without: 1024 pictures of 256 x 256 at scan group 5 280 / 273, four records of
-// 1024 photographs at 1 708 / 695, at 10 6022 / 6042.
+// has one scan group at most.  us a call with k_index / without: 1024 pictures of 256 x 256 at scan group 5 271 / 263, four records of
+// 1024 photographs at 1 708 / 695, at 10 6022 / 6042, of 64 x 64 at 10 721 / 717.  (The line is no loss's: 2048 pictures of 256 x 256
+// at 1 209 / 197, at 5 502 / 492, at 10 1158 / 1151, four such records at 10 3992 / 3979.)
 constexpr uint32_t kOwnIndexImages = 1024;
 
 // Record bytes by record offset: from the staged window, or (past it: long comments and profiles) from memory.
@@ -1407,7 +1408,7 @@ __global__ void __launch_bounds__(256) k_refine_blocks(DevRecord R, const Refine
 //   k > 0: replay the AC scans of the component in file order: first scans only extend the
 //          non-zero mask, refinement scans add a correction bit or place a new +-2^Al.
 // --------------------------------------------------------------------------------------
-// k_apply_prep (apply_prep) has gathered, per (image, component), the scans that matter for refinement; k_apply then
+// apply_prep (in the unstuffing launch) has gathered, per (image, component), the scans that matter for refinement; k_apply then
 // runs one lane per coefficient, a workgroup covering kApplyChunk consecutive coefficients.
 constexpr uint32_t kApplyChunk = 4096;
 
@@ -1586,7 +1587,7 @@ __global__ void __launch_bounds__(256) k_crop_resize(const uint32_t* __restrict_
 // The refinement is applied here, on the way in: the coefficient planes hold what the first scans wrote, and the
 // lane replays the component's refinement scans from the records the refinement kernels left (exactly what k_apply
 // does for the coefficient export, the only caller that needs the refined values in memory).  lists / list_idx:
-// the per-(image, component) scan lists of k_apply_prep and their index by image * 3 + component (-1: nothing to
+// the per-(image, component) scan lists of apply_prep and their index by image * 3 + component (-1: nothing to
 // refine); both null if no scan <= k refines.  kRefine = false compiles the replay out.
 // boxes (optional): one box per image; runs of MCUs that do not touch their image's box are skipped altogether
 // (their pixels are left as they are): for callers that go on to read only the boxes (pcr_decode_crop_batch).
@@ -1893,7 +1894,7 @@ PCR_D void pix_quant_table(const PixQuant& Q, const PixSteps& S, uint32_t nc, fl
     if (nthreads == 128 && wave == 0 && nc > 2) qz[2][k] = step(2, 1);    // (two wavefronts: the first has component 2 as well)
 }
 // the refinement scan lists of the image's components into LDS (all of them under way together)
-PCR_D void pix_lists(const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx, uint32_t img, uint32_t nc, ApplyList* rl, uint32_t tid, uint32_t nthreads) {
+PCR_D void pix_lists(const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx, uint32_t img, uint32_t nc, ApplyList* rl, uint32_t tid) {
     constexpr uint32_t kWords = sizeof(ApplyList) / 4;
     const int32_t* at = list_idx + img * kMaxComp;
     const int32_t l0 = at[0], l1 = at[1], l2 = at[2];
@@ -1956,8 +1957,9 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
     // Everything the run needs to know of its image, asked for at once, and the quantiser steps, the block's coefficients and
     // the lists behind it: three round trips to memory ahead of the transform where there were eight, one after the other,
     // half of a workgroup's time (measured: 53 % of the wavefronts' cycles waiting, now 39).  With the rows of the MCUs apart
-    // in LDS (pixel_mcu_samples) and both refinement passes at once (pix_refine), us alone: 1024 x 256 x 256 at scan group 5
-    // 137 -> 115, 128 x 1024 x 1024 310 -> 191, 256 x 600 x 450 4:4:4 at scan group 10 356 -> 219, 1024 photographs 460 -> 317.
+    // in LDS (pixel_mcu_samples) and both refinement passes at once (pix_refine), us for a record
+    // decoded alone: 1024 x 256 x 256 at scan group 5 137 -> 114, 128 x 1024 x 1024 254 -> 224, 256 x 600 x 450 4:4:4 at scan group 10
+    // 356 -> 219, 1024 photographs 460 -> 317.
     ImgDesc D;
     load_desc(R.img + timg, &D);
     const bool dead = load_const(&R.status[timg]) != kOk;
@@ -2004,7 +2006,7 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
         dc = pix_load(B, v);
     }
     // ---- prologue tables (the loads above are under way meanwhile) ----
-    if (kRefine) pix_lists(lists, list_idx, timg, nc, rl, tid, kPixLanes);
+    if (kRefine) pix_lists(lists, list_idx, timg, nc, rl, tid);
     pix_quant_table(Q, steps, nc, qz, tid, kPixLanes);
     if (tid < nm) {
         const uint32_t M = mcu0 + tid, my = M / mcux, mx = M - my * mcux;
@@ -2713,7 +2715,7 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
         pix_block(R, G, coef0, j, my, mc0 + ml, &B, &by, &bx);
         dc = pix_load(B, v);
     }
-    if (kRefine) pix_lists(lists, list_idx, timg, nc, rl, tid, kTailLanes);
+    if (kRefine) pix_lists(lists, list_idx, timg, nc, rl, tid);
     pix_quant_table(Q, steps, nc, qz, tid, kTailLanes);
     if (tid == 0) { row_lo = 0xFFFFFFFFu; row_hi = 0; }
     __syncthreads();

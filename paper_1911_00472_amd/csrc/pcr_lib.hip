@@ -597,7 +597,7 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, const
 
 // Steps 1-5 of the path (index .. entropy decode + refinement) for scans 1..k.
 // refine_in_memory: also run k_apply, which leaves the refined coefficients in the planes (the coefficient
-// export needs that; the pixel kernel replays the refinement itself from the lists of k_apply_prep).
+// export needs that; the pixel kernel replays the refinement itself from the lists of apply_prep).
 // k0 > 0: a fidelity upgrade -- groups 1 .. k0 are in the planes and masks already, only k0+1 .. k are decoded.
 int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_in_memory, Plan** plan_out) {
     Plan* plan = nullptr;

@@ -1,5 +1,5 @@
 """The runs of MCUs of k_pixel at their edges: pictures one MCU short of, at and beyond what a workgroup holds (121 gray
-MCUs, 42 of 4:4:4, 30 of 4:2:2 and 4:4:0, 21 of 4:2:0), in one row, in one column and in rows a run ends inside of, with
+MCUs, 42 of 4:4:4, 30 of 4:2:2, 32 of 4:4:0, 21 of 4:2:0), in one row, in one column and in rows a run ends inside of, with
 every refinement script a pass can be made alone or together with the one before it."""
 import numpy as np
 import pytest
