@@ -78,9 +78,11 @@ PCR_HD int parse_record_header(const uint8_t* bytes, uint64_t nbytes, RecordHead
 // entropy-coded data) and fills the image and scan descriptors.
 //   rec      record bytes: a pointer, or on the device anything indexed by record offset (HeaderBytes)
 //   off,len  index tables [G][n] (absolute offsets / lengths of the regions)
-// Every read is bounds-checked against the region it belongs to.  Bytes are taken twenty-four at a time (bytes24), enough
-// for a segment's marker and length with what is looked at of its payload, at one place in the code: on the device
-// code that runs once costs what it takes to fetch it, and a chain of byte reads would be as slow.
+// Every read is bounds-checked against the region it belongs to.  On the device bytes are taken twenty-four at a time (head_at),
+// enough for a segment's marker and length with what is looked at of its payload, at one place in the code: code that runs once
+// costs what it takes to fetch it, and a chain of byte reads would be as slow.  The host reads them where they are (through the
+// same twenty-four bytes its parse of 2048 small 4:4:4 pictures, three regions each, took 383 us; byte reads and selects
+// before 336; now 301).
 // The walk over a region's segments (walk_region) needs nothing from other regions; what a scan takes over from
 // earlier ones -- tables in force, restart interval, the scans it refines -- is put together afterwards
 // (resolve_scan, scan_history).  The host goes through an image's regions one by one (parse_image), the device
@@ -94,21 +96,30 @@ struct RegionWalk {
     int32_t ri;                            // restart interval defined here, -1: none
 };
 
-// Bytes p .. p + 23, little endian; what lies at `end` or behind it says nothing.
-PCR_HD void bytes24(const uint8_t* rec, uint32_t p, uint32_t end, uint64_t v[3]) {
-    v[0] = v[1] = v[2] = 0;
-    if (end - p >= 24) { __builtin_memcpy(v, rec + p, 24); return; }
-    for (uint32_t b = 0; b < 24; b++) if (b < end - p) v[b >> 3] |= (uint64_t)rec[p + b] << (8 * (b & 7));
-}
 PCR_HD uint32_t byte_of(uint64_t v, uint32_t b) { return (uint32_t)(v >> (8 * b)) & 255u; }
-// sum of the eight bytes
-PCR_HD uint32_t sum_bytes(uint64_t v) {
+// What walk_region sees of a segment, or of a table in one: its first bytes.  Host: where they are (walk_region has looked at the
+// bounds before it asks).  Device: twenty-four of them in scalar registers (head_at for HeaderBytes, pcr_kernels.h).
+struct HostHead {
+    const uint8_t* q; uint32_t there;
+    PCR_HD uint32_t byte(uint32_t i) const { return q[i]; }
+    PCR_HD void skip_marker() { q += 4; there -= 4; }
+    PCR_HD uint32_t counts() const { uint32_t t = 0; for (uint32_t i = 1; i <= 16; i++) t += q[i]; return t; }        // of a Huffman table
+    PCR_HD void first16(uint64_t h[2]) const {                      // (what is not there: zeros)
+        h[0] = h[1] = 0;
+        if (there >= 16) { __builtin_memcpy(h, q, 16); return; }
+        for (uint32_t i = 0; i < there; i++) h[i >> 3] |= (uint64_t)q[i] << (8 * (i & 7));
+    }
+};
+PCR_HD HostHead head_at(const uint8_t* rec, uint32_t p, uint32_t end) { return HostHead{rec + p, end - p}; }
+
+// a[i] = v, i < N.  (Device: one store to LDS.  Host: a select per entry, because what one entry was stored to is read as a whole
+// right after, and a wide load waits for a narrow store it overlaps.)
+template <int N, class T>
+PCR_HD void set_entry(T* a, uint32_t i, T v) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    return __builtin_amdgcn_sad_u8((uint32_t)v, 0u, __builtin_amdgcn_sad_u8((uint32_t)(v >> 32), 0u, 0u));
+    a[i] = v;
 #else
-    uint32_t t = 0;
-    for (uint32_t b = 0; b < 8; b++) t += byte_of(v, b);
-    return t;
+    for (uint32_t t = 0; t < (uint32_t)N; t++) a[t] = t == i ? v : a[t];
 #endif
 }
 
@@ -127,7 +138,7 @@ PCR_HD void setup_geometry(ImgDesc* d) {
 }
 
 // The segments of region g up to its scan header.  The frame header goes into *img (region 0 must hold it, later
-// regions must not).  On the device a wavefront walks a region: what bytes24 returns is the same in all lanes and known to
+// regions must not).  On the device a wavefront walks a region: what head_at returns is the same in all lanes and known to
 // be (uni), so that all of this is scalar code, and *w and *img lie in LDS.
 template <class Bytes>
 PCR_HD int walk_region(const Bytes& rec, uint32_t p, uint32_t end, uint32_t g, RegionWalk* w, ImgDesc* img) {
@@ -143,48 +154,46 @@ PCR_HD int walk_region(const Bytes& rec, uint32_t p, uint32_t end, uint32_t g, R
     while (true) {                                           // one turn per segment, or per table of a segment that holds several
         const bool fresh = s >= se;
         if (fresh && end - p < 4) return kEFormat;
-        uint64_t v[3];
-        bytes24(rec, fresh ? p : s, end, v);
+        auto h = head_at(rec, fresh ? p : s, end);
         if (fresh) {
-            if (byte_of(v[0], 0) != 0xFF) return kEFormat;
-            m = byte_of(v[0], 1);
+            if (h.byte(0) != 0xFF) return kEFormat;
+            m = h.byte(1);
             if (m == 0xFF) { p++; continue; }
-            const uint32_t L = (byte_of(v[0], 2) << 8) | byte_of(v[0], 3);
+            const uint32_t L = (h.byte(2) << 8) | h.byte(3);
             if (L < 2 || L + 2 > end - p) return kEFormat;
             s = p + 4; se = p + 2 + L;
             p = se;
-            v[0] = (v[0] >> 32) | (v[1] << 32); v[1] = (v[1] >> 32) | (v[2] << 32); v[2] >>= 32;
+            h.skip_marker();
         }
-        const uint32_t first = byte_of(v[0], 0), left = se - s;
+        const uint32_t left = se - s, first = left ? h.byte(0) : 0u;
         if (m == 0xDB) {
             if (left == 0) continue;
             const uint32_t pq = first >> 4, tq = first & 15;
             if (tq > 3 || pq > 1 || left - 1 < 64 * (pq + 1)) return kEFormat;
-            w->qoff[tq] = s + 1; w->qprec[tq] = (uint8_t)pq;
+            set_entry<4>(w->qoff, tq, s + 1); set_entry<4>(w->qprec, tq, (uint8_t)pq);
             s += 1 + 64 * (pq + 1);
         } else if (m == 0xC4) {
             if (left == 0) continue;
             const uint32_t tc = first >> 4, th = first & 15;
             if (tc > 1 || th > 3 || left < 17) return kEFormat;
-            const uint32_t nv = sum_bytes(v[0] >> 8) + sum_bytes(v[1]) + byte_of(v[2], 0);
+            const uint32_t nv = h.counts();
             if (nv > 256 || left - 17 < nv) return kEFormat;
-            w->dht[tc * 4 + th] = s + 1;
+            set_entry<8>(w->dht, tc * 4 + th, s + 1);
             s += 17 + nv;
         } else if (m == 0xC0 || m == 0xC1 || m == 0xC2) {
             if (have_frame || left < 6) return kEFormat;
             if (first != 8) return kEUnsupported;
-            const uint32_t nc = byte_of(v[0], 5);
+            const uint32_t nc = h.byte(5);
             img->progressive = (m == 0xC2);
-            img->H = (uint16_t)((byte_of(v[0], 1) << 8) | byte_of(v[0], 2)); img->W = (uint16_t)((byte_of(v[0], 3) << 8) | byte_of(v[0], 4)); img->nc = (uint8_t)nc;
+            img->H = (uint16_t)((h.byte(1) << 8) | h.byte(2)); img->W = (uint16_t)((h.byte(3) << 8) | h.byte(4)); img->nc = (uint8_t)nc;
             if (img->H == 0 || img->W == 0) return kEUnsupported;
             if (nc != 1 && nc != 3) return kEUnsupported;
             if (left < 6u + 3u * nc) return kEFormat;
-            const uint64_t comps[3] = {(v[0] >> 48) | (v[1] << 16), v[1] >> 8, v[1] >> 32};      // three bytes each
             for (uint32_t c = 0; c < (uint32_t)kMaxComp; c++) {
                 if (c >= nc) continue;
-                const uint32_t h = byte_of(comps[c], 1) >> 4, vs = byte_of(comps[c], 1) & 15, tq = byte_of(comps[c], 2);
-                img->cid[c] = (uint8_t)byte_of(comps[c], 0); img->hs[c] = (uint8_t)h; img->vs[c] = (uint8_t)vs; img->tq[c] = (uint8_t)tq;
-                if (h < 1 || h > 2 || vs < 1 || vs > 2 || tq > 3) return kEUnsupported;
+                const uint32_t hs = h.byte(7 + 3 * c) >> 4, vs = h.byte(7 + 3 * c) & 15, tq = h.byte(8 + 3 * c);
+                img->cid[c] = (uint8_t)h.byte(6 + 3 * c); img->hs[c] = (uint8_t)hs; img->vs[c] = (uint8_t)vs; img->tq[c] = (uint8_t)tq;
+                if (hs < 1 || hs > 2 || vs < 1 || vs > 2 || tq > 3) return kEUnsupported;
             }
             if (nc == 1) { img->hs[0] = 1; img->vs[0] = 1; }
             setup_geometry(img);
@@ -194,12 +203,12 @@ PCR_HD int walk_region(const Bytes& rec, uint32_t p, uint32_t end, uint32_t g, R
             return kEUnsupported;                  // lossless, hierarchical, arithmetic coding, DNL
         } else if (m == 0xDD) {
             if (left < 2) return kEFormat;
-            w->ri = (int32_t)((first << 8) | byte_of(v[0], 1));
+            w->ri = (int32_t)((first << 8) | h.byte(1));
             s = se;
         } else if (m == 0xDA) {
             if (!have_frame || left < 1) return kEFormat;
             w->sos = s; w->sos_end = se;
-            w->sos_head[0] = v[0]; w->sos_head[1] = v[1];
+            h.first16(w->sos_head);
             return kOk;
         } else {
             s = se;                                // APPn, COM, anything else with a length: skipped
@@ -227,7 +236,11 @@ PCR_HD int resolve_scan(const RegionWalk& w, uint32_t end, const uint32_t dht[8]
         sd->comp[j] = (uint8_t)c;
         if (j == 0) comp0 = (uint32_t)c;
         if (td > 3 || ta > 3) return kEFormat;
-        for (uint32_t t = 0; t < 4; t++) { dc_def[j] = t == td ? dht[t] : dc_def[j]; ac_def[j] = t == ta ? dht[4 + t] : ac_def[j]; }
+#if defined(__HIP_DEVICE_COMPILE__)
+        for (uint32_t t = 0; t < 4; t++) { dc_def[j] = t == td ? dht[t] : dc_def[j]; ac_def[j] = t == ta ? dht[4 + t] : ac_def[j]; }   // (indexed, they would go to scratch memory)
+#else
+        dc_def[j] = dht[td]; ac_def[j] = dht[4 + ta];
+#endif
     }
     const uint64_t band = ns == 1 ? h0 >> 24 : ns == 2 ? h0 >> 40 : (h0 >> 56) | (h1 << 8);      // behind the components: Ss, Se, Ah and Al
     const uint32_t Ss = byte_of(band, 0), Se = byte_of(band, 1), Ah = byte_of(band, 2) >> 4, Al = byte_of(band, 2) & 15;

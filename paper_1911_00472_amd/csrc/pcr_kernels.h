@@ -163,8 +163,17 @@ struct HeaderBytes {
     GlobalBytes rec; LdsBytes lds; uint32_t base, count, room;   // room: bytes of the window, of which `count` are staged
     PCR_D uint8_t operator[](uint32_t p) const { const uint32_t o = p - base; return o < count ? lds[o] : rec[p]; }
 };
+// Twenty-four bytes, little endian; what lies at the region's end or behind it says nothing.
+struct DeviceHead {
+    uint64_t v[3];
+    PCR_D uint32_t byte(uint32_t i) const { return byte_of(v[i >> 3], i & 7); }     // (i: a constant, after inlining)
+    PCR_D void skip_marker() { v[0] = (v[0] >> 32) | (v[1] << 32); v[1] = (v[1] >> 32) | (v[2] << 32); v[2] >>= 32; }
+    PCR_D static uint32_t sum_bytes(uint64_t x) { return __builtin_amdgcn_sad_u8((uint32_t)x, 0u, __builtin_amdgcn_sad_u8((uint32_t)(x >> 32), 0u, 0u)); }
+    PCR_D uint32_t counts() const { return sum_bytes(v[0] >> 8) + sum_bytes(v[1]) + byte_of(v[2], 0); }
+    PCR_D void first16(uint64_t h[2]) const { h[0] = v[0]; h[1] = v[1]; }
+};
 // (Called with a wavefront, all lanes the same.  end: of the region the window is the head of.  The window starts on 16 bytes, and four bytes behind it may be read.)
-PCR_D void bytes24(const HeaderBytes& b, uint32_t p, uint32_t end, uint64_t v[3]) {
+PCR_D DeviceHead head_at(const HeaderBytes& b, uint32_t p, uint32_t end) {
     const uint32_t o = p - b.base;
     uint32_t w[6] = {0, 0, 0, 0, 0, 0};
     if (o + 24 <= b.room) {
@@ -181,8 +190,10 @@ PCR_D void bytes24(const HeaderBytes& b, uint32_t p, uint32_t end, uint64_t v[3]
             w[5] = (w[5] >> 8) | (x << 24);
         }
     }
+    DeviceHead h;
 #pragma unroll
-    for (int t = 0; t < 3; t++) v[t] = ((uint64_t)uni(w[2 * t + 1]) << 32) | uni(w[2 * t]);
+    for (int t = 0; t < 3; t++) h.v[t] = ((uint64_t)uni(w[2 * t + 1]) << 32) | uni(w[2 * t]);
+    return h;
 }
 
 // A canonical code's lengths, for building look-ups entry by entry: lim[L] = first left-aligned 16-bit value that is not
