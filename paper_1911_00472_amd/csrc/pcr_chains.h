@@ -146,7 +146,7 @@ struct DcLaunch {
         for (int j = 0; j < sd.ns; j++) per_mcu += sd.ns > 1 ? (uint32_t)img.hs[sd.comp[j]] * img.vs[sd.comp[j]] : 1u;
         if (n == 0) return;
         units += n; scans++; blocks += (uint64_t)sd.mcus * per_mcu;
-        longest = std::max(longest, (sd.mcus + n - 1) / n * per_mcu);
+        longest = std::max(longest, (n == 1 ? sd.mcus : (sd.mcus + n - 1) / n) * per_mcu);
     }
     // several: the process has more than one record open; beside: the launch could be part of one of AC scans by wavefronts
     bool by_lanes(bool several, bool beside) const {
@@ -165,18 +165,19 @@ inline uint32_t dc_mcu_shape(const ImgDesc& img, const ScanDesc& sd) {
     return dc_shape(sd.ns, f[0], f[1], f[2], f[3], f[4], f[5]);
 }
 
-// The units of a launch of DC first scans: run e, of which all MCUs have shape[e], has count[e] units; emit(e, unit) is called for
+// The units of a launch of DC first scans: of n runs, run e has run(e).count units, all of MCUs of run(e).shape; emit(e, unit) is called for
 // each of them in the order of the launch.  A wavefront of `lanes` lanes takes shapes one after the other, so where there are
 // several no wavefront gets more than one: returns the unit at which each begins, and their number at the end (empty: one
 // shape, a wavefront every `lanes` units).  Otherwise the order is that of the runs.  8192 pictures of 77 to 192 pixels a
 // side in four samplings, whole scans, scan group 1: 1204 us a call with the shapes as they come, 639 when a trip of the lane
 // decoder took a symbol of each lane whatever its shape; now 701 by lanes (and by wavefronts, to which they go).
-template <class Emit>
-std::vector<uint32_t> dc_units_by_shape(const std::vector<uint32_t>& shape, const std::vector<uint32_t>& count, uint32_t lanes, Emit emit) {
+template <class RunOf, class Emit>
+std::vector<uint32_t> dc_units_by_shape(uint32_t n, RunOf run, uint32_t lanes, Emit emit) {
     struct Group { uint32_t shape; std::vector<std::pair<uint32_t, uint32_t>> units; };
     std::vector<Group> groups;
     std::vector<uint32_t> starts;
-    const bool one = std::all_of(shape.begin(), shape.end(), [&](uint32_t v) { return v == shape[0]; });
+    bool one = true;
+    for (uint32_t e = 1; e < n; e++) one = one && run(e).shape == run(0).shape;
     if (!one) starts.push_back(0);
     auto wavefront = [&](Group& g) {
         if (g.units.empty()) return;
@@ -184,12 +185,13 @@ std::vector<uint32_t> dc_units_by_shape(const std::vector<uint32_t>& shape, cons
         starts.push_back(starts.back() + (uint32_t)g.units.size());
         g.units.clear();
     };
-    for (uint32_t e = 0; e < shape.size(); e++) {
-        if (one) { for (uint32_t j = 0; j < count[e]; j++) emit(e, j); continue; }
+    for (uint32_t e = 0; e < n; e++) {
+        const uint32_t count = run(e).count, shape = run(e).shape;
+        if (one) { for (uint32_t j = 0; j < count; j++) emit(e, j); continue; }
         size_t g = 0;
-        while (g < groups.size() && groups[g].shape != shape[e]) g++;
-        if (g == groups.size()) groups.push_back(Group{shape[e], {}});
-        for (uint32_t j = 0; j < count[e]; j++) {
+        while (g < groups.size() && groups[g].shape != shape) g++;
+        if (g == groups.size()) groups.push_back(Group{shape, {}});
+        for (uint32_t j = 0; j < count; j++) {
             groups[g].units.emplace_back(e, j);
             if (groups[g].units.size() == lanes) wavefront(groups[g]);
         }

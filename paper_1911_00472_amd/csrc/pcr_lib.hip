@@ -312,8 +312,9 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     Plan plan;
     // Per (dependency level, kind of scan), the runs of units that belong to one scan (bytes: the scan's mean per unit):
     // ordering a list scan by scan moves whole runs, a few thousand of them, not hundreds of thousands of units.
-    struct Run { uint32_t img, scan, count, bytes; };
+    struct Run { uint32_t img, scan, count, bytes, shape; };         // (shape: DC first scans)
     std::vector<std::vector<Run>> runs((size_t)r->max_level * kNumKinds);
+    std::vector<DcLaunch> dc(r->max_level);
     std::vector<std::vector<RefineScan>> rlists(r->max_level);
     std::vector<ApplyUnit> apply; uint32_t max_blk = 0;
     // (what the tables below take: every list is rounded up to kArenaAlign, jobs are one per window of scans at least)
@@ -339,7 +340,9 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
                 plan_bytes += sizeof(RefineScan) + 2 * sizeof(RefineTile) * (((uint32_t)r->img[i].bw[c] * r->img[i].bh[c] + 255) / 256);
             }
             const size_t li = (size_t)(r->level[ig] - 1) * kNumKinds + kind;
-            if (cnt) runs[li].push_back(Run{i, g, cnt, sd.data_len / cnt});
+            uint32_t shape = 0;
+            if (kind == kDcFirst) { shape = dc_mcu_shape(r->img[i], sd); dc[r->level[ig] - 1].add(r->img[i], sd, cnt); }
+            if (cnt) runs[li].push_back(Run{i, g, cnt, sd.data_len / cnt, shape});
             plan_bytes += cnt * sizeof(Unit) + (cnt / kEntropyLanes + 1) * sizeof(LaneJob);   // (more than dc_units_by_shape's starts take)
         }
         if (have_dc != (1u << r->img[i].nc) - 1u) plan.dc_complete = false;
@@ -373,14 +376,8 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         const bool by_length = lanes && !r->unit_bits.empty();
         uint32_t at = 0;
         if (ll.kind == kDcFirst) {
-            std::vector<uint32_t> shape(rn.size()), count(rn.size());
-            for (size_t e = 0; e < rn.size(); e++) {
-                const ImgDesc& im = r->img[rn[e].img];
-                const ScanDesc& sd = r->scan[(size_t)rn[e].img * G + rn[e].scan];
-                ll.dc.add(im, sd, rn[e].count);
-                shape[e] = dc_mcu_shape(im, sd); count[e] = rn[e].count;
-            }
-            const std::vector<uint32_t> starts = dc_units_by_shape(shape, count, kEntropyLanes, [&](uint32_t e, uint32_t j) {
+            ll.dc = dc[li / kNumKinds];
+            const std::vector<uint32_t> starts = dc_units_by_shape((uint32_t)rn.size(), [&](uint32_t e) -> const Run& { return rn[e]; }, kEntropyLanes, [&](uint32_t e, uint32_t j) {
                 units[at++] = Unit{rn[e].img, rn[e].scan, j, r->slot_base[(size_t)rn[e].img * G + rn[e].scan]};
             });
             ll.n_dc_waves = starts.empty() ? (ll.n + kEntropyLanes - 1) / kEntropyLanes : (uint32_t)starts.size() - 1;

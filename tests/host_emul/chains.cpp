@@ -84,7 +84,8 @@ extern "C" int dc_by_lanes(uint32_t scans, uint32_t units, uint32_t blocks, uint
 // order of the units of n runs: out[2 i], out[2 i + 1] = run and number of the i-th; starts: where wavefronts begin; returns how many
 extern "C" int dc_order(const uint32_t* shape, const uint32_t* count, uint32_t n, uint32_t lanes, uint32_t* out, uint32_t* starts) {
     size_t at = 0;
-    const auto v = dc_units_by_shape(std::vector<uint32_t>(shape, shape + n), std::vector<uint32_t>(count, count + n), lanes, [&](uint32_t e, uint32_t j) { out[at++] = e; out[at++] = j; });
+    struct Run { uint32_t shape, count; };
+    const auto v = dc_units_by_shape(n, [&](uint32_t e) { return Run{shape[e], count[e]}; }, lanes, [&](uint32_t e, uint32_t j) { out[at++] = e; out[at++] = j; });
     std::copy(v.begin(), v.end(), starts);
     return (int)v.size() - 1;
 }
