@@ -1434,9 +1434,10 @@ static void ssim_layout(const pcr_record* r, uint32_t* rows, uint32_t* tiles_max
 }
 static int launch_ssim(pcr_record* r, const uint8_t* d_a, const uint8_t* d_b, float2* part, uint32_t rows, uint32_t tmax, float* d_scores, hipStream_t s) {
     const uint32_t n = r->hdr.n;
-    if ((uint64_t)tmax * n >= (1ull << 31)) return PCR_E_UNSUPPORTED;
-    if (r->img[0].nc == 3) hipLaunchKernelGGL(k_ssim_tiles<3>, dim3(tmax * n), dim3(64), 0, s, r->d_dims, r->d.out_off, d_a, d_b, part, n, tmax, rows);
-    else hipLaunchKernelGGL(k_ssim_tiles<1>, dim3(tmax * n), dim3(64), 0, s, r->d_dims, r->d.out_off, d_a, d_b, part, n, tmax, rows);
+    const uint32_t every = ssim_workgroups(tmax);
+    if ((uint64_t)every * n >= (1ull << 31)) return PCR_E_UNSUPPORTED;
+    if (r->img[0].nc == 3) hipLaunchKernelGGL(k_ssim_tiles<3>, dim3(every * n), dim3(64), 0, s, r->d_dims, r->d.out_off, d_a, d_b, part, n, tmax, every, rows);
+    else hipLaunchKernelGGL(k_ssim_tiles<1>, dim3(every * n), dim3(64), 0, s, r->d_dims, r->d.out_off, d_a, d_b, part, n, tmax, every, rows);
     hipLaunchKernelGGL(k_ssim_score, dim3(n), dim3(64), 0, s, r->d_dims, part, tmax, rows, d_scores);
     return hipGetLastError() == hipSuccess ? PCR_OK : PCR_E_DEVICE;
 }

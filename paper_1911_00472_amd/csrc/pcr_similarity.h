@@ -62,6 +62,14 @@ __host__ __device__ inline uint32_t ssim_tiles_all(uint32_t W, uint32_t H, uint3
 constexpr uint32_t kSsimRowChoices[3] = {128, 64, 32};
 inline bool ssim_rows_suit(uint32_t n, uint32_t tiles_max) { return (uint64_t)n * tiles_max >= 8192; }
 
+// Workgroups per picture: one for each tile, and one more where that is a multiple of four.  Workgroups are dealt out to a die's 32
+// compute units in turn, and with such a number the long tiles of pictures of one size -- of the smallest scales, whose rows are
+// sixteen of pixels -- came to the same few units again and again.  us a call for n tiles a picture and n + 1: 220 pictures of
+// 375 x 500 (40 tiles of 128 rows) 570 / 427, of 350 x 350 (60 of 64) 343 / 273, 90 of 512 x 512 (108) 304 / 275, 300 of 128 x 128
+// (16 of 32) 76 / 61.  With n + 2 and n + 4 375 x 500 took 472 and 549; numbers that are twice an odd one are left alone (100 of
+// 200 x 200, 34 tiles: 66 / 76; 200: 120 / 114; 400 of 100 x 100, 10: 49 / 53).
+inline uint32_t ssim_workgroups(uint32_t tiles_max) { return tiles_max % 4 == 0 ? tiles_max + 1 : tiles_max; }
+
 // What the entry point that allocates nothing counts its limit in: tiles of 32 x 32 window positions of all scales.
 inline uint32_t ssim_limit_tiles(uint32_t W, uint32_t H) {
     uint32_t t = 0;
@@ -275,18 +283,19 @@ __device__ inline float ssim_strip(const uint8_t* A, const uint8_t* B, uint32_t 
 
 // part[i * tiles_max + t] = (sum of contrast-structure, sum of luminance x contrast-structure; only the one its scale
 // contributes) over the window positions of tile t of picture i; tiles are numbered scale by scale.
+// Workgroups: `every` per picture (ssim_workgroups), those beyond tiles_max have nothing to do.
 template <int C>
 __global__ void __launch_bounds__(64, 4) k_ssim_tiles(const uint32_t* __restrict__ dims, const uint64_t* __restrict__ out_off,
                                                     const uint8_t* __restrict__ pa, const uint8_t* __restrict__ pb,
-                                                    float2* __restrict__ part, uint32_t n, uint32_t tiles_max, uint32_t rows) {
+                                                    float2* __restrict__ part, uint32_t n, uint32_t tiles_max, uint32_t every, uint32_t rows) {
     // (a workgroup of one wavefront: with four to a workgroup the strips of a workgroup waited for its tallest before
     // the next workgroup had its LDS: twelve wavefronts a compute unit on average instead of fourteen, 1.64 ms and 1.56)
     __shared__ __attribute__((aligned(16))) SsimRows buf;
     const uint32_t lane = threadIdx.x;
     // (every die works through a contiguous eighth of the pictures: the scales of a picture read the same pixels)
-    const uint32_t item = xcd_major(blockIdx.x, gridDim.x), i = item / tiles_max;
+    const uint32_t item = xcd_major(blockIdx.x, gridDim.x), i = item / every;
     if (i >= n) return;
-    uint32_t t = item - i * tiles_max;
+    uint32_t t = item - i * every;
     const uint32_t W = dims[2 * i], H = dims[2 * i + 1];
     const int M = ssim_scale_count(W, H);
     const uint32_t slot = t;

@@ -41,3 +41,17 @@ def test_blocks_at_both_ends_of_the_buffer(w, h, C, sub, copies):
         got = r.msssim_batch(r.decode_batch(2), r.decode_batch(r.G)).cpu().numpy()
     assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
     assert abs(got[0] - oracle.msssim(a, b)) <= TOL
+
+
+@pytest.mark.parametrize("w,h,C,copies", [(40, 40, 3, 3), (64, 64, 3, 3), (65, 64, 1, 3), (128, 128, 3, 5), (200, 200, 1, 5), (220, 220, 3, 5), (65, 64, 1, 1100)])
+def test_workgroups_without_a_tile(w, h, C, copies):
+    """2, 4, 6, 16, 34 and 40 tiles of 32 rows a picture, and 4 of 128: a multiple of four has a workgroup more than tiles."""
+    sub = 2 if C == 3 else 1
+    files = [pcrgen.make_jpeg(820 + i, 1, w, h, C, 9.0, sub, sub, 85) for i in range(2)]
+    rec = pcrgen.write_record(files * copies)
+    want = [oracle.msssim(*(oracle.decode_record_image(rec, i, k)[1] for k in (2, oracle.record_header(rec)["G"]))) for i in range(2)]
+    with pkg.Record(rec) as r:
+        a, b = r.decode_batch(2), r.decode_batch(r.G)
+        got = r.msssim_batch(a, b).cpu().numpy().reshape(copies, 2)
+        assert np.array_equal(got, np.broadcast_to(got[0], got.shape))
+        assert np.abs(got[0] - np.array(want)).max() <= TOL
