@@ -57,8 +57,9 @@ __host__ __device__ inline uint32_t ssim_tiles_all(uint32_t W, uint32_t H, uint3
     return t;
 }
 // Rows per tile: ten rows are walked down before the first window is complete, so tall tiles waste less, but tiles of very
-// different heights leave the last wave of wavefronts ragged.  1024 photographs, ms: 192 rows 1.32, 128 1.31, 96 1.34,
-// 64 1.49.  A launch wants eight wavefronts per SIMD (8192); few or small pictures are cut finer to have them.
+// different heights leave the last wave of wavefronts ragged.  1024 photographs, ms: 192 rows 1.27, 128 1.28, 96 1.29,
+// 64 1.32, 32 1.43.  A launch wants eight wavefronts per SIMD (8192); few or small pictures are cut finer to have them.  us in strips
+// of 128 / 32 rows: 10 of 1024 x 1024 351 / 261, 30 471 / 398, 500 of 128 x 128 77 / 87, 100 photographs 255 / 273.
 constexpr uint32_t kSsimRowChoices[3] = {128, 64, 32};
 inline bool ssim_rows_suit(uint32_t n, uint32_t tiles_max) { return (uint64_t)n * tiles_max >= 8192; }
 
