@@ -1073,8 +1073,8 @@ PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab*
 }
 
 // Workgroup b: chain b of `chains`, or (without them) unit b of `units`, with a wavefront per unit.  Dynamic LDS:
-// kWaveTabBytes per wavefront.  ROLES: which kinds of scans there may be among them (each kind on its own leaves the
-// scalar registers to it).  FOLLOW: some scan of the launch follows another one; without it the decoders carry nothing of
+// kWaveTabBytes per wavefront.  ROLES: which kinds of scans there may be among them (each kind on its own has
+// more of the scalar registers: 26 are spilled for AC scans that follow, 107 with all kinds).  FOLLOW: some scan of the launch follows another one; without it the decoders carry nothing of
 // the gate, which costs an AC first scan three per cent of its instructions (plain photographs, four records in flight at
 // scan group 5, ms per step: 8.55 with, 7.95 without).
 constexpr int kWavesDc = 1, kWavesAc = 2;
