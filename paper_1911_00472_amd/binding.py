@@ -487,7 +487,7 @@ def transcode_symbol_counts(src_jpeg, coef, restart_interval=0):
 
 def transcode_files(files, device=0, threads=None, restart_interval=0, device_counts=True):
     """The paper's encoding step for a list of JPEG files (baseline or progressive): their coefficients are decoded
-    and the symbols of the new scans counted on the device, the progressive files written on the host.  Returns the
+    and coded as progressive scans on the device (on the host where device_counts is false or there are restart markers).  Returns the
     progressive files; record_write() groups them."""
     import torch
     bufs, ptrs, sizes = _file_table(files)

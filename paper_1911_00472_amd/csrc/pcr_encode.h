@@ -3,9 +3,9 @@
 // coefficients of a file as a progressive file (the lossless transcode the paper does with a stock tool
 // before it groups scans: same coefficients, ten scans for colour, six for gray).
 //
-// Everything here runs on the CPU: it is done once per dataset, not per batch.  The coefficients a transcode
+// What is here runs on the CPU: it is done once per dataset, not per batch.  The coefficients a transcode
 // starts from come from the device decoder (pcr_decode_coefficients), which reads baseline and progressive
-// sources alike.
+// sources alike; a whole batch is coded there as well (pcr_coder.h), and put together here.
 #pragma once
 #include <algorithm>
 #include <atomic>
@@ -21,6 +21,7 @@
 #include "pcr_format.h"
 #include "pcr_entropy.h"
 #include "pcr_hist.h"
+#include "pcr_coder.h"
 
 namespace pcr {
 namespace enc {
@@ -694,21 +695,11 @@ inline std::vector<ScanSpec> default_script(int nc) {
     return s;
 }
 
-// src: a JPEG file (baseline or progressive) whose frame header and quantisation tables are kept; coef: its
-// quantised coefficients, component planes one after the other, each [bh][bw][64] in natural order over the
-// MCU-padded block grid.  Appends the progressive file to *out.
-// restart_interval: MCUs of each scan between restart markers (0: none; a scan of one component counts its blocks).
-// counts (optional): the symbol counts of the scans, [scan][table slot][symbol] (kHistPerImage entries, as k_symbol_hist
-// writes them), used for the Huffman tables instead of counting the tokens here.  counts_out (optional): receives the
-// counts of the tokens; with it and out == nullptr nothing is written.
-inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int16_t* coef, size_t coef_count, uint32_t restart_interval,
-                                 std::vector<uint8_t>* out, const uint32_t* counts = nullptr, uint32_t* counts_out = nullptr) {
-    std::vector<uint8_t> scratch;
-    if (!out) out = &scratch;
-    if (counts_out) memset(counts_out, 0, sizeof(uint32_t) * kHistPerImage);
+// The frame of a file (its header and quantisation tables) whose coefficients, coef_count of them from `coef` on (null: elsewhere), are
+// to be coded.
+inline int read_frame(const uint8_t* src, size_t src_bytes, const int16_t* coef, size_t coef_count, ImgDesc* img_out, Frame* frame) {
     if (src_bytes >= (1ull << 32)) return kEUnsupported;
-    if (restart_interval > 65535) return kERange;
-    ImgDesc img; memset(&img, 0, sizeof img);
+    ImgDesc& img = *img_out; memset(&img, 0, sizeof img);
     ScanDesc first; memset(&first, 0, sizeof first);
     RegionWalk w;
     int rc = walk_region(src, 0, (uint32_t)src_bytes, 0, &w, &img);                   // up to the first scan header
@@ -716,18 +707,22 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
     if (rc == kOk) rc = scan_history(&first, 0);
     for (int t = 0; t < 4; t++) { img.qoff[t] = w.qoff[t]; img.qprec[t] = w.qprec[t]; }
     if (rc != kOk) return rc;
-    Frame F;
+    Frame& F = *frame;
     F.W = img.W; F.H = img.H; F.nc = img.nc; F.hmax = img.hmax; F.vmax = img.vmax; F.mcux = img.mcux; F.mcuy = img.mcuy;
     size_t need = 0;
     for (int c = 0; c < img.nc; c++) {
         F.hs[c] = img.hs[c]; F.vs[c] = img.vs[c]; F.tq[c] = img.tq[c]; F.cid[c] = img.cid[c];
         F.bw[c] = img.bw[c]; F.bh[c] = img.bh[c]; F.cw[c] = img.cw[c]; F.ch[c] = img.ch[c];
         if (!img.qoff[img.tq[c]]) return kEFormat;
-        F.plane[c] = coef + need;
+        F.plane[c] = coef ? coef + need : nullptr;
         need += (size_t)img.bw[c] * img.bh[c] * 64;
     }
     if (need != coef_count) return kERange;
-    for (int c = 0; c < img.nc; c++) F.masks[c].fill(F.plane[c], (size_t)img.bw[c] * img.bh[c]);
+    return kOk;
+}
+
+// What stands in a progressive file before its scans.
+inline void write_file_head(const uint8_t* src, const ImgDesc& img, const Frame& F, uint32_t restart_interval, std::vector<uint8_t>* out) {
     std::vector<uint8_t>& o = *out;
     o.push_back(0xFF); o.push_back(0xD8);
     bool done[4] = {false, false, false, false};
@@ -749,6 +744,84 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
         o.push_back(0xFF); o.push_back(0xDD);
         put_be16(&o, 4); put_be16(&o, restart_interval);
     }
+}
+
+// What stands in front of a scan's data behind its tables.
+inline void write_scan_head(const Frame& F, const ScanSpec& S, std::vector<uint8_t>* out) {
+    std::vector<uint8_t>& o = *out;
+    o.push_back(0xFF); o.push_back(0xDA);
+    put_be16(&o, (uint32_t)(6 + 2 * S.ns));
+    o.push_back((uint8_t)S.ns);
+    for (int j = 0; j < S.ns; j++) {
+        o.push_back((uint8_t)F.cid[S.comp[j]]);
+        const int slot = (S.Ss == 0 && j > 0) ? 1 : 0;
+        o.push_back((uint8_t)(S.Ss == 0 ? (slot << 4) : slot));
+    }
+    o.push_back((uint8_t)S.Ss); o.push_back((uint8_t)S.Se); o.push_back((uint8_t)((S.Ah << 4) | S.Al));
+}
+
+// The progressive file of a frame from what the device made of its coefficients (pcr_coder.h): specs, the tables of its scans (kCodeSlots);
+// bits, how many every scan has (kScriptScansMax); words, the scan's first words, number word_off[scan] of them on.  Writes at most
+// `room` bytes of it to dst and returns how many it has.  (Straight to where they go: by way of a vector, with the pages that takes,
+// 64 photographs took longer with sixteen threads than with one.)
+inline size_t assemble_progressive(const uint8_t* src, const ImgDesc& img, const Frame& F, const CodeSpec* specs, const uint64_t* bits,
+                                   const uint32_t* words, const uint64_t* word_off, uint8_t* dst, size_t room) {
+    size_t size = 0;
+    auto put = [&](const uint8_t* p, size_t n) {
+        if (size < room) memcpy(dst + size, p, std::min(n, room - size));
+        size += n;
+    };
+    std::vector<uint8_t> head;
+    auto put_head = [&]() { put(head.data(), head.size()); head.clear(); };
+    write_file_head(src, img, F, 0, &head);
+    int at = 0;
+    for (const ScanSpec& S : default_script(img.nc)) {
+        for (int s = 0; s < 2; s++) {
+            const CodeSpec& C = specs[2 * at + s];
+            if (C.nsym == 0) continue;
+            HuffSpec H;
+            H.nsym = (int)C.nsym;
+            memcpy(H.counts + 1, C.counts, 16);
+            memcpy(H.symbols, C.symbols, C.nsym);
+            write_dht(&head, S.Ss == 0 ? 0 : 1, s, H);
+        }
+        write_scan_head(F, S, &head);
+        put_head();
+        const uint8_t* d = reinterpret_cast<const uint8_t*>(words + word_off[at]);
+        for (size_t left = (size_t)((bits[at] + 7) / 8); left > 0;) {         // a zero behind every byte 0xFF
+            const void* ff = memchr(d, 0xFF, left);
+            const size_t n = ff ? (size_t)((const uint8_t*)ff - d) + 1 : left;
+            put(d, n);
+            if (ff) put((const uint8_t*)"", 1);
+            d += n; left -= n;
+        }
+        at++;
+    }
+    head.push_back(0xFF); head.push_back(0xD9);
+    put_head();
+    return size;
+}
+
+// src: a JPEG file (baseline or progressive) whose frame header and quantisation tables are kept; coef: its
+// quantised coefficients, component planes one after the other, each [bh][bw][64] in natural order over the
+// MCU-padded block grid.  Appends the progressive file to *out.
+// restart_interval: MCUs of each scan between restart markers (0: none; a scan of one component counts its blocks).
+// counts (optional): the symbol counts of the scans, [scan][table slot][symbol] (kHistPerImage entries, as k_symbol_hist
+// writes them), used for the Huffman tables instead of counting the tokens here.  counts_out (optional): receives the
+// counts of the tokens; with it and out == nullptr nothing is written.
+inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int16_t* coef, size_t coef_count, uint32_t restart_interval,
+                                 std::vector<uint8_t>* out, const uint32_t* counts = nullptr, uint32_t* counts_out = nullptr) {
+    std::vector<uint8_t> scratch;
+    if (!out) out = &scratch;
+    if (counts_out) memset(counts_out, 0, sizeof(uint32_t) * kHistPerImage);
+    if (src_bytes >= (1ull << 32)) return kEUnsupported;
+    if (restart_interval > 65535) return kERange;
+    ImgDesc img; Frame F;
+    const int rc = read_frame(src, src_bytes, coef, coef_count, &img, &F);
+    if (rc != kOk) return rc;
+    for (int c = 0; c < img.nc; c++) F.masks[c].fill(F.plane[c], (size_t)img.bw[c] * img.bh[c]);
+    std::vector<uint8_t>& o = *out;
+    write_file_head(src, img, F, restart_interval, out);
     int scan_index = -1;
     for (const ScanSpec& S : default_script(img.nc)) {
         scan_index++;
@@ -770,15 +843,7 @@ inline int transcode_progressive(const uint8_t* src, size_t src_bytes, const int
             if (used[s]) { build_table(freq[s], &H[s]); write_dht(&o, cls, s, H[s]); }
             else memset(H[s].size, 0, sizeof H[s].size);
         }
-        o.push_back(0xFF); o.push_back(0xDA);
-        put_be16(&o, (uint32_t)(6 + 2 * S.ns));
-        o.push_back((uint8_t)S.ns);
-        for (int j = 0; j < S.ns; j++) {
-            o.push_back((uint8_t)F.cid[S.comp[j]]);
-            const int slot = (S.Ss == 0 && j > 0) ? 1 : 0;
-            o.push_back((uint8_t)(cls == 0 ? (slot << 4) : slot));
-        }
-        o.push_back((uint8_t)S.Ss); o.push_back((uint8_t)S.Se); o.push_back((uint8_t)((S.Ah << 4) | S.Al));
+        write_scan_head(F, S, &o);
         BitWriter bw(&o);
         FileSink file(&bw, H);
         if (counts) {

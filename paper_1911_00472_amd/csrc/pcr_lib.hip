@@ -22,6 +22,7 @@
 #include "pcr_kernels.h"
 #include "pcr_sequential.h"
 #include "pcr_hist.h"
+#include "pcr_coder.h"
 #include "pcr_similarity.h"
 #include "pcr_encode.h"
 
@@ -723,6 +724,167 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     }
     if (plan->n_apply) mark(r, PCR_STAGE_REFINE_APPLY, s);
     if (hipGetLastError() != hipSuccess) { r->cur = nullptr; return PCR_E_DEVICE; }
+    return PCR_OK;
+}
+
+// Images in groups of about this many bytes of what comes back from the device: what is pinned is bounded, except by a single image.
+constexpr size_t kTranscodePinned = 64u << 20;
+
+// Cuts images 0 .. n - 1 into such groups: offset[i] is where image i begins, offset[n] the end.  Returns the first images of the groups
+// and n; *most: the longest group.
+std::vector<uint32_t> transcode_groups(const std::vector<uint64_t>& offset, size_t unit, size_t* most) {
+    const uint32_t n = (uint32_t)offset.size() - 1;
+    std::vector<uint32_t> group(1, 0);
+    *most = 0;
+    for (uint32_t i = 0; i < n; i++) {
+        if (i > group.back() && (offset[i + 1] - offset[group.back()]) * unit > kTranscodePinned) group.push_back(i);
+        *most = std::max<size_t>(*most, (offset[i + 1] - offset[group.back()]) * unit);
+    }
+    group.push_back(n);
+    return group;
+}
+
+// Files first .. last - 1 by up to `threads` threads: write(i, where, room, &size) writes file i, as much of it as there is room for,
+// or says why not.
+template <class Write> int transcode_write(uint32_t first, uint32_t last, uint32_t threads, void* out, const uint64_t* out_off, uint64_t* written, int* status, const Write& write) {
+    std::atomic<uint32_t> next(first);
+    auto work = [&]() {
+        for (;;) {
+            const uint32_t i = next.fetch_add(1);
+            if (i >= last) break;
+            size_t size = 0;
+            const size_t room = (size_t)(out_off[i + 1] - out_off[i]);
+            status[i] = write(i, (uint8_t*)out + out_off[i], room, &size);
+            written[i] = size;
+            if (!status[i] && size > room) status[i] = PCR_E_RANGE;
+        }
+    };
+    return enc::on_threads(std::min(threads, last - first), work) ? PCR_OK : PCR_E_NOMEM;
+}
+
+// Device and pinned memory of a call, given back when what it has enqueued is done.
+struct CallMemory {
+    hipStream_t stream;
+    std::vector<void*> dev, host;
+    explicit CallMemory(hipStream_t s) : stream(s) {}
+    CallMemory(const CallMemory&) = delete;
+    CallMemory& operator=(const CallMemory&) = delete;
+    ~CallMemory() { (void)hipStreamSynchronize(stream); for (void* p : dev) (void)hipFree(p); for (void* p : host) (void)hipHostFree(p); }
+    template <class T> T* device(size_t count) {
+        void* p = nullptr;
+        dev.reserve(dev.size() + 1);
+        if (hipMalloc(&p, count * sizeof(T) + 1) != hipSuccess) return nullptr;
+        dev.push_back(p);
+        return (T*)p;
+    }
+    template <class T> T* pinned(size_t count) {
+        void* p = nullptr;
+        host.reserve(host.size() + 1);
+        if (hipHostMalloc(&p, count * sizeof(T) + 1, hipHostMallocDefault) != hipSuccess) return nullptr;
+        host.push_back(p);
+        return (T*)p;
+    }
+};
+
+// The files by the device's coder (pcr_coder.h), without restart markers.  frames[i]: what read_frame said of file i, kOk for all
+// that are to be written.
+struct SourceFrame { int rc; ImgDesc img; enc::Frame frame; };
+bool same_frame(const ImgDesc& a, const ImgDesc& b) {
+    bool same = a.nc == b.nc && (a.nc == 1 || a.nc == 3) && a.mcux == b.mcux && a.mcuy == b.mcuy;
+    for (int c = 0; same && c < a.nc; c++)
+        same = a.hs[c] == b.hs[c] && a.vs[c] == b.vs[c] && a.bw[c] == b.bw[c] && a.bh[c] == b.bh[c] && a.cw[c] == b.cw[c] && a.ch[c] == b.ch[c];
+    return same;
+}
+int transcode_on_device(pcr_record* r, const void* const* files, const std::vector<SourceFrame>& frames, uint32_t threads, void* out, const uint64_t* out_off, uint64_t* written,
+                               int* status, hipStream_t s) {
+    const uint32_t n = r->hdr.n;
+    const size_t scans = (size_t)n * kScriptScansMax;
+    CallMemory M(s);
+    uint32_t* d_hist = M.device<uint32_t>((size_t)n * kHistPerImage);
+    ScanMarks* d_marks = M.device<ScanMarks>(scan_marks_of_image(r->coef_off[n], n));
+    uint32_t* d_raw = M.device<uint32_t>(scans);
+    uint32_t* d_codes = M.device<uint32_t>(scans * 2 * 256);
+    uint64_t* d_off = M.device<uint64_t>(scans + 1);
+    const size_t spec_bytes = arena_round(scans * 2 * sizeof(CodeSpec));     // (tables and bit counts come back together)
+    uint8_t *d_made = M.device<uint8_t>(spec_bytes + scans * sizeof(uint64_t)), *made = M.pinned<uint8_t>(spec_bytes + scans * sizeof(uint64_t));
+    if (!d_hist || !d_marks || !d_raw || !d_codes || !d_off || !d_made || !made) return PCR_E_NOMEM;
+    CodeSpec* d_specs = reinterpret_cast<CodeSpec*>(d_made);
+    uint64_t* d_bits = reinterpret_cast<uint64_t*>(d_made + spec_bytes);
+    const ImgDesc* d_img = r->d.img;
+    const int16_t* d_coef = r->d.coef;
+    hipLaunchKernelGGL(k_symbol_hist, dim3(n, kScriptScansMax), dim3(kHistLanes), 0, s, d_img, d_coef, r->d.coef_off, 0u, d_hist, d_marks, d_raw);
+    hipLaunchKernelGGL(k_code_tables, dim3(n, kScriptScansMax), dim3(128), 0, s, d_img, (const uint32_t*)d_hist, (const uint32_t*)d_raw, d_specs, d_codes, d_bits);
+    if (hipGetLastError() != hipSuccess || hipMemcpyAsync(made, d_made, spec_bytes + scans * sizeof(uint64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess) return PCR_E_DEVICE;
+    const CodeSpec* specs = reinterpret_cast<const CodeSpec*>(made);
+    const uint64_t* bits = reinterpret_cast<const uint64_t*>(made + spec_bytes);
+    std::vector<uint64_t> at(n + 1, 0);                        // words of the images
+    for (uint32_t i = 0; i < n; i++) {
+        at[i + 1] = at[i];
+        for (int g = 0; g < kScriptScansMax; g++) at[i + 1] += (bits[(size_t)i * kScriptScansMax + g] + 31) / 32;
+    }
+    size_t most;
+    const std::vector<uint32_t> group = transcode_groups(at, sizeof(uint32_t), &most);
+    most /= sizeof(uint32_t);
+    uint32_t *d_words = M.device<uint32_t>(most), *words = M.pinned<uint32_t>(most);
+    uint64_t* off = M.pinned<uint64_t>(scans + 1);
+    if (!d_words || !words || !off) return PCR_E_NOMEM;
+    for (size_t e = 0; e + 1 < group.size(); e++) {
+        const uint32_t first = group[e], last = group[e + 1];
+        const size_t mine = (size_t)(last - first) * kScriptScansMax;
+        off[0] = 0;
+        for (size_t q = 0; q < mine; q++) off[q + 1] = off[q] + (bits[(size_t)first * kScriptScansMax + q] + 31) / 32;
+        if (hipMemcpyAsync(d_off, off, (mine + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, s) != hipSuccess) return PCR_E_DEVICE;
+        hipLaunchKernelGGL(k_code_scans, dim3(last - first, kScriptScansMax), dim3(kCodeLanes), 0, s, d_img, d_coef, r->d.coef_off, (const ScanMarks*)d_marks, (const uint32_t*)d_codes,
+                           (const uint64_t*)d_off, first, d_words);
+        if (hipGetLastError() != hipSuccess || (off[mine] && hipMemcpyAsync(words, d_words, off[mine] * sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess) ||
+            hipStreamSynchronize(s) != hipSuccess) return PCR_E_DEVICE;
+        // (a thread for every two megabytes: more of them take longer to start than to do it)
+        const uint32_t useful = (uint32_t)std::min<uint64_t>(threads, 1 + off[mine] * sizeof(uint32_t) / (2u << 20));
+        const int rc = transcode_write(first, last, useful, out, out_off, written, status, [&](uint32_t i, uint8_t* dst, size_t room, size_t* size) {
+            const SourceFrame& F = frames[i];
+            if (F.rc) return F.rc;
+            const size_t scan = (size_t)i * kScriptScansMax;
+            *size = enc::assemble_progressive((const uint8_t*)files[i], F.img, F.frame, specs + 2 * scan, bits + scan, words, off + (size_t)(i - first) * kScriptScansMax, dst, room);
+            return (int)kOk;
+        });
+        if (rc) return rc;
+    }
+    return PCR_OK;
+}
+
+// The files by the host's coder: coefficients (and, device_counts, symbol counts) to pinned memory (30 MB of coefficients took 10 ms
+// through pageable memory), the files coded by several threads straight from there.
+int transcode_on_host(pcr_record* r, const void* const* files, const size_t* sizes, uint32_t restart_interval, bool device_counts, uint32_t threads, void* out, const uint64_t* out_off,
+                             uint64_t* written, int* status, hipStream_t s) {
+    const uint32_t n = r->hdr.n;
+    size_t most;
+    const std::vector<uint32_t> group = transcode_groups(r->coef_off, sizeof(int16_t), &most);
+    const size_t counts_of = device_counts ? (size_t)n * kHistPerImage : 0;
+    CallMemory M(s);
+    int16_t *host = M.pinned<int16_t>(most / sizeof(int16_t)), *d_coef = M.device<int16_t>((size_t)r->coef_off[n]);
+    uint32_t *hist = M.pinned<uint32_t>(counts_of), *d_hist = M.device<uint32_t>(counts_of);
+    if (!host || !d_coef || !hist || !d_hist) return PCR_E_NOMEM;
+    hipLaunchKernelGGL(k_export_natural, dim3(2048), dim3(256), 0, s, r->d.coef, d_coef, (size_t)r->coef_off[n]);
+    if (device_counts)
+        hipLaunchKernelGGL(k_symbol_hist, dim3(n, kScriptScansMax), dim3(kHistLanes), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off, restart_interval, d_hist,
+                           (ScanMarks*)nullptr, (uint32_t*)nullptr);
+    if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
+    if (device_counts && hipMemcpyAsync(hist, d_hist, counts_of * sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess) return PCR_E_DEVICE;
+    for (size_t e = 0; e + 1 < group.size(); e++) {
+        const uint32_t first = group[e], last = group[e + 1];
+        const uint64_t at = r->coef_off[first];
+        if (hipMemcpyAsync(host, d_coef + at, (size_t)(r->coef_off[last] - at) * sizeof(int16_t), hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return PCR_E_DEVICE;
+        const int rc = transcode_write(first, last, threads, out, out_off, written, status, [&](uint32_t i, uint8_t* dst, size_t room, size_t* size) {
+            std::vector<uint8_t> bytes;
+            const int made = enc::transcode_progressive((const uint8_t*)files[i], sizes[i], host + (r->coef_off[i] - at), (size_t)(r->coef_off[i + 1] - r->coef_off[i]), restart_interval, &bytes,
+                                                        device_counts ? hist + (size_t)i * kHistPerImage : nullptr);
+            *size = bytes.size();
+            if (!made && bytes.size() <= room) memcpy(dst, bytes.data(), bytes.size());
+            return made;
+        });
+        if (rc) return rc;
+    }
     return PCR_OK;
 }
 
@@ -1580,9 +1742,8 @@ int pcr_transcode_symbol_counts(const void* src_jpeg, size_t src_bytes, const in
     return enc::transcode_progressive((const uint8_t*)src_jpeg, src_bytes, coef, coef_count, restart_interval, nullptr, nullptr, counts);
 }
 
-// The batch of pcr_transcode_progressive(_counted) for the files a record was made of: one decode for coefficients and
-// counts, one copy of both to pinned memory (30 MB of coefficients took 10 ms through pageable memory), the files coded by
-// several threads straight from there.
+// The batch of pcr_transcode_progressive(_counted) for the files a record was made of: one decode for coefficients, then the
+// files, coded on the device where it counts the symbols too and no restart markers are asked for.
 int pcr_transcode_batch(pcr_record* r, const void* const* files, const size_t* sizes, uint32_t n, uint32_t restart_interval, int device_counts, int threads,
                         void* out, const uint64_t* out_off, uint64_t* written, void* stream) {
     if (!r || !files || !sizes || !out || !out_off || !written || n != r->hdr.n || threads < 1) return PCR_E_ARG;
@@ -1597,58 +1758,22 @@ int pcr_transcode_batch(pcr_record* r, const void* const* files, const size_t* s
     rc = run_entropy_stages(r, 0, k, s, true, &plan);
     if (rc) return rc;
     call_end(r);
-    // Images in groups of about kTranscodePinned bytes of coefficients: what is pinned is bounded, except by a single image.
-    constexpr size_t kTranscodePinned = 64u << 20;
-    size_t most = 0;
-    std::vector<uint32_t> group(1, 0);
-    for (uint32_t i = 0; i < n; i++) {
-        if (i > group.back() && (r->coef_off[i + 1] - r->coef_off[group.back()]) * sizeof(int16_t) > kTranscodePinned) group.push_back(i);
-        most = std::max<size_t>(most, (r->coef_off[i + 1] - r->coef_off[group.back()]) * sizeof(int16_t));
+    try {
+    // (files whose frames are not those of the record's images are coded by their own: on the host, which has no others)
+    bool on_device = device_counts && restart_interval == 0;
+    std::vector<SourceFrame> frames(on_device ? n : 0);
+    for (uint32_t i = 0; on_device && i < n; i++) {
+        SourceFrame& F = frames[i];
+        F.rc = enc::read_frame((const uint8_t*)files[i], sizes[i], nullptr, (size_t)(r->coef_off[i + 1] - r->coef_off[i]), &F.img, &F.frame);
+        if (F.rc == kOk) on_device = same_frame(F.img, r->img[i]);
     }
-    group.push_back(n);
-    const size_t hist_bytes = device_counts ? (size_t)n * kHistPerImage * sizeof(uint32_t) : 0, hist_at = arena_round(most);
-    uint8_t *host = nullptr, *dev = nullptr;
-    if (hipHostMalloc((void**)&host, hist_at + hist_bytes + 1, hipHostMallocDefault) != hipSuccess ||
-        hipMalloc((void**)&dev, arena_round((size_t)r->coef_off[n] * sizeof(int16_t)) + hist_bytes + 1) != hipSuccess) rc = PCR_E_NOMEM;
-    int16_t* d_coef = reinterpret_cast<int16_t*>(dev);
-    uint32_t* d_hist = reinterpret_cast<uint32_t*>(dev + arena_round((size_t)r->coef_off[n] * sizeof(int16_t)));
-    if (!rc) {
-        hipLaunchKernelGGL(k_export_natural, dim3(2048), dim3(256), 0, s, r->d.coef, d_coef, (size_t)r->coef_off[n]);
-        if (device_counts)
-            hipLaunchKernelGGL(k_symbol_hist, dim3(n, kScriptScansMax), dim3(kHistLanes), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off, restart_interval, d_hist);
-        if (hipGetLastError() != hipSuccess) rc = PCR_E_DEVICE;
-    }
-    if (!rc && device_counts && hipMemcpyAsync(host + hist_at, d_hist, hist_bytes, hipMemcpyDeviceToHost, s) != hipSuccess) rc = PCR_E_DEVICE;
     std::vector<int> status(n, PCR_OK);
-    for (size_t e = 0; !rc && e + 1 < group.size(); e++) {
-        const uint32_t first = group[e], last = group[e + 1];
-        const uint64_t at = r->coef_off[first];
-        if (hipMemcpyAsync(host, d_coef + at, (size_t)(r->coef_off[last] - at) * sizeof(int16_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess) { rc = PCR_E_DEVICE; break; }
-        std::atomic<uint32_t> next(first);
-        auto work = [&]() {
-            std::vector<uint8_t> bytes;
-            for (;;) {
-                const uint32_t i = next.fetch_add(1);
-                if (i >= last) break;
-                bytes.clear();
-                const int16_t* coef = reinterpret_cast<const int16_t*>(host) + (r->coef_off[i] - at);
-                const uint32_t* counts = device_counts ? reinterpret_cast<const uint32_t*>(host + hist_at) + (size_t)i * kHistPerImage : nullptr;
-                status[i] = enc::transcode_progressive((const uint8_t*)files[i], sizes[i], coef, (size_t)(r->coef_off[i + 1] - r->coef_off[i]), restart_interval, &bytes, counts);
-                written[i] = bytes.size();
-                if (status[i]) continue;
-                if (bytes.size() > out_off[i + 1] - out_off[i]) status[i] = PCR_E_RANGE;
-                else memcpy((uint8_t*)out + out_off[i], bytes.data(), bytes.size());
-            }
-        };
-        if (!enc::on_threads(std::min((uint32_t)threads, last - first), work)) rc = PCR_E_NOMEM;
-    }
-    if (rc) (void)hipStreamSynchronize(s);                    // (the buffers go)
-    if (dev) (void)hipFree(dev);
-    if (host) (void)hipHostFree(host);
+    rc = on_device ? transcode_on_device(r, files, frames, (uint32_t)threads, out, out_off, written, status.data(), s)
+                   : transcode_on_host(r, files, sizes, restart_interval, device_counts != 0, (uint32_t)threads, out, out_off, written, status.data(), s);
     if (rc) { (void)hipGetLastError(); return rc; }
     for (uint32_t i = 0; i < n; i++) if (status[i] && status[i] != PCR_E_RANGE) return status[i];
     for (uint32_t i = 0; i < n; i++) if (status[i]) return status[i];
+    } catch (const std::bad_alloc&) { return PCR_E_NOMEM; }
     return PCR_OK;
 }
 
@@ -1667,7 +1792,7 @@ int pcr_symbol_histograms(pcr_record* r, uint32_t restart_interval, uint32_t* d_
     call_end(r);
     static_assert(PCR_HIST_ENTRIES == kHistPerImage, "header and kernel agree on the layout of the counts");
     hipLaunchKernelGGL(k_symbol_hist, dim3(r->hdr.n, kScriptScansMax), dim3(kHistLanes), 0, s, (const ImgDesc*)r->d.img, (const int16_t*)r->d.coef, r->d.coef_off,
-                       restart_interval, d_hist);
+                       restart_interval, d_hist, (ScanMarks*)nullptr, (uint32_t*)nullptr);
     if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
     return PCR_OK;
 }

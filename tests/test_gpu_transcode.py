@@ -78,3 +78,38 @@ def test_symbol_histograms_on_the_device(rgb_small, gray64, extreme_record):
     files = _sequential_files()[:5] + list(rgb_small[1][:3])
     for ri in (0, 9):
         assert pkg.transcode_files(files, restart_interval=ri) == pkg.transcode_files(files, restart_interval=ri, device_counts=False)
+
+
+@pytest.mark.parametrize("name", ["tiny", "edges", "dense", "runs", "mixed"])
+def test_device_coder_writes_the_host_coders_files(name, extreme_record):
+    """pcr_coder.h against pcr_encode.h, byte for byte: pictures of one block, of 512 blocks and one more or fewer (a workgroup's
+    turn), noise at quality 100 (more bits per turn than its words in LDS hold), end-of-band runs over several turns and beyond
+    32767 blocks, and planes of every kind in one batch."""
+    import pcrgen
+    import torch
+    assert torch.cuda.is_available()
+    rng = np.random.default_rng(5)
+
+    def noise(w, h, nc, quality=100):
+        return pcrgen.encode_pixels(rng.integers(0, 256, (h, w, nc)).astype(np.uint8), 1, 1, quality, "sequential")
+
+    def spot(w, h, *at):                                    # flat but for a few blocks
+        pix = np.full((h, w, 1), 120, np.uint8)
+        for x, y in at:
+            pix[y:y + 8, x:x + 8, 0] = np.arange(64, dtype=np.uint8).reshape(8, 8) * 3
+        return pcrgen.encode_pixels(pix, 1, 1, 90, "sequential")
+
+    if name == "tiny":
+        files = [noise(1, 1, 1), noise(1, 1, 3), noise(8, 8, 3), noise(9, 7, 1), spot(8, 8)]
+    elif name == "edges":
+        files = [pcrgen.make_jpeg(40 + i, 1, w, h, nc, 9.0, s, s, 90) for i, (w, h, nc, s) in enumerate(
+            [(512, 64, 1, 1), (504, 64, 1, 1), (520, 64, 1, 1), (512, 64, 3, 1), (513, 65, 3, 2), (1024, 64, 3, 2), (4104, 8, 1, 1), (8, 4104, 3, 1)])]
+    elif name == "dense":
+        files = [noise(256, 256, 1), noise(200, 190, 3), noise(512, 72, 3, 97)]
+    elif name == "runs":
+        files = [spot(1464, 1456, (0, 0)), spot(1464, 1456), spot(1464, 1456, (800, 0), (1456, 1448)), spot(1472, 2960, (0, 0), (1464, 2952)), spot(512, 128, (504, 56), (0, 64))]
+    else:
+        files = _sequential_files()[:4] + list(extreme_record[1])[:4] + [noise(40, 30, 3), spot(640, 64, (632, 56))]
+    got, want = pkg.transcode_files(files), pkg.transcode_files(files, device_counts=False)
+    for i, (a, b) in enumerate(zip(got, want)):
+        assert a == b, (name, i, len(a), len(b))
