@@ -146,17 +146,124 @@ inline void write_record(const RecordPlan& P, const void* const* files, const in
 struct EntryPoint { uint32_t mcu, bit; int16_t pred[3]; uint16_t zero; };
 static_assert(sizeof(EntryPoint) == kEntryBytes, "entry layout");
 
-struct BitCursor {
-    const uint8_t* d; uint64_t nbits, pos; bool bad;
-    // the 32 bits at the cursor (the buffer is padded beyond its end)
-    uint32_t peek() const {
-        uint64_t v;
-        memcpy(&v, d + (pos >> 3), 8);
-        return (uint32_t)(__builtin_bswap64(v) << (pos & 7) >> 32);
+// Bytes the data of a scan are padded with: a walk looks where it stands once a block, and a block is at most 64 symbols of 32 bits
+// and as many correction bits.
+constexpr size_t kWalkPad = 512;
+
+// The 57 bits and more at a position, at the upper end.
+inline uint64_t bits_at(const uint8_t* d, uint64_t pos) {
+    uint64_t v;
+    memcpy(&v, d + (pos >> 3), 8);
+    return __builtin_bswap64(v) << (pos & 7);
+}
+
+// What a walk wants to know of the symbol at the head of a window: the bits it takes, how many positions it goes on by and whether
+// a coefficient lies there (in a refinement scan: the zeros it passes), or the run it begins.  Codes of up to kWalkBits bits by look-up, by their
+// first kWalkBits bits (0: another one, or none).
+constexpr int kWalkBits = 11;
+struct WalkTable {
+    enum : uint32_t { kCoef = 1u << 16, kRun = 1u << 17, kBad = 1u << 18 };       // | positions or log2 of the run << 8 | bits
+    uint32_t lut[1u << kWalkBits];
+    const AcTab* tab; bool refine;
+    uint32_t entry(uint32_t a) const {                         // a: ac_code's answer
+        if (!a) return kBad;
+        const uint32_t r = (a >> 4) & 15, sz = a & 15, len = a >> 8;
+        if (refine) return sz > 1 ? (uint32_t)kBad : (sz ? kCoef | r << 8 | (len + 1) : (r < 15 ? kRun | r << 8 | (len + r) : 15u << 8 | len));
+        return sz ? kCoef | (r + 1) << 8 | (len + sz) : (r < 15 ? kRun | r << 8 | (len + r) : 16u << 8 | len);
     }
-    void skip(uint32_t n) { pos += n; if (pos > nbits) bad = true; }
-    uint32_t take(uint32_t n) { const uint32_t v = n ? peek() >> (32 - n) : 0; skip(n); return v; }
+    void build(const AcTab* t, bool refinement) {
+        tab = t; refine = refinement;
+        for (uint32_t i = 0; i < 1u << kWalkBits; i++) {
+            // (the same code at both ends of the windows that begin so: it is that code in between)
+            const uint32_t a = ac_code(t, i << (32 - kWalkBits)), z = ac_code(t, i << (32 - kWalkBits) | ((1u << (32 - kWalkBits)) - 1));
+            lut[i] = a && a == z && (a >> 8) <= (uint32_t)kWalkBits ? entry(a) : 0;
+        }
+    }
+    uint32_t at(uint64_t window) const {
+        const uint32_t e = lut[window >> (64 - kWalkBits)];
+        return e ? e : entry(ac_code(tab, (uint32_t)(window >> 32)));
+    }
 };
+
+// Bits set, and the lowest set bit behind the first n set ones (0: there are fewer); BMI2: where the machine has those instructions.
+template <bool BMI2> inline uint32_t walk_popcount(uint64_t x) {
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+    if (BMI2) { uint64_t n; asm("popcnt %1, %0" : "=r"(n) : "r"(x) : "cc"); return (uint32_t)n; }
+#endif
+    return (uint32_t)__builtin_popcountll(x);
+}
+template <bool BMI2> inline uint64_t walk_nth(uint64_t x, uint32_t n) {
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+    if (BMI2) { uint64_t one; asm("pdep %1, %2, %0" : "=r"(one) : "r"(x), "r"(1ull << n)); return one; }
+#endif
+    for (; n && x; n--) x &= x - 1;
+    return x & (0 - x);
+}
+inline bool walk_bmi2() {
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+    static const bool has = __builtin_cpu_supports("bmi2") && __builtin_cpu_supports("popcnt");
+    return has;
+#else
+    return false;
+#endif
+}
+
+// One block of an AC scan outside a run: from bit *pos on, h its non-zero positions so far.  Returns the blocks of the run it ends in,
+// itself included (0: none), or -1: no stream that can be followed.
+inline int walk_first_block(const uint8_t* d, const WalkTable& T, uint64_t* pos, uint64_t* h, uint32_t Ss, uint32_t Se) {
+    uint64_t at = *pos, known = *h;
+    uint32_t k = Ss;
+    int run = 0;
+    while (k <= Se) {
+        uint64_t w = bits_at(d, at);
+        uint32_t used = 0;
+        do {                                                   // (57 bits at least: two symbols of 25 or one of 32)
+            const uint32_t e = T.at(w << used);
+            if (e & WalkTable::kBad) return -1;
+            used += e & 255u;
+            if (e & WalkTable::kRun) {
+                const uint32_t r = (e >> 8) & 15u;
+                run = (int)(1u << r);
+                if (r) run += (int)(bits_at(d, at + used - r) >> (64 - r));
+                k = 64;
+                break;
+            }
+            k += (e >> 8) & 255u;
+            if (e & WalkTable::kCoef) {
+                if (k > Se + 1) return -1;
+                known |= 1ull << (k - 1);
+            }
+        } while (k <= Se && used <= 25);
+        at += used;
+    }
+    *pos = at; *h = known;
+    return run;
+}
+template <bool BMI2> inline int walk_refine_block(const uint8_t* d, const WalkTable& T, uint64_t* pos, uint64_t* h, uint64_t band) {
+    uint64_t at = *pos, known = *h & band, fresh = 0;         // (a position this scan has made non-zero holds no correction bit, and is no zero behind it)
+    uint64_t from = band;                                      // the positions not passed yet
+    int run = 0;
+    while (from) {
+        const uint32_t e = T.at(bits_at(d, at));
+        if (e & WalkTable::kBad) return -1;
+        at += e & 255u;
+        const uint32_t r = (e >> 8) & 15u;
+        if (e & WalkTable::kRun) {
+            run = (int)(1u << r);
+            if (r) run += (int)(bits_at(d, at - r) >> (64 - r));
+            break;
+        }
+        const uint64_t one = walk_nth<BMI2>(~known & from, r);        // over r zeros; a correction bit at every non-zero on the way
+        if (!one && (e & WalkTable::kCoef)) return -1;
+        const uint64_t passed = one ? one - 1 : ~0ull;
+        at += walk_popcount<BMI2>(known & from & passed);
+        from &= one ? ~(one | passed) : 0;
+        if (e & WalkTable::kCoef) fresh |= one;
+    }
+    if (run) at += walk_popcount<BMI2>(known & from);          // the rest of the block: corrections only
+    *pos = at; *h |= fresh;
+    return run;
+}
 
 // Entropy-coded data of a scan without stuffed zeros, fill bytes and restart markers; starts[j] = first byte of
 // restart interval j.  Stops at the first other marker.
@@ -191,6 +298,8 @@ inline int find_entry_points(const uint8_t* file, const uint64_t* ends, uint32_t
     for (int c = 0; c < img.nc; c++) nz[c].assign((size_t)img.bw[c] * img.bh[c], 0);
     std::vector<uint8_t> clean; std::vector<uint32_t> starts;
     std::vector<DcTab> dt(kMaxComp); std::vector<AcTab> at(kMaxComp);
+    WalkTable walk;
+    const bool bmi2 = walk_bmi2();
     for (uint32_t g = 0; g < nscans; g++) {
         const ScanDesc& sd = sc[g];
         const bool seq = !img.progressive;
@@ -199,18 +308,18 @@ inline int find_entry_points(const uint8_t* file, const uint64_t* ends, uint32_t
         const uint32_t nint = sd.ri ? (sd.mcus + sd.ri - 1) / sd.ri : 1;
         if (starts.size() != nint) return kOk;                        // damaged: the decoder will say so
         starts.push_back((uint32_t)clean.size());
-        const uint64_t total_bits = (uint64_t)clean.size() * 8;
-        clean.resize(clean.size() + 16, 0xFF);
+        clean.resize(clean.size() + kWalkPad, 0xFF);
+        const uint8_t* d = clean.data();
         if (seq || sd.Ss == 0) for (int j = 0; j < sd.ns; j++) dctab_build(&dt[j], file + sd.dc_off[j]);
         if (seq) for (int j = 0; j < sd.ns; j++) actab_build(&at[j], file + sd.ac_offc[j]);
-        else if (sd.Ss > 0) actab_build(&at[0], file + sd.ac_off);
+        else if (sd.Ss > 0) { actab_build(&at[0], file + sd.ac_off); walk.build(&at[0], sd.Ah > 0); }
         const int c0 = sd.comp[0];
         const uint64_t band = (sd.Se >= 63 ? ~0ull : ((1ull << (sd.Se + 1)) - 1)) & ~((1ull << sd.Ss) - 1);
         std::vector<EntryPoint>& E = ent[g];
-        BitCursor b{clean.data(), total_bits, 0, false};
-        for (uint32_t iv = 0; iv < nint && !b.bad; iv++) {
-            b.pos = (uint64_t)starts[iv] * 8;
-            b.nbits = (uint64_t)starts[iv + 1] * 8;
+        bool bad = false;
+        for (uint32_t iv = 0; iv < nint && !bad; iv++) {
+            uint64_t pos = (uint64_t)starts[iv] * 8;
+            const uint64_t nbits = (uint64_t)starts[iv + 1] * 8;
             int pred[kMaxComp] = {0, 0, 0};
             uint32_t eobrun = 0;
             const uint32_t m0 = sd.ri ? iv * sd.ri : 0, m1 = sd.ri ? std::min(m0 + sd.ri, sd.mcus) : sd.mcus;
@@ -221,80 +330,57 @@ inline int find_entry_points(const uint8_t* file, const uint64_t* ends, uint32_t
             const bool halved = !seq && interval >= 2 && ((sd.Ss > 0 && sd.Ah > 0) || sd.Ss == 0);
             const uint32_t step = halved ? interval / 2 : interval;
             uint32_t next_entry = step;
-            for (uint32_t m = m0; m < m1 && !b.bad; m++) {
-                if (sd.ri == 0 && m >= next_entry && eobrun == 0 && E.size() < kMaxEntriesPerScan) {
-                    EntryPoint e; e.mcu = m; e.bit = (uint32_t)b.pos; e.zero = (!seq && sd.Ss > 0) ? 1 : 0;   // (in memory: 1 = written in the short form)
-                    for (int j = 0; j < kMaxComp; j++) e.pred[j] = (int16_t)pred[j];
-                    E.push_back(e);
-                    next_entry = (m / step + 1) * step;
-                }
-                if (seq || sd.Ss == 0) {                             // blocks of every scan component of the MCU
-                    for (int j = 0; j < sd.ns && !b.bad; j++) {
+            auto entry = [&](uint32_t m) {
+                EntryPoint e; e.mcu = m; e.bit = (uint32_t)pos; e.zero = (!seq && sd.Ss > 0) ? 1 : 0;   // (in memory: 1 = written in the short form)
+                for (int j = 0; j < kMaxComp; j++) e.pred[j] = (int16_t)pred[j];
+                E.push_back(e);
+                next_entry = (m / step + 1) * step;
+            };
+            if (seq || sd.Ss == 0) {                                 // blocks of every scan component of the MCU
+                for (uint32_t m = m0; m < m1 && !bad; m++) {
+                    if (sd.ri == 0 && m >= next_entry && E.size() < kMaxEntriesPerScan) entry(m);
+                    for (int j = 0; j < sd.ns && !bad; j++) {
                         const int c = sd.comp[j];
                         const uint32_t nb = sd.ns > 1 ? (uint32_t)img.hs[c] * img.vs[c] : 1u;
-                        for (uint32_t q = 0; q < nb && !b.bad; q++) {
-                            const uint32_t e = dc_code(&dt[j], b.peek());
-                            if (!e) { b.bad = true; break; }
-                            b.skip(e >> 4);
-                            pred[j] += extend(b.take(e & 15), (int)(e & 15));
-                            if (!seq) continue;
-                            for (int k = 1; k < 64 && !b.bad;) {
-                                const uint32_t a = ac_code(&at[j], b.peek());
-                                if (!a) { b.bad = true; break; }
-                                const uint32_t r = (a >> 4) & 15, sz = a & 15;
-                                b.skip(a >> 8);
-                                if (sz) { k += (int)r + 1; b.skip(sz); }
+                        for (uint32_t q = 0; q < nb && !bad; q++) {
+                            uint64_t w = bits_at(d, pos);
+                            const uint32_t e = dc_code(&dt[j], (uint32_t)(w >> 32));
+                            if (!e) { bad = true; break; }
+                            const uint32_t len = e >> 4, sz = e & 15;
+                            pred[j] += extend(sz ? (uint32_t)(w << len >> (64 - sz)) : 0u, (int)sz);
+                            pos += len + sz;
+                            for (int k = 1; seq && k < 64;) {
+                                const uint32_t a = ac_code(&at[j], (uint32_t)(bits_at(d, pos) >> 32));
+                                if (!a) { bad = true; break; }
+                                const uint32_t r = (a >> 4) & 15, s = a & 15;
+                                pos += a >> 8;
+                                if (s) { k += (int)r + 1; pos += s; }
                                 else if (r == 15) k += 16;
                                 else break;
                             }
+                            bad = bad || pos > nbits;
                         }
                     }
-                    continue;
                 }
-                uint64_t& h = nz[c0][(size_t)(m / sd.mcu_w) * img.bw[c0] + m % sd.mcu_w];
-                if (sd.Ah == 0) {                                    // AC first
-                    if (eobrun) { eobrun--; continue; }
-                    for (int k = sd.Ss; k <= sd.Se && !b.bad;) {
-                        const uint32_t a = ac_code(&at[0], b.peek());
-                        if (!a) { b.bad = true; break; }
-                        const uint32_t r = (a >> 4) & 15, sz = a & 15;
-                        b.skip(a >> 8);
-                        if (sz) {
-                            k += (int)r;
-                            if (k > sd.Se) { b.bad = true; break; }
-                            b.skip(sz); h |= 1ull << k; k++;
-                        } else if (r == 15) k += 16;
-                        else { eobrun = (1u << r) - 1 + b.take(r); break; }
-                    }
-                } else {                                             // AC refinement
-                    int k = sd.Ss;
-                    if (eobrun == 0) {
-                        while (k <= sd.Se && !b.bad) {
-                            const uint32_t a = ac_code(&at[0], b.peek());
-                            if (!a) { b.bad = true; break; }
-                            uint32_t r = (a >> 4) & 15; const uint32_t sz = a & 15;
-                            b.skip(a >> 8);
-                            if (sz > 1) { b.bad = true; break; }
-                            if (sz == 0 && r < 15) { eobrun = (1u << r) + b.take(r); break; }   // (counts this block)
-                            if (sz) b.skip(1);                       // the sign
-                            const uint64_t from = band & ~((1ull << k) - 1);
-                            uint64_t zeros = ~h & from;              // over r zeros; a correction bit at every non-zero on the way
-                            for (; r && zeros; r--) zeros &= zeros - 1;
-                            k = zeros ? __builtin_ctzll(zeros) : (int)sd.Se + 1;
-                            b.skip((uint32_t)__builtin_popcountll(h & from & (k < 64 ? (1ull << k) - 1 : ~0ull)));
-                            if (sz) { if (k > sd.Se) { b.bad = true; break; } h |= 1ull << k; }
-                            k++;
-                        }
-                    }
-                    if (eobrun) {                                    // the rest of the block: corrections only
-                        const uint64_t rest = k <= 63 ? (h & band & ~((1ull << k) - 1)) : 0;
-                        b.skip((uint32_t)__builtin_popcountll(rest));
-                        eobrun--;
-                    }
-                }
+                continue;
+            }
+            uint64_t* h = nz[c0].data();
+            uint32_t col = m0 % sd.mcu_w;
+            h += (size_t)(m0 / sd.mcu_w) * img.bw[c0];
+            for (uint32_t m = m0; m < m1 && !bad; m++) {
+                if (sd.ri == 0 && m >= next_entry && eobrun == 0 && E.size() < kMaxEntriesPerScan) entry(m);
+                int run;
+                if (eobrun) {
+                    if (sd.Ah > 0) pos += bmi2 ? walk_popcount<true>(h[col] & band) : walk_popcount<false>(h[col] & band);
+                    run = (int)eobrun;
+                } else if (sd.Ah == 0) run = walk_first_block(d, walk, &pos, &h[col], sd.Ss, sd.Se);
+                else run = bmi2 ? walk_refine_block<true>(d, walk, &pos, &h[col], band) : walk_refine_block<false>(d, walk, &pos, &h[col], band);
+                bad = run < 0 || pos > nbits;
+                eobrun = run > 0 ? (uint32_t)run - 1u : 0u;
+                if (++col == sd.mcu_w) { col = 0; h += img.bw[c0]; }
             }
         }
-        if (b.bad) { E.clear(); return kOk; }                         // no entries from here on: later scans build on this one
+        if (bad) { E.clear(); return kOk; }                         // no entries from here on: later scans build on this one
     }
     return kOk;
 }
