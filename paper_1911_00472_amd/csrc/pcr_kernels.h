@@ -79,7 +79,6 @@ struct DevRecord {
                                // coefficient export
     uint64_t* masks;
     int32_t* status;           // [n]
-    int32_t* status_out;       // [n], the caller's (null: not wanted): filled by the pixel kernel of the call (hand_out_status)
     AcTab* tabs;               // Huffman tables of the AC scans, written by k_headers
     const uint32_t* tab_idx;   // [n][G] index into tabs
     DcTab* dctabs;             // the DC tables of the DC first scans, three slots per scan (one per scan component)
@@ -150,15 +149,11 @@ constexpr uint32_t kMaxGroups = 64;                        // (parse_record_head
 constexpr uint32_t kHeaderStage = 16384;                   // bytes of LDS for the heads of the regions, shared out evenly
 constexpr uint32_t kHeaderWindow = 1024;                   // ... but at most this much per region (a first region with its tables is 600-700 bytes)
 constexpr uint32_t kHeaderWideImages = 512;                // kHeaderWaves wavefronts per workgroup whatever the scan group up to this many images
-// Beyond this many images the workgroups are more than find room at once with eight wavefronts each: four at most.  us a call, eight / four:
-// 2048 pictures of 24 x 34 at scan group 9 262 / 245, of 15 to 40 pixels at 7 215 / 195, two records of 2048 of 70 x 54 at 5 314 / 295,
-// four of 2048 of 30 x 30 at 9 715 / 646; but 800 of 64 x 64 at 10 249 / 255, 1000 of 48 x 48 at 10 246 / 253.
-constexpr uint32_t kHeaderNarrowImages = 1024;
-// own_index up to this many images (a workgroup sums n lengths per scan group), but beyond half of it only up to scan group
-// kHeaderWaves.  us a call with k_index / without: 1024 pictures of 256 x 256 at scan group 5 271 / 263, four records of
-// 1024 photographs at 1 708 / 695, at 10 6022 / 6042, of 64 x 64 at 10 721 / 717; 2048 pictures of 256 x 256 at 1 209 / 197, at 5 502 / 492,
-// at 10 1158 / 1151.
-constexpr uint32_t kOwnIndexImages = 2048;
+// own_index up to this many images (a workgroup sums n lengths per scan group), but beyond half of it only where every wavefront
+// has one scan group at most.  us a call with k_index / without: 1024 pictures of 256 x 256 at scan group 5 271 / 263, four records of
+// 1024 photographs at 1 708 / 695, at 10 6022 / 6042, of 64 x 64 at 10 721 / 717.  (The line is no loss's: 2048 pictures of 256 x 256
+// at 1 209 / 197, at 5 502 / 492, at 10 1158 / 1151, four such records at 10 3992 / 3979.)
+constexpr uint32_t kOwnIndexImages = 1024;
 
 // Record bytes by record offset: from the staged window, or (past it: long comments and profiles) from memory.
 // (The address spaces are spelled out: through two generic pointers every read became a flat one.)
@@ -260,22 +255,14 @@ PCR_D void dctab_build_wave(DcTab* t, const CanonCode* c, uint32_t lane) {
     if (lane < 8) t->valptr[lane] = (uint16_t)c->first[9 + lane];
 }
 
-// LDS of a workgroup: the heads of the regions of kmax scan groups, a code per wavefront, what the walks found.  (With room for the most
-// of everything, 30 KB, five workgroups fitted a compute unit whatever there was to do.  us a launch for 2048 pictures at scan groups 1 / 3 / 4, then and now: 37.6 / 43.4 / 45.0,
-// 25.0 / 34.8 / 35.5.)
-PCR_HD uint32_t header_stage(uint32_t kmax) { return kmax * kHeaderWindow < kHeaderStage ? kmax * kHeaderWindow : kHeaderStage; }
-PCR_HD uint32_t header_lds(uint32_t kmax, uint32_t waves) {
-    static_assert(sizeof(CanonCode) % 4 == 0 && sizeof(RegionWalk) % alignof(ScanDesc) == 0 && sizeof(ScanDesc) % 4 == 0 && alignof(RegionWalk) <= 8 && sizeof(CanonCode) % 8 == 0, "they follow each other");
-    return header_stage(kmax) + 16 + waves * (uint32_t)sizeof(CanonCode) + kmax * (uint32_t)(sizeof(RegionWalk) + sizeof(ScanDesc));
-}
 __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32_t kmax, uint32_t keep_status, uint32_t own_index, uint32_t k0, uint32_t dc_too) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t stage[];          // (header_lds: as much as the scans of the call take)
-    CanonCode* const s_code = reinterpret_cast<CanonCode*>(stage + header_stage(kmax) + 16);
-    RegionWalk* const s_walk = reinterpret_cast<RegionWalk*>(s_code + (blockDim.x >> 6));
-    ScanDesc* const s_scan = reinterpret_cast<ScanDesc*>(s_walk + kmax);
+    __shared__ __attribute__((aligned(16))) uint8_t stage[kHeaderStage + 16];
     __shared__ uint32_t s_off[kMaxGroups], s_len[kMaxGroups];
+    __shared__ ScanDesc s_scan[kMaxGroups];
+    __shared__ RegionWalk s_walk[kMaxGroups];
     __shared__ int s_rc[kMaxGroups];
     __shared__ ImgDesc s_img;
+    __shared__ CanonCode s_code[kHeaderWaves];
     __shared__ uint16_t s_job[kMaxGroups * kMaxComp];        // tables to build: scan group | component of the scan << 8
     __shared__ uint32_t s_njobs;
     short_kernel_priority();
@@ -289,7 +276,7 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
             const uint32_t* len = R.len + (size_t)g * n;
             const uint64_t start = ld_le64(R.rec + (g == 0 ? 16 : hdr_group_end_pos(g - 1)));
             const uint32_t mine = len[i];
-            constexpr uint32_t kHalf = 8;
+            constexpr uint32_t kHalf = kOwnIndexImages / 2 / 64;
             uint32_t before = 0;
             for (uint32_t first = 0; first < i; first += 64 * kHalf) {
                 uint32_t t[kHalf];
@@ -475,7 +462,7 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
 // (Before: a workgroup per scan, 2 KB per step with four barriers and no loads ahead, 128 us for the 81 MB of 1024
 // photographs, and 71 us for the fill after it.)
 // --------------------------------------------------------------------------------------
-constexpr uint32_t kUnstuffWaves = 4, kUnstuffManyWaves = 16, kUnstuffStep = 1024;
+constexpr uint32_t kUnstuffWaves = 4, kUnstuffStep = 1024;
 constexpr int kMaxFills = 3;
 struct FillList { uint4* p[kMaxFills]; size_t n16[kMaxFills]; uint32_t rows; };        // 16-byte pieces; rows of workgroups that share the work
 
@@ -497,14 +484,9 @@ struct __attribute__((packed, aligned(1))) LooseU16 { uint16_t v; };
 // of 600 x 450 in 4:4:4 at 5 90 / 90 / 90 / 105 / 152; 128 of 1024 x 1024 at 10 114 / 114 / 131 / 131 / 279; 1024 of 256 x 256 at
 // 5 43 / 31 / 31 / 31 / 31.
 constexpr uint32_t kUnstuffWide = 6144;
-// Few long scans leave most of the chip idle while each takes a step after the other: a workgroup has kUnstuffManyWaves wavefronts
-// where all scans of a launch find room at once that way and the longest group's are several steps of the narrower ones.
-// us of the launch, four wavefronts and sixteen: 38 pictures of 361 to 924 pixels at scan group 8 84 / 66, 24 of 896 x 952 at 6 57 / 47, one of
-// 1000 x 700 at 3 37 / 30, the baseline file of a picture of 393 x 609 38.6 / 27.7.
-constexpr uint32_t kUnstuffManyScans = 512, kUnstuffManyBytes = 12288;
 struct UnstuffPlan { uint64_t wide; uint32_t count; uint32_t first[kMaxGroups + 1]; uint8_t group[kMaxGroups]; };
 
-// One scan by W wavefronts (1, or those of a workgroup); wave: this one's number among them.  buf: W steps and
+// One scan by W wavefronts (1, or the kUnstuffWaves of a workgroup); wave: this one's number among them.  buf: W steps and
 // 32 bytes; tot: W words.
 template <uint32_t W>
 PCR_D void unstuff_scan(const DevRecord& R, uint32_t i, uint32_t g, uint8_t* buf, uint32_t* tot, uint32_t wave, uint32_t lane) {
@@ -664,9 +646,10 @@ struct ApplyJob { const ApplyUnit* au; ApplyList* lists; uint32_t nau, kmax, gro
 // refinement scans) into a compact list.
 // A wavefront per (image, component), a lane per scan: the loads of all scans are under way together.  (A lane per image
 // and component walking its scans took 9.4 us for 1024 images, nearly all of it waiting for one load after another.)
-constexpr int kApplyPrepWaves = 4;                          // (in a launch of its own; else as many as a workgroup of that launch has)
+constexpr int kApplyPrepWaves = 4;
+static_assert(kApplyPrepWaves == (int)kUnstuffWaves, "they share a launch");
 PCR_D void apply_prep(const DevRecord& R, const ApplyUnit* __restrict__ au, uint32_t nau, uint32_t kmax, ApplyList* lists, uint32_t group) {
-    const uint32_t u = group * (blockDim.x >> 6) + uni(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const uint32_t u = group * kApplyPrepWaves + uni(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     if (u >= nau) return;
     const ApplyUnit a = au[u];
     const ImgDesc* img = &R.img[a.img];
@@ -712,10 +695,9 @@ __global__ void __launch_bounds__(64 * kApplyPrepWaves) k_apply_prep(DevRecord R
 // The other P.first[P.count] + kDies * F.rows: fill_turn says which of them fill, the others unstuff.  (Every second
 // or fourth single workgroup, as before, put the whole fill on four or two of the eight dies: 202 and 214 us for 1024
 // photographs at scan groups 9 and 10, of which the 0.5 GB fill is the larger part, against 118 and 131.)
-template <uint32_t WAVES>
-__global__ void __launch_bounds__(64 * WAVES) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period, ApplyJob A) {
-    __shared__ __attribute__((aligned(16))) uint8_t buf[WAVES * (kUnstuffStep + 32)];
-    __shared__ uint32_t tot[WAVES];
+__global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period, ApplyJob A) {
+    __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffWaves * (kUnstuffStep + 32)];
+    __shared__ uint32_t tot[kUnstuffWaves];
     short_kernel_priority();
     const uint32_t tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
     if (blockIdx.x < A.groups) { apply_prep(R, A.au, A.nau, A.kmax, A.lists, blockIdx.x); return; }
@@ -723,8 +705,8 @@ __global__ void __launch_bounds__(64 * WAVES) k_unstuff(DevRecord R, UnstuffPlan
     if (turn.fills) {
         for (int f = 0; f < kMaxFills; f++) {
             uint4* p = F.p[f];
-            const size_t n16 = F.n16[f], stride = (size_t)F.rows * kDies * (64 * WAVES);
-            for (size_t e = (size_t)turn.index * (64 * WAVES) + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
+            const size_t n16 = F.n16[f], stride = (size_t)F.rows * kDies * 256;
+            for (size_t e = (size_t)turn.index * 256 + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
         }
         return;
     }
@@ -734,9 +716,9 @@ __global__ void __launch_bounds__(64 * WAVES) k_unstuff(DevRecord R, UnstuffPlan
     if (e >= P.count) return;
     const uint32_t g = P.group[e], at = u - P.first[e];
     if ((P.wide >> e) & 1) {
-        if (at < R.n) unstuff_scan<WAVES>(R, at, g, buf, tot, wave, lane);
+        if (at < R.n) unstuff_scan<kUnstuffWaves>(R, at, g, buf, tot, wave, lane);
     } else {
-        const uint32_t i = at * WAVES + wave;
+        const uint32_t i = at * kUnstuffWaves + wave;
         if (i < R.n) unstuff_scan<1>(R, i, g, buf + wave * (kUnstuffStep + 32), tot, 0, lane);
     }
 }
@@ -829,15 +811,6 @@ PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __rest
 // What earlier kernels wrote and this one only reads, at a wave-uniform address: a scalar load, which arrives in scalar
 // registers and does not stand in the way of the loads behind it.
 template <class T> PCR_D T load_const(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
-// The caller's copy of an image's status, from the workgroup of the pixel kernel that has the image's first tile.  (As a copy of its own
-// behind that kernel it was one more command that waits for the one before it.  Pictures of 16 to 43 pixels, two records of 130 at scan
-// group 2: 112 us a call with it, 80 without; 120 of 88 x 103 at 6: 135 and 130.)
-PCR_D void hand_out_status(const DevRecord& R, uint32_t img, uint32_t tile) {
-    if (R.status_out && tile == 0) {
-        const int32_t st = load_const(&R.status[img]);
-        if (threadIdx.x == 0) R.status_out[img] = st;
-    }
-}
 // Where this stands its arguments have been loaded: loads that depend on nothing but the image's number are then under
 // way together.  (The compiler moves each to its first use, behind the branches, and waits for one after the other.)
 PCR_D void wanted_now(uint32_t a) { asm volatile("" :: "s"(a)); }
@@ -1991,7 +1964,6 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), mcu0 = uni(tiles[item].mcu0);
-    hand_out_status(R, timg, mcu0);
     const uint32_t tid = threadIdx.x;
     // Everything the run needs to know of its image, asked for at once, and the quantiser steps, the block's coefficients and
     // the lists behind it: three round trips to memory ahead of the transform where there were eight, one after the other,
@@ -2239,7 +2211,6 @@ __global__ void __launch_bounds__(kFlatLanes) k_pixel_flat(DevRecord R, const Pi
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), cell0 = uni(tiles[item].mcu0);
-    hand_out_status(R, timg, cell0);
     ImgDesc D;
     load_desc(R.img + timg, &D);
     const uint32_t nc = D.nc, W = D.W, H = D.H;
@@ -2302,7 +2273,6 @@ __global__ void __launch_bounds__(kFlatRowLanes) k_pixel_flat_rows(DevRecord R, 
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), cy = uni(tiles[item].mcu0);      // (mcu0: the row of cells)
-    hand_out_status(R, timg, cy);
     ImgDesc D;
     load_desc(R.img + timg, &D);
     const uint32_t nc = D.nc, W = D.W, H = D.H, tid = threadIdx.x;
@@ -2531,7 +2501,6 @@ __global__ void __launch_bounds__(kFlatLanes) k_pixel_smooth_flat(DevRecord R, c
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), cell0 = uni(tiles[item].mcu0);
-    hand_out_status(R, timg, cell0);
     ImgDesc D;
     load_desc(R.img + timg, &D);
     const uint32_t nc = D.nc, W = D.W, H = D.H;
@@ -2725,7 +2694,6 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), mcu0 = uni(tiles[item].mcu0);
-    hand_out_status(R, timg, mcu0);
     const uint32_t tid = threadIdx.x;
     ImgDesc D;
     load_desc(R.img + timg, &D);

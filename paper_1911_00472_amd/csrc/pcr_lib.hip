@@ -56,7 +56,6 @@ struct Plan {                               // launch geometry for one scan grou
     ApplyUnit* d_apply = nullptr; ApplyList* d_apply_lists = nullptr; int32_t* d_list_idx = nullptr; uint32_t n_apply = 0, apply_grid_x = 0;
     bool has_ac = false;                     // some scan <= k is an AC scan (else only element 0 of every block is ever touched)
     bool had_ac = false;                     // ... some scan <= k0 (the fidelity an upgrade starts from)
-    bool smooths = false;                    // some component of a progressive image has its DC first scan and no other among the scans <= k
     bool dc_complete = true;                 // every component of every image has its first DC scan among the scans <= k
 };
 
@@ -324,11 +323,10 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     for (uint32_t i = 0; i < n; i++) {
         const uint32_t upto = std::min<uint32_t>(r->img[i].nscans, (uint32_t)k);
         bool refine[kMaxComp] = {false, false, false};
-        uint32_t have_dc = 0, carried[kMaxComp] = {0, 0, 0};
+        uint32_t have_dc = 0;
         for (uint32_t g = 0; g < upto; g++) {
             const size_t ig = (size_t)i * G + g;
             const ScanDesc& sd = r->scan[ig];
-            for (int j = 0; j < sd.ns; j++) carried[sd.comp[j]]++;
             if (sd.Ah > 0) for (int j = 0; j < sd.ns; j++) refine[sd.comp[j]] = true;
             if (sd.Ss == 0 && sd.Ah == 0) for (int j = 0; j < sd.ns; j++) have_dc |= 1u << sd.comp[j];
             const bool seq = is_sequential_scan(sd);
@@ -349,7 +347,6 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             plan_bytes += cnt * sizeof(Unit) + (cnt / kEntropyLanes + 1) * sizeof(LaneJob);   // (more than dc_units_by_shape's starts take)
         }
         if (have_dc != (1u << r->img[i].nc) - 1u) plan.dc_complete = false;
-        for (int c = 0; c < r->img[i].nc; c++) if (carried[c] == 1 && (have_dc >> c & 1) && r->img[i].progressive) plan.smooths = true;
         for (int c = 0; c < r->img[i].nc; c++) if (refine[c]) {
             apply.push_back(ApplyUnit{i, (uint32_t)c});
             max_blk = std::max<uint32_t>(max_blk, (uint32_t)r->img[i].bw[c] * r->img[i].bh[c]);
@@ -562,14 +559,13 @@ void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bo
     const uint32_t n = r->hdr.n;
     const bool own = n <= kOwnIndexImages / 2 || (n <= kOwnIndexImages && k <= (uint32_t)kHeaderWaves);
     if (!own) hipLaunchKernelGGL(k_index, dim3(k), dim3(256), 0, s, r->d, k);
-    const uint32_t waves = n <= kHeaderWideImages ? (uint32_t)kHeaderWaves : std::min<uint32_t>(k, n <= kHeaderNarrowImages ? kHeaderWaves : kHeaderWaves / 2);
-    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * waves), header_lds(k, waves), s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
+    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * (n <= kHeaderWideImages ? kHeaderWaves : std::min<uint32_t>(k, kHeaderWaves))), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
 }
 
 // Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, rows of filling
 // workgroups spread evenly between the others (fill_turn) so that they run beside them all the way (as many as unstuff at
 // most, or they would go ahead of them; 1024 where that is more: there is room for all at once).
-void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, ApplyJob lists, bool with_lists, hipStream_t s) {
+void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, const ApplyJob& lists, hipStream_t s) {
     const uint32_t n = r->hdr.n, count = k - k0;
     UnstuffPlan P{};
     uint64_t mean[kMaxGroups];
@@ -581,24 +577,20 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, Apply
         for (; e > 0 && mean[P.group[e - 1]] < mean[g]; e--) P.group[e] = P.group[e - 1];
         P.group[e] = (uint8_t)g;
     }
-    const bool many = n * count <= kUnstuffManyScans && count && mean[P.group[0]] >= kUnstuffManyBytes;
-    const uint32_t waves = many ? kUnstuffManyWaves : kUnstuffWaves;
-    if (with_lists) lists.groups = ((lists.nau + waves - 1) / waves + kDies - 1) / kDies * kDies;
     uint32_t groups = 0;
     for (uint32_t e = 0; e < count; e++) {
         P.first[e] = groups;
         const bool wide = mean[P.group[e]] >= kUnstuffWide;
         if (wide) P.wide |= 1ull << e;
-        groups += wide ? n : (n + waves - 1) / waves;
+        groups += wide ? n : (n + kUnstuffWaves - 1) / kUnstuffWaves;
     }
     P.first[count] = groups;
     size_t pieces = 0;
     for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
-    const uint32_t lanes = 64 * waves;                       // (eight pieces per lane, but for the last row)
-    fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 8 * lanes - 1) / (8 * lanes), std::min<size_t>(many ? 512 : 2048, std::max<size_t>(groups, many ? 256 : 1024))));
+    fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 2047) / 2048, std::min<size_t>(2048, std::max<size_t>(groups, 1024))));   // (eight pieces per lane, but for the last row)
     const uint32_t total = lists.groups + groups + kDies * fill.rows;
     if (total == 0) return;
-    hipLaunchKernelGGL((many ? k_unstuff<kUnstuffManyWaves> : k_unstuff<kUnstuffWaves>), dim3(total), dim3(lanes), 0, s, r->d, P, fill, fill_period(groups, fill.rows), lists);
+    hipLaunchKernelGGL(k_unstuff, dim3(total), dim3(64 * kUnstuffWaves), 0, s, r->d, P, fill, fill_period(groups, fill.rows), lists);
 }
 
 // Steps 1-5 of the path (index .. entropy decode + refinement) for scans 1..k.
@@ -666,7 +658,8 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // (with stage timing on the lists are a launch of their own: the stage that uses them is theirs)
     ApplyJob lists{plan->d_apply, plan->d_apply_lists, plan->n_apply, (uint32_t)k, 0};
     const uint32_t list_groups = (plan->n_apply + kApplyPrepWaves - 1) / kApplyPrepWaves;
-    launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, lists, !r->timing, s);
+    if (!r->timing) lists.groups = (list_groups + kDies - 1) / kDies * kDies;
+    launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, lists, s);
     mark(r, PCR_STAGE_UNSTUFF, s);
     const uint32_t* c32 = reinterpret_cast<const uint32_t*>(r->d.clean);
     // (a launch of DC scans alone asks for their tables only: with an AC table's room each, the wavefronts of one record left
@@ -725,7 +718,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         }
     }
     if (plan->n_apply) {
-        if (r->timing) hipLaunchKernelGGL(k_apply_prep, dim3(list_groups), dim3(64 * kApplyPrepWaves), 0, s, r->d, lists);
+        if (!lists.groups) hipLaunchKernelGGL(k_apply_prep, dim3(list_groups), dim3(64 * kApplyPrepWaves), 0, s, r->d, lists);
         if (refine_in_memory)
             hipLaunchKernelGGL(k_apply, dim3(plan->apply_grid_x, plan->n_apply), dim3(256), 0, s, r->d, plan->d_apply, plan->d_apply_lists);
     }
@@ -1407,27 +1400,25 @@ static int decode_to_pixels(pcr_record* r, int k0, int k, uint8_t* out, size_t c
     int rc = run_entropy_stages(r, k0, k, s, false, &plan);
     if (rc) return rc;
     // smoothing: with DC first scans only, a kernel of its own; otherwise the predicted coefficients go into the planes
-    // for the pixel kernel and are taken out again after it (where there is a component to predict at all: the two
-    // launches took 150 of the 1550 us of 2048 pictures of 132 x 133 at scan group 10, to find that there is none)
-    DevRecord d = r->d;
-    d.status_out = d_status;
+    // for the pixel kernel and are taken out again after it
     const bool smooth_flat = smooth && !plan->has_ac && !plan->n_apply && !boxes;
-    if (smooth_flat || !plan->smooths) smooth = false;
+    if (smooth_flat) smooth = false;
     if (smooth) hipLaunchKernelGGL(k_smooth<false>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
     if (smooth_flat)
-        hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out);
+        hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, r->d, r->d_flat_tiles, out);
     else if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
+        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
     else if (plan->has_ac || smooth)
-        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
+        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
     else if (r->n_flat_rows && !boxes)                       // DC scans only: every block is flat
-        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
+        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, r->d, r->d_flat_rows, out, r->flat_row_cells);
     else
-        hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out, boxes);
+        hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, r->d, r->d_flat_tiles, out, boxes);
     if (smooth) hipLaunchKernelGGL(k_smooth<true>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
     mark(r, PCR_STAGE_PIXEL, s);
     call_end(r);
     if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
+    if (d_status) HIP_TRY(hipMemcpyAsync(d_status, r->d.status, r->hdr.n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     r->resident_k = k;
     return PCR_OK;
 }
@@ -1462,18 +1453,17 @@ int pcr_decode_batch_triangle(pcr_record* r, int k, uint8_t* out, size_t cap, vo
     r->resident_k = 0;
     rc = run_entropy_stages(r, 0, k, s, false, &plan);
     if (rc) return rc;
-    DevRecord d = r->d;
-    d.status_out = d_status;
     if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr);
     else
-        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr);
     uint32_t items = 1;
     for (uint32_t i = 0; i < n; i++) items = std::max(items, (((uint32_t)r->img[i].W + 3) / 4) * (uint32_t)r->img[i].H);
     hipLaunchKernelGGL(k_triangle_rgb, dim3((items + 255) / 256, n), dim3(256), 0, s, r->d, (const uint8_t*)r->d_planes, out);
     mark(r, PCR_STAGE_PIXEL, s);
     call_end(r);
     if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
+    if (d_status) HIP_TRY(hipMemcpyAsync(d_status, r->d.status, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     r->resident_k = k;
     return PCR_OK;
 }
@@ -1559,24 +1549,23 @@ int pcr_decode_crop_batch(pcr_record* r, int k, const pcr_crop* d_crops, uint8_t
         r->resident_k = 0;
         rc = run_entropy_stages(r, 0, k, s, false, &plan);
         if (rc) return rc;
-        DevRecord d = r->d;
-        d.status_out = d_status;
         TailParams P;
         P.out_h = out_h; P.out_w = out_w;
         for (int c = 0; c < 3; c++) { P.mean[c] = c < C ? mean[c] : 0.f; P.istd[c] = c < C ? inv_std[c] : 1.f; }
         static_assert(sizeof(pcr_crop) == sizeof(CropBox), "crop box layout");
         const CropBox* boxes = reinterpret_cast<const CropBox*>(d_crops);
         if (plan->n_apply)
-            hipLaunchKernelGGL(k_pixel_tail<true>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, d, r->d_tail_tiles, plan->d_apply_lists, plan->d_list_idx,
+            hipLaunchKernelGGL(k_pixel_tail<true>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, r->d, r->d_tail_tiles, plan->d_apply_lists, plan->d_list_idx,
                                boxes, P, reinterpret_cast<__half*>(d_out_f16), r->d_edge, r->d_edge_off);
         else
-            hipLaunchKernelGGL(k_pixel_tail<false>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, d, r->d_tail_tiles, (const ApplyList*)nullptr,
+            hipLaunchKernelGGL(k_pixel_tail<false>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, r->d, r->d_tail_tiles, (const ApplyList*)nullptr,
                                (const int32_t*)nullptr, boxes, P, reinterpret_cast<__half*>(d_out_f16), r->d_edge, r->d_edge_off);
         hipLaunchKernelGGL(k_tail_edges, dim3((uint32_t)out_h, n), dim3(64), 0, s, r->d_dims, r->d_mcu_px_h, C, boxes, P, r->d_edge, r->d_edge_off,
                            reinterpret_cast<__half*>(d_out_f16));
         mark(r, PCR_STAGE_PIXEL, s);
         call_end(r);
         if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
+        if (d_status) HIP_TRY(hipMemcpyAsync(d_status, r->d.status, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
         r->resident_k = k;
         return PCR_OK;
     }
