@@ -462,7 +462,7 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
 // (Before: a workgroup per scan, 2 KB per step with four barriers and no loads ahead, 128 us for the 81 MB of 1024
 // photographs, and 71 us for the fill after it.)
 // --------------------------------------------------------------------------------------
-constexpr uint32_t kUnstuffWaves = 4, kUnstuffStep = 1024;
+constexpr uint32_t kUnstuffWaves = 4, kUnstuffManyWaves = 16, kUnstuffStep = 1024;
 constexpr int kMaxFills = 3;
 struct FillList { uint4* p[kMaxFills]; size_t n16[kMaxFills]; uint32_t rows; };        // 16-byte pieces; rows of workgroups that share the work
 
@@ -484,9 +484,14 @@ struct __attribute__((packed, aligned(1))) LooseU16 { uint16_t v; };
 // of 600 x 450 in 4:4:4 at 5 90 / 90 / 90 / 105 / 152; 128 of 1024 x 1024 at 10 114 / 114 / 131 / 131 / 279; 1024 of 256 x 256 at
 // 5 43 / 31 / 31 / 31 / 31.
 constexpr uint32_t kUnstuffWide = 6144;
+// Few long scans leave most of the chip idle while each takes a step after the other: a workgroup has kUnstuffManyWaves wavefronts
+// where all scans of a launch find room at once that way and the longest group's are several steps of the narrower ones.
+// us of the launch, four wavefronts and sixteen: 38 pictures of 361 to 924 pixels at scan group 8 84 / 66, 24 of 896 x 952 at 6 57 / 47, one of
+// 1000 x 700 at 3 37 / 30, the baseline file of a picture of 393 x 609 38.6 / 27.7.
+constexpr uint32_t kUnstuffManyScans = 512, kUnstuffManyBytes = 12288;
 struct UnstuffPlan { uint64_t wide; uint32_t count; uint32_t first[kMaxGroups + 1]; uint8_t group[kMaxGroups]; };
 
-// One scan by W wavefronts (1, or the kUnstuffWaves of a workgroup); wave: this one's number among them.  buf: W steps and
+// One scan by W wavefronts (1, or those of a workgroup); wave: this one's number among them.  buf: W steps and
 // 32 bytes; tot: W words.
 template <uint32_t W>
 PCR_D void unstuff_scan(const DevRecord& R, uint32_t i, uint32_t g, uint8_t* buf, uint32_t* tot, uint32_t wave, uint32_t lane) {
@@ -646,10 +651,9 @@ struct ApplyJob { const ApplyUnit* au; ApplyList* lists; uint32_t nau, kmax, gro
 // refinement scans) into a compact list.
 // A wavefront per (image, component), a lane per scan: the loads of all scans are under way together.  (A lane per image
 // and component walking its scans took 9.4 us for 1024 images, nearly all of it waiting for one load after another.)
-constexpr int kApplyPrepWaves = 4;
-static_assert(kApplyPrepWaves == (int)kUnstuffWaves, "they share a launch");
+constexpr int kApplyPrepWaves = 4;                          // (in a launch of its own; else as many as a workgroup of that launch has)
 PCR_D void apply_prep(const DevRecord& R, const ApplyUnit* __restrict__ au, uint32_t nau, uint32_t kmax, ApplyList* lists, uint32_t group) {
-    const uint32_t u = group * kApplyPrepWaves + uni(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const uint32_t u = group * (blockDim.x >> 6) + uni(threadIdx.x >> 6), lane = threadIdx.x & 63u;
     if (u >= nau) return;
     const ApplyUnit a = au[u];
     const ImgDesc* img = &R.img[a.img];
@@ -695,9 +699,10 @@ __global__ void __launch_bounds__(64 * kApplyPrepWaves) k_apply_prep(DevRecord R
 // The other P.first[P.count] + kDies * F.rows: fill_turn says which of them fill, the others unstuff.  (Every second
 // or fourth single workgroup, as before, put the whole fill on four or two of the eight dies: 202 and 214 us for 1024
 // photographs at scan groups 9 and 10, of which the 0.5 GB fill is the larger part, against 118 and 131.)
-__global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period, ApplyJob A) {
-    __shared__ __attribute__((aligned(16))) uint8_t buf[kUnstuffWaves * (kUnstuffStep + 32)];
-    __shared__ uint32_t tot[kUnstuffWaves];
+template <uint32_t WAVES>
+__global__ void __launch_bounds__(64 * WAVES) k_unstuff(DevRecord R, UnstuffPlan P, FillList F, uint32_t period, ApplyJob A) {
+    __shared__ __attribute__((aligned(16))) uint8_t buf[WAVES * (kUnstuffStep + 32)];
+    __shared__ uint32_t tot[WAVES];
     short_kernel_priority();
     const uint32_t tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63;
     if (blockIdx.x < A.groups) { apply_prep(R, A.au, A.nau, A.kmax, A.lists, blockIdx.x); return; }
@@ -705,8 +710,8 @@ __global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, Uns
     if (turn.fills) {
         for (int f = 0; f < kMaxFills; f++) {
             uint4* p = F.p[f];
-            const size_t n16 = F.n16[f], stride = (size_t)F.rows * kDies * 256;
-            for (size_t e = (size_t)turn.index * 256 + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
+            const size_t n16 = F.n16[f], stride = (size_t)F.rows * kDies * (64 * WAVES);
+            for (size_t e = (size_t)turn.index * (64 * WAVES) + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
         }
         return;
     }
@@ -716,9 +721,9 @@ __global__ void __launch_bounds__(64 * kUnstuffWaves) k_unstuff(DevRecord R, Uns
     if (e >= P.count) return;
     const uint32_t g = P.group[e], at = u - P.first[e];
     if ((P.wide >> e) & 1) {
-        if (at < R.n) unstuff_scan<kUnstuffWaves>(R, at, g, buf, tot, wave, lane);
+        if (at < R.n) unstuff_scan<WAVES>(R, at, g, buf, tot, wave, lane);
     } else {
-        const uint32_t i = at * kUnstuffWaves + wave;
+        const uint32_t i = at * WAVES + wave;
         if (i < R.n) unstuff_scan<1>(R, i, g, buf + wave * (kUnstuffStep + 32), tot, 0, lane);
     }
 }

@@ -565,7 +565,7 @@ void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bo
 // Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, rows of filling
 // workgroups spread evenly between the others (fill_turn) so that they run beside them all the way (as many as unstuff at
 // most, or they would go ahead of them; 1024 where that is more: there is room for all at once).
-void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, const ApplyJob& lists, hipStream_t s) {
+void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, ApplyJob lists, bool with_lists, hipStream_t s) {
     const uint32_t n = r->hdr.n, count = k - k0;
     UnstuffPlan P{};
     uint64_t mean[kMaxGroups];
@@ -577,20 +577,24 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, const
         for (; e > 0 && mean[P.group[e - 1]] < mean[g]; e--) P.group[e] = P.group[e - 1];
         P.group[e] = (uint8_t)g;
     }
+    const bool many = n * count <= kUnstuffManyScans && count && mean[P.group[0]] >= kUnstuffManyBytes;
+    const uint32_t waves = many ? kUnstuffManyWaves : kUnstuffWaves;
+    if (with_lists) lists.groups = ((lists.nau + waves - 1) / waves + kDies - 1) / kDies * kDies;
     uint32_t groups = 0;
     for (uint32_t e = 0; e < count; e++) {
         P.first[e] = groups;
         const bool wide = mean[P.group[e]] >= kUnstuffWide;
         if (wide) P.wide |= 1ull << e;
-        groups += wide ? n : (n + kUnstuffWaves - 1) / kUnstuffWaves;
+        groups += wide ? n : (n + waves - 1) / waves;
     }
     P.first[count] = groups;
     size_t pieces = 0;
     for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
-    fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 2047) / 2048, std::min<size_t>(2048, std::max<size_t>(groups, 1024))));   // (eight pieces per lane, but for the last row)
+    const uint32_t lanes = 64 * waves;                       // (eight pieces per lane, but for the last row)
+    fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 8 * lanes - 1) / (8 * lanes), std::min<size_t>(many ? 512 : 2048, std::max<size_t>(groups, many ? 256 : 1024))));
     const uint32_t total = lists.groups + groups + kDies * fill.rows;
     if (total == 0) return;
-    hipLaunchKernelGGL(k_unstuff, dim3(total), dim3(64 * kUnstuffWaves), 0, s, r->d, P, fill, fill_period(groups, fill.rows), lists);
+    hipLaunchKernelGGL((many ? k_unstuff<kUnstuffManyWaves> : k_unstuff<kUnstuffWaves>), dim3(total), dim3(lanes), 0, s, r->d, P, fill, fill_period(groups, fill.rows), lists);
 }
 
 // Steps 1-5 of the path (index .. entropy decode + refinement) for scans 1..k.
@@ -658,8 +662,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // (with stage timing on the lists are a launch of their own: the stage that uses them is theirs)
     ApplyJob lists{plan->d_apply, plan->d_apply_lists, plan->n_apply, (uint32_t)k, 0};
     const uint32_t list_groups = (plan->n_apply + kApplyPrepWaves - 1) / kApplyPrepWaves;
-    if (!r->timing) lists.groups = (list_groups + kDies - 1) / kDies * kDies;
-    launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, lists, s);
+    launch_unstuff(r, (uint32_t)k0, (uint32_t)k, fill, lists, !r->timing, s);
     mark(r, PCR_STAGE_UNSTUFF, s);
     const uint32_t* c32 = reinterpret_cast<const uint32_t*>(r->d.clean);
     // (a launch of DC scans alone asks for their tables only: with an AC table's room each, the wavefronts of one record left
@@ -718,7 +721,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         }
     }
     if (plan->n_apply) {
-        if (!lists.groups) hipLaunchKernelGGL(k_apply_prep, dim3(list_groups), dim3(64 * kApplyPrepWaves), 0, s, r->d, lists);
+        if (r->timing) hipLaunchKernelGGL(k_apply_prep, dim3(list_groups), dim3(64 * kApplyPrepWaves), 0, s, r->d, lists);
         if (refine_in_memory)
             hipLaunchKernelGGL(k_apply, dim3(plan->apply_grid_x, plan->n_apply), dim3(256), 0, s, r->d, plan->d_apply, plan->d_apply_lists);
     }

@@ -29,3 +29,21 @@ def test_scan_lengths_restarts_and_fill(side, restart):
         for i in range(r.n):
             want, _, _ = oracle.decode_record_image(rec, i, r.G)
             assert np.array_equal(got[int(lay[i]):int(lay[i + 1])], want), i
+
+
+@pytest.mark.parametrize("restart", [0, 3])
+@pytest.mark.parametrize("side,count", [(128, 3), (136, 3), (144, 3), (200, 3), (264, 2), (136, 170), (136, 171), (136, 520)])
+def test_many_wavefronts_per_scan(side, count, restart):
+    """Few long scans: sixteen wavefronts each, steps of 16384 bytes, scans that end short of, at and beyond one; short scans
+    beside them; as many scans as still go that way, and more."""
+    files = [pcrgen.encode_pixels(_noise(300 * side + i, side), 1, 1, 98 - (i % 3), "sequential", restart=restart) for i in range(3)]
+    files = (files * (count // 3 + 1))[:count]
+    files[1] = pcrgen.encode_pixels(_noise(side, 11), 1, 1, 50, "sequential", restart=restart)
+    files[-1] = with_fill_bytes(files[-1])
+    rec = pcrgen.write_record(files)
+    with pkg.pcr_open(rec, 0) as r:
+        lay = r.coef_layout()
+        got = r.decode_coefficients(r.G).cpu().numpy()
+        for i in list(range(min(4, r.n))) + [r.n - 1]:
+            want, _, _ = oracle.decode_record_image(rec, i, r.G)
+            assert np.array_equal(got[int(lay[i]):int(lay[i + 1])], want), i
