@@ -79,6 +79,7 @@ struct DevRecord {
                                // coefficient export
     uint64_t* masks;
     int32_t* status;           // [n]
+    int32_t* status_out;       // [n], the caller's (null: not wanted): filled by the pixel kernel of the call (hand_out_status)
     AcTab* tabs;               // Huffman tables of the AC scans, written by k_headers
     const uint32_t* tab_idx;   // [n][G] index into tabs
     DcTab* dctabs;             // the DC tables of the DC first scans, three slots per scan (one per scan component)
@@ -816,6 +817,15 @@ PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __rest
 // What earlier kernels wrote and this one only reads, at a wave-uniform address: a scalar load, which arrives in scalar
 // registers and does not stand in the way of the loads behind it.
 template <class T> PCR_D T load_const(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
+// The caller's copy of an image's status, from the workgroup of the pixel kernel that has the image's first tile.  (As a copy of its own
+// behind that kernel it was one more command that waits for the one before it.  Pictures of 16 to 43 pixels, two records of 130 at scan
+// group 2: 112 us a call with it, 80 without; 120 of 88 x 103 at 6: 135 and 130.)
+PCR_D void hand_out_status(const DevRecord& R, uint32_t img, uint32_t tile) {
+    if (R.status_out && tile == 0) {
+        const int32_t st = load_const(&R.status[img]);
+        if (threadIdx.x == 0) R.status_out[img] = st;
+    }
+}
 // Where this stands its arguments have been loaded: loads that depend on nothing but the image's number are then under
 // way together.  (The compiler moves each to its first use, behind the branches, and waits for one after the other.)
 PCR_D void wanted_now(uint32_t a) { asm volatile("" :: "s"(a)); }
@@ -1969,6 +1979,7 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), mcu0 = uni(tiles[item].mcu0);
+    hand_out_status(R, timg, mcu0);
     const uint32_t tid = threadIdx.x;
     // Everything the run needs to know of its image, asked for at once, and the quantiser steps, the block's coefficients and
     // the lists behind it: three round trips to memory ahead of the transform where there were eight, one after the other,
@@ -2216,6 +2227,7 @@ __global__ void __launch_bounds__(kFlatLanes) k_pixel_flat(DevRecord R, const Pi
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), cell0 = uni(tiles[item].mcu0);
+    hand_out_status(R, timg, cell0);
     ImgDesc D;
     load_desc(R.img + timg, &D);
     const uint32_t nc = D.nc, W = D.W, H = D.H;
@@ -2278,6 +2290,7 @@ __global__ void __launch_bounds__(kFlatRowLanes) k_pixel_flat_rows(DevRecord R, 
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), cy = uni(tiles[item].mcu0);      // (mcu0: the row of cells)
+    hand_out_status(R, timg, cy);
     ImgDesc D;
     load_desc(R.img + timg, &D);
     const uint32_t nc = D.nc, W = D.W, H = D.H, tid = threadIdx.x;
@@ -2506,6 +2519,7 @@ __global__ void __launch_bounds__(kFlatLanes) k_pixel_smooth_flat(DevRecord R, c
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), cell0 = uni(tiles[item].mcu0);
+    hand_out_status(R, timg, cell0);
     ImgDesc D;
     load_desc(R.img + timg, &D);
     const uint32_t nc = D.nc, W = D.W, H = D.H;
@@ -2699,6 +2713,7 @@ __global__ void __launch_bounds__(kTailLanes) k_pixel_tail(DevRecord R, const Pi
     short_kernel_priority();
     const uint32_t item = xcd_major(blockIdx.x, gridDim.x);
     const uint32_t timg = uni(tiles[item].img), mcu0 = uni(tiles[item].mcu0);
+    hand_out_status(R, timg, mcu0);
     const uint32_t tid = threadIdx.x;
     ImgDesc D;
     load_desc(R.img + timg, &D);

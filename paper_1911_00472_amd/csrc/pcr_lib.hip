@@ -56,6 +56,7 @@ struct Plan {                               // launch geometry for one scan grou
     ApplyUnit* d_apply = nullptr; ApplyList* d_apply_lists = nullptr; int32_t* d_list_idx = nullptr; uint32_t n_apply = 0, apply_grid_x = 0;
     bool has_ac = false;                     // some scan <= k is an AC scan (else only element 0 of every block is ever touched)
     bool had_ac = false;                     // ... some scan <= k0 (the fidelity an upgrade starts from)
+    bool smooths = false;                    // some component of a progressive image has its DC first scan and no other among the scans <= k
     bool dc_complete = true;                 // every component of every image has its first DC scan among the scans <= k
 };
 
@@ -323,10 +324,11 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     for (uint32_t i = 0; i < n; i++) {
         const uint32_t upto = std::min<uint32_t>(r->img[i].nscans, (uint32_t)k);
         bool refine[kMaxComp] = {false, false, false};
-        uint32_t have_dc = 0;
+        uint32_t have_dc = 0, carried[kMaxComp] = {0, 0, 0};
         for (uint32_t g = 0; g < upto; g++) {
             const size_t ig = (size_t)i * G + g;
             const ScanDesc& sd = r->scan[ig];
+            for (int j = 0; j < sd.ns; j++) carried[sd.comp[j]]++;
             if (sd.Ah > 0) for (int j = 0; j < sd.ns; j++) refine[sd.comp[j]] = true;
             if (sd.Ss == 0 && sd.Ah == 0) for (int j = 0; j < sd.ns; j++) have_dc |= 1u << sd.comp[j];
             const bool seq = is_sequential_scan(sd);
@@ -347,6 +349,7 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             plan_bytes += cnt * sizeof(Unit) + (cnt / kEntropyLanes + 1) * sizeof(LaneJob);   // (more than dc_units_by_shape's starts take)
         }
         if (have_dc != (1u << r->img[i].nc) - 1u) plan.dc_complete = false;
+        for (int c = 0; c < r->img[i].nc; c++) if (carried[c] == 1 && (have_dc >> c & 1) && r->img[i].progressive) plan.smooths = true;
         for (int c = 0; c < r->img[i].nc; c++) if (refine[c]) {
             apply.push_back(ApplyUnit{i, (uint32_t)c});
             max_blk = std::max<uint32_t>(max_blk, (uint32_t)r->img[i].bw[c] * r->img[i].bh[c]);
@@ -1403,25 +1406,27 @@ static int decode_to_pixels(pcr_record* r, int k0, int k, uint8_t* out, size_t c
     int rc = run_entropy_stages(r, k0, k, s, false, &plan);
     if (rc) return rc;
     // smoothing: with DC first scans only, a kernel of its own; otherwise the predicted coefficients go into the planes
-    // for the pixel kernel and are taken out again after it
+    // for the pixel kernel and are taken out again after it (where there is a component to predict at all: the two
+    // launches took 150 of the 1550 us of 2048 pictures of 132 x 133 at scan group 10, to find that there is none)
+    DevRecord d = r->d;
+    d.status_out = d_status;
     const bool smooth_flat = smooth && !plan->has_ac && !plan->n_apply && !boxes;
-    if (smooth_flat) smooth = false;
+    if (smooth_flat || !plan->smooths) smooth = false;
     if (smooth) hipLaunchKernelGGL(k_smooth<false>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
     if (smooth_flat)
-        hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, r->d, r->d_flat_tiles, out);
+        hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out);
     else if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
+        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
     else if (plan->has_ac || smooth)
-        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
+        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
     else if (r->n_flat_rows && !boxes)                       // DC scans only: every block is flat
-        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, r->d, r->d_flat_rows, out, r->flat_row_cells);
+        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
     else
-        hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, r->d, r->d_flat_tiles, out, boxes);
+        hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out, boxes);
     if (smooth) hipLaunchKernelGGL(k_smooth<true>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
     mark(r, PCR_STAGE_PIXEL, s);
     call_end(r);
     if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
-    if (d_status) HIP_TRY(hipMemcpyAsync(d_status, r->d.status, r->hdr.n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     r->resident_k = k;
     return PCR_OK;
 }
@@ -1456,17 +1461,18 @@ int pcr_decode_batch_triangle(pcr_record* r, int k, uint8_t* out, size_t cap, vo
     r->resident_k = 0;
     rc = run_entropy_stages(r, 0, k, s, false, &plan);
     if (rc) return rc;
+    DevRecord d = r->d;
+    d.status_out = d_status;
     if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr);
     else
-        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, r->d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr);
     uint32_t items = 1;
     for (uint32_t i = 0; i < n; i++) items = std::max(items, (((uint32_t)r->img[i].W + 3) / 4) * (uint32_t)r->img[i].H);
     hipLaunchKernelGGL(k_triangle_rgb, dim3((items + 255) / 256, n), dim3(256), 0, s, r->d, (const uint8_t*)r->d_planes, out);
     mark(r, PCR_STAGE_PIXEL, s);
     call_end(r);
     if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
-    if (d_status) HIP_TRY(hipMemcpyAsync(d_status, r->d.status, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     r->resident_k = k;
     return PCR_OK;
 }
@@ -1552,23 +1558,24 @@ int pcr_decode_crop_batch(pcr_record* r, int k, const pcr_crop* d_crops, uint8_t
         r->resident_k = 0;
         rc = run_entropy_stages(r, 0, k, s, false, &plan);
         if (rc) return rc;
+        DevRecord d = r->d;
+        d.status_out = d_status;
         TailParams P;
         P.out_h = out_h; P.out_w = out_w;
         for (int c = 0; c < 3; c++) { P.mean[c] = c < C ? mean[c] : 0.f; P.istd[c] = c < C ? inv_std[c] : 1.f; }
         static_assert(sizeof(pcr_crop) == sizeof(CropBox), "crop box layout");
         const CropBox* boxes = reinterpret_cast<const CropBox*>(d_crops);
         if (plan->n_apply)
-            hipLaunchKernelGGL(k_pixel_tail<true>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, r->d, r->d_tail_tiles, plan->d_apply_lists, plan->d_list_idx,
+            hipLaunchKernelGGL(k_pixel_tail<true>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, d, r->d_tail_tiles, plan->d_apply_lists, plan->d_list_idx,
                                boxes, P, reinterpret_cast<__half*>(d_out_f16), r->d_edge, r->d_edge_off);
         else
-            hipLaunchKernelGGL(k_pixel_tail<false>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, r->d, r->d_tail_tiles, (const ApplyList*)nullptr,
+            hipLaunchKernelGGL(k_pixel_tail<false>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, d, r->d_tail_tiles, (const ApplyList*)nullptr,
                                (const int32_t*)nullptr, boxes, P, reinterpret_cast<__half*>(d_out_f16), r->d_edge, r->d_edge_off);
         hipLaunchKernelGGL(k_tail_edges, dim3((uint32_t)out_h, n), dim3(64), 0, s, r->d_dims, r->d_mcu_px_h, C, boxes, P, r->d_edge, r->d_edge_off,
                            reinterpret_cast<__half*>(d_out_f16));
         mark(r, PCR_STAGE_PIXEL, s);
         call_end(r);
         if (hipGetLastError() != hipSuccess) return PCR_E_DEVICE;
-        if (d_status) HIP_TRY(hipMemcpyAsync(d_status, r->d.status, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
         r->resident_k = k;
         return PCR_OK;
     }
