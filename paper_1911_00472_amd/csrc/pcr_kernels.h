@@ -150,11 +150,15 @@ constexpr uint32_t kMaxGroups = 64;                        // (parse_record_head
 constexpr uint32_t kHeaderStage = 16384;                   // bytes of LDS for the heads of the regions, shared out evenly
 constexpr uint32_t kHeaderWindow = 1024;                   // ... but at most this much per region (a first region with its tables is 600-700 bytes)
 constexpr uint32_t kHeaderWideImages = 512;                // kHeaderWaves wavefronts per workgroup whatever the scan group up to this many images
-// own_index up to this many images (a workgroup sums n lengths per scan group), but beyond half of it only where every wavefront
-// has one scan group at most.  us a call with k_index / without: 1024 pictures of 256 x 256 at scan group 5 271 / 263, four records of
-// 1024 photographs at 1 708 / 695, at 10 6022 / 6042, of 64 x 64 at 10 721 / 717.  (The line is no loss's: 2048 pictures of 256 x 256
-// at 1 209 / 197, at 5 502 / 492, at 10 1158 / 1151, four such records at 10 3992 / 3979.)
-constexpr uint32_t kOwnIndexImages = 1024;
+// Beyond this many images the workgroups are more than find room at once with eight wavefronts each: four at most.  us a call, eight / four:
+// 2048 pictures of 24 x 34 at scan group 9 262 / 245, of 15 to 40 pixels at 7 215 / 195, two records of 2048 of 70 x 54 at 5 314 / 295,
+// four of 2048 of 30 x 30 at 9 715 / 646; but 800 of 64 x 64 at 10 249 / 255, 1000 of 48 x 48 at 10 246 / 253.
+constexpr uint32_t kHeaderNarrowImages = 1024;
+// own_index up to this many images (a workgroup sums n lengths per scan group), but beyond half of it only up to scan group
+// kHeaderWaves.  us a call with k_index / without: 1024 pictures of 256 x 256 at scan group 5 271 / 263, four records of
+// 1024 photographs at 1 708 / 695, at 10 6022 / 6042, of 64 x 64 at 10 721 / 717; 2048 pictures of 256 x 256 at 1 209 / 197, at 5 502 / 492,
+// at 10 1158 / 1151.
+constexpr uint32_t kOwnIndexImages = 2048;
 
 // Record bytes by record offset: from the staged window, or (past it: long comments and profiles) from memory.
 // (The address spaces are spelled out: through two generic pointers every read became a flat one.)
@@ -256,14 +260,22 @@ PCR_D void dctab_build_wave(DcTab* t, const CanonCode* c, uint32_t lane) {
     if (lane < 8) t->valptr[lane] = (uint16_t)c->first[9 + lane];
 }
 
+// LDS of a workgroup: the heads of the regions of kmax scan groups, a code per wavefront, what the walks found.  (With room for the most
+// of everything, 30 KB, five workgroups fitted a compute unit whatever there was to do.  us a launch for 2048 pictures at scan groups 1 / 3 / 4, then and now: 37.6 / 43.4 / 45.0,
+// 25.0 / 34.8 / 35.5.)
+PCR_HD uint32_t header_stage(uint32_t kmax) { return kmax * kHeaderWindow < kHeaderStage ? kmax * kHeaderWindow : kHeaderStage; }
+PCR_HD uint32_t header_lds(uint32_t kmax, uint32_t waves) {
+    static_assert(sizeof(CanonCode) % 4 == 0 && sizeof(RegionWalk) % alignof(ScanDesc) == 0 && sizeof(ScanDesc) % 4 == 0 && alignof(RegionWalk) <= 8 && sizeof(CanonCode) % 8 == 0, "they follow each other");
+    return header_stage(kmax) + 16 + waves * (uint32_t)sizeof(CanonCode) + kmax * (uint32_t)(sizeof(RegionWalk) + sizeof(ScanDesc));
+}
 __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32_t kmax, uint32_t keep_status, uint32_t own_index, uint32_t k0, uint32_t dc_too) {
-    __shared__ __attribute__((aligned(16))) uint8_t stage[kHeaderStage + 16];
+    extern __shared__ __attribute__((aligned(16))) uint8_t stage[];          // (header_lds: as much as the scans of the call take)
+    CanonCode* const s_code = reinterpret_cast<CanonCode*>(stage + header_stage(kmax) + 16);
+    RegionWalk* const s_walk = reinterpret_cast<RegionWalk*>(s_code + (blockDim.x >> 6));
+    ScanDesc* const s_scan = reinterpret_cast<ScanDesc*>(s_walk + kmax);
     __shared__ uint32_t s_off[kMaxGroups], s_len[kMaxGroups];
-    __shared__ ScanDesc s_scan[kMaxGroups];
-    __shared__ RegionWalk s_walk[kMaxGroups];
     __shared__ int s_rc[kMaxGroups];
     __shared__ ImgDesc s_img;
-    __shared__ CanonCode s_code[kHeaderWaves];
     __shared__ uint16_t s_job[kMaxGroups * kMaxComp];        // tables to build: scan group | component of the scan << 8
     __shared__ uint32_t s_njobs;
     short_kernel_priority();
@@ -277,7 +289,7 @@ __global__ void __launch_bounds__(kHeaderLanes, 8) k_headers(DevRecord R, uint32
             const uint32_t* len = R.len + (size_t)g * n;
             const uint64_t start = ld_le64(R.rec + (g == 0 ? 16 : hdr_group_end_pos(g - 1)));
             const uint32_t mine = len[i];
-            constexpr uint32_t kHalf = kOwnIndexImages / 2 / 64;
+            constexpr uint32_t kHalf = 8;
             uint32_t before = 0;
             for (uint32_t first = 0; first < i; first += 64 * kHalf) {
                 uint32_t t[kHalf];

@@ -562,7 +562,8 @@ void launch_headers(pcr_record* r, uint32_t k, bool keep_status, uint32_t k0, bo
     const uint32_t n = r->hdr.n;
     const bool own = n <= kOwnIndexImages / 2 || (n <= kOwnIndexImages && k <= (uint32_t)kHeaderWaves);
     if (!own) hipLaunchKernelGGL(k_index, dim3(k), dim3(256), 0, s, r->d, k);
-    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * (n <= kHeaderWideImages ? kHeaderWaves : std::min<uint32_t>(k, kHeaderWaves))), 0, s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
+    const uint32_t waves = n <= kHeaderWideImages ? (uint32_t)kHeaderWaves : std::min<uint32_t>(k, n <= kHeaderNarrowImages ? kHeaderWaves : kHeaderWaves / 2);
+    hipLaunchKernelGGL(k_headers, dim3(n), dim3(64 * waves), header_lds(k, waves), s, r->d, k, (uint32_t)keep_status, (uint32_t)own, k0, (uint32_t)dc_tables);
 }
 
 // Unstuffing of scan groups k0 + 1 .. k and the fills, one launch: the groups with the longest scans first, rows of filling

@@ -125,3 +125,24 @@ def test_region_offsets_where_the_parser_sums_them_itself(n):
     """Up to 1024 images the lengths ahead of a region are summed by the parser for scan groups 1 .. 8, beyond by k_index."""
     few = [pcrgen.make_jpeg(90 + i, 1, 8 + i, 9, 3, 6.0, 1, 1, 80) for i in range(5)]
     _same(pcrgen.write_record([few[i % 5] for i in range(n)]), images=sorted({0, 63, 64, 511, 512, 513, 1023, n - 1}))
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 2048, 2049])
+def test_many_small_images(n):
+    """Workgroups of eight wavefronts and of four, offsets summed in the kernel and by k_index, at scan groups that need little
+    room on the chip and more."""
+    sizes = [(8, 8), (17, 9), (24, 30), (9, 33)]
+    files = [pcrgen.make_jpeg(60 + i, 1, w, h, 3, 12.0, 2 - i % 2, 2 - i % 2, 88) for i, (w, h) in enumerate(sizes)]
+    rec = pcrgen.write_record((files * (n // len(files) + 1))[:n])
+    images = [0, 1, 2, 3, n // 2, n - 2, n - 1]
+    with pkg.pcr_open(rec, 0) as r:
+        lay = r.output_layout()
+        for k in (1, 3, 5, 8, 9, 10):
+            status = torch.full((n,), 77, dtype=torch.int32, device="cuda")
+            got = r.decode_batch(k, status=status).cpu().numpy()
+            assert (status.cpu().numpy() == 0).all()
+            for i in images:
+                _, want, _ = oracle.decode_record_image(rec, i, k)
+                assert np.abs(got[int(lay[i]):int(lay[i + 1])].astype(int) - want.reshape(-1)).max() <= 1, (i, k)
+            for i in range(n):
+                assert np.array_equal(got[int(lay[i]):int(lay[i + 1])], got[int(lay[i % 4]):int(lay[i % 4 + 1])]), (i, k)
