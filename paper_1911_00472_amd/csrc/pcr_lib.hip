@@ -217,10 +217,11 @@ struct pcr_record {
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
     std::vector<uint32_t> unit_bits;        // records opened from host bytes: entropy-coded bits of every unit, by slot (else empty)
-    // decode fused with the training tail (allocated at its first call): one tile per MCU row, the side buffer of first
+    // decode fused with the training tail (allocated at its first call): one tile per run of an MCU row, the side buffer of first
     // and last pixel rows, where each image's part of it starts, pixel rows per MCU row of every image
     PixelTile* d_tail_tiles = nullptr; uint32_t n_tail_tiles = 0;
-    uint8_t* d_edge = nullptr; uint64_t* d_edge_off = nullptr; uint32_t* d_mcu_px_h = nullptr;
+    uint32_t tail_lds = 0, tail_rows = 0;   // LDS of a workgroup; MCU rows of the tallest image
+    uint32_t* d_edge = nullptr; uint64_t* d_edge_off = nullptr; uint32_t* d_mcu_px_h = nullptr;
     float2* d_ssim_part = nullptr;          // per-tile sums of the similarity kernels (allocated at their first call)
     uint8_t* d_planes = nullptr;            // rounded samples per component, for pcr_decode_batch_triangle (allocated at its first call)
     uint8_t* d_gather = nullptr; size_t gather_cap = 0;
@@ -1518,19 +1519,20 @@ static int prepare_fused_tail(pcr_record* r) {
     if (r->d_tail_tiles) return PCR_OK;
     const uint32_t n = r->hdr.n;
     std::vector<PixelTile> tiles; std::vector<uint64_t> eoff(n + 1, 0); std::vector<uint32_t> mh(n);
+    r->tail_lds = 0; r->tail_rows = 1;
     for (uint32_t i = 0; i < n; i++) {
         const ImgDesc& d = r->img[i];
-        if (d.mcux > 1 && 2 * blocks_per_mcu(d) > (uint32_t)kTailLanes) return PCR_E_UNSUPPORTED;   // (a pass holds two MCUs at least)
-        for (uint32_t my = 0; my < d.mcuy; my++) tiles.push_back(PixelTile{i, my * d.mcux});
-        eoff[i + 1] = eoff[i] + (uint64_t)2 * d.mcuy * d.W * d.nc;
+        for (uint32_t my = 0; my < d.mcuy; my++) for (uint32_t run = 0, runs = tail_runs(d); run < runs; run++) tiles.push_back(PixelTile{i, my * d.mcux + run});
+        eoff[i + 1] = eoff[i] + (uint64_t)2 * d.mcuy * d.W;
         mh[i] = 8u * d.vmax;
+        r->tail_lds = std::max(r->tail_lds, tail_lds(d)); r->tail_rows = std::max<uint32_t>(r->tail_rows, d.mcuy);
     }
     PixelTile* dt = nullptr;
     Uploads up(&r->big, &r->stage);
     up.add(&r->d_edge_off, eoff);
     up.add(&r->d_mcu_px_h, mh);
     up.add(&dt, tiles);
-    int rc = arena_alloc(&r->big, &r->d_edge, (size_t)eoff[n] + 16);
+    int rc = arena_alloc(&r->big, &r->d_edge, (size_t)eoff[n]);
     if (!rc) rc = up.flush();
     if (rc) return rc;
     r->d_tail_tiles = dt; r->n_tail_tiles = (uint32_t)tiles.size();
@@ -1566,13 +1568,11 @@ int pcr_decode_crop_batch(pcr_record* r, int k, const pcr_crop* d_crops, uint8_t
         for (int c = 0; c < 3; c++) { P.mean[c] = c < C ? mean[c] : 0.f; P.istd[c] = c < C ? inv_std[c] : 1.f; }
         static_assert(sizeof(pcr_crop) == sizeof(CropBox), "crop box layout");
         const CropBox* boxes = reinterpret_cast<const CropBox*>(d_crops);
-        if (plan->n_apply)
-            hipLaunchKernelGGL(k_pixel_tail<true>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, d, r->d_tail_tiles, plan->d_apply_lists, plan->d_list_idx,
-                               boxes, P, reinterpret_cast<__half*>(d_out_f16), r->d_edge, r->d_edge_off);
-        else
-            hipLaunchKernelGGL(k_pixel_tail<false>, dim3(r->n_tail_tiles), dim3(kTailLanes), 0, s, d, r->d_tail_tiles, (const ApplyList*)nullptr,
-                               (const int32_t*)nullptr, boxes, P, reinterpret_cast<__half*>(d_out_f16), r->d_edge, r->d_edge_off);
-        hipLaunchKernelGGL(k_tail_edges, dim3((uint32_t)out_h, n), dim3(64), 0, s, r->d_dims, r->d_mcu_px_h, C, boxes, P, r->d_edge, r->d_edge_off,
+        auto* kernel = plan->n_apply ? (C == 1 ? k_pixel_tail<true, true> : k_pixel_tail<true, false>) : (C == 1 ? k_pixel_tail<false, true> : k_pixel_tail<false, false>);
+        hipLaunchKernelGGL(kernel, dim3(r->n_tail_tiles), dim3(kTailLanes), r->tail_lds, s, d, r->d_tail_tiles, plan->n_apply ? (const ApplyList*)plan->d_apply_lists : nullptr,
+                           plan->n_apply ? (const int32_t*)plan->d_list_idx : nullptr, boxes, P, reinterpret_cast<__half*>(d_out_f16), r->d_edge, r->d_edge_off);
+        if (r->tail_rows > 1)
+            hipLaunchKernelGGL(k_tail_edges, dim3(r->tail_rows - 1, n), dim3(64), 0, s, r->d_dims, r->d_mcu_px_h, (uint32_t)C, boxes, P, r->d_edge, r->d_edge_off,
                            reinterpret_cast<__half*>(d_out_f16));
         mark(r, PCR_STAGE_PIXEL, s);
         call_end(r);

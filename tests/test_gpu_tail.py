@@ -205,6 +205,35 @@ def test_decode_and_tail_in_one_kernel_equals_the_two_calls(rgb_small, gray64):
         r.decode_crop_batch(1, tb, 8, 8, MEAN, ISTD, pixels=work)                 # the two-kernel form of the same call
 
 
+@pytest.mark.parametrize("C,hs,vs,per,px", [(3, 2, 2, 21, 16), (3, 1, 1, 42, 8), (3, 2, 1, 30, 16), (1, 1, 1, 121, 8)])
+def test_runs_of_the_fused_tail_at_their_ends(C, hs, vs, per, px):
+    """A run of the fused kernel holds `per` MCUs of `px` columns and serves all but its last one; runs begin at the box's first MCU.
+    Boxes of exactly the columns one, two and three runs serve, one more and one less, from the first and a later MCU and from columns
+    inside one; strong reduction and enlargement, one output row, one column; pictures of one MCU beside wide ones."""
+    torch = _torch()
+    served = (per - 1) * px
+    W = 2 * served + px + 5
+    files = [pcrgen.make_jpeg(950 + i, 1, w, h, C, 7.0, hs, vs, 88) for i, (w, h) in enumerate([(W, 19), (W, 50), (px, 9), (W - 7, 33)])]
+    shapes = [(W, 19), (W, 50), (px, 9), (W - 7, 33)]
+    rec = pcrgen.write_record(files)
+    mean, istd = (MEAN, ISTD) if C == 3 else (MEAN[:1], ISTD[:1])
+    with pkg.pcr_open(rec, 0) as r:
+        rng = np.random.default_rng(C * 100 + per)
+        for t, (x0, w) in enumerate([(0, served), (0, served + 1), (0, served + px), (0, served + px + 1), (0, 2 * served + px), (px, served + px - 1),
+                                     (5, served - 5), (5, served - 4), (px + 3, 2 * served), (0, W)]):
+            boxes = []
+            for i, (iw, ih) in enumerate(shapes):
+                h = int(rng.integers(1, ih + 1))
+                boxes.append((min(x0, iw - 1), int(rng.integers(0, ih - h + 1)), max(1, min(w, iw - x0)), h, (i + t) & 1))
+            tb = torch.tensor(boxes, dtype=torch.int32, device="cuda")
+            for oh, ow in ((1, 130), (70, 1), (9, 33), (130, 64)):
+                for k in (1, r.G):
+                    want = r.crop_resize_batch(r.decode_batch(k), tb, oh, ow, mean, istd)
+                    got = torch.full_like(want, 9.0)
+                    r.decode_crop_batch(k, tb, oh, ow, mean, istd, pixels=None, out=got)
+                    assert torch.equal(got, want), (t, oh, ow, k, int((got != want).sum()))
+
+
 def test_tail_argument_errors(gray64):
     torch = _torch()
     g = [pcrgen.make_jpeg(i, 0, 40, 24, 1, 8.0, 1, 1, 90) for i in range(2)]
