@@ -108,6 +108,57 @@ private:
     }
 };
 
+// A launch of first scans by wavefronts, and whether k_first_split -- many lanes for every unit -- goes ahead of it.
+//
+// The wavefronts take as long as the longest unit, 7.5 ns a bit and 60 a block of an AC scan, 75 a block of a DC scan, and more
+// with many of them; the lanes some 35 us, what a DC scan takes to fall into step (longest where its MCUs have many blocks),
+// and what the workgroups cost that find no room at once.  us a call of plain records, wavefronts / lanes:
+//                                          one picture     32            256           1024
+//   4:2:0, quality 90, noisy, scan group 5
+//      64 x 64                              94 / 90      101 / 103     105 / 115     134 / 222
+//      100 x 100                           148 / 101     162 / 142     176 / 174     219 / 292
+//      128 x 128                           196 / 130     214 / 151     231 / 190     278 / 321
+//   the same at 2, 128 x 128               125 / 129     126 / 148     143 / 184     190 / 254
+//   less noise, at 5, 256 x 256            299 / 161     334 / 200     386 / 307     506 / 500
+//   quality 75, smooth, at 5, 256 x 256    174 / 165     187 / 273     237 / 274     356 / 458
+//      400 x 400                           340 / 155     352 / 208     435 / 301
+//      700 x 700                           899 / 166     947 / 252
+//   4:4:4, quality 95, at 5, 200 x 200     873 / 237     921 / 270    1012 / 377    1124 / 728
+//   gray, at 3, 300 x 300                  658 / 107     717 / 122     774 / 168
+//   scan group 1: 4:2:0 256 x 256          174 / 154     181 / 189     186 / 258     246 / 300
+//      400 x 400                           332 / 139     339 / 172     365 / 240
+//   4:4:4 200 x 200                        222 / 101     230 / 150     245 / 162     289 / 187
+//   gray 300 x 300                         190 / 77      200 / 99      207 / 104
+// 1024 lanes a unit instead of 256 are better only for very long units: 1000 x 1000 at quality 90, noisy, scan group 5 401 / 673 us a
+// call (8264 by wavefronts), 32 of them 491 / 801; 4:4:4 200 x 200 as above 243 / 237.
+struct FirstSplitLaunch {
+    uint32_t units = 0, ac_bits = 0, ac_blocks = 0, dc_units = 0, dc_blocks = 0, dc_per_mcu = 0;      // bits, blocks: of the longest unit
+    uint64_t ac_visits = 0, dc_visits = 0;                    // blocks of all units
+    void add(const ImgDesc& img, const ScanDesc& sd, uint32_t count) {
+        if (sd.Ah != 0 || is_sequential_scan(sd) || count == 0) return;
+        uint32_t per_mcu = sd.ns > 1 ? 0u : 1u;
+        for (int j = 0; j < sd.ns && sd.ns > 1; j++) per_mcu += (uint32_t)img.hs[sd.comp[j]] * img.vs[sd.comp[j]];
+        const uint32_t blocks = (uint32_t)((uint64_t)sd.mcus * per_mcu / count);
+        if (sd.Ss > 0) {
+            units += count; ac_visits += (uint64_t)sd.mcus;
+            ac_bits = std::max(ac_bits, (uint32_t)((uint64_t)sd.data_len * 8 / count)); ac_blocks = std::max(ac_blocks, blocks);
+        } else {
+            dc_units += count; dc_visits += (uint64_t)sd.mcus * per_mcu;
+            dc_blocks = std::max(dc_blocks, blocks); dc_per_mcu = std::max(dc_per_mcu, per_mcu);
+        }
+    }
+    // with_dc: the DC scans are part of the launch
+    bool pays(bool with_dc) const {
+        const float n = (float)(units + (with_dc ? dc_units : 0u)), dc = with_dc ? (float)dc_blocks : 0.f, seen = (float)ac_visits + (with_dc ? (float)dc_visits : 0.f);
+        if (n == 0.f) return false;
+        const float in_step = dc_per_mcu > 3 ? 120.f : (dc_per_mcu > 1 ? 60.f : 30.f);
+        const float waves = std::max(0.0075f * (float)ac_bits + 0.06f * (float)ac_blocks, 0.075f * dc) + 0.0001f * (float)ac_visits + (with_dc ? 0.00004f * (float)dc_visits : 0.f);
+        const float lanes = 35.f + std::max(std::min(in_step, 0.1f * dc), 0.0008f * (float)ac_bits) + 0.028f * n + 0.00004f * seen;
+        return lanes < waves;
+    }
+    bool wide(bool with_dc) const { return units + (with_dc ? dc_units : 0u) <= 512 && ac_bits >= 131072; }
+};
+
 // A launch of DC first scans, and whether it goes to the lane decoders instead of to a wavefront per unit.
 //
 // A lane decodes a DC symbol with a fifth of the instructions a wavefront spends on it, but a launch of lanes takes as long as

@@ -1115,9 +1115,10 @@ PCR_D __attribute__((always_inline)) void wave_unit(const DevRecord& R, const Un
 }
 template <int ROLES, bool FOLLOW>
 __global__ void __launch_bounds__(kEntropyLanes * kChainWaves) k_decode_waves(DevRecord R, const Unit* __restrict__ units, const UnitChain* __restrict__ chains,
-        const uint32_t* __restrict__ clean32, uint32_t to_planes) {
+        const uint32_t* __restrict__ clean32, uint32_t to_planes, const uint32_t* __restrict__ had) {
     extern __shared__ uint4 wave_tabs[];
     __shared__ uint32_t done[kChainWaves];
+    if (!FOLLOW && had && had[blockIdx.x]) return;            // (the many lanes of k_first_split have dealt with it)
     const uint32_t wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
     UnitChain ch{blockIdx.x, 1, 0};
     if (chains) ch = chains[blockIdx.x];

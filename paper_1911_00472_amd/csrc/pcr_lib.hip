@@ -21,6 +21,7 @@
 #include "pcr_chains.h"
 #include "pcr_kernels.h"
 #include "pcr_sequential.h"
+#include "pcr_first_split.h"
 #include "pcr_hist.h"
 #include "pcr_coder.h"
 #include "pcr_similarity.h"
@@ -45,12 +46,15 @@ struct LevelList {
     DcLaunch dc;                                                                 // DC first scans: what decides between lanes and wavefronts
     uint32_t* d_dc_starts = nullptr; uint32_t n_dc_waves = 0;                    // ... wavefronts of lanes, and where they begin if their MCUs are of several shapes
     bool chained = false;                                                        // the plan's chains hold these units too
+    FirstSplitLaunch split;                                                      // DC first scans: what decides whether k_first_split goes ahead (d_done: what it has dealt with)
 };
 
 struct Plan {                               // launch geometry for one scan group k
     std::vector<LevelList> levels;
     // the scans decoded side by side (k_decode_waves): AC chains first, the DC units (chains of one) behind them
     Unit* d_chain_units = nullptr; UnitChain* d_chains = nullptr; uint32_t n_ac_chains = 0, n_chains = 0, chain_waves = 0;
+    uint32_t* d_chain_done = nullptr;        // chains of one: which units k_first_split has dealt with
+    FirstSplitLaunch split;                  // ... and what decides whether it is launched
     LevelList refined;                       // the refinement scans among them, for k_refine_blocks
     bool chains_built = false;
     ApplyUnit* d_apply = nullptr; ApplyList* d_apply_lists = nullptr; int32_t* d_list_idx = nullptr; uint32_t n_apply = 0, apply_grid_x = 0;
@@ -297,10 +301,14 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
         if (set == &chains.ac) plan->n_ac_chains = (uint32_t)list.size();
     }
     plan->n_chains = (uint32_t)list.size();
+    if (plan->chain_waves == 1)
+        for (auto* set : {&chains.ac, &chains.dc})
+            for (const ScanChain& c : *set) plan->split.add(r->img[c.img], r->scan[(size_t)c.img * G + c.scan[0]], c.units);
     Uploads up(&r->big, &r->stage);
     if (plan->n_chains) { up.add(&plan->d_chain_units, units); up.add(&plan->d_chains, list); }
     if (!refined.empty()) refine_tiles(r, refined, &plan->refined, false, &up);
-    const int rc = up.flush();
+    int rc = up.flush();
+    if (!rc && (plan->split.pays(true) || plan->split.pays(false))) rc = arena_alloc(&r->big, &plan->d_chain_done, plan->n_chains);
     if (rc) return rc;
     plan->chains_built = true;
     return PCR_OK;
@@ -387,6 +395,8 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             });
             ll.n_dc_waves = starts.empty() ? (ll.n + kEntropyLanes - 1) / kEntropyLanes : (uint32_t)starts.size() - 1;
             if (!starts.empty()) up.add(&ll.d_dc_starts, starts);
+            for (const Run& q : rn) ll.split.add(r->img[q.img], r->scan[(size_t)q.img * G + q.scan], q.count);
+            if (ll.split.pays(true)) { const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc; }
         }
         for (size_t w0 = 0; w0 < rn.size() && ll.kind != kDcFirst; w0 += kLaneTabs) {
             const size_t w1 = std::min(rn.size(), w0 + kLaneTabs);
@@ -673,17 +683,26 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // (a launch of DC scans alone asks for their tables only: with an AC table's room each, the wavefronts of one record left
     // fewer to those of the others.  Four records of 1024 pictures of 256 x 256 without entry points at scan group 1:
     // 715 us a call with room for an AC table and the words of a stream, 655 with room for the DC tables; gray photographs 1470, 1405.)
+    // Long first scans by many lanes each, ahead of the wavefronts, which take what is left: null, or what is not.
+    auto split = [&](const FirstSplitLaunch& sp, bool with_dc, const Unit* units, uint32_t n_units, uint32_t* done) -> const uint32_t* {
+        if (!done || r->timing || r->lane_mode < 0 || !sp.pays(with_dc)) return nullptr;
+        if (sp.wide(with_dc)) hipLaunchKernelGGL(k_first_split<1024>, dim3(n_units), dim3(1024), 0, s, r->d, units, done, c32, dc_to_planes ? 1u : 0u);
+        else hipLaunchKernelGGL(k_first_split<256>, dim3(n_units), dim3(256), 0, s, r->d, units, done, c32, dc_to_planes ? 1u : 0u);
+        return done;
+    };
     auto waves = [&](const LevelList& l) {
         const bool dc = l.kind == kDcFirst;
+        const uint32_t* had = dc ? split(l.split, true, l.d_units, l.n, l.d_done) : nullptr;
         hipLaunchKernelGGL((dc ? k_decode_waves<kWavesDc, false> : k_decode_waves<kWavesAc, false>), dim3(l.n), dim3(kEntropyLanes), dc ? kWaveDcTabBytes : kWaveTabBytes, s, r->d, l.d_units,
-                           (const UnitChain*)nullptr, c32, dc_to_planes ? 1u : 0u);
+                           (const UnitChain*)nullptr, c32, dc_to_planes ? 1u : 0u, had);
     };
     if (side_by_side) {
+        const uint32_t* had = split(plan->split, dc_beside, plan->d_chain_units, dc_beside ? plan->n_chains : plan->n_ac_chains, plan->d_chain_done);   // (chains of one: unit u is chain u)
         const uint32_t w = plan->chain_waves;                // (chains of several scans are those in which some follow others)
         auto* kernel = w > 1 ? (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, true> : k_decode_waves<kWavesAc, true>)
                              : (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, false> : k_decode_waves<kWavesAc, false>);
         hipLaunchKernelGGL(kernel, dim3(dc_beside ? plan->n_chains : plan->n_ac_chains), dim3(kEntropyLanes * w), w * kWaveTabBytes, s, r->d,
-                           plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u);
+                           plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u, had);
         const LevelList& f = plan->refined;
         if (f.n_cov_tiles) hipLaunchKernelGGL(k_refine_blocks, dim3(f.n_cov_tiles), dim3(256), 0, s, r->d, f.d_refine, f.d_cov_tiles);
     }

@@ -1,0 +1,101 @@
+"""Long first scans decoded by many lanes each (k_first_split) against the oracle and the wavefront decoders (which
+set_lane_decoders(-1) keeps to): every sampling, scans of one piece and of thousands, streams that hardly fall into step (smooth pictures,
+one colour) and are left to the wavefronts, codes and runs of every length, restart intervals and entry points far apart, upgrades, damaged data."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1911_00472_amd as pkg
+import pcrgen
+
+pytestmark = pytest.mark.gpu
+
+
+def _both(rec, ks, check=()):
+    """Coefficients, pixels and status of the decoder the rule picks and of the wavefront decoders are the same; some images, the oracle's."""
+    with pkg.pcr_open(rec, 0) as r:
+        clay = r.coef_layout()
+        for k in ks:
+            got = []
+            for mode in (0, -1):
+                r.set_lane_decoders(mode)
+                st = torch.full((r.n,), 77, dtype=torch.int32, device="cuda")
+                pix = r.decode_batch(k, status=st).cpu().numpy().copy()
+                got.append((r.decode_coefficients(k).cpu().numpy().copy(), pix, st.cpu().numpy().copy()))
+            good = got[0][2] == 0
+            assert np.array_equal(got[0][2], got[1][2]), (k, got[0][2], got[1][2])
+            for i in np.flatnonzero(good):
+                a, b = int(clay[i]), int(clay[i + 1])
+                assert np.array_equal(got[0][0][a:b], got[1][0][a:b]), (k, i)
+            if good.all():
+                assert np.array_equal(got[0][1], got[1][1]), k
+            for i in check:
+                want, _, _ = oracle.decode_record_image(rec, i, k)
+                assert np.array_equal(got[0][0][int(clay[i]):int(clay[i + 1])], want), (k, i)
+        return got[0][2]
+
+
+@pytest.mark.parametrize("C,hs,vs", [(1, 1, 1), (3, 1, 1), (3, 2, 1), (3, 1, 2), (3, 2, 2)])
+@pytest.mark.parametrize("side", [40, 100, 257, 640])
+def test_every_sampling_and_size(C, hs, vs, side):
+    files = [pcrgen.make_jpeg(30 + side + i, i % 3, side, side + 7 * i, C, 3.0 + 12 * i, hs, vs, 80 + 6 * i) for i in range(3)]
+    st = _both(pcrgen.write_record(files), (1, 2, 3) if C == 1 else (1, 2, 3, 5), check=(0, 2))
+    assert (st == 0).all()
+
+
+def test_streams_that_hardly_fall_into_step():
+    flat = np.full((900, 900, 3), 90, np.uint8)
+    ramp = np.broadcast_to((np.arange(900, dtype=np.uint16)[:, None, None] // 4).astype(np.uint8), (900, 900, 3)).copy()
+    half = flat.copy()
+    half[:450] = np.random.default_rng(3).integers(0, 256, (450, 900, 3), dtype=np.uint8)
+    files = [pcrgen.encode_pixels(a, hs, hs, q) for a in (flat, ramp, half) for hs, q in ((2, 75), (1, 95))]
+    assert (_both(pcrgen.write_record(files), (1, 2, 5), check=(2, 5)) == 0).all()
+
+
+@pytest.mark.parametrize("n,side", [(70, 500), (300, 200)])
+def test_more_units_than_find_room_at_once(n, side):
+    files = [pcrgen.make_jpeg(500 + i, 1, side - 7 * i, side + i, 3, 20.0, 2 - i % 2, 2 - i % 2, 90) for i in range(5)]
+    assert (_both(pcrgen.write_record((files * n)[:n]), (1, 5), check=(0, 1)) == 0).all()
+
+
+def test_restart_intervals_and_entry_points_far_apart():
+    files = [pcrgen.make_jpeg(610 + i, 1, 700, 500, 3, 15.0, 2, 2, 90, restart=12 if i % 2 else 0) for i in range(4)]
+    assert (_both(pcrgen.write_record(files), (1, 5), check=(0, 1)) == 0).all()
+    assert (_both(pkg.record_write_indexed(files, None, 4096), (1, 2, 5), check=(0, 1)) == 0).all()
+
+
+def test_one_long_scan_takes_a_thousand_lanes():
+    files = [pcrgen.make_jpeg(640, 2, 1100, 1000, 3, 30.0, 1, 1, 97)]
+    assert (_both(pcrgen.write_record(files), (1, 4, 5), check=(0,)) == 0).all()
+
+
+def test_upgrades_start_from_what_it_left():
+    rec = pcrgen.write_record([pcrgen.make_jpeg(660 + i, 1, 300 + 20 * i, 280, 3, 18.0, 2, 2, 90) for i in range(3)])
+    with pkg.pcr_open(rec, 0) as r:
+        for k0, k in ((1, 2), (1, 5), (2, 5), (3, 10), (5, 7)):
+            r.decode_batch(k0)
+            got = r.upgrade_batch(k).cpu().numpy().copy()
+            assert np.array_equal(got, r.decode_batch(k).cpu().numpy()), (k0, k)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_damaged_data_flag_the_same_images(seed):
+    """Bytes changed, dropped and put in behind the first scans' headers; scans cut short; both decoders flag the same images and
+    agree on the others."""
+    rng = np.random.default_rng(70 + seed)
+    files = []
+    for i in range(8):
+        f = bytearray(pcrgen.make_jpeg(680 + i, 1, 260, 200 + 11 * i, 3, 20.0, 2 - i % 2, 2 - i % 2, 90))
+        ends = pcrgen.split_scans(bytes(f))
+        g = int(rng.integers(0, 5))
+        at = int(rng.integers(ends[g] - (ends[g] - (ends[g - 1] if g else 0)) // 3, ends[g] - 4))
+        kind = (i + seed) % 4
+        if kind == 0:
+            f[at] = f[at] ^ 0x55 if f[at] not in (0xFF, 0xAA) and f[at - 1] != 0xFF else f[at]
+        elif kind == 1:
+            del f[at:ends[g]]
+        elif kind == 2:
+            f[at:at] = bytes(rng.integers(0, 255, 9, dtype=np.uint8))
+        files.append(bytes(f))
+    _both(pcrgen.write_record(files), (1, 2, 5))
