@@ -55,7 +55,7 @@ struct Plan {                               // launch geometry for one scan grou
     Unit* d_chain_units = nullptr; UnitChain* d_chains = nullptr; uint32_t n_ac_chains = 0, n_chains = 0, chain_waves = 0;
     uint32_t* d_chain_done = nullptr;        // chains of one: which units k_first_split has dealt with
     FirstSplitLaunch split;                  // ... and what decides whether it is launched
-    LevelList refined;                       // the refinement scans among them, for k_refine_blocks
+    LevelList refined;                       // all refinement scans of the call, for k_refine_blocks
     bool chains_built = false;
     ApplyUnit* d_apply = nullptr; ApplyList* d_apply_lists = nullptr; int32_t* d_list_idx = nullptr; uint32_t n_apply = 0, apply_grid_x = 0;
     bool has_ac = false;                     // some scan <= k is an AC scan (else only element 0 of every block is ever touched)
@@ -277,11 +277,15 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
         const uint32_t upto = std::min<uint32_t>(r->img[i].nscans, (uint32_t)k);
         const size_t at = (size_t)i * G;
         chains.add(i, &r->scan[at], &r->slot_cnt[at], &r->ent_off_h[at], (uint32_t)k0, upto);
-        for (uint32_t g = (uint32_t)k0; g < upto; g++) if (r->scan[at + g].Ss > 0 && r->scan[at + g].Ah > 0) refined.push_back(RefineScan{i, g});
+    }
+    for (uint32_t i = 0; i < n; i++) {
+        const size_t at = (size_t)i * G;
+        for (uint32_t g = (uint32_t)k0; g < std::min<uint32_t>(r->img[i].nscans, (uint32_t)k); g++)
+            if (r->scan[at + g].Ss > 0 && r->scan[at + g].Ah > 0) refined.push_back(RefineScan{i, g});
     }
     const bool in_step = chains.possible;
     if (!in_step) {                                          // the refinement scans follow level by level
-        chains = ChainSet(); refined.clear();
+        chains = ChainSet();
         for (uint32_t i = 0; i < n; i++) {
             const size_t at = (size_t)i * G;
             chains.add_level_one(i, &r->scan[at], &r->level[at], &r->slot_cnt[at], (uint32_t)k0, std::min<uint32_t>(r->img[i].nscans, (uint32_t)k));
@@ -703,8 +707,6 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
                              : (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, false> : k_decode_waves<kWavesAc, false>);
         hipLaunchKernelGGL(kernel, dim3(dc_beside ? plan->n_chains : plan->n_ac_chains), dim3(kEntropyLanes * w), w * kWaveTabBytes, s, r->d,
                            plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u, had);
-        const LevelList& f = plan->refined;
-        if (f.n_cov_tiles) hipLaunchKernelGGL(k_refine_blocks, dim3(f.n_cov_tiles), dim3(256), 0, s, r->d, f.d_refine, f.d_cov_tiles);
     }
     for (size_t li = 0; li < plan->levels.size(); li++) {
         auto& l = plan->levels[li];
@@ -740,10 +742,15 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         else {
             waves(l);
             mark(r, PCR_STAGE_AC_REFINE, s);
-            if (l.n_cov_tiles) hipLaunchKernelGGL(k_refine_blocks, dim3(l.n_cov_tiles), dim3(256), 0, s, r->d, l.d_refine, l.d_cov_tiles);
+            if (l.n_cov_tiles && !side_by_side) hipLaunchKernelGGL(k_refine_blocks, dim3(l.n_cov_tiles), dim3(256), 0, s, r->d, l.d_refine, l.d_cov_tiles);
             mark(r, PCR_STAGE_REFINE_BLOCKS, s);
         }
     }
+    // The blocks of all refinement scans the wavefronts have walked, in one launch: of an earlier refinement scan a later one needs
+    // what the wavefronts themselves leave (kRefNz, kRefHist).  (A launch behind every level held up the next one: 256 pictures
+    // of 17 to 320 pixels with entry points at scan group 10 358 us a call with two launches of 26, 345 with one.)
+    if (side_by_side && plan->refined.n_cov_tiles)
+        hipLaunchKernelGGL(k_refine_blocks, dim3(plan->refined.n_cov_tiles), dim3(256), 0, s, r->d, plan->refined.d_refine, plan->refined.d_cov_tiles);
     if (plan->n_apply) {
         if (r->timing) hipLaunchKernelGGL(k_apply_prep, dim3(list_groups), dim3(64 * kApplyPrepWaves), 0, s, r->d, lists);
         if (refine_in_memory)

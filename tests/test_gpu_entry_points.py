@@ -39,6 +39,23 @@ def test_mixed_files_every_scan_group_and_interval():
                 assert torch.equal(r.decode_batch(k), want[k])
 
 
+@pytest.mark.parametrize("k0, k", [(0, 7), (0, 10), (1, 9), (5, 10), (6, 10), (9, 10)])
+def test_refinement_levels_by_wavefronts(k0, k):
+    """One launch decodes the blocks of all refinement scans the wavefronts have walked, whatever levels they are of: the same bytes
+    as by the lane decoders, which go level by level, from scratch and as an upgrade."""
+    torch = _torch()
+    with pkg.pcr_open(pkg.record_write_indexed(_files(), None, 16), 0) as r:
+        out = []
+        for mode in (-1, 1):
+            r.set_lane_decoders(mode)
+            if k0:
+                r.decode_batch(k0)
+            st = torch.full((r.n,), 77, dtype=torch.int32, device="cuda")
+            out.append(r.upgrade_batch(k, status=st).clone() if k0 else r.decode_batch(k, status=st).clone())
+            assert (st.cpu().numpy() == 0).all()
+        assert torch.equal(*out)
+
+
 def test_baseline_files_with_entries():
     files = [pcrgen.encode_pixels(pcrgen.synth(700 + i, 1 + (i % 2), w, h, c, 8.0), hs, vs, q, "sequential", restart=0)
              for i, (w, h, c, hs, vs, q) in enumerate([(333, 211, 3, 2, 2, 95), (64, 64, 1, 1, 1, 85), (129, 165, 3, 1, 1, 90), (140, 200, 3, 2, 1, 75),
