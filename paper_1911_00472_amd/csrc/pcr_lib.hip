@@ -952,10 +952,20 @@ static int validate_index(const uint8_t* hdr, const RecordHeader& h, std::vector
     return PCR_OK;
 }
 
+// What a bind clears, one launch of it.  (ptr: of an arena, whose pieces are rounded up to more than 16 bytes.)
+static void add_fill(BindFill* F, void* ptr, size_t bytes, uint32_t word) { F->p[F->count] = (uint4*)ptr; F->n16[F->count] = (bytes + 15) / 16; F->word[F->count++] = word; }
+static int launch_fill(const BindFill& F, hipStream_t s) {
+    size_t most = 0;
+    for (uint32_t f = 0; f < F.count; f++) most = std::max<size_t>(most, F.n16[f]);
+    const uint32_t groups = (uint32_t)std::min<size_t>(2048, (most + 1023) / 1024 + 1);       // (four pieces a lane)
+    hipLaunchKernelGGL(k_bind_fill, dim3(groups), dim3(256), 0, s, F);
+    return hipGetLastError() == hipSuccess ? PCR_OK : PCR_E_DEVICE;
+}
+
 // Everything after the image/scan descriptors are known (r->img, r->scan filled, r->d.rec set):
 // dependency levels, buffer layout, the buffers themselves (out of r->big), their initial contents.
-// Fills are enqueued on s; the caller synchronises s before anything else uses the handle.
-static int finish_open(pcr_record* r, hipStream_t s) {
+// Fills are enqueued on s, with those in `fill` in one launch; the caller synchronises s before anything else uses the handle.
+static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
     const uint32_t n = r->hdr.n, G = r->hdr.G;
     const size_t nbytes = r->nbytes;
     for (uint32_t i = 0; i < n; i++) if (r->img[i].status != kOk) return r->img[i].status;
@@ -1064,15 +1074,18 @@ static int finish_open(pcr_record* r, hipStream_t s) {
     d.ent_off = d_ent_off;
     d.tab_idx = d_tab_idx;
     d.coef_off = d_coef_off; d.out_off = d_out_off; d.mask_off = d_mask_off; d.slot_base = d_sb; d.slot_cnt = d_sc;
-    if (!rc && hipMemsetAsync(d.clean, 0xFF, padded, s) != hipSuccess) rc = PCR_E_DEVICE;
     // (the refinement records need no initial contents: every word a kernel reads was written earlier in the same
     // call, or by the call an upgrade builds on; consumers skip blocks outside the scans' own grids)
-    if (!rc && hipMemsetAsync(d.ivl_start, 0, (ns ? ns : 1) * sizeof(uint32_t), s) != hipSuccess) rc = PCR_E_DEVICE;
+    if (!rc) {
+        add_fill(&fill, d.clean, padded, 0xFFFFFFFFu);
+        add_fill(&fill, d.ivl_start, (ns ? ns : 1) * sizeof(uint32_t), 0);
+        rc = launch_fill(fill, s);
+    }
     return rc;
 }
 
-// Buffers the index and parse kernels write (out of r->small); needed before the descriptors exist.
-static int alloc_descriptor_buffers(pcr_record* r, hipStream_t s) {
+// Buffers the index and parse kernels write (out of r->small); needed before the descriptors exist.  *fill: what is to be cleared.
+static int alloc_descriptor_buffers(pcr_record* r, BindFill* fill) {
     const uint32_t n = r->hdr.n, G = r->hdr.G;
     DevRecord& d = r->d;
     const size_t ng = (size_t)G * n;
@@ -1082,9 +1095,7 @@ static int alloc_descriptor_buffers(pcr_record* r, hipStream_t s) {
     if (!rc) rc = arena_alloc(&r->small, &d.img, n);
     if (!rc) rc = arena_alloc(&r->small, &d.scan, ng);
     if (!rc) rc = arena_alloc(&r->small, &d.status, n);
-    if (!rc && hipMemsetAsync(d.off, 0, ng * sizeof(uint32_t), s) != hipSuccess) rc = PCR_E_DEVICE;
-    if (!rc && hipMemsetAsync(d.scan, 0, ng * sizeof(ScanDesc), s) != hipSuccess) rc = PCR_E_DEVICE;
-    if (!rc && hipMemsetAsync(d.img, 0, (size_t)n * sizeof(ImgDesc), s) != hipSuccess) rc = PCR_E_DEVICE;
+    if (!rc) { add_fill(fill, d.off, ng * sizeof(uint32_t), 0); add_fill(fill, d.scan, ng * sizeof(ScanDesc), 0); add_fill(fill, d.img, (size_t)n * sizeof(ImgDesc), 0); }
     d.n = n; d.G = G; d.nbytes = r->nbytes;
     d.len = (const uint32_t*)(d.rec + hdr_len_pos(n, G, 0, 0));
     d.nscans = (const uint32_t*)(d.rec + hdr_nscans_pos(n, G, 0));
@@ -1152,9 +1163,9 @@ int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out)
     if (!rc) rc = parse_on_host(r, bytes, off, len, nsc);
     if (!rc && hipMalloc((void**)&r->d_rec, nbytes + 64) != hipSuccess) { (void)hipGetLastError(); rc = PCR_E_NOMEM; }
     if (!rc && hipMemcpy(r->d_rec, bytes, nbytes, hipMemcpyHostToDevice) != hipSuccess) rc = PCR_E_DEVICE;
-    if (!rc && hipMemset(r->d_rec + nbytes, 0, 64) != hipSuccess) rc = PCR_E_DEVICE;
-    if (!rc) { r->d.rec = r->d_rec; rc = alloc_descriptor_buffers(r, nullptr); }
-    if (!rc) rc = finish_open(r, nullptr);
+    BindFill fill{};
+    if (!rc) { r->d.rec = r->d_rec; fill.tail = r->d_rec + nbytes; rc = alloc_descriptor_buffers(r, &fill); }
+    if (!rc) rc = finish_open(r, fill, nullptr);
     if (!rc) measure_units(r, bytes, nbytes);
     if (!rc && hipStreamSynchronize(nullptr) != hipSuccess) rc = PCR_E_DEVICE;
     if (rc) { (void)hipGetLastError(); pcr_close(r); return rc; }
@@ -1166,8 +1177,8 @@ int pcr_open(const void* bytes_, size_t nbytes, int device_id, pcr_record** out)
 // Binds handle r (fresh, or one whose earlier work has finished) to record bytes in device memory.  Without a host copy of
 // them (host null): header checks on the host, index and marker parse ON THE DEVICE, and only the small descriptor tables
 // come back.  With one, everything is read from it, while the bytes may still be on their way to the device (enqueued on s
-// before).  Then the buffer layout.  Everything is enqueued on s, which is synchronised before returning.  On failure the
-// handle holds no record (pcr_close is all that may follow).
+// before), and 64 bytes behind them are cleared.  Then the buffer layout.  Everything is enqueued on s, which is synchronised
+// before returning.  On failure the handle holds no record (pcr_close is all that may follow).
 static int bind_bytes(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s);
 static int bind_device(pcr_record* r, const void* d_bytes, size_t nbytes, const uint8_t* host, hipStream_t s) {
     auto holds_nothing = [&]() {                             // until the bind succeeds: no images, and layouts of no images
@@ -1212,12 +1223,17 @@ static int bind_bytes(pcr_record* r, const void* d_bytes, size_t nbytes, const u
     rc = validate_index(r->header.data(), h, &off, &len, &nsc);
     if (rc) return rc;
     r->d.rec = (const uint8_t*)d_bytes;
-    rc = alloc_descriptor_buffers(r, s);
+    BindFill fill{};
+    rc = alloc_descriptor_buffers(r, &fill);
     if (rc) return rc;
     if (host) {
+        fill.tail = (uint8_t*)d_bytes + nbytes;              // (a loader's own buffer)
         rc = parse_on_host(r, host, off, len, nsc);
         if (rc) return rc;
     } else {
+        rc = launch_fill(fill, s);
+        if (rc) return rc;
+        fill = BindFill{};
         launch_headers(r, h.k_avail, false, h.k_avail, false, s);          // (no tables: where they go is not laid out yet)
         r->img.resize(n); r->scan.resize((size_t)n * G);
         HIP_TRY(hipMemcpyAsync(r->img.data(), r->d.img, n * sizeof(ImgDesc), hipMemcpyDeviceToHost, s));
@@ -1225,7 +1241,7 @@ static int bind_bytes(pcr_record* r, const void* d_bytes, size_t nbytes, const u
         HIP_TRY(hipStreamSynchronize(s));
     }
     // (the units are not measured: ordering them takes longer than it saves where a record is decoded once)
-    return finish_open(r, s);
+    return finish_open(r, fill, s);
 }
 
 static int check_device_bytes(const void* d_bytes, size_t nbytes, int* device) {
@@ -1994,7 +2010,6 @@ int pcr_loader_upload(pcr_loader* ld, int slot, size_t nbytes, pcr_record** rec)
     HIP_TRY(hipStreamSynchronize(sl->stream));                // the slot's buffers and handle are free again
     loader_take_tokens(ld, (double)nbytes);
     HIP_TRY(hipMemcpyAsync(sl->dev, sl->host, nbytes, hipMemcpyHostToDevice, sl->stream));
-    HIP_TRY(hipMemsetAsync(sl->dev + nbytes, 0, 64, sl->stream));
     // (the handle is laid out from the host's bytes while the copy runs; bind_device waits for the copy)
     const bool fresh = !sl->rec;
     if (fresh) {

@@ -161,6 +161,26 @@ def test_loader_to_training_tensors():
             assert torch.equal(out, want)
 
 
+def test_one_slot_takes_records_of_every_length():
+    """What a bind clears (the units' starts, the descriptors, the bytes behind the record) is cleared for records that end anywhere
+    in a 16-byte piece, in buffers that held a longer or shorter one before."""
+    files = [pcrgen.make_jpeg(40 + i, 1 + (i % 2), 9 + 11 * (i % 5), 8 + 7 * (i % 4), 3, 6.0, 2, 2, 90, restart=int(i % 3 == 2)) for i in range(8)]
+    recs = [pcrgen.write_record([files[(i + j) % 8] for j in range(1 + (5 * i) // 3 % 5)]) for i in range(24)]
+    assert len({len(r) % 16 for r in recs}) >= 8
+    torch = _torch()
+    with pkg.Loader(1, max(len(r) for r in recs)) as ld:
+        for i, rec in enumerate(recs):
+            k = 1 + i % 10
+            want, st, lay = _fresh(rec, k)
+            ld.staging(0)[:] = 0xD9
+            ld.staging(0)[:len(rec)] = np.frombuffer(rec, np.uint8)
+            h = ld.upload(0, len(rec))
+            out, got = torch.empty(int(lay[-1]), dtype=torch.uint8, device="cuda"), torch.full((h.n,), 77, dtype=torch.int32, device="cuda")
+            ld.decode(0, k, out, got)
+            ld.wait(0)
+            assert np.array_equal(out.cpu().numpy(), want) and np.array_equal(got.cpu().numpy(), st), (i, len(rec), k)
+
+
 def test_loader_rate_limit_and_errors():
     torch = _torch()
     gray, _ = pcrgen.make_workload("gray64")
