@@ -403,12 +403,13 @@ int pcr_transcode_batch(pcr_record* rec, const void* const* files, const size_t*
  * (restart intervals, entry-point units); a launch either gives every unit a wavefront that decodes it on the scalar
  * unit, or every unit a lane (64 units per wavefront).  Lanes need a fifth of the instructions but take longer per unit:
  * they win when the GPU is shared between the decodes of several records, or when a launch has very many units.
- * mode 0 (default): lanes for AC launches of at least 8192 units if the process has more than one record open, of at
- * least 32768 units otherwise.  DC first scans share the launch of AC first scans that go to the lanes; by themselves they go
- * there by the number of their units, a launch with some much longer than others counting as the fewer that many of its longest
- * would be: from 8192 on where wavefronts would decode them in the launch of the AC scans, and from 6144 where not (whole scans of
- * 64 to 768 blocks: 3584 or 4608).  If the process has more than one record open, from 4096 units on that count as 2000 at least
- * (3000, if the longest has more than 768 blocks).
+ * mode 0 (default): lanes for AC launches whose units are many against the longest of them (and, where that is close or the units are of
+ * more than a hundred blocks, from 8192 units on if the process has more than one record open and from 32768 otherwise).
+ * DC first scans share the launch of AC first scans that go to the lanes; by themselves they go there by the number of their
+ * units, a launch with some much longer than others counting as the fewer that many of its longest would be: from 8192 on where
+ * wavefronts would decode them in the launch of the AC scans, and from 6144 where not (whole scans of 64 to 768 blocks: 3584 or
+ * 4608).  If the process has more than one record open, from 4096 units on that count as 2000 at least (3000, if the longest
+ * has more than 768 blocks).
  * 1: lanes wherever the kernels exist and the record's scans have several units; -1: never.
  * The results are the same bit for bit.  Takes effect from the next decode call.  PCR_E_ARG: null handle or another
  * mode. */

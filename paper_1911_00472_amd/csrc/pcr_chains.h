@@ -209,6 +209,51 @@ struct DcLaunch {
     }
 };
 
+// A launch of AC scans (first scans, or refinement scans of one level) of records with several units a scan, and whether a lane
+// decodes a unit, 64 of them a wavefront, or a wavefront does.
+//
+// Wavefronts are bound by the scalar instructions of all units, lanes by the symbols of the longest unit one after the other, with a
+// fifth of the instructions in total.  What decides is the launch's bits and blocks against those of its longest unit: the figures
+// below are a fit (non-negative, of the difference) to what calls of 49 sizes of one record took at three or four scan groups
+// each.  us a call by wavefronts / by lanes, one record open (units of the launch of first scans, thousands):
+//                                              scan group 2             5                       6                       10
+//   340 x 340, quality 90, noisy, entries 64   5.6  193 / 186    14  243 / 325     421 / 598      715 / 1004
+//                                             11    275 / 222    29  382 / 370     718 / 706     1267 / 1214
+//                                             22    467 / 313    57  689 / 488    1308 / 844     2359 / 1394
+//   the same at quality 85, entries 32         4.8  135 / 123    12  150 / 146     231 / 250      364 / 413
+//                                             11    183 / 151    28  218 / 170     363 / 287      625 / 474
+//                                             22    267 / 182    56  337 / 202     619 / 347     1114 / 559
+//   700 x 700, quality 80, entries 64          5.4  180 / 166    12  199 / 175     313 / 308      530 / 554
+//                                             11    245 / 198    25  260 / 207     470 / 363      861 / 630
+//   340 x 340, 4:4:4, quality 88, entries 64   5.6  223 / 193    22  303 / 286     462 / 496      993 / 1021
+//                                             11    353 / 255    45  570 / 376     858 / 682     1895 / 1306
+//   128 x 128, quality 85, entries 64          2.3  142 / 161     6  170 / 192     254 / 374      410 / 683
+//                                              5.5  198 / 178    14  238 / 224     395 / 418      693 / 763
+// A record decoded beside others leaves them what it does not use, in part (they share hardware queues): its own work counts half as
+// much again.  (Over 50 sizes of two and four records that loses 1 % against the better of the two, counted as often as there are
+// records 3 to 5 %.)  Where the fit says less than its error, and for units of more than a hundred blocks, their number decides:
+// 8192 with others open and 32768 without; so it does for refinement scans whose wavefronts of lanes would be a quarter empty (2048
+// pictures of 82 x 120 at scan group 7: 481 us a call with those by wavefronts, 535 by lanes).
+struct LanesLaunch {
+    uint32_t units = 0, jobs = 0, longest_bits = 0, longest_blocks = 0;      // of the scan whose units are longest on average
+    uint64_t bits = 0, blocks = 0;
+    void add(const ScanDesc& sd, uint32_t n) {
+        if (n == 0) return;
+        units += n; bits += (uint64_t)sd.data_len * 8; blocks += sd.mcus;
+        longest_bits = std::max(longest_bits, (uint32_t)((uint64_t)sd.data_len * 8 / n)); longest_blocks = std::max(longest_blocks, sd.mcus / n);
+    }
+    bool many(bool several) const { return units >= (several ? 8192u : 32768u) && units >= 32u * jobs; }     // (jobs half full at least)
+    bool by_lanes(bool refine, bool several) const {
+        const bool many = this->many(several);
+        if (blocks > 100ull * units || (refine && units < 50u * jobs)) return many;
+        const float much = several ? 1.5f : 1.f, mbit = much * (float)bits * 1e-6f, kblk = much * (float)blocks * 1e-3f;
+        const float gain = refine ? 1.2f * mbit + 0.22f * kblk - 0.058f * (float)longest_bits - 1.1f * (float)longest_blocks - 10.f
+                                  : 1.75f * mbit + 0.064f * kblk - 0.041f * (float)longest_bits - 0.029f * (float)longest_blocks - 0.011f * much * (float)jobs + 15.f;
+        const float unsure = several ? 30.f : (refine ? 25.f : 12.f);
+        return gain > (many ? -unsure : unsure);
+    }
+};
+
 // The MCUs of a DC scan, as far as lanes that decode them in step have to agree on them.
 inline uint32_t dc_mcu_shape(const ImgDesc& img, const ScanDesc& sd) {
     uint32_t f[2 * kMaxComp] = {1, 1, 1, 1, 1, 1};

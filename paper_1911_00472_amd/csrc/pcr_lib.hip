@@ -46,6 +46,7 @@ struct LevelList {
     DcLaunch dc;                                                                 // DC first scans: what decides between lanes and wavefronts
     uint32_t* d_dc_starts = nullptr; uint32_t n_dc_waves = 0;                    // ... wavefronts of lanes, and where they begin if their MCUs are of several shapes
     bool chained = false;                                                        // the plan's chains hold these units too
+    LanesLaunch lanes;                                                           // AC scans: what decides between lanes and wavefronts
     FirstSplitLaunch split;                                                      // DC first scans: what decides whether k_first_split goes ahead (d_done: what it has dealt with)
 };
 
@@ -216,6 +217,7 @@ struct pcr_record {
     uint32_t flat_row_cells = 0;                                    // cells per row of the widest image
     PixelTile* d_flat_rows = nullptr; uint32_t n_flat_rows = 0;     // ... and rows of cells (none if an image is too wide for k_pixel_flat_rows)
     uint32_t* d_dims = nullptr;             // [n][2] width, height (for kernels that run without a decode before them)
+    bool entry_units = false;               // some scan has units that start at entry points
     bool several_units = false;             // some scan has several units (restart intervals, entry points): lane decoders are worth considering
     int lane_mode = 0;                      // pcr_set_lane_decoders: 0 by the number of units, 1 wherever possible, -1 never
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
@@ -433,7 +435,8 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         }
         ll.level = (uint32_t)(li / kNumKinds);
         if (!jobs.empty()) {
-            ll.n_jobs = (uint32_t)jobs.size();
+            ll.n_jobs = ll.lanes.jobs = (uint32_t)jobs.size();
+            for (const Run& q : rn) ll.lanes.add(r->scan[(size_t)q.img * G + q.scan], q.count);
             up.add(&ll.d_jobs, jobs);
         }
         if (ll.kind == kSequential) {
@@ -522,21 +525,11 @@ int add_call_times(const CallTiming& c, double* ms, uint32_t* marks) {
     return PCR_OK;
 }
 
-// One lane per unit or one wavefront per unit?  The wavefront decoders are bound by scalar instruction issue over all
-// units of a launch (about 14 instructions per symbol, 256 issued per cycle), the lane decoders (pcr_lanes.h) by the
-// latency of one symbol after another in the longest unit of a wavefront (about a microsecond per symbol), with a
-// fifth of the instructions in total.  A launch that has the GPU to itself is therefore faster with lanes only from
-// some tens of thousands of units on (measured on 1024-image records with an entry every 128 MCUs, every 64 in refinement
-// scans: 53, 58 and 40 thousand units per launch, a record alone 5.4 ms against 6.6); a launch that shares the GPU with
-// the decodes of other records (other streams) already from a few thousand, because what it leaves idle the others use:
-// four records in flight decode twice as fast with lanes.  The library cannot see what
-// else runs on the device; it takes the number of records the process has open as the sign of it.
-constexpr uint32_t kLanesMinUnitsShared = 8192, kLanesMinUnitsAlone = 32768;
-bool lanes_pay(const pcr_record* r, const LevelList& l) {
+// One lane per unit or one wavefront per unit?  (The line: LanesLaunch.)  The library cannot see what else runs on the device; it
+// takes the number of records the process has open as the sign of it.
+bool lanes_pay(const pcr_record* r, const LevelList& l, bool several) {
     if (!r->several_units || r->lane_mode < 0 || l.n_jobs == 0) return false;
-    if (r->lane_mode > 0) return true;
-    const uint32_t least = g_open_records.load(std::memory_order_relaxed) > 1 ? kLanesMinUnitsShared : kLanesMinUnitsAlone;
-    return l.n >= least && l.n >= 32u * l.n_jobs;            // (jobs half full at least: few tables per 64 units)
+    return r->lane_mode > 0 || l.lanes.by_lanes(l.kind == kAcRefine, several);
 }
 
 // The same question for a launch of DC first scans (with AC first scans by lanes they share a launch, see with_ac; the line:
@@ -628,13 +621,26 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     const uint32_t n = r->hdr.n;
     call_begin(r, s);
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
+    const bool several = g_open_records.load(std::memory_order_relaxed) > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
     r->last_lane_launches = r->last_wave_launches = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
         if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
         else if (l.kind != kDcFirst) {
-            by_lanes[li] = lanes_pay(r, l) ? 1 : 0;
+            by_lanes[li] = lanes_pay(r, l, several) ? 1 : 0;
+            if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
+        }
+    }
+    // Scans cut by restart markers alone can be decoded side by side, which one launch by lanes between the others rules out: where the launches
+    // of a call differ their number of units decides for each, as it does where the fit is unsure.  (20 pictures of 382 x 561 with
+    // a marker every MCU row, scan group 6: 253 us a call side by side, 299 with the first scans by lanes.)
+    if (!r->entry_units && r->lane_mode == 0 && r->last_lane_launches && r->last_wave_launches) {
+        r->last_lane_launches = r->last_wave_launches = 0;
+        for (size_t li = 0; li < plan->levels.size(); li++) {
+            const LevelList& l = plan->levels[li];
+            if (l.kind != kAcFirst && l.kind != kAcRefine) continue;
+            by_lanes[li] = r->several_units && l.n_jobs && l.lanes.many(several) ? 1 : 0;
             if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
         }
     }
@@ -979,7 +985,7 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
     uint64_t nm = 0; uint64_t ns = 0;
     std::vector<uint32_t> tab_idx((size_t)n * G, 0); uint32_t ntabs = 0;
     std::vector<uint32_t> dctab_idx((size_t)n * G, 0); uint32_t ndctabs = 0;
-    r->several_units = false;
+    r->several_units = r->entry_units = false;
     // version 2: where the entry points of every scan lie (behind the regions of the scan's group)
     std::vector<uint32_t> ent_off((size_t)n * G, 0), ent_cnt((size_t)n * G, 0);
     if (r->hdr.version == 2) {
@@ -1018,6 +1024,7 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
             const bool serial = !(d.progressive && sd.Ss == 0 && sd.Ah > 0);          // (DC refinement is read in place, without units)
             if (sd.ri == 0 && serial && ent_cnt[ig] > 0) cnt = 1 + ent_cnt[ig];         // units start at the entry points
             else ent_off[ig] = 0;
+            if (ent_off[ig]) r->entry_units = true;
             if (d.progressive && sd.Ss == 0 && sd.Ah == 0) { dctab_idx[ig] = ndctabs; ndctabs += kMaxComp; }
             if (cnt > 1 && (sd.Ss > 0 || d.progressive)) r->several_units = true;
             r->slot_base[ig] = (uint32_t)ns; r->slot_cnt[ig] = cnt;

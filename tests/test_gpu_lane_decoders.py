@@ -191,3 +191,27 @@ def test_refinement_units_that_are_mostly_end_of_band_runs():
                 for i in range(len(files)):
                     want, _, _ = oracle.decode_record_image(rec, i, k)
                     assert np.array_equal(got[int(lay[i]):int(lay[i + 1])], want), (i, k)
+
+
+@pytest.mark.parametrize("side, n, entry, restart", [(384, 256, 32, 0), (96, 512, 32, 0), (384, 96, 0, 1), (250, 128, 100, 0)])
+def test_launches_that_go_to_lanes_by_themselves(side, n, entry, restart):
+    """What the rule sends to the lanes below the line by number -- all AC launches of a call or some of them -- gives the bytes of the
+    wavefront decoders, from scratch and as an upgrade."""
+    torch = _torch()
+    some = [pcrgen.make_jpeg(60 + i, 1 + (i % 2), side - 3 * i, side + i, 3, 12.0, 2, 2, 80, restart=restart) for i in range(6)]
+    files, took = [some[i % 6] for i in range(n)], 0
+    rec = pkg.record_write_indexed(files, None, entry) if entry else pcrgen.write_record(files)
+    with pkg.pcr_open(rec, 0) as r:
+        for k0, k in ((0, 2), (0, 5), (0, 6), (0, 10), (2, 8)):
+            out = []
+            for mode in (0, -1):
+                r.set_lane_decoders(mode)
+                if k0:
+                    r.decode_batch(k0)
+                st = torch.full((r.n,), 77, dtype=torch.int32, device="cuda")
+                out.append(r.upgrade_batch(k, status=st).clone() if k0 else r.decode_batch(k, status=st).clone())
+                assert (st.cpu().numpy() == 0).all()
+                if mode == 0:
+                    took += r.last_decoder_shapes()[0]
+            assert torch.equal(*out), (k0, k)
+    assert took > 0 or (side, entry) != (384, 32)
