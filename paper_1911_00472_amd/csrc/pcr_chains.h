@@ -129,11 +129,14 @@ private:
 //      400 x 400                           332 / 139     339 / 172     365 / 240
 //   4:4:4 200 x 200                        222 / 101     230 / 150     245 / 162     289 / 187
 //   gray 300 x 300                         190 / 77      200 / 99      207 / 104
+// DC scans of MCUs of more than three blocks that take more than six bits a block (strong, coarse contrasts: few symbols in a piece, codes of luma and chroma
+// of like lengths) do not fall into step in a scan or two of a hundred, and then the launch by wavefronts is as long as without: photographs of
+// 7.8 bits a block at scan group 1, 128 of them 583 / 735, 1024 699 / 876, where those of 3.7 to 5.4 bits a block are the gains above.
 // 1024 lanes a unit instead of 256 are better only for very long units: 1000 x 1000 at quality 90, noisy, scan group 5 401 / 673 us a
 // call (8264 by wavefronts), 32 of them 491 / 801; 4:4:4 200 x 200 as above 243 / 237.
 struct FirstSplitLaunch {
     uint32_t units = 0, ac_bits = 0, ac_blocks = 0, dc_units = 0, dc_blocks = 0, dc_per_mcu = 0;      // bits, blocks: of the longest unit
-    uint64_t ac_visits = 0, dc_visits = 0;                    // blocks of all units
+    uint64_t ac_visits = 0, dc_visits = 0, dc_bits = 0;       // blocks of all units
     void add(const ImgDesc& img, const ScanDesc& sd, uint32_t count) {
         if (sd.Ah != 0 || is_sequential_scan(sd) || count == 0) return;
         uint32_t per_mcu = sd.ns > 1 ? 0u : 1u;
@@ -143,7 +146,7 @@ struct FirstSplitLaunch {
             units += count; ac_visits += (uint64_t)sd.mcus;
             ac_bits = std::max(ac_bits, (uint32_t)((uint64_t)sd.data_len * 8 / count)); ac_blocks = std::max(ac_blocks, blocks);
         } else {
-            dc_units += count; dc_visits += (uint64_t)sd.mcus * per_mcu;
+            dc_units += count; dc_visits += (uint64_t)sd.mcus * per_mcu; dc_bits += (uint64_t)sd.data_len * 8;
             dc_blocks = std::max(dc_blocks, blocks); dc_per_mcu = std::max(dc_per_mcu, per_mcu);
         }
     }
@@ -153,7 +156,9 @@ struct FirstSplitLaunch {
         if (n == 0.f) return false;
         const float in_step = dc_per_mcu > 3 ? 120.f : (dc_per_mcu > 1 ? 60.f : 30.f);
         const float waves = std::max(0.0075f * (float)ac_bits + 0.06f * (float)ac_blocks, 0.075f * dc) + 0.0001f * (float)ac_visits + (with_dc ? 0.00004f * (float)dc_visits : 0.f);
-        const float lanes = 35.f + std::max(std::min(in_step, 0.1f * dc), 0.0008f * (float)ac_bits) + 0.028f * n + 0.00004f * seen;
+        // (what does not fall into step the wavefronts decode behind the lanes)
+        const float again = dc_per_mcu > 3 && dc_bits > 6 * dc_visits ? 0.075f * dc : 0.f;
+        const float lanes = 35.f + std::max(std::min(in_step, 0.1f * dc), 0.0008f * (float)ac_bits) + 0.028f * n + 0.00004f * seen + again;
         return lanes < waves;
     }
     bool wide(bool with_dc) const { return units + (with_dc ? dc_units : 0u) <= 512 && ac_bits >= 131072; }

@@ -99,3 +99,21 @@ def test_damaged_data_flag_the_same_images(seed):
             f[at:at] = bytes(rng.integers(0, 255, 9, dtype=np.uint8))
         files.append(bytes(f))
     _both(pcrgen.write_record(files), (1, 2, 5))
+
+
+@pytest.mark.parametrize("contrast", [1, 8])
+def test_dc_scans_of_many_bits_a_block(contrast):
+    """DC scans that fall into step and DC scans that do not (the wavefronts decode those), with and without AC scans beside them: the
+    bytes of the wavefront decoders."""
+    rng = np.random.default_rng(31)
+    base = [np.kron(rng.integers(0, 256, (40, 50, 3)), np.ones((8, 8, 1))) for _ in range(2)]
+    files = [pcrgen.encode_pixels(np.clip((b - 128) * contrast / 8 + 128, 0, 255).astype(np.uint8), 2, 2, 90) for b in base] * 12
+    with pkg.pcr_open(pkg.record_write(files), 0) as r:
+        for k in (1, 2, 5):
+            out = []
+            for mode in (0, -1):
+                r.set_lane_decoders(mode)
+                st = torch.full((r.n,), 77, dtype=torch.int32, device="cuda")
+                out.append(r.decode_batch(k, status=st).clone())
+                assert (st.cpu().numpy() == 0).all()
+            assert torch.equal(*out), k
