@@ -59,6 +59,21 @@ PCR_HD uint32_t code_entry(uint32_t len, uint32_t sym) {
 // ... and back: (length << 8) | symbol
 PCR_HD uint32_t entry_code(uint32_t e) { return (e & 0x1F00u) | ((e & kCodeEob) ? (e & 15u) << 4 : e & 255u); }
 
+// A canonical code's lengths, for building look-ups entry by entry: lim[L] = first left-aligned 16-bit value that is not
+// a code of length <= L (so codes of length L occupy lim[L-1] .. lim[L]), first[L] = index of the first code of length L.
+struct CanonCode { uint32_t lim[17]; uint32_t first[17]; uint8_t vals[256]; };
+
+// (length << 8) | index of the code at the head of the left-aligned 16-bit value c16; 0 if none of the lengths kLo .. kHi.
+// (The limits are counted, not searched: eight reads of LDS that wait for nothing, then two for the length found.)
+template <int kLo, int kHi>
+PCR_HD uint32_t canon_find(const CanonCode* c, uint32_t c16) {
+    uint32_t L = kLo;
+#pragma unroll
+    for (int q = kLo; q < kHi; q++) L += c16 >= c->lim[q] ? 1u : 0u;
+    const uint32_t below = c->lim[L - 1], idx = c->first[L] + ((c16 - below) >> (16 - L));
+    return (c16 < c->lim[kHi] && c16 >= below && idx < 256u) ? (L << 8) | idx : 0u;
+}
+
 struct DcTab {                  // DC symbols are categories 0..15
     uint8_t lut[256];           // (length << 4) | symbol for codes of <= 8 bits, 0xFF otherwise
     uint32_t limit[9];

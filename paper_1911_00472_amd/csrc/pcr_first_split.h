@@ -24,9 +24,12 @@ struct FirstTables {
     static_assert(sizeof(DcTab) * kMaxComp <= sizeof(uint4) * kLaneTabPieces && sizeof(DcTab) % 4 == 0, "they share the room");
 };
 
+// The bits a walk moves on by: one at least, whatever the data and the tables hold, so that every walk ends.
+PCR_HD uint32_t split_step(uint32_t bits) { return bits < 1u ? 1u : bits; }
+
 // From `from` (bk: the place in the band) to the first symbol at or behind bit `end` of an AC first scan.  WRITE: stores what it passes, from
-// block `block` of the scan to block `stop`; returns false where the data are no valid stream.  Not WRITE: every symbol moves on by a
-// bit at least and the result depends on nothing but the state it starts in; *blocks: blocks ended.
+// block `block` of the scan to block `stop`; returns false where the data are no valid stream.  Not WRITE: the result depends on
+// nothing but the state it starts in; *blocks: blocks ended.
 template <bool WRITE>
 PCR_D __attribute__((always_inline)) bool first_ac_walk(const LaneLookup& code, const SplitScan& S, uint32_t Ss, uint32_t Se, uint32_t Al, const SplitState& from, uint32_t end, LaneRing* ring, uint32_t lane,
                       SplitState* to, uint32_t* blocks, int16_t* plane, uint32_t elems, uint32_t block, uint32_t stop) {
@@ -43,9 +46,9 @@ PCR_D __attribute__((always_inline)) bool first_ac_walk(const LaneLookup& code, 
             if (WRITE && left == 0) break;                    // what follows the last block is padding
             if (PCR_RARELY((int)(st.n - low) < 0)) { st.refill(); low = st.low_water(1); }
             const uint32_t win = st.window(), e = code.resolve(code.entry(win), win);
-            const uint32_t len = bit_range(e, 8, 5), nx = e & 15u, none = bit_mask(e, 15);
+            const uint32_t len = bit_range(e, 8, 5), nx = e & 15u;
             const uint32_t x = win << len, extra = bit_range(x, 32u - nx, nx);
-            st.consume(len + nx + (none & 1u));
+            st.consume(split_step(len + nx));
             const uint32_t at = k + bit_range(e, 4, 4), room = Se - at, coef = e << 17;
             if (WRITE) {
                 // no code; a coefficient beyond the band; bits beyond the unit's
@@ -102,7 +105,7 @@ PCR_D __attribute__((always_inline)) bool first_dc_walk(const DcTab* tabs, const
             }
             const uint32_t x = win << len;
             const int value = (int)(bit_range(x, 32u - nx, nx) - (~sign_mask(x) & ((1u << nx) - 1u)));
-            st.consume(len + nx + none);
+            st.consume(split_step(len + nx));
             dc0 += c == 0 ? value : 0; dc1 += c == 1 ? value : 0; dc2 += c == 2 ? value : 0;
             if (WRITE) {
                 if (none || (int)st.beyond() < 0) { good = false; break; }
@@ -120,6 +123,8 @@ PCR_D __attribute__((always_inline)) bool first_dc_walk(const DcTab* tabs, const
     return good;
 }
 
+#if defined(__HIPCC__)
+
 // done[u] = 1: unit u needs nothing more.  A workgroup per unit.
 template <uint32_t LANES>
 __global__ void __launch_bounds__(LANES) k_first_split(DevRecord R, const Unit* __restrict__ units, uint32_t* __restrict__ done, const uint32_t* __restrict__ clean32, uint32_t to_planes) {
@@ -134,13 +139,13 @@ __global__ void __launch_bounds__(LANES) k_first_split(DevRecord R, const Unit* 
     const Unit un = units[blockIdx.x];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     UnitSetup L;
-    unit_setup(R, un, clean32, &L);
+    unit_setup(R, un, clean32, group_status(R, un.img), &L);
     const size_t ig = (size_t)un.img * R.G + un.scan;
     const ScanDesc* sd = &R.scan[ig];
     const uint32_t bit0 = L.byte_off * 8 + L.sub_bits, bit1 = L.byte_off * 8 + L.nbits;
     const bool ac = uni((int)sd->Ss) > 0;
     const uint32_t ns = L.ok ? (uint32_t)L.ls.ns : 0u;
-    // (the same for the whole workgroup)
+    // (the same for the whole workgroup: nothing but the status is written while this runs, and that all have from one lane)
     const bool mine = L.ok && R.img[un.img].progressive && uni((int)sd->Ah) == 0 && !is_sequential_scan(*sd) && ns >= 1 && ns <= (uint32_t)kMaxComp && (!ac || ns == 1) && bit1 > bit0;
     SplitScan S{L.words, bit1, 0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 0, 0, 0, 0, 0, 0};
     uint32_t total = 0;
@@ -237,5 +242,7 @@ __global__ void __launch_bounds__(LANES) k_first_split(DevRecord R, const Unit* 
         done[blockIdx.x] = 1;
     }
 }
+
+#endif  // __HIPCC__
 
 }  // namespace pcr

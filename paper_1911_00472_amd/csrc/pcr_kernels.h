@@ -201,10 +201,6 @@ PCR_D DeviceHead head_at(const HeaderBytes& b, uint32_t p, uint32_t end) {
     return h;
 }
 
-// A canonical code's lengths, for building look-ups entry by entry: lim[L] = first left-aligned 16-bit value that is not
-// a code of length <= L (so codes of length L occupy lim[L-1] .. lim[L]), first[L] = index of the first code of length L.
-struct CanonCode { uint32_t lim[17]; uint32_t first[17]; uint8_t vals[256]; };
-
 // From a DHT payload (16 counts, then the symbols in code order); call with a whole wavefront.
 PCR_D void canon_build(CanonCode* c, const HeaderBytes& def, uint32_t at, uint32_t lane) {
     const uint32_t mine = lane < 16 ? def[at + lane] : 0u;
@@ -215,16 +211,6 @@ PCR_D void canon_build(CanonCode* c, const HeaderBytes& def, uint32_t at, uint32
     const uint32_t first = lanes_prefix_sum(mine) - mine;
     if (lane < 16) { c->lim[lane + 1] = lim; c->first[lane + 1] = first; }
     if (lane == 16) c->lim[0] = 0;
-}
-// (length << 8) | index of the code at the head of the left-aligned 16-bit value c16; 0 if none of the lengths kLo .. kHi.
-// (The limits are counted, not searched: eight reads of LDS that wait for nothing, then two for the length found.)
-template <int kLo, int kHi>
-PCR_D uint32_t canon_find(const CanonCode* c, uint32_t c16) {
-    uint32_t L = kLo;
-#pragma unroll
-    for (int q = kLo; q < kHi; q++) L += c16 >= c->lim[q] ? 1u : 0u;
-    const uint32_t below = c->lim[L - 1], idx = c->first[L] + ((c16 - below) >> (16 - L));
-    return (c16 < c->lim[kHi] && c16 >= below && idx < 256u) ? (L << 8) | idx : 0u;
 }
 // What actab_build and actab_pack make of the definition, entry by entry (same contents).
 PCR_D void actab_build_wave(AcTab* t, const CanonCode* c, bool first, uint32_t lane) {
@@ -786,10 +772,19 @@ struct UnitSetup {
     bool ok;
 };
 
-PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __restrict__ clean32, UnitSetup* L) {
+// The status of an image, read once for all wavefronts of the workgroup.  Workgroups that decode other units of the image write that word
+// in the same launch: wavefronts that are to meet at a barrier behind it must not each read it for themselves.
+PCR_D int group_status(const DevRecord& R, uint32_t img) {
+    __shared__ int s_status;
+    if (threadIdx.x == 0) s_status = R.status[img];
+    __syncthreads();
+    return uni(s_status);
+}
+// status: the image's.
+PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __restrict__ clean32, int status, UnitSetup* L) {
     L->ok = false;
     const ImgDesc* img = &R.img[un.img];
-    if (R.status[un.img] != kOk || un.scan >= img->nscans) return;
+    if (status != kOk || un.scan >= img->nscans) return;
     const size_t ig = (size_t)un.img * R.G + un.scan;
     const ScanDesc* sd = &R.scan[ig];
     if (!sd->valid) return;
@@ -1145,7 +1140,7 @@ __global__ void __launch_bounds__(kEntropyLanes * kChainWaves) k_decode_waves(De
     if (wave >= ch.count) return;
     const Unit un = units[ch.first + wave];
     UnitSetup L;
-    unit_setup(R, un, clean32, &L);
+    unit_setup(R, un, clean32, R.status[un.img], &L);
     if (FOLLOW) {
         uint64_t all = ch.waits | (ch.waits >> 32);
         all |= all >> 16; all |= all >> 8;
@@ -1282,7 +1277,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const
     if (done && done[blockIdx.x]) return;
     const Unit un = units[blockIdx.x];
     UnitSetup L;
-    unit_setup(R, un, clean32, &L);
+    unit_setup(R, un, clean32, R.status[un.img], &L);
     if (!L.ok) return;
     const ScanDesc* sd = &R.scan[(size_t)un.img * R.G + un.scan];
     if (!is_sequential_scan(*sd)) { R.status[un.img] = kEFormat; return; }      // (a unit in the wrong launch)

@@ -31,7 +31,10 @@
 // with Applications to JPEG Files" (The Computer Journal 46, 2003), and, on GPUs, of Weissenberger and Schmidt, "Accelerating
 // JPEG Decompression on GPUs" (HiPC 2021); what is here was written from the idea.
 #pragma once
+#include "pcr_lanes.h"
+#if defined(__HIPCC__)
 #include "pcr_kernels.h"
+#endif
 
 namespace pcr {
 
@@ -158,6 +161,8 @@ PCR_D bool split_stops(uint32_t round, uint32_t count, uint32_t* half_left) {
     return round >= 8 && left > (float)kSplitLeft;
 }
 
+#if defined(__HIPCC__)
+
 // done[u] = 1: unit u needs nothing more.
 __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, const Unit* __restrict__ units, uint32_t* __restrict__ done, const uint32_t* __restrict__ clean32) {
     __shared__ SplitTables T;
@@ -171,7 +176,7 @@ __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, c
     const Unit un = units[blockIdx.x];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     UnitSetup L;
-    unit_setup(R, un, clean32, &L);
+    unit_setup(R, un, clean32, R.status[un.img], &L);
     const ScanDesc* sd = &R.scan[(size_t)un.img * R.G + un.scan];
     const uint32_t bit0 = L.byte_off * 8 + L.sub_bits, bit1 = L.byte_off * 8 + L.nbits;
     const bool mine = L.ok && is_sequential_scan(*sd) && L.ls.ns >= 1 && L.ls.ns <= kMaxComp && bit1 > bit0 && bit1 - bit0 >= kSplitLeastBits;
@@ -273,5 +278,7 @@ __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, c
         done[blockIdx.x] = 1;
     }
 }
+
+#endif  // __HIPCC__
 
 }  // namespace pcr

@@ -8,6 +8,7 @@ import torch
 import oracle
 import paper_1911_00472_amd as pkg
 import pcrgen
+from test_record_entry_points import _entry_at
 
 pytestmark = pytest.mark.gpu
 
@@ -99,6 +100,26 @@ def test_damaged_data_flag_the_same_images(seed):
             f[at:at] = bytes(rng.integers(0, 255, 9, dtype=np.uint8))
         files.append(bytes(f))
     _both(pcrgen.write_record(files), (1, 2, 5))
+
+
+def test_entries_out_of_order_flag_their_images_only():
+    """An entry that lies beyond its scan flags its image while other workgroups of the launch begin with the image's other units: both
+    decoders flag the same images, blank them and agree on the others."""
+    files = [pcrgen.make_jpeg(700 + i, 1, 600 - 9 * i, 480 + 7 * i, 3, 18.0, 2, 2, 90) for i in range(12)]
+    good = pkg.record_write_indexed(files, None, 1024)
+    bad = bytearray(good)
+    hit = {1: 0, 4: 1, 5: 4, 8: 1, 11: 4}                      # image: the scan whose entry is moved
+    for i, g in hit.items():
+        at, _ = _entry_at(good, g, i, 1)
+        bad[at:at + 4] = (10 ** 9).to_bytes(4, "little")
+    for k in (1, 2, 5):
+        st = _both(bytes(bad), (k,))
+        assert sorted(np.flatnonzero(st)) == sorted(i for i, g in hit.items() if g < k), k
+    with pkg.pcr_open(bytes(bad), 0) as b, pkg.pcr_open(good, 0) as r:
+        lay, want, got = r.output_layout(), r.decode_batch(5).cpu().numpy(), b.decode_batch(5).cpu().numpy()
+        for i in range(len(files)):
+            a, e = int(lay[i]), int(lay[i + 1])
+            assert not got[a:e].any() if i in hit else np.array_equal(got[a:e], want[a:e]), i
 
 
 @pytest.mark.parametrize("contrast", [1, 8])
