@@ -24,9 +24,6 @@ struct FirstTables {
     static_assert(sizeof(DcTab) * kMaxComp <= sizeof(uint4) * kLaneTabPieces && sizeof(DcTab) % 4 == 0, "they share the room");
 };
 
-// The bits a walk moves on by: one at least, whatever the data and the tables hold, so that every walk ends.
-PCR_HD uint32_t split_step(uint32_t bits) { return bits < 1u ? 1u : bits; }
-
 // From `from` (bk: the place in the band) to the first symbol at or behind bit `end` of an AC first scan.  WRITE: stores what it passes, from
 // block `block` of the scan to block `stop`; returns false where the data are no valid stream.  Not WRITE: the result depends on
 // nothing but the state it starts in; *blocks: blocks ended.

@@ -73,9 +73,12 @@ PCR_D uint32_t split_long_code(const CanonCode* c, uint32_t c16, bool dc) {
 
 PCR_D uint32_t pick(uint32_t c, uint32_t v0, uint32_t v1, uint32_t v2) { return c == 0 ? v0 : (c == 1 ? v1 : v2); }
 
+// The bits a walk moves on by: one at least, whatever the data and the tables hold, so that every walk ends.
+PCR_HD uint32_t split_step(uint32_t bits) { return bits < 1u ? 1u : bits; }
+
 // From `from` to the first symbol at or behind bit `end`.  WRITE: stores what it passes, as far as block `total` (block numbers
-// count from the unit's first); returns false where the data are no valid stream.  Not WRITE: whatever the data are, every
-// symbol moves on by a bit at least and the result depends on nothing but the state it starts in.
+// count from the unit's first); returns false where the data are no valid stream.  Not WRITE: whatever the data are, the result
+// depends on nothing but the state it starts in.
 template <bool WRITE>
 PCR_D __attribute__((always_inline)) bool split_walk(const SplitScan& S, const SplitTables& T, const SplitState& from, uint32_t end, LaneRing* ring, uint32_t lane, SplitState* to, SplitSums* sums,
                       int16_t* base, int16_t* dense, uint32_t elems, uint32_t block, uint32_t total) {
@@ -117,7 +120,7 @@ PCR_D __attribute__((always_inline)) bool split_walk(const SplitScan& S, const S
             const uint32_t eob = bit_mask(e, 13) & ~dc, none = bit_mask(e, 15);
             // no code; an end-of-band run; a coefficient beyond position 63
             uint32_t bad = none | (eob & sign_mask(0u - nx)) | (bit_mask(e, 14) & sign_mask(63u - at));
-            st.consume(len + nx + (none & 1u));
+            st.consume(split_step(len + nx));
             if (WRITE) {
                 const uint32_t c = c4 >> 2;
                 if (dc) {
@@ -176,11 +179,11 @@ __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, c
     const Unit un = units[blockIdx.x];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     UnitSetup L;
-    unit_setup(R, un, clean32, R.status[un.img], &L);
+    unit_setup(R, un, clean32, group_status(R, un.img), &L);
     const ScanDesc* sd = &R.scan[(size_t)un.img * R.G + un.scan];
     const uint32_t bit0 = L.byte_off * 8 + L.sub_bits, bit1 = L.byte_off * 8 + L.nbits;
     const bool mine = L.ok && is_sequential_scan(*sd) && L.ls.ns >= 1 && L.ls.ns <= kMaxComp && bit1 > bit0 && bit1 - bit0 >= kSplitLeastBits;
-    if (!mine) { if (tid == 0) done[blockIdx.x] = 0; return; }         // (the same for the whole workgroup)
+    if (!mine) { if (tid == 0) done[blockIdx.x] = 0; return; }         // (the same for the whole workgroup: it has the status from one lane)
     // ---- the tables, each once ----
     const uint32_t ns = (uint32_t)L.ls.ns;
     SplitScan S{L.words, bit1, 0, 0, 0, 0, 0, 0, L.ls.mcu0, L.ls.mcu_w, 1, 1, 1, 1, 1, 1, L.ls.bw[0], L.ls.bw[1], L.ls.bw[2], L.ls.poff[0], L.ls.poff[1], L.ls.poff[2]};

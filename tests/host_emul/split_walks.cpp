@@ -1,4 +1,4 @@
-// CPU build of the walks of k_first_split (pcr_first_split.h) on look-ups whose entries no code has, codes of no bits among them: every
+// CPU build of the walks of k_first_split and k_sequential_split (pcr_first_split.h, pcr_sequential.h) on look-ups whose entries no code has, codes of no bits among them: every
 // walk ends.  Prints how far behind the end it was given each of them stopped.  Test-only.
 #include <cstdio>
 #include <cstring>
@@ -12,6 +12,7 @@ int main() {
     std::vector<uint32_t> words(kBits / 32 + 64);
     LaneRing ring;
     FirstTables T;
+    static SplitTables Q;
     const uint32_t fills[] = {0u, 0xFFFFFFFFu, 0x20002000u, 0x40004000u, 0x80008000u, 0xA000A000u, 0x01010101u, 0x0F0F0F0Fu, 0xFF00FF00u, 0x00F000F0u};
     for (uint32_t fill : fills)
         for (uint32_t data = 0; data < 3; data++) {
@@ -37,6 +38,15 @@ int main() {
             printf(" dc %d", (int)(to.pos - (kBits - 100)));
             sums = SplitSums{0, 0, 0, 0};
             first_dc_walk<true>(reinterpret_cast<const DcTab*>(T.piece), S, 1, SplitState{7, 0}, kBits - 100, &ring, 0, &to, &sums, plane.data(), dense.data(), 64 * 64, 64);
+            fill_with(&Q, sizeof Q);
+            for (CanonCode& c : Q.code)
+                for (uint32_t l = 0; l < 17; l++) { c.lim[l] = l < 16 ? 0u : fill & 65535u; c.first[l] = 0; }       // (codes of sixteen bits, or none)
+            S.dc_tabs = 0; S.ac_tabs = 3; S.hs0 = S.vs0 = 1;
+            sums = SplitSums{0, 0, 0, 0};
+            split_walk<false>(S, Q, SplitState{7, 0}, kBits - 100, &ring, 0, &to, &sums, nullptr, nullptr, 0, 0, 0);
+            printf(" whole %d", (int)(to.pos - (kBits - 100)));
+            sums = SplitSums{0, 0, 0, 0};
+            split_walk<true>(S, Q, SplitState{7, 0}, kBits - 100, &ring, 0, &to, &sums, plane.data(), dense.data(), 64 * 64, 0, 64);
             printf("\n"); fflush(stdout);
         }
     printf("walks end\n");

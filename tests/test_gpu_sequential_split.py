@@ -77,6 +77,27 @@ def test_damaged_data_flag_their_image_only():
     assert flagged >= 2
 
 
+@pytest.mark.parametrize("scan", [0, 1, 2])
+def test_one_damaged_scan_of_several(scan):
+    """Workgroups that decode an image's other scans begin and end around the one that flags it: that image is flagged and blank,
+    the others are as they were."""
+    files = [planar_sequential(20 + i, 420, 333, 95) for i in range(6)]
+    rec = pcrgen.write_record(files)
+    with pkg.pcr_open(rec, 0) as r:
+        G, (off, length) = r.G, r.index()
+    _, _, st, pix, lay = _coefficients(rec)
+    assert G == 3 and (st == 0).all() and int(np.asarray(length).min()) * 8 > 65536
+    bad = bytearray(rec)
+    for i in (1, 3, 4):
+        at = int(np.asarray(off).reshape(G, -1)[scan][i]) + int(np.asarray(length).reshape(G, -1)[scan][i]) - 3000
+        bad[at:at + 2998] = b"\xff\xd9" + bytes(2996)           # (the data end early)
+    _, _, st, p, _ = _coefficients(bytes(bad))
+    assert [int(v != 0) for v in st] == [0, 1, 0, 1, 1, 0]
+    for i in range(6):
+        got, want = p[int(lay[i]):int(lay[i + 1])], pix[int(lay[i]):int(lay[i + 1])]
+        assert not got.any() if st[i] else np.array_equal(got, want), i
+
+
 @pytest.mark.parametrize("quality,noise,sub,side", [(97, 16.0, 2, 240), (100, 40.0, 1, 240), (100, 8.0, 2, 120), (100, 40.0, 2, 800), (97, 16.0, 1, 120)])
 def test_high_qualities_at_which_the_rounds_are_given_up_early_or_go_on_to_the_end(quality, noise, sub, side):
     _check([pcrgen.encode_pixels(pcrgen.synth(3 + i, 2, side, side, 3, noise), sub, sub, quality, "sequential") for i in range(2)])

@@ -1,5 +1,5 @@
-"""The walks of first scans decoded by many lanes (pcr_first_split.h, compiled for the CPU) on look-ups no code has made, entries of no
-bits among them: every trip moves on by a bit at least, so that they end whatever the tables hold."""
+"""The walks of scans decoded by many lanes each (pcr_first_split.h, pcr_sequential.h, compiled for the CPU) on look-ups no code has made,
+entries of no bits among them: every trip moves on by a bit at least, so that they end whatever the tables hold."""
 import os
 import subprocess
 
@@ -13,5 +13,5 @@ def test_walks_end_whatever_the_tables_hold(tmp_path):
     lines = out.splitlines()
     assert lines[-1] == "walks end" and len(lines) == 31
     for line in lines[:-1]:                                   # a symbol takes 46 bits at most (a length of five bits, fifteen more)
-        _, _, _, ac, _, dc = line.split()
-        assert 0 <= int(ac) < 46 and 0 <= int(dc) < 46, line
+        _, _, _, ac, _, dc, _, whole = line.split()
+        assert all(0 <= int(v) < 46 for v in (ac, dc, whole)), line
