@@ -388,7 +388,7 @@ int pcr_transcode_progressive(const void* src_jpeg, size_t src_bytes, const int1
  * pcr_transcode_batch: all of it for the n files an opened record was made of (the record's images, in order): decode,
  *   counts (device_counts != 0; otherwise counted on the host), and the progressive files, coded on the device (on the host
  *   where it counts, or restart markers are asked for) and written by up to `threads` threads; file i goes to out + out_off[i], where it has out_off[i + 1] - out_off[i] bytes of room, and written[i]
- *   is its size.  PCR_E_RANGE: some file needs the room written[] says, call again with it.  Synchronous. */
+ *   is its size.  PCR_E_RANGE: some file needs the room written[] says, call again with it (nothing of such a file is written).  Synchronous. */
 #define PCR_HIST_SCANS 10
 #define PCR_HIST_ENTRIES (PCR_HIST_SCANS * 2 * 256)
 int pcr_symbol_histograms(pcr_record* rec, uint32_t restart_interval, uint32_t* d_hist, void* hip_stream);

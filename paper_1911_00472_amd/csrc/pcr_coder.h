@@ -11,7 +11,6 @@
 
 namespace pcr {
 
-constexpr uint32_t kCodeSlots = kScriptScansMax * 2;           // tables of an image
 // A table as a file holds it.
 struct CodeSpec { uint8_t counts[16]; uint32_t nsym; uint8_t symbols[256]; };      // counts[l]: codes of l + 1 bits
 

@@ -846,22 +846,33 @@ inline void write_scan_head(const Frame& F, const ScanSpec& S, std::vector<uint8
     o.push_back((uint8_t)S.Ss); o.push_back((uint8_t)S.Se); o.push_back((uint8_t)((S.Ah << 4) | S.Al));
 }
 
-// The progressive file of a frame from what the device made of its coefficients (pcr_coder.h): specs, the tables of its scans (kCodeSlots);
-// bits, how many every scan has (kScriptScansMax); words, the scan's first words, number word_off[scan] of them on.  Writes at most
-// `room` bytes of it to dst and returns how many it has.  (Straight to where they go: by way of a vector, with the pages that takes,
-// 64 photographs took longer with sixteen threads than with one.)
+// How many of n bytes are 0xFF.
+inline size_t count_ff(const uint8_t* d, size_t n) {
+    size_t all = 0;
+    while (n > 0) {                                            // (sums of bytes, which a compiler adds up sixteen at a time)
+        const size_t m = std::min<size_t>(n, 240);
+        uint8_t some = 0;
+        for (size_t i = 0; i < m; i++) some = (uint8_t)(some + (d[i] == 0xFF ? 1 : 0));
+        all += some; d += m; n -= m;
+    }
+    return all;
+}
+
+// The progressive file of a frame from what the device made of its coefficients (pcr_coder.h): specs, the tables of its scans (two each);
+// bits, how many every scan has (kScriptScansMax); words, the scan's first words, number word_off[scan] of them on.  Returns how
+// many bytes it has, and writes them to dst if there is room for them, or else nothing.  (Straight to where they go: by way of a vector,
+// with the pages that takes, 64 photographs took longer with sixteen threads than with one.)
 inline size_t assemble_progressive(const uint8_t* src, const ImgDesc& img, const Frame& F, const CodeSpec* specs, const uint64_t* bits,
                                    const uint32_t* words, const uint64_t* word_off, uint8_t* dst, size_t room) {
-    size_t size = 0;
-    auto put = [&](const uint8_t* p, size_t n) {
-        if (size < room) memcpy(dst + size, p, std::min(n, room - size));
-        size += n;
-    };
-    std::vector<uint8_t> head;
-    auto put_head = [&]() { put(head.data(), head.size()); head.clear(); };
+    const std::vector<ScanSpec> script = default_script(img.nc);
+    std::vector<uint8_t> head;                                 // what stands ahead of the data of the scans, one behind the other
+    std::vector<size_t> ends(script.size());
     write_file_head(src, img, F, 0, &head);
-    int at = 0;
-    for (const ScanSpec& S : default_script(img.nc)) {
+    size_t size = 2;
+    auto data_of = [&](size_t at) { return reinterpret_cast<const uint8_t*>(words + word_off[at]); };
+    auto bytes_of = [&](size_t at) { return (size_t)((bits[at] + 7) / 8); };
+    for (size_t at = 0; at < script.size(); at++) {
+        const ScanSpec& S = script[at];
         for (int s = 0; s < 2; s++) {
             const CodeSpec& C = specs[2 * at + s];
             if (C.nsym == 0) continue;
@@ -872,19 +883,25 @@ inline size_t assemble_progressive(const uint8_t* src, const ImgDesc& img, const
             write_dht(&head, S.Ss == 0 ? 0 : 1, s, H);
         }
         write_scan_head(F, S, &head);
-        put_head();
-        const uint8_t* d = reinterpret_cast<const uint8_t*>(words + word_off[at]);
-        for (size_t left = (size_t)((bits[at] + 7) / 8); left > 0;) {         // a zero behind every byte 0xFF
+        ends[at] = head.size();
+        size += bytes_of(at) + count_ff(data_of(at), bytes_of(at));
+    }
+    size += head.size();
+    if (size > room) return size;
+    auto put = [&](const uint8_t* p, size_t n) { memcpy(dst, p, n); dst += n; };
+    for (size_t at = 0; at < script.size(); at++) {
+        const size_t from = at ? ends[at - 1] : 0;
+        put(head.data() + from, ends[at] - from);
+        const uint8_t* d = data_of(at);
+        for (size_t left = bytes_of(at); left > 0;) {          // a zero behind every byte 0xFF
             const void* ff = memchr(d, 0xFF, left);
             const size_t n = ff ? (size_t)((const uint8_t*)ff - d) + 1 : left;
             put(d, n);
-            if (ff) put((const uint8_t*)"", 1);
+            if (ff) *dst++ = 0;
             d += n; left -= n;
         }
-        at++;
     }
-    head.push_back(0xFF); head.push_back(0xD9);
-    put_head();
+    *dst++ = 0xFF; *dst++ = 0xD9;
     return size;
 }
 

@@ -784,8 +784,8 @@ std::vector<uint32_t> transcode_groups(const std::vector<uint64_t>& offset, size
     return group;
 }
 
-// Files first .. last - 1 by up to `threads` threads: write(i, where, room, &size) writes file i, as much of it as there is room for,
-// or says why not.
+// Files first .. last - 1 by up to `threads` threads: write(i, where, room, &size) writes file i where there is room for it, or says
+// why not.
 template <class Write> int transcode_write(uint32_t first, uint32_t last, uint32_t threads, void* out, const uint64_t* out_off, uint64_t* written, int* status, const Write& write) {
     std::atomic<uint32_t> next(first);
     auto work = [&]() {

@@ -113,3 +113,27 @@ def test_device_coder_writes_the_host_coders_files(name, extreme_record):
     got, want = pkg.transcode_files(files), pkg.transcode_files(files, device_counts=False)
     for i, (a, b) in enumerate(zip(got, want)):
         assert a == b, (name, i, len(a), len(b))
+
+
+@pytest.mark.parametrize("device_counts", [1, 0])
+def test_files_there_is_no_room_for_are_not_written(device_counts):
+    """Room of exactly a file's size, one byte less, hardly any and none: what fits is whole, of the rest nothing is written, and the sizes
+    of all come back."""
+    import ctypes
+    import pcrgen
+    from paper_1911_00472_amd import binding as B
+    files = [pcrgen.make_jpeg(80 + i, i % 3, 90 + 7 * i, 60, 3 if i % 4 else 1, 14.0, 1, 1, 92) for i in range(8)]
+    want = pkg.transcode_files(files)
+    short = [0, 1, 0, len(want[3]) - 20, 0, 2, len(want[6]), 700]
+    room = [len(w) - s for w, s in zip(want, short)]
+    off = np.concatenate([[0], np.cumsum(room)]).astype(np.uint64)
+    out = np.full(int(off[-1]), 0xA5, np.uint8)
+    written = np.zeros(len(files), np.uint64)
+    bufs, ptrs, sizes = B._file_table(files)
+    with pkg.pcr_open(pkg.record_write(files), 0) as r:
+        rc = B.lib().pcr_transcode_batch(r._h, ptrs, sizes, len(files), 0, device_counts, 4, out.ctypes.data_as(ctypes.c_void_p), off.ctypes.data_as(ctypes.c_void_p),
+                                         written.ctypes.data_as(ctypes.c_void_p), None)
+    assert rc == pkg.E_RANGE and written.tolist() == [len(w) for w in want]
+    for i, w in enumerate(want):
+        got = out[int(off[i]):int(off[i + 1])].tobytes()
+        assert got == (w if short[i] == 0 else b"\xa5" * room[i]), i
