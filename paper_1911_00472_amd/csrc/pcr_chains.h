@@ -108,6 +108,12 @@ private:
     }
 };
 
+// The larger of a launch's longest unit so far and of a scan of `all` in `units` units, on average (divided only where it is larger: records
+// have tens of thousands of scans).
+inline void longest_of(uint32_t* longest, uint64_t all, uint32_t units) {
+    if (all >= ((uint64_t)*longest + 1) * units) *longest = (uint32_t)(all / units);
+}
+
 // A launch of first scans by wavefronts, and whether k_first_split -- many lanes for every unit -- goes ahead of it.
 //
 // The wavefronts take as long as the longest unit, 7.5 ns a bit and 60 a block of an AC scan, 75 a block of a DC scan, and more
@@ -141,13 +147,12 @@ struct FirstSplitLaunch {
         if (sd.Ah != 0 || is_sequential_scan(sd) || count == 0) return;
         uint32_t per_mcu = sd.ns > 1 ? 0u : 1u;
         for (int j = 0; j < sd.ns && sd.ns > 1; j++) per_mcu += (uint32_t)img.hs[sd.comp[j]] * img.vs[sd.comp[j]];
-        const uint32_t blocks = (uint32_t)((uint64_t)sd.mcus * per_mcu / count);
         if (sd.Ss > 0) {
             units += count; ac_visits += (uint64_t)sd.mcus;
-            ac_bits = std::max(ac_bits, (uint32_t)((uint64_t)sd.data_len * 8 / count)); ac_blocks = std::max(ac_blocks, blocks);
+            longest_of(&ac_bits, (uint64_t)sd.data_len * 8, count); longest_of(&ac_blocks, (uint64_t)sd.mcus * per_mcu, count);
         } else {
             dc_units += count; dc_visits += (uint64_t)sd.mcus * per_mcu; dc_bits += (uint64_t)sd.data_len * 8;
-            dc_blocks = std::max(dc_blocks, blocks); dc_per_mcu = std::max(dc_per_mcu, per_mcu);
+            longest_of(&dc_blocks, (uint64_t)sd.mcus * per_mcu, count); dc_per_mcu = std::max(dc_per_mcu, per_mcu);
         }
     }
     // with_dc: the DC scans are part of the launch
@@ -245,7 +250,7 @@ struct LanesLaunch {
     void add(const ScanDesc& sd, uint32_t n) {
         if (n == 0) return;
         units += n; bits += (uint64_t)sd.data_len * 8; blocks += sd.mcus;
-        longest_bits = std::max(longest_bits, (uint32_t)((uint64_t)sd.data_len * 8 / n)); longest_blocks = std::max(longest_blocks, sd.mcus / n);
+        longest_of(&longest_bits, (uint64_t)sd.data_len * 8, n); longest_of(&longest_blocks, sd.mcus, n);
     }
     bool many(bool several) const { return units >= (several ? 8192u : 32768u) && units >= 32u * jobs; }     // (jobs half full at least)
     bool by_lanes(bool refine, bool several) const {

@@ -37,9 +37,7 @@ enum Kind { kDcFirst = 0, kAcFirst = 1, kAcRefine = 2, kSequential = 3, kNumKind
 struct LevelList {
     Unit* d_units = nullptr; uint32_t n = 0; int kind = 0;
     uint32_t level = 0;                                                          // (0-based)
-    RefineScan* d_refine = nullptr; uint32_t n_refine = 0;                      // the scans of an AC refinement launch, for its per-block kernels
-    RefineTile* d_plane_tiles = nullptr; uint32_t n_plane_tiles = 0;              // k_refine_history: chunks of the padded planes of those scans
-    RefineTile* d_cov_tiles = nullptr; uint32_t n_cov_tiles = 0;                  // k_refine_deal, k_refine_blocks: chunks of the blocks the images cover
+    uint32_t plane_tile = 0, n_plane_tiles = 0, cov_tile = 0, n_cov_tiles = 0;    // AC refinement: the level's share of the plan's lists for the per-block kernels
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
     uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units k_sequential_split has dealt with
     uint32_t n_long = 0; uint64_t long_bytes = 0; bool subsampled = false;        // ... how many those are, their bytes, whether some have MCUs of several blocks per component
@@ -56,7 +54,10 @@ struct Plan {                               // launch geometry for one scan grou
     Unit* d_chain_units = nullptr; UnitChain* d_chains = nullptr; uint32_t n_ac_chains = 0, n_chains = 0, chain_waves = 0;
     uint32_t* d_chain_done = nullptr;        // chains of one: which units k_first_split has dealt with
     FirstSplitLaunch split;                  // ... and what decides whether it is launched
-    LevelList refined;                       // all refinement scans of the call, for k_refine_blocks
+    // the AC refinement scans of the call, level after level, and the lists of the per-block kernels
+    RefineScan* d_refine = nullptr;
+    RefineTile* d_refine_tiles = nullptr;    // k_refine_history: chunks of the padded planes of those scans; behind them, from cov_tile on,
+    uint32_t cov_tile = 0, n_cov_tiles = 0;  // k_refine_deal, k_refine_blocks: chunks of the blocks the images cover
     bool chains_built = false;
     ApplyUnit* d_apply = nullptr; ApplyList* d_apply_lists = nullptr; int32_t* d_list_idx = nullptr; uint32_t n_apply = 0, apply_grid_x = 0;
     bool has_ac = false;                     // some scan <= k is an AC scan (else only element 0 of every block is ever touched)
@@ -251,22 +252,43 @@ void compute_levels(pcr_record* r) {
         r->max_level = std::max(r->max_level, scan_levels(&r->scan[(size_t)i * G], r->img[i].nscans, &r->level[(size_t)i * G]));
 }
 
-// The work lists of the per-block kernels of refinement scans.
-void refine_tiles(const pcr_record* r, const std::vector<RefineScan>& rl, LevelList* ll, bool planes_too, Uploads* up) {
-    const uint32_t G = r->hdr.G;
-    ll->n_refine = (uint32_t)rl.size();
-    up->add(&ll->d_refine, rl);
-    std::vector<RefineTile> plane_tiles, cov_tiles;
-    for (uint32_t e = 0; e < ll->n_refine; e++) {
-        const ImgDesc& im = r->img[rl[e].img];
-        const int c = r->scan[(size_t)rl[e].img * G + rl[e].scan].comp[0];
-        const uint32_t plane = (uint32_t)im.bw[c] * im.bh[c], cov = (uint32_t)im.cw[c] * im.ch[c];
-        if (planes_too) for (uint32_t ch = 0; ch * 256 < plane; ch++) plane_tiles.push_back(RefineTile{e, ch});
-        for (uint32_t ch = 0; ch * 256 < cov; ch++) cov_tiles.push_back(RefineTile{e, ch});
+// The AC refinement scans of a plan by level, and how many chunks of 256 blocks their padded planes and the blocks they cover have.
+struct RefineLevel { std::vector<RefineScan> scans; uint32_t planes = 0, covs = 0; };
+uint32_t refine_chunks(const ImgDesc& im, const ScanDesc& sd, bool whole_plane) {
+    const int c = sd.comp[0];
+    return ((whole_plane ? (uint32_t)im.bw[c] * im.bh[c] : (uint32_t)im.cw[c] * im.ch[c]) + 255u) / 256u;
+}
+// The work lists of the per-block kernels of refinement scans: one list of each kind for the plan, which a launch behind all levels
+// takes whole and a level its share of.
+void refine_tiles(const pcr_record* r, const std::vector<RefineLevel>& levels, Plan* plan, Uploads* up) {
+    size_t count = 0;
+    uint32_t planes = 0, covs = 0;
+    std::vector<uint32_t> plane_at, cov_at;
+    for (const RefineLevel& l : levels) {
+        plane_at.push_back(planes); cov_at.push_back(covs);
+        count += l.scans.size(); planes += l.planes; covs += l.covs;
     }
-    ll->n_plane_tiles = (uint32_t)plane_tiles.size(); ll->n_cov_tiles = (uint32_t)cov_tiles.size();
-    if (ll->n_plane_tiles) up->add(&ll->d_plane_tiles, plane_tiles);
-    if (ll->n_cov_tiles) up->add(&ll->d_cov_tiles, cov_tiles);
+    if (count == 0) return;
+    for (LevelList& ll : plan->levels) {
+        if (ll.kind != kAcRefine) continue;
+        const RefineLevel& l = levels[ll.level];
+        ll.plane_tile = plane_at[ll.level]; ll.n_plane_tiles = l.planes; ll.cov_tile = planes + cov_at[ll.level]; ll.n_cov_tiles = l.covs;
+    }
+    plan->cov_tile = planes; plan->n_cov_tiles = covs;
+    if (RefineScan* at = up->make(&plan->d_refine, count))
+        for (const RefineLevel& l : levels) at = std::copy(l.scans.begin(), l.scans.end(), at);
+    RefineTile* plane = up->make(&plan->d_refine_tiles, (size_t)planes + covs);
+    if (!plane) return;                                      // (the flush says so)
+    RefineTile* cov = plane + planes;
+    uint32_t e = 0;
+    for (const RefineLevel& l : levels)
+        for (const RefineScan& q : l.scans) {
+            const ImgDesc& im = r->img[q.img];
+            const ScanDesc& sd = r->scan[(size_t)q.img * r->hdr.G + q.scan];
+            for (uint32_t ch = 0, n = refine_chunks(im, sd, true); ch < n; ch++) *plane++ = RefineTile{e, ch};
+            for (uint32_t ch = 0, n = refine_chunks(im, sd, false); ch < n; ch++) *cov++ = RefineTile{e, ch};
+            e++;
+        }
 }
 
 // The chains of a plan (once, when a call first wants them).
@@ -274,16 +296,10 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
     if (plan->chains_built) return PCR_OK;
     const uint32_t n = r->hdr.n, G = r->hdr.G;
     ChainSet chains;
-    std::vector<RefineScan> refined;
     for (uint32_t i = 0; i < n && chains.possible; i++) {
         const uint32_t upto = std::min<uint32_t>(r->img[i].nscans, (uint32_t)k);
         const size_t at = (size_t)i * G;
         chains.add(i, &r->scan[at], &r->slot_cnt[at], &r->ent_off_h[at], (uint32_t)k0, upto);
-    }
-    for (uint32_t i = 0; i < n; i++) {
-        const size_t at = (size_t)i * G;
-        for (uint32_t g = (uint32_t)k0; g < std::min<uint32_t>(r->img[i].nscans, (uint32_t)k); g++)
-            if (r->scan[at + g].Ss > 0 && r->scan[at + g].Ah > 0) refined.push_back(RefineScan{i, g});
     }
     const bool in_step = chains.possible;
     if (!in_step) {                                          // the refinement scans follow level by level
@@ -312,7 +328,6 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
             for (const ScanChain& c : *set) plan->split.add(r->img[c.img], r->scan[(size_t)c.img * G + c.scan[0]], c.units);
     Uploads up(&r->big, &r->stage);
     if (plan->n_chains) { up.add(&plan->d_chain_units, units); up.add(&plan->d_chains, list); }
-    if (!refined.empty()) refine_tiles(r, refined, &plan->refined, false, &up);
     int rc = up.flush();
     if (!rc && (plan->split.pays(true) || plan->split.pays(false))) rc = arena_alloc(&r->big, &plan->d_chain_done, plan->n_chains);
     if (rc) return rc;
@@ -332,7 +347,9 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     struct Run { uint32_t img, scan, count, bytes, shape; };         // (shape: DC first scans)
     std::vector<std::vector<Run>> runs((size_t)r->max_level * kNumKinds);
     std::vector<DcLaunch> dc(r->max_level);
-    std::vector<std::vector<RefineScan>> rlists(r->max_level);
+    std::vector<LanesLaunch> lane_launch(runs.size());
+    std::vector<FirstSplitLaunch> dc_split(r->max_level);
+    std::vector<RefineLevel> refine_levels(r->max_level);
     std::vector<ApplyUnit> apply; uint32_t max_blk = 0;
     // (what the tables below take: every list is rounded up to kArenaAlign, jobs are one per window of scans at least)
     size_t plan_bytes = runs.size() * 6 * kArenaAlign + 2 * kArenaAlign + (size_t)n * kMaxComp * (sizeof(ApplyUnit) + sizeof(int32_t));
@@ -353,13 +370,18 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             const int kind = seq ? kSequential : (sd.Ss == 0 ? kDcFirst : (sd.Ah == 0 ? kAcFirst : kAcRefine));
             const uint32_t cnt = r->slot_cnt[ig];
             if (kind == kAcRefine) {
-                rlists[r->level[ig] - 1].push_back(RefineScan{i, g});
-                const int c = sd.comp[0];
-                plan_bytes += sizeof(RefineScan) + 2 * sizeof(RefineTile) * (((uint32_t)r->img[i].bw[c] * r->img[i].bh[c] + 255) / 256);
+                RefineLevel& l = refine_levels[r->level[ig] - 1];
+                const uint32_t planes = refine_chunks(r->img[i], sd, true), covs = refine_chunks(r->img[i], sd, false);
+                l.scans.push_back(RefineScan{i, g}); l.planes += planes; l.covs += covs;
+                plan_bytes += sizeof(RefineScan) + sizeof(RefineTile) * (planes + covs);
             }
             const size_t li = (size_t)(r->level[ig] - 1) * kNumKinds + kind;
             uint32_t shape = 0;
-            if (kind == kDcFirst) { shape = dc_mcu_shape(r->img[i], sd); dc[r->level[ig] - 1].add(r->img[i], sd, cnt); }
+            // (what the launches are judged by is gathered here, where the descriptors come one after the other: in the order of the runs, by
+            // length, it was a cache miss per scan.  First decode of a record of 1024 pictures of 60 to 90 pixels at scan group 6, us till the call
+            // returns: 465 and 437)
+            if (kind == kDcFirst) { shape = dc_mcu_shape(r->img[i], sd); dc[r->level[ig] - 1].add(r->img[i], sd, cnt); dc_split[r->level[ig] - 1].add(r->img[i], sd, cnt); }
+            else if (!seq) lane_launch[li].add(sd, cnt);
             if (cnt) runs[li].push_back(Run{i, g, cnt, sd.data_len / cnt, shape});
             plan_bytes += cnt * sizeof(Unit) + (cnt / kEntropyLanes + 1) * sizeof(LaneJob);   // (more than dc_units_by_shape's starts take)
         }
@@ -401,7 +423,7 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             });
             ll.n_dc_waves = starts.empty() ? (ll.n + kEntropyLanes - 1) / kEntropyLanes : (uint32_t)starts.size() - 1;
             if (!starts.empty()) up.add(&ll.d_dc_starts, starts);
-            for (const Run& q : rn) ll.split.add(r->img[q.img], r->scan[(size_t)q.img * G + q.scan], q.count);
+            ll.split = dc_split[li / kNumKinds];
             if (ll.split.pays(true)) { const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc; }
         }
         for (size_t w0 = 0; w0 < rn.size() && ll.kind != kDcFirst; w0 += kLaneTabs) {
@@ -435,8 +457,8 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         }
         ll.level = (uint32_t)(li / kNumKinds);
         if (!jobs.empty()) {
+            ll.lanes = lane_launch[li];
             ll.n_jobs = ll.lanes.jobs = (uint32_t)jobs.size();
-            for (const Run& q : rn) ll.lanes.add(r->scan[(size_t)q.img * G + q.scan], q.count);
             up.add(&ll.d_jobs, jobs);
         }
         if (ll.kind == kSequential) {
@@ -448,11 +470,8 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             }
             if (ll.n_long) { const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc; }
         }
-        if (ll.kind == kAcRefine) {
-            const auto& rl = rlists[li / kNumKinds];
-            refine_tiles(r, rl, &ll, true, &up);
-        }
     }
+    refine_tiles(r, refine_levels, &plan, &up);
     plan.n_apply = (uint32_t)apply.size();
     plan.apply_grid_x = (max_blk * 64 + kApplyChunk - 1) / kApplyChunk;
     if (plan.n_apply) {
@@ -738,25 +757,25 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
             mark(r, PCR_STAGE_AC_FIRST, s);
         }
         else if (by_lanes[li]) {
-            if (l.n_plane_tiles) hipLaunchKernelGGL(k_refine_history, dim3(l.n_plane_tiles), dim3(256), 0, s, r->d, l.d_refine, l.d_plane_tiles);
+            if (l.n_plane_tiles) hipLaunchKernelGGL(k_refine_history, dim3(l.n_plane_tiles), dim3(256), 0, s, r->d, plan->d_refine, plan->d_refine_tiles + l.plane_tile);
             mark(r, PCR_STAGE_REFINE_BLOCKS, s);
             hipLaunchKernelGGL(k_ac_refine_lanes, dim3(l.n_jobs), block, 0, s, r->d, l.d_units, l.d_jobs, c32);
             mark(r, PCR_STAGE_AC_REFINE, s);
-            if (l.n_cov_tiles) hipLaunchKernelGGL(k_refine_deal, dim3(l.n_cov_tiles), dim3(256), 0, s, r->d, l.d_refine, l.d_cov_tiles);
+            if (l.n_cov_tiles) hipLaunchKernelGGL(k_refine_deal, dim3(l.n_cov_tiles), dim3(256), 0, s, r->d, plan->d_refine, plan->d_refine_tiles + l.cov_tile);
             mark(r, PCR_STAGE_REFINE_BLOCKS, s);
         }
         else {
             waves(l);
             mark(r, PCR_STAGE_AC_REFINE, s);
-            if (l.n_cov_tiles && !side_by_side) hipLaunchKernelGGL(k_refine_blocks, dim3(l.n_cov_tiles), dim3(256), 0, s, r->d, l.d_refine, l.d_cov_tiles);
+            if (l.n_cov_tiles && !side_by_side) hipLaunchKernelGGL(k_refine_blocks, dim3(l.n_cov_tiles), dim3(256), 0, s, r->d, plan->d_refine, plan->d_refine_tiles + l.cov_tile);
             mark(r, PCR_STAGE_REFINE_BLOCKS, s);
         }
     }
     // The blocks of all refinement scans the wavefronts have walked, in one launch: of an earlier refinement scan a later one needs
     // what the wavefronts themselves leave (kRefNz, kRefHist).  (A launch behind every level held up the next one: 256 pictures
     // of 17 to 320 pixels with entry points at scan group 10 358 us a call with two launches of 26, 345 with one.)
-    if (side_by_side && plan->refined.n_cov_tiles)
-        hipLaunchKernelGGL(k_refine_blocks, dim3(plan->refined.n_cov_tiles), dim3(256), 0, s, r->d, plan->refined.d_refine, plan->refined.d_cov_tiles);
+    if (side_by_side && plan->n_cov_tiles)
+        hipLaunchKernelGGL(k_refine_blocks, dim3(plan->n_cov_tiles), dim3(256), 0, s, r->d, plan->d_refine, plan->d_refine_tiles + plan->cov_tile);
     if (plan->n_apply) {
         if (r->timing) hipLaunchKernelGGL(k_apply_prep, dim3(list_groups), dim3(64 * kApplyPrepWaves), 0, s, r->d, lists);
         if (refine_in_memory)
