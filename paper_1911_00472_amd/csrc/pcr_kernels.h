@@ -2700,9 +2700,14 @@ __global__ void __launch_bounds__(kFlatLanes) k_pixel_smooth_flat(DevRecord R, c
 // atomics in LDS: 318).  us a launch, with a workgroup of 256 lanes and 64 KB per MCU row that converted four pixels for every output
 // sample, and now: 512 photographs to 224 x 224 at scan group 5 342 / 227, at 10 390 / 290; 2048 of 26 x 26 to 96 311 / 92; 1485 of 57 x 32
 // to 160 385 / 126; 2048 of 169 x 126 to 160 622 / 193; 2048 of 64 x 64 to 224 1067 / 270; 300 gray of 300 to 500 180 / 64; 200 of
-// 4:4:4 180 / 124; 64 of 1024 x 1024 to 224 123 / 136.
+// 4:4:4 180 / 124; 64 of 1024 x 1024 to 224 123 / 123 (kTailSparse).
 // --------------------------------------------------------------------------------------
 constexpr int kTailLanes = kPixLanes;
+// Colour pictures whose box has this many rows to an output row and more: an output row wants two of them, so a third of the rows and more
+// is wanted by nobody, and a lane has a group of one wanted row instead of one of two rows.  us a launch, all rows / the wanted ones: 64 of 1024 x 1024 to 224 x 224
+// 133 / 123, to 96 123 / 98; us a call: 512 photographs to 128 500 / 500 (a few boxes above the line), 100 of 700 x 800 to 96 374 / 363.  (From twofold
+// on: gray pictures of 400 x 400 to 180 638 / 645, colour ones the same; gray pixels are hardly any work, to 64 625 / 629.)
+constexpr int kTailSparse = 3;
 struct TailParams { int out_h, out_w; float mean[3], istd[3]; };
 // MCUs of a run, runs of an MCU row (whatever its box), and LDS of a workgroup: the samples of half a run, and its pixels in their place
 PCR_HD uint32_t tail_run(const ImgDesc& d) { const uint32_t per = pixel_mcus_per_tile(d); return per < d.mcux ? per : d.mcux; }
@@ -2786,14 +2791,21 @@ __global__ void __launch_bounds__(kTailLanes, 4) k_pixel_tail(DevRecord R, const
     const int xs = max(b.x0, (int)xorg), xe = last ? b.x0 + b.w : (int)(s1 * mcu_px_w);      // source columns served here: [xs, xe)
     // output rows and columns served here, [lo, hi) x [left, right): every wavefront looks by itself (with lanes of both and atomics in LDS it
     // took longer)
+    // Sparse: pixel rows that no output row and no neighbouring MCU row wants are not converted (wanted: a bit per row).
     int lo = 1 << 30, hi = 0, left = 1 << 30, right = 0;
+    const bool above = (int)ylo > b.y0, below = (int)yhi < b.y0 + b.h, sparse = !kGray && b.h >= kTailSparse * P.out_h;
+    uint32_t wanted = sparse ? (above ? 1u : 0u) | (below ? 1u << (yhi - 1 - ylo) : 0u) : ~0u;
     {
         int o0, o1;
         tail_range(P.out_h, b.h, (int)ylo - b.y0, (int)yhi - b.y0, &o0, &o1);
         for (; o0 < o1; o0 += 64) {
             const TailTap y = tail_row(b, min(o0 + (int)lane, P.out_h - 1), P.out_h);
-            const uint64_t in = __ballot(o0 + (int)lane < o1 && y.a >= (int)ylo && y.b < (int)yhi);
+            uint64_t in = __ballot(o0 + (int)lane < o1 && y.a >= (int)ylo && y.b < (int)yhi);
             if (in) { lo = min(lo, o0 + __builtin_ctzll(in)); hi = o0 + 64 - __builtin_clzll(in); }
+            for (; sparse && in; in &= in - 1) {
+                const int l = __builtin_ctzll(in);
+                wanted |= 1u << (__builtin_amdgcn_readlane(y.a, l) - (int)ylo) | 1u << (__builtin_amdgcn_readlane(y.b, l) - (int)ylo);
+            }
         }
         tail_range(P.out_w, b.w, xs - b.x0, xe - b.x0, &o0, &o1);
         for (; o0 < o1; o0 += 64) {
@@ -2829,6 +2841,39 @@ __global__ void __launch_bounds__(kTailLanes, 4) k_pixel_tail(DevRecord R, const
             s[0] = s[1] = s[2] = s[3] = f;
         } else four_samples(tile + mm * mstride + (G.rb[c] >> 1) + (ly >> shy) * G.rs[c], x0, shx, s);
     };
+    // the pixels of a group in one row (of the half whose samples lie in LDS)
+    auto convert = [&](uint32_t mm, uint32_t ly, uint32_t x0, uint32_t w[3]) {
+        if (kGray) {
+#pragma unroll
+            for (uint32_t h = 0; h < 2; h++) {
+                float a[4];
+                fetch(0, mm, ly, x0 + 4 * h, 0, 0, a);
+                w[h] = four_u8(a[0], a[1], a[2], a[3]);
+            }
+        } else {
+            float ys[4], cb[4], cr[4];
+            fetch(0, mm, ly, x0, shx0, shy0, ys); fetch(1, mm, ly, x0, shx1, shy1, cb); fetch(2, mm, ly, x0, shx2, shy2, cr);
+#pragma unroll
+            for (int i = 0; i < 4; i++) { cb[i] -= 128.f; cr[i] -= 128.f; }
+            rgb_words(ys, cb, cr, w);
+        }
+    };
+    // Sparse: the wanted rows of each half alone, a lane per group of one row: their numbers, four bits each, and how many groups there are.
+    uint32_t row_list[2] = {0, 0}, row_items[2] = {0, 0};
+    if (sparse) {
+#pragma unroll
+        for (uint32_t half = 0; half < 2; half++) {
+            uint32_t some = (wanted >> (half * half_h)) & ((1u << half_h) - 1u), n = 0;
+            for (; some; some &= some - 1, n++) row_list[half] |= (uint32_t)__builtin_ctz(some) << (4 * n);
+            row_items[half] = n * nm * gpm;
+        }
+    }
+    // Where group `it` is: its MCU, the number of its row pair (sparse: of its row in the list), its first pixel.
+    struct Place { uint32_t mm, n, x0; };
+    auto place = [&](uint32_t it) {
+        const uint32_t q = it >> lg, n = nm > 1 ? __umulhi(q, rcpn) : q;
+        return Place{q - n * nm, n, (it & (gpm - 1)) * ppg};
+    };
 #pragma unroll
     for (int half = 0; half < 2; half++) {
         if (half) __syncthreads();                          // (the upper half has been read)
@@ -2838,55 +2883,61 @@ __global__ void __launch_bounds__(kTailLanes, 4) k_pixel_tail(DevRecord R, const
             else pix_put_half<1>(S, flatb, B.vs, by, dst, B.hs * 8);
         }
         __syncthreads();
+        if (sparse) {
 #pragma unroll
-        for (uint32_t t = 0; t < kTrips; t++) {
-            const uint32_t it = tid + t * kTailLanes;
-            uint32_t (*const w)[3] = px[half][t];
+            for (uint32_t e = 0; e < 2 * kTrips; e++) {
+                const uint32_t it = tid + e * kTailLanes;
+                uint32_t* const w = px[half][e >> 1][e & 1];
+                w[0] = w[1] = w[2] = 0;
+                if (it >= row_items[half] || dead) continue;
+                const Place p = place(it);
+                convert(p.mm, (row_list[half] >> (4 * p.n)) & 15u, p.x0, w);
+            }
+        } else {
 #pragma unroll
-            for (int e = 0; e < 6; e++) w[e / 3][e % 3] = 0;
-            if (it >= items || dead) continue;
-            const uint32_t g = it & (gpm - 1), q = it >> lg;
-            const uint32_t lyp = nm > 1 ? __umulhi(q, rcpn) : q, mm = q - lyp * nm, ly = 2 * lyp, x0 = g * ppg;
-            if (kGray) {
+            for (uint32_t t = 0; t < kTrips; t++) {
+                const uint32_t it = tid + t * kTailLanes;
+                uint32_t (*const w)[3] = px[half][t];
 #pragma unroll
-                for (uint32_t e = 0; e < 4; e++) {
-                    float a[4];
-                    fetch(0, mm, ly + (e >> 1), x0 + 4 * (e & 1), 0, 0, a);
-                    w[e >> 1][e & 1] = four_u8(a[0], a[1], a[2], a[3]);
-                }
-            } else {
+                for (int e = 0; e < 6; e++) w[e / 3][e % 3] = 0;
+                if (it >= items || dead) continue;
+                const Place p = place(it);
 #pragma unroll
-                for (uint32_t row = 0; row < 2; row++) {
-                    float ys[4], cb[4], cr[4];
-                    fetch(0, mm, ly + row, x0, shx0, shy0, ys); fetch(1, mm, ly + row, x0, shx1, shy1, cb); fetch(2, mm, ly + row, x0, shx2, shy2, cr);
-#pragma unroll
-                    for (int i = 0; i < 4; i++) { cb[i] -= 128.f; cr[i] -= 128.f; }
-                    rgb_words(ys, cb, cr, w[row]);
-                }
+                for (uint32_t row = 0; row < 2; row++) convert(p.mm, 2 * p.n + row, p.x0, w[row]);
             }
         }
     }
     __syncthreads();
     uint32_t* const words = reinterpret_cast<uint32_t*>(tile);
-#pragma unroll
-    for (uint32_t e = 0; e < 4 * kTrips; e++) {
-        const uint32_t half = e & 1, row = (e >> 1) & 1, t = e >> 2, it = tid + t * kTailLanes;
-        if (it >= items) continue;
-        const uint32_t g = it & (gpm - 1), q = it >> lg;
-        const uint32_t lyp = nm > 1 ? __umulhi(q, rcpn) : q, mm = q - lyp * nm;
-        const uint32_t* const w = px[half][t][row];
-        uint32_t* const to = words + (half * half_h + 2 * lyp + row) * pitch + mm * mcu_px_w + g * ppg;
+    auto leave = [&](const Place& p, uint32_t y, const uint32_t w[3]) {
+        uint32_t* const to = words + y * pitch + p.mm * mcu_px_w + p.x0;
         if (kGray) {
 #pragma unroll
             for (int h = 0; h < 2; h++) *reinterpret_cast<uint4*>(to + 4 * h) = uint4{w[h] & 255u, (w[h] >> 8) & 255u, (w[h] >> 16) & 255u, w[h] >> 24};
         } else                                              // (a word's top byte is another pixel's)
             *reinterpret_cast<uint4*>(to) = uint4{w[0], __builtin_amdgcn_alignbyte(w[1], w[0], 3), __builtin_amdgcn_alignbyte(w[2], w[1], 2), w[2] >> 8};
+    };
+    if (sparse) {
+#pragma unroll
+        for (uint32_t e = 0; e < 4 * kTrips; e++) {
+            const uint32_t half = e & 1, slot = e >> 1, it = tid + slot * kTailLanes;
+            if (it >= row_items[half]) continue;
+            const Place p = place(it);
+            leave(p, half * half_h + ((row_list[half] >> (4 * p.n)) & 15u), px[half][slot >> 1][slot & 1]);
+        }
+    } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 4 * kTrips; e++) {
+            const uint32_t half = e & 1, row = (e >> 1) & 1, t = e >> 2, it = tid + t * kTailLanes;
+            if (it >= items) continue;
+            const Place p = place(it);
+            leave(p, half * half_h + 2 * p.n + row, px[half][t][row]);
+        }
     }
     __syncthreads();
     // ---- the first and the last pixel row, for the output rows that need a neighbouring MCU row as well ----
     {
         const int span = xe - xs;
-        const bool above = (int)ylo > b.y0, below = (int)yhi < b.y0 + b.h;
         uint32_t* const e = edge + edge0 + (size_t)(2 * my) * W + xs;
         const uint32_t* const w = words + (xs - (int)xorg);
         for (int x = (int)tid; x < span; x += kTailLanes) {

@@ -234,6 +234,35 @@ def test_runs_of_the_fused_tail_at_their_ends(C, hs, vs, per, px):
                     assert torch.equal(got, want), (t, oh, ow, k, int((got != want).sum()))
 
 
+@pytest.mark.parametrize("C,hs,vs", [(3, 2, 2), (3, 1, 1), (3, 2, 1), (3, 1, 2), (1, 1, 1)])
+def test_boxes_of_which_few_rows_are_wanted(C, hs, vs):
+    """Around three box rows to an output row, where the fused kernel begins to convert the wanted rows alone: exactly, one less, one more; up to a
+    whole picture to one row; boxes from every row of an MCU on, so that wanted rows lie in every place, first and last rows of an MCU row and
+    boundaries between two among them; damaged pictures beside good ones."""
+    torch = _torch()
+    W, H, oh = 353, 217, 20
+    files = [pcrgen.make_jpeg(970 + i, 1, W, H, C, 9.0, hs, vs, 88) for i in range(18)]
+    rec = pcrgen.write_record(files)
+    bad = bytearray(rec)
+    off, ln, _, _, _ = oracle.record_index(rec)
+    at = int(off[0, 5]) + int(ln[0, 5]) - 80
+    bad[at:at + 80] = b"\xff\xd9" + bytes(78)
+    mean, istd = (MEAN, ISTD) if C == 3 else (MEAN[:1], ISTD[:1])
+    for data in (rec, bytes(bad)):
+        with pkg.pcr_open(data, 0) as r:
+            for t, (size, ow) in enumerate([((3 * oh - 1, 90), 31), ((3 * oh, 300), 64), ((3 * oh + 1, 353), 117), ((7 * oh, 200), 350), ((190, 353), 5)]):
+                boxes = [(0 if i % 3 else W - size[1], i, size[1], size[0], i & 1) for i in range(r.n)]
+                tb = torch.tensor(boxes, dtype=torch.int32, device="cuda")
+                for h in (oh, 1, 3):
+                    for k in (1, r.G):
+                        want = r.crop_resize_batch(r.decode_batch(k), tb, h, ow, mean, istd)
+                        got = torch.full_like(want, 9.0)
+                        st = torch.full((r.n,), 77, dtype=torch.int32, device="cuda")
+                        r.decode_crop_batch(k, tb, h, ow, mean, istd, pixels=None, out=got, status=st)
+                        assert torch.equal(got, want), (t, h, k, int((got != want).sum()))
+                        assert [i for i in range(r.n) if int(st[i])] == ([5] if data is not rec else []), (t, h, k)
+
+
 def test_tail_argument_errors(gray64):
     torch = _torch()
     g = [pcrgen.make_jpeg(i, 0, 40, 24, 1, 8.0, 1, 1, 90) for i in range(2)]
