@@ -410,16 +410,22 @@ int pcr_transcode_batch(pcr_record* rec, const void* const* files, const size_t*
  * wavefronts would decode them in the launch of the AC scans, and from 6144 where not (whole scans of 64 to 768 blocks: 3584 or
  * 4608).  If the process has more than one record open, from 4096 units on that count as 2000 at least (3000, if the longest
  * has more than 768 blocks).
- * 1: lanes wherever the kernels exist and the record's scans have several units; -1: never.
+ * First scans for the wavefronts that take one of them long go to many lanes each ahead of that launch, which decodes what those leave
+ * (streams that do not fall into step); pcr_last_first_splits tells.
+ * 1: lanes wherever the kernels exist and the record's scans have several units; -1: never, and no first scans by many lanes either.
  * The results are the same bit for bit.  Takes effect from the next decode call.  PCR_E_ARG: null handle or another
  * mode. */
 int pcr_set_lane_decoders(pcr_record* rec, int mode);
 /* How the last decode call on this handle decoded its AC scans: launches that gave every unit a lane, launches that gave
  * every unit a wavefront (host ints; both 0 before the first call or when only DC scans were decoded). */
 int pcr_last_decoder_shapes(pcr_record* rec, int* lane_launches, int* wavefront_launches);
+/* Launches of the last decode call that gave every first scan (AC or DC) many lanes, ahead of those for the wavefronts, and how many
+ * of them a thousand lanes each instead of 256 (host ints). */
+int pcr_last_first_splits(pcr_record* rec, int* launches, int* wide_launches);
 
 /* Stage timing with HIP events recorded on the call's own stream (off by default; switching it on
- * starts a new history).  While it is on, every stage has launches of its own.  Without it, scans for the wavefront
+ * starts a new history).  While it is on, every stage has launches of its own, and first scans are not given many lanes each (DC_FIRST and
+ * AC_FIRST of plain records then take up to twenty times as long as in an ordinary call).  Without it, scans for the wavefront
  * decoders share one launch where they can, whatever their stage, DC and AC first scans for the lanes share one, and the lists of
  * REFINE_APPLY are made by the launch that unstuffs: the times reported are those of launches that an ordinary call does not
  * make (512 photographs without entry points: 6.7 ms, stage by stage 15).  A stage is one kernel or a short run of kernels:

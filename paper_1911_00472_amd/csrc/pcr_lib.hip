@@ -222,6 +222,7 @@ struct pcr_record {
     bool several_units = false;             // some scan has several units (restart intervals, entry points): lane decoders are worth considering
     int lane_mode = 0;                      // pcr_set_lane_decoders: 0 by the number of units, 1 wherever possible, -1 never
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
+    int last_splits = 0, last_wide_splits = 0;            // ... launches of k_first_split, and those with a thousand lanes a unit
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
     std::vector<uint32_t> unit_bits;        // records opened from host bytes: entropy-coded bits of every unit, by slot (else empty)
     // decode fused with the training tail (allocated at its first call): one tile per run of an MCU row, the side buffer of first
@@ -642,7 +643,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
     const bool several = g_open_records.load(std::memory_order_relaxed) > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
-    r->last_lane_launches = r->last_wave_launches = 0;
+    r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
         if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
@@ -715,7 +716,9 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // Long first scans by many lanes each, ahead of the wavefronts, which take what is left: null, or what is not.
     auto split = [&](const FirstSplitLaunch& sp, bool with_dc, const Unit* units, uint32_t n_units, uint32_t* done) -> const uint32_t* {
         if (!done || r->timing || r->lane_mode < 0 || !sp.pays(with_dc)) return nullptr;
-        if (sp.wide(with_dc)) hipLaunchKernelGGL(k_first_split<1024>, dim3(n_units), dim3(1024), 0, s, r->d, units, done, c32, dc_to_planes ? 1u : 0u);
+        const bool wide = sp.wide(with_dc);
+        r->last_splits++; r->last_wide_splits += wide ? 1 : 0;
+        if (wide) hipLaunchKernelGGL(k_first_split<1024>, dim3(n_units), dim3(1024), 0, s, r->d, units, done, c32, dc_to_planes ? 1u : 0u);
         else hipLaunchKernelGGL(k_first_split<256>, dim3(n_units), dim3(256), 0, s, r->d, units, done, c32, dc_to_planes ? 1u : 0u);
         return done;
     };
@@ -1414,6 +1417,12 @@ int pcr_set_lane_decoders(pcr_record* r, int mode) {
 int pcr_last_decoder_shapes(pcr_record* r, int* lane_launches, int* wavefront_launches) {
     if (!r || !lane_launches || !wavefront_launches) return PCR_E_ARG;
     *lane_launches = r->last_lane_launches; *wavefront_launches = r->last_wave_launches;
+    return PCR_OK;
+}
+
+int pcr_last_first_splits(pcr_record* r, int* launches, int* wide_launches) {
+    if (!r || !launches || !wide_launches) return PCR_E_ARG;
+    *launches = r->last_splits; *wide_launches = r->last_wide_splits;
     return PCR_OK;
 }
 

@@ -42,8 +42,8 @@ extern "C" int chain_plan(const int* scans, int count, int k0, int k, int* out) 
     return in_step;
 }
 
-// The DC first scans of scan groups 1 .. k of a record, as one launch: units, scans, blocks.
-static int dc_launch(const uint8_t* rec, size_t nbytes, uint32_t k, DcLaunch* L) {
+// The scans of scan groups 1 .. k of a record: each(image, its scans, number of the scan, its units).
+template <class Each> static int each_scan(const uint8_t* rec, size_t nbytes, uint32_t k, const Each& each) {
     RecordHeader h;
     const int rc = parse_record_header(rec, nbytes, &h);
     if (rc) return rc;
@@ -61,12 +61,37 @@ static int dc_launch(const uint8_t* rec, size_t nbytes, uint32_t k, DcLaunch* L)
         if (img.status) return img.status;
         for (uint32_t g = 0; g < img.nscans; g++) {
             const ScanDesc& sd = sc[g];
-            if (sd.Ss != 0 || sd.Ah != 0 || is_sequential_scan(sd)) continue;
             const uint32_t entries = h.version == 2 && sd.ri == 0 ? entry_count(ld_le16(rec + hdr_ecount_pos(n, G, g, i))) : 0;
-            L->add(img, sd, sd.ri ? (sd.mcus + sd.ri - 1) / sd.ri : 1 + entries);
+            each(img, sc.data(), g, sd.ri ? (sd.mcus + sd.ri - 1) / sd.ri : 1 + entries);
         }
     }
     return 0;
+}
+// The DC first scans, as one launch: units, scans, blocks.
+static int dc_launch(const uint8_t* rec, size_t nbytes, uint32_t k, DcLaunch* L) {
+    return each_scan(rec, nbytes, k, [&](const ImgDesc& img, const ScanDesc* sc, uint32_t g, uint32_t units) {
+        if (sc[g].Ss == 0 && sc[g].Ah == 0 && !is_sequential_scan(sc[g])) L->add(img, sc[g], units);
+    });
+}
+// The first scans: out: whether many lanes a scan pay, and a thousand of them.
+extern "C" int first_split_of(const uint8_t* rec, size_t nbytes, uint32_t k, int with_dc, uint32_t* out) {
+    FirstSplitLaunch L;
+    const int rc = each_scan(rec, nbytes, k, [&](const ImgDesc& img, const ScanDesc* sc, uint32_t g, uint32_t units) { L.add(img, sc[g], units); });
+    out[0] = L.pays(with_dc != 0); out[1] = out[0] && L.wide(with_dc != 0); out[2] = L.units; out[3] = L.dc_units;
+    return rc;
+}
+// The AC scans of one level (0: the first scans), as one launch of so many jobs: out: whether it goes to the lanes, whether it would by the
+// number of its units, that number, blocks of the longest.
+extern "C" int lanes_launch_of(const uint8_t* rec, size_t nbytes, uint32_t k, uint32_t level, uint32_t jobs, int several, uint32_t* out) {
+    LanesLaunch L;
+    const int rc = each_scan(rec, nbytes, k, [&](const ImgDesc&, const ScanDesc* sc, uint32_t g, uint32_t units) {
+        std::vector<uint8_t> at(g + 1);
+        scan_levels(sc, g + 1, at.data());
+        if (sc[g].Ss > 0 && !is_sequential_scan(sc[g]) && at[g] == level + 1) L.add(sc[g], units);
+    });
+    L.jobs = jobs;
+    out[0] = L.by_lanes(level > 0, several != 0); out[1] = L.many(several != 0); out[2] = L.units; out[3] = L.longest_blocks;
+    return rc;
 }
 extern "C" int dc_launch_of(const uint8_t* rec, size_t nbytes, uint32_t k, uint32_t* out) {
     DcLaunch L;

@@ -168,3 +168,40 @@ def test_a_dc_scan_s_shape_is_of_its_own_components(plan):
     assert of(1, (0, 0, 0), (2, 1, 1), (2, 1, 1)) == of(1, (2, 0, 0), (1, 1, 1), (1, 1, 1))
     assert of(3, (0, 1, 2), (2, 1, 1), (2, 1, 1)) != of(3, (0, 1, 2), (2, 1, 1), (1, 1, 1))
     assert of(2, (0, 1, 0), (2, 1, 1), (2, 1, 1)) != of(2, (0, 1, 0), (1, 1, 1), (1, 1, 1))
+
+
+def _asked(plan, name, rec, *args):
+    u32p, u8p = ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(ctypes.c_uint8)
+    a, out = np.frombuffer(rec, np.uint8), np.zeros(4, np.uint32)
+    f = getattr(plan.lib, name)
+    f.argtypes = [u8p, ctypes.c_size_t] + [ctypes.c_uint32] * len(args) + [u32p]
+    assert f(a.ctypes.data_as(u8p), a.size, *args, out.ctypes.data_as(u32p)) == 0
+    return [int(v) for v in out]
+
+
+def test_first_scans_the_gpu_tests_give_many_lanes(plan):
+    """The rule says of the records of the GPU tests of first scans by many lanes what those say that the launches were."""
+    import test_gpu_first_split as gpu
+    records = [gpu.size_record(*s, side) for side in gpu.SIZES for s in gpu.SAMPLINGS] + [(gpu.mixed_record(), {1: gpu.YES, 2: gpu.WIDE, 5: gpu.WIDE})]
+    for rec, splits in records:
+        for k, want in splits.items():
+            assert tuple(_asked(plan, "first_split_of", rec, k, 1)[:2]) == want, k
+
+
+def test_ac_launches_the_gpu_tests_send_to_the_lanes(plan):
+    """The same of the launches of first scans that go to the lanes by themselves (a job: sixty units of scans that share its tables); one
+    record's are by lanes for their bits and blocks, and would not be by their number."""
+    import paper_1911_00472_amd as pkg
+    import pcrgen
+    import test_gpu_lane_decoders as gpu
+    below = 0
+    for side, n, entry, restart, shapes in gpu.BY_THEMSELVES:
+        some = [pcrgen.make_jpeg(60 + i, 1 + (i % 2), side - 3 * i, side + i, 3, 12.0, 2, 2, 80, restart=restart) for i in range(6)]
+        files = [some[i % 6] for i in range(n)]
+        rec = pkg.record_write_indexed(files, None, entry) if entry else pcrgen.write_record(files)
+        for k, (lanes, _) in zip((2, 5), shapes):
+            units = _asked(plan, "lanes_launch_of", rec, k, 0, 1, 0)[2]
+            got, many, _, _ = _asked(plan, "lanes_launch_of", rec, k, 0, units // 60, 0)
+            assert got == lanes, (side, n, k)
+            below += got and not many
+    assert below >= 3

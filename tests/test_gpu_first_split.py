@@ -13,8 +13,13 @@ from test_record_entry_points import _entry_at
 pytestmark = pytest.mark.gpu
 
 
-def _both(rec, ks, check=()):
-    """Coefficients, pixels and status of the decoder the rule picks and of the wavefront decoders are the same; some images, the oracle's."""
+NO, YES, WIDE = (0, 0), (1, 0), (1, 1)                       # launches of many lanes a scan; those of them of a thousand lanes
+
+
+def _both(rec, splits, check=()):
+    """Coefficients, pixels and status of the decoder the rule picks and of the wavefront decoders are the same; some images, the oracle's.
+    splits: {k: the launches of many lanes a scan there are}."""
+    ks = sorted(splits)
     with pkg.pcr_open(rec, 0) as r:
         clay = r.coef_layout()
         for k in ks:
@@ -23,6 +28,8 @@ def _both(rec, ks, check=()):
                 r.set_lane_decoders(mode)
                 st = torch.full((r.n,), 77, dtype=torch.int32, device="cuda")
                 pix = r.decode_batch(k, status=st).cpu().numpy().copy()
+                took = r.last_first_splits()
+                assert took == ((0, 0) if mode else splits[k]), (k, mode, took)
                 got.append((r.decode_coefficients(k).cpu().numpy().copy(), pix, st.cpu().numpy().copy()))
             good = got[0][2] == 0
             assert np.array_equal(got[0][2], got[1][2]), (k, got[0][2], got[1][2])
@@ -37,12 +44,34 @@ def _both(rec, ks, check=()):
         return got[0][2]
 
 
-@pytest.mark.parametrize("C,hs,vs", [(1, 1, 1), (3, 1, 1), (3, 2, 1), (3, 1, 2), (3, 2, 2)])
-@pytest.mark.parametrize("side", [40, 100, 257, 640])
-def test_every_sampling_and_size(C, hs, vs, side):
+SAMPLINGS = [(1, 1, 1), (3, 1, 1), (3, 2, 1), (3, 1, 2), (3, 2, 2)]
+# by side, in the order of SAMPLINGS: at 1, 2, 3 (and 5)
+SIZES = {40: ["nnn", "nnnn", "nnnn", "nnnn", "nnnn"], 100: ["nyy", "nnyy", "nnny", "nnny", "nnny"], 257: ["yyy", "yyyy", "nnyy", "nnyy", "nyyy"],
+         640: ["yww", "ywww", "ywww", "ywww", "ywww"]}
+
+
+def size_record(C, hs, vs, side):
+    """A record of three pictures and the launches a decode of it makes."""
     files = [pcrgen.make_jpeg(30 + side + i, i % 3, side, side + 7 * i, C, 3.0 + 12 * i, hs, vs, 80 + 6 * i) for i in range(3)]
-    st = _both(pcrgen.write_record(files), (1, 2, 3) if C == 1 else (1, 2, 3, 5), check=(0, 2))
-    assert (st == 0).all()
+    takes = SIZES[side][SAMPLINGS.index((C, hs, vs))]
+    return pcrgen.write_record(files), {k: {"n": NO, "y": YES, "w": WIDE}[t] for k, t in zip((1, 2, 3, 5), takes)}
+
+
+@pytest.mark.parametrize("C,hs,vs", SAMPLINGS)
+@pytest.mark.parametrize("side", sorted(SIZES))
+def test_every_sampling_and_size(C, hs, vs, side):
+    rec, splits = size_record(C, hs, vs, side)
+    assert (_both(rec, splits, check=(0, 2)) == 0).all()
+
+
+def mixed_record():
+    """A picture that is worth many lanes beside pictures of a few blocks."""
+    small = [(8, 8, 1, 1), (17, 9, 2, 2), (40, 33, 2, 1), (24, 40, 1, 2), (60, 50, 1, 1), (100, 90, 2, 2), (9, 120, 2, 1)]
+    return pcrgen.write_record([pcrgen.make_jpeg(400 + i, 1, w, h, 3, 20.0, hs, vs, 92) for i, (w, h, hs, vs) in enumerate([(900, 700, 2, 2)] + small)])
+
+
+def test_scans_of_one_piece_beside_scans_of_thousands():
+    assert (_both(mixed_record(), {1: YES, 2: WIDE, 3: WIDE, 5: WIDE}, check=range(8)) == 0).all()
 
 
 def test_streams_that_hardly_fall_into_step():
@@ -51,32 +80,34 @@ def test_streams_that_hardly_fall_into_step():
     half = flat.copy()
     half[:450] = np.random.default_rng(3).integers(0, 256, (450, 900, 3), dtype=np.uint8)
     files = [pcrgen.encode_pixels(a, hs, hs, q) for a in (flat, ramp, half) for hs, q in ((2, 75), (1, 95))]
-    assert (_both(pcrgen.write_record(files), (1, 2, 5), check=(2, 5)) == 0).all()
+    assert (_both(pcrgen.write_record(files), {1: YES, 2: WIDE, 5: WIDE}, check=(2, 5)) == 0).all()
 
 
-@pytest.mark.parametrize("n,side", [(70, 500), (300, 200)])
-def test_more_units_than_find_room_at_once(n, side):
+@pytest.mark.parametrize("n,side,splits", [(70, 500, {1: YES, 5: WIDE}), (300, 200, {1: NO, 5: NO}), (300, 400, {1: YES, 2: YES, 5: YES}), (600, 300, {1: NO, 5: YES})])
+def test_more_units_than_find_room_at_once(n, side, splits):
     files = [pcrgen.make_jpeg(500 + i, 1, side - 7 * i, side + i, 3, 20.0, 2 - i % 2, 2 - i % 2, 90) for i in range(5)]
-    assert (_both(pcrgen.write_record((files * n)[:n]), (1, 5), check=(0, 1)) == 0).all()
+    assert (_both(pcrgen.write_record((files * n)[:n]), splits, check=(0, 1)) == 0).all()
 
 
 def test_restart_intervals_and_entry_points_far_apart():
     files = [pcrgen.make_jpeg(610 + i, 1, 700, 500, 3, 15.0, 2, 2, 90, restart=12 if i % 2 else 0) for i in range(4)]
-    assert (_both(pcrgen.write_record(files), (1, 5), check=(0, 1)) == 0).all()
-    assert (_both(pkg.record_write_indexed(files, None, 4096), (1, 2, 5), check=(0, 1)) == 0).all()
+    assert (_both(pcrgen.write_record(files), {1: YES, 5: YES}, check=(0, 1)) == 0).all()
+    assert (_both(pkg.record_write_indexed(files, None, 4096), {1: YES, 2: YES, 5: YES}, check=(0, 1)) == 0).all()
 
 
 def test_one_long_scan_takes_a_thousand_lanes():
     files = [pcrgen.make_jpeg(640, 2, 1100, 1000, 3, 30.0, 1, 1, 97)]
-    assert (_both(pcrgen.write_record(files), (1, 4, 5), check=(0,)) == 0).all()
+    assert (_both(pcrgen.write_record(files), {1: YES, 4: WIDE, 5: WIDE}, check=(0,)) == 0).all()
 
 
 def test_upgrades_start_from_what_it_left():
     rec = pcrgen.write_record([pcrgen.make_jpeg(660 + i, 1, 300 + 20 * i, 280, 3, 18.0, 2, 2, 90) for i in range(3)])
     with pkg.pcr_open(rec, 0) as r:
-        for k0, k in ((1, 2), (1, 5), (2, 5), (3, 10), (5, 7)):
+        for k0, k, took in ((1, 2, [NO, YES]), (1, 5, [NO, YES]), (2, 5, [NO, YES]), (3, 10, [NO, NO]), (5, 7, [YES, NO])):
             r.decode_batch(k0)
+            assert r.last_first_splits() == took[0], k0
             got = r.upgrade_batch(k).cpu().numpy().copy()
+            assert r.last_first_splits() == took[1], (k0, k)
             assert np.array_equal(got, r.decode_batch(k).cpu().numpy()), (k0, k)
 
 
@@ -99,7 +130,7 @@ def test_damaged_data_flag_the_same_images(seed):
         elif kind == 2:
             f[at:at] = bytes(rng.integers(0, 255, 9, dtype=np.uint8))
         files.append(bytes(f))
-    _both(pcrgen.write_record(files), (1, 2, 5))
+    _both(pcrgen.write_record(files), {1: NO, 2: NO, 5: YES})
 
 
 def test_entries_out_of_order_flag_their_images_only():
@@ -113,7 +144,7 @@ def test_entries_out_of_order_flag_their_images_only():
         at, _ = _entry_at(good, g, i, 1)
         bad[at:at + 4] = (10 ** 9).to_bytes(4, "little")
     for k in (1, 2, 5):
-        st = _both(bytes(bad), (k,))
+        st = _both(bytes(bad), {k: YES})
         assert sorted(np.flatnonzero(st)) == sorted(i for i, g in hit.items() if g < k), k
     with pkg.pcr_open(bytes(bad), 0) as b, pkg.pcr_open(good, 0) as r:
         lay, want, got = r.output_layout(), r.decode_batch(5).cpu().numpy(), b.decode_batch(5).cpu().numpy()
@@ -137,4 +168,5 @@ def test_dc_scans_of_many_bits_a_block(contrast):
                 st = torch.full((r.n,), 77, dtype=torch.int32, device="cuda")
                 out.append(r.decode_batch(k, status=st).clone())
                 assert (st.cpu().numpy() == 0).all()
+                assert r.last_first_splits() == (YES if mode == 0 and (contrast == 1 or k == 5) else NO), (k, mode)
             assert torch.equal(*out), k

@@ -120,11 +120,11 @@ def test_a_refinement_that_builds_on_as_many_scans_as_can_be():
         _same(pcrgen.write_record([f]))
 
 
-@pytest.mark.parametrize("n", [1024, 1025])
+@pytest.mark.parametrize("n", [1024, 1025, 2048, 2049])
 def test_region_offsets_where_the_parser_sums_them_itself(n):
-    """Up to 1024 images the lengths ahead of a region are summed by the parser for scan groups 1 .. 8, beyond by k_index."""
+    """The lengths ahead of a region are summed by the parser up to 2048 images for scan groups 1 .. 8 and up to 1024 beyond; else by k_index."""
     few = [pcrgen.make_jpeg(90 + i, 1, 8 + i, 9, 3, 6.0, 1, 1, 80) for i in range(5)]
-    _same(pcrgen.write_record([few[i % 5] for i in range(n)]), images=sorted({0, 63, 64, 511, 512, 513, 1023, n - 1}))
+    _same(pcrgen.write_record([few[i % 5] for i in range(n)]), images=sorted({0, 63, 64, 511, 512, 513, 1023, n // 2, n - 1}))
 
 
 @pytest.mark.parametrize("n", [1024, 1025, 2048, 2049])

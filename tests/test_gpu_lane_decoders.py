@@ -193,13 +193,20 @@ def test_refinement_units_that_are_mostly_end_of_band_runs():
                     assert np.array_equal(got[int(lay[i]):int(lay[i + 1])], want), (i, k)
 
 
-@pytest.mark.parametrize("side, n, entry, restart", [(384, 256, 32, 0), (96, 512, 32, 0), (384, 96, 0, 1), (250, 128, 100, 0)])
-def test_launches_that_go_to_lanes_by_themselves(side, n, entry, restart):
+# (lane launches, wavefront launches) of decodes at 2, 5, 6 and 10 and of an upgrade from 2 to 8.  (400, 200): of records without entry points
+# the number of units decides where the launches of a call differ, so that the first scans, by lanes at 5, are the wavefronts' at 6.
+BY_THEMSELVES = [(384, 256, 32, 0, [(1, 0), (1, 0), (2, 0), (3, 0), (2, 0)]), (96, 512, 32, 0, [(0, 1), (0, 1), (0, 2), (0, 3), (0, 2)]),
+                 (384, 96, 0, 1, [(0, 1), (0, 1), (0, 2), (0, 3), (0, 2)]), (250, 128, 100, 0, [(0, 1), (0, 1), (0, 2), (0, 3), (0, 2)]),
+                 (400, 200, 0, 1, [(0, 1), (1, 0), (0, 2), (0, 3), (0, 2)]), (300, 400, 0, 1, [(1, 0), (1, 0), (1, 1), (1, 2), (2, 0)])]
+
+
+@pytest.mark.parametrize("side, n, entry, restart, shapes", BY_THEMSELVES)
+def test_launches_that_go_to_lanes_by_themselves(side, n, entry, restart, shapes):
     """What the rule sends to the lanes below the line by number -- all AC launches of a call or some of them -- gives the bytes of the
     wavefront decoders, from scratch and as an upgrade."""
     torch = _torch()
     some = [pcrgen.make_jpeg(60 + i, 1 + (i % 2), side - 3 * i, side + i, 3, 12.0, 2, 2, 80, restart=restart) for i in range(6)]
-    files, took = [some[i % 6] for i in range(n)], 0
+    files, took = [some[i % 6] for i in range(n)], []
     rec = pkg.record_write_indexed(files, None, entry) if entry else pcrgen.write_record(files)
     with pkg.pcr_open(rec, 0) as r:
         for k0, k in ((0, 2), (0, 5), (0, 6), (0, 10), (2, 8)):
@@ -212,6 +219,8 @@ def test_launches_that_go_to_lanes_by_themselves(side, n, entry, restart):
                 out.append(r.upgrade_batch(k, status=st).clone() if k0 else r.decode_batch(k, status=st).clone())
                 assert (st.cpu().numpy() == 0).all()
                 if mode == 0:
-                    took += r.last_decoder_shapes()[0]
+                    took.append(r.last_decoder_shapes())
+                else:
+                    assert r.last_decoder_shapes()[0] == 0
             assert torch.equal(*out), (k0, k)
-    assert took > 0 or (side, entry) != (384, 32)
+    assert took == shapes

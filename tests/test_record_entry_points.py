@@ -4,6 +4,8 @@ serial stream, so the writer adds places where a decoder may start.  CPU checks:
 the oracle are those of the plain record; the entries agree with what the oracle's own decode says about the same
 places (DC predictions = the previous block's DC coefficient); and the library's lane code, started at the entries on
 the CPU, gives the oracle's coefficients and pixels."""
+import os
+
 import numpy as np
 import pytest
 
@@ -176,3 +178,15 @@ def test_damaged_entries_are_refused_or_harmless_never_out_of_range(emul):  # no
         with pytest.raises(AssertionError, match="-2"):
             emul(bytes(bad), 0, 10, info)
     # (entry counts that do not fit the group are refused when the record is opened: tests/test_gpu_entry_points.py)
+
+
+def test_the_walk_agrees_with_one_that_takes_bit_after_bit(tmp_path):
+    """Block by block, on valid codes and on noise, with the machine's bit-scan instructions and without; under the sanitizers."""
+    import subprocess
+    here = os.path.dirname(os.path.abspath(__file__))
+    exe = str(tmp_path / "entry_walk")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-w", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan", "-o", exe,
+                           os.path.join(here, "host_emul", "entry_walk.cpp"), "-lpthread"])
+    env = {k: v for k, v in os.environ.items() if k != "LD_PRELOAD"}
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
+    assert out.returncode == 0 and out.stdout.endswith("walks agree\n"), (out.stdout[-300:], out.stderr[-2000:])
