@@ -132,17 +132,19 @@ __global__ void __launch_bounds__(LANES) k_first_split(DevRecord R, const Unit* 
     __shared__ SplitSums s_sums[LANES], s_part[kWaves];
     __shared__ uint16_t s_list[LANES];
     __shared__ uint32_t s_count[2];
-    __shared__ int s_bad;
+    __shared__ int s_bad, s_status;
     const Unit un = units[blockIdx.x];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     UnitSetup L;
-    unit_setup(R, un, clean32, group_status(R, un.img), &L);
+    // What becomes of the unit the wavefronts decide together: what they look at here nothing writes while this runs, but for the image's status
+    // (workgroups that decode its other units write that word), which one lane reads for all, to be asked behind the first barrier.
+    if (tid == 0) s_status = R.status[un.img];
+    unit_setup(R, un, clean32, &L, []() { return true; });
     const size_t ig = (size_t)un.img * R.G + un.scan;
     const ScanDesc* sd = &R.scan[ig];
     const uint32_t bit0 = L.byte_off * 8 + L.sub_bits, bit1 = L.byte_off * 8 + L.nbits;
     const bool ac = uni((int)sd->Ss) > 0;
     const uint32_t ns = L.ok ? (uint32_t)L.ls.ns : 0u;
-    // (the same for the whole workgroup: nothing but the status is written while this runs, and that all have from one lane)
     const bool mine = L.ok && R.img[un.img].progressive && uni((int)sd->Ah) == 0 && !is_sequential_scan(*sd) && ns >= 1 && ns <= (uint32_t)kMaxComp && (!ac || ns == 1) && bit1 > bit0;
     SplitScan S{L.words, bit1, 0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 1, 0, 0, 0, 0, 0, 0};
     uint32_t total = 0;
@@ -178,6 +180,7 @@ __global__ void __launch_bounds__(LANES) k_first_split(DevRecord R, const Unit* 
     if (tid <= last) { s_start[tid] = SplitState{bit0 + tid * piece, first_bk}; s_list[tid] = (uint16_t)tid; }
     if (tid == 0) { s_count[0] = last + 1; s_count[1] = 0; s_bad = 0; }
     __syncthreads();
+    if (uni(s_status) != kOk) { if (tid == 0) done[blockIdx.x] = 0; return; }
     LaneLookup code;
     code.init(reinterpret_cast<const LaneTab*>(T.piece));     // (of a DC scan: looked at by nobody)
     const DcTab* const dct = reinterpret_cast<const DcTab*>(T.piece);

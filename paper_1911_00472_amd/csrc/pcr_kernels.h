@@ -465,7 +465,7 @@ constexpr uint32_t kUnstuffWaves = 4, kUnstuffManyWaves = 16, kUnstuffStep = 102
 // What binding a handle to a record clears, pieces of 16 bytes, and 64 bytes behind the record (anywhere; null: none), in one launch: five or
 // six memory fills were a dispatch of some microseconds each, behind the copy of the bytes and one after the other.  Bound by the launch
 // (the largest piece is as long as the record).  us from host memory to training tensors: two
-// photographs at scan group 1 368 -> 305, 293 of 139 to 356 pixels at 6 475 -> 430, 4 x 512 photographs at 5 3565 -> 3355.
+// photographs at scan group 1 368 -> 305, 293 of 139 to 356 pixels at 6 475 -> 430 (of 4 x 512 photographs at 5 the runs differ by more than that).
 struct BindFill { uint4* p[5]; uint64_t n16[5]; uint32_t word[5], count; uint8_t* tail; };
 __global__ void __launch_bounds__(256) k_bind_fill(BindFill F) {
     const uint64_t at = (uint64_t)blockIdx.x * 256 + threadIdx.x, step = (uint64_t)gridDim.x * 256;
@@ -780,11 +780,13 @@ PCR_D int group_status(const DevRecord& R, uint32_t img) {
     __syncthreads();
     return uni(s_status);
 }
-// status: the image's.
-PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __restrict__ clean32, int status, UnitSetup* L) {
+// good: whether the image's status is kOk.  (A call, so that where a wavefront reads the word for itself it does so behind the image's address: ahead of
+// it the decoders of short launches took 0.3 to 0.5 % longer.)
+template <class Good>
+PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __restrict__ clean32, UnitSetup* L, const Good& good) {
     L->ok = false;
     const ImgDesc* img = &R.img[un.img];
-    if (status != kOk || un.scan >= img->nscans) return;
+    if (!good() || un.scan >= img->nscans) return;
     const size_t ig = (size_t)un.img * R.G + un.scan;
     const ScanDesc* sd = &R.scan[ig];
     if (!sd->valid) return;
@@ -835,6 +837,11 @@ PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __rest
     L->base_elems = (uint32_t)poff[kMaxComp];
     L->words = clean32 + (uni(clean_base(sd->data_off)) >> 2);
     L->ok = true;
+}
+
+// The same for a wavefront that is alone with its unit.
+PCR_D void unit_setup(const DevRecord& R, const Unit& un, const uint32_t* __restrict__ clean32, UnitSetup* L) {
+    unit_setup(R, un, clean32, L, [&]() { return R.status[un.img] == kOk; });
 }
 
 // What earlier kernels wrote and this one only reads, at a wave-uniform address: a scalar load, which arrives in scalar
@@ -1140,7 +1147,7 @@ __global__ void __launch_bounds__(kEntropyLanes * kChainWaves) k_decode_waves(De
     if (wave >= ch.count) return;
     const Unit un = units[ch.first + wave];
     UnitSetup L;
-    unit_setup(R, un, clean32, R.status[un.img], &L);
+    unit_setup(R, un, clean32, &L);
     if (FOLLOW) {
         uint64_t all = ch.waits | (ch.waits >> 32);
         all |= all >> 16; all |= all >> 8;
@@ -1277,7 +1284,7 @@ __global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const
     if (done && done[blockIdx.x]) return;
     const Unit un = units[blockIdx.x];
     UnitSetup L;
-    unit_setup(R, un, clean32, R.status[un.img], &L);
+    unit_setup(R, un, clean32, &L);
     if (!L.ok) return;
     const ScanDesc* sd = &R.scan[(size_t)un.img * R.G + un.scan];
     if (!is_sequential_scan(*sd)) { R.status[un.img] = kEFormat; return; }      // (a unit in the wrong launch)
@@ -1549,9 +1556,9 @@ PCR_D void floor_div(int num, int den, float inv_den, int* q, int* r) {
 }
 
 // Where output sample (oy, ox) of a resize looks: the two source rows and columns (absolute, the box's edge samples
-// repeated) and the weights of the second (f) and the first (g) of them, as exact fractions of 2 * out size.
-// (Both weights are made here, each with one rounding, so that every kernel that interpolates gives the very same bits however it
-// hands them on.)
+// repeated) and the weights of the second (f) and the first (g) of them.
+// (f is the remainder times the rounded reciprocal of 2 * out size, g one minus that product, rounded once: their sum can miss one by a
+// last place.  Both are made here, so that every kernel that interpolates gives the very same bits however it hands them on.)
 struct TailTap { int a, b; float f, g; };
 PCR_D TailTap tail_tap(int o, int out, int first, int size) {
     const int d = 2 * out;

@@ -789,7 +789,8 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     return PCR_OK;
 }
 
-// Images in groups of about this many bytes of what comes back from the device: what is pinned is bounded, except by a single image.
+// Images in groups of about this many bytes of what the host codes or puts together from: so much is pinned for it, or what a single image takes.
+// (The device's tables, bit counts and offsets of all images come back at once, 5.7 KB an image, as the symbol counts do where the host codes, 20 KB.)
 constexpr size_t kTranscodePinned = 64u << 20;
 
 // Cuts images 0 .. n - 1 into such groups: offset[i] is where image i begins, offset[n] the end.  Returns the first images of the groups

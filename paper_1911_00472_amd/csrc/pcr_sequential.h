@@ -179,7 +179,8 @@ __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, c
     const Unit un = units[blockIdx.x];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
     UnitSetup L;
-    unit_setup(R, un, clean32, group_status(R, un.img), &L);
+    const int status = group_status(R, un.img);
+    unit_setup(R, un, clean32, &L, [status]() { return status == kOk; });
     const ScanDesc* sd = &R.scan[(size_t)un.img * R.G + un.scan];
     const uint32_t bit0 = L.byte_off * 8 + L.sub_bits, bit1 = L.byte_off * 8 + L.nbits;
     const bool mine = L.ok && is_sequential_scan(*sd) && L.ls.ns >= 1 && L.ls.ns <= kMaxComp && bit1 > bit0 && bit1 - bit0 >= kSplitLeastBits;
