@@ -412,7 +412,8 @@ int pcr_transcode_batch(pcr_record* rec, const void* const* files, const size_t*
  * has more than 768 blocks).
  * First scans for the wavefronts that take one of them long go to many lanes each ahead of that launch, which decodes what those leave
  * (streams that do not fall into step); pcr_last_first_splits tells.
- * 1: lanes wherever the kernels exist and the record's scans have several units; -1: never, and no first scans by many lanes either.
+ * 1: lanes wherever the kernels exist and the record's scans have several units; -1: never, and no first scans by many lanes and no
+ * refinement scans by three wavefronts either.
  * The results are the same bit for bit.  Takes effect from the next decode call.  PCR_E_ARG: null handle or another
  * mode. */
 int pcr_set_lane_decoders(pcr_record* rec, int mode);
@@ -422,6 +423,9 @@ int pcr_last_decoder_shapes(pcr_record* rec, int* lane_launches, int* wavefront_
 /* Launches of the last decode call that gave every first scan (AC or DC) many lanes, ahead of those for the wavefronts, and how many
  * of them a thousand lanes each instead of 256 (host ints). */
 int pcr_last_first_splits(pcr_record* rec, int* launches, int* wide_launches);
+/* Launches of the last decode call in which every unit of a refinement scan had three wavefronts (taken by launches for the wavefronts that take
+ * as long as their longest unit; never in mode -1). */
+int pcr_last_refine_trios(pcr_record* rec, int* launches);
 
 /* Stage timing with HIP events recorded on the call's own stream (off by default; switching it on
  * starts a new history).  While it is on, every stage has launches of its own, and first scans are not given many lanes each (DC_FIRST and

@@ -40,6 +40,7 @@ SYMBOLS = {
     "pcr_enable_stage_timing": (ctypes.c_int, [_vp, ctypes.c_int]),
     "pcr_set_lane_decoders": (ctypes.c_int, [_vp, ctypes.c_int]),
     "pcr_last_decoder_shapes": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
+    "pcr_last_refine_trios": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_first_splits": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_stage_ms": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_float)]),
     "pcr_probe_scalar_issue_rate": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]),
@@ -354,6 +355,12 @@ class Record:
         a, b = ctypes.c_int(0), ctypes.c_int(0)
         _check(lib().pcr_last_decoder_shapes(self._h, ctypes.byref(a), ctypes.byref(b)), "pcr_last_decoder_shapes")
         return a.value, b.value
+
+    def last_refine_trios(self):
+        """Launches of the last decode call in which every unit of a refinement scan had three wavefronts."""
+        a = ctypes.c_int()
+        _check(lib().pcr_last_refine_trios(self._h, ctypes.byref(a)), "pcr_last_refine_trios")
+        return a.value
 
     def last_first_splits(self):
         """(launches that gave first scans many lanes each, those of them of a thousand lanes) of the last decode call."""

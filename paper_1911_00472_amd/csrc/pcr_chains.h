@@ -264,6 +264,35 @@ struct LanesLaunch {
     }
 };
 
+// A launch of refinement scans by wavefronts (of one level, or of all where the scans of a component are decoded side by side), and
+// whether their units have three wavefronts each (pcr_refine_trio.h).
+//
+// Three take two thirds of the time of one while the launch takes as long as its longest unit, and half as many instructions again once it fills
+// the chip.  So what decides is the launch's work over that of its longest unit, a block counted as 14 bits: `full`, the number
+// of units where all are alike.  us a call by one wavefront a unit / by three, one record open:
+//   plain records, all scans side by side, scan group 10 (gray: 6)
+//     64 x 64, quality 90, noisy        64 of them  191 / 165    256  200 / 174    512  222 / 207   1024  256 / 314    (full 115, 460, 920, 1850)
+//     256 x 256                         64         1548 / 1144   400 1688 / 1272   600 1817 / 1562   800 2006 / 2104   (full 117, 726, 1088, 1448)
+//     256 x 256, 4:4:4, quality 85     128         1500 / 1155   300 1711 / 1438   400 1864 / 1848   512 2005 / 2173   (full 270, 630, 835, 1070)
+//     256 x 256, gray                  256         1564 / 1159   600 1687 / 1269   800 1811 / 1817                     (full 357, 837, 1114)
+//     300 to 500 pixels a side         512         5934 / 4265  1024 6453 / 6378                                       (full 744, 1488)
+//   entry points every 64 MCUs, level by level, scan group 10
+//     17 to 320 pixels a side           32          228 / 211     64  240 / 220    128  281 / 288    256  357 / 400    (full 461, 1091, 1902, 3711)
+//   a marker every MCU row, 256 x 256   16          160 / 155     64  229 / 316                                        (full 940, 3812)
+//   four records at a time, plain, 128 x 128 128 in each 1098 / 861  256 1209 / 1039 512 1502 / 1576                 (full 230, 460, 920)
+//     300 to 500 pixels a side         400 in each 14431 / 12421  512 13144 / 14470; of two 512 7789 / 7010             (full 581, 744)
+//     128 x 128, entry points every 64 MCUs  64   487 / 453   128  531 / 536                                            (full 490, 980)
+// (Where several are decoded at a time the line would lie at some 650; one alone, at 650 to 850, gains more than four together lose there,
+// and how many records the process has open does not say which it is.)
+struct TrioLaunch {
+    uint64_t work = 0; uint32_t longest = 0;
+    void add(const LanesLaunch& l) {
+        work += l.bits + 14 * l.blocks;
+        longest = std::max(longest, l.longest_bits + 14 * l.longest_blocks);
+    }
+    bool pays() const { return longest > 0 && work <= 850ull * longest; }
+};
+
 // The MCUs of a DC scan, as far as lanes that decode them in step have to agree on them.
 inline uint32_t dc_mcu_shape(const ImgDesc& img, const ScanDesc& sd) {
     uint32_t f[2 * kMaxComp] = {1, 1, 1, 1, 1, 1};

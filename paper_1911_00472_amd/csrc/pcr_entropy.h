@@ -1289,11 +1289,11 @@ constexpr uint32_t kRefinePast = 0x00C00040u;
     "s_lshr_b32 m0, %[q], 16\n\t"                      \
     "s_and_b32 %[e], %[q], %[mask]\n\t"                \
     branch "\n\t"
-PCR_HD uint32_t ac_refine_symbols(const WindowReader* wr, const ZeroTable& zt, uint32_t* p_io, uint32_t* q_out, uint64_t* taken_io, uint32_t past) {
-    uint32_t p = *p_io, q, st;
-    uint64_t taken = *taken_io;
 #if defined(__HIP_DEVICE_COMPILE__)
-    uint32_t e;
+// o: window offset of the first symbol; vstep, ventry: the lanes' steps and table entries
+__device__ inline uint32_t refine_symbols(uint32_t o, uint32_t vstep, uint32_t ventry, uint32_t* p_io, uint32_t* q_out, uint64_t* taken_io, uint32_t past) {
+    uint32_t p = *p_io, q, st, e;
+    uint64_t taken = *taken_io;
     asm volatile(
         "s_mov_b32 m0, %[o]\n"
         "1:\n\t"
@@ -1303,10 +1303,18 @@ PCR_HD uint32_t ac_refine_symbols(const WindowReader* wr, const ZeroTable& zt, u
         PCR_REFINE_SYMBOL("s_cbranch_scc0 1b")
         "2:"
         : [st] "=&s"(st), [e] "=&s"(e), [p] "+s"(p), [q] "=&s"(q), [tk] "+s"(taken)
-        : [o] "s"(wr->o), [vstep] "v"(wr->vstep), [vent] "v"(zt.ventry), [mask] "s"(past)
+        : [o] "s"(o), [vstep] "v"(vstep), [vent] "v"(ventry), [mask] "s"(past)
         : "m0", "scc");
+    *p_io = p; *q_out = q; *taken_io = taken;
+    return st;
+}
+#endif
+PCR_HD uint32_t ac_refine_symbols(const WindowReader* wr, const ZeroTable& zt, uint32_t* p_io, uint32_t* q_out, uint64_t* taken_io, uint32_t past) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return refine_symbols(wr->o, wr->vstep, zt.ventry, p_io, q_out, taken_io, past);
 #else
-    uint32_t o = wr->o;
+    uint32_t p = *p_io, q, st, o = wr->o;
+    uint64_t taken = *taken_io;
     do {
         taken |= 1ull << (p & 63u);
         st = refine_step(wr->lookup(o));
@@ -1314,9 +1322,9 @@ PCR_HD uint32_t ac_refine_symbols(const WindowReader* wr, const ZeroTable& zt, u
         q = p + zt.at(p & 63u);
         o = q >> 16;
     } while ((q & past) == 0);
-#endif
     *p_io = p; *q_out = q; *taken_io = taken;
     return st;
+#endif
 }
 #undef PCR_REFINE_SYMBOL
 

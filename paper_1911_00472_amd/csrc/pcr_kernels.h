@@ -18,6 +18,7 @@
 #include "pcr_format.h"
 #include "pcr_chains.h"
 #include "pcr_entropy.h"
+#include "pcr_refine_trio.h"
 #include "pcr_lanes.h"
 #include "pcr_pixel.h"
 
@@ -1027,7 +1028,8 @@ PCR_D uint32_t lane_table_slot(const DevRecord& R, const LaneJob& job, uint32_t 
 // on one compute unit and share its vector cache: no more than the order of the operations is needed to see them).  A
 // wavefront waits only for wavefronts before it in the chain, and every wavefront ends by releasing all of its blocks,
 // whatever became of its unit: every wait ends.
-struct UnitChain { uint32_t first, count; uint64_t waits; };     // units [first, first + count), a wavefront each; byte w of waits: the earlier wavefronts that wavefront w follows
+// units [first, first + count), a wavefront each; refines: those of them that are of refinement scans; byte w of waits: the earlier wavefronts that wavefront w follows
+struct UnitChain { uint32_t first; uint16_t count, refines; uint64_t waits; };
 
 struct ChainGate {
     uint32_t* done;
@@ -1055,6 +1057,14 @@ struct ChainGate {
         __hip_atomic_store(&done[self], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 };
+
+PCR_D ChainGate chain_gate(const UnitChain& ch, uint32_t* done, uint32_t wave) {
+    uint64_t all = ch.waits | (ch.waits >> 32);
+    all |= all >> 16; all |= all >> 8;
+    ChainGate gate{done, wave, (uint32_t)(ch.waits >> (8 * wave)) & 255u, ((all >> wave) & 1u) != 0, 0u};
+    if (gate.waits == 0) gate.avail = ~0u;
+    return gate;
+}
 
 // What a wavefront keeps in LDS: the AC table of its scan and the words of the stream it is at, or the DC tables of its components.
 constexpr uint32_t kWaveTabBytes = sizeof(AcTab) + kStageWords * sizeof(uint32_t), kWaveDcTabBytes = kMaxComp * sizeof(DcTab);
@@ -1087,23 +1097,13 @@ PCR_D int wave_dc_first(const DevRecord& R, const Unit& un, const UnitSetup& L, 
     return decode_dc_first(&wr, L.ls, &sink);
 }
 
-template <class Gate>
-PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab* tab, uint32_t lane, Gate& gate) {
-    const size_t ig = (size_t)un.img * R.G + un.scan;
-    const ScanDesc* sd = &R.scan[ig];
-    {                                                       // the scan's table (built by k_headers)
-        const uint4* src = reinterpret_cast<const uint4*>(&R.tabs[R.tab_idx[ig]]);
-        uint4* dst = reinterpret_cast<uint4*>(tab);
-        for (uint32_t e = lane; e < sizeof(AcTab) / 16; e += kEntropyLanes) dst[e] = src[e];
-    }
+PCR_D void bring_ac_table(const DevRecord& R, size_t ig, AcTab* tab, uint32_t lane) {         // (built by k_headers)
+    const uint4* src = reinterpret_cast<const uint4*>(&R.tabs[R.tab_idx[ig]]);
+    uint4* dst = reinterpret_cast<uint4*>(tab);
+    for (uint32_t e = lane; e < sizeof(AcTab) / 16; e += kEntropyLanes) dst[e] = src[e];
     wave_sync();
-    WindowReader wr;
-    if (sd->Ah == 0) {
-        wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, true, lane, reinterpret_cast<uint32_t*>(tab + 1));
-        IndexSink sink;
-        sink.init(L.plane[0], L.plane_elems[0], L.ls.Al);
-        return decode_ac_first(&wr, L.ls, &sink, gate);
-    }
+}
+PCR_D HistPlanes hist_planes(const DevRecord& R, const Unit& un, const ScanDesc* sd, const UnitSetup& L) {
     // (the history is read through plain pointers: earlier scans may be writing it in this very launch)
     HistPlanes hp;
     hp.coef = L.plane[0];
@@ -1113,8 +1113,50 @@ PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab*
     hp.n = uni(hp.n);
     hp.some = hp.n > 0 ? ~0ull : 0ull;
     if (hp.n == 0) hp.p[0] = reinterpret_cast<const uint64_t*>(hp.coef);   // (16 bytes a block are read of its 128)
+    return hp;
+}
+template <class Gate>
+PCR_D int wave_ac(const DevRecord& R, const Unit& un, const UnitSetup& L, AcTab* tab, uint32_t lane, Gate& gate) {
+    const size_t ig = (size_t)un.img * R.G + un.scan;
+    const ScanDesc* sd = &R.scan[ig];
+    bring_ac_table(R, ig, tab, lane);
+    WindowReader wr;
+    if (sd->Ah == 0) {
+        wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, true, lane, reinterpret_cast<uint32_t*>(tab + 1));
+        IndexSink sink;
+        sink.init(L.plane[0], L.plane_elems[0], L.ls.Al);
+        return decode_ac_first(&wr, L.ls, &sink, gate);
+    }
+    const HistPlanes hp = hist_planes(R, un, sd, L);
     wr.init(L.words, L.byte_off, L.sub_bits, L.nbits, L.pos0, tab, false, lane, reinterpret_cast<uint32_t*>(tab + 1));
     return skim_ac_refine(&wr, L.ls, hp, R.masks + uni((uint64_t)R.mask_off[ig]), L.plane_elems[0] >> 6, gate);
+}
+
+// One of the three wavefronts of a refinement unit (pcr_refine_trio.h).
+constexpr uint32_t kTrioWalk = 0, kTrioFeed = 1, kTrioKeep = 2;
+template <class Gate>
+PCR_D __attribute__((always_inline)) void trio_unit(const DevRecord& R, const Unit& un, const UnitSetup& L, uint4* area, uint32_t part, uint32_t lane, Gate& gate) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const size_t ig = (size_t)un.img * R.G + un.scan;
+    const ScanDesc* sd = &R.scan[ig];
+    AcTab* tab = reinterpret_cast<AcTab*>(area);
+    const TrioLds T = (TrioLds)(reinterpret_cast<uint8_t*>(area) + kWaveTabBytes);
+    const uint32_t mis = (L.byte_off & 3) * 8, bits = L.nbits + mis, wb0 = L.pos0 - mis;
+    const uint32_t* const words = L.words + (L.byte_off >> 2);
+    if (part == kTrioFeed) {
+        bring_ac_table(R, ig, tab, lane);
+        trio_feed(T, tab, reinterpret_cast<uint32_t*>(tab + 1), words, bits, wb0, lane);
+        return;
+    }
+    uint32_t bad;
+    if (part == kTrioWalk) {
+        bad = trio_walk(T, tab, words, bits, wb0, mis + L.sub_bits, L.ls.mcu1 - L.ls.mcu0, lane);
+    } else {
+        const HistPlanes hp = hist_planes(R, un, sd, L);
+        bad = trio_keep(T, L.ls, hp, R.masks + uni((uint64_t)R.mask_off[ig]), L.plane_elems[0] >> 6, lane, gate);
+    }
+    if (bad) R.status[un.img] = kEFormat;
+#endif
 }
 
 // Workgroup b: chain b of `chains`, or (without them) unit b of `units`, with a wavefront per unit.  Dynamic LDS:
@@ -1138,7 +1180,7 @@ __global__ void __launch_bounds__(kEntropyLanes * kChainWaves) k_decode_waves(De
     __shared__ uint32_t done[kChainWaves];
     if (!FOLLOW && had && had[blockIdx.x]) return;            // (the many lanes of k_first_split have dealt with it)
     const uint32_t wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    UnitChain ch{blockIdx.x, 1, 0};
+    UnitChain ch{blockIdx.x, 1, 0, 0};
     if (chains) ch = chains[blockIdx.x];
     if (FOLLOW) {
         if (threadIdx.x < kChainWaves) done[threadIdx.x] = 0;
@@ -1149,13 +1191,54 @@ __global__ void __launch_bounds__(kEntropyLanes * kChainWaves) k_decode_waves(De
     UnitSetup L;
     unit_setup(R, un, clean32, &L);
     if (FOLLOW) {
-        uint64_t all = ch.waits | (ch.waits >> 32);
-        all |= all >> 16; all |= all >> 8;
-        ChainGate gate{done, wave, (uint32_t)(ch.waits >> (8 * wave)) & 255u, ((all >> wave) & 1u) != 0, 0u};
-        if (gate.waits == 0) gate.avail = ~0u;
+        ChainGate gate = chain_gate(ch, done, wave);
         if (L.ok) wave_unit<ROLES>(R, un, L, wave_tabs + wave * (kWaveTabBytes / 16), lane, to_planes != 0, gate);
         gate.publish(~0u);
     } else if (L.ok) { FreeRun gate; wave_unit<ROLES>(R, un, L, wave_tabs, lane, to_planes != 0, gate); }
+}
+
+// The same with three wavefronts for every unit of a refinement scan (pcr_refine_trio.h): wavefronts 0 .. count - 1 are those of
+// k_decode_waves, behind them come the feeder and the keeper of the first refinement scan of the chain, of the second, and so on.  Without chains
+// every unit is of a refinement scan.  Dynamic LDS: kWaveTabBytes per scan and sizeof(TrioRings) per refinement scan.  All wavefronts of a
+// workgroup have to agree on whether there is anything to decode, so the image's status is read once.
+constexpr uint32_t kTrioChainWaves = 16;
+template <int ROLES, bool FOLLOW>
+__global__ void __launch_bounds__(kEntropyLanes * kTrioChainWaves) k_decode_trios(DevRecord R, const Unit* __restrict__ units, const UnitChain* __restrict__ chains,
+        const uint32_t* __restrict__ clean32, uint32_t to_planes, const uint32_t* __restrict__ had) {
+    extern __shared__ uint4 wave_tabs[];
+    __shared__ uint32_t done[kChainWaves];
+    if (had && had[blockIdx.x]) return;                       // (the many lanes of k_first_split have dealt with it)
+    const uint32_t wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    UnitChain ch{blockIdx.x, 1, 1, 0};
+    if (FOLLOW) ch = chains[blockIdx.x];
+    const uint32_t count = ch.count, refines = ch.refines, trios = (uint32_t)__builtin_popcount(refines);
+    uint32_t which = wave, part = kTrioWalk;                  // the scan, and the part of it if it is a refinement scan
+    if (wave >= count) {
+        uint32_t rest = refines;
+        for (uint32_t j = (wave - count) >> 1; j && rest; j--) rest &= rest - 1;
+        which = rest ? (uint32_t)__builtin_ctz(rest) : 0u;
+        part = ((wave - count) & 1u) ? kTrioKeep : kTrioFeed;
+    }
+    auto area_of = [&](uint32_t scan) { return wave_tabs + (scan * kWaveTabBytes + (uint32_t)__builtin_popcount(refines & ((1u << scan) - 1u)) * (uint32_t)sizeof(TrioRings)) / 16; };
+    if (FOLLOW && threadIdx.x < kChainWaves) done[threadIdx.x] = 0;
+    if (wave < count && ((refines >> wave) & 1u) && lane < 8) {
+        const TrioLds T = (TrioLds)(reinterpret_cast<uint8_t*>(area_of(wave)) + kWaveTabBytes);
+        (&T->win_ready)[lane] = 0;
+    }
+    const Unit un = units[ch.first + which];
+    const int status = group_status(R, un.img);               // (behind its barrier: the counters are zero)
+    if (wave >= count + 2 * trios) return;
+    UnitSetup L;
+    unit_setup(R, un, clean32, &L, [&]() { return status == kOk; });
+    uint4* const area = area_of(which);
+    const bool refine = (refines >> which) & 1u;
+    if (part == kTrioWalk) __builtin_amdgcn_s_setprio(1);
+    if (FOLLOW) {
+        ChainGate gate = chain_gate(ch, done, which);
+        if (L.ok && refine) trio_unit(R, un, L, area, part, lane, gate);
+        else if (L.ok) wave_unit<ROLES>(R, un, L, area, lane, to_planes != 0, gate);
+        if (!refine || part == kTrioKeep) gate.publish(~0u);
+    } else if (L.ok) { FreeRun gate; trio_unit(R, un, L, area, part, lane, gate); }
 }
 
 // The same scan kind with one LANE per unit (pcr_lanes.h).  One wavefront per job: up to 64 consecutive units of the

@@ -52,6 +52,7 @@ struct Plan {                               // launch geometry for one scan grou
     std::vector<LevelList> levels;
     // the scans decoded side by side (k_decode_waves): AC chains first, the DC units (chains of one) behind them
     Unit* d_chain_units = nullptr; UnitChain* d_chains = nullptr; uint32_t n_ac_chains = 0, n_chains = 0, chain_waves = 0;
+    uint32_t trio_waves = 0, trio_lds = 0;   // a workgroup's wavefronts and LDS where refinement scans have three wavefronts each (k_decode_trios)
     uint32_t* d_chain_done = nullptr;        // chains of one: which units k_first_split has dealt with
     FirstSplitLaunch split;                  // ... and what decides whether it is launched
     // the AC refinement scans of the call, level after level, and the lists of the per-block kernels
@@ -223,6 +224,7 @@ struct pcr_record {
     int lane_mode = 0;                      // pcr_set_lane_decoders: 0 by the number of units, 1 wherever possible, -1 never
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
     int last_splits = 0, last_wide_splits = 0;            // ... launches of k_first_split, and those with a thousand lanes a unit
+    int last_trios = 0;                                   // ... launches of k_decode_trios
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
     std::vector<uint32_t> unit_bits;        // records opened from host bytes: entropy-coded bits of every unit, by slot (else empty)
     // decode fused with the training tail (allocated at its first call): one tile per run of an MCU row, the side buffer of first
@@ -317,7 +319,12 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
         for (const ScanChain& c : *set) {
             plan->chain_waves = std::max(plan->chain_waves, c.count);
             for (uint32_t j = 0; j < c.units; j++) {
-                list.push_back(UnitChain{(uint32_t)units.size(), c.count, c.waits});
+                uint32_t refines = 0;
+                for (uint32_t a = 0; a < c.count; a++) refines |= r->scan[(size_t)c.img * G + c.scan[a]].Ah > 0 ? 1u << a : 0u;
+                const uint32_t trios = (uint32_t)__builtin_popcount(refines);
+                plan->trio_waves = std::max(plan->trio_waves, c.count + 2 * trios);
+                plan->trio_lds = std::max(plan->trio_lds, c.count * kWaveTabBytes + trios * (uint32_t)sizeof(TrioRings));
+                list.push_back(UnitChain{(uint32_t)units.size(), (uint16_t)c.count, (uint16_t)refines, c.waits});
                 for (uint32_t a = 0; a < c.count; a++) units.push_back(Unit{c.img, c.scan[a], j, r->slot_base[(size_t)c.img * G + c.scan[a]]});
             }
         }
@@ -643,7 +650,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
     const bool several = g_open_records.load(std::memory_order_relaxed) > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
-    r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = 0;
+    r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = r->last_trios = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
         if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
@@ -722,9 +729,21 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         else hipLaunchKernelGGL(k_first_split<256>, dim3(n_units), dim3(256), 0, s, r->d, units, done, c32, dc_to_planes ? 1u : 0u);
         return done;
     };
+    // Whether the refinement scans of a level, or of all levels in one launch, get three wavefronts a unit.
+    auto trios = [&](const LevelList* one) {
+        TrioLaunch t;
+        for (const LevelList& l : plan->levels) if (l.kind == kAcRefine && (!one || one == &l)) t.add(l.lanes);
+        const bool pays = r->lane_mode >= 0 && t.pays();
+        r->last_trios += pays ? 1 : 0;
+        return pays;
+    };
     auto waves = [&](const LevelList& l) {
         const bool dc = l.kind == kDcFirst;
         const uint32_t* had = dc ? split(l.split, true, l.d_units, l.n, l.d_done) : nullptr;
+        if (l.kind == kAcRefine && trios(&l)) {
+            hipLaunchKernelGGL((k_decode_trios<kWavesAc, false>), dim3(l.n), dim3(3 * kEntropyLanes), kWaveTabBytes + sizeof(TrioRings), s, r->d, l.d_units, (const UnitChain*)nullptr, c32, 0u, (const uint32_t*)nullptr);
+            return;
+        }
         hipLaunchKernelGGL((dc ? k_decode_waves<kWavesDc, false> : k_decode_waves<kWavesAc, false>), dim3(l.n), dim3(kEntropyLanes), dc ? kWaveDcTabBytes : kWaveTabBytes, s, r->d, l.d_units,
                            (const UnitChain*)nullptr, c32, dc_to_planes ? 1u : 0u, had);
     };
@@ -733,8 +752,12 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         const uint32_t w = plan->chain_waves;                // (chains of several scans are those in which some follow others)
         auto* kernel = w > 1 ? (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, true> : k_decode_waves<kWavesAc, true>)
                              : (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, false> : k_decode_waves<kWavesAc, false>);
-        hipLaunchKernelGGL(kernel, dim3(dc_beside ? plan->n_chains : plan->n_ac_chains), dim3(kEntropyLanes * w), w * kWaveTabBytes, s, r->d,
-                           plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u, had);
+        const dim3 groups(dc_beside ? plan->n_chains : plan->n_ac_chains);
+        if (plan->trio_waves > w && plan->trio_waves <= kTrioChainWaves && trios(nullptr))
+            hipLaunchKernelGGL((dc_beside ? k_decode_trios<kWavesDc | kWavesAc, true> : k_decode_trios<kWavesAc, true>), groups, dim3(kEntropyLanes * plan->trio_waves), plan->trio_lds, s, r->d,
+                               plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u, had);
+        else
+            hipLaunchKernelGGL(kernel, groups, dim3(kEntropyLanes * w), w * kWaveTabBytes, s, r->d, plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u, had);
     }
     for (size_t li = 0; li < plan->levels.size(); li++) {
         auto& l = plan->levels[li];
@@ -1421,6 +1444,11 @@ int pcr_last_decoder_shapes(pcr_record* r, int* lane_launches, int* wavefront_la
     return PCR_OK;
 }
 
+int pcr_last_refine_trios(pcr_record* r, int* launches) {
+    if (!r || !launches) return PCR_E_ARG;
+    *launches = r->last_trios;
+    return PCR_OK;
+}
 int pcr_last_first_splits(pcr_record* r, int* launches, int* wide_launches) {
     if (!r || !launches || !wide_launches) return PCR_E_ARG;
     *launches = r->last_splits; *wide_launches = r->last_wide_splits;
