@@ -1356,15 +1356,15 @@ __global__ void __launch_bounds__(kEntropyLanes, 4) k_first_lanes(DevRecord R, c
     else ac_first_job(R, ac_units, jobs[blockIdx.x - dc_blocks], clean32, tabs, &rings);
 }
 
-// Sequential (baseline) scans: the DC and AC tables of every scan component, once per distinct table.  done (may be null): the
-// units k_sequential_split has dealt with.
-__global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const Unit* __restrict__ units, const uint32_t* __restrict__ done,
+// Sequential (baseline) scans: the DC and AC tables of every scan component, once per distinct table.  done: which of the
+// first n_done units the lanes have dealt with (k_split_settle).
+__global__ void __launch_bounds__(kEntropyLanes) k_sequential(DevRecord R, const Unit* __restrict__ units, const uint32_t* __restrict__ done, uint32_t n_done,
         const uint32_t* __restrict__ clean32) {
     __shared__ uint32_t stage_[1 + kStageWords];            // (a word is read ahead of it)
     uint32_t* stage = stage_ + 1;
     __shared__ DcTab dtabs[kMaxComp];
     __shared__ AcTab atabs[kMaxComp];
-    if (done && done[blockIdx.x]) return;
+    if (blockIdx.x < n_done && done[blockIdx.x]) return;
     const Unit un = units[blockIdx.x];
     UnitSetup L;
     unit_setup(R, un, clean32, &L);

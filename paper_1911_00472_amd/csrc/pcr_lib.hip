@@ -39,8 +39,12 @@ struct LevelList {
     uint32_t level = 0;                                                          // (0-based)
     uint32_t plane_tile = 0, n_plane_tiles = 0, cov_tile = 0, n_cov_tiles = 0;    // AC refinement: the level's share of the plan's lists for the per-block kernels
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
-    uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units k_sequential_split has dealt with
-    uint32_t n_long = 0; uint64_t long_bytes = 0; bool subsampled = false;        // ... how many those are, their bytes, whether some have MCUs of several blocks per component
+    uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units have been dealt with by many lanes
+    uint32_t n_long = 0; uint64_t long_bytes = 0;                                // ... how many those are, their bytes
+    // ... and what k_split_tries and the kernels behind it work in: workgroups a unit
+    // needs at most; what they are judged by (split_pays): us of their work, MCUs of several blocks per component, of several blocks
+    SplitRoom* d_rooms = nullptr; SplitNode* d_nodes = nullptr; uint32_t* d_next = nullptr; SplitPiece* d_pieces = nullptr;
+    uint32_t split_tries = 0, split_stores = 0; float split_work = 0; bool subsampled = false, several_tries = false, by_tries = false;
     DcLaunch dc;                                                                 // DC first scans: what decides between lanes and wavefronts
     uint32_t* d_dc_starts = nullptr; uint32_t n_dc_waves = 0;                    // ... wavefronts of lanes, and where they begin if their MCUs are of several shapes
     bool chained = false;                                                        // the plan's chains hold these units too
@@ -343,6 +347,62 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
     return PCR_OK;
 }
 
+enum SplitBy { kSplitNever = 0, kSplitBySteps = 1, kSplitByTries = 2 };
+SplitBy split_pays(const LevelList& l, int open_records);
+
+// Blocks of an MCU of a sequential scan: the tries of a piece (k_split_tries).
+uint32_t split_tries_of(const ImgDesc& im, const ScanDesc& sd) {
+    uint32_t tries = 0;
+    for (int j = 0; j < sd.ns; j++) tries += sd.ns == 1 ? 1u : (uint32_t)im.hs[sd.comp[j]] * im.vs[sd.comp[j]];
+    return std::max(1u, tries);
+}
+// Room for a unit of `bytes` of a scan, in pieces of `least` bits and more.  (More nodes are decoded on than half of those a unit begins with
+// hardly ever.)
+SplitRoom split_room_of(const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t least) {
+    SplitRoom room{};
+    room.tries = split_tries_of(im, sd);
+    const uint64_t blocks = std::max<uint64_t>((uint64_t)room.tries * sd.mcus, 1);
+    room.run_in = (uint32_t)std::min<uint64_t>(kSplitRunInMost, std::max<uint64_t>(kSplitRunInLeast, kSplitRunInBlocks * 8 * (uint64_t)sd.data_len / blocks));
+    room.least = std::max(room.run_in, least);
+    room.pieces = std::min<uint32_t>(std::min(kSplitPieces, kSplitFirstNodes / room.tries), (uint32_t)((uint64_t)bytes * 8 / room.least + 1));
+    const uint32_t first = room.pieces * room.tries;
+    room.nodes = std::min(kSplitNodes, first + first / 2 + 1024);
+    return room;
+}
+// What the kernels of a launch's long sequential scans work in (pcr_sequential.h).  Pieces are as long as that a launch of few scans fills the
+// chip once, within what the constants say; no memory for it: no long scans.
+template <class Run> void lay_out_split(const pcr_record* r, const Run* runs, size_t count, LevelList* ll, Uploads* up) {
+    pcr_record* const rec = const_cast<pcr_record*>(r);
+    uint64_t tried = 0;                                      // bits to be decoded once per try
+    uint32_t units = 0;
+    size_t n_runs = 0;
+    for (; n_runs < count && units < ll->n_long; n_runs++) {
+        const Run& q = runs[n_runs];
+        tried += (uint64_t)split_tries_of(r->img[q.img], r->scan[(size_t)q.img * r->hdr.G + q.scan]) * q.bytes * 8 * q.count;
+        units += q.count;
+    }
+    const uint32_t fills = (uint32_t)std::min<uint64_t>(kSplitPieceMost, tried / (256 * kSplitLanes));
+    std::vector<SplitRoom> rooms;
+    rooms.reserve(ll->n_long);
+    uint64_t nodes = 0;
+    uint32_t pieces = 0;
+    for (size_t e = 0; e < n_runs; e++) {
+        const Run& q = runs[e];
+        SplitRoom room = split_room_of(r->img[q.img], r->scan[(size_t)q.img * r->hdr.G + q.scan], q.bytes, fills);
+        const uint32_t per = kSplitLanes / room.tries;
+        ll->split_tries = std::max(ll->split_tries, std::max(1u, (room.pieces - 1 + per - 2) / (per - 1)));
+        ll->split_stores = std::max(ll->split_stores, (room.pieces + kSplitStoreLanes - 1) / kSplitStoreLanes);
+        for (uint32_t j = 0; j < q.count; j++) {
+            room.node0 = nodes; room.piece0 = pieces;
+            rooms.push_back(room);
+            nodes += room.nodes; pieces += room.pieces + 1;
+        }
+    }
+    if (arena_alloc(&rec->big, &ll->d_nodes, nodes) != PCR_OK || arena_alloc(&rec->big, &ll->d_next, nodes) != PCR_OK || arena_alloc(&rec->big, &ll->d_pieces, pieces) != PCR_OK) return;
+    up->add(&ll->d_rooms, rooms);
+    ll->by_tries = true;
+}
+
 // Launch geometry for decoding scan groups k0+1 .. k (k0 = 0: from scratch) and turning groups 1 .. k into pixels.
 int build_plan(pcr_record* r, int k0, int k, Plan** out) {
     const int key = k0 * 256 + k;
@@ -472,11 +532,13 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
         if (ll.kind == kSequential) {
             for (const Run& q : rn) {
                 if ((uint64_t)q.bytes * 8 < kSplitLeastBits) break;          // (the longest on average come first)
-                const ScanDesc& sd = r->scan[(size_t)q.img * G + q.scan];
+                const uint32_t tries = split_tries_of(r->img[q.img], r->scan[(size_t)q.img * G + q.scan]);
                 ll.n_long += q.count; ll.long_bytes += (uint64_t)q.bytes * q.count;
-                for (int j = 0; j < sd.ns && sd.ns > 1; j++) ll.subsampled = ll.subsampled || r->img[q.img].hs[sd.comp[j]] > 1 || r->img[q.img].vs[sd.comp[j]] > 1;
+                ll.split_work += (22.f + 4.5f * (float)tries) * (float)q.bytes * (float)q.count;
+                ll.subsampled = ll.subsampled || tries > (uint32_t)r->img[q.img].nc; ll.several_tries = ll.several_tries || tries > 1;
             }
             if (ll.n_long) { const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc; }
+            if (split_pays(ll, 1) == kSplitByTries) lay_out_split(r, rn.data(), rn.size(), &ll, &up);
         }
     }
     refine_tiles(r, refine_levels, &plan, &up);
@@ -567,27 +629,31 @@ bool dc_lanes_pay(const pcr_record* r, const LevelList& l, bool beside) {
     return l.dc.by_lanes(g_open_records.load(std::memory_order_relaxed) > 1, beside);
 }
 
-// Many lanes per long sequential scan, or one wavefront?  k_sequential_split has room for one scan per compute unit (150 KB
-// of LDS), 256 at a time, and spends up to three times the work; k_sequential takes as long as its longest scan until some
-// thousand of them fill the scalar units.  Measured (ms for n files, k_sequential / k_sequential_split):
-//                        n = 64         512           1024          2048          4096
-//   4:2:0, 110 KB    11.3 / 2.1    11.5 / 3.9    12.6 / 7.5    15.7 / 12.7   23.3 / 24.9
-//   4:2:0, 29 KB      3.0 / 1.5     3.1 / 2.8     3.5 / 4.8     4.4 / 8.6     6.4 / 16.8
-//   4:2:0, 11 KB      1.2 / 1.5     1.3 / 2.3     1.4 / 3.7     1.8 / 6.4     2.6 / 12.2
-//   4:4:4, 110 KB    11.9 / 1.2    12.1 / 2.1    13.7 / 4.0    17.1 / 7.4    24.9 / 14.0
-//   4:4:4, 13 KB      1.5 / 0.6     1.6 / 1.0     1.8 / 1.7     2.2 / 3.1     3.2 / 6.1
-//   gray, 146 KB     13.3 / 1.0    13.6 / 2.0    15.3 / 3.7    19.2 / 6.8    28.2 / 13.0
-//   gray, 17 KB       1.7 / 0.5     1.7 / 0.8     2.0 / 1.4     2.5 / 2.6     3.6 / 5.0
-// The two lines below follow these figures (in us; kb: the mean of the long scans).  A record decoded beside others shares
+// Many lanes per long sequential scan, or one wavefront?  k_sequential takes as long as its longest scan until some thousand of them fill the
+// scalar units.  k_sequential_split has room for one scan per compute unit (150 KB of LDS), 256 at a time, and a step takes as long as its
+// slowest lane.  k_split_tries and what follows use the whole chip for few scans, but decode up to thirteen times what one decoder would.
+// ms for n files, by tries / k_sequential_split / k_sequential (the whole call; -: not measured):
+//                        n = 1              32             128            512            2048
+//   4:2:0, 166 KB    0.9/ 1.9/17     1.1/ 2.4/17    1.9/ 2.3/17    5.0/ 4.6/ -      -  /16.1/ -
+//   4:2:0, 50 KB     0.7/ 1.6/5.1    0.9/ 2.1/5.1   0.9/ 2.0/5.1   2.0/ 3.7/ -     8.4/ -  /4.3
+//   4:2:0, 19 KB     0.6/ 1.4/1.9    0.8/ 1.6/1.9   0.8/ 1.5/1.9   1.2/ 2.3/1.4    6.4/ -  /1.7
+//   4:4:4, 203 KB    0.8/ 1.3/21     1.0/ 1.4/21    1.9/ 1.4/ -    4.8/ 3.1/ -      -  /11.7/ -
+//   q 97, 99 KB      1.5/ 6.2/5.3    1.6/ 6.4/5.4   1.6/ 6.4/5.5   4.0/ 7.3/ -      -  /12.6/ -
+//   gray, 163 KB     0.8/ 0.8/17     0.9/ 1.2/17    1.1/ 1.1/17    2.6/ 2.2/ -      -  / 8.2/ -
+//   2.5 MP, 1.8 MB   3.6/ 6.5/ -     4.9/ 8.0/ -   11.0/ 8.5/ -   45.8/21.4/ -      -
+// (steps at quality 97: given up, and decoded by k_sequential behind it.)  The lines below follow these figures (in us; kb: the mean of the long
+// scans); where every MCU is one block there is one try, and nothing to be had of them.  A record decoded beside others shares
 // the compute units with them; the records the process has open (four at most count) are taken as the sign of it, as by
 // lanes_pay.  (Without this choice 4096 baseline photographs in four records took 29.1 ms instead of 23.2.)
-bool split_pays(const LevelList& l) {
-    if (l.n_long == 0) return false;
-    const float n = (float)l.n_long * (float)std::min(4, std::max(1, g_open_records.load(std::memory_order_relaxed)));
+SplitBy split_pays(const LevelList& l, int open_records) {
+    if (l.n_long == 0) return kSplitNever;
+    const float beside = (float)std::min(4, std::max(1, open_records)), n = (float)l.n_long * beside;
     const float kb = (float)l.long_bytes / (float)l.n_long / 1000.f, turns = std::ceil(n / 256.f);
-    const float split = l.subsampled ? 550.f + turns * (850.f + 6.f * kb) : 150.f + turns * (260.f + 4.5f * kb);
+    const float tries = 150.f + turns * 400.f + beside * l.split_work * 1e-6f;
+    const float long_kb = std::max(0.f, kb - 300.f);         // (a lane's piece is beyond a wrong block then)
+    const float steps = l.subsampled ? 550.f + turns * (850.f + 6.f * kb - 3.f * long_kb) : 150.f + turns * (260.f + 4.5f * kb);
     const float sequential = 102.f * kb * std::max(1.f, 0.72f + n / 3072.f);
-    return split < sequential;
+    return l.several_tries && tries < steps && tries < sequential ? kSplitByTries : (steps < sequential ? kSplitBySteps : kSplitNever);
 }
 
 // Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
@@ -653,7 +719,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = r->last_trios = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
-        if (l.kind == kSequential) by_lanes[li] = split_pays(l) ? 1 : 0;
+        if (l.kind == kSequential) by_lanes[li] = (char)split_pays(l, g_open_records.load(std::memory_order_relaxed));
         else if (l.kind != kDcFirst) {
             by_lanes[li] = lanes_pay(r, l, several) ? 1 : 0;
             if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
@@ -773,8 +839,13 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
             mark(r, PCR_STAGE_DC_FIRST, s);
         }
         else if (l.kind == kSequential) {
-            if (by_lanes[li]) hipLaunchKernelGGL(k_sequential_split, dim3(l.n), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
-            hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, by_lanes[li] ? (const uint32_t*)l.d_done : (const uint32_t*)nullptr, c32);
+            const bool by_tries = by_lanes[li] == kSplitByTries && l.by_tries;
+            if (by_tries) {
+                hipLaunchKernelGGL(k_split_tries, dim3(l.n_long, l.split_tries), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, l.d_nodes, l.d_next, c32);
+                hipLaunchKernelGGL(k_split_settle, dim3(l.n_long), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, l.d_nodes, l.d_next, l.d_pieces, l.d_done, c32);
+                hipLaunchKernelGGL(k_split_store, dim3(l.n_long, l.split_stores), dim3(kSplitStoreLanes), 0, s, r->d, l.d_units, l.d_rooms, l.d_pieces, l.d_done, c32);
+            } else if (by_lanes[li]) hipLaunchKernelGGL(k_sequential_split, dim3(l.n), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
+            hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, (const uint32_t*)l.d_done, by_tries ? l.n_long : (by_lanes[li] ? l.n : 0u), c32);
             mark(r, PCR_STAGE_SEQUENTIAL, s);
         }
         else if (l.kind == kAcFirst) {
@@ -1028,7 +1099,7 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
     uint32_t flat_tiles = 0, flat_rows = 0;                       // (listed when a plan first needs them)
     bool rows_fit = true;
     r->flat_row_cells = 0;
-    uint64_t nm = 0; uint64_t ns = 0;
+    uint64_t nm = 0; uint64_t ns = 0, split_nodes = 0;
     std::vector<uint32_t> tab_idx((size_t)n * G, 0); uint32_t ntabs = 0;
     std::vector<uint32_t> dctab_idx((size_t)n * G, 0); uint32_t ndctabs = 0;
     r->several_units = r->entry_units = false;
@@ -1072,6 +1143,7 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
             else ent_off[ig] = 0;
             if (ent_off[ig]) r->entry_units = true;
             if (d.progressive && sd.Ss == 0 && sd.Ah == 0) { dctab_idx[ig] = ndctabs; ndctabs += kMaxComp; }
+            if (is_sequential_scan(sd) && cnt == 1 && n <= 256 && sd.data_len * 8ull >= kSplitLeastBits && split_tries_of(d, sd) > 1) split_nodes += split_room_of(d, sd, sd.data_len, 0).nodes;
             if (cnt > 1 && (sd.Ss > 0 || d.progressive)) r->several_units = true;
             r->slot_base[ig] = (uint32_t)ns; r->slot_cnt[ig] = cnt;
             ns += cnt + 1;
@@ -1098,6 +1170,7 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
                   arena_round(((size_t)ntabs + 1) * sizeof(AcTab)) + arena_round(((size_t)ndctabs + 1) * sizeof(DcTab)) + arena_round(((size_t)n * G + 1) * sizeof(uint32_t)) + arena_round(((size_t)n * G + 1) * sizeof(uint32_t));
     need += 8 * ((ns + (size_t)n * G) * sizeof(Unit) + (size_t)n * kMaxComp * 64) + (1u << 20);
     need += 8 * (r->coef_off[n] / 64 / 256 + (size_t)n * G) * 2 * sizeof(RefineTile);     // (the tile lists of the refinement helpers: one entry per 256 blocks)
+    need += split_nodes * (sizeof(SplitNode) + sizeof(uint32_t)) + split_nodes / 4 * sizeof(SplitPiece);      // (the pieces of long sequential scans)
     int rc = arena_reset(&r->big, need);
     if (!rc) rc = arena_alloc(&r->big, &d.clean, padded);
     if (!rc) rc = arena_alloc(&r->big, &d.coef, r->coef_off[n]);

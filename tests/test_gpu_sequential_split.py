@@ -119,3 +119,12 @@ def test_more_long_scans_than_the_split_pays_for(others):
             assert np.array_equal(coef[int(lay[i]):int(lay[i + 1])], want[i % 8]), (n, i)
     for r in open_beside:
         r.close()
+
+
+@pytest.mark.parametrize("n,w,h,c,hs,vs,quality,noise,restart", [
+    (3, 97, 90, 3, 2, 2, 95, 20.0, 0), (2, 640, 600, 3, 2, 1, 90, 14.0, 0), (1, 2000, 1500, 3, 2, 2, 92, 20.0, 0), (2, 900, 700, 3, 1, 1, 97, 30.0, 0),
+    (2, 700, 640, 3, 1, 2, 90, 18.0, 900), (2, 1024, 1024, 3, 2, 2, 90, 0.0, 0), (1, 300, 300, 3, 2, 2, 97, 40.0, 0), (2, 500, 500, 1, 1, 1, 92, 26.0, 0)])
+def test_few_scans_by_tries(n, w, h, c, hs, vs, quality, noise, restart):
+    """Few scans, which go by tries: from a few pieces to as many as a scan is cut into, pieces of several workgroups, units between
+    restart markers, every sampling layout; noise at a high quality, of which most pieces fall in with no try; pictures that hold next to nothing."""
+    _check([pcrgen.encode_pixels(pcrgen.synth(31 + i, 2, w + 16 * i, h - 9 * i, c, noise), hs, vs, quality, "sequential", restart=restart) for i in range(n)])
