@@ -656,6 +656,25 @@ SplitBy split_pays(const LevelList& l, int open_records) {
     return l.several_tries && tries < steps && tries < sequential ? kSplitByTries : (steps < sequential ? kSplitBySteps : kSplitNever);
 }
 
+// Which stores ask the caches to make no room for what they store (put_past).  The chip's memory-side cache holds 256 MB for all records in flight:
+// coefficient planes that fit are still there when the pixel kernel reads them unless its own pixels push them out, planes that do not are better
+// written past it, so that what other records have there stays.  Both ways, the call's time past the cache over its time through it (MB of planes, or of
+// pixels for DC-only decodes; records in flight):
+//   k_pixel          12 x 1 0.99    24 x 1 0.99    48 x 1 0.99    96 x 1 1.00 (scan group 10: 0.98)   192 x 1 0.92 and 0.95    228 x 1 0.98    384 x 1 1.01    456 x 1 1.01
+//                    48 x 4 0.98    96 x 4 0.96   192 x 2 1.01    228 x 4 1.03
+//   the zero fill    12 to 456 x 1 1.00 to 1.03   48 x 4 1.02     96 x 4 0.99 (pixels past it as well: 0.98)     192 x 2 0.97 and 0.99    228 x 4 0.98    490 x 4 0.98
+//   pixel rows       445 x 1 1.05   192 x 1 1.00  111 x 4 1.01   445 x 2 1.01   222 x 4 0.99    445 x 4 0.97    192 x 2 0.89 (rows of whole lines; 384 x 2 0.98)
+// (Records that are open and idle look like records in flight; so it takes four of them to count.)
+struct CacheRule {
+    static constexpr size_t kMB = 1u << 20;
+    size_t planes, pixel_bytes;
+    bool four;
+    explicit CacheRule(const pcr_record* r) : planes(r->coef_off[r->hdr.n] * sizeof(int16_t)), pixel_bytes((size_t)r->out_off[r->hdr.n]), four(g_open_records.load(std::memory_order_relaxed) >= 4) {}
+    bool pixels() const { return planes >= 16 * kMB && planes <= (four ? 128 : 208) * kMB; }
+    bool fill() const { return four && planes > 208 * kMB; }
+    bool flat_rows() const { return four && pixel_bytes > 256 * kMB; }
+};
+
 // Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
 // regions in the same kernel: a launch costs about as much as k_index runs, and a workgroup of k_headers sums at most
 // kOwnIndexImages lengths per scan group (the line: see there).
@@ -695,6 +714,7 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, Apply
     P.first[count] = groups;
     size_t pieces = 0;
     for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
+    fill.past = CacheRule(r).fill() ? 1u : 0u;
     const uint32_t lanes = 64 * waves;                       // (eight pieces per lane, but for the last row)
     fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 8 * lanes - 1) / (8 * lanes), std::min<size_t>(many ? 512 : 2048, std::max<size_t>(groups, many ? 256 : 1024))));
     const uint32_t total = lists.groups + groups + kDies * fill.rows;
@@ -1591,17 +1611,19 @@ static int decode_to_pixels(pcr_record* r, int k0, int k, uint8_t* out, size_t c
     // launches took 150 of the 1550 us of 2048 pictures of 132 x 133 at scan group 10, to find that there is none)
     DevRecord d = r->d;
     d.status_out = d_status;
+    const CacheRule cache(r);
+    const uint32_t pixels_past = cache.pixels() ? 1u : 0u;
     const bool smooth_flat = smooth && !plan->has_ac && !plan->n_apply && !boxes;
     if (smooth_flat || !plan->smooths) smooth = false;
     if (smooth) hipLaunchKernelGGL(k_smooth<false>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
     if (smooth_flat)
         hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out);
     else if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
+        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes, pixels_past);
     else if (plan->has_ac || smooth)
-        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
+        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes, pixels_past);
     else if (r->n_flat_rows && !boxes)                       // DC scans only: every block is flat
-        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
+        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells, cache.flat_rows() ? 1u : 0u);
     else
         hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out, boxes);
     if (smooth) hipLaunchKernelGGL(k_smooth<true>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
@@ -1645,9 +1667,9 @@ int pcr_decode_batch_triangle(pcr_record* r, int k, uint8_t* out, size_t cap, vo
     DevRecord d = r->d;
     d.status_out = d_status;
     if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr, 0u);
     else
-        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr, 0u);
     uint32_t items = 1;
     for (uint32_t i = 0; i < n; i++) items = std::max(items, (((uint32_t)r->img[i].W + 3) / 4) * (uint32_t)r->img[i].H);
     hipLaunchKernelGGL(k_triangle_rgb, dim3((items + 255) / 256, n), dim3(256), 0, s, r->d, (const uint8_t*)r->d_planes, out);
