@@ -664,14 +664,16 @@ SplitBy split_pays(const LevelList& l, int open_records) {
 //                    48 x 4 0.98    96 x 4 0.96   192 x 2 1.01    228 x 4 1.03
 //   the zero fill    12 to 456 x 1 1.00 to 1.03   48 x 4 1.02     96 x 4 0.99 (pixels past it as well: 0.98)     192 x 2 0.97 and 0.99    228 x 4 0.98    490 x 4 0.98
 //   pixel rows       445 x 1 1.05   192 x 1 1.00  111 x 4 1.01   445 x 2 1.01   222 x 4 0.99    445 x 4 0.97    192 x 2 0.89 (rows of whole lines; 384 x 2 0.98)
-// (Records that are open and idle look like records in flight; so it takes four of them to count.)
+// (Records that are open and idle look like records in flight; so it takes four of them to count.  The zero fill's line is the cache's size and not
+// less, because of loaders: their slots are open but decode one after the other, and at 228 MB a record the unstuffing launch with the fill took
+// 56 us a slot past the cache and 45 through it.)
 struct CacheRule {
     static constexpr size_t kMB = 1u << 20;
     size_t planes, pixel_bytes;
     bool four;
     explicit CacheRule(const pcr_record* r) : planes(r->coef_off[r->hdr.n] * sizeof(int16_t)), pixel_bytes((size_t)r->out_off[r->hdr.n]), four(g_open_records.load(std::memory_order_relaxed) >= 4) {}
     bool pixels() const { return planes >= 16 * kMB && planes <= (four ? 128 : 208) * kMB; }
-    bool fill() const { return four && planes > 208 * kMB; }
+    bool fill() const { return four && planes > 256 * kMB; }
     bool flat_rows() const { return four && pixel_bytes > 256 * kMB; }
 };
 
