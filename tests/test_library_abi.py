@@ -120,3 +120,18 @@ def test_no_kernel_spills_to_scratch_memory(tmp_path):
     subprocess.check_call([hipcc] + flags + ["-S", "--cuda-device-only", "-o", str(asm), build.SRC], stderr=subprocess.DEVNULL)
     sizes = [line.split()[-1] for line in asm.read_text().splitlines() if ".amdhsa_private_segment_fixed_size" in line]
     assert len(sizes) > 30 and all(s == "0" for s in sizes), sizes
+
+
+def test_pixel_kernel_leaves_registers_for_another_launch(tmp_path):
+    """Four wavefronts of k_pixel on a SIMD (its bound) leave 32 of the 512 registers, which are handed out by eights: enough for a
+    wavefront of a loader's next slot, which otherwise waits for the whole pixel kernel."""
+    import os
+    import re
+    import subprocess
+    from paper_1911_00472_amd import build
+    asm = tmp_path / "pcr.s"
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.check_call([hipcc] + flags + ["-S", "--cuda-device-only", "-o", str(asm), build.SRC], stderr=subprocess.DEVNULL)
+    used = re.findall(r"\.amdhsa_kernel \S*k_pixelILb\S*\n(?:.*\n)*?\s+\.amdhsa_next_free_vgpr (\d+)", asm.read_text())
+    assert len(used) == 4 and all(int(v) <= 120 for v in used), used
