@@ -198,6 +198,8 @@ struct CallTiming {
 
 // Records this process has open: the default choice between the two shapes of entropy decoder looks at it (lanes_pay).
 static std::atomic<int> g_open_records{0};
+// The streams of the last three decoding calls of this process, to be compared and nothing else (four_in_turn).
+static std::atomic<uintptr_t> g_last_streams[3];
 
 struct pcr_record {
     pcr_record() { g_open_records.fetch_add(1, std::memory_order_relaxed); }
@@ -229,6 +231,8 @@ struct pcr_record {
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
     int last_splits = 0, last_wide_splits = 0;            // ... launches of k_first_split, and those with a thousand lanes a unit
     int last_trios = 0;                                   // ... launches of k_decode_trios
+    bool of_loader = false;                               // the handle of a loader's slot
+    bool four = false;                                    // four_in_turn, of the last call
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
     std::vector<uint32_t> unit_bits;        // records opened from host bytes: entropy-coded bits of every unit, by slot (else empty)
     // decode fused with the training tail (allocated at its first call): one tile per run of an MCU row, the side buffer of first
@@ -322,12 +326,12 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
         std::stable_sort(set->begin(), set->end(), [](const ScanChain& a, const ScanChain& b) { return a.cost > b.cost; });     // the longest first
         for (const ScanChain& c : *set) {
             plan->chain_waves = std::max(plan->chain_waves, c.count);
+            uint32_t refines = 0;
+            for (uint32_t a = 0; a < c.count; a++) refines |= r->scan[(size_t)c.img * G + c.scan[a]].Ah > 0 ? 1u << a : 0u;
+            const uint32_t trios = (uint32_t)__builtin_popcount(refines);
+            plan->trio_waves = std::max(plan->trio_waves, c.count + 2 * trios);
+            plan->trio_lds = std::max(plan->trio_lds, c.count * kWaveTabBytes + trios * (uint32_t)sizeof(TrioRings));
             for (uint32_t j = 0; j < c.units; j++) {
-                uint32_t refines = 0;
-                for (uint32_t a = 0; a < c.count; a++) refines |= r->scan[(size_t)c.img * G + c.scan[a]].Ah > 0 ? 1u << a : 0u;
-                const uint32_t trios = (uint32_t)__builtin_popcount(refines);
-                plan->trio_waves = std::max(plan->trio_waves, c.count + 2 * trios);
-                plan->trio_lds = std::max(plan->trio_lds, c.count * kWaveTabBytes + trios * (uint32_t)sizeof(TrioRings));
                 list.push_back(UnitChain{(uint32_t)units.size(), (uint16_t)c.count, (uint16_t)refines, c.waits});
                 for (uint32_t a = 0; a < c.count; a++) units.push_back(Unit{c.img, c.scan[a], j, r->slot_base[(size_t)c.img * G + c.scan[a]]});
             }
@@ -664,18 +668,27 @@ SplitBy split_pays(const LevelList& l, int open_records) {
 //                    48 x 4 0.98    96 x 4 0.96   192 x 2 1.01    228 x 4 1.03
 //   the zero fill    12 to 456 x 1 1.00 to 1.03   48 x 4 1.02     96 x 4 0.99 (pixels past it as well: 0.98)     192 x 2 0.97 and 0.99    228 x 4 0.98    490 x 4 0.98
 //   pixel rows       445 x 1 1.05   192 x 1 1.00  111 x 4 1.01   445 x 2 1.01   222 x 4 0.99    445 x 4 0.97    192 x 2 0.89 (rows of whole lines; 384 x 2 0.98)
-// (Records that are open and idle look like records in flight; so it takes four of them to count.  The zero fill's line is the cache's size and not
-// less, because of loaders: their slots are open but decode one after the other, and at 228 MB a record the unstuffing launch with the fill took
-// 56 us a slot past the cache and 45 through it.)
+// ("Four in flight" is taken from four calls in a row on four streams (four_in_turn), not from open records, which may be idle or decoded one after the
+// other; and not of a loader's slots, each of which waits for its upload first: at 228 MB a slot the unstuffing launch with the fill took 56 us past the
+// cache and 45 through it.)
 struct CacheRule {
     static constexpr size_t kMB = 1u << 20;
     size_t planes, pixel_bytes;
     bool four;
-    explicit CacheRule(const pcr_record* r) : planes(r->coef_off[r->hdr.n] * sizeof(int16_t)), pixel_bytes((size_t)r->out_off[r->hdr.n]), four(g_open_records.load(std::memory_order_relaxed) >= 4) {}
+    explicit CacheRule(const pcr_record* r) : planes(r->coef_off[r->hdr.n] * sizeof(int16_t)), pixel_bytes((size_t)r->out_off[r->hdr.n]), four(r->four) {}
     bool pixels() const { return planes >= 16 * kMB && planes <= (four ? 128 : 208) * kMB; }
-    bool fill() const { return four && planes > 256 * kMB; }
+    bool fill() const { return four && planes > 208 * kMB; }
     bool flat_rows() const { return four && pixel_bytes > 256 * kMB; }
 };
+// Once per decoding call: whether this one and the last three were on four different streams.  A hint: calls of other threads in between may hide it.
+bool four_in_turn(const pcr_record* r, hipStream_t s) {
+    uintptr_t q[4] = {(uintptr_t)s};
+    for (int i = 0; i < 3; i++) q[i + 1] = g_last_streams[i].load(std::memory_order_relaxed);
+    for (int i = 0; i < 3; i++) g_last_streams[i].store(q[i], std::memory_order_relaxed);
+    bool four = !r->of_loader;
+    for (int i = 0; i < 4; i++) for (int j = 0; j < i; j++) four = four && q[i] != q[j];
+    return four;
+}
 
 // Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
 // regions in the same kernel: a launch costs about as much as k_index runs, and a workgroup of k_headers sums at most
@@ -735,6 +748,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     *plan_out = plan;
     const uint32_t n = r->hdr.n;
     call_begin(r, s);
+    r->four = four_in_turn(r, s);
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
     const bool several = g_open_records.load(std::memory_order_relaxed) > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
@@ -2176,7 +2190,7 @@ int pcr_loader_upload(pcr_loader* ld, int slot, size_t nbytes, pcr_record** rec)
     if (fresh) {
         sl->rec = new (std::nothrow) pcr_record();
         if (!sl->rec) { (void)hipStreamSynchronize(sl->stream); return PCR_E_NOMEM; }
-        sl->rec->device = ld->device; sl->rec->borrowed = true; sl->rec->stage.pinned = true;
+        sl->rec->device = ld->device; sl->rec->borrowed = true; sl->rec->stage.pinned = true; sl->rec->of_loader = true;
     }
     const int rc = bind_device(sl->rec, sl->dev, nbytes, (const uint8_t*)sl->host, sl->stream);
     if (rc && fresh) { pcr_close(sl->rec); sl->rec = nullptr; }
