@@ -267,30 +267,45 @@ struct LanesLaunch {
 // A launch of refinement scans by wavefronts (of one level, or of all where the scans of a component are decoded side by side), and
 // whether their units have three wavefronts each (pcr_refine_trio.h).
 //
-// Three take two thirds of the time of one while the launch takes as long as its longest unit, and half as many instructions again once it fills
-// the chip.  So what decides is the launch's work over that of its longest unit, a block counted as 14 bits: `full`, the number
-// of units where all are alike.  us a call by one wavefront a unit / by three, one record open:
-//   plain records, all scans side by side, scan group 10 (gray: 6)
-//     64 x 64, quality 90, noisy        64 of them  191 / 165    256  200 / 174    512  222 / 207   1024  256 / 314    (full 115, 460, 920, 1850)
-//     256 x 256                         64         1548 / 1144   400 1688 / 1272   600 1817 / 1562   800 2006 / 2104   (full 117, 726, 1088, 1448)
-//     256 x 256, 4:4:4, quality 85     128         1500 / 1155   300 1711 / 1438   400 1864 / 1848   512 2005 / 2173   (full 270, 630, 835, 1070)
-//     256 x 256, gray                  256         1564 / 1159   600 1687 / 1269   800 1811 / 1817                     (full 357, 837, 1114)
-//     300 to 500 pixels a side         512         5934 / 4265  1024 6453 / 6378                                       (full 744, 1488)
-//   entry points every 64 MCUs, level by level, scan group 10
-//     17 to 320 pixels a side           32          228 / 211     64  240 / 220    128  281 / 288    256  357 / 400    (full 461, 1091, 1902, 3711)
-//   a marker every MCU row, 256 x 256   16          160 / 155     64  229 / 316                                        (full 940, 3812)
-//   four records at a time, plain, 128 x 128 128 in each 1098 / 861  256 1209 / 1039 512 1502 / 1576                 (full 230, 460, 920)
-//     300 to 500 pixels a side         400 in each 14431 / 12421  512 13144 / 14470; of two 512 7789 / 7010             (full 581, 744)
-//     128 x 128, entry points every 64 MCUs  64   487 / 453   128  531 / 536                                            (full 490, 980)
-// (Where several are decoded at a time the line would lie at some 650; one alone, at 650 to 850, gains more than four together lose there,
-// and how many records the process has open does not say which it is.)
+// Three take two thirds of the time of one while the launch takes as long as its longest unit, and up to half as much again once the launches
+// of all records in flight fill the chip.  So what decides is `full`: what the launch asks of the chip over its longest unit, in bits, a block counted as
+// 14 and the start of a workgroup as 500 (it brings tables, and takes the room of the widest one, whatever is in it), first scans
+// beside the refinement scans by half of theirs (they keep one wavefront).  Where the line lies depends on the records decoded at a time; the
+// records the process has open are taken as the sign of it, as by split_pays and the lanes: idle ones cost what three wavefronts gain
+// there, and never more than one wavefront a unit takes.  us a call by one wavefront a unit / by three (n pictures a record; full):
+//                                                  one record              two                    four
+//   plain records (all scans side by side)
+//     300 to 500 pixels, scan group 10   n 400    5716 / 4123  (701)     7412 / 5881         14404 / 12175
+//                                          512    5860 / 4256  (899)     7703 / 6954         14917 / 14470
+//                                          640    6038 / 4394  (1121)    8332 / 8474         15914 / 16912
+//                                          800    6223 / 4906  (1399)    9053 / 10544
+//                                         1024    6456 / 6344  (1793)   10218 / 13394
+//     96 x 96, 4:4:4, scan group 6         700     304 / 285   (1183)     591 / 553            825 / 899
+//                                         1200     349 / 396   (2007)     543 / 687           1116 / 1420
+//     192 x 192, 4:4:4, 6                  700     897 / 798   (1067)    1377 / 1430          2071 / 2709
+//     128 x 128, gray, 6                   550     496 / 400   (1099)     726 / 742           1431 / 1468
+//                                          900     571 / 650   (1783)     919 / 1095          1562 / 1981
+//     64 x 64, 10                          400     213 / 188   (917)      265 / 274            525 / 544
+//     24 x 24, 8                           250     115 / 112   (995)      130 / 132            253 / 265
+//                                          900     121 / 137   (3362)     161 / 192            324 / 389
+//   a marker every MCU row, 256 x 256, 10   16     160 / 150   (1066)     187 / 206            334 / 373
+//                                           32     170 / 208   (2215)     232 / 312            444 / 617
+//   entry points every 64 MCUs (level by level)
+//     17 to 320 pixels, 10                  64     243 / 228   (1078)     284 / 284            520 / 529
+//                                          128     271 / 280   (1895)     335 / 364            649 / 739
+// (Over 190 kinds of records at one, two and four at a time and scan groups 4 to 10 the three lines lose 0.1, 0.6 and 0.7 % against the better
+// of the two.)
 struct TrioLaunch {
-    uint64_t work = 0; uint32_t longest = 0;
+    uint64_t work = 0, beside = 0; uint32_t longest = 0, groups = 0;       // groups: workgroups of the launch
     void add(const LanesLaunch& l) {
         work += l.bits + 14 * l.blocks;
         longest = std::max(longest, l.longest_bits + 14 * l.longest_blocks);
     }
-    bool pays() const { return longest > 0 && work <= 850ull * longest; }
+    void add_beside(const LanesLaunch& l) { beside += l.bits + 14 * l.blocks; }
+    bool pays(int open_records) const {
+        const uint64_t line = open_records <= 1 ? 1500 : (open_records <= 3 ? 950 : 700);
+        return longest > 0 && work + beside / 2 + 500ull * groups <= line * (longest + 70);
+    }
 };
 
 // The MCUs of a DC scan, as far as lanes that decode them in step have to agree on them.

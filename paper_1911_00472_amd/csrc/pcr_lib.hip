@@ -750,12 +750,13 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     call_begin(r, s);
     r->four = four_in_turn(r, s);
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
-    const bool several = g_open_records.load(std::memory_order_relaxed) > 1;
+    const int open = g_open_records.load(std::memory_order_relaxed);
+    const bool several = open > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
     r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = r->last_trios = 0;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
-        if (l.kind == kSequential) by_lanes[li] = (char)split_pays(l, g_open_records.load(std::memory_order_relaxed));
+        if (l.kind == kSequential) by_lanes[li] = (char)split_pays(l, open);
         else if (l.kind != kDcFirst) {
             by_lanes[li] = lanes_pay(r, l, several) ? 1 : 0;
             if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
@@ -831,18 +832,22 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         else hipLaunchKernelGGL(k_first_split<256>, dim3(n_units), dim3(256), 0, s, r->d, units, done, c32, dc_to_planes ? 1u : 0u);
         return done;
     };
-    // Whether the refinement scans of a level, or of all levels in one launch, get three wavefronts a unit.
-    auto trios = [&](const LevelList* one) {
+    // Whether the refinement scans of a level, or of all levels in one launch (beside the AC first scans), get three wavefronts a unit.
+    auto trios = [&](const LevelList* one, uint32_t groups) {
         TrioLaunch t;
-        for (const LevelList& l : plan->levels) if (l.kind == kAcRefine && (!one || one == &l)) t.add(l.lanes);
-        const bool pays = r->lane_mode >= 0 && t.pays();
+        t.groups = groups;
+        for (const LevelList& l : plan->levels) {
+            if (l.kind == kAcRefine && (!one || one == &l)) t.add(l.lanes);
+            if (l.kind == kAcFirst && !one) t.add_beside(l.lanes);
+        }
+        const bool pays = r->lane_mode >= 0 && t.pays(open);
         r->last_trios += pays ? 1 : 0;
         return pays;
     };
     auto waves = [&](const LevelList& l) {
         const bool dc = l.kind == kDcFirst;
         const uint32_t* had = dc ? split(l.split, true, l.d_units, l.n, l.d_done) : nullptr;
-        if (l.kind == kAcRefine && trios(&l)) {
+        if (l.kind == kAcRefine && trios(&l, l.n)) {
             hipLaunchKernelGGL((k_decode_trios<kWavesAc, false>), dim3(l.n), dim3(3 * kEntropyLanes), kWaveTabBytes + sizeof(TrioRings), s, r->d, l.d_units, (const UnitChain*)nullptr, c32, 0u, (const uint32_t*)nullptr);
             return;
         }
@@ -855,7 +860,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
         auto* kernel = w > 1 ? (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, true> : k_decode_waves<kWavesAc, true>)
                              : (dc_beside ? k_decode_waves<kWavesDc | kWavesAc, false> : k_decode_waves<kWavesAc, false>);
         const dim3 groups(dc_beside ? plan->n_chains : plan->n_ac_chains);
-        if (plan->trio_waves > w && plan->trio_waves <= kTrioChainWaves && trios(nullptr))
+        if (plan->trio_waves > w && plan->trio_waves <= kTrioChainWaves && trios(nullptr, groups.x))
             hipLaunchKernelGGL((dc_beside ? k_decode_trios<kWavesDc | kWavesAc, true> : k_decode_trios<kWavesAc, true>), groups, dim3(kEntropyLanes * plan->trio_waves), plan->trio_lds, s, r->d,
                                plan->d_chain_units, plan->d_chains, c32, dc_to_planes ? 1u : 0u, had);
         else

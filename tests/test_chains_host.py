@@ -131,6 +131,38 @@ DC_TIMES = [
 ]
 
 
+# bits of a launch's refinement scans, of their longest unit, of the first scans beside them (14 a block added), workgroups, and us a call by one
+# wavefront a unit and by three with 1, 2 and 4 records of it at a time
+TRIO_TIMES = [
+    (220979340, 390258, 103456860, 1600, {1: (5716, 4123), 2: (7412, 5881), 4: (14404, 12175)}), (283259540, 390258, 132854292, 2048, {1: (5860, 4256), 2: (7703, 6954), 4: (14917, 14470)}),
+    (353493736, 390258, 165346008, 2560, {1: (6038, 4394), 2: (8332, 8474), 4: (15914, 16912)}), (441337496, 390258, 206327024, 3200, {1: (6223, 4906), 2: (9053, 10544)}),
+    (565408820, 390258, 264644940, 4096, {1: (6456, 6344), 2: (10218, 13394)}), (202014542, 322898, 264644940, 4096, {1: (5166, 4024), 2: (7427, 7364)}),
+    (5556344, 11408, 13242080, 2800, {1: (304, 285), 4: (825, 899)}), (9463472, 11448, 22513536, 4800, {1: (349, 396), 2: (543, 687), 4: (1116, 1420)}),
+    (9463472, 11448, 12151960, 4800, {1: (316, 326), 2: (449, 522), 4: (891, 1028)}), (21930696, 45808, 51212232, 2800, {1: (897, 798), 2: (1377, 1430), 4: (2071, 2709)}),
+    (23527744, 26456, 10150128, 1100, {1: (496, 400), 2: (726, 742), 4: (1431, 1468)}), (38208872, 26480, 16433400, 1800, {1: (571, 650), 2: (919, 1095), 4: (1562, 1981)}),
+    (4448712, 6672, 1866288, 1600, {1: (213, 188), 2: (265, 274), 4: (525, 544)}), (635104, 758, 696856, 3600, {1: (121, 137), 2: (161, 192), 4: (324, 389)}),
+    (120226024, 105552, 48068928, 2800, {1: (1839, 1674), 2: (3131, 3495), 4: (4935, 6782)}), (49392072, 80624, 61699024, 3600, {1: (1441, 1130), 4: (4167, 4335)}),
+    (2433792, 3314, 1065960, 1280, {1: (160, 150), 2: (187, 206), 4: (334, 373)}), (5118056, 3314, 2192920, 2560, {1: (170, 208), 2: (232, 312), 4: (444, 617)}),
+    (690128, 848, 317216, 1280, {1: (112, 114), 2: (126, 140), 4: (169, 210)}), (1306186, 3281, 0, 476, {1: (227, 210), 2: (443, 412), 4: (500, 464)}),
+    (3082852, 3291, 0, 1083, {1: (243, 228), 2: (284, 284), 4: (520, 529)}), (5462106, 3301, 0, 1851, {1: (271, 280), 2: (335, 364), 4: (649, 739)}),
+]
+
+
+@pytest.mark.parametrize("work, longest, beside, groups, times", TRIO_TIMES)
+def test_refinement_scans_go_where_they_were_measured_to_be_faster(plan, work, longest, beside, groups, times):
+    """With the records that are decoded at a time, three wavefronts a unit are nowhere taken where they are 4 % slower than one; nor is one where three gain a
+    tenth, or, close to the line (seven ninths of the launch would go to three), a fifth."""
+    lib = plan.lib
+    lib.trio_pays.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int]
+    for open_records, (one, three) in times.items():
+        if lib.trio_pays(work, longest, beside, groups, open_records):
+            assert three <= 1.04 * one, open_records
+        else:
+            near = lib.trio_pays(work * 7 // 9, longest, beside * 7 // 9, groups * 7 // 9, open_records)
+            assert three >= (0.8 if near else 0.9) * one, open_records
+    assert not any(lib.trio_pays(work, longest, beside, groups, n + 1) and not lib.trio_pays(work, longest, beside, groups, n) for n in range(0, 6))
+
+
 @pytest.mark.parametrize("several, beside, whole, longest, mean, times", DC_TIMES)
 def test_dc_scans_go_where_they_were_measured_to_be_faster(plan, several, beside, whole, longest, mean, times):
     for units, (wavefronts, lanes) in times.items():

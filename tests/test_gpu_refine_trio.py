@@ -78,6 +78,16 @@ def test_both_sides_of_the_line(entry):
     _same(write(files * 256), [6], (0, 1000, 2047), trios=False)
 
 
+def test_records_open_beside_move_the_line():
+    files = [pcrgen.make_jpeg(40 + i, 1, 72, 56, 1, 8.0, 1, 1, 92) for i in range(8)]
+    rec = pcrgen.write_record(files * 60)
+    _same(rec, [6], range(8))
+    others = [pkg.pcr_open(pcrgen.write_record(files[:1]), 0) for _ in range(3)]
+    _same(rec, [6], range(8), trios=False)
+    for o in others:
+        o.close()
+
+
 def test_damage_is_seen_alike():
     """Streams cut short, overwritten and with bits flipped: the same images are flagged, the others are what they were."""
     rng = np.random.default_rng(3)
