@@ -426,6 +426,9 @@ int pcr_last_first_splits(pcr_record* rec, int* launches, int* wide_launches);
 /* Launches of the last decode call in which every unit of a refinement scan had three wavefronts (taken by launches for the wavefronts that take
  * as long as their longest unit; never in mode -1). */
 int pcr_last_refine_trios(pcr_record* rec, int* launches);
+/* Whether the pixels of the last decode call were stored past the chip's caches (records whose coefficient planes fit in the 256 MB of the memory-side cache but
+ * not beside the pixels; the pixels are the same). */
+int pcr_last_past_stores(pcr_record* rec, int* past);
 
 /* Stage timing with HIP events recorded on the call's own stream (off by default; switching it on
  * starts a new history).  While it is on, every stage has launches of its own, and first scans are not given many lanes each (DC_FIRST and

@@ -41,6 +41,7 @@ SYMBOLS = {
     "pcr_set_lane_decoders": (ctypes.c_int, [_vp, ctypes.c_int]),
     "pcr_last_decoder_shapes": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_refine_trios": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int)]),
+    "pcr_last_past_stores": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_first_splits": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_stage_ms": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_float)]),
     "pcr_probe_scalar_issue_rate": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]),
@@ -361,6 +362,12 @@ class Record:
         a = ctypes.c_int()
         _check(lib().pcr_last_refine_trios(self._h, ctypes.byref(a)), "pcr_last_refine_trios")
         return a.value
+
+    def last_past_stores(self):
+        """Whether the last decode call stored its pixels past the chip's caches."""
+        a = ctypes.c_int()
+        _check(lib().pcr_last_past_stores(self._h, ctypes.byref(a)), "pcr_last_past_stores")
+        return bool(a.value)
 
     def last_first_splits(self):
         """(launches that gave first scans many lanes each, those of them of a thousand lanes) of the last decode call."""

@@ -198,8 +198,6 @@ struct CallTiming {
 
 // Records this process has open: the default choice between the two shapes of entropy decoder looks at it (lanes_pay).
 static std::atomic<int> g_open_records{0};
-// The streams of the last three decoding calls of this process, to be compared and nothing else (four_in_turn).
-static std::atomic<uintptr_t> g_last_streams[3];
 
 struct pcr_record {
     pcr_record() { g_open_records.fetch_add(1, std::memory_order_relaxed); }
@@ -231,8 +229,7 @@ struct pcr_record {
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
     int last_splits = 0, last_wide_splits = 0;            // ... launches of k_first_split, and those with a thousand lanes a unit
     int last_trios = 0;                                   // ... launches of k_decode_trios
-    bool of_loader = false;                               // the handle of a loader's slot
-    bool four = false;                                    // four_in_turn, of the last call
+    bool last_past = false;                               // ... whether its pixels were stored past the caches (pixels_past)
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
     std::vector<uint32_t> unit_bits;        // records opened from host bytes: entropy-coded bits of every unit, by slot (else empty)
     // decode fused with the training tail (allocated at its first call): one tile per run of an MCU row, the side buffer of first
@@ -660,34 +657,35 @@ SplitBy split_pays(const LevelList& l, int open_records) {
     return l.several_tries && tries < steps && tries < sequential ? kSplitByTries : (steps < sequential ? kSplitBySteps : kSplitNever);
 }
 
-// Which stores ask the caches to make no room for what they store (put_past).  The chip's memory-side cache holds 256 MB for all records in flight:
-// coefficient planes that fit are still there when the pixel kernel reads them unless its own pixels push them out, planes that do not are better
-// written past it, so that what other records have there stays.  Both ways, the call's time past the cache over its time through it (MB of planes, or of
-// pixels for DC-only decodes; records in flight):
-//   k_pixel          12 x 1 0.99    24 x 1 0.99    48 x 1 0.99    96 x 1 1.00 (scan group 10: 0.98)   192 x 1 0.92 and 0.95    228 x 1 0.98    384 x 1 1.01    456 x 1 1.01
-//                    48 x 4 0.98    96 x 4 0.96   192 x 2 1.01    228 x 4 1.03
-//   the zero fill    12 to 456 x 1 1.00 to 1.03   48 x 4 1.02     96 x 4 0.99 (pixels past it as well: 0.98)     192 x 2 0.97 and 0.99    228 x 4 0.98    490 x 4 0.98
-//   pixel rows       445 x 1 1.05   192 x 1 1.00  111 x 4 1.01   445 x 2 1.01   222 x 4 0.99    445 x 4 0.97    192 x 2 0.89 (rows of whole lines; 384 x 2 0.98)
-// ("Four in flight" is taken from four calls in a row on four streams (four_in_turn), not from open records, which may be idle or decoded one after the
-// other; and not of a loader's slots, each of which waits for its upload first: at 228 MB a slot the unstuffing launch with the fill took 56 us past the
-// cache and 45 through it.)
-struct CacheRule {
-    static constexpr size_t kMB = 1u << 20;
-    size_t planes, pixel_bytes;
-    bool four;
-    explicit CacheRule(const pcr_record* r) : planes(r->coef_off[r->hdr.n] * sizeof(int16_t)), pixel_bytes((size_t)r->out_off[r->hdr.n]), four(r->four) {}
-    bool pixels() const { return planes >= 16 * kMB && planes <= (four ? 128 : 208) * kMB; }
-    bool fill() const { return four && planes > 208 * kMB; }
-    bool flat_rows() const { return four && pixel_bytes > 256 * kMB; }
-};
-// Once per decoding call: whether this one and the last three were on four different streams.  A hint: calls of other threads in between may hide it.
-bool four_in_turn(const pcr_record* r, hipStream_t s) {
-    uintptr_t q[4] = {(uintptr_t)s};
-    for (int i = 0; i < 3; i++) q[i + 1] = g_last_streams[i].load(std::memory_order_relaxed);
-    for (int i = 0; i < 3; i++) g_last_streams[i].store(q[i], std::memory_order_relaxed);
-    bool four = !r->of_loader;
-    for (int i = 0; i < 4; i++) for (int j = 0; j < i; j++) four = four && q[i] != q[j];
-    return four;
+// Whether the pixel kernel asks the caches to make no room for its pixels (put_past).
+//
+// The chip's memory-side cache holds 256 MB.  Planes of a record that fit in it are still there when the pixel kernel reads them, but pixels that
+// do not fit beside them push them out as they are written.  Where both fit, or the planes alone do not, or other records' planes and pixels pass through
+// the cache meanwhile, nothing is gained, and who reads the pixels next finds them in memory only.  So: a record whose planes fit
+// and whose pixels do not fit beside them, with no more than three records open (as by split_pays; of two or three that are decoded at the same time
+// some lose), without refinement (which reads masks and records beside the planes), and whole pictures (pixels of boxes are for the training tail, at
+// once).  Time past the cache over the time through it: the call alone / with a conversion of all pixels to half precision behind it / with their maximum
+//   MB of planes + pixels; in flight    1                         2                         4                         8
+//     24 + 24                        0.98 / 1.11 / 1.00
+//     96 + 96                        0.99 / 1.16 / 1.05
+//    120 + 120                       0.98 / 1.02 / 1.02        0.94 / 0.98 / 0.98        1.00 / 1.00 / 1.01        1.00 / 1.00 / 1.01
+//    150 + 150                       0.94 / 0.99 / 0.94        0.99 / 1.00 / 1.02        1.01 / 1.00 / 1.00        1.01 / 1.00 / 1.01
+//    159 + 154, odd widths           0.94 / 0.99 / 0.94        1.02 / 1.02 / 1.05        1.05 / 1.02 / 1.05        1.05 / 1.01 / 1.04
+//    192 + 192                       0.88 / 0.98 / 0.94        0.95 / 0.97 / 0.93        0.98 / 1.00 / 0.98        0.99 / 1.00 / 0.98
+//    192 + 192, 1024 x 1024          0.89 / 0.97 / 0.93        1.00 / 1.01 / 1.02        0.99 / 1.00 / 0.99        1.00 / 1.00 / 1.00
+//    202 + 195, odd widths           0.89 / 0.98 / 0.94        0.96 / 0.98 / 0.94        1.02 / 1.01 / 1.02        1.04 / 1.01 / 1.03
+//    234 + 234                       0.93 / 0.98 / 0.96        1.02 / 1.00 / 1.01        1.00 / 1.00 / 0.99        1.01 / 1.00 / 0.99
+//    255 + 255                       0.96 / 1.00 / 0.98        1.02 / 1.00 / 1.01        1.02 / 1.00 / 1.01        1.01 / 1.00 / 1.01
+//    150 + 75, 4:4:4                 1.00 / 1.06 / 1.02        0.99 / 1.04 / 1.02        0.99 / 1.00 / 1.02        0.99 / 1.00 / 1.01
+//    210 + 105, 4:4:4                0.94 / 1.00 / 0.95        0.99 / 1.00 / 1.01        0.98 / 1.00 / 0.99        0.99 / 1.00 / 1.00
+//    225 + 112, gray                 0.92 / 1.00 / 0.97        0.96 / 1.00 / 0.96        0.98 / 1.00 / 1.00        0.99 / 1.00 / 1.00
+//    150 + 150, scan group 10        0.98 / 1.00 / 0.98        0.99 / 1.00 / 1.01        0.99 / 1.00 / 1.00        0.99 / 1.00 / 1.00
+//    192 + 192, scan group 10        0.99 / 1.01 / 1.00        0.99 / 1.01 / 1.00        0.99 / 1.00 / 1.00        0.99 / 1.00 / 1.00
+// The training tail behind it, from the buffer: 24 + 24 1.08, 96 + 96 1.16, 192 + 192 0.98 (of boxes 1.01), 192 + 96 1.03 (1.07).
+bool pixels_past(const pcr_record* r, const Plan* plan, bool boxes) {
+    constexpr uint64_t kMB = 1u << 20;
+    const uint64_t planes = r->coef_off[r->hdr.n] * sizeof(int16_t), pixels = r->out_off[r->hdr.n];
+    return planes <= 256 * kMB && planes + pixels > 280 * kMB && plan->has_ac && !plan->n_apply && !boxes && g_open_records.load(std::memory_order_relaxed) <= 3;
 }
 
 // Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
@@ -729,7 +727,6 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, Apply
     P.first[count] = groups;
     size_t pieces = 0;
     for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
-    fill.past = CacheRule(r).fill() ? 1u : 0u;
     const uint32_t lanes = 64 * waves;                       // (eight pieces per lane, but for the last row)
     fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 8 * lanes - 1) / (8 * lanes), std::min<size_t>(many ? 512 : 2048, std::max<size_t>(groups, many ? 256 : 1024))));
     const uint32_t total = lists.groups + groups + kDies * fill.rows;
@@ -748,12 +745,12 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     *plan_out = plan;
     const uint32_t n = r->hdr.n;
     call_begin(r, s);
-    r->four = four_in_turn(r, s);
     // (decided once per call: the answer depends on how many records the process has open, which another thread may change)
     const int open = g_open_records.load(std::memory_order_relaxed);
     const bool several = open > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
     r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = r->last_trios = 0;
+    r->last_past = false;
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
         if (l.kind == kSequential) by_lanes[li] = (char)split_pays(l, open);
@@ -1563,6 +1560,11 @@ int pcr_last_refine_trios(pcr_record* r, int* launches) {
     *launches = r->last_trios;
     return PCR_OK;
 }
+int pcr_last_past_stores(pcr_record* r, int* past) {
+    if (!r || !past) return PCR_E_ARG;
+    *past = r->last_past ? 1 : 0;
+    return PCR_OK;
+}
 int pcr_last_first_splits(pcr_record* r, int* launches, int* wide_launches) {
     if (!r || !launches || !wide_launches) return PCR_E_ARG;
     *launches = r->last_splits; *wide_launches = r->last_wide_splits;
@@ -1632,19 +1634,18 @@ static int decode_to_pixels(pcr_record* r, int k0, int k, uint8_t* out, size_t c
     // launches took 150 of the 1550 us of 2048 pictures of 132 x 133 at scan group 10, to find that there is none)
     DevRecord d = r->d;
     d.status_out = d_status;
-    const CacheRule cache(r);
-    const uint32_t pixels_past = cache.pixels() ? 1u : 0u;
+    r->last_past = pixels_past(r, plan, boxes != nullptr);
     const bool smooth_flat = smooth && !plan->has_ac && !plan->n_apply && !boxes;
     if (smooth_flat || !plan->smooths) smooth = false;
     if (smooth) hipLaunchKernelGGL(k_smooth<false>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
     if (smooth_flat)
         hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out);
     else if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes, pixels_past);
+        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
     else if (plan->has_ac || smooth)
-        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes, pixels_past);
+        hipLaunchKernelGGL((r->last_past ? k_pixel<false, false, true> : k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
     else if (r->n_flat_rows && !boxes)                       // DC scans only: every block is flat
-        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells, cache.flat_rows() ? 1u : 0u);
+        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
     else
         hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out, boxes);
     if (smooth) hipLaunchKernelGGL(k_smooth<true>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
@@ -1688,9 +1689,9 @@ int pcr_decode_batch_triangle(pcr_record* r, int k, uint8_t* out, size_t cap, vo
     DevRecord d = r->d;
     d.status_out = d_status;
     if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr, 0u);
+        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr);
     else
-        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr, 0u);
+        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr);
     uint32_t items = 1;
     for (uint32_t i = 0; i < n; i++) items = std::max(items, (((uint32_t)r->img[i].W + 3) / 4) * (uint32_t)r->img[i].H);
     hipLaunchKernelGGL(k_triangle_rgb, dim3((items + 255) / 256, n), dim3(256), 0, s, r->d, (const uint8_t*)r->d_planes, out);
@@ -2195,7 +2196,7 @@ int pcr_loader_upload(pcr_loader* ld, int slot, size_t nbytes, pcr_record** rec)
     if (fresh) {
         sl->rec = new (std::nothrow) pcr_record();
         if (!sl->rec) { (void)hipStreamSynchronize(sl->stream); return PCR_E_NOMEM; }
-        sl->rec->device = ld->device; sl->rec->borrowed = true; sl->rec->stage.pinned = true; sl->rec->of_loader = true;
+        sl->rec->device = ld->device; sl->rec->borrowed = true; sl->rec->stage.pinned = true;
     }
     const int rc = bind_device(sl->rec, sl->dev, nbytes, (const uint8_t*)sl->host, sl->stream);
     if (rc && fresh) { pcr_close(sl->rec); sl->rec = nullptr; }
