@@ -321,15 +321,17 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
     std::vector<Unit> units; std::vector<UnitChain> list;
     for (auto* set : {&chains.ac, &chains.dc}) {
         std::stable_sort(set->begin(), set->end(), [](const ScanChain& a, const ScanChain& b) { return a.cost > b.cost; });     // the longest first
+        uint32_t count = 0, refines = 0;                     // of the chain before: most are alike
         for (const ScanChain& c : *set) {
-            plan->chain_waves = std::max(plan->chain_waves, c.count);
-            uint32_t refines = 0;
-            for (uint32_t a = 0; a < c.count; a++) refines |= r->scan[(size_t)c.img * G + c.scan[a]].Ah > 0 ? 1u << a : 0u;
-            const uint32_t trios = (uint32_t)__builtin_popcount(refines);
-            plan->trio_waves = std::max(plan->trio_waves, c.count + 2 * trios);
-            plan->trio_lds = std::max(plan->trio_lds, c.count * kWaveTabBytes + trios * (uint32_t)sizeof(TrioRings));
+            if (c.count != count || c.refines != refines) {
+                count = c.count; refines = c.refines;
+                const uint32_t trios = (uint32_t)__builtin_popcount(refines);
+                plan->chain_waves = std::max(plan->chain_waves, count);
+                plan->trio_waves = std::max(plan->trio_waves, count + 2 * trios);
+                plan->trio_lds = std::max(plan->trio_lds, count * kWaveTabBytes + trios * (uint32_t)sizeof(TrioRings));
+            }
             for (uint32_t j = 0; j < c.units; j++) {
-                list.push_back(UnitChain{(uint32_t)units.size(), (uint16_t)c.count, (uint16_t)refines, c.waits});
+                list.push_back(UnitChain{(uint32_t)units.size(), c.count, c.refines, c.waits});
                 for (uint32_t a = 0; a < c.count; a++) units.push_back(Unit{c.img, c.scan[a], j, r->slot_base[(size_t)c.img * G + c.scan[a]]});
             }
         }

@@ -9,7 +9,8 @@ using namespace pcr;
 // Scans k0 .. k - 1 of an image, `count` scans in all; row g of scans: components (a bit each), Ss, Se, Ah, Al, restart
 // interval, units, entry points.  Row g of out: the launch that decodes the scan (0: the chains, 1 + level: a launch of
 // its level after them, -1: none), its chain (AC: from 0 on, DC: from 1000 on), its place in the chain, the places of the
-// scans of the chain that it waits for (a bit each).  Returns whether all scans of the call keep in step.
+// scans of the chain that it waits for (a bit each).  Returns whether all scans of the call keep in step (-1: a chain is wrong about which of its scans
+// are refinement scans).
 extern "C" int chain_plan(const int* scans, int count, int k0, int k, int* out) {
     std::vector<ScanDesc> s((size_t)count);
     std::vector<uint32_t> units((size_t)count), entries((size_t)count);
@@ -35,6 +36,7 @@ extern "C" int chain_plan(const int* scans, int count, int k0, int k, int* out) 
         const auto& list = kind ? set.dc : set.ac;
         for (size_t c = 0; c < list.size(); c++)
             for (uint32_t a = 0; a < list[c].count; a++) {
+                if ((list[c].refines >> a & 1u) != (s[list[c].scan[a]].Ah > 0 ? 1u : 0u)) return -1;
                 int* o = out + 4 * list[c].scan[a];
                 o[0] = 0; o[1] = (int)c + 1000 * kind; o[2] = (int)a; o[3] = (int)(list[c].waits >> (8 * a) & 255u);
             }

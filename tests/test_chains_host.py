@@ -22,6 +22,7 @@ def plan(tmp_path_factory):
         a = np.ascontiguousarray(scans, np.int32).reshape(-1, 8)
         out = np.zeros((len(a), 4), np.int32)
         step = lib.chain_plan(a.ctypes.data_as(ctypes.POINTER(ctypes.c_int)), len(a), k0, len(a) if k is None else k, out.ctypes.data_as(ctypes.POINTER(ctypes.c_int)))
+        assert step >= 0
         return bool(step), out
     run.lib = lib
     return run
