@@ -417,6 +417,15 @@ int pcr_transcode_batch(pcr_record* rec, const void* const* files, const size_t*
  * The results are the same bit for bit.  Takes effect from the next decode call.  PCR_E_ARG: null handle or another
  * mode. */
 int pcr_set_lane_decoders(pcr_record* rec, int mode);
+/* Sequential (baseline) scans by one decoder or many.  mode 0 (default): long scans by as many as are faster for the launch; 1: one wavefront for every
+ * scan or restart interval; 2: long ones by many lanes in steps; 3: long ones by many lanes by tries.  Streams that do not fall into step are
+ * left to one wavefront in every mode.  The results are the same bit for bit.  Takes effect from the next decode call, which makes its plan (mode 3: and the
+ * memory the tries work in) anew.  PCR_E_ARG: null handle or another mode. */
+int pcr_set_sequential_decoders(pcr_record* rec, int mode);
+/* How the last decode call decoded its sequential scans.  by: 0 there were none, else the mode it came to (the highest of its launches).  Of the units
+ * given to many lanes counts[0] fell into step by tries, counts[1] in steps, counts[2] were left to one wavefront; rounds[0] and rounds[1]: the most
+ * rounds one of those took (0 by tries: every piece began where some try had ended).  Once that call is done on the device. */
+int pcr_last_sequential_decoders(pcr_record* rec, int* by, uint32_t counts[3], uint32_t rounds[2]);
 /* How the last decode call on this handle decoded its AC scans: launches that gave every unit a lane, launches that gave
  * every unit a wavefront (host ints; both 0 before the first call or when only DC scans were decoded). */
 int pcr_last_decoder_shapes(pcr_record* rec, int* lane_launches, int* wavefront_launches);

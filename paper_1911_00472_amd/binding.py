@@ -41,6 +41,8 @@ SYMBOLS = {
     "pcr_set_lane_decoders": (ctypes.c_int, [_vp, ctypes.c_int]),
     "pcr_last_decoder_shapes": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_refine_trios": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int)]),
+    "pcr_set_sequential_decoders": (ctypes.c_int, [_vp, ctypes.c_int]),
+    "pcr_last_sequential_decoders": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.c_uint32 * 3, ctypes.c_uint32 * 2]),
     "pcr_last_past_stores": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_first_splits": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_stage_ms": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_float)]),
@@ -362,6 +364,16 @@ class Record:
         a = ctypes.c_int()
         _check(lib().pcr_last_refine_trios(self._h, ctypes.byref(a)), "pcr_last_refine_trios")
         return a.value
+
+    def set_sequential_decoders(self, mode):
+        """Sequential scans: 0 by what is faster, 1 a wavefront each, 2 long ones in steps, 3 long ones by tries."""
+        _check(lib().pcr_set_sequential_decoders(self._h, mode), "pcr_set_sequential_decoders")
+
+    def last_sequential_decoders(self):
+        """(mode the last decode call came to, units that fell into step by tries, in steps, left to one wavefront, most rounds by tries, in steps)."""
+        by, counts, rounds = ctypes.c_int(), (ctypes.c_uint32 * 3)(), (ctypes.c_uint32 * 2)()
+        _check(lib().pcr_last_sequential_decoders(self._h, ctypes.byref(by), counts, rounds), "pcr_last_sequential_decoders")
+        return (by.value,) + tuple(counts) + tuple(rounds)
 
     def last_past_stores(self):
         """Whether the last decode call stored its pixels past the chip's caches."""

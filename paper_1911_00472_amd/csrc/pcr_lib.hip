@@ -34,17 +34,90 @@ using namespace pcr;
 namespace {
 
 enum Kind { kDcFirst = 0, kAcFirst = 1, kAcRefine = 2, kSequential = 3, kNumKinds = 4 };
+enum SplitBy { kSplitNever = 0, kSplitBySteps = 1, kSplitByTries = 2 };
+// Blocks of an MCU of a sequential scan: the tries of a piece (k_split_tries).
+uint32_t split_tries_of(const ImgDesc& im, const ScanDesc& sd) {
+    uint32_t tries = 0;
+    for (int j = 0; j < sd.ns; j++) tries += sd.ns == 1 ? 1u : (uint32_t)im.hs[sd.comp[j]] * im.vs[sd.comp[j]];
+    return std::max(1u, tries);
+}
+// The long sequential scans of a launch: many lanes each, or one wavefront?  k_sequential takes as long as its longest scan until some thousand of them fill the
+// scalar units.  k_sequential_split has room for one scan per compute unit (150 KB of LDS), 256 at a time, and a step takes as long as its
+// slowest lane.  k_split_tries and what follows use the whole chip for few scans, but decode up to thirteen times what one decoder would.
+// ms for n files, by tries / k_sequential_split / k_sequential (the whole call; -: not measured):
+//                        n = 1              32             128            512            2048
+//   4:2:0, 166 KB    0.9/ 1.9/17     1.1/ 2.4/17    1.9/ 2.3/17    5.0/ 4.6/ -      -  /16.1/ -
+//   4:2:0, 50 KB     0.7/ 1.6/5.1    0.9/ 2.1/5.1   0.9/ 2.0/5.1   2.0/ 3.7/ -     8.4/ -  /4.3
+//   4:2:0, 19 KB     0.6/ 1.4/1.9    0.8/ 1.6/1.9   0.8/ 1.5/1.9   1.2/ 2.3/1.4    6.4/ -  /1.7
+//   4:4:4, 203 KB    0.8/ 1.3/21     1.0/ 1.4/21    1.9/ 1.4/ -    4.8/ 3.1/ -      -  /11.7/ -
+//   q 97, 99 KB      1.5/ 6.2/5.3    1.6/ 6.4/5.4   1.6/ 6.4/5.5   4.0/ 7.3/ -      -  /12.6/ -
+//   gray, 163 KB     0.8/ 0.8/17     0.9/ 1.2/17    1.1/ 1.1/17    2.6/ 2.2/ -      -  / 8.2/ -
+//   2.5 MP, 1.8 MB   3.6/ 6.5/ -     4.9/ 8.0/ -   11.0/ 8.5/ -   45.8/21.4/ -      -
+// (steps at quality 97: given up, and decoded by k_sequential behind it.)  The lines below follow these figures (in us; kb: the mean of the long
+// scans); where every MCU is one block there is one try, and nothing to be had of them.  A record decoded beside others shares
+// the compute units with them; the records the process has open (four at most count) are taken as the sign of it, as by
+// lanes_pay.  (Without this choice 4096 baseline photographs in four records took 29.1 ms instead of 23.2.)
+//
+// The tries work in memory of the record (SplitSpace), which it has where some number of open records would have them chosen.
+struct SplitLaunch {
+    uint32_t units = 0; uint64_t bytes = 0, tried = 0;       // tried: bits to be decoded, once per try
+    float work = 0; bool subsampled = false, several = false;       // us by tries with the chip full; some MCUs of several blocks per component, of several blocks
+    // `count` units of a scan, of so many bytes each on average; false: they are not long
+    bool add(const ImgDesc& im, const ScanDesc& sd, uint32_t each, uint32_t count) {
+        if ((uint64_t)each * 8 < kSplitLeastBits) return false;
+        const uint32_t tries = split_tries_of(im, sd);
+        units += count; bytes += (uint64_t)each * count; tried += (uint64_t)tries * each * 8 * count;
+        work += (22.f + 4.5f * (float)tries) * 1e-6f * (float)each * (float)count;
+        subsampled = subsampled || tries > (uint32_t)im.nc; several = several || tries > 1;
+        return true;
+    }
+    // room: the tries have memory to work in
+    SplitBy by(int open_records, bool room) const {
+        if (units == 0) return kSplitNever;
+        const float beside = (float)std::min(4, std::max(1, open_records)), n = (float)units * beside;
+        const float kb = (float)bytes / (float)units / 1000.f, turns = std::ceil(n / 256.f);
+        const float tries = 150.f + turns * 400.f + beside * work;
+        const float long_kb = std::max(0.f, kb - 300.f);     // (a lane's piece is beyond a wrong block then)
+        const float steps = subsampled ? 550.f + turns * (850.f + 6.f * kb - 3.f * long_kb) : 150.f + turns * (260.f + 4.5f * kb);
+        const float sequential = 102.f * kb * std::max(1.f, 0.72f + n / 3072.f);
+        return room && several && tries < steps && tries < sequential ? kSplitByTries : (steps < sequential ? kSplitBySteps : kSplitNever);
+    }
+    bool by_tries_perhaps() const {
+        for (int open_records = 1; open_records <= 4; open_records++) if (by(open_records, true) == kSplitByTries) return true;
+        return false;
+    }
+    // Pieces are as long as that a launch of few scans fills the chip once, within what the constants say.
+    uint32_t piece_bits() const { return (uint32_t)std::min<uint64_t>(kSplitPieceMost, tried / (256 * kSplitLanes)); }
+};
+// Room for a unit of `bytes` of a scan, in pieces of `least` bits and more.  (More nodes are decoded on than half of those a unit begins with
+// hardly ever.)
+SplitRoom split_room_of(const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t least) {
+    SplitRoom room{};
+    room.tries = split_tries_of(im, sd);
+    const uint64_t blocks = std::max<uint64_t>((uint64_t)room.tries * sd.mcus, 1);
+    room.run_in = (uint32_t)std::min<uint64_t>(kSplitRunInMost, std::max<uint64_t>(kSplitRunInLeast, kSplitRunInBlocks * 8 * (uint64_t)sd.data_len / blocks));
+    room.least = std::max(room.run_in, least);
+    room.pieces = std::min<uint32_t>(std::min(kSplitPieces, kSplitFirstNodes / room.tries), (uint32_t)((uint64_t)bytes * 8 / room.least + 1));
+    const uint32_t first = room.pieces * room.tries;
+    room.nodes = std::min(kSplitNodes, first + first / 2 + 1024);
+    return room;
+}
+// Nodes and pieces of several units.
+struct SplitSpace {
+    uint64_t nodes = 0; uint32_t pieces = 0;
+    void add(const SplitRoom& room) { nodes += room.nodes; pieces += room.pieces + 1; }
+    bool holds(const SplitSpace& o) const { return o.nodes <= nodes && o.pieces <= pieces; }
+};
+
 struct LevelList {
     Unit* d_units = nullptr; uint32_t n = 0; int kind = 0;
     uint32_t level = 0;                                                          // (0-based)
     uint32_t plane_tile = 0, n_plane_tiles = 0, cov_tile = 0, n_cov_tiles = 0;    // AC refinement: the level's share of the plan's lists for the per-block kernels
     LaneJob* d_jobs = nullptr; uint32_t n_jobs = 0;                              // the same units cut into jobs of a lane-per-unit kernel
     uint32_t* d_done = nullptr;                                                  // sequential scans, some of them long: which units have been dealt with by many lanes
-    uint32_t n_long = 0; uint64_t long_bytes = 0;                                // ... how many those are, their bytes
-    // ... and what k_split_tries and the kernels behind it work in: workgroups a unit
-    // needs at most; what they are judged by (split_pays): us of their work, MCUs of several blocks per component, of several blocks
-    SplitRoom* d_rooms = nullptr; SplitNode* d_nodes = nullptr; uint32_t* d_next = nullptr; SplitPiece* d_pieces = nullptr;
-    uint32_t split_tries = 0, split_stores = 0; float split_work = 0; bool subsampled = false, several_tries = false, by_tries = false;
+    // ... how many those are at most and what they are judged by; by tries, if there is room for them, the rooms of those units, and the most workgroups a unit needs
+    SplitLaunch seq;
+    SplitRoom* d_rooms = nullptr; uint32_t split_tries = 0, split_stores = 0; bool by_tries = false;
     DcLaunch dc;                                                                 // DC first scans: what decides between lanes and wavefronts
     uint32_t* d_dc_starts = nullptr; uint32_t n_dc_waves = 0;                    // ... wavefronts of lanes, and where they begin if their MCUs are of several shapes
     bool chained = false;                                                        // the plan's chains hold these units too
@@ -229,6 +302,11 @@ struct pcr_record {
     int last_lane_launches = 0, last_wave_launches = 0;   // AC entropy launches of the last decode call, by decoder shape
     int last_splits = 0, last_wide_splits = 0;            // ... launches of k_first_split, and those with a thousand lanes a unit
     int last_trios = 0;                                   // ... launches of k_decode_trios
+    // what the tries of long sequential scans work in, for one launch at a time: the most that a plan from scratch needs of them
+    SplitNode* d_nodes = nullptr; uint32_t* d_next = nullptr; SplitPiece* d_pieces = nullptr; SplitSpace split_space;
+    int seq_mode = 0;                                     // pcr_set_sequential_decoders
+    struct SeqDone { uint32_t* d_done; uint32_t units; };
+    int last_seq = 0; std::vector<SeqDone> last_done;     // how the last decode call decoded its sequential scans (SplitBy + 1), its launches by many lanes
     bool last_past = false;                               // ... whether its pixels were stored past the caches (pixels_past)
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
     std::vector<uint32_t> unit_bits;        // records opened from host bytes: entropy-coded bits of every unit, by slot (else empty)
@@ -350,60 +428,64 @@ int build_chains(pcr_record* r, int k0, int k, Plan* plan) {
     return PCR_OK;
 }
 
-enum SplitBy { kSplitNever = 0, kSplitBySteps = 1, kSplitByTries = 2 };
-SplitBy split_pays(const LevelList& l, int open_records);
-
-// Blocks of an MCU of a sequential scan: the tries of a piece (k_split_tries).
-uint32_t split_tries_of(const ImgDesc& im, const ScanDesc& sd) {
-    uint32_t tries = 0;
-    for (int j = 0; j < sd.ns; j++) tries += sd.ns == 1 ? 1u : (uint32_t)im.hs[sd.comp[j]] * im.vs[sd.comp[j]];
-    return std::max(1u, tries);
-}
-// Room for a unit of `bytes` of a scan, in pieces of `least` bits and more.  (More nodes are decoded on than half of those a unit begins with
-// hardly ever.)
-SplitRoom split_room_of(const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t least) {
-    SplitRoom room{};
-    room.tries = split_tries_of(im, sd);
-    const uint64_t blocks = std::max<uint64_t>((uint64_t)room.tries * sd.mcus, 1);
-    room.run_in = (uint32_t)std::min<uint64_t>(kSplitRunInMost, std::max<uint64_t>(kSplitRunInLeast, kSplitRunInBlocks * 8 * (uint64_t)sd.data_len / blocks));
-    room.least = std::max(room.run_in, least);
-    room.pieces = std::min<uint32_t>(std::min(kSplitPieces, kSplitFirstNodes / room.tries), (uint32_t)((uint64_t)bytes * 8 / room.least + 1));
-    const uint32_t first = room.pieces * room.tries;
-    room.nodes = std::min(kSplitNodes, first + first / 2 + 1024);
-    return room;
-}
-// What the kernels of a launch's long sequential scans work in (pcr_sequential.h).  Pieces are as long as that a launch of few scans fills the
-// chip once, within what the constants say; no memory for it: no long scans.
-template <class Run> void lay_out_split(const pcr_record* r, const Run* runs, size_t count, LevelList* ll, Uploads* up) {
-    pcr_record* const rec = const_cast<pcr_record*>(r);
-    uint64_t tried = 0;                                      // bits to be decoded once per try
-    uint32_t units = 0;
-    size_t n_runs = 0;
-    for (; n_runs < count && units < ll->n_long; n_runs++) {
-        const Run& q = runs[n_runs];
-        tried += (uint64_t)split_tries_of(r->img[q.img], r->scan[(size_t)q.img * r->hdr.G + q.scan]) * q.bytes * 8 * q.count;
-        units += q.count;
-    }
-    const uint32_t fills = (uint32_t)std::min<uint64_t>(kSplitPieceMost, tried / (256 * kSplitLanes));
+// The rooms of a launch's long sequential scans (runs: the longest first), and whether there are any.
+template <class Run> int lay_out_split(pcr_record* r, const std::vector<Run>& runs, LevelList* ll, Uploads* up) {
+    const uint32_t G = r->hdr.G, bits = ll->seq.piece_bits();
     std::vector<SplitRoom> rooms;
-    rooms.reserve(ll->n_long);
-    uint64_t nodes = 0;
-    uint32_t pieces = 0;
-    for (size_t e = 0; e < n_runs; e++) {
+    rooms.reserve(ll->seq.units);
+    SplitSpace space;
+    uint32_t tries = 0, stores = 0;
+    for (size_t e = 0; e < runs.size() && rooms.size() < ll->seq.units; e++) {
         const Run& q = runs[e];
-        SplitRoom room = split_room_of(r->img[q.img], r->scan[(size_t)q.img * r->hdr.G + q.scan], q.bytes, fills);
+        SplitRoom room = split_room_of(r->img[q.img], r->scan[(size_t)q.img * G + q.scan], q.bytes, bits);
         const uint32_t per = kSplitLanes / room.tries;
-        ll->split_tries = std::max(ll->split_tries, std::max(1u, (room.pieces - 1 + per - 2) / (per - 1)));
-        ll->split_stores = std::max(ll->split_stores, (room.pieces + kSplitStoreLanes - 1) / kSplitStoreLanes);
+        tries = std::max(tries, std::max(1u, (room.pieces - 1 + per - 2) / (per - 1)));
+        stores = std::max(stores, (room.pieces + kSplitStoreLanes - 1) / kSplitStoreLanes);
         for (uint32_t j = 0; j < q.count; j++) {
-            room.node0 = nodes; room.piece0 = pieces;
+            room.node0 = space.nodes; room.piece0 = space.pieces;
             rooms.push_back(room);
-            nodes += room.nodes; pieces += room.pieces + 1;
+            space.add(room);
         }
     }
-    if (arena_alloc(&rec->big, &ll->d_nodes, nodes) != PCR_OK || arena_alloc(&rec->big, &ll->d_next, nodes) != PCR_OK || arena_alloc(&rec->big, &ll->d_pieces, pieces) != PCR_OK) return;
+    if (!r->split_space.holds(space)) {
+        if (r->seq_mode != 3) return PCR_OK;                 // (an upgrade's scans may be cut finer than those from scratch: they go without)
+        SplitNode* nodes = nullptr; uint32_t* next = nullptr; SplitPiece* pieces = nullptr;
+        int rc = arena_alloc(&r->big, &nodes, space.nodes);
+        if (!rc) rc = arena_alloc(&r->big, &next, space.nodes);
+        if (!rc) rc = arena_alloc(&r->big, &pieces, space.pieces);
+        if (rc) return rc;
+        r->d_nodes = nodes; r->d_next = next; r->d_pieces = pieces; r->split_space = space;
+    }
     up->add(&ll->d_rooms, rooms);
-    ll->by_tries = true;
+    ll->split_tries = tries; ll->split_stores = stores; ll->by_tries = true;
+    return PCR_OK;
+}
+// What those of any plan from scratch need at most.
+SplitSpace split_space_of(const pcr_record* r) {
+    const uint32_t n = r->hdr.n, G = r->hdr.G;
+    SplitSpace most;
+    for (uint32_t k = 1; k <= G; k++)
+        for (uint32_t level = 1; level <= r->max_level; level++) {
+            auto each = [&](auto&& f) {
+                for (uint32_t i = 0; i < n; i++)
+                    for (uint32_t g = 0; g < std::min<uint32_t>(k, r->img[i].nscans); g++) {
+                        const size_t ig = (size_t)i * G + g;
+                        const uint32_t count = r->slot_cnt[ig];
+                        if (r->level[ig] == level && count && is_sequential_scan(r->scan[ig])) f(r->img[i], r->scan[ig], r->scan[ig].data_len / count, count);
+                    }
+            };
+            SplitLaunch launch;
+            each([&](const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t count) { launch.add(im, sd, bytes, count); });
+            if (!launch.by_tries_perhaps()) continue;
+            SplitSpace space;
+            each([&](const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t count) {
+                if ((uint64_t)bytes * 8 < kSplitLeastBits) return;
+                const SplitRoom room = split_room_of(im, sd, bytes, launch.piece_bits());
+                for (uint32_t j = 0; j < count; j++) space.add(room);
+            });
+            most.nodes = std::max(most.nodes, space.nodes); most.pieces = std::max(most.pieces, space.pieces);
+        }
+    return most;
 }
 
 // Launch geometry for decoding scan groups k0+1 .. k (k0 = 0: from scratch) and turning groups 1 .. k into pixels.
@@ -533,15 +615,10 @@ int build_plan(pcr_record* r, int k0, int k, Plan** out) {
             up.add(&ll.d_jobs, jobs);
         }
         if (ll.kind == kSequential) {
-            for (const Run& q : rn) {
-                if ((uint64_t)q.bytes * 8 < kSplitLeastBits) break;          // (the longest on average come first)
-                const uint32_t tries = split_tries_of(r->img[q.img], r->scan[(size_t)q.img * G + q.scan]);
-                ll.n_long += q.count; ll.long_bytes += (uint64_t)q.bytes * q.count;
-                ll.split_work += (22.f + 4.5f * (float)tries) * (float)q.bytes * (float)q.count;
-                ll.subsampled = ll.subsampled || tries > (uint32_t)r->img[q.img].nc; ll.several_tries = ll.several_tries || tries > 1;
-            }
-            if (ll.n_long) { const int rc = arena_alloc(&r->big, &ll.d_done, ll.n); if (rc) return rc; }
-            if (split_pays(ll, 1) == kSplitByTries) lay_out_split(r, rn.data(), rn.size(), &ll, &up);
+            for (const Run& q : rn) if (!ll.seq.add(r->img[q.img], r->scan[(size_t)q.img * G + q.scan], q.bytes, q.count)) break;      // (the longest on average come first)
+            int rc = ll.seq.units ? arena_alloc(&r->big, &ll.d_done, ll.n) : PCR_OK;
+            if (!rc && ll.seq.units && (ll.seq.by_tries_perhaps() || r->seq_mode == 3)) rc = lay_out_split(r, rn, &ll, &up);
+            if (rc) return rc;
         }
     }
     refine_tiles(r, refine_levels, &plan, &up);
@@ -630,33 +707,6 @@ bool dc_lanes_pay(const pcr_record* r, const LevelList& l, bool beside) {
     if (r->lane_mode < 0) return false;
     if (r->lane_mode > 0) return l.n >= (uint32_t)kEntropyLanes;
     return l.dc.by_lanes(g_open_records.load(std::memory_order_relaxed) > 1, beside);
-}
-
-// Many lanes per long sequential scan, or one wavefront?  k_sequential takes as long as its longest scan until some thousand of them fill the
-// scalar units.  k_sequential_split has room for one scan per compute unit (150 KB of LDS), 256 at a time, and a step takes as long as its
-// slowest lane.  k_split_tries and what follows use the whole chip for few scans, but decode up to thirteen times what one decoder would.
-// ms for n files, by tries / k_sequential_split / k_sequential (the whole call; -: not measured):
-//                        n = 1              32             128            512            2048
-//   4:2:0, 166 KB    0.9/ 1.9/17     1.1/ 2.4/17    1.9/ 2.3/17    5.0/ 4.6/ -      -  /16.1/ -
-//   4:2:0, 50 KB     0.7/ 1.6/5.1    0.9/ 2.1/5.1   0.9/ 2.0/5.1   2.0/ 3.7/ -     8.4/ -  /4.3
-//   4:2:0, 19 KB     0.6/ 1.4/1.9    0.8/ 1.6/1.9   0.8/ 1.5/1.9   1.2/ 2.3/1.4    6.4/ -  /1.7
-//   4:4:4, 203 KB    0.8/ 1.3/21     1.0/ 1.4/21    1.9/ 1.4/ -    4.8/ 3.1/ -      -  /11.7/ -
-//   q 97, 99 KB      1.5/ 6.2/5.3    1.6/ 6.4/5.4   1.6/ 6.4/5.5   4.0/ 7.3/ -      -  /12.6/ -
-//   gray, 163 KB     0.8/ 0.8/17     0.9/ 1.2/17    1.1/ 1.1/17    2.6/ 2.2/ -      -  / 8.2/ -
-//   2.5 MP, 1.8 MB   3.6/ 6.5/ -     4.9/ 8.0/ -   11.0/ 8.5/ -   45.8/21.4/ -      -
-// (steps at quality 97: given up, and decoded by k_sequential behind it.)  The lines below follow these figures (in us; kb: the mean of the long
-// scans); where every MCU is one block there is one try, and nothing to be had of them.  A record decoded beside others shares
-// the compute units with them; the records the process has open (four at most count) are taken as the sign of it, as by
-// lanes_pay.  (Without this choice 4096 baseline photographs in four records took 29.1 ms instead of 23.2.)
-SplitBy split_pays(const LevelList& l, int open_records) {
-    if (l.n_long == 0) return kSplitNever;
-    const float beside = (float)std::min(4, std::max(1, open_records)), n = (float)l.n_long * beside;
-    const float kb = (float)l.long_bytes / (float)l.n_long / 1000.f, turns = std::ceil(n / 256.f);
-    const float tries = 150.f + turns * 400.f + beside * l.split_work * 1e-6f;
-    const float long_kb = std::max(0.f, kb - 300.f);         // (a lane's piece is beyond a wrong block then)
-    const float steps = l.subsampled ? 550.f + turns * (850.f + 6.f * kb - 3.f * long_kb) : 150.f + turns * (260.f + 4.5f * kb);
-    const float sequential = 102.f * kb * std::max(1.f, 0.72f + n / 3072.f);
-    return l.several_tries && tries < steps && tries < sequential ? kSplitByTries : (steps < sequential ? kSplitBySteps : kSplitNever);
 }
 
 // Whether the pixel kernel asks the caches to make no room for its pixels (put_past).
@@ -752,10 +802,10 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     const bool several = open > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
     r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = r->last_trios = 0;
-    r->last_past = false;
+    r->last_past = false; r->last_seq = 0; r->last_done.clear();
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
-        if (l.kind == kSequential) by_lanes[li] = (char)split_pays(l, open);
+        if (l.kind == kSequential) by_lanes[li] = (char)(r->seq_mode == 0 ? l.seq.by(open, l.by_tries) : (l.seq.units == 0 || r->seq_mode == 1 ? kSplitNever : (r->seq_mode == 2 ? kSplitBySteps : (l.by_tries ? kSplitByTries : kSplitNever))));
         else if (l.kind != kDcFirst) {
             by_lanes[li] = lanes_pay(r, l, several) ? 1 : 0;
             if (by_lanes[li]) r->last_lane_launches++; else r->last_wave_launches++;
@@ -879,13 +929,15 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
             mark(r, PCR_STAGE_DC_FIRST, s);
         }
         else if (l.kind == kSequential) {
-            const bool by_tries = by_lanes[li] == kSplitByTries && l.by_tries;
-            if (by_tries) {
-                hipLaunchKernelGGL(k_split_tries, dim3(l.n_long, l.split_tries), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, l.d_nodes, l.d_next, c32);
-                hipLaunchKernelGGL(k_split_settle, dim3(l.n_long), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, l.d_nodes, l.d_next, l.d_pieces, l.d_done, c32);
-                hipLaunchKernelGGL(k_split_store, dim3(l.n_long, l.split_stores), dim3(kSplitStoreLanes), 0, s, r->d, l.d_units, l.d_rooms, l.d_pieces, l.d_done, c32);
-            } else if (by_lanes[li]) hipLaunchKernelGGL(k_sequential_split, dim3(l.n), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
-            hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, (const uint32_t*)l.d_done, by_tries ? l.n_long : (by_lanes[li] ? l.n : 0u), c32);
+            const uint32_t lanes = by_lanes[li] == kSplitByTries ? l.seq.units : (by_lanes[li] ? l.n : 0u);
+            if (by_lanes[li] == kSplitByTries) {
+                hipLaunchKernelGGL(k_split_tries, dim3(lanes, l.split_tries), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, r->d_nodes, r->d_next, c32);
+                hipLaunchKernelGGL(k_split_settle, dim3(lanes), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, r->d_nodes, r->d_next, r->d_pieces, l.d_done, c32);
+                hipLaunchKernelGGL(k_split_store, dim3(lanes, l.split_stores), dim3(kSplitStoreLanes), 0, s, r->d, l.d_units, l.d_rooms, r->d_pieces, l.d_done, c32);
+            } else if (by_lanes[li]) hipLaunchKernelGGL(k_sequential_split, dim3(lanes), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
+            if (lanes) r->last_done.push_back(pcr_record::SeqDone{l.d_done, l.seq.units});
+            r->last_seq = std::max(r->last_seq, by_lanes[li] + 1);
+            hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, (const uint32_t*)l.d_done, lanes, c32);
             mark(r, PCR_STAGE_SEQUENTIAL, s);
         }
         else if (l.kind == kAcFirst) {
@@ -1139,7 +1191,7 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
     uint32_t flat_tiles = 0, flat_rows = 0;                       // (listed when a plan first needs them)
     bool rows_fit = true;
     r->flat_row_cells = 0;
-    uint64_t nm = 0; uint64_t ns = 0, split_nodes = 0;
+    uint64_t nm = 0; uint64_t ns = 0; bool long_scans = false;
     std::vector<uint32_t> tab_idx((size_t)n * G, 0); uint32_t ntabs = 0;
     std::vector<uint32_t> dctab_idx((size_t)n * G, 0); uint32_t ndctabs = 0;
     r->several_units = r->entry_units = false;
@@ -1183,7 +1235,7 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
             else ent_off[ig] = 0;
             if (ent_off[ig]) r->entry_units = true;
             if (d.progressive && sd.Ss == 0 && sd.Ah == 0) { dctab_idx[ig] = ndctabs; ndctabs += kMaxComp; }
-            if (is_sequential_scan(sd) && cnt == 1 && n <= 256 && sd.data_len * 8ull >= kSplitLeastBits && split_tries_of(d, sd) > 1) split_nodes += split_room_of(d, sd, sd.data_len, 0).nodes;
+            long_scans = long_scans || (sd.data_len * 8ull >= kSplitLeastBits && is_sequential_scan(sd));
             if (cnt > 1 && (sd.Ss > 0 || d.progressive)) r->several_units = true;
             r->slot_base[ig] = (uint32_t)ns; r->slot_cnt[ig] = cnt;
             ns += cnt + 1;
@@ -1210,8 +1262,18 @@ static int finish_open(pcr_record* r, BindFill fill, hipStream_t s) {
                   arena_round(((size_t)ntabs + 1) * sizeof(AcTab)) + arena_round(((size_t)ndctabs + 1) * sizeof(DcTab)) + arena_round(((size_t)n * G + 1) * sizeof(uint32_t)) + arena_round(((size_t)n * G + 1) * sizeof(uint32_t));
     need += 8 * ((ns + (size_t)n * G) * sizeof(Unit) + (size_t)n * kMaxComp * 64) + (1u << 20);
     need += 8 * (r->coef_off[n] / 64 / 256 + (size_t)n * G) * 2 * sizeof(RefineTile);     // (the tile lists of the refinement helpers: one entry per 256 blocks)
-    need += split_nodes * (sizeof(SplitNode) + sizeof(uint32_t)) + split_nodes / 4 * sizeof(SplitPiece);      // (the pieces of long sequential scans)
-    int rc = arena_reset(&r->big, need);
+    r->last_done.clear();
+    r->d_nodes = nullptr; r->d_next = nullptr; r->d_pieces = nullptr;
+    r->split_space = long_scans ? split_space_of(r) : SplitSpace();
+    const SplitSpace space = r->split_space;
+    const size_t tries_need = space.nodes ? arena_round(space.nodes * sizeof(SplitNode)) + arena_round(space.nodes * sizeof(uint32_t)) + arena_round(space.pieces * sizeof(SplitPiece)) : 0;
+    int rc = arena_reset(&r->big, need + tries_need);
+    if (rc && tries_need) { r->split_space = SplitSpace(); rc = arena_reset(&r->big, need); }      // (long sequential scans are decoded without it as well)
+    if (!rc && r->split_space.nodes) {
+        rc = arena_alloc(&r->big, &r->d_nodes, space.nodes);
+        if (!rc) rc = arena_alloc(&r->big, &r->d_next, space.nodes);
+        if (!rc) rc = arena_alloc(&r->big, &r->d_pieces, space.pieces);
+    }
     if (!rc) rc = arena_alloc(&r->big, &d.clean, padded);
     if (!rc) rc = arena_alloc(&r->big, &d.coef, r->coef_off[n]);
     if (!rc) rc = arena_alloc(&r->big, &d.dc, r->coef_off[n] / 64 + 8);              // (+8: cleared in 16-byte units)
@@ -1548,6 +1610,29 @@ int pcr_reassemble(pcr_record* r, int i, int k, uint8_t* dst, size_t cap, size_t
 int pcr_set_lane_decoders(pcr_record* r, int mode) {
     if (!r || mode < -1 || mode > 1) return PCR_E_ARG;
     r->lane_mode = mode;
+    return PCR_OK;
+}
+
+int pcr_set_sequential_decoders(pcr_record* r, int mode) {
+    if (!r || mode < 0 || mode > 3) return PCR_E_ARG;
+    if (mode != r->seq_mode) free_plans(r);                  // (their rooms are laid out for the mode)
+    r->seq_mode = mode;
+    return PCR_OK;
+}
+int pcr_last_sequential_decoders(pcr_record* r, int* by, uint32_t* counts, uint32_t* rounds) {
+    if (!r || !by || !counts || !rounds) return PCR_E_ARG;
+    *by = r->last_seq; counts[0] = counts[1] = counts[2] = rounds[0] = rounds[1] = 0;
+    HIP_TRY(hipSetDevice(r->device));
+    std::vector<uint32_t> done;
+    for (const pcr_record::SeqDone& l : r->last_done) {
+        done.resize(l.units);
+        HIP_TRY(hipMemcpy(done.data(), l.d_done, l.units * sizeof(uint32_t), hipMemcpyDeviceToHost));
+        for (uint32_t v : done) {
+            const uint32_t how = v == 0 ? 2u : (v > kSplitInSteps ? 1u : 0u);
+            counts[how]++;
+            if (how < 2) rounds[how] = std::max(rounds[how], v - 1 - how * kSplitInSteps);
+        }
+    }
     return PCR_OK;
 }
 

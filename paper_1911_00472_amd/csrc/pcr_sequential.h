@@ -168,7 +168,7 @@ PCR_D __attribute__((always_inline)) bool split_walk(const SplitScan& S, const S
 
 // Whether round `round` of steps, with `count` pieces left, is not worth starting.  half_left: the pieces that were left at half the
 // round the fall is looked at next.
-constexpr uint32_t kSplitStepRounds = 64, kSplitLeft = 64;
+constexpr uint32_t kSplitStepRounds = 64, kSplitLeft = 64, kSplitInSteps = 1u << 16;
 PCR_D bool split_stops(uint32_t round, uint32_t count, uint32_t* half_left) {
     if (round < 4 || (round & (round - 1)) != 0) return false;
     if (round == kSplitStepRounds) return true;
@@ -349,7 +349,8 @@ PCR_D bool split_follow(const uint16_t* next, uint32_t planned, uint32_t H, uint
 }
 
 // One workgroup a unit: what ends in a state that the next piece was not started in is decoded on, a piece a round, until it falls in
-// with a node; then the path and the sums along it.  done[u] = 1: unit u has its pieces, and needs nothing but k_split_store.
+// with a node; then the path and the sums along it.  done[u], where it is not 0: unit u has its pieces, and needs nothing but k_split_store; one more
+// than the rounds it took.
 __global__ void __launch_bounds__(kSplitLanes) k_split_settle(DevRecord R, const Unit* __restrict__ units, const SplitRoom* __restrict__ rooms, SplitNode* __restrict__ all_nodes,
         const uint32_t* __restrict__ all_next, SplitPiece* __restrict__ all_pieces, uint32_t* __restrict__ done, const uint32_t* __restrict__ clean32) {
     __shared__ SplitTables T;
@@ -386,8 +387,8 @@ __global__ void __launch_bounds__(kSplitLanes) k_split_settle(DevRecord R, const
     }
     __syncthreads();
     bool tables = false;
-    uint32_t from = planned;
-    for (uint32_t round = 0;; round++) {
+    uint32_t from = planned, round = 0;
+    for (;; round++) {
         const uint32_t upto = s_count;
         if (split_follow(s_next, planned, H, C.last, &s_path, path)) break;   // (what is left does not lie on the path)
         if (upto > room.nodes || upto == from || round == kSplitRounds) { if (tid == 0) done[blockIdx.x] = 0; return; }       // (the same for everyone)
@@ -427,7 +428,7 @@ __global__ void __launch_bounds__(kSplitLanes) k_split_settle(DevRecord R, const
     SplitPiece* const pieces = all_pieces + room.piece0;
     if (p0 <= C.last) pieces[p0] = SplitPiece{start0, at};
     if (p0 + 1 <= C.last) pieces[p0 + 1] = SplitPiece{start1, SplitSums{at.blocks + one.blocks, at.dc0 + one.dc0, at.dc1 + one.dc1, at.dc2 + one.dc2}};
-    if (tid == 0) { pieces[C.last + 1].at.blocks = all; done[blockIdx.x] = 1; }
+    if (tid == 0) { pieces[C.last + 1].at.blocks = all; done[blockIdx.x] = 1 + round; }
 }
 
 // Every piece once more, storing: workgroup (u, c) pieces c * kSplitStoreLanes and on of unit u.
@@ -459,7 +460,7 @@ __global__ void __launch_bounds__(kSplitStoreLanes) k_split_store(DevRecord R, c
     if (!good) R.status[un.img] = kEFormat;
 }
 
-// By steps; done[u] = 1: unit u needs nothing more.
+// By steps; done[u], where it is not 0: unit u needs nothing more; one more than the rounds it took, and kSplitInSteps.
 __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, const Unit* __restrict__ units, uint32_t* __restrict__ done, const uint32_t* __restrict__ clean32) {
     __shared__ SplitTables T;
     __shared__ LaneRing rings[kSplitWaves];
@@ -483,8 +484,8 @@ __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, c
     __syncthreads();
     // (The pieces of a round are packed into as few wavefronts as hold them: a wavefront with one lane at work takes as long
     // as a full one, and gets in the way of others.)
-    uint32_t half_left = 1;                                   // pieces left at half the round the fall is looked at next
-    for (uint32_t round = 0;; round++) {
+    uint32_t half_left = 1, round = 0;                        // half_left: pieces left at half the round the fall is looked at next
+    for (;; round++) {
         const uint32_t count = s_count[round & 1];
         if (count == 0) break;
         if (split_stops(round, count, &half_left)) { if (tid == 0) done[blockIdx.x] = 0; return; }       // (the same for everyone)
@@ -534,7 +535,7 @@ __global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, c
     __syncthreads();
     if (tid == 0) {
         if (s_bad) R.status[un.img] = kEFormat;
-        done[blockIdx.x] = 1;
+        done[blockIdx.x] = kSplitInSteps + 1 + round;
     }
 }
 
