@@ -418,8 +418,8 @@ int pcr_transcode_batch(pcr_record* rec, const void* const* files, const size_t*
  * mode. */
 int pcr_set_lane_decoders(pcr_record* rec, int mode);
 /* Sequential (baseline) scans by one decoder or many.  mode 0 (default): long scans by as many as are faster for the launch; 1: one wavefront for every
- * scan or restart interval; 2: long ones by many lanes in steps; 3: long ones by many lanes by tries.  Streams that do not fall into step are
- * left to one wavefront in every mode.  The results are the same bit for bit.  Takes effect from the next decode call, which makes its plan (mode 3: and the
+ * scan or restart interval; 2: long ones by many lanes in steps; 3: long ones by many lanes by tries, and in steps what those leave.  Streams that
+ * do not fall into step are left to one wavefront in every mode.  The results are the same bit for bit.  Takes effect from the next decode call, which makes its plan (mode 3: and the
  * memory the tries work in) anew.  PCR_E_ARG: null handle or another mode. */
 int pcr_set_sequential_decoders(pcr_record* rec, int mode);
 /* How the last decode call decoded its sequential scans.  by: 0 there were none, else the mode it came to (the highest of its launches).  Of the units

@@ -41,6 +41,24 @@ uint32_t split_tries_of(const ImgDesc& im, const ScanDesc& sd) {
     for (int j = 0; j < sd.ns; j++) tries += sd.ns == 1 ? 1u : (uint32_t)im.hs[sd.comp[j]] * im.vs[sd.comp[j]];
     return std::max(1u, tries);
 }
+// Whether the tries would not fall into step: eight blocks are not enough where a block is of many bits, and what is decoded on outgrows its room (the more
+// the longer the scan).  Such units go in steps, and so does, behind the tries, whatever else they leave: 85 ms for four of 1.5 MB at quality 99, 166 for one of 3.2 MB,
+// when one wavefront took what the tries left, and 10 and 15 in steps.  ms by tries, and in steps behind them where they left any / in steps / one wavefront:
+//                      bits a block:  350 ..                 380 ..                 400 ..                 420 ..                 440 ..
+//   4:2:0, 24 to 37 KB       4 of  0.9 / 3.3 / 1.5        1.1 / 1.9 / 1.6        1.4 / 1.9 / 1.7        1.5 / 2.0 / 1.7        2.0 / 2.0 / 1.7
+//          52 to 82          4     1.4 / 3.8 / 3.4        1.5 / 4.0 / 3.5        1.6 / 4.0 / 3.6        1.8 / 4.2 / 3.7        2.4 / 4.2 / 3.8
+//          93 to 146         4     1.2 / 8.7 / 5.9        1.6 / 6.9 / 6.2        2.3 / 7.0 / 6.3        9.2 / 7.2 / 6.5        8.4 / 7.3 / 6.6
+//          230 to 366        4     1.9 / 22 / 15          2.7 / 23 / 16          9.5 / 6.6 / 17         25 / 23 / 16           26 / 25 / 17
+//          570 to 910        4     2.9 / 7.2 / 37         3.2 / 7.0 / 38         14 / 10 / 39           12 / 9.9 / 40          17 / 14 / 41
+//          2.2 to 3.6 MB     1     9.1 / 10 / 145         13 / 14 / 153          25 / 15 / 153          27 / 20 / 159          28 / 21 / 162
+//   4:4:4, 41 to 73 KB       4     1.5 / 3.7 / 3.2        1.8 / 3.7 / 3.3        1.6 / 3.8 / 3.3        1.6 / 3.8 / 3.4        6.0 / 3.9 / 3.6
+//          163 to 293        4     2.6 / 5.4 / 13         2.9 / 5.3 / 13         20 / 19 / 13           21 / 19 / 13           16 / 15 / 14
+//          1.0 to 1.8 MB     4     3.6 / 6.1 / 76         11 / 8.2 / 80          15 / 9.4 / 82          13 / 10 / 83           15 / 14 / 87
+bool split_dense(const ImgDesc& im, const ScanDesc& sd, uint32_t each) {
+    const uint64_t blocks = std::max<uint64_t>((uint64_t)split_tries_of(im, sd) * sd.mcus, 1);
+    const uint32_t line = each < 100000u ? 445u : (each < 150000u ? 426u : (each < 350000u ? 405u : (each < 1000000u ? 385u : 372u)));
+    return 8ull * sd.data_len > line * blocks;
+}
 // The long sequential scans of a launch: many lanes each, or one wavefront?  k_sequential takes as long as its longest scan until some thousand of them fill the
 // scalar units.  k_sequential_split has room for one scan per compute unit (150 KB of LDS), 256 at a time, and a step takes as long as its
 // slowest lane.  k_split_tries and what follows use the whole chip for few scans, but decode up to thirteen times what one decoder would.
@@ -53,34 +71,39 @@ uint32_t split_tries_of(const ImgDesc& im, const ScanDesc& sd) {
 //   q 97, 99 KB      1.5/ 6.2/5.3    1.6/ 6.4/5.4   1.6/ 6.4/5.5   4.0/ 7.3/ -      -  /12.6/ -
 //   gray, 163 KB     0.8/ 0.8/17     0.9/ 1.2/17    1.1/ 1.1/17    2.6/ 2.2/ -      -  / 8.2/ -
 //   2.5 MP, 1.8 MB   3.6/ 6.5/ -     4.9/ 8.0/ -   11.0/ 8.5/ -   45.8/21.4/ -      -
-// (steps at quality 97: given up, and decoded by k_sequential behind it.)  The lines below follow these figures (in us; kb: the mean of the long
-// scans); where every MCU is one block there is one try, and nothing to be had of them.  A record decoded beside others shares
+// (steps at quality 97: given up, and decoded by k_sequential behind it.)  What the lines below say follows these figures (in us; kb: the mean of
+// the long scans); where every MCU is one block there is one try, and nothing to be had of them.  A record decoded beside others shares
 // the compute units with them; the records the process has open (four at most count) are taken as the sign of it, as by
 // lanes_pay.  (Without this choice 4096 baseline photographs in four records took 29.1 ms instead of 23.2.)
 //
 // The tries work in memory of the record (SplitSpace), which it has where some number of open records would have them chosen.
 struct SplitLaunch {
-    uint32_t units = 0; uint64_t bytes = 0, tried = 0;       // tried: bits to be decoded, once per try
+    uint32_t units = 0, dense = 0; uint64_t bytes = 0, dense_bytes = 0, tried = 0;       // dense: of the units; tried: bits to be decoded, once per try
     float work = 0; bool subsampled = false, several = false;       // us by tries with the chip full; some MCUs of several blocks per component, of several blocks
     // `count` units of a scan, of so many bytes each on average; false: they are not long
     bool add(const ImgDesc& im, const ScanDesc& sd, uint32_t each, uint32_t count) {
         if ((uint64_t)each * 8 < kSplitLeastBits) return false;
         const uint32_t tries = split_tries_of(im, sd);
-        units += count; bytes += (uint64_t)each * count; tried += (uint64_t)tries * each * 8 * count;
-        work += (22.f + 4.5f * (float)tries) * 1e-6f * (float)each * (float)count;
+        units += count; bytes += (uint64_t)each * count;
         subsampled = subsampled || tries > (uint32_t)im.nc; several = several || tries > 1;
+        if (split_dense(im, sd, each)) { dense += count; dense_bytes += (uint64_t)each * count; return true; }
+        tried += (uint64_t)tries * each * 8 * count;
+        work += (22.f + 4.5f * (float)tries) * 1e-6f * (float)each * (float)count;
         return true;
+    }
+    // us in steps of so many units, with those of other records beside them
+    float steps(uint32_t count, uint64_t all, float beside) const {
+        const float kb = (float)all / (float)count / 1000.f, turns = std::ceil((float)count * beside / 256.f);
+        const float long_kb = std::max(0.f, kb - 300.f);     // (a lane's piece is beyond a wrong block then)
+        return subsampled ? 550.f + turns * (850.f + 6.f * kb - 3.f * long_kb) : 150.f + turns * (260.f + 4.5f * kb);
     }
     // room: the tries have memory to work in
     SplitBy by(int open_records, bool room) const {
         if (units == 0) return kSplitNever;
-        const float beside = (float)std::min(4, std::max(1, open_records)), n = (float)units * beside;
-        const float kb = (float)bytes / (float)units / 1000.f, turns = std::ceil(n / 256.f);
-        const float tries = 150.f + turns * 400.f + beside * work;
-        const float long_kb = std::max(0.f, kb - 300.f);     // (a lane's piece is beyond a wrong block then)
-        const float steps = subsampled ? 550.f + turns * (850.f + 6.f * kb - 3.f * long_kb) : 150.f + turns * (260.f + 4.5f * kb);
-        const float sequential = 102.f * kb * std::max(1.f, 0.72f + n / 3072.f);
-        return room && several && tries < steps && tries < sequential ? kSplitByTries : (steps < sequential ? kSplitBySteps : kSplitNever);
+        const float beside = (float)std::min(4, std::max(1, open_records)), n = (float)units * beside, kb = (float)bytes / (float)units / 1000.f;
+        const float tries = 150.f + std::ceil((float)(units - dense) * beside / 256.f) * 400.f + beside * work + (dense ? steps(dense, dense_bytes, beside) : 0.f);
+        const float in_steps = steps(units, bytes, beside), sequential = 102.f * kb * std::max(1.f, 0.72f + n / 3072.f);
+        return room && several && units > dense && tries < in_steps && tries < sequential ? kSplitByTries : (in_steps < sequential ? kSplitBySteps : kSplitNever);
     }
     bool by_tries_perhaps() const {
         for (int open_records = 1; open_records <= 4; open_records++) if (by(open_records, true) == kSplitByTries) return true;
@@ -91,9 +114,10 @@ struct SplitLaunch {
 };
 // Room for a unit of `bytes` of a scan, in pieces of `least` bits and more.  (More nodes are decoded on than half of those a unit begins with
 // hardly ever.)
-SplitRoom split_room_of(const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t least) {
+SplitRoom split_room_of(const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t least, bool dense) {
     SplitRoom room{};
     room.tries = split_tries_of(im, sd);
+    if (dense) { room.pieces = 1; room.tries = 0; return room; }
     const uint64_t blocks = std::max<uint64_t>((uint64_t)room.tries * sd.mcus, 1);
     room.run_in = (uint32_t)std::min<uint64_t>(kSplitRunInMost, std::max<uint64_t>(kSplitRunInLeast, kSplitRunInBlocks * 8 * (uint64_t)sd.data_len / blocks));
     room.least = std::max(room.run_in, least);
@@ -437,8 +461,10 @@ template <class Run> int lay_out_split(pcr_record* r, const std::vector<Run>& ru
     uint32_t tries = 0, stores = 0;
     for (size_t e = 0; e < runs.size() && rooms.size() < ll->seq.units; e++) {
         const Run& q = runs[e];
-        SplitRoom room = split_room_of(r->img[q.img], r->scan[(size_t)q.img * G + q.scan], q.bytes, bits);
-        const uint32_t per = kSplitLanes / room.tries;
+        const ImgDesc& im = r->img[q.img];
+        const ScanDesc& sd = r->scan[(size_t)q.img * G + q.scan];
+        SplitRoom room = split_room_of(im, sd, q.bytes, bits, r->seq_mode != 3 && split_dense(im, sd, q.bytes));
+        const uint32_t per = kSplitLanes / std::max(1u, room.tries);
         tries = std::max(tries, std::max(1u, (room.pieces - 1 + per - 2) / (per - 1)));
         stores = std::max(stores, (room.pieces + kSplitStoreLanes - 1) / kSplitStoreLanes);
         for (uint32_t j = 0; j < q.count; j++) {
@@ -480,7 +506,7 @@ SplitSpace split_space_of(const pcr_record* r) {
             SplitSpace space;
             each([&](const ImgDesc& im, const ScanDesc& sd, uint32_t bytes, uint32_t count) {
                 if ((uint64_t)bytes * 8 < kSplitLeastBits) return;
-                const SplitRoom room = split_room_of(im, sd, bytes, launch.piece_bits());
+                const SplitRoom room = split_room_of(im, sd, bytes, launch.piece_bits(), split_dense(im, sd, bytes));
                 for (uint32_t j = 0; j < count; j++) space.add(room);
             });
             most.nodes = std::max(most.nodes, space.nodes); most.pieces = std::max(most.pieces, space.pieces);
@@ -934,7 +960,8 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
                 hipLaunchKernelGGL(k_split_tries, dim3(lanes, l.split_tries), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, r->d_nodes, r->d_next, c32);
                 hipLaunchKernelGGL(k_split_settle, dim3(lanes), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_rooms, r->d_nodes, r->d_next, r->d_pieces, l.d_done, c32);
                 hipLaunchKernelGGL(k_split_store, dim3(lanes, l.split_stores), dim3(kSplitStoreLanes), 0, s, r->d, l.d_units, l.d_rooms, r->d_pieces, l.d_done, c32);
-            } else if (by_lanes[li]) hipLaunchKernelGGL(k_sequential_split, dim3(lanes), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, c32);
+            }
+            if (lanes) hipLaunchKernelGGL(k_sequential_split, dim3(lanes), dim3(kSplitLanes), 0, s, r->d, l.d_units, l.d_done, by_lanes[li] == kSplitByTries ? 1u : 0u, c32);
             if (lanes) r->last_done.push_back(pcr_record::SeqDone{l.d_done, l.seq.units});
             r->last_seq = std::max(r->last_seq, by_lanes[li] + 1);
             hipLaunchKernelGGL(k_sequential, dim3(l.n), block, 0, s, r->d, l.d_units, (const uint32_t*)l.d_done, lanes, c32);

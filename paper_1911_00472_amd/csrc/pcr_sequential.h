@@ -20,8 +20,9 @@
 // with several scans, by the latency of a symbol (some 75 instructions and two reads of LDS that wait for each other) with one.  64
 // photographs of 90 KB, us: 2570 by steps, 990 now (tries 390, settle 350, store 250); one of 99 KB at quality 97, which no step settled, 6200 -> 1500
 // the whole call.  The end that is tried is eight blocks long: with six the 64 photographs take 1340 (more to decode on), with ten 1140.
+// Blocks of very many bits have more to be decoded on than there is room for (split_dense in pcr_lib.hip); what is left goes in steps.
 //
-// By steps (k_sequential_split; many scans, and scans whose MCUs are one block), a workgroup per scan: every lane decodes its piece as if a first
+// By steps (k_sequential_split; many scans, scans whose MCUs are one block, and what the tries leave), a workgroup per scan: every lane decodes its piece as if a first
 // block began there; every piece that turns out to begin in another state than was assumed is decoded again, until nothing changes (20 to 40
 // rounds, most of them with few pieces); then steps 3 and 4.  Streams that do not fall into step are left to k_sequential, as are short
 // ones: `done` says which.
@@ -183,6 +184,7 @@ PCR_D bool split_stops(uint32_t round, uint32_t count, uint32_t* half_left) {
 
 // What a unit is given to work in: pieces it is cut into at most, tries of each (the blocks of an MCU), nodes there is room for, where
 // its nodes and pieces begin, bits of a piece at least and bits of its end the tries are made on.  The host lays it out from the scan's mean bytes; units that turn out longer have longer pieces.
+// No tries: a unit that is not for them.
 struct SplitRoom { uint64_t node0; uint32_t piece0, pieces, tries, nodes, least, run_in; };
 // A start state of a piece, where its decoder ended and what it passed.  Node p * tries + h: piece p from where try h of the piece
 // before ended; behind those, in no order, the starts that no try had.
@@ -461,7 +463,9 @@ __global__ void __launch_bounds__(kSplitStoreLanes) k_split_store(DevRecord R, c
 }
 
 // By steps; done[u], where it is not 0: unit u needs nothing more; one more than the rounds it took, and kSplitInSteps.
-__global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, const Unit* __restrict__ units, uint32_t* __restrict__ done, const uint32_t* __restrict__ clean32) {
+// left: only the units that are left (done[u] is 0), behind the tries.
+__global__ void __launch_bounds__(kSplitLanes) k_sequential_split(DevRecord R, const Unit* __restrict__ units, uint32_t* __restrict__ done, uint32_t left, const uint32_t* __restrict__ clean32) {
+    if (left && done[blockIdx.x]) return;
     __shared__ SplitTables T;
     __shared__ LaneRing rings[kSplitWaves];
     // per piece: the state its decoder was last set down in, the one it ended in, what it passed; and the pieces of a round

@@ -72,8 +72,19 @@ def test_who_decodes_what():
            steps=lambda by, t, s, left, rt, rs: (s, left) == (1, 0) and rs >= 8, one=lambda by, *n: by == ONE and sum(n) == 0)
     _check([pcrgen.encode_pixels(flat, 2, 2, 90, "sequential")], tries=lambda by, t, s, left, rt, rs: (t, left, rt) == (1, 0, 0), steps=lambda by, t, s, left, *r: (s, left) == (0, 1))
     _check([pcrgen.encode_pixels(pcrgen.synth(3, 2, 500, 440, 1, 26.0), 1, 1, 90, "sequential")], auto=lambda by, t, s, left, *r: by == STEPS and (s, left) == (1, 0))
-    _check([pcrgen.encode_pixels(_noise(5, 250, 250, 3), 2, 2, 100, "sequential")], steps=lambda by, t, s, left, *r: (s, left) == (0, 1), tries=lambda by, t, *r: t == 0)
+    _check([pcrgen.encode_pixels(_noise(5, 250, 250, 3), 2, 2, 100, "sequential")], steps=lambda by, t, s, left, *r: (s, left) == (0, 1), tries=lambda by, t, s, left, *r: (t, s, left) == (0, 0, 1))
     _check([planar_sequential(5, 200, 170, 95)], auto=lambda by, t, s, left, *r: by == STEPS and (s, left) == (3, 0), tries=lambda by, t, s, left, *r: (t, left) == (3, 0))
+
+
+@pytest.mark.parametrize("sub", [1, 2])
+def test_blocks_of_very_many_bits_go_in_steps(sub):
+    """Noise at quality 100: what is to be decoded on outgrows the room of the tries, and one wavefront takes four times as long as the steps.  Alone; asked to go by
+    tries all the same; beside pictures that do."""
+    dense = pcrgen.encode_pixels(pcrgen.synth(3, 2, 800, 800, 3, 10.0), sub, sub, 100, "sequential")
+    usual = [pcrgen.encode_pixels(pcrgen.synth(9 + i, 2, 500, 440, 3, 26.0), sub, sub, 90, "sequential") for i in range(3)]
+    assert len(dense) > 800000
+    _check([dense], auto=lambda by, t, s, left, *r: by == STEPS and (t, s, left) == (0, 1, 0), tries=lambda by, t, s, left, *r: (t, s, left) == (0, 1, 0))
+    _check(usual[:2] + [dense] + usual[2:], auto=lambda by, t, s, left, *r: by != ONE and left == 0, tries=lambda by, t, s, left, *r: (t, s, left) == (3, 1, 0))
 
 
 def _free():
