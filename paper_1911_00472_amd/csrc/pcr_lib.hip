@@ -78,24 +78,28 @@ bool split_dense(const ImgDesc& im, const ScanDesc& sd, uint32_t each) {
 //
 // The tries work in memory of the record (SplitSpace), which it has where some number of open records would have them chosen.
 struct SplitLaunch {
-    uint32_t units = 0, dense = 0; uint64_t bytes = 0, dense_bytes = 0, tried = 0;       // dense: of the units; tried: bits to be decoded, once per try
+    uint32_t units = 0, dense = 0; uint64_t bytes = 0, dense_bytes = 0, tried = 0, blocks = 0, mcu_blocks = 0;       // dense: of the units; tried: bits to be decoded, once per try; blocks, and those of an MCU, of all units
     float work = 0; bool subsampled = false, several = false;       // us by tries with the chip full; some MCUs of several blocks per component, of several blocks
     // `count` units of a scan, of so many bytes each on average; false: they are not long
     bool add(const ImgDesc& im, const ScanDesc& sd, uint32_t each, uint32_t count) {
         if ((uint64_t)each * 8 < kSplitLeastBits) return false;
         const uint32_t tries = split_tries_of(im, sd);
-        units += count; bytes += (uint64_t)each * count;
+        units += count; bytes += (uint64_t)each * count; blocks += (uint64_t)tries * sd.mcus; mcu_blocks += (uint64_t)tries * count;
         subsampled = subsampled || tries > (uint32_t)im.nc; several = several || tries > 1;
         if (split_dense(im, sd, each)) { dense += count; dense_bytes += (uint64_t)each * count; return true; }
         tried += (uint64_t)tries * each * 8 * count;
         work += (22.f + 4.5f * (float)tries) * 1e-6f * (float)each * (float)count;
         return true;
     }
-    // us in steps of so many units, with those of other records beside them
+    // us in steps of so many units, with those of other records beside them.  (Faster the fewer blocks an MCU has and the fewer bits a block: fewer places
+    // to be off by, and more blocks to a piece.  ms by tries / in steps, 128 and 300 files of 4:2:0: 50 KB at 247 bits a block 1.0 / 2.0 and 1.6 / 3.2; 98 KB at 193
+    // 1.2 / 1.4 and 2.5 / 2.3; 147 KB at 135 1.6 / 1.4 and 2.9 / 2.4; 87 KB at 113 1.1 / 1.4; of 4:2:2, 96 KB at 230 1.0 / 1.2 and 1.9 / 1.8, 99 KB at 150 0.9 / 0.8.)
     float steps(uint32_t count, uint64_t all, float beside) const {
         const float kb = (float)all / (float)count / 1000.f, turns = std::ceil((float)count * beside / 256.f);
         const float long_kb = std::max(0.f, kb - 300.f);     // (a lane's piece is beyond a wrong block then)
-        return subsampled ? 550.f + turns * (850.f + 6.f * kb - 3.f * long_kb) : 150.f + turns * (260.f + 4.5f * kb);
+        if (!subsampled) return 150.f + turns * (260.f + 4.5f * kb);
+        const float a_block = (float)bytes * 8.f / (float)std::max<uint64_t>(blocks, 1), an_mcu = (float)mcu_blocks / (float)units;
+        return std::min(1.f, std::max(0.62f, a_block / 270.f)) * std::min(1.f, an_mcu / 6.f) * (550.f + turns * (850.f + 6.f * kb - 3.f * long_kb));
     }
     // room: the tries have memory to work in
     SplitBy by(int open_records, bool room) const {

@@ -76,6 +76,22 @@ def test_who_decodes_what():
     _check([planar_sequential(5, 200, 170, 95)], auto=lambda by, t, s, left, *r: by == STEPS and (s, left) == (3, 0), tries=lambda by, t, s, left, *r: (t, left) == (3, 0))
 
 
+@pytest.mark.parametrize("hs,vs,quality,noise,side,by", [(2, 2, 75, 8.0, 600, {16: TRIES, 200: STEPS}), (2, 1, 90, 20.0, 325, {64: TRIES, 300: STEPS}), (2, 2, 90, 26.0, 255, {64: TRIES, 300: TRIES})])
+def test_many_scans_of_few_bits_a_block_go_in_steps(hs, vs, quality, noise, side, by):
+    """Where the steps were measured to be faster, and where not."""
+    files = [pcrgen.encode_pixels(pcrgen.synth(3 + i, 2, side, side - 5, 3, noise), hs, vs, quality, "sequential", restart=0) for i in range(8)]
+    for n, want in by.items():
+        with pkg.pcr_open(pcrgen.write_record([files[i % 8] for i in range(n)]), 0) as r:
+            st = torch.empty(n, dtype=torch.int32, device="cuda")
+            a = r.decode_coefficients(r.G) if n == min(by) else None
+            r.decode_batch(r.G, status=st)
+            route = r.last_sequential_decoders()
+            assert route[0] == want and route[3] == 0 and not st.any(), (n, route)
+            if a is not None:
+                r.set_sequential_decoders(ONE)
+                assert torch.equal(a, r.decode_coefficients(r.G))
+
+
 @pytest.mark.parametrize("sub", [1, 2])
 def test_blocks_of_very_many_bits_go_in_steps(sub):
     """Noise at quality 100: what is to be decoded on outgrows the room of the tries, and one wavefront takes four times as long as the steps.  Alone; asked to go by
