@@ -70,6 +70,21 @@ def test_color_and_blocks_longer_than_the_ring_of_windows():
     _same(pcrgen.write_record(files), range(6, 11), range(len(files)), (0, 5, 9))
 
 
+@pytest.mark.parametrize("firsts,refines,trios", [(4, 4, True), (3, 4, True), (3, 5, False)])
+def test_the_widest_chains(firsts, refines, trios):
+    """Eight scans of a component, four of them refinement scans: sixteen wavefronts, as many as a workgroup has; with five the chains keep one wavefront a unit."""
+    cuts = [1, 6, 21, 41][:firsts] + [64]
+    script = [(1, 0, 0, 0, 0, 0, 0, 0)] + [(1, 0, 0, 0, a, b - 1, 0, refines) for a, b in zip(cuts, cuts[1:])] + [(1, 0, 0, 0, 1, 63, l, l - 1) for l in range(refines, 0, -1)]
+    q, rng = np.ones((2, 64), np.uint16), np.random.default_rng(firsts)
+    n = pcrgen.plane_blocks(120, 72, 1, 1, 1)[0]
+    files = [pcrgen.encode_coefs((_blocks(kind, rng, n) * rng.choice([1, 1, 3, 7], (n, 1))).reshape(-1), 120, 72, 1, 1, 1, q, script, r) for kind in KINDS for r in (0, 2)]
+    rec = pcrgen.write_record(files)
+    G = len(script)
+    _same(rec, [G], range(len(files)), trios=trios)
+    _same(rec, [G], (0, 3), (1 + firsts,))                    # (an upgrade: the refinement scans alone)
+    _same(rec, [G - 1], (0, 3), trios=True)
+
+
 @pytest.mark.parametrize("entry", [0, 16])
 def test_both_sides_of_the_line(entry):
     files = [pcrgen.make_jpeg(40 + i, 1, 72, 56, 1, 8.0, 1, 1, 92) for i in range(8)]
