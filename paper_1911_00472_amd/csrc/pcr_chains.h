@@ -273,9 +273,10 @@ struct LanesLaunch {
 // Three take two thirds of the time of one while the launch takes as long as its longest unit, and up to half as much again once the launches
 // of all records in flight fill the chip.  So what decides is `full`: what the launch asks of the chip over its longest unit, in bits, a block counted as
 // 14 and the start of a workgroup as 500 (it brings tables, and takes the room of the widest one, whatever is in it), first scans
-// beside the refinement scans by half of theirs (they keep one wavefront).  Where the line lies depends on the records decoded at a time; the
-// records the process has open are taken as the sign of it, as by split_pays and the lanes: idle ones cost what three wavefronts gain
-// there, and never more than one wavefront a unit takes.  us a call by one wavefront a unit / by three (n pictures a record; full):
+// beside the refinement scans by half of theirs (they keep one wavefront).  Where the line lies depends on the records decoded at a time, of which
+// the records the process has open are all that is known: a program may keep several open and decode them one after another, each when the
+// last one is done.  Three wavefronts gain most there, so the lines for several are no lower than that what is lost where all are in flight
+// stays within 4 %.  us a call by one wavefront a unit / by three (n pictures a record; full), calls of all records issued without waiting for any:
 //                                                  one record              two                    four
 //   plain records (all scans side by side)
 //     300 to 500 pixels, scan group 10   n 400    5716 / 4123  (701)     7412 / 5881         14404 / 12175
@@ -296,8 +297,13 @@ struct LanesLaunch {
 //   entry points every 64 MCUs (level by level)
 //     17 to 320 pixels, 10                  64     243 / 228   (1078)     284 / 284            520 / 529
 //                                          128     271 / 280   (1895)     335 / 364            649 / 739
-// (Over 190 kinds of records at one, two and four at a time and scan groups 4 to 10 the three lines lose 0.1, 0.6 and 0.7 % against the better
-// of the two.)
+// and calls that set out together and are waited for together (four of 500: 805):
+//     300 to 500 pixels, scan group 10   n 512    5674 / 4132  (943)     8780 / 7165         14515 / 14170
+//                                          640    5798 / 4238  (1180)    9123 / 8337
+//     256 x 256, 10                        500    1673 / 1255  (874)     2721 / 2387          4696 / 4626
+//     192 x 192, 4:4:4, 6                  700     825 / 729   (1127)    1369 / 1346          2388 / 2597; of 500 2035 / 2000
+//     128 x 128, gray, 6                   550     493 / 394   (954)      797 / 729           1356 / 1345
+// (With lines of 950 for two and three and 700 from four on three records of 512 photographs, decoded one after another, took 5241 instead of 4155.)
 struct TrioLaunch {
     uint64_t work = 0, beside = 0; uint32_t longest = 0, groups = 0;       // groups: workgroups of the launch
     void add(const LanesLaunch& l) {
@@ -306,7 +312,7 @@ struct TrioLaunch {
     }
     void add_beside(const LanesLaunch& l) { beside += l.bits + 14 * l.blocks; }
     bool pays(int open_records) const {
-        const uint64_t line = open_records <= 1 ? 1500 : (open_records <= 3 ? 950 : 700);
+        const uint64_t line = open_records <= 1 ? 1500 : (open_records <= 3 ? 1050 : 950);
         return longest > 0 && work + beside / 2 + 500ull * groups <= line * (longest + 70);
     }
 };
