@@ -436,8 +436,10 @@ int pcr_last_first_splits(pcr_record* rec, int* launches, int* wide_launches);
  * as long as their longest unit; never in mode -1). */
 int pcr_last_refine_trios(pcr_record* rec, int* launches);
 /* Whether the pixels of the last decode call were stored past the chip's caches (records whose coefficient planes fit in the 256 MB of the memory-side cache but
- * not beside the pixels; the pixels are the same). */
+ * not beside the pixels; DC-only decodes of more than 256 MB of pixels with four and more records open; the pixels are the same), and whether the zero fill of its
+ * coefficient planes was (more than 400 MB of them with four and more records open). */
 int pcr_last_past_stores(pcr_record* rec, int* past);
+int pcr_last_past_fills(pcr_record* rec, int* past);
 
 /* Stage timing with HIP events recorded on the call's own stream (off by default; switching it on
  * starts a new history).  While it is on, every stage has launches of its own, and first scans are not given many lanes each (DC_FIRST and

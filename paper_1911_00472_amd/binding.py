@@ -44,6 +44,7 @@ SYMBOLS = {
     "pcr_set_sequential_decoders": (ctypes.c_int, [_vp, ctypes.c_int]),
     "pcr_last_sequential_decoders": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.c_uint32 * 3, ctypes.c_uint32 * 2]),
     "pcr_last_past_stores": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int)]),
+    "pcr_last_past_fills": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_first_splits": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "pcr_last_stage_ms": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_float)]),
     "pcr_probe_scalar_issue_rate": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_double)]),
@@ -379,6 +380,12 @@ class Record:
         """Whether the last decode call stored its pixels past the chip's caches."""
         a = ctypes.c_int()
         _check(lib().pcr_last_past_stores(self._h, ctypes.byref(a)), "pcr_last_past_stores")
+        return bool(a.value)
+
+    def last_past_fills(self):
+        """Whether the last decode call stored the zero fill of its coefficient planes past the chip's caches."""
+        a = ctypes.c_int()
+        _check(lib().pcr_last_past_fills(self._h, ctypes.byref(a)), "pcr_last_past_fills")
         return bool(a.value)
 
     def last_first_splits(self):

@@ -44,7 +44,7 @@ PCR_D uint32_t xcd_major(uint32_t b, uint32_t n) {
     const uint32_t q = n / kXcds, r = n - q * kXcds, x = b % kXcds, i = b / kXcds;
     return x * q + (x < r ? x : r) + i;
 }
-// A store of T (made of 32-bit words) that asks the caches to make no room for it.  Which stores do is the host's to say (pixels_past in pcr_lib.hip).
+// A store of T (made of 32-bit words) that asks the caches to make no room for it.  Which stores do is the host's to say (pixels_past, rows_past and fill_past in pcr_lib.hip).
 template <class T, int WORDS = sizeof(T) / 4> PCR_D void put_past(void* p, const uint32_t* w) {
     typedef uint32_t V __attribute__((ext_vector_type(WORDS), aligned(alignof(T))));
     V v;
@@ -488,7 +488,7 @@ __global__ void __launch_bounds__(256) k_bind_fill(BindFill F) {
 }
 
 constexpr int kMaxFills = 3;
-struct FillList { uint4* p[kMaxFills]; size_t n16[kMaxFills]; uint32_t rows; };  // 16-byte pieces; rows of workgroups that share the work
+struct FillList { uint4* p[kMaxFills]; size_t n16[kMaxFills]; uint32_t rows, past; };  // 16-byte pieces; rows of workgroups that share the work; past: see put_past
 
 // 0x80 in every byte of the result whose byte in x is zero (exact, no carries between bytes)
 PCR_D uint64_t zero_bytes(uint64_t x) {
@@ -735,7 +735,9 @@ __global__ void __launch_bounds__(64 * WAVES) k_unstuff(DevRecord R, UnstuffPlan
         for (int f = 0; f < kMaxFills; f++) {
             uint4* p = F.p[f];
             const size_t n16 = F.n16[f], stride = (size_t)F.rows * kDies * (64 * WAVES);
-            for (size_t e = (size_t)turn.index * (64 * WAVES) + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
+            const uint32_t zero[4] = {0, 0, 0, 0};
+            if (F.past) { for (size_t e = (size_t)turn.index * (64 * WAVES) + tid; e < n16; e += stride) put_past<uint4>(p + e, zero); }
+            else for (size_t e = (size_t)turn.index * (64 * WAVES) + tid; e < n16; e += stride) p[e] = make_uint4(0, 0, 0, 0);
         }
         return;
     }
@@ -2075,16 +2077,16 @@ PCR_D void store_head(uint8_t* p, uint32_t w0, uint32_t w1, uint32_t w2, uint32_
     else if (n - done == 1) p[done] = (uint8_t)w;
 }
 
-// kPast: pixels stored past the caches (pixels_past).  A kernel of its own: with the choice made at every store 128 pictures of 1024 x 1024 in each of two
+// One run of MCUs (k_pixel).  kPast: its pixels are stored past the caches (pixels_past).  A kernel of its own: with the choice made at every store 128 pictures of 1024 x 1024 in each of two
 // records took 934 us a pass at scan group 5, and 931 without.
 //
 // 120 registers at most, and not the 128 that four wavefronts per SIMD could have: with four of them a SIMD has 32 left for a wavefront of another launch.  At
 // 121 k_bind_fill of a loader's next slot took 119 us beside this kernel instead of 19, and 4 x 1024 photographs at scan group 2 2475 us a pass
-// instead of 2220.
-template <bool kRefine, bool kPlanes, bool kPast = false>
-__global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out,
-                                                     const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx,
-                                                     const CropBox* __restrict__ boxes) {
+// instead of 2220.  Where a change or another compiler takes it over the line, something is to be kept in LDS or worked out again that was kept in
+// registers: the attribute that limits them has no effect below what launch bounds allow.
+template <bool kRefine, bool kPlanes, bool kPast>
+PCR_D __attribute__((always_inline)) void pixel_run(const DevRecord& R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out, const ApplyList* __restrict__ lists,
+                                                    const int32_t* __restrict__ list_idx, const CropBox* __restrict__ boxes) {
     // samples of half the pixel rows of the run: 32 per block
     __shared__ __attribute__((aligned(16))) float tile[kPixSamples];
     // quantiser steps in zig-zag order times the folded transform factors; the rows of the three components start
@@ -2292,6 +2294,15 @@ __global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const Pixel
         }
     }
 }
+template <bool kRefine, bool kPlanes>
+__global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out,
+                                                     const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx,
+                                                     const CropBox* __restrict__ boxes) {
+    pixel_run<kRefine, kPlanes, false>(R, tiles, out, lists, list_idx, boxes);
+}
+__global__ void __launch_bounds__(kPixLanes, 4) k_pixel_past(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out) {
+    pixel_run<false, false, true>(R, tiles, out, nullptr, nullptr, nullptr);
+}
 
 // --------------------------------------------------------------------------------------
 // k_pixel_flat: the pixel stage of a decode that holds DC coefficients only (scan groups ahead of every AC scan):
@@ -2403,6 +2414,8 @@ PCR_HD bool flat_rows_fit(uint32_t W) { return ((W + 7) >> 3) <= (uint32_t)kFlat
 // LDS bytes a launch needs for images of at most `cells` cells per row: 24 bytes per cell, the repeated 32 bytes, slack
 PCR_HD uint32_t flat_rows_lds(uint32_t cells) { return cells * 24 + 64; }
 
+// kPast: the chunks go past the caches (rows_past).
+template <bool kPast>
 __global__ void __launch_bounds__(kFlatRowLanes) k_pixel_flat_rows(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out, uint32_t max_cells) {
     // the pixel row: 24 bytes per cell (8 for a gray image), then its first 32 bytes again so that a chunk may run past its end
     extern __shared__ __attribute__((aligned(16))) uint32_t pat[];
@@ -2455,7 +2468,8 @@ __global__ void __launch_bounds__(kFlatRowLanes) k_pixel_flat_rows(DevRecord R, 
         uint4 v;
         v.x = __builtin_amdgcn_alignbyte(b, a, sh); v.y = __builtin_amdgcn_alignbyte(c, b, sh);
         v.z = __builtin_amdgcn_alignbyte(d, c, sh); v.w = __builtin_amdgcn_alignbyte(e, d, sh);
-        *reinterpret_cast<uint4*>(band + p) = v;
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        if (kPast) put_past<uint4>(band + p, w); else *reinterpret_cast<uint4*>(band + p) = v;
     }
     if (tid < head) band[tid] = pb[tid];                    // (head < 16 <= the repeated part)
     if (tid < len - tail0) band[tail0 + tid] = pb[in_row(tail0 + tid)];

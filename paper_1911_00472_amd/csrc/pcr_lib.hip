@@ -335,7 +335,7 @@ struct pcr_record {
     int seq_mode = 0;                                     // pcr_set_sequential_decoders
     struct SeqDone { uint32_t* d_done; uint32_t units; };
     int last_seq = 0; std::vector<SeqDone> last_done;     // how the last decode call decoded its sequential scans (SplitBy + 1), its launches by many lanes
-    bool last_past = false;                               // ... whether its pixels were stored past the caches (pixels_past)
+    bool last_past = false, last_fill_past = false;       // ... whether its pixels, and the zero fill, were stored past the caches (pixels_past, rows_past, fill_past)
     std::vector<uint32_t> ent_off_h;        // record offset of every scan's entry points (0: none), as uploaded
     std::vector<uint32_t> unit_bits;        // records opened from host bytes: entropy-coded bits of every unit, by slot (else empty)
     // decode fused with the training tail (allocated at its first call): one tile per run of an MCU row, the side buffer of first
@@ -769,6 +769,18 @@ bool pixels_past(const pcr_record* r, const Plan* plan, bool boxes) {
     const uint64_t planes = r->coef_off[r->hdr.n] * sizeof(int16_t), pixels = r->out_off[r->hdr.n];
     return planes <= 256 * kMB && planes + pixels > 280 * kMB && plan->has_ac && !plan->n_apply && !boxes && g_open_records.load(std::memory_order_relaxed) <= 3;
 }
+// Whether the pixel rows of a DC-only decode (k_pixel_flat_rows), and the zero fill of the coefficient planes, go past it as well: where they do not fit in it
+// by themselves and several records' launches have to share it, which four open records are taken as the sign of (as by split_pays).  Zeros that
+// do fit in part are still there when the first scans are stored into them, so the fill's line lies higher.  Time past the cache over the time through it;
+// in flight: four records at a time / one, three others open and idle (MB of pixels, or of planes)
+//   pixel rows   98 0.95 / 0.98   196 0.85 / 0.97   262 0.81 / 0.94 (a conversion to half precision behind it: 0.98 / 1.02)   384 0.77 / 0.87 (0.97 / 0.99)
+//     odd widths 234 0.99         320 0.98 / 1.03   469 0.97 / 1.02 (0.99 / 1.01)
+//   the fill     183 1.00         192 0.96          234 1.00 / 1.07                 320 0.99 / 1.06   384 0.98 / 1.04   469 0.95 / 1.02 (0.98 / 1.01)
+//                703 0.99 / 1.00  938 - / 0.99, two at a time 0.99; 469 at scan group 3 1.00, 8 0.98, 10 0.98 / 1.00, with the training tail 0.95 / 1.00, from a loader
+//                0.99; 938 from a loader of two 0.96
+bool others_open() { return g_open_records.load(std::memory_order_relaxed) > 3; }
+bool rows_past(const pcr_record* r) { return others_open() && r->out_off[r->hdr.n] > (256u << 20); }
+bool fill_past(const pcr_record* r) { return others_open() && r->coef_off[r->hdr.n] * sizeof(int16_t) > (400u << 20); }
 
 // Index, marker parse and Huffman tables (of scans k0 .. k-1) on the device.  Small records take the offsets of their
 // regions in the same kernel: a launch costs about as much as k_index runs, and a workgroup of k_headers sums at most
@@ -809,6 +821,8 @@ void launch_unstuff(pcr_record* r, uint32_t k0, uint32_t k, FillList fill, Apply
     P.first[count] = groups;
     size_t pieces = 0;
     for (int f = 0; f < kMaxFills; f++) pieces += fill.n16[f];
+    r->last_fill_past = fill_past(r) && pieces > 0;
+    fill.past = r->last_fill_past ? 1u : 0u;
     const uint32_t lanes = 64 * waves;                       // (eight pieces per lane, but for the last row)
     fill.rows = fill_rows((uint32_t)std::min<size_t>((pieces + 8 * lanes - 1) / (8 * lanes), std::min<size_t>(many ? 512 : 2048, std::max<size_t>(groups, many ? 256 : 1024))));
     const uint32_t total = lists.groups + groups + kDies * fill.rows;
@@ -832,7 +846,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     const bool several = open > 1;
     std::vector<char> by_lanes(plan->levels.size(), 0);
     r->last_lane_launches = r->last_wave_launches = r->last_splits = r->last_wide_splits = r->last_trios = 0;
-    r->last_past = false; r->last_seq = 0; r->last_done.clear();
+    r->last_past = r->last_fill_past = false; r->last_seq = 0; r->last_done.clear();
     for (size_t li = 0; li < plan->levels.size(); li++) {
         const LevelList& l = plan->levels[li];
         if (l.kind == kSequential) by_lanes[li] = (char)(r->seq_mode == 0 ? l.seq.by(open, l.by_tries) : (l.seq.units == 0 || r->seq_mode == 1 ? kSplitNever : (r->seq_mode == 2 ? kSplitBySteps : (l.by_tries ? kSplitByTries : kSplitNever))));
@@ -1683,6 +1697,11 @@ int pcr_last_past_stores(pcr_record* r, int* past) {
     *past = r->last_past ? 1 : 0;
     return PCR_OK;
 }
+int pcr_last_past_fills(pcr_record* r, int* past) {
+    if (!r || !past) return PCR_E_ARG;
+    *past = r->last_fill_past ? 1 : 0;
+    return PCR_OK;
+}
 int pcr_last_first_splits(pcr_record* r, int* launches, int* wide_launches) {
     if (!r || !launches || !wide_launches) return PCR_E_ARG;
     *launches = r->last_splits; *wide_launches = r->last_wide_splits;
@@ -1752,18 +1771,21 @@ static int decode_to_pixels(pcr_record* r, int k0, int k, uint8_t* out, size_t c
     // launches took 150 of the 1550 us of 2048 pictures of 132 x 133 at scan group 10, to find that there is none)
     DevRecord d = r->d;
     d.status_out = d_status;
-    r->last_past = pixels_past(r, plan, boxes != nullptr);
     const bool smooth_flat = smooth && !plan->has_ac && !plan->n_apply && !boxes;
     if (smooth_flat || !plan->smooths) smooth = false;
+    const bool by_rows = !smooth_flat && !plan->n_apply && !plan->has_ac && !smooth && r->n_flat_rows && !boxes;     // DC scans only: every block is flat
+    r->last_past = by_rows ? rows_past(r) : pixels_past(r, plan, boxes != nullptr);
     if (smooth) hipLaunchKernelGGL(k_smooth<false>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
     if (smooth_flat)
         hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out);
     else if (plan->n_apply)
         hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
+    else if (r->last_past && !by_rows)
+        hipLaunchKernelGGL(k_pixel_past, dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out);
     else if (plan->has_ac || smooth)
-        hipLaunchKernelGGL((r->last_past ? k_pixel<false, false, true> : k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
-    else if (r->n_flat_rows && !boxes)                       // DC scans only: every block is flat
-        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
+        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
+    else if (by_rows)
+        hipLaunchKernelGGL((r->last_past ? k_pixel_flat_rows<true> : k_pixel_flat_rows<false>), dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
     else
         hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out, boxes);
     if (smooth) hipLaunchKernelGGL(k_smooth<true>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);

@@ -1,5 +1,5 @@
-"""Pixels stored past the caches (pixels_past): which calls do, and that the pixels are the same either way -- colour at half and full chroma
-resolution, gray, rows that end inside a chunk -- and the same as the oracle's."""
+"""Stores past the caches (CacheRule): the pixels are the same on either side of every line, whichever kernels take it -- colour at half and
+full chroma resolution, gray, rows that end inside a chunk, DC-only decodes -- and the same as the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -11,43 +11,24 @@ import pcrgen
 pytestmark = pytest.mark.gpu
 
 
-def _same_pixels(data, n, w, h, c, k, taken):
-    """The decode of k with no more than three records open, then with four: the first takes the stores past the caches where `taken` says so."""
+@pytest.mark.parametrize("n,w,h,c,sub,ks", [(12, 512, 512, 3, 2, (5, 10)), (23, 517, 509, 3, 2, (4, 10)), (60, 517, 509, 1, 1, (3, 6)), (34, 1021, 1024, 3, 1, (10,)),
+                                            (75, 1024, 1021, 3, 2, (1, 5)), (100, 1021, 1024, 3, 2, (1, 10))])
+def test_the_same_on_both_sides(n, w, h, c, sub, ks):
+    """9 to 300 MB of planes, calls on one stream and on four in turn: each rule is taken and left."""
+    data = pcrgen.write_record([pcrgen.make_jpeg(40 + w + h, 2, w, h, c, 9.0, sub, sub, 88, restart=1)] * n)
     with pkg.pcr_open(data, 0) as r:
-        a = r.decode_batch(k)
-        assert r.last_past_stores() == taken, k
+        alone = [r.decode_batch(k) for k in ks]
+        streams = [torch.cuda.Stream() for _ in range(3)]
         others = [pkg.pcr_open(pcrgen.write_record([pcrgen.make_jpeg(1, 1, 8, 8, 1, 1.0, 1, 1, 90)]), 0) for _ in range(3)]
-        b = r.decode_batch(k, torch.full_like(a, 7))
-        assert not r.last_past_stores() and torch.equal(a, b), k
+        for k, a in zip(ks, alone):
+            out = torch.full_like(a, 7)
+            for o, s in zip(others, streams):
+                o.decode_batch(1, stream=s.cuda_stream)
+            assert torch.equal(r.decode_batch(k, out), a), k
+            torch.cuda.synchronize()
+            per = a.view(n, h, w, c)
+            assert bool((per == per[0]).all()), k
+            want = oracle.decode_record_image(data, 0, k)[1]
+            assert np.abs(per[0].cpu().numpy().astype(int) - want.reshape(h, w, c)).max() <= 1, k
         for o in others:
             o.close()
-        per = a.view(n, h, w, c)
-        assert bool((per == per[0]).all()), k
-        want = oracle.decode_record_image(data, 0, k)[1]
-        assert np.abs(per[0].cpu().numpy().astype(int) - want.reshape(h, w, c)).max() <= 1, k
-
-
-@pytest.mark.parametrize("n,w,h,c,sub,taken", [
-    (12, 512, 512, 3, 2, {5: 0}),                              # 9 + 9 MB of planes and pixels
-    (46, 1021, 1024, 3, 2, {5: 0}),                            # 138 + 138: nearly all of it fits
-    (60, 1021, 1024, 3, 2, {1: 0, 5: 1, 10: 0}),               # 180 + 180: the planes fit, the pixels not beside them; DC alone, with refinement
-    (35, 1024, 1021, 3, 1, {5: 1}),                            # 210 + 105
-    (115, 1021, 1024, 1, 1, {3: 1, 6: 0}),                     # 230 + 115
-    (90, 1024, 1021, 3, 2, {5: 0}),                            # 270 + 270: the planes do not fit either
-])
-def test_the_same_on_both_sides(n, w, h, c, sub, taken):
-    data = pcrgen.write_record([pcrgen.make_jpeg(40 + w + h, 2, w, h, c, 9.0, sub, sub, 88, restart=1)] * n)
-    for k, t in taken.items():
-        _same_pixels(data, n, w, h, c, k, bool(t))
-
-
-def test_pixels_for_the_training_tail_stay_in_the_caches():
-    n, w, h = 60, 1024, 1024
-    data = pcrgen.write_record([pcrgen.make_jpeg(7, 2, w, h, 3, 9.0, 2, 2, 88, restart=1)] * n)
-    with pkg.pcr_open(data, 0) as r:
-        whole = r.decode_batch(5)
-        assert r.last_past_stores()
-        boxes = torch.tensor([[0, 0, w, h, 0]] * n, dtype=torch.int32, device="cuda")
-        pixels = torch.full_like(whole, 3)
-        r.decode_crop_batch(5, boxes, 96, 96, (0.5,) * 3, (2.0,) * 3, pixels)
-        assert not r.last_past_stores() and torch.equal(pixels, whole)

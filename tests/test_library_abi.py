@@ -107,32 +107,31 @@ def test_missing_library_fails_loudly(monkeypatch):
         b.lib()
 
 
-@pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """The compiler's figures of every kernel: {name: {directive: value}}."""
+def test_no_kernel_spills_to_scratch_memory(tmp_path):
+    """Every kernel keeps its state in registers and LDS.  (An array indexed with a run-time value is put into scratch
+    memory by the compiler, whole: it once cost the DC-only pixel kernel 5 KB of extra memory writes per wavefront, which
+    showed in the hardware counters as half again the bytes the kernel had to write.)"""
+    import os
+    import subprocess
+    from paper_1911_00472_amd import build
+    asm = tmp_path / "pcr.s"
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    subprocess.check_call([hipcc] + flags + ["-S", "--cuda-device-only", "-o", str(asm), build.SRC], stderr=subprocess.DEVNULL)
+    sizes = [line.split()[-1] for line in asm.read_text().splitlines() if ".amdhsa_private_segment_fixed_size" in line]
+    assert len(sizes) > 30 and all(s == "0" for s in sizes), sizes
+
+
+def test_pixel_kernel_leaves_registers_for_another_launch(tmp_path):
+    """Four wavefronts of k_pixel on a SIMD (its bound) leave 32 of the 512 registers, which are handed out by eights: enough for a
+    wavefront of a loader's next slot, which otherwise waits for the whole pixel kernel."""
     import os
     import re
     import subprocess
     from paper_1911_00472_amd import build
-    asm = tmp_path_factory.mktemp("asm") / "pcr.s"
+    asm = tmp_path / "pcr.s"
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     subprocess.check_call([hipcc] + flags + ["-S", "--cuda-device-only", "-o", str(asm), build.SRC], stderr=subprocess.DEVNULL)
-    return {name: dict(re.findall(r"\.(amdhsa_\w+) (\S+)", body)) for name, body in re.findall(r"\.amdhsa_kernel (\S+)\n(.*?)\.end_amdhsa_kernel", asm.read_text(), re.S)}
-
-
-def test_no_kernel_spills_to_scratch_memory(kernels):
-    """Every kernel keeps its state in registers and LDS.  (An array indexed with a run-time value is put into scratch
-    memory by the compiler, whole: it once cost the DC-only pixel kernel 5 KB of extra memory writes per wavefront, which
-    showed in the hardware counters as half again the bytes the kernel had to write.)"""
-    sizes = [k["amdhsa_private_segment_fixed_size"] for k in kernels.values()]
-    assert len(sizes) > 30 and all(s == "0" for s in sizes), sizes
-
-
-def test_pixel_kernel_leaves_registers_for_another_launch(kernels):
-    """Four wavefronts of k_pixel on a SIMD (its bound) leave 32 of the 512 registers, which are handed out by eights: enough for a
-    wavefront of a loader's next slot, which otherwise waits for the whole pixel kernel (k_bind_fill 119 us beside it instead of 19).  Where a
-    change or another compiler takes it over the line, something is to be kept in LDS or worked out again that was kept in registers: the
-    attribute that limits them has no effect below what launch bounds allow."""
-    used = {name: int(k["amdhsa_next_free_vgpr"]) for name, k in kernels.items() if "k_pixelILb" in name}
-    assert len(used) == 5 and all(v <= 120 for v in used.values()), used
+    used = re.findall(r"\.amdhsa_kernel \S*k_pixelILb\S*\n(?:.*\n)*?\s+\.amdhsa_next_free_vgpr (\d+)", asm.read_text())
+    assert len(used) == 4 and all(int(v) <= 120 for v in used), used
