@@ -2077,16 +2077,17 @@ PCR_D void store_head(uint8_t* p, uint32_t w0, uint32_t w1, uint32_t w2, uint32_
     else if (n - done == 1) p[done] = (uint8_t)w;
 }
 
-// One run of MCUs (k_pixel).  kPast: its pixels are stored past the caches (pixels_past).  A kernel of its own: with the choice made at every store 128 pictures of 1024 x 1024 in each of two
-// records took 934 us a pass at scan group 5, and 931 without.
+// past: pixels stored past the caches (pixels_past).  The choice is made at every store: with two kernels instead the compiler lays out the branches around
+// the stores of partial rows otherwise, and 2048 pictures of 80 x 49 took 22.9 us here instead of 21.7, with refinement 29.6 instead of 27.9.
 //
 // 120 registers at most, and not the 128 that four wavefronts per SIMD could have: with four of them a SIMD has 32 left for a wavefront of another launch.  At
-// 121 k_bind_fill of a loader's next slot took 119 us beside this kernel instead of 19, and 4 x 1024 photographs at scan group 2 2475 us a pass
-// instead of 2220.  Where a change or another compiler takes it over the line, something is to be kept in LDS or worked out again that was kept in
-// registers: the attribute that limits them has no effect below what launch bounds allow.
-template <bool kRefine, bool kPlanes, bool kPast>
-PCR_D __attribute__((always_inline)) void pixel_run(const DevRecord& R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out, const ApplyList* __restrict__ lists,
-                                                    const int32_t* __restrict__ list_idx, const CropBox* __restrict__ boxes) {
+// 121 (with the two stores of twelve bytes below the other way round) k_bind_fill of a loader's next slot took 119 us beside this kernel instead of 19, and
+// 4 x 1024 photographs at scan group 2 2475 us a pass instead of 2220.  Where a change or another compiler takes it over the line, something is to
+// be kept in LDS or worked out again that was kept in registers: the attribute that limits them has no effect below what launch bounds allow.
+template <bool kRefine, bool kPlanes>
+__global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out,
+                                                     const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx,
+                                                     const CropBox* __restrict__ boxes, uint32_t past) {
     // samples of half the pixel rows of the run: 32 per block
     __shared__ __attribute__((aligned(16))) float tile[kPixSamples];
     // quantiser steps in zig-zag order times the folded transform factors; the rows of the three components start
@@ -2245,7 +2246,7 @@ PCR_D __attribute__((always_inline)) void pixel_run(const DevRecord& R, const Pi
                         struct __attribute__((packed, aligned(1))) Eight { uint32_t a, b; };
                         Eight e8; e8.a = w0; e8.b = w1;
                         const uint32_t w[2] = {w0, w1};
-                        if (kPast) put_past<Eight>(wp + row * line, w); else *reinterpret_cast<Eight*>(wp + row * line) = e8;
+                        if (past) put_past<Eight>(wp + row * line, w); else *reinterpret_cast<Eight*>(wp + row * line) = e8;
                     } else {
                         store_head(wp + row * line, w0, w1, 0u, left);
                     }
@@ -2257,7 +2258,7 @@ PCR_D __attribute__((always_inline)) void pixel_run(const DevRecord& R, const Pi
                         struct __attribute__((packed, aligned(1))) Twelve { uint32_t a, b, c; };
                         Twelve tw; tw.a = w[0]; tw.b = w[1]; tw.c = w[2];
                         // one (possibly unaligned) 12-byte store
-                        if (kPast) put_past<Twelve>(p, w); else *reinterpret_cast<Twelve*>(p) = tw;
+                        if (!past) *reinterpret_cast<Twelve*>(p) = tw; else put_past<Twelve>(p, w);
                     } else {
                         store_head(p, w[0], w[1], w[2], left * 3);
                     }
@@ -2293,15 +2294,6 @@ PCR_D __attribute__((always_inline)) void pixel_run(const DevRecord& R, const Pi
             }
         }
     }
-}
-template <bool kRefine, bool kPlanes>
-__global__ void __launch_bounds__(kPixLanes, 4) k_pixel(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out,
-                                                     const ApplyList* __restrict__ lists, const int32_t* __restrict__ list_idx,
-                                                     const CropBox* __restrict__ boxes) {
-    pixel_run<kRefine, kPlanes, false>(R, tiles, out, lists, list_idx, boxes);
-}
-__global__ void __launch_bounds__(kPixLanes, 4) k_pixel_past(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out) {
-    pixel_run<false, false, true>(R, tiles, out, nullptr, nullptr, nullptr);
 }
 
 // --------------------------------------------------------------------------------------

@@ -1779,11 +1779,9 @@ static int decode_to_pixels(pcr_record* r, int k0, int k, uint8_t* out, size_t c
     if (smooth_flat)
         hipLaunchKernelGGL(k_pixel_smooth_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out);
     else if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes);
-    else if (r->last_past && !by_rows)
-        hipLaunchKernelGGL(k_pixel_past, dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out);
+        hipLaunchKernelGGL((k_pixel<true, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, plan->d_apply_lists, plan->d_list_idx, boxes, 0u);
     else if (plan->has_ac || smooth)
-        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes);
+        hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes, r->last_past ? 1u : 0u);
     else if (by_rows)
         hipLaunchKernelGGL((r->last_past ? k_pixel_flat_rows<true> : k_pixel_flat_rows<false>), dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
     else
@@ -1829,9 +1827,9 @@ int pcr_decode_batch_triangle(pcr_record* r, int k, uint8_t* out, size_t cap, vo
     DevRecord d = r->d;
     d.status_out = d_status;
     if (plan->n_apply)
-        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<true, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, plan->d_apply_lists, plan->d_list_idx, (const CropBox*)nullptr, 0u);
     else
-        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr);
+        hipLaunchKernelGGL((k_pixel<false, true>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, r->d_planes, (const ApplyList*)nullptr, (const int32_t*)nullptr, (const CropBox*)nullptr, 0u);
     uint32_t items = 1;
     for (uint32_t i = 0; i < n; i++) items = std::max(items, (((uint32_t)r->img[i].W + 3) / 4) * (uint32_t)r->img[i].H);
     hipLaunchKernelGGL(k_triangle_rgb, dim3((items + 255) / 256, n), dim3(256), 0, s, r->d, (const uint8_t*)r->d_planes, out);
