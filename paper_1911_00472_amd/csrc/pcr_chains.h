@@ -272,7 +272,7 @@ struct LanesLaunch {
 //
 // Three take two thirds of the time of one while the launch takes as long as its longest unit, and up to half as much again once the launches
 // of all records in flight fill the chip.  So what decides is `full`: what the launch asks of the chip over its longest unit, in bits, a block counted as
-// 14 and the start of a workgroup as 500 (it brings tables, and takes the room of the widest one, whatever is in it), first scans
+// 14 and the start of a workgroup as 500 where it is of a chain (it brings tables, and takes the room of the widest one, whatever is in it), as 100 where it is of a unit, first scans
 // beside the refinement scans by half of theirs (they keep one wavefront).  Where the line lies depends on the records decoded at a time, of which
 // the records the process has open are all that is known: a program may keep several open and decode them one after another, each when the
 // last one is done.  Three wavefronts gain most there, so the lines for several are no lower than that what is lost where all are in flight
@@ -295,17 +295,22 @@ struct LanesLaunch {
 //   a marker every MCU row, 256 x 256, 10   16     160 / 150   (1066)     187 / 206            334 / 373
 //                                           32     170 / 208   (2215)     232 / 312            444 / 617
 //   entry points every 64 MCUs (level by level)
-//     17 to 320 pixels, 10                  64     243 / 228   (1078)     284 / 284            520 / 529
-//                                          128     271 / 280   (1895)     335 / 364            649 / 739
+//     17 to 320 pixels, 10                  64     243 / 228    (949)     284 / 284            520 / 529
+//                                          128     271 / 280   (1675)     335 / 364            649 / 739
 // and calls that set out together and are waited for together (four of 500: 805):
 //     300 to 500 pixels, scan group 10   n 512    5674 / 4132  (943)     8780 / 7165         14515 / 14170
 //                                          640    5798 / 4238  (1180)    9123 / 8337
 //     256 x 256, 10                        500    1673 / 1255  (874)     2721 / 2387          4696 / 4626
 //     192 x 192, 4:4:4, 6                  700     825 / 729   (1127)    1369 / 1346          2388 / 2597; of 500 2035 / 2000
 //     128 x 128, gray, 6                   550     493 / 394   (954)      797 / 729           1356 / 1345
+//   entry points, level by level, two launches a call (the larger full)
+//     17 to 320 pixels, every 64, 10        64     246 / 231   (949)      343 / 329            541 / 539
+//     429 x 559, gray, every 32, 6           4     140 / 134   (889)      191 / 184            289 / 288
+//                                            6     142 / 140              198 / 200            308 / 322
+//     300 x 300, 4:4:4, every 128, 8        20     214 / 205              301 / 285            481 / 462
 // (With lines of 950 for two and three and 700 from four on three records of 512 photographs, decoded one after another, took 5241 instead of 4155.)
 struct TrioLaunch {
-    uint64_t work = 0, beside = 0; uint32_t longest = 0, groups = 0;       // groups: workgroups of the launch
+    uint64_t work = 0, beside = 0; uint32_t longest = 0, groups = 0; bool chains = false;      // groups: workgroups of the launch; chains: each of a chain of scans, not of a unit
     void add(const LanesLaunch& l) {
         work += l.bits + 14 * l.blocks;
         longest = std::max(longest, l.longest_bits + 14 * l.longest_blocks);
@@ -313,7 +318,7 @@ struct TrioLaunch {
     void add_beside(const LanesLaunch& l) { beside += l.bits + 14 * l.blocks; }
     bool pays(int open_records) const {
         const uint64_t line = open_records <= 1 ? 1500 : (open_records <= 3 ? 1050 : 950);
-        return longest > 0 && work + beside / 2 + 500ull * groups <= line * (longest + 70);
+        return longest > 0 && work + beside / 2 + (chains ? 500ull : 100ull) * groups <= line * (longest + 70);
     }
 };
 

@@ -928,7 +928,7 @@ int run_entropy_stages(pcr_record* r, int k0, int k, hipStream_t s, bool refine_
     // Whether the refinement scans of a level, or of all levels in one launch (beside the AC first scans), get three wavefronts a unit.
     auto trios = [&](const LevelList* one, uint32_t groups) {
         TrioLaunch t;
-        t.groups = groups;
+        t.groups = groups; t.chains = !one;
         for (const LevelList& l : plan->levels) {
             if (l.kind == kAcRefine && (!one || one == &l)) t.add(l.lanes);
             if (l.kind == kAcFirst && !one) t.add_beside(l.lanes);

@@ -95,10 +95,10 @@ extern "C" int lanes_launch_of(const uint8_t* rec, size_t nbytes, uint32_t k, ui
     out[0] = L.by_lanes(level > 0, several != 0); out[1] = L.many(several != 0); out[2] = L.units; out[3] = L.longest_blocks;
     return rc;
 }
-// does a launch of refinement scans of so much work, the longest unit of so much, beside so much of first scans, go to three wavefronts a unit?
+// does a launch of refinement scans of so much work, the longest unit of so much, beside so much of first scans (then it is one of chains), go to three wavefronts a unit?
 extern "C" int trio_pays(uint64_t work, uint32_t longest, uint64_t beside, uint32_t groups, int open_records) {
     TrioLaunch t;
-    t.work = work; t.longest = longest; t.beside = beside; t.groups = groups;
+    t.work = work; t.longest = longest; t.beside = beside; t.groups = groups; t.chains = beside > 0;
     return t.pays(open_records);
 }
 extern "C" int dc_launch_of(const uint8_t* rec, size_t nbytes, uint32_t k, uint32_t* out) {
