@@ -272,43 +272,48 @@ struct LanesLaunch {
 //
 // Three take two thirds of the time of one while the launch takes as long as its longest unit, and up to half as much again once the launches
 // of all records in flight fill the chip.  So what decides is `full`: what the launch asks of the chip over its longest unit, in bits, a block counted as
-// 14 and the start of a workgroup as 500 where it is of a chain (it brings tables, and takes the room of the widest one, whatever is in it), as 100 where it is of a unit, first scans
+// 14 and the start of a workgroup as 800 where it is of a chain (it brings tables, and takes the room of the widest one, whatever is in it), as 100 where it is of a unit, first scans
 // beside the refinement scans by half of theirs (they keep one wavefront).  Where the line lies depends on the records decoded at a time, of which
 // the records the process has open are all that is known: a program may keep several open and decode them one after another, each when the
 // last one is done.  Three wavefronts gain most there, so the lines for several are no lower than that what is lost where all are in flight
 // stays within 4 %.  us a call by one wavefront a unit / by three (n pictures a record; full), calls of all records issued without waiting for any:
 //                                                  one record              two                    four
 //   plain records (all scans side by side)
-//     300 to 500 pixels, scan group 10   n 400    5716 / 4123  (701)     7412 / 5881         14404 / 12175
-//                                          512    5860 / 4256  (899)     7703 / 6954         14917 / 14470
-//                                          640    6038 / 4394  (1121)    8332 / 8474         15914 / 16912
-//                                          800    6223 / 4906  (1399)    9053 / 10544
-//                                         1024    6456 / 6344  (1793)   10218 / 13394
-//     96 x 96, 4:4:4, scan group 6         700     304 / 285   (1183)     591 / 553            825 / 899
-//                                         1200     349 / 396   (2007)     543 / 687           1116 / 1420
-//     192 x 192, 4:4:4, 6                  700     897 / 798   (1067)    1377 / 1430          2071 / 2709
-//     128 x 128, gray, 6                   550     496 / 400   (1099)     726 / 742           1431 / 1468
-//                                          900     571 / 650   (1783)     919 / 1095          1562 / 1981
-//     64 x 64, 10                          400     213 / 188   (917)      265 / 274            525 / 544
-//     24 x 24, 8                           250     115 / 112   (995)      130 / 132            253 / 265
-//                                          900     121 / 137   (3362)     161 / 192            324 / 389
-//   a marker every MCU row, 256 x 256, 10   16     160 / 150   (1066)     187 / 206            334 / 373
-//                                           32     170 / 208   (2215)     232 / 312            444 / 617
+//     300 to 500 pixels, scan group 10   n 400    5716 / 4123  (702)     7412 / 5881         14404 / 12175
+//                                          512    5860 / 4256  (900)     7703 / 6954         14917 / 14470
+//                                          640    6038 / 4394  (1123)    8332 / 8474         15914 / 16912
+//                                          800    6223 / 4906  (1402)    9053 / 10544
+//                                         1024    6456 / 6344  (1796)   10218 / 13394
+//     96 x 96, 4:4:4, scan group 6         700     304 / 285   (1256)     591 / 553            825 / 899
+//                                         1200     349 / 396   (2132)     543 / 687           1116 / 1420
+//     192 x 192, 4:4:4, 6                  700     897 / 798   (1085)    1377 / 1430          2071 / 2709
+//     128 x 128, gray, 6                   550     496 / 400   (1111)     726 / 742           1431 / 1468
+//                                          900     571 / 650   (1803)     919 / 1095          1562 / 1981
+//     64 x 64, 10                          400     213 / 188   (988)      265 / 274            525 / 544
+//     24 x 24, 8                           250     115 / 112   (1357)      130 / 132            253 / 265
+//                                          900     121 / 137   (4666)     161 / 192            324 / 389
+//   a marker every MCU row, 256 x 256, 10   16     160 / 150   (1179)     187 / 206            334 / 373
+//                                           32     170 / 208   (2442)     232 / 312            444 / 617
 //   entry points every 64 MCUs (level by level)
 //     17 to 320 pixels, 10                  64     243 / 228    (949)     284 / 284            520 / 529
 //                                          128     271 / 280   (1675)     335 / 364            649 / 739
-// and calls that set out together and are waited for together (four of 500: 805):
-//     300 to 500 pixels, scan group 10   n 512    5674 / 4132  (943)     8780 / 7165         14515 / 14170
-//                                          640    5798 / 4238  (1180)    9123 / 8337
-//     256 x 256, 10                        500    1673 / 1255  (874)     2721 / 2387          4696 / 4626
-//     192 x 192, 4:4:4, 6                  700     825 / 729   (1127)    1369 / 1346          2388 / 2597; of 500 2035 / 2000
-//     128 x 128, gray, 6                   550     493 / 394   (954)      797 / 729           1356 / 1345
+// and calls that set out together and are waited for together:
+//     300 to 500 pixels, scan group 10   n 512    5674 / 4132   (945)     8780 / 7165         14515 / 14170
+//                                          600    5880 / 4282  (1090)     9000 / 7853         15355 / 16027
+//                                          640    5911 / 4329  (1182)     9122 / 8320         15787 / 16927
+//                                          720    5984 / 4538  (1290)     9453 / 9360
+//     256 x 256, 10                        500    1673 / 1255   (882)     2721 / 2387          4696 / 4626
+//                                          600    1720 / 1378  (1055)     2906 / 2752          5029 / 5387
+//     192 x 192, 4:4:4, 6                  700     825 / 727   (1145)     1369 / 1344          2386 / 2596; of 500 (818) 2035 / 2000
+//     128 x 128, gray, 6                   550     493 / 395    (966)      797 / 728           1354 / 1347
+//     64 x 64, 10                          500     211 / 191                314 / 318            546 / 586
+//   a marker every MCU row, 256 x 256, 10   16     159 / 153                225 / 234            364 / 394
 //   entry points, level by level, two launches a call (the larger full)
 //     17 to 320 pixels, every 64, 10        64     246 / 231   (949)      343 / 329            541 / 539
 //     429 x 559, gray, every 32, 6           4     140 / 134   (889)      191 / 184            289 / 288
 //                                            6     142 / 140              198 / 200            308 / 322
 //     300 x 300, 4:4:4, every 128, 8        20     214 / 205              301 / 285            481 / 462
-// (With lines of 950 for two and three and 700 from four on three records of 512 photographs, decoded one after another, took 5241 instead of 4155.)
+// (With lines of 950 for two and three records, 700 from four on and 500 a workgroup three records of 512 photographs, decoded one after another, took 5241 instead of 4155.)
 struct TrioLaunch {
     uint64_t work = 0, beside = 0; uint32_t longest = 0, groups = 0; bool chains = false;      // groups: workgroups of the launch; chains: each of a chain of scans, not of a unit
     void add(const LanesLaunch& l) {
@@ -317,8 +322,8 @@ struct TrioLaunch {
     }
     void add_beside(const LanesLaunch& l) { beside += l.bits + 14 * l.blocks; }
     bool pays(int open_records) const {
-        const uint64_t line = open_records <= 1 ? 1500 : (open_records <= 3 ? 1050 : 950);
-        return longest > 0 && work + beside / 2 + (chains ? 500ull : 100ull) * groups <= line * (longest + 70);
+        const uint64_t line = open_records <= 1 ? 1500 : (open_records <= 3 ? 1170 : 1025);
+        return longest > 0 && work + beside / 2 + (chains ? 800ull : 100ull) * groups <= line * (longest + 70);
     }
 };
 
