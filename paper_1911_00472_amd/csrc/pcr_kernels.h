@@ -2077,8 +2077,7 @@ PCR_D void store_head(uint8_t* p, uint32_t w0, uint32_t w1, uint32_t w2, uint32_
     else if (n - done == 1) p[done] = (uint8_t)w;
 }
 
-// past: pixels stored past the caches (pixels_past).  The choice is made at every store: with two kernels instead the compiler lays out the branches around
-// the stores of partial rows otherwise, and 2048 pictures of 80 x 49 took 22.9 us here instead of 21.7, with refinement 29.6 instead of 27.9.
+// past: pixels stored past the caches (pixels_past).  The choice is made at every store; as a kernel of its own for them it takes the same time.
 //
 // 120 registers at most, and not the 128 that four wavefronts per SIMD could have: with four of them a SIMD has 32 left for a wavefront of another launch.  At
 // 121 (with the two stores of twelve bytes below the other way round) k_bind_fill of a loader's next slot took 119 us beside this kernel instead of 19, and
@@ -2406,9 +2405,7 @@ PCR_HD bool flat_rows_fit(uint32_t W) { return ((W + 7) >> 3) <= (uint32_t)kFlat
 // LDS bytes a launch needs for images of at most `cells` cells per row: 24 bytes per cell, the repeated 32 bytes, slack
 PCR_HD uint32_t flat_rows_lds(uint32_t cells) { return cells * 24 + 64; }
 
-// kPast: the chunks go past the caches (rows_past).
-template <bool kPast>
-__global__ void __launch_bounds__(kFlatRowLanes) k_pixel_flat_rows(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out, uint32_t max_cells) {
+__global__ void __launch_bounds__(kFlatRowLanes) k_pixel_flat_rows(DevRecord R, const PixelTile* __restrict__ tiles, uint8_t* __restrict__ out, uint32_t max_cells, uint32_t past) {
     // the pixel row: 24 bytes per cell (8 for a gray image), then its first 32 bytes again so that a chunk may run past its end
     extern __shared__ __attribute__((aligned(16))) uint32_t pat[];
     short_kernel_priority();
@@ -2461,7 +2458,7 @@ __global__ void __launch_bounds__(kFlatRowLanes) k_pixel_flat_rows(DevRecord R, 
         v.x = __builtin_amdgcn_alignbyte(b, a, sh); v.y = __builtin_amdgcn_alignbyte(c, b, sh);
         v.z = __builtin_amdgcn_alignbyte(d, c, sh); v.w = __builtin_amdgcn_alignbyte(e, d, sh);
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        if (kPast) put_past<uint4>(band + p, w); else *reinterpret_cast<uint4*>(band + p) = v;
+        if (past) put_past<uint4>(band + p, w); else *reinterpret_cast<uint4*>(band + p) = v;
     }
     if (tid < head) band[tid] = pb[tid];                    // (head < 16 <= the repeated part)
     if (tid < len - tail0) band[tail0 + tid] = pb[in_row(tail0 + tid)];

@@ -744,11 +744,11 @@ bool dc_lanes_pay(const pcr_record* r, const LevelList& l, bool beside) {
 // The chip's memory-side cache holds 256 MB.  Planes of a record that fit in it are still there when the pixel kernel reads them, but pixels that
 // do not fit beside them push them out as they are written.  Where both fit, or the planes alone do not, or other records' planes and pixels pass through
 // the cache meanwhile, nothing is gained, and who reads the pixels next finds them in memory only.  So: a record whose planes fit
-// and whose pixels do not fit beside them, with no more than three records open (as by split_pays; of two or three that are decoded at the same time
+// and whose pixels do not fit beside them, with no more than three records open (as by SplitLaunch; of two or three that are decoded at the same time
 // some lose), without refinement (which reads masks and records beside the planes), and whole pictures (pixels of boxes are for the training tail, at
 // once).  Time past the cache over the time through it: the call alone / with a conversion of all pixels to half precision behind it / with their maximum
 //   MB of planes + pixels; in flight    1                         2                         4                         8
-//     24 + 24                        0.98 / 1.11 / 1.00
+//     24 + 24                        0.98 / 1.11 / 1.00       (31 + 24, 80 x 49: 0.92 the kernel, 0.97 the call)
 //     96 + 96                        0.99 / 1.16 / 1.05
 //    120 + 120                       0.98 / 1.02 / 1.02        0.94 / 0.98 / 0.98        1.00 / 1.00 / 1.01        1.00 / 1.00 / 1.01
 //    150 + 150                       0.94 / 0.99 / 0.94        0.99 / 1.00 / 1.02        1.01 / 1.00 / 1.00        1.01 / 1.00 / 1.01
@@ -770,7 +770,7 @@ bool pixels_past(const pcr_record* r, const Plan* plan, bool boxes) {
     return planes <= 256 * kMB && planes + pixels > 280 * kMB && plan->has_ac && !plan->n_apply && !boxes && g_open_records.load(std::memory_order_relaxed) <= 3;
 }
 // Whether the pixel rows of a DC-only decode (k_pixel_flat_rows), and the zero fill of the coefficient planes, go past it as well: where they do not fit in it
-// by themselves and several records' launches have to share it, which four open records are taken as the sign of (as by split_pays).  Zeros that
+// by themselves and several records' launches have to share it, which four open records are taken as the sign of (as by SplitLaunch).  Zeros that
 // do fit in part are still there when the first scans are stored into them, so the fill's line lies higher.  Time past the cache over the time through it;
 // in flight: four records at a time / one, three others open and idle (MB of pixels, or of planes)
 //   pixel rows   98 0.95 / 0.98   196 0.85 / 0.97   262 0.81 / 0.94 (a conversion to half precision behind it: 0.98 / 1.02)   384 0.77 / 0.87 (0.97 / 0.99)
@@ -1783,7 +1783,7 @@ static int decode_to_pixels(pcr_record* r, int k0, int k, uint8_t* out, size_t c
     else if (plan->has_ac || smooth)
         hipLaunchKernelGGL((k_pixel<false, false>), dim3(r->n_tiles), dim3(kPixLanes), 0, s, d, r->d_tiles, out, (const ApplyList*)nullptr, (const int32_t*)nullptr, boxes, r->last_past ? 1u : 0u);
     else if (by_rows)
-        hipLaunchKernelGGL((r->last_past ? k_pixel_flat_rows<true> : k_pixel_flat_rows<false>), dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells);
+        hipLaunchKernelGGL(k_pixel_flat_rows, dim3(r->n_flat_rows), dim3(kFlatRowLanes), flat_rows_lds(r->flat_row_cells), s, d, r->d_flat_rows, out, r->flat_row_cells, r->last_past ? 1u : 0u);
     else
         hipLaunchKernelGGL(k_pixel_flat, dim3(r->n_flat_tiles), dim3(kFlatLanes), 0, s, d, r->d_flat_tiles, out, boxes);
     if (smooth) hipLaunchKernelGGL(k_smooth<true>, dim3(kSmoothGroups, r->hdr.n), dim3(256), 0, s, r->d);
