@@ -2077,7 +2077,8 @@ PCR_D void store_head(uint8_t* p, uint32_t w0, uint32_t w1, uint32_t w2, uint32_
     else if (n - done == 1) p[done] = (uint8_t)w;
 }
 
-// past: pixels stored past the caches (pixels_past).  The choice is made at every store; as a kernel of its own for them it takes the same time.
+// past: pixels stored past the caches (pixels_past).  The choice is made at every store; as a kernel of its own for them it takes the same time (0.3 % less for
+// two records of 128 pictures of 1024 x 1024).
 //
 // 120 registers at most, and not the 128 that four wavefronts per SIMD could have: with four of them a SIMD has 32 left for a wavefront of another launch.  At
 // 121 (with the two stores of twelve bytes below the other way round) k_bind_fill of a loader's next slot took 119 us beside this kernel instead of 19, and
